@@ -692,14 +692,13 @@ int merge_group_sets(int64_t n_max) {
     g = std::max<int64_t>(1, std::min<int64_t>(g, SEG_TABLE_MAX));
     return (int)g;
 }
-struct MergeWs { size_t xn, sim, slot, kept, total; };
+struct MergeWs { size_t xn, sim, slot, total; };
 MergeWs merge_ws(int64_t n_tok, int64_t n_max, int64_t C) {
     MergeWs W; size_t o = 0;
     const size_t ld = (size_t)(n_max + 7) / 8 * 8;
     W.xn = o;   o += align_up((size_t)n_tok * C * 2);
     W.sim = o;  o += align_up((size_t)merge_group_sets(n_max) * n_max * ld * 4);
     W.slot = o; o += align_up((size_t)n_tok * 4);
-    W.kept = o; o += align_up((size_t)n_tok);
     W.total = o;
     return W;
 }
@@ -736,7 +735,6 @@ int skipffn_token_merge(const void* x, const int32_t* seg_host, int64_t S, int64
     bf16_t* xn = reinterpret_cast<bf16_t*>(ws + W.xn);
     float* sim = reinterpret_cast<float*>(ws + W.sim);
     int32_t* slot_of = reinterpret_cast<int32_t*>(ws + W.slot);
-    uint8_t* kept = reinterpret_cast<uint8_t*>(ws + W.kept);
     const bf16_t* xb = static_cast<const bf16_t*>(x);
     const int ld = (int)((n_max + 7) / 8 * 8);
     const int64_t sim_stride = n_max * ld;
@@ -753,7 +751,7 @@ int skipffn_token_merge(const void* x, const int32_t* seg_host, int64_t S, int64
         // S_i = Xn_i Xn_i^T  [n_i, n_i] fp32 on the MFMA core, every set of the group in one grid
         e = launch_gemm_selfsim(xn, (int)C, st, gmax, sim, ld, sim_stride, s);
         if (e != hipSuccess) break;
-        e = launch_merge_group(xb, st, gmax, (int)C, (int)k, (int)g0, sim, ld, sim_stride, avg_sim, kept,
+        e = launch_merge_group(xb, st, gmax, (int)C, (int)k, (int)g0, sim, ld, sim_stride, avg_sim,
                                slot_of, kept_idx, assign, static_cast<bf16_t*>(out), s);
     }
     profile_mark_end(KC_MERGE, s);

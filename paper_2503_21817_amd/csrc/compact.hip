@@ -30,10 +30,6 @@ __device__ __forceinline__ uint32_t load_mask4(const uint8_t* mask, int64_t tok,
     return w;
 }
 
-__device__ __forceinline__ int lanes_below(uint64_t m) {
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
-}
-
 // A wave walks its range 1024 tokens at a time: the four 4-byte mask loads of a lane are issued
 // together (the walk is bound by load latency, not by the ballots), then the four 256-token
 // slabs are ranked one after the other.

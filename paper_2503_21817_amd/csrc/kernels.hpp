@@ -114,7 +114,7 @@ hipError_t launch_row_normalize(const bf16_t* x, int64_t rows, int C, bf16_t* xn
 hipError_t launch_gemm_selfsim(const bf16_t* xn, int C, const SegTable& st, int n_max, float* sim, int ld,
                                int64_t sim_stride, hipStream_t s);
 hipError_t launch_merge_group(const bf16_t* x, const SegTable& st, int n_max, int C, int k, int set_base,
-                              const float* sim, int ld, int64_t sim_stride, float* avg, uint8_t* kept,
+                              const float* sim, int ld, int64_t sim_stride, float* avg,
                               int32_t* slot_of, int32_t* kept_idx, int32_t* assign, bf16_t* out,
                               hipStream_t s);
 hipError_t launch_merge_bwd_group(const bf16_t* dout, const SegTable& st, int n_max, int C, int k, int set_base,

@@ -13,6 +13,7 @@
 // a token whose similarities are all NaN goes to no slot (assign = -1) and gets a zero gradient.
 #include "kernels.hpp"
 #include "segments.hpp"
+#include "topk.hpp"
 
 namespace skipffn {
 
@@ -64,51 +65,49 @@ __global__ __launch_bounds__(MG_THREADS) void sim_rowmean_kernel(const float* __
     if (lane == 0) avg[lo + i] = n > 1 ? acc / (float)(n - 1) : 0.0f;
 }
 
-// ---- kept[t] = 1 iff fewer than k tokens of the set have a lower average -----------------------
-__global__ __launch_bounds__(MG_THREADS) void merge_rank_kernel(const float* __restrict__ avg, SegTable st,
-                                                                int k, uint8_t* __restrict__ kept) {
-    __shared__ __align__(16) uint32_t sav[MERGE_MAX_N];       // rank keys of the averages
-    const int set = blockIdx.y;
+// ---- which tokens are kept, and their slots ------------------------------------------------------
+// One workgroup per set: the k tokens of lowest average (topk.hpp), then the position of every kept
+// token among the kept ones, in index order.  slot_of[t] = slot or -1; kept_idx[set][slot] = lo + t, -1
+// padding.
+constexpr int MG_MAXV = MERGE_MAX_N / TOPK_THREADS;
+__global__ __launch_bounds__(TOPK_THREADS) void merge_select_kernel(const float* __restrict__ avg, SegTable st,
+                                                                    int k, int set_base,
+                                                                    int32_t* __restrict__ slot_of,
+                                                                    int32_t* __restrict__ kept_idx) {
+    __shared__ TopkShared sh;
+    const int set = blockIdx.x, tid = threadIdx.x;
     const int lo = st.off[set], n = st.off[set + 1] - lo;
-    if ((int)blockIdx.x * MG_THREADS >= n) return;          // uniform over the workgroup
-    for (int u = threadIdx.x; u < n; u += MG_THREADS) sav[u] = rank_key<false>(avg[lo + u]);
-    __syncthreads();
-    const int t = blockIdx.x * MG_THREADS + threadIdx.x;
-    if (t >= n) return;
-    const int lower = rank_in_lds(sav, n, t);
-    kept[lo + t] = lower < k ? 1 : 0;
-}
-
-// ---- slots: position of every kept token among the kept tokens, in index order ----------------
-// one workgroup per set; slot_of[t] = slot or -1; kept_idx[set][slot] = lo + t, -1 padding
-__global__ __launch_bounds__(MG_THREADS) void merge_slot_kernel(const uint8_t* __restrict__ kept, SegTable st,
-                                                                int k, int set_base,
-                                                                int32_t* __restrict__ slot_of,
-                                                                int32_t* __restrict__ kept_idx) {
-    __shared__ int cnt[MG_THREADS];
-    const int set = blockIdx.x;
-    const int lo = st.off[set], n = st.off[set + 1] - lo;
-    const int tid = threadIdx.x;
-    const int per = (n + MG_THREADS - 1) / MG_THREADS;       // consecutive tokens per thread
-    const int b = tid * per, e = b + per < n ? b + per : n;
-    int c = 0;
-    for (int t = b; t < e; ++t) c += kept[lo + t];
-    cnt[tid] = c;
-    __syncthreads();
-    int slot = 0;
-    for (int u = 0; u < tid; ++u) slot += cnt[u];
     int32_t* kout = kept_idx + (int64_t)(set_base + set) * k;
-    for (int t = b; t < e; ++t) {
-        if (kept[lo + t] && slot < k) {      // the rank order is total, so slot < k always holds: belt and braces
-            slot_of[lo + t] = slot;
-            kout[slot] = lo + t;
-            ++slot;
-        } else {
-            slot_of[lo + t] = -1;
-        }
+    for (int s = (k < n ? k : n) + tid; s < k; s += TOPK_THREADS) kout[s] = -1;
+    if (n <= 0) return;
+    const int nv = (n + TOPK_THREADS - 1) / TOPK_THREADS;
+    uint32_t key[MG_MAXV];
+    int before[MG_MAXV];
+    bool in[MG_MAXV];
+#pragma unroll
+    for (int i = 0; i < MG_MAXV; ++i) {
+        const int t = i * TOPK_THREADS + tid;
+        key[i] = t < n ? rank_key<false>(avg[lo + t]) : TOPK_NONE;
+        before[i] = 0;
+        in[i] = k >= n && t < n;
     }
-    const int kk = k < n ? k : n;
-    for (int sidx = kk + tid; sidx < k; sidx += MG_THREADS) kout[sidx] = -1;
+    if (k > 0 && k < n) {                        // uniform
+        const TopkCut cut = topk_cut<MG_MAXV>([&](int i) { return key[i]; }, nv, k, sh);
+        if (cut.ties > 0)
+            topk_prefix<MG_MAXV>([&](int i) { return key[i] == cut.cut && i * TOPK_THREADS + tid < n; }, nv, sh, before);
+#pragma unroll
+        for (int i = 0; i < MG_MAXV; ++i)
+            in[i] = i * TOPK_THREADS + tid < n && (key[i] < cut.cut || (key[i] == cut.cut && before[i] < cut.ties));
+    }
+    topk_prefix<MG_MAXV>([&](int i) { return in[i]; }, nv, sh, before);
+#pragma unroll
+    for (int i = 0; i < MG_MAXV; ++i) {
+        const int t = i * TOPK_THREADS + tid;
+        if (t >= n) continue;
+        // exactly min(k, n) tokens are in, so a slot is below k
+        slot_of[lo + t] = in[i] ? before[i] : -1;
+        if (in[i]) kout[before[i]] = lo + t;
+    }
 }
 
 // ---- destination of every token: own slot if kept, else the most similar kept token ----------
@@ -255,7 +254,7 @@ hipError_t launch_row_normalize(const bf16_t* x, int64_t rows, int C, bf16_t* xn
 
 // steps after the similarity GEMMs for the sets of one table (set_base = index of its first set)
 hipError_t launch_merge_group(const bf16_t* x, const SegTable& st, int n_max, int C, int k, int set_base,
-                              const float* sim, int ld, int64_t sim_stride, float* avg, uint8_t* kept,
+                              const float* sim, int ld, int64_t sim_stride, float* avg,
                               int32_t* slot_of, int32_t* kept_idx, int32_t* assign, bf16_t* out,
                               hipStream_t s) {
     hipError_t e = hipSuccess;
@@ -265,11 +264,8 @@ hipError_t launch_merge_group(const bf16_t* x, const SegTable& st, int n_max, in
         hipLaunchKernelGGL(sim_rowmean_kernel, dim3((unsigned)((n_max + 3) / 4), sets), dim3(MG_THREADS), 0, s,
                            sim, st, ld, sim_stride, avg);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(merge_rank_kernel, dim3((unsigned)((n_max + MG_THREADS - 1) / MG_THREADS), sets),
-                           dim3(MG_THREADS), 0, s, avg, st, k, kept);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(merge_slot_kernel, dim3(sets), dim3(MG_THREADS), 0, s, kept, st, k, set_base, slot_of,
+    hipLaunchKernelGGL(merge_select_kernel, dim3(sets), dim3(TOPK_THREADS), 0, s, avg, st, k, set_base, slot_of,
                        kept_idx);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (n_max > 0) {

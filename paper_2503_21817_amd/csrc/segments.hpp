@@ -15,34 +15,44 @@ __device__ __forceinline__ void seg_bounds(const int32_t* __restrict__ seg, int 
     b = seg[i];
     b = b < 0 ? 0 : (b > e ? e : b);
 }
-// chunk q -> (set s, first position t0, count nt); false past the last chunk
+// chunk q -> (set s, first position t0, count nt); false past the last chunk.  Called by whole
+// wavefronts: a lane takes a set, a prefix sum over the lanes finds the chunk's set.  (A scalar walk over the
+// sets costs a load's latency per few sets before a workgroup knows its rows: the reducing kernels of the
+// summary layer 13.4 -> 11.7 and 7.3 -> 5.9 us at 32 sets.)
 template <int CH>
 __device__ __forceinline__ bool locate_chunk(const int32_t* __restrict__ seg, int S, int n_tok, int q,
                                              int& s, int& t0, int& nt) {
+    const int lane = threadIdx.x & 63;
     int cc = 0;
-    for (int i = 0; i < S; ++i) {
-        int b, e;
-        seg_bounds(seg, i, n_tok, b, e);
+    for (int i0 = 0; i0 < S; i0 += 64) {
+        int b = 0, e = 0;
+        if (i0 + lane < S) seg_bounds(seg, i0 + lane, n_tok, b, e);
         const int nc = (e - b + CH - 1) / CH;
-        if (q < cc + nc) {
-            s = i;
-            t0 = b + (q - cc) * CH;
+        const int incl = wave_inclusive_sum(nc);
+        const uint64_t past = __ballot(q < cc + incl);
+        if (past != 0) {
+            const int l = __builtin_ctzll(past);
+            b = __builtin_amdgcn_readlane(b, l);
+            e = __builtin_amdgcn_readlane(e, l);
+            s = i0 + l;
+            t0 = b + (q - cc - __builtin_amdgcn_readlane(incl - nc, l)) * CH;
             nt = e - t0 < CH ? e - t0 : CH;
             return true;
         }
-        cc += nc;
+        cc += __builtin_amdgcn_readlane(incl, 63);
     }
     return false;
 }
-// chunks [q0, q1) of set s, clamped to the nq_max chunks the launch covers
+// chunks [q0, q1) of set s, clamped to the nq_max chunks the launch covers (called by whole wavefronts)
 template <int CH>
 __device__ __forceinline__ void chunk_range(const int32_t* __restrict__ seg, int s, int n_tok, int nq_max,
                                             int& q0, int& q1) {
+    const int lane = threadIdx.x & 63;
     int cc = 0;
-    for (int i = 0; i < s; ++i) {
-        int b, e;
-        seg_bounds(seg, i, n_tok, b, e);
-        cc += (e - b + CH - 1) / CH;
+    for (int i0 = 0; i0 < s; i0 += 64) {
+        int b = 0, e = 0;
+        if (i0 + lane < s) seg_bounds(seg, i0 + lane, n_tok, b, e);
+        cc += __builtin_amdgcn_readlane(wave_inclusive_sum((e - b + CH - 1) / CH), 63);
     }
     int b, e;
     seg_bounds(seg, s, n_tok, b, e);
@@ -59,13 +69,10 @@ __device__ __forceinline__ void unpack8s(const u32x4& v, float* f) {
     }
 }
 
-// The order of the rank counts: "DESCENDING ? larger first : smaller first", equal values (+0 and
+// The order of the selections: "DESCENDING ? larger first : smaller first", equal values (+0 and
 // -0 are equal) ordered by index.  The order is total: a NaN comes after every number (NaNs among
 // themselves by index), so exactly min(k, n) entries have rank < k whatever the values are.
-// rank_key maps a value to an unsigned key that increases along that order, so that "entry (v, u)
-// comes before entry (vt, t)" is one 64-bit comparison of (key, index) pairs: the rank loops do a
-// compare and an add per entry instead of the five float comparisons of the direct form (which
-// took the rank kernels from 28 to 82 us at 1024-token sets).
+// rank_key maps a value to an unsigned key that increases along that order (equal values share a key).
 template <bool DESCENDING>
 __device__ __forceinline__ uint32_t rank_key(float v) {
     if (v != v) return 0xFFFFFFFFu;
@@ -75,17 +82,6 @@ __device__ __forceinline__ uint32_t rank_key(float v) {
     // complement of that range, so 0xFFFFFFFF is left to the NaNs in both orders
     const uint32_t asc = (b & 0x80000000u) ? ~b : (b | 0x80000000u);
     return DESCENDING ? ~asc : asc;
-}
-__device__ __forceinline__ uint64_t rank_pair(uint32_t key, int index) {
-    return ((uint64_t)key << 32) | (uint32_t)index;
-}
-// Number of entries u of keys[0..n) (an LDS array of rank_key values) that come before entry t.
-// (One value per LDS read: a four-wide version was measured twice as slow.)
-__device__ __forceinline__ int rank_in_lds(const uint32_t* keys, int n, int t) {
-    const uint64_t mine = rank_pair(keys[t], t);
-    int before = 0;
-    for (int u = 0; u < n; ++u) before += rank_pair(keys[u], u) < mine ? 1 : 0;
-    return before;
 }
 
 __device__ __forceinline__ float block_sum256(float v, float* red) {

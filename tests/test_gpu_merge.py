@@ -199,3 +199,19 @@ def test_non_finite_tokens_keep_exactly_k_and_stay_inside_the_outputs():
         assert np.array_equal(kept_h[s, :kk], want)
         assert np.all((assign_h[lo:hi] >= -1) & (assign_h[lo:hi] < kk))
         assert np.array_equal(assign_h[kept_h[s, :kk]], np.arange(kk))
+
+
+@pytest.mark.parametrize("n", [63, 1024, 1025, 2047])
+@pytest.mark.parametrize("distinct", [4, 10**9], ids=["repeated-rows", "random-rows"])
+def test_kept_set_edges(n, distinct):
+    """Set sizes around the steps of the cut search; with four different rows the cut falls inside a
+    run of equal averages, which go by index."""
+    print(f"kept set n={n} distinct={distinct}", flush=True)
+    rng = np.random.default_rng(n)
+    rows = rng.standard_normal((min(n, distinct), 64))
+    xb = O.f64_to_bf16_bits(rows[rng.integers(0, len(rows), n)] if distinct < n else rows)
+    for k in (1, n // 3, n - 1, n):
+        _, kept, assign, avg = run_gpu(xb, [0, n], k)
+        want = np.sort(np.argsort(avg, kind="stable")[:k])
+        assert np.array_equal(kept[0], want)
+        assert np.array_equal(assign[want], np.arange(k))

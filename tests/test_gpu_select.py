@@ -113,3 +113,21 @@ def test_non_finite_features_still_retain_exactly_n():
             lo, hi = off[b], off[b + 1]
             assert int((mask[lo:hi] == 0).sum()) == min(keep, hi - lo)
             assert np.array_equal(mask[lo:hi], O.select_top_n(sim[lo:hi], keep))
+
+
+@pytest.mark.parametrize("lens", [(1, 63, 64, 65), (1023, 1024, 1025), (16384,), (16385,), (3,) * 130],
+                         ids=["one-wave-edges", "one-step-edges", "last-in-registers", "first-from-memory", "many-sets"])
+@pytest.mark.parametrize("distinct", [3, 10**9], ids=["repeated-rows", "random-rows"])
+def test_cut_search_edges(lens, distinct):
+    """Lengths around the steps of the cut search, with similarities that all differ and with only
+    three different ones (the cut then falls inside a run of equal values, told apart by index)."""
+    print(f"cut search lens={lens[:4]} distinct={distinct}", flush=True)
+    rng = np.random.default_rng(len(lens) + lens[0])
+    n, Cv = sum(lens), 8
+    rows = rng.standard_normal((min(n, distinct), Cv))
+    feat = O.f64_to_bf16_bits(rows[rng.integers(0, len(rows), n)] if distinct < n else rows)
+    cls = O.f64_to_bf16_bits(rng.standard_normal((len(lens), Cv)))
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    for share in (0.0, 0.25, 0.5, 1.0):
+        keep = [min(m, int(m * share) + (1 if 0 < share < 1 else 0)) for m in lens]
+        check(feat, cls, off, keep)
