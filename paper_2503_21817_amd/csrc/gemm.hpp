@@ -76,8 +76,8 @@ struct GemmArgs {
     int accumulate;              // EPI_STORE: 1 = +=
     int no_residual;             // EPI_RESID_SCATTER: 1 = do not add the residual
     int narrow;                  // host side: 1 = launch the 128-row tile variant (tiles_m counts 128-row tiles)
-    int tail_narrow;             // 1 = the rows past tiles_m * 256 (at most 128 of them) form one extra row of
-                                 // 128-row tiles, run by the last tiles_n workgroups of the grid
+    int tail_narrow;             // 1 = a last tile row of at most 128 rows is a row of 128-row tiles, run by
+                                 // the last tiles_n live workgroups of the grid
 };
 
 // Row offsets of up to SEG_TABLE_MAX token sets, passed by value in the kernel arguments
@@ -839,30 +839,38 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
 template <bool A_KC, int EPI>
 constexpr bool kTailNarrowOk = A_KC && EPI == EPI_SWIGLU;
 
-// One workgroup's share of a plain (optionally split-K, optionally batched) GEMM: `block` of
-// `nblocks` in the launch order of this problem.
+// One workgroup's share of a plain (optionally split-K, optionally batched) GEMM: workgroup `block`
+// in the launch order of this problem.  The tile map is laid over the EFFECTIVE rows: with the
+// row count on the device the grid covers the host's bound, and a map over the bound would give
+// the live tile rows - the first ones of each panel - to some XCDs only (640 of 2944 rows: 5.3 of the 8
+// XCDs had work).  Workgroups past the live tiles come last in the launch order and leave at once.
 template <bool A_KC, bool B_KC, int EPI, bool NARROW = false>
-__device__ __forceinline__ void gemm_block(GemmArgs P, const int block, const int nblocks) {
+__device__ __forceinline__ void gemm_block(GemmArgs P, const int block) {
     const int Meff = effective_rows(P.M, P.m_dev);
     const int Keff = effective_rows(P.K, P.k_dev);
+    constexpr int TM = NARROW ? BM / 2 : BM;
     if constexpr (!NARROW && kTailNarrowOk<A_KC, EPI>) {
-        // host contract: tail_narrow comes with splits == 1, batch == 1 and a host-side row count
-        const int full = P.tiles_m * P.tiles_n;
-        if (P.tail_narrow && block >= full) {
+        // host contract: tail_narrow comes with splits == 1 and batch == 1
+        const int rem = Meff % BM;
+        if (P.tail_narrow && rem > 0 && rem <= BM / 2) {
+            const int tiles_m = Meff / BM, full = tiles_m * P.tiles_n;
+            if (block >= full + P.tiles_n) return;
             const int ktotal = ((Keff + BK - 1) / BK) * P.pairs;
-            gemm_tile<A_KC, B_KC, EPI, true>(P, 2 * P.tiles_m, block - full, 0, 0, ktotal, Meff, Keff);
-            return;
-        }
-        if (P.tail_narrow) {
-            int tm, tn, z;
-            tile_of_block(block, full, P.tiles_m, P.tiles_n, tm, tn, z);
-            const int ktotal = ((Keff + BK - 1) / BK) * P.pairs;
-            gemm_tile<A_KC, B_KC, EPI, false>(P, tm, tn, 0, 0, ktotal, Meff, Keff);
+            if (block >= full) {
+                gemm_tile<A_KC, B_KC, EPI, true>(P, 2 * tiles_m, block - full, 0, 0, ktotal, Meff, Keff);
+            } else {
+                int tm, tn, z;
+                tile_of_block(block, full, tiles_m, P.tiles_n, tm, tn, z);
+                gemm_tile<A_KC, B_KC, EPI, false>(P, tm, tn, 0, 0, ktotal, Meff, Keff);
+            }
             return;
         }
     }
+    const int tiles_m = (Meff + TM - 1) / TM;
+    const int nblocks = tiles_m * P.tiles_n * P.splits * P.batch;
+    if (block >= nblocks) return;                        // whole block leaves together: no barrier was reached yet
     int tm, tn, z;
-    tile_of_block(block, nblocks, P.tiles_m, P.tiles_n, tm, tn, z);
+    tile_of_block(block, nblocks, tiles_m, P.tiles_n, tm, tn, z);
     // batched launch (two problems in one grid, used for dW_gate / dW_up): the upper half of
     // the z range is problem 1
     const bool second = P.batch == 2 && z >= P.splits;
@@ -871,7 +879,6 @@ __device__ __forceinline__ void gemm_block(GemmArgs P, const int block, const in
         P.A0 = P.A1;
         P.out0 = P.out1;
     }
-    if (tm * (NARROW ? BM / 2 : BM) >= Meff) return;    // whole block leaves together: no barrier was reached yet
     const int ktotal = ((Keff + BK - 1) / BK) * P.pairs;
     const int per_split = (ktotal + P.splits - 1) / P.splits;
     const int kt_begin = z * per_split;
@@ -882,7 +889,7 @@ __device__ __forceinline__ void gemm_block(GemmArgs P, const int block, const in
 
 template <bool A_KC, bool B_KC, int EPI, bool NARROW = false>
 __global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_kernel(GemmArgs P) {
-    gemm_block<A_KC, B_KC, EPI, NARROW>(P, (int)blockIdx.x, (int)gridDim.x);
+    gemm_block<A_KC, B_KC, EPI, NARROW>(P, (int)blockIdx.x);
 }
 
 // Two independent GEMMs in one grid: workgroups [0, nblocks0) run problem 0 (launched
@@ -892,12 +899,12 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_kernel(GemmArgs P) {
 // XCD assignment from its start.
 template <bool A0_KC, bool B0_KC, int EPI0, bool A1_KC, bool B1_KC, int EPI1>
 __global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_dual_kernel(GemmArgs P0, GemmArgs P1,
-                                                                      int nblocks0, int real0) {
+                                                                      int nblocks0) {
     const int b = (int)blockIdx.x;
     if (b < nblocks0) {
-        if (b < real0) gemm_block<A0_KC, B0_KC, EPI0>(P0, b, real0);
+        gemm_block<A0_KC, B0_KC, EPI0>(P0, b);      // workgroups past its tiles leave
     } else {
-        gemm_block<A1_KC, B1_KC, EPI1>(P1, b - nblocks0, (int)gridDim.x - nblocks0);
+        gemm_block<A1_KC, B1_KC, EPI1>(P1, b - nblocks0);
     }
 }
 

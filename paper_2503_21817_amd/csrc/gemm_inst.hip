@@ -42,17 +42,12 @@ static void finish_args(int epi, GemmArgs& a) {
     a.tiles_n = (epi == EPI_SWIGLU || epi == EPI_PARTIAL_GU) ? (a.N + BN / 2 - 1) / (BN / 2) : (a.N + BN - 1) / BN;
     if (a.splits < 1) a.splits = 1;
     if (a.batch < 1) a.batch = 1;
-    // a last tile row of at most 128 rows runs on 128-row tiles (host-side row count, one
-    // workgroup per tile: the gate/up GEMM)
-    const int rem = a.M % BM;
-    a.tail_narrow = (!a.narrow && epi == EPI_SWIGLU && a.m_dev == nullptr &&
-                     a.splits == 1 && a.batch == 1 && rem > 0 && rem <= BM / 2) ? 1 : 0;
-    if (a.tail_narrow) a.tiles_m = a.M / BM;           // full tile rows only; the tail row is extra
+    // a last tile row of at most 128 rows runs on 128-row tiles (one workgroup per tile: the gate/up GEMM);
+    // the kernel looks at the effective row count
+    a.tail_narrow = (!a.narrow && epi == EPI_SWIGLU && a.splits == 1 && a.batch == 1) ? 1 : 0;
 }
 // workgroups of a one-tile-per-workgroup launch
-static unsigned grid_blocks(const GemmArgs& a) {
-    return (unsigned)(a.tiles_m * a.tiles_n * a.splits * a.batch + (a.tail_narrow ? a.tiles_n : 0));
-}
+static unsigned grid_blocks(const GemmArgs& a) { return (unsigned)(a.tiles_m * a.tiles_n * a.splits * a.batch); }
 
 template <bool A_KC, bool B_KC, int EPI, bool NARROW = false>
 static hipError_t launch_one(const GemmArgs& a, hipStream_t s) {
@@ -71,7 +66,7 @@ hipError_t launch_gemm_dual(int which, GemmArgs& a0, GemmArgs& a1, hipStream_t s
     const int n1 = a1.tiles_m * a1.tiles_n * a1.splits * a1.batch;
     if (real0 <= 0 || n1 <= 0) return hipErrorInvalidValue;
     hipLaunchKernelGGL((gemm_bf16_dual_kernel<true, false, EPI_SWIGLU_BWD, true, true, EPI_STORE>),
-                       dim3((unsigned)(n0 + n1)), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a0, a1, n0, real0);
+                       dim3((unsigned)(n0 + n1)), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a0, a1, n0);
     return hipGetLastError();
 }
 

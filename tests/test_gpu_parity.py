@@ -562,3 +562,23 @@ def test_last_tile_row_of_at_most_128_rows(R):
     assert max_slice_rel_l2(O.bf16_bits_to_f64(gb[idx]), O.bf16_bits_to_f64(bo["dx_bits"][idx]), axis=1) < REL_L2_TOL
     for t, k in zip(dw, ("dw_gate", "dw_up", "dw_down")):
         assert rel_l2(f64_of(t), bo[k]) < REL_L2_TOL, k
+
+
+@pytest.mark.parametrize("R,T", [(1, 2400), (100, 2400), (256, 2400), (257, 2400), (640, 2944), (700, 4400)])
+def test_device_row_count_far_below_the_bound(R, T):
+    """The tile map is laid over the effective rows: the bound has 10 to 18 tile rows (two or three panels),
+    of which one to three are live - with a last row of at most 128 rows, a full one, or one in between."""
+    w = W.small(C=520, I=1368, visual=(T - 1,), text=(1,), keep=(R - 1,), seed=4000 + R)
+    print(f"device count R={R} bound T={T}", flush=True)
+    p = Problem(w, unit_gain=True, with_gain_tensor=False)
+    out, bufs = gpu_forward(p, R_host=False)
+    gx, dw = gpu_backward(p, bufs, R_host=False)
+    fo = O.skipffn_forward(p.hidden, p.mask, p.wg, p.wu, p.wd, None, w.eps)
+    bo = O.skipffn_backward(p.hidden, p.mask, p.wg, p.wu, p.wd, p.grad, None, w.eps)
+    idx = fo["idx"]
+    assert rel_l2(f64_of(out)[idx], O.bf16_bits_to_f64(fo["out_bits"][idx])) < REL_L2_TOL
+    assert rel_l2(f64_of(gx)[idx], O.bf16_bits_to_f64(bo["dx_bits"][idx])) < REL_L2_TOL
+    for a, k in zip(dw, ("dw_gate", "dw_up", "dw_down")):
+        assert rel_l2(f64_of(a), bo[k]) < REL_L2_TOL, k
+    sk = p.mask != 0
+    assert np.array_equal(bits_of(out)[sk], p.hidden[sk])
