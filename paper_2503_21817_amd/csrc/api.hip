@@ -253,7 +253,7 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
     }
 
     hipError_t e;
-    if (out != hidden) {
+    if (out != hidden && R != T) {       // R == T: every row is retained
         e = launch_passthrough(hidden, out, T, C * 2, idx, (int)Rb, r_dev, s);
         if (e != hipSuccess) return hip_fail(e);
     }
@@ -282,14 +282,36 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
     }
     float* partial = reinterpret_cast<float*>(ws + W.partial);
 
+    // a handful of rows: both GEMMs stream the weights once, each in one launch with its epilogue fused.  Without a
+    // saved buffer (whose layout is the caller's to read) the activations lie chunk-major, as they are loaded.
+    const bool few = few_rows(Rb, C, I, saved != nullptr) && !(flags & SKIPFFN_FLAG_BALANCED_SPLIT);
+    const bool chunk_major = few && saved == nullptr;
     // (2) gather + RMSNorm
     e = launch_gather_rmsnorm(static_cast<const bf16_t*>(hidden), idx, (int)Rb, r_dev, (int)C, eps,
-                              static_cast<const bf16_t*>(rms_gain), xrows, xn, rstd, s);
+                              static_cast<const bf16_t*>(rms_gain), xrows, xn, rstd, chunk_major, s);
     if (e != hipSuccess) return hip_fail(e);
     if (xnT != nullptr) {   // K-contiguous copy of the normalised rows for the dW_gate / dW_up GEMMs
         e = launch_gather_transpose(xn, (int)C, nullptr, (int)Rb, r_dev, nullptr, xnT,
                                     (int)ld_transposed(Rb), s);
         if (e != hipSuccess) return hip_fail(e);
+    }
+
+    if (few) {
+        profile_mark_begin(KC_GEMM_GATE_UP, s);
+        e = launch_few_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, static_cast<const bf16_t*>(w_gate),
+                                    static_cast<const bf16_t*>(w_up), H, G, U, chunk_major, s);
+        profile_mark_end(KC_GEMM_GATE_UP, s);
+        if (e != hipSuccess) return hip_fail(e);
+        if (HT != nullptr) {
+            e = launch_gather_transpose(H, (int)I, nullptr, (int)Rb, r_dev, nullptr, HT, (int)ld_transposed(Rb), s);
+            if (e != hipSuccess) return hip_fail(e);
+        }
+        profile_mark_begin(KC_GEMM_DOWN, s);
+        e = launch_few_rows_down(H, (int)Rb, r_dev, (int)C, (int)I, static_cast<const bf16_t*>(w_down), idx,
+                                 static_cast<const bf16_t*>(hidden), static_cast<bf16_t*>(out),
+                                 (flags & SKIPFFN_FLAG_NO_RESIDUAL) ? 1 : 0, chunk_major, s);
+        profile_mark_end(KC_GEMM_DOWN, s);
+        return e == hipSuccess ? SKIPFFN_OK : hip_fail(e);
     }
 
     // (3) gate/up GEMM + SiLU*mul
@@ -397,7 +419,7 @@ int skipffn_backward(int64_t T, int64_t C, int64_t I, float eps, const void* gra
         if (st != SKIPFFN_OK) return st;
     }
     hipError_t e;
-    if (T > 0 && grad_hidden != grad_out) {
+    if (T > 0 && grad_hidden != grad_out && R != T) {
         e = launch_passthrough(grad_out, grad_hidden, T, C * 2, idx, (int)Rb, r_dev, s);
         if (e != hipSuccess) return hip_fail(e);
     }

@@ -49,10 +49,10 @@ hipError_t launch_validate_idx(const int32_t* idx, int R, const int32_t* r_dev, 
                                hipStream_t s);
 
 // ---- row kernels ---------------------------------------------------------------
-// x rows (optional copy), normalised rows and 1/rms for rows idx[0..R)
+// x rows (optional copy), normalised rows and 1/rms for rows idx[0..R); chunk_major: xn is [C / 8][R][8]
 hipError_t launch_gather_rmsnorm(const bf16_t* hidden, const int32_t* idx, int R,
                                  const int32_t* r_dev, int C, float eps, const bf16_t* gain,
-                                 bf16_t* xrows, bf16_t* xn, float* rstd, hipStream_t s);
+                                 bf16_t* xrows, bf16_t* xn, float* rstd, bool chunk_major, hipStream_t s);
 // How many fp32 partial slabs a reducing kernel adds per output element: `splits` for a plain
 // split-K GEMM (sk_nbg == 0), else the per-tile count of the balanced split (streamk_count)
 // with sk_nbg workgroups per n-tile group and sk_kt K slabs per tile.
@@ -124,6 +124,15 @@ hipError_t launch_merge_bwd_group(const bf16_t* dout, const SegTable& st, int n_
 // out: blocks * 256 floats; clocks: 2 * blocks int64 (shader cycles, 100 MHz wall ticks per workgroup)
 hipError_t launch_mfma_probe(int blocks, int iters, int random_operands, float* out, long long* clocks,
                              hipStream_t s);
+
+// ---- the forward GEMMs of a handful of rows (rows <= 64) -----------------------------------------------
+// H = silu(xn Wg^T) * (xn Wu^T); G and U optional.  chunk_major: xn and H are [C / 8][rows][8] instead of row-major
+hipError_t launch_few_rows_gate_up(const bf16_t* xn, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_gate,
+                                   const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major, hipStream_t s);
+// out[idx[r]] = bf16(res[idx[r]] + H[r] Wd^T)
+hipError_t launch_few_rows_down(const bf16_t* H, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_down,
+                                const int32_t* idx, const bf16_t* res, bf16_t* out, int no_residual, bool chunk_major,
+                                hipStream_t s);
 
 // ---- GEMMs -----------------------------------------------------------------------
 hipError_t gemm_init();   // raises the dynamic-LDS limit of every instantiation (once per process)

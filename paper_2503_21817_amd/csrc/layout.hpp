@@ -65,6 +65,18 @@ inline KPartition choose_k_partition(int tiles_m, int tiles_n, int ktiles, bool 
     return best;
 }
 
+// A handful of rows: the forward GEMMs stream the weights straight to registers (fewrows.hip).  Every 16
+// columns read all activations again - a time that grows with rows * C * I, in steps of 16 rows - while what
+// is saved, two reducing launches and the ends of the K split, does not.  Layer forward, us, against the 128-row
+// tiles:  C = 4096: 8 rows 77 / 87, 16 rows 83 / 89, 20 rows 94 / 89;  C = 3072: 16 rows 57 / 59, 32 rows 68 / 62;
+// C = 2048: 32 rows 38 / 45, 64 rows 48 / 48;  C = 1024: 64 rows 21 / 35;  C = 256: 64 rows 14 / 28.  Row-major
+// activations (a saved buffer) cost about twice as much to read: 16 rows 98 / 94 at C = 4096, 37 / 42 at 2048.
+constexpr int64_t kFewRowsMax = 64;
+inline bool few_rows(int64_t rows, int64_t C, int64_t I, bool has_saved) {
+    const int64_t limit = (int64_t)4096 * 14336 * (rows <= 16 ? 16 : 8) / (has_saved ? 2 : 1);
+    return rows <= kFewRowsMax && rows * C * I <= limit;
+}
+
 // Few rows: the GEMMs of the forward pass run on 128-row tiles (twice the workgroups per row of
 // tiles, a loop bound by streaming the weights instead of by MFMA work on empty rows).
 // Measured at C=4096, I=14336: gate/up 86 -> 75 us and down 44 -> 38 us up to 128 rows, a few

@@ -39,7 +39,7 @@ template <bool IN_REGS>
 __global__ __launch_bounds__(ROW_THREADS) void gather_rmsnorm_kernel(
     const bf16_t* __restrict__ hidden, const int32_t* __restrict__ idx, int Rbound,
     const int32_t* __restrict__ r_dev, int C, float eps, const bf16_t* __restrict__ gain,
-    bf16_t* __restrict__ xrows, bf16_t* __restrict__ xn, float* __restrict__ rstd_out) {
+    bf16_t* __restrict__ xrows, bf16_t* __restrict__ xn, int64_t xn_row, int xn_chunk, float* __restrict__ rstd_out) {
     __shared__ float red[4];
     const int R = effective_rows(Rbound, r_dev);
     const int tid = threadIdx.x;
@@ -48,7 +48,7 @@ __global__ __launch_bounds__(ROW_THREADS) void gather_rmsnorm_kernel(
     const int chunks = C >> 3;
     const u32x4* src = reinterpret_cast<const u32x4*>(hidden + (int64_t)idx[r] * C);
     const u32x4* gsrc = reinterpret_cast<const u32x4*>(gain);
-    u32x4* dxn = reinterpret_cast<u32x4*>(xn + (int64_t)r * C);
+    u32x4* dxn = reinterpret_cast<u32x4*>(xn) + r * xn_row;      // strides in 16-byte chunks
     u32x4* dxr = xrows ? reinterpret_cast<u32x4*>(xrows + (int64_t)r * C) : nullptr;
 
     u32x4 held[IN_REGS ? RMS_MAXV : 1];
@@ -89,7 +89,7 @@ __global__ __launch_bounds__(ROW_THREADS) void gather_rmsnorm_kernel(
 #pragma unroll
             for (int j = 0; j < 8; ++j) f[j] = f[j] * rstd;
         }
-        dxn[c] = pack8(f);
+        dxn[(int64_t)c * xn_chunk] = pack8(f);
         if (dxr) dxr[c] = raw;
     };
     if (IN_REGS) {
@@ -105,16 +105,18 @@ __global__ __launch_bounds__(ROW_THREADS) void gather_rmsnorm_kernel(
 
 hipError_t launch_gather_rmsnorm(const bf16_t* hidden, const int32_t* idx, int R,
                                  const int32_t* r_dev, int C, float eps, const bf16_t* gain,
-                                 bf16_t* xrows, bf16_t* xn, float* rstd, hipStream_t s) {
+                                 bf16_t* xrows, bf16_t* xn, float* rstd, bool chunk_major, hipStream_t s) {
     if (R <= 0) return hipSuccess;
+    const int64_t xn_row = chunk_major ? 1 : C >> 3;
+    const int xn_chunk = chunk_major ? R : 1;
     dim3 grid(R), block(ROW_THREADS);
     profile_mark_begin(KC_GATHER_RMSNORM, s);
     if (C <= ROW_THREADS * 8 * RMS_MAXV)
         hipLaunchKernelGGL(gather_rmsnorm_kernel<true>, grid, block, 0, s, hidden, idx, R, r_dev, C,
-                           eps, gain, xrows, xn, rstd);
+                           eps, gain, xrows, xn, xn_row, xn_chunk, rstd);
     else
         hipLaunchKernelGGL(gather_rmsnorm_kernel<false>, grid, block, 0, s, hidden, idx, R, r_dev, C,
-                           eps, gain, xrows, xn, rstd);
+                           eps, gain, xrows, xn, xn_row, xn_chunk, rstd);
     profile_mark_end(KC_GATHER_RMSNORM, s);
     return hipGetLastError();
 }

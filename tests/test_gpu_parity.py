@@ -582,3 +582,35 @@ def test_device_row_count_far_below_the_bound(R, T):
         assert rel_l2(f64_of(a), bo[k]) < REL_L2_TOL, k
     sk = p.mask != 0
     assert np.array_equal(bits_of(out)[sk], p.hidden[sk])
+
+
+@pytest.mark.parametrize("R", [1, 15, 16, 17, 32, 33, 48, 49, 64])
+@pytest.mark.parametrize("C,I", [(136, 344), (512, 1368), (1032, 2056)], ids=["ragged-k", "whole-k", "batches-and-rest"])
+@pytest.mark.parametrize("r_host", [True, False], ids=["R-host", "R-device"])
+def test_weights_streamed_to_registers(R, C, I, r_host):
+    """A handful of rows: 1, 2 or 4 fragments of 16 rows, K ranges of a wavefront that are empty, shorter than a batch
+    of loads, or end inside a k-step, column counts that are no multiple of 16; activations chunk-major (no
+    saved buffer) and row-major.  Rows and columns are checked one by one."""
+    from helpers import max_slice_rel_l2
+    w = W.small(C=C, I=I, visual=(R + (0 if r_host is False else 23),), text=(1,), keep=(R - 1,), seed=5000 + R,
+                name=f"few-{R}")
+    assert w.R == R
+    print(f"few rows R={R} T={w.T} C={C} I={I} r_host={r_host}", flush=True)
+    p = Problem(w, unit_gain=False, with_gain_tensor=True)
+    fo = O.skipffn_forward(p.hidden, p.mask, p.wg, p.wu, p.wd, p.gain, w.eps, no_residual=True)
+    idx, sk = fo["idx"], p.mask != 0
+    want = O.bf16_bits_to_f64(fo["out_bits"][idx])
+    for saved in (False, True):
+        out, bufs = gpu_forward(p, R_host=r_host, saved=saved, flags=B.FLAG_NO_RESIDUAL)
+        got = bits_of(out)
+        assert np.array_equal(got[sk], p.hidden[sk])
+        # bf16 rounding of xn, H and out (2^-9 rms each) on one row or one column of few elements
+        assert max_slice_rel_l2(O.bf16_bits_to_f64(got[idx]), want, axis=1) < REL_L2_TOL
+    sv = bufs.saved_views(R)
+    for k in ("G", "U", "H"):
+        assert max_slice_rel_l2(f64_of(sv[k]), fo[k], axis=1) < REL_L2_TOL, k
+    full = O.skipffn_forward(p.hidden, p.mask, p.wg, p.wu, p.wd, p.gain, w.eps)
+    out, _ = gpu_forward(p, R_host=r_host, saved=False, inplace=True)
+    got = bits_of(out)
+    assert np.array_equal(got[sk], p.hidden[sk])
+    assert max_slice_rel_l2(O.bf16_bits_to_f64(got[idx]), O.bf16_bits_to_f64(full["out_bits"][idx]), axis=1) < REL_L2_TOL
