@@ -36,7 +36,10 @@ std::vector<std::pair<hipEvent_t, hipEvent_t>> g_prof_pool;
 std::once_flag g_gemm_once;
 hipError_t g_gemm_init_err = hipSuccess;
 hipError_t ensure_gemm_init() {
-    std::call_once(g_gemm_once, [] { g_gemm_init_err = gemm_init(); });
+    std::call_once(g_gemm_once, [] {
+        g_gemm_init_err = gemm_init();
+        if (g_gemm_init_err == hipSuccess) g_gemm_init_err = mid_rows_init();
+    });
     return g_gemm_init_err;
 }
 
@@ -282,9 +285,11 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
     }
     float* partial = reinterpret_cast<float*>(ws + W.partial);
 
-    // a handful of rows: both GEMMs stream the weights once, each in one launch with its epilogue fused.  Without a
-    // saved buffer (whose layout is the caller's to read) the activations lie chunk-major, as they are loaded.
-    const bool few = few_rows(Rb, C, I, saved != nullptr) && !(flags & SKIPFFN_FLAG_BALANCED_SPLIT);
+    // which GEMMs: see layout.hpp.  Without a saved buffer (whose layout is the caller's to read) a handful of rows lie
+    // chunk-major, as they are loaded.
+    const bool balanced = (flags & SKIPFFN_FLAG_BALANCED_SPLIT) != 0;
+    const bool few = !balanced && few_rows(Rb, C, I, saved != nullptr);
+    const bool mid = !balanced && !few && mid_rows(Rb);
     const bool chunk_major = few && saved == nullptr;
     // (2) gather + RMSNorm
     e = launch_gather_rmsnorm(static_cast<const bf16_t*>(hidden), idx, (int)Rb, r_dev, (int)C, eps,
@@ -296,21 +301,29 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
         if (e != hipSuccess) return hip_fail(e);
     }
 
-    if (few) {
+    if (few || mid) {
+        const bf16_t *wg = static_cast<const bf16_t*>(w_gate), *wu = static_cast<const bf16_t*>(w_up);
+        const bf16_t *wd = static_cast<const bf16_t*>(w_down), *res = static_cast<const bf16_t*>(hidden);
+        const int no_residual = (flags & SKIPFFN_FLAG_NO_RESIDUAL) ? 1 : 0;
         profile_mark_begin(KC_GEMM_GATE_UP, s);
-        e = launch_few_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, static_cast<const bf16_t*>(w_gate),
-                                    static_cast<const bf16_t*>(w_up), H, G, U, chunk_major, s);
+        e = few ? launch_few_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major, s)
+                : launch_mid_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, s);
         profile_mark_end(KC_GEMM_GATE_UP, s);
         if (e != hipSuccess) return hip_fail(e);
+        // the K-contiguous copy of H for the dW_down GEMM comes from a copy kernel
         if (HT != nullptr) {
             e = launch_gather_transpose(H, (int)I, nullptr, (int)Rb, r_dev, nullptr, HT, (int)ld_transposed(Rb), s);
             if (e != hipSuccess) return hip_fail(e);
         }
+        const int splits = mid ? choose_k_split_narrow(1, (int)((C + 127) / 128), (int)((I + BK - 1) / BK), num_cus()).splits : 0;
         profile_mark_begin(KC_GEMM_DOWN, s);
-        e = launch_few_rows_down(H, (int)Rb, r_dev, (int)C, (int)I, static_cast<const bf16_t*>(w_down), idx,
-                                 static_cast<const bf16_t*>(hidden), static_cast<bf16_t*>(out),
-                                 (flags & SKIPFFN_FLAG_NO_RESIDUAL) ? 1 : 0, chunk_major, s);
+        e = few ? launch_few_rows_down(H, (int)Rb, r_dev, (int)C, (int)I, wd, idx, res, static_cast<bf16_t*>(out),
+                                       no_residual, chunk_major, s)
+                : launch_mid_rows_down(H, (int)Rb, r_dev, (int)C, (int)I, wd, splits, partial, s);
         profile_mark_end(KC_GEMM_DOWN, s);
+        if (e == hipSuccess && mid)
+            e = launch_resid_scatter(partial, PartialLayout{splits, 0, 0}, (int)Rb, r_dev, (int)C, idx, res,
+                                     static_cast<bf16_t*>(out), no_residual, s);
         return e == hipSuccess ? SKIPFFN_OK : hip_fail(e);
     }
 
@@ -323,26 +336,10 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
         a.ldb = (int)C; a.b_bytes = (uint32_t)(I * C * 2);
         a.pairs = 1; a.splits = 1;
         a.out0 = H; a.out1 = G; a.out2 = U; a.ldo = (int)I;
-        const int gu_splits = gate_up_splits(Rb, C, I, num_cus());
+        a.outT0 = HT; a.ldt = (int)ld_transposed(Rb);         // written by the epilogue when training
         profile_mark_begin(KC_GEMM_GATE_UP, s);
-        if (gu_splits) {
-            // few rows: split K on 128-row tiles, fp32 partial sums, SwiGLU in the reducing kernel
-            a.narrow = 1;
-            a.splits = gu_splits;
-            a.partial = reinterpret_cast<float*>(ws + W.gu_partial);
-            e = launch_gemm(true, true, EPI_PARTIAL_GU, a, s);
-            if (e == hipSuccess)
-                e = launch_swiglu_reduce(a.partial, gu_splits, (int)Rb, r_dev, (int)I, a.tiles_n * BN, H, G, U, s);
-            profile_mark_end(KC_GEMM_GATE_UP, s);
-            // few rows: the K-contiguous copy of H for the dW_down GEMM comes from a copy kernel
-            if (e == hipSuccess && HT != nullptr)
-                e = launch_gather_transpose(H, (int)I, nullptr, (int)Rb, r_dev, nullptr, HT, (int)ld_transposed(Rb), s);
-        } else {
-            a.narrow = narrow_rows(Rb) ? 1 : 0;
-            a.outT0 = HT; a.ldt = (int)ld_transposed(Rb);     // written by the epilogue when training
-            e = launch_gemm(true, true, EPI_SWIGLU, a, s);
-            profile_mark_end(KC_GEMM_GATE_UP, s);
-        }
+        e = launch_gemm(true, true, EPI_SWIGLU, a, s);
+        profile_mark_end(KC_GEMM_GATE_UP, s);
         if (e != hipSuccess) return hip_fail(e);
     }
 
@@ -353,13 +350,9 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
         a.A0 = H; a.lda = (int)I; a.a_bytes = (uint32_t)(Rb * I * 2);
         a.B0 = static_cast<const bf16_t*>(w_down); a.ldb = (int)I; a.b_bytes = (uint32_t)(C * I * 2);
         a.pairs = 1;
-        const bool balanced = (flags & SKIPFFN_FLAG_BALANCED_SPLIT) != 0;
-        a.narrow = (narrow_rows(Rb) && !balanced) ? 1 : 0;
-        const int tile_rows = a.narrow ? BM / 2 : BM;
-        const int tiles_m = (int)((Rb + tile_rows - 1) / tile_rows), tiles_n = (int)((C + BN - 1) / BN);
+        const int tiles_m = (int)((Rb + BM - 1) / BM), tiles_n = (int)((C + BN - 1) / BN);
         const int ktiles = (int)((I + BK - 1) / BK);
-        const KPartition kp = a.narrow ? choose_k_split_narrow(tiles_m, tiles_n, ktiles, num_cus())
-                                       : choose_k_partition(tiles_m, tiles_n, ktiles, balanced, num_cus());
+        const KPartition kp = choose_k_partition(tiles_m, tiles_n, ktiles, balanced, num_cus());
         a.splits = kp.splits;
         a.idx = idx; a.ldo = (int)C;
         a.no_residual = (flags & SKIPFFN_FLAG_NO_RESIDUAL) ? 1 : 0;

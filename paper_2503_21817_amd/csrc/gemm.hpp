@@ -51,9 +51,7 @@ enum EpiKind : int {
     EPI_STORE = 1,         // out0 [M,N] bf16 or fp32, overwrite or accumulate
     EPI_PARTIAL = 2,       // fp32 partial[z][M][N]
     EPI_RESID_SCATTER = 3, // out0[idx[m]][n] = bf16(res[idx[m]][n] + acc)
-    EPI_SWIGLU_BWD = 4,    // acc = dH; e0=G, e1=U -> out0 = dG, out1 = dU (bf16)
-    EPI_PARTIAL_GU = 6     // B as for EPI_SWIGLU, fp32 partial[z][M][tiles_n * 256]: tile tn owns columns
-                           // tn*256 .. +127 (gate) and +128 .. +255 (up); the SwiGLU is applied by the reducing kernel
+    EPI_SWIGLU_BWD = 4     // acc = dH; e0=G, e1=U -> out0 = dG, out1 = dU (bf16)
 };
 
 struct GemmArgs {
@@ -75,7 +73,6 @@ struct GemmArgs {
     int out_f32;                 // EPI_STORE: 1 = fp32 output
     int accumulate;              // EPI_STORE: 1 = +=
     int no_residual;             // EPI_RESID_SCATTER: 1 = do not add the residual
-    int narrow;                  // host side: 1 = launch the 128-row tile variant (tiles_m counts 128-row tiles)
     int tail_narrow;             // 1 = a last tile row of at most 128 rows is a row of 128-row tiles, run by
                                  // the last tiles_n live workgroups of the grid
 };
@@ -197,8 +194,7 @@ __device__ __forceinline__ void tile_of_block(int b, int nb, int tiles_m, int ti
 // One output tile (tm, tn) over the K slabs [kt_begin, kt_end) of the concatenated pairs;
 // z selects the fp32 slab an EPI_PARTIAL result goes to.
 //
-// NARROW: the tile is 128 rows tall (for GEMMs with few rows: twice the workgroups per row of
-// tiles, half the MFMA work per slab, so that the loop is bound by streaming B).  The eight
+// NARROW: the tile is 128 rows tall (a last tile row of at most 128 rows: half the MFMA work per slab).  The eight
 // waves keep their 2 x 4 arrangement, each owning 64 x 64 = 4 x 4 MFMA tiles; only the first
 // 16 KB of an A stage are used.  KC A operands only.
 template <bool A_KC, bool B_KC, int EPI, bool NARROW = false>
@@ -211,12 +207,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
     constexpr int MT = WROWS / 32;                  // epilogue passes (32 rows per row group each)
     constexpr int MI = WROWS / 16;                  // MFMA tiles per wave along M (4 along N)
     constexpr int A_LOADS = TM / 64;                // 1 KB regions of an A slab each wave fills
-    constexpr bool GU = (EPI == EPI_SWIGLU || EPI == EPI_PARTIAL_GU);   // B tile = 128 rows of W_gate + 128 of W_up
+    constexpr bool GU = EPI == EPI_SWIGLU;   // B tile = 128 rows of W_gate + 128 of W_up
     // The A ring: 2 stages of 32 KB, fetched one slab ahead - or, for the 128-row tile, 3 stages
-    // of 16 KB fetched two slabs ahead, in the same phase as B.  The 128-row tile streams its B
-    // operand from HBM (few or no other tiles of the grid share it in L2); issuing everything in
-    // the first phase of slab j lets a load stay in flight for 2 slab times instead of 1 (A) and
-    // 1.4 (B): measured 4-6 % faster on the gate/up GEMM up to 256 rows.
+    // of 16 KB fetched two slabs ahead, in the same phase as B: issuing everything in the first phase of
+    // slab j lets a load stay in flight for 2 slab times instead of 1 (A) and 1.4 (B), 4-6 % faster.
     constexpr int NSA = NARROW ? 3 : NSTAGE_A;
     constexpr int A_STAGE = NARROW ? OPER_BYTES / 2 : OPER_BYTES;
     constexpr int A_AHEAD = NARROW ? 2 : 1;
@@ -648,7 +642,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
                 const f32x4 v = acc[2 * mt + s2][ni];
                 int col, mat;
                 if (EPI == EPI_SWIGLU)          { mat = ni >> 1; col = wn * 32 + (ni & 1) * 16 + 4 * cq; }
-                else if (EPI == EPI_PARTIAL_GU) { mat = 0;  col = (ni >> 1) * 128 + wn * 32 + (ni & 1) * 16 + 4 * cq; }
                 else                            { mat = 0;  col = wn * 64 + ni * 16 + 4 * cq; }
                 *reinterpret_cast<f32x4*>(sbuf + mat * EPI_ROWS * SLICE_STRIDE +
                                           (s2 * 16 + (lane & 15)) * SLICE_STRIDE + col * 4) = v;
@@ -663,7 +656,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
             const int r = rbase + i * RSTEP, c = cc;
             const int row = m0 + wm * WROWS + mt * 32 + r;
             const int col = n0 + c * 8;
-            const bool live = row < Meff && (EPI == EPI_PARTIAL_GU || col < P.N);
+            const bool live = row < Meff && col < P.N;
             if (HAS_T) {
 #pragma unroll
                 for (int m = 0; m < T_MATS; ++m)
@@ -727,13 +720,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
                     for (int k = 0; k < 4; ++k) pk[k] = pack_bf16x2(v[2 * k], v[2 * k + 1]);
                     *O = pk;
                 }
-            } else if (EPI == EPI_PARTIAL_GU) {
-                // every column of the tile is written (rows of W beyond N read as zeros)
-                f32x4* O = reinterpret_cast<f32x4*>(P.partial + ((int64_t)z * P.M + row) * ((int64_t)P.tiles_n * BN) +
-                                                    (int64_t)tn * BN + c * 8);
-                f32x4 lo = {v[0], v[1], v[2], v[3]}, hi = {v[4], v[5], v[6], v[7]};
-                O[0] = lo;
-                O[1] = hi;
             } else if (EPI == EPI_PARTIAL) {
                 f32x4* O = reinterpret_cast<f32x4*>(P.partial + ((int64_t)z * P.M + row) * P.N + col);
                 f32x4 lo = {v[0], v[1], v[2], v[3]}, hi = {v[4], v[5], v[6], v[7]};
@@ -844,12 +830,11 @@ constexpr bool kTailNarrowOk = A_KC && EPI == EPI_SWIGLU;
 // row count on the device the grid covers the host's bound, and a map over the bound would give
 // the live tile rows - the first ones of each panel - to some XCDs only (640 of 2944 rows: 5.3 of the 8
 // XCDs had work).  Workgroups past the live tiles come last in the launch order and leave at once.
-template <bool A_KC, bool B_KC, int EPI, bool NARROW = false>
+template <bool A_KC, bool B_KC, int EPI>
 __device__ __forceinline__ void gemm_block(GemmArgs P, const int block) {
     const int Meff = effective_rows(P.M, P.m_dev);
     const int Keff = effective_rows(P.K, P.k_dev);
-    constexpr int TM = NARROW ? BM / 2 : BM;
-    if constexpr (!NARROW && kTailNarrowOk<A_KC, EPI>) {
+    if constexpr (kTailNarrowOk<A_KC, EPI>) {
         // host contract: tail_narrow comes with splits == 1 and batch == 1
         const int rem = Meff % BM;
         if (P.tail_narrow && rem > 0 && rem <= BM / 2) {
@@ -866,7 +851,7 @@ __device__ __forceinline__ void gemm_block(GemmArgs P, const int block) {
             return;
         }
     }
-    const int tiles_m = (Meff + TM - 1) / TM;
+    const int tiles_m = (Meff + BM - 1) / BM;
     const int nblocks = tiles_m * P.tiles_n * P.splits * P.batch;
     if (block >= nblocks) return;                        // whole block leaves together: no barrier was reached yet
     int tm, tn, z;
@@ -884,12 +869,12 @@ __device__ __forceinline__ void gemm_block(GemmArgs P, const int block) {
     const int kt_begin = z * per_split;
     int kt_end = kt_begin + per_split;
     if (kt_end > ktotal) kt_end = ktotal;
-    gemm_tile<A_KC, B_KC, EPI, NARROW>(P, tm, tn, z, kt_begin, kt_end, Meff, Keff);
+    gemm_tile<A_KC, B_KC, EPI>(P, tm, tn, z, kt_begin, kt_end, Meff, Keff);
 }
 
-template <bool A_KC, bool B_KC, int EPI, bool NARROW = false>
+template <bool A_KC, bool B_KC, int EPI>
 __global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_kernel(GemmArgs P) {
-    gemm_block<A_KC, B_KC, EPI, NARROW>(P, (int)blockIdx.x);
+    gemm_block<A_KC, B_KC, EPI>(P, (int)blockIdx.x);
 }
 
 // Two independent GEMMs in one grid: workgroups [0, nblocks0) run problem 0 (launched

@@ -61,9 +61,6 @@ struct PartialLayout { int splits; int sk_nbg; int sk_kt; };
 hipError_t launch_resid_scatter(const float* partial, PartialLayout pl, int R, const int32_t* r_dev,
                                 int C, const int32_t* idx, const bf16_t* res, bf16_t* out,
                                 int no_residual, hipStream_t s);
-// SwiGLU over the split-K partial sums of a gate/up GEMM run with EPI_PARTIAL_GU (ldp = tiles_n * 256)
-hipError_t launch_swiglu_reduce(const float* partial, int splits, int R, const int32_t* r_dev, int I, int ldp,
-                                bf16_t* H, bf16_t* G, bf16_t* U, hipStream_t s);
 // dst[r] = src[idx[r]]  (rows of row_bytes, multiple of 16)
 hipError_t launch_gather_rows(const void* src, void* dst, int64_t row_bytes, const int32_t* idx,
                               int R, const int32_t* r_dev, hipStream_t s);
@@ -133,6 +130,14 @@ hipError_t launch_few_rows_gate_up(const bf16_t* xn, int rows, const int32_t* r_
 hipError_t launch_few_rows_down(const bf16_t* H, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_down,
                                 const int32_t* idx, const bf16_t* res, bf16_t* out, int no_residual, bool chunk_major,
                                 hipStream_t s);
+
+// ---- the forward GEMMs of up to 256 rows ------------------------------------------------------------------
+hipError_t mid_rows_init();      // raises the dynamic-LDS limit of every instantiation (once per process)
+hipError_t launch_mid_rows_gate_up(const bf16_t* xn, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_gate,
+                                   const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, hipStream_t s);
+// fp32 partial[splits][rows][C]
+hipError_t launch_mid_rows_down(const bf16_t* H, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_down,
+                                int splits, float* partial, hipStream_t s);
 
 // ---- GEMMs -----------------------------------------------------------------------
 hipError_t gemm_init();   // raises the dynamic-LDS limit of every instantiation (once per process)

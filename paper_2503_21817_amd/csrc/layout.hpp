@@ -23,7 +23,7 @@ inline size_t gain_partial_bytes(int64_t R, int64_t C) {
 }
 
 constexpr int kMaxSplits = 8;
-constexpr int kMaxSplitsNarrow = 16;     // few rows: small fp32 slabs, and every CU has to stream weights
+constexpr int kMaxSplitsNarrow = 16;     // up to 256 rows: small fp32 slabs, and every CU has to stream weights
 
 // How the K range of a GEMM with tiles_m x tiles_n output tiles and `ktiles` K slabs is cut
 // on `ncu` CUs (one workgroup per CU).  Costs are in units of one K slab of one tile: every
@@ -65,25 +65,13 @@ inline KPartition choose_k_partition(int tiles_m, int tiles_n, int ktiles, bool 
     return best;
 }
 
-// A handful of rows: the forward GEMMs stream the weights straight to registers (fewrows.hip).  Every 16
-// columns read all activations again - a time that grows with rows * C * I, in steps of 16 rows - while what
-// is saved, two reducing launches and the ends of the K split, does not.  Layer forward, us, against the 128-row
-// tiles:  C = 4096: 8 rows 77 / 87, 16 rows 83 / 89, 20 rows 94 / 89;  C = 3072: 16 rows 57 / 59, 32 rows 68 / 62;
-// C = 2048: 32 rows 38 / 45, 64 rows 48 / 48;  C = 1024: 64 rows 21 / 35;  C = 256: 64 rows 14 / 28.  Row-major
-// activations (a saved buffer) cost about twice as much to read: 16 rows 98 / 94 at C = 4096, 37 / 42 at 2048.
-constexpr int64_t kFewRowsMax = 64;
-inline bool few_rows(int64_t rows, int64_t C, int64_t I, bool has_saved) {
-    const int64_t limit = (int64_t)4096 * 14336 * (rows <= 16 ? 16 : 8) / (has_saved ? 2 : 1);
-    return rows <= kFewRowsMax && rows * C * I <= limit;
-}
-
-// Few rows: the GEMMs of the forward pass run on 128-row tiles (twice the workgroups per row of
-// tiles, a loop bound by streaming the weights instead of by MFMA work on empty rows).
-// Measured at C=4096, I=14336: gate/up 86 -> 75 us and down 44 -> 38 us up to 128 rows, a few
-// per cent up to 256 rows, slower beyond (the half-height tiles are bound by the load / barrier
-// skeleton of the loop, not by MFMA work).
-inline bool narrow_rows(int64_t rows) { return rows <= 256; }
-// plain split-K for the 128-row tiles: fill the CUs, keep at least 8 slabs per workgroup
+// Up to 256 rows the forward GEMMs are bound by streaming the 6 * C * I bytes of weights.  They run on tiles of ALL
+// rows and 128 weight rows (midrows.hip), the down GEMM with its K range split into fp32 slabs.  Layer forward, us,
+// against 128-row tiles that shared the weights through L2:  C = 4096: 64 rows 77 / 104, 184 rows 102 / 117,
+// 256 rows 117 / 128;  C = 3072: 128 rows 70 / 76;  C = 2048: 128 rows 49 / 56;  C = 1024: 128 rows 30 / 38.
+// Beyond 256 rows a second row of tiles would stream the weights again: 256-row tiles of the general core.
+inline bool mid_rows(int64_t rows) { return rows <= 256; }
+// plain split-K: fill the CUs, keep at least 8 slabs per workgroup
 inline KPartition choose_k_split_narrow(int tiles_m, int tiles_n, int ktiles, int ncu) {
     const int tiles = tiles_m * tiles_n;
     KPartition best{1, 0};
@@ -98,28 +86,22 @@ inline KPartition choose_k_split_narrow(int tiles_m, int tiles_n, int ktiles, in
     return best;
 }
 
-// Gate/up GEMM with few rows: one row of tiles has only I / 128 workgroups (112 for I = 14336), and a
-// workgroup cannot keep enough weight bytes in flight to make up for the idle CUs.  Up to 128 rows
-// the K range is therefore split over 2..4 workgroups per tile, which write fp32 partial sums of
-// gate and up; the SwiGLU moves to the reducing kernel.  0 = not used (fused epilogue instead).
-// Measured at C=4096, I=14336 (GEMM + reduction against the fused 128-row GEMM): 53 / 72 us at 16
-// rows, 57 / 71 at 64, 65 / 73 at 128; at 184 and 256 rows the partial sums (229 KB per row, written
-// and read) cost what the split gains.
-constexpr int64_t kGateUpSplitMaxRows = BM / 2;
-inline int gate_up_splits(int64_t rows, int64_t C, int64_t I, int ncu) {
-    if (rows > kGateUpSplitMaxRows) return 0;
-    const int64_t tiles_n = (I + BN / 2 - 1) / (BN / 2), ktiles = (C + BK - 1) / BK;
-    int64_t s = std::min<int64_t>(4, ncu / std::max<int64_t>(tiles_n, 1));
-    while (s > 1 && ktiles / s < 8) --s;
-    return s >= 2 ? (int)s : 0;
+// A handful of rows of a narrow layer: the weights go straight to registers (fewrows.hip), two launches with
+// fused epilogues instead of three.  Every 16 columns read all activations again - a time that grows with
+// rows * C * I - while what is saved, a reducing launch and the ends of the split, does not.  Layer forward, us,
+// against the tiles above:  C = 4096: 1 row 75 / 74, 16 rows 83 / 74;  C = 3072: 16 rows 57 / 55;  C = 2048: 16 rows
+// 32 / 43, 32 rows 38 / 43, 48 rows 46 / 43;  C = 1024: 64 rows 21 / 27;  C = 256: 64 rows 14 / 20.  Row-major
+// activations (a saved buffer) cost more to read: C = 2048: 16 rows 38 / 43, 32 rows 49 / 43.
+constexpr int64_t kFewRowsMax = 64;
+inline bool few_rows(int64_t rows, int64_t C, int64_t I, bool has_saved) {
+    const int64_t weight = C * I, limit = (int64_t)40 * 2048 * 7168;
+    return rows <= kFewRowsMax && weight <= (int64_t)24 << 20 && rows * weight <= (has_saved ? limit / 2 : limit);
 }
-inline size_t gate_up_partial_bytes(int64_t R, int64_t C, int64_t I, int ncu) {
-    // sized for the largest row count that takes this path, so that a bound covers every smaller count
-    const int64_t rows = std::min<int64_t>(R, kGateUpSplitMaxRows);
-    const int s = gate_up_splits(rows, C, I, ncu);
-    const int64_t tiles_n = (I + BN / 2 - 1) / (BN / 2);
-    return s ? (size_t)s * (size_t)rows * (size_t)tiles_n * BN * 4 : 0;
-}
+
+// The gate/up GEMM is not split along K: with 64 columns of each weight per workgroup it has enough workgroups, and
+// its epilogue needs complete sums.
+inline int gate_up_splits(int64_t, int64_t, int64_t, int) { return 0; }
+inline size_t gate_up_partial_bytes(int64_t, int64_t, int64_t, int) { return 0; }
 
 // Leading dimension of the transposed copies ([columns][rows]): rows rounded up to 64 elements, so that every
 // row of a copy starts on a 128-byte line (with a multiple of 8 only, each 128-byte piece the GEMMs load
@@ -148,8 +130,7 @@ inline FwdWs fwd_ws(int64_t R, int64_t C, int64_t I, bool has_saved, int ncu) {
     w.xn = o;   if (!has_saved) o += align_up((size_t)R * C * 2);
     w.rstd = o; if (!has_saved) o += align_up((size_t)R * 4);
     w.h = o;    if (!has_saved) o += align_up((size_t)R * I * 2);
-    // a buffer sized for R_max rows must do for every smaller count: the 128-row variant (up to
-    // 256 rows) may use more slabs than the 256-row tiles
+    // a buffer sized for R_max rows must do for every smaller count: up to 256 rows may use more slabs
     const size_t slab_rows = std::max<size_t>((size_t)kMaxSplits * R, (size_t)kMaxSplitsNarrow * std::min<int64_t>(R, 256));
     w.partial = o; o += align_up(slab_rows * C * 4);
     w.gu_partial = o; o += align_up(gate_up_partial_bytes(R, C, I, ncu));

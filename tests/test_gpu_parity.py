@@ -614,3 +614,28 @@ def test_weights_streamed_to_registers(R, C, I, r_host):
     got = bits_of(out)
     assert np.array_equal(got[sk], p.hidden[sk])
     assert max_slice_rel_l2(O.bf16_bits_to_f64(got[idx]), O.bf16_bits_to_f64(full["out_bits"][idx]), axis=1) < REL_L2_TOL
+
+
+@pytest.mark.parametrize("R,C,I", [(41, 2056, 7176), (64, 2048, 7168), (65, 264, 328), (128, 640, 1664), (129, 640, 1664),
+                                   (192, 264, 328), (193, 136, 2056), (256, 640, 1664)])
+@pytest.mark.parametrize("r_host", [True, False], ids=["R-host", "R-device"])
+def test_tiles_of_all_rows(R, C, I, r_host):
+    """Up to 256 rows in one tile of 64, 128, 192 or 256: K ranges of a few slabs (fewer than the ring holds), ragged ones,
+    whole ones (workgroups start at different slabs), one split and several, column tiles that are cut off."""
+    from helpers import max_slice_rel_l2
+    w = W.small(C=C, I=I, visual=(R + (0 if r_host is False else 23),), text=(1,), keep=(R - 1,), seed=6000 + R,
+                name=f"all-rows-{R}")
+    assert w.R == R
+    print(f"tiles of all rows R={R} T={w.T} C={C} I={I} r_host={r_host}", flush=True)
+    p = Problem(w, unit_gain=True, with_gain_tensor=False)
+    fo = O.skipffn_forward(p.hidden, p.mask, p.wg, p.wu, p.wd, None, w.eps, no_residual=True)
+    idx, sk = fo["idx"], p.mask != 0
+    out, bufs = gpu_forward(p, R_host=r_host, saved=True, flags=B.FLAG_NO_RESIDUAL)
+    got = bits_of(out)
+    assert np.array_equal(got[sk], p.hidden[sk])
+    want = O.bf16_bits_to_f64(fo["out_bits"][idx])
+    for axis in (0, 1):                  # every column and every row on its own
+        assert max_slice_rel_l2(O.bf16_bits_to_f64(got[idx]), want, axis=axis) < REL_L2_TOL
+    sv = bufs.saved_views(R)
+    for k in ("G", "U", "H"):
+        assert max_slice_rel_l2(f64_of(sv[k]), fo[k], axis=1) < REL_L2_TOL, k
