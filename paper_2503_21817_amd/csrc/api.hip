@@ -39,6 +39,7 @@ hipError_t ensure_gemm_init() {
     std::call_once(g_gemm_once, [] {
         g_gemm_init_err = gemm_init();
         if (g_gemm_init_err == hipSuccess) g_gemm_init_err = mid_rows_init();
+        if (g_gemm_init_err == hipSuccess) g_gemm_init_err = merge_init();
     });
     return g_gemm_init_err;
 }
@@ -764,7 +765,7 @@ int skipffn_token_merge(const void* x, const int32_t* seg_host, int64_t S, int64
         for (int i = st.count + 1; i <= SEG_TABLE_MAX; ++i) st.off[i] = st.off[st.count];
         for (int i = 0; i < st.count; ++i) gmax = std::max(gmax, st.off[i + 1] - st.off[i]);
         // S_i = Xn_i Xn_i^T  [n_i, n_i] fp32 on the MFMA core, every set of the group in one grid
-        e = launch_gemm_selfsim(xn, (int)C, st, gmax, sim, ld, sim_stride, s);
+        e = launch_selfsim(xn, (int)C, st, gmax, sim, ld, sim_stride, s);
         if (e != hipSuccess) break;
         e = launch_merge_group(xb, st, gmax, (int)C, (int)k, (int)g0, sim, ld, sim_stride, avg_sim,
                                slot_of, kept_idx, assign, static_cast<bf16_t*>(out), s);

@@ -25,9 +25,6 @@ hipError_t gemm_init() {
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_streamk_kernel<true, false>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS_BYTES);
     if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_selfsim_kernel<EPI_STORE>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS_BYTES);
-    if (e != hipSuccess) return e;
     return hipSuccess;
 }
 
@@ -76,22 +73,6 @@ hipError_t launch_gemm_streamk(bool a_kc, bool b_kc, GemmArgs& a, int nbg, hipSt
     else
         hipLaunchKernelGGL((gemm_bf16_streamk_kernel<true, false>), dim3(blocks), dim3(GEMM_THREADS),
                            GEMM_LDS_BYTES, s, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_gemm_selfsim(const bf16_t* xn, int C, const SegTable& st, int n_max, float* sim, int ld,
-                               int64_t sim_stride, hipStream_t s) {
-    if (st.count <= 0 || n_max <= 0) return hipSuccess;
-    GemmArgs a{};
-    a.M = n_max; a.N = n_max; a.K = C;
-    a.A0 = xn; a.lda = C; a.B0 = xn; a.ldb = C;
-    a.pairs = 1; a.splits = 1; a.batch = 1;
-    a.out0 = sim; a.ldo = ld; a.out_f32 = 1; a.accumulate = 0;
-    const int tiles_1d = (n_max + BM - 1) / BM;
-    a.tiles_m = a.tiles_n = tiles_1d;
-    const unsigned blocks = (unsigned)(st.count * tiles_1d * tiles_1d);
-    hipLaunchKernelGGL(gemm_bf16_selfsim_kernel<EPI_STORE>, dim3(blocks), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a, st,
-                       tiles_1d, sim_stride);
     return hipGetLastError();
 }
 
