@@ -4,6 +4,7 @@
 // Kernels that reduce over a row give the row to one 256-thread workgroup (R is a few
 // thousand at most, so a wavefront per row would leave most of the chip without work in
 // flight); purely elementwise ones run one thread per 16-byte chunk.
+#include "colsum.hpp"
 #include "kernels.hpp"
 
 namespace skipffn {
@@ -147,7 +148,25 @@ __global__ __launch_bounds__(ROW_THREADS) void resid_scatter_kernel(
     for (int j = 0; j < 8; ++j) acc[j] = 0.0f;
     const float* p = partial + (int64_t)r * C + c * 8;
     const int splits = partial_count(pl, R, r, c * 8);
-    for (int z = 0; z < splits; ++z) {
+    const u32x4 xraw = no_residual ? u32x4{0u, 0u, 0u, 0u} : *reinterpret_cast<const u32x4*>(res + orow + c * 8);
+    // four slabs in flight (few rows: a load after the other is all the time there is)
+    int z = 0;
+    for (; z + 4 <= splits; z += 4) {
+        f32x4 a[4], b[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            a[k] = *reinterpret_cast<const f32x4*>(p + (z + k) * zstride);
+            b[k] = *reinterpret_cast<const f32x4*>(p + (z + k) * zstride + 4);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                acc[j] += a[k][j];
+                acc[4 + j] += b[k][j];
+            }
+    }
+    for (; z < splits; ++z) {
         f32x4 a = *reinterpret_cast<const f32x4*>(p + z * zstride);
         f32x4 b = *reinterpret_cast<const f32x4*>(p + z * zstride + 4);
 #pragma unroll
@@ -158,7 +177,7 @@ __global__ __launch_bounds__(ROW_THREADS) void resid_scatter_kernel(
     }
     if (!no_residual) {
         float x[8];
-        unpack8(*reinterpret_cast<const u32x4*>(res + orow + c * 8), x);
+        unpack8(xraw, x);
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc[j] += x[j];
     }
@@ -475,33 +494,12 @@ __global__ __launch_bounds__(ROW_THREADS) void rmsnorm_bwd_scatter_kernel(
     }
 }
 
-// dgain[c] (+)= sum over strips of gpart[strip][c]: eight interleaved partial sums per column,
-// added in a fixed order (deterministic).  32 columns per workgroup.
-__global__ __launch_bounds__(ROW_THREADS) void gain_grad_reduce_kernel(
+// dgain[c] (+)= sum over strips of gpart[strip][c]
+__global__ __launch_bounds__(COLSUM_THREADS) void gain_grad_reduce_kernel(
     const float* __restrict__ gpart, int Rbound, const int32_t* __restrict__ r_dev, int C,
     float* __restrict__ dgain, int accumulate) {
-    __shared__ float part8[8][32];
     const int R = effective_rows(Rbound, r_dev);
-    const int nstrips = (R + GAIN_STRIP - 1) / GAIN_STRIP;
-    const int cx = threadIdx.x & 31, sy = threadIdx.x >> 5;
-    const int c = blockIdx.x * 32 + cx;
-    float a0 = 0.0f, a1 = 0.0f;
-    if (c < C) {
-        int q = sy;
-        for (; q + 8 < nstrips; q += 16) {             // two loads in flight per thread
-            a0 += gpart[(int64_t)q * C + c];
-            a1 += gpart[(int64_t)(q + 8) * C + c];
-        }
-        if (q < nstrips) a0 += gpart[(int64_t)q * C + c];
-    }
-    part8[sy][cx] = a0 + a1;
-    __syncthreads();
-    if (sy == 0 && c < C) {
-        float v = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v += part8[k][cx];
-        dgain[c] = accumulate ? dgain[c] + v : v;
-    }
+    column_sum(gpart, (R + GAIN_STRIP - 1) / GAIN_STRIP, C, dgain, accumulate);
 }
 
 hipError_t launch_rmsnorm_bwd_scatter(const float* dxn_partial, PartialLayout pl, int R,
@@ -530,7 +528,7 @@ hipError_t launch_rmsnorm_bwd_scatter(const float* dxn_partial, PartialLayout pl
     }
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && gg) {
-        hipLaunchKernelGGL(gain_grad_reduce_kernel, dim3((C + 31) / 32), block, 0, s, gain_partial, R,
+        hipLaunchKernelGGL(gain_grad_reduce_kernel, dim3((C + 31) / 32), dim3(COLSUM_THREADS), 0, s, gain_partial, R,
                            r_dev, C, dgain, accumulate);
         e = hipGetLastError();
     }
