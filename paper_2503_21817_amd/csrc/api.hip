@@ -291,10 +291,11 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
     const bool balanced = (flags & SKIPFFN_FLAG_BALANCED_SPLIT) != 0;
     const bool few = !balanced && few_rows(Rb, C, I, saved != nullptr);
     const bool mid = !balanced && !few && mid_rows(Rb);
-    const bool chunk_major = few && saved == nullptr;
+    const bool few_down = few || (mid && few_rows_down(Rb, saved != nullptr));
+    const bool chunk_major_xn = few && saved == nullptr, chunk_major_h = few_down && saved == nullptr;
     // (2) gather + RMSNorm
     e = launch_gather_rmsnorm(static_cast<const bf16_t*>(hidden), idx, (int)Rb, r_dev, (int)C, eps,
-                              static_cast<const bf16_t*>(rms_gain), xrows, xn, rstd, chunk_major, s);
+                              static_cast<const bf16_t*>(rms_gain), xrows, xn, rstd, chunk_major_xn, s);
     if (e != hipSuccess) return hip_fail(e);
     if (xnT != nullptr) {   // K-contiguous copy of the normalised rows for the dW_gate / dW_up GEMMs
         e = launch_gather_transpose(xn, (int)C, nullptr, (int)Rb, r_dev, nullptr, xnT,
@@ -307,8 +308,8 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
         const bf16_t *wd = static_cast<const bf16_t*>(w_down), *res = static_cast<const bf16_t*>(hidden);
         const int no_residual = (flags & SKIPFFN_FLAG_NO_RESIDUAL) ? 1 : 0;
         profile_mark_begin(KC_GEMM_GATE_UP, s);
-        e = few ? launch_few_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major, s)
-                : launch_mid_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, s);
+        e = few ? launch_few_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_xn, s)
+                : launch_mid_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_h, s);
         profile_mark_end(KC_GEMM_GATE_UP, s);
         if (e != hipSuccess) return hip_fail(e);
         // the K-contiguous copy of H for the dW_down GEMM comes from a copy kernel
@@ -316,13 +317,13 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
             e = launch_gather_transpose(H, (int)I, nullptr, (int)Rb, r_dev, nullptr, HT, (int)ld_transposed(Rb), s);
             if (e != hipSuccess) return hip_fail(e);
         }
-        const int splits = mid ? choose_k_split_narrow(1, (int)((C + 127) / 128), (int)((I + BK - 1) / BK), num_cus()).splits : 0;
+        const int splits = !few_down ? choose_k_split_narrow(1, (int)((C + 127) / 128), (int)((I + BK - 1) / BK), num_cus()).splits : 0;
         profile_mark_begin(KC_GEMM_DOWN, s);
-        e = few ? launch_few_rows_down(H, (int)Rb, r_dev, (int)C, (int)I, wd, idx, res, static_cast<bf16_t*>(out),
-                                       no_residual, chunk_major, s)
-                : launch_mid_rows_down(H, (int)Rb, r_dev, (int)C, (int)I, wd, splits, partial, s);
+        e = few_down ? launch_few_rows_down(H, (int)Rb, r_dev, (int)C, (int)I, wd, idx, res, static_cast<bf16_t*>(out),
+                                            no_residual, chunk_major_h, s)
+                     : launch_mid_rows_down(H, (int)Rb, r_dev, (int)C, (int)I, wd, splits, partial, s);
         profile_mark_end(KC_GEMM_DOWN, s);
-        if (e == hipSuccess && mid)
+        if (e == hipSuccess && !few_down)
             e = launch_resid_scatter(partial, PartialLayout{splits, 0, 0}, (int)Rb, r_dev, (int)C, idx, res,
                                      static_cast<bf16_t*>(out), no_residual, s);
         return e == hipSuccess ? SKIPFFN_OK : hip_fail(e);

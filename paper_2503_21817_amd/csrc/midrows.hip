@@ -27,7 +27,8 @@ struct MidRowsArgs {
     const bf16_t* A; uint32_t a_bytes;        // [rows][K]
     const bf16_t* B0; const bf16_t* B1; uint32_t b_bytes;   // [N][K]; gate/up: W_gate, W_up
     int splits;                               // gate/up: 1
-    bf16_t* H; bf16_t* G; bf16_t* U;          // gate/up: [rows][N]; G, U optional
+    // gate/up: 16-byte chunk c (8 columns) of row r of H at byte r * h_row + c * h_chunk; G, U [rows][N], optional
+    bf16_t* H; uint32_t h_row, h_chunk; bf16_t* G; bf16_t* U;
     float* partial;                           // down: [splits][rows][N]
 };
 
@@ -77,9 +78,10 @@ __global__ __launch_bounds__(SLAB_THREADS) void mid_rows_kernel(MidRowsArgs P) {
             float h[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) h[j] = g[j] * sigmoid_f(g[j]) * u[j];
-            const int64_t o = (int64_t)row * P.N + n;
-            *reinterpret_cast<u32x2*>(P.H + o) = u32x2{pack_bf16x2(h[0], h[1]), pack_bf16x2(h[2], h[3])};
+            *reinterpret_cast<u32x2*>(reinterpret_cast<char*>(P.H) + (uint32_t)row * P.h_row + (uint32_t)(n >> 3) * P.h_chunk +
+                                      (n & 4) * 2) = u32x2{pack_bf16x2(h[0], h[1]), pack_bf16x2(h[2], h[3])};
             if (P.G != nullptr) {
+                const int64_t o = (int64_t)row * P.N + n;
                 *reinterpret_cast<u32x2*>(P.G + o) = u32x2{pack_bf16x2(g[0], g[1]), pack_bf16x2(g[2], g[3])};
                 *reinterpret_cast<u32x2*>(P.U + o) = u32x2{pack_bf16x2(u[0], u[1]), pack_bf16x2(u[2], u[3])};
             }
@@ -127,12 +129,13 @@ hipError_t mid_rows_init() {
 }
 
 hipError_t launch_mid_rows_gate_up(const bf16_t* xn, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_gate,
-                                   const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, hipStream_t s) {
+                                   const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major_h, hipStream_t s) {
     MidRowsArgs a{};
     a.rows = rows; a.r_dev = r_dev; a.N = I; a.K = C;
     a.A = xn; a.a_bytes = (uint32_t)((int64_t)rows * C * 2);
     a.B0 = w_gate; a.B1 = w_up; a.b_bytes = (uint32_t)((int64_t)I * C * 2);
     a.splits = 1; a.H = H; a.G = G; a.U = U;
+    a.h_row = chunk_major_h ? 16u : (uint32_t)I * 2; a.h_chunk = chunk_major_h ? (uint32_t)rows * 16 : 16u;
     return launch_mid_rows<true>(a, s);
 }
 

@@ -639,3 +639,22 @@ def test_tiles_of_all_rows(R, C, I, r_host):
     sv = bufs.saved_views(R)
     for k in ("G", "U", "H"):
         assert max_slice_rel_l2(f64_of(sv[k]), fo[k], axis=1) < REL_L2_TOL, k
+
+
+@pytest.mark.parametrize("R", [1, 9, 16, 17])
+def test_decode_of_a_wide_layer(R):
+    """A layer too wide for the register path of the gate/up GEMM: up to 16 rows its down GEMM takes that path, on the
+    chunk-major result of the tiles; from 17 rows (and with a saved buffer) both run on tiles."""
+    from helpers import max_slice_rel_l2
+    w = W.small(C=2056, I=12296, visual=(R,), text=(1,), keep=(R - 1,), seed=7000 + R, name=f"wide-{R}")
+    assert w.R == R
+    p = Problem(w, unit_gain=True, with_gain_tensor=False)
+    fo = O.skipffn_forward(p.hidden, p.mask, p.wg, p.wu, p.wd, None, w.eps)
+    idx, sk = fo["idx"], p.mask != 0
+    want = O.bf16_bits_to_f64(fo["out_bits"][idx])
+    for saved in (False, True):
+        for r_host in (True, False):
+            print(f"wide layer R={R} saved={saved} r_host={r_host}", flush=True)
+            got = bits_of(gpu_forward(p, R_host=r_host, saved=saved)[0])
+            assert np.array_equal(got[sk], p.hidden[sk])
+            assert max_slice_rel_l2(O.bf16_bits_to_f64(got[idx]), want, axis=1) < REL_L2_TOL
