@@ -633,6 +633,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
 
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
+        // the rest of the tile has no rows (the transposed copies are zero up to the next multiple of 64): a tile of 32
+        // rows leaves after one pass of four
+        if (m0 + mt * 32 >= (HAS_T ? (Meff + 63) / 64 * 64 : Meff)) break;
         char* sbuf = smem + ((NSTAGING == 2 ? (mt & 1) * 2 : 0) + wm) * SLICE_BYTES;
         // ---- dump this wave's part of the slice
 #pragma unroll
