@@ -319,7 +319,10 @@ hipError_t launch_gather_transpose(const bf16_t* src, int C, const int32_t* idx,
 }
 
 // ---- bit copy of skipped rows (out-of-place calls) ---------------------------------------
-// A row t is copied unless a binary search finds it in the ascending list idx.
+// A wavefront takes a row t and copies it unless t is in the ascending list idx.  The search probes 64 positions at a
+// time: two dependent loads up to 4096 entries, where halving takes 12 before the copy can begin; the row is then
+// copied with eight loads in flight per lane (a row of 4096 at once).  616 rows 7.8 -> 5.2 us, 1232 rows 9.8 ->
+// 6.1, 4928 rows 16.4 -> 14.0.
 __global__ __launch_bounds__(ROW_THREADS) void passthrough_kernel(
     const u32x4* __restrict__ src, u32x4* __restrict__ dst, int64_t T, int64_t row_chunks,
     const int32_t* __restrict__ idx, int Rbound, const int32_t* __restrict__ r_dev) {
@@ -327,15 +330,28 @@ __global__ __launch_bounds__(ROW_THREADS) void passthrough_kernel(
     const int lane = threadIdx.x & 63;
     const int64_t t = (int64_t)blockIdx.x * ROWS_PER_BLOCK + (threadIdx.x >> 6);
     if (t >= T) return;
-    int lo = 0, hi = R;              // first position with idx[pos] >= t
-    while (lo < hi) {
-        int mid = (lo + hi) >> 1;
-        if (idx[mid] < t) lo = mid + 1; else hi = mid;
+    int lo = 0, hi = R;              // the first position with idx[pos] >= t lies in [lo, hi]
+    while (hi - lo > 63) {
+        const int step = (hi - lo + 63) >> 6;
+        const int p = lo + lane * step;
+        const int below = __popcll(__ballot(p < hi && idx[p < hi ? p : lo] < t));    // ascending: a prefix of the lanes
+        const int end = lo + below * step;
+        if (below == 0) hi = lo;
+        else { lo = end - step + 1; hi = end < hi ? end : hi; }
     }
-    if (lo < R && idx[lo] == t) return;   // retained: written by the scatter epilogue
+    const int p = lo + lane;
+    if (__ballot(p <= hi && p < R && idx[p < R ? p : 0] == t) != 0) return;   // retained: written by the scatter epilogue
     const u32x4* s = src + t * row_chunks;
     u32x4* d = dst + t * row_chunks;
-    for (int64_t c = lane; c < row_chunks; c += 64) d[c] = s[c];
+    int64_t c = lane;
+    for (; c + 7 * 64 < row_chunks; c += 8 * 64) {
+        u32x4 v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = s[c + k * 64];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) d[c + k * 64] = v[k];
+    }
+    for (; c < row_chunks; c += 64) d[c] = s[c];
 }
 
 hipError_t launch_passthrough(const void* src, void* dst, int64_t T, int64_t row_bytes,
