@@ -29,6 +29,8 @@ constexpr int kMaxSplitsNarrow = 16;     // up to 256 rows: small fp32 slabs, an
 // on `ncu` CUs (one workgroup per CU).  Costs are in units of one K slab of one tile: every
 // round of `ncu` workgroups costs its slab count plus a fixed prologue/epilogue, partial tiles
 // cost a write now and a read in the reducing kernel.
+// A split of fewer than 4 slabs would be all prologue (at least 8 before: the dXn GEMM of the 32-row, C = 256 layer, 22
+// slabs on 2 workgroups, ended its training step at 65.1 us, on 5 at 61.3).
 //   splits == 1, sk_nbg == 0 : one workgroup per tile, epilogue fused
 //   splits  > 1, sk_nbg == 0 : plain split-K into `splits` fp32 slabs
 //   sk_nbg  > 0              : balanced split (gemm_bf16_streamk_kernel), sk_nbg workgroups per
@@ -41,7 +43,7 @@ inline KPartition choose_k_partition(int tiles_m, int tiles_n, int ktiles, bool 
     double best_cost = 1e30;
     for (int s = 1; s <= kMaxSplits; ++s) {
         int per = (ktiles + s - 1) / s;
-        if (s > 1 && per < 8) break;
+        if (s > 1 && per < 4) break;
         int rounds = (tiles * s + ncu - 1) / ncu;
         double cost = rounds * (per + 8.0 + (s > 1 ? 8.0 : 0.0)) + (s > 1 ? 0.04 * s * tiles : 0.0);
         if (cost < best_cost - 1e-9) { best_cost = cost; best = KPartition{s, 0}; }
@@ -71,14 +73,14 @@ inline KPartition choose_k_partition(int tiles_m, int tiles_n, int ktiles, bool 
 // 256 rows 117 / 128;  C = 3072: 128 rows 70 / 76;  C = 2048: 128 rows 49 / 56;  C = 1024: 128 rows 30 / 38.
 // Beyond 256 rows a second row of tiles would stream the weights again: 256-row tiles of the general core.
 inline bool mid_rows(int64_t rows) { return rows <= 256; }
-// plain split-K: fill the CUs, keep at least 8 slabs per workgroup
+// plain split-K: fill the CUs, keep at least 4 slabs per workgroup (see choose_k_partition)
 inline KPartition choose_k_split_narrow(int tiles_m, int tiles_n, int ktiles, int ncu) {
     const int tiles = tiles_m * tiles_n;
     KPartition best{1, 0};
     double best_cost = 1e30;
     for (int s = 1; s <= kMaxSplitsNarrow; ++s) {
         const int per = (ktiles + s - 1) / s;
-        if (s > 1 && per < 8) break;
+        if (s > 1 && per < 4) break;
         const int rounds = (tiles * s + ncu - 1) / ncu;
         const double cost = rounds * (per + 8.0 + (s > 1 ? 8.0 : 0.0)) + (s > 1 ? 0.02 * s * tiles : 0.0);
         if (cost < best_cost - 1e-9) { best_cost = cost; best = KPartition{s, 0}; }
