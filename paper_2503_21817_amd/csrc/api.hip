@@ -290,7 +290,7 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
     // chunk-major, as they are loaded.
     const bool balanced = (flags & SKIPFFN_FLAG_BALANCED_SPLIT) != 0;
     const bool few = !balanced && few_rows(Rb, C, I, saved != nullptr);
-    const bool mid = !balanced && !few && mid_rows(Rb);
+    const bool mid = !balanced && !few && mid_rows(Rb, I, num_cus());
     const bool few_down = few || (mid && few_rows_down(Rb, saved != nullptr));
     const bool chunk_major_xn = few && saved == nullptr, chunk_major_h = few_down && saved == nullptr;
     // (2) gather + RMSNorm
@@ -317,7 +317,8 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
             e = launch_gather_transpose(H, (int)I, nullptr, (int)Rb, r_dev, nullptr, HT, (int)ld_transposed(Rb), s);
             if (e != hipSuccess) return hip_fail(e);
         }
-        const int splits = !few_down ? choose_k_split_narrow(1, (int)((C + 127) / 128), (int)((I + BK - 1) / BK), num_cus()).splits : 0;
+        int splits = choose_k_split_narrow(mid_row_tiles(Rb), (int)((C + 127) / 128), (int)((I + BK - 1) / BK), num_cus()).splits;
+        if (Rb > 256) splits = std::min(splits, kMaxSplits);            // what the workspace holds (fwd_ws)
         profile_mark_begin(KC_GEMM_DOWN, s);
         e = few_down ? launch_few_rows_down(H, (int)Rb, r_dev, (int)C, (int)I, wd, idx, res, static_cast<bf16_t*>(out),
                                             no_residual, chunk_major_h, s)

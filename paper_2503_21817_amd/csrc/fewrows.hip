@@ -13,9 +13,9 @@
 // rows are out of range and cost nothing.  More columns per workgroup (32, 64) would read them less
 // often, but leave fewer workgroups: no faster below 32 rows, up to 60 % slower at C = 2048.
 //
-// Measured at C = 4096, I = 14336, 8 rows: gate/up 48.6 us and down 24.6 us (4.8 TB/s of weights; the loads
-// alone, without activations and epilogue, 44.5 + 21.1), where 128-row tiles with split K took 51 + 4.7 (SwiGLU of
-// the split sums) and 24 + 8.2 (their reduction).
+// Measured at C = 4096, I = 14336, 8 rows: down 24.6 us (4.8 TB/s of weights; the loads alone, without activations and
+// epilogue, 21), where tiles with split K take 25.8 + 5.5 for the reduction; gate/up 48.6, slower than the tiles of
+// midrows.hip (42), which read the activations once per 64 columns.  Which layers and row counts come here: layout.hpp.
 #include "kernels.hpp"
 
 namespace skipffn {

@@ -71,8 +71,14 @@ inline KPartition choose_k_partition(int tiles_m, int tiles_n, int ktiles, bool 
 // rows and 128 weight rows (midrows.hip), the down GEMM with its K range split into fp32 slabs.  Layer forward, us,
 // against 128-row tiles that shared the weights through L2:  C = 4096: 64 rows 77 / 104, 184 rows 102 / 117,
 // 256 rows 117 / 128;  C = 3072: 128 rows 70 / 76;  C = 2048: 128 rows 49 / 56;  C = 1024: 128 rows 30 / 38.
-// Beyond 256 rows a second row of tiles would stream the weights again: 256-row tiles of the general core.
-inline bool mid_rows(int64_t rows) { return rows <= 256; }
+// Beyond 256 rows a second row of tiles reads the weights again, from L2, and pays where it finds idle CUs: a narrow
+// layer whose gate/up tiles all fit on the chip at once (the general core gives such a layer a few dozen 256-row
+// tiles).  C = 2048: 300 rows 55 / 79, 512 rows 67 / 86;  C = 1024: 300 rows 34 / 51, 1024 rows 47 / 58;  C = 256: 1024 rows
+// 30 / 41;  C = 3072, I = 8192: 512 rows 105 / 112.  One tile more than the chip holds (1500 rows, C = 1024) is even.
+inline int mid_row_tiles(int64_t rows) { return (int)((rows + 255) / 256); }
+inline bool mid_rows(int64_t rows, int64_t I, int ncu) {
+    return rows <= 256 || mid_row_tiles(rows) * ((I + 63) / 64) <= ncu;
+}
 // plain split-K: fill the CUs, keep at least 4 slabs per workgroup (see choose_k_partition)
 inline KPartition choose_k_split_narrow(int tiles_m, int tiles_n, int ktiles, int ncu) {
     const int tiles = tiles_m * tiles_n;

@@ -1,4 +1,5 @@
-// The two forward GEMMs for up to 256 retained rows (decode batches, prefill of an image, small training batches).
+// The two forward GEMMs for up to 256 retained rows (decode batches, prefill of an image, small training batches), and
+// for more rows of a narrow layer, in several row tiles.
 //
 // Bound by streaming the weights from HBM.  A tile is ALL rows (16 * MT of them) times 128 weight rows, so that every
 // weight byte goes to one CU only and the tiles are many (I / 64 for gate/up; C / 128 with K split for down, whose
@@ -22,7 +23,7 @@ namespace skipffn {
 constexpr int MID_CHANNEL_K = 4096;           // rows this many k apart share their L2 channels
 
 struct MidRowsArgs {
-    int rows; const int32_t* r_dev;           // row bound (<= 16 * MT), optional device count
+    int rows; const int32_t* r_dev;           // row bound, optional device count
     int N, K;                                 // output columns, contraction length (multiples of 8)
     const bf16_t* A; uint32_t a_bytes;        // [rows][K]
     const bf16_t* B0; const bf16_t* B1; uint32_t b_bytes;   // [N][K]; gate/up: W_gate, W_up
@@ -41,15 +42,20 @@ __global__ __launch_bounds__(SLAB_THREADS) void mid_rows_kernel(MidRowsArgs P) {
     const int wm = wave >> 2, wn = wave & 3;  // row group, column quarter
     const int R = effective_rows(P.rows, P.r_dev);
     if (R <= 0) return;                       // uniform
-    const int z = (int)blockIdx.x % P.splits;
-    const int n0 = ((int)blockIdx.x / P.splits) * (GATE_UP ? SLAB_B_ROWS / 2 : SLAB_B_ROWS);
+    // row tile by row tile, in each the column tiles, in each the K splits
+    constexpr int COLS = GATE_UP ? SLAB_B_ROWS / 2 : SLAB_B_ROWS;
+    const int per_m = (P.N + COLS - 1) / COLS * P.splits;
+    const int tm = (int)blockIdx.x / per_m, b = (int)blockIdx.x - tm * per_m;
+    const int z = b % P.splits;
+    const int m0 = tm * 16 * MT, n0 = b / P.splits * COLS;
+    if (m0 >= R) return;                      // uniform: the bound of a device count
     const int r16 = lane & 15, kq = lane >> 4;
 
     const int ktiles = (P.K + BK - 1) / BK, per = (ktiles + P.splits - 1) / P.splits;
     const int kt0 = z * per, kt1 = kt0 + per < ktiles ? kt0 + per : ktiles;
     const int nk = kt1 > kt0 ? kt1 - kt0 : 0;
     // where in its K range the workgroup starts (blocks b, b + 8, ... share an XCD); see the note above
-    const int rot = nk > 0 && P.K % MID_CHANNEL_K == 0 ? (int)(((blockIdx.x >> 3) * 2) % (unsigned)nk) : 0;
+    const int rot = nk > 0 && P.K % MID_CHANNEL_K == 0 ? (b >> 3) * 2 % nk : 0;
 
     const __amdgpu_buffer_rsrc_t ra = make_rsrc(P.A, P.a_bytes),
                                  rb = make_rsrc(GATE_UP && wave >= 4 ? P.B1 : P.B0, P.b_bytes);
@@ -60,7 +66,7 @@ __global__ __launch_bounds__(SLAB_THREADS) void mid_rows_kernel(MidRowsArgs P) {
     for (int l = 0; l < NL; ++l) {
         const int q = l < NLA ? wave * NLA + l : wave * 2 + (l - NLA);
         const int row = 8 * q + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
-        const int gr = l < NLA ? row : n0 + (GATE_UP ? row & 63 : row);
+        const int gr = l < NLA ? m0 + row : n0 + (GATE_UP ? row & 63 : row);
         const bool in = l < NLA ? gr < R : gr < P.N;
         goff[l] = in ? (uint32_t)(((int64_t)gr * P.K + c * 8) * 2) : kOobOffset;
     }
@@ -69,7 +75,7 @@ __global__ __launch_bounds__(SLAB_THREADS) void mid_rows_kernel(MidRowsArgs P) {
 
 #pragma unroll
     for (int m = 0; m < MI; ++m) {
-        const int row = (wm * MI + m) * 16 + r16;
+        const int row = m0 + (wm * MI + m) * 16 + r16;
         if (row >= R) continue;
         if (GATE_UP) {
             const int n = n0 + wn * 16 + 4 * kq;
@@ -97,18 +103,21 @@ __global__ __launch_bounds__(SLAB_THREADS) void mid_rows_kernel(MidRowsArgs P) {
 
 template <int MT, bool GATE_UP>
 static hipError_t launch_mid(const MidRowsArgs& a, hipStream_t s) {
-    const unsigned tiles = (unsigned)((a.N + (GATE_UP ? 63 : 127)) / (GATE_UP ? 64 : 128));
-    hipLaunchKernelGGL((mid_rows_kernel<MT, GATE_UP>), dim3(tiles * (unsigned)a.splits), dim3(SLAB_THREADS), kSlabLds<16 * MT>, s, a);
+    const int tiles_m = (a.rows + 16 * MT - 1) / (16 * MT), cols = GATE_UP ? SLAB_B_ROWS / 2 : SLAB_B_ROWS;
+    const int tiles_n = (a.N + cols - 1) / cols;
+    hipLaunchKernelGGL((mid_rows_kernel<MT, GATE_UP>), dim3((unsigned)(tiles_m * tiles_n * a.splits)), dim3(SLAB_THREADS),
+                       kSlabLds<16 * MT>, s, a);
     return hipGetLastError();
 }
 template <bool GATE_UP>
 static hipError_t launch_mid_rows(const MidRowsArgs& a, hipStream_t s) {
     if (a.rows <= 0 || a.N <= 0) return hipSuccess;
-    if (a.rows <= 64) return launch_mid<4, GATE_UP>(a, s);
-    if (a.rows <= 128) return launch_mid<8, GATE_UP>(a, s);
-    if (a.rows <= 192) return launch_mid<12, GATE_UP>(a, s);
-    if (a.rows <= 256) return launch_mid<16, GATE_UP>(a, s);
-    return hipErrorInvalidValue;
+    // as few row tiles as 256 rows allow, and those no taller than they have to be
+    const int tiles_m = mid_row_tiles(a.rows), per = (a.rows + tiles_m - 1) / tiles_m;
+    if (per <= 64) return launch_mid<4, GATE_UP>(a, s);
+    if (per <= 128) return launch_mid<8, GATE_UP>(a, s);
+    if (per <= 192) return launch_mid<12, GATE_UP>(a, s);
+    return launch_mid<16, GATE_UP>(a, s);
 }
 
 template <int MT, bool GATE_UP>

@@ -567,8 +567,9 @@ def test_last_tile_row_of_at_most_128_rows(R):
 @pytest.mark.parametrize("R,T", [(1, 2400), (100, 2400), (256, 2400), (257, 2400), (640, 2944), (700, 4400)])
 def test_device_row_count_far_below_the_bound(R, T):
     """The tile map is laid over the effective rows: the bound has 10 to 18 tile rows (two or three panels),
-    of which one to three are live - with a last row of at most 128 rows, a full one, or one in between."""
-    w = W.small(C=520, I=1368, visual=(T - 1,), text=(1,), keep=(R - 1,), seed=4000 + R)
+    of which one to three are live - with a last row of at most 128 rows, a full one, or one in between.  The layer is
+    wide enough for the 256-row tiles at this bound."""
+    w = W.small(C=520, I=2056, visual=(T - 1,), text=(1,), keep=(R - 1,), seed=4000 + R)
     print(f"device count R={R} bound T={T}", flush=True)
     p = Problem(w, unit_gain=True, with_gain_tensor=False)
     out, bufs = gpu_forward(p, R_host=False)
@@ -617,10 +618,11 @@ def test_weights_streamed_to_registers(R, C, I, r_host):
 
 
 @pytest.mark.parametrize("R,C,I", [(41, 2056, 7176), (64, 2048, 7168), (65, 264, 328), (128, 640, 1664), (129, 640, 1664),
-                                   (192, 264, 328), (193, 136, 2056), (256, 640, 1664)])
+                                   (192, 264, 328), (193, 136, 2056), (256, 640, 1664), (257, 264, 328), (385, 640, 1664),
+                                   (640, 264, 1000)])
 @pytest.mark.parametrize("r_host", [True, False], ids=["R-host", "R-device"])
 def test_tiles_of_all_rows(R, C, I, r_host):
-    """Up to 256 rows in one tile of 64, 128, 192 or 256: K ranges of a few slabs (fewer than the ring holds), ragged ones,
+    """Up to 256 rows in one tile of 64, 128, 192 or 256, more in several (the last one cut off): K ranges of a few slabs (fewer than the ring holds), ragged ones,
     whole ones (workgroups start at different slabs), one split and several, column tiles that are cut off."""
     from helpers import max_slice_rel_l2
     w = W.small(C=C, I=I, visual=(R + (0 if r_host is False else 23),), text=(1,), keep=(R - 1,), seed=6000 + R,
