@@ -219,7 +219,7 @@ int skipffn_saved_layout(int64_t R_max, int64_t C, int64_t I, size_t* offsets) {
 }
 size_t skipffn_forward_workspace_bytes(int64_t R_max, int64_t C, int64_t I, int has_saved) {
     if (R_max < 0 || C <= 0 || I <= 0) return 0;
-    return fwd_ws(R_max, C, I, has_saved != 0, num_cus()).total + 256;
+    return fwd_ws(R_max, C, I, has_saved != 0).total + 256;
 }
 size_t skipffn_backward_workspace_bytes(int64_t R_max, int64_t C, int64_t I) {
     if (R_max < 0 || C <= 0 || I <= 0) return 0;
@@ -246,13 +246,13 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
     if (Rb > 0) {
         if (idx == nullptr || (reinterpret_cast<uintptr_t>(idx) & 3u)) return SKIPFFN_EINVAL;
         if (bad_ptr(w_gate) || bad_ptr(w_up) || bad_ptr(w_down)) return SKIPFFN_EINVAL;
-        FwdWs W = fwd_ws(Rb, C, I, saved != nullptr, num_cus());
+        FwdWs W = fwd_ws(Rb, C, I, saved != nullptr);
         if (workspace == nullptr || !aligned16(workspace)) return SKIPFFN_EWORKSPACE;
         if (workspace_bytes < W.total) return SKIPFFN_EWORKSPACE;
     }
     if (T == 0) return SKIPFFN_OK;
     if ((flags & SKIPFFN_FLAG_VALIDATE_IDX) && Rb > 0) {
-        st = validate_idx_now(idx, Rb, r_dev, T, static_cast<char*>(workspace) + fwd_ws(Rb, C, I, saved != nullptr, num_cus()).status, s);
+        st = validate_idx_now(idx, Rb, r_dev, T, static_cast<char*>(workspace) + fwd_ws(Rb, C, I, saved != nullptr).status, s);
         if (st != SKIPFFN_OK) return st;
     }
 
@@ -264,7 +264,7 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
     if (Rb == 0) return SKIPFFN_OK;
     if ((e = ensure_gemm_init()) != hipSuccess) return hip_fail(e);
 
-    FwdWs W = fwd_ws(Rb, C, I, saved != nullptr, num_cus());
+    FwdWs W = fwd_ws(Rb, C, I, saved != nullptr);
     char* ws = static_cast<char*>(workspace);
     bf16_t *xrows = nullptr, *xn, *xnT = nullptr, *G = nullptr, *U = nullptr, *H, *HT = nullptr;
     float* rstd;
@@ -288,11 +288,8 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
 
     // which GEMMs: see layout.hpp.  Without a saved buffer (whose layout is the caller's to read) a handful of rows lie
     // chunk-major, as they are loaded.
-    const bool balanced = (flags & SKIPFFN_FLAG_BALANCED_SPLIT) != 0;
-    const bool few = !balanced && few_rows(Rb, C, I, saved != nullptr);
-    const bool mid = !balanced && !few && mid_rows(Rb, I, num_cus());
-    const bool few_down = few || (mid && few_rows_down(Rb, saved != nullptr));
-    const bool chunk_major_xn = few && saved == nullptr, chunk_major_h = few_down && saved == nullptr;
+    const ForwardPlan plan = plan_forward(Rb, C, I, saved != nullptr, (flags & SKIPFFN_FLAG_BALANCED_SPLIT) != 0, num_cus());
+    const bool chunk_major_xn = plan.gate_up == FWD_FEW && saved == nullptr, chunk_major_h = plan.down == FWD_FEW && saved == nullptr;
     // (2) gather + RMSNorm
     e = launch_gather_rmsnorm(static_cast<const bf16_t*>(hidden), idx, (int)Rb, r_dev, (int)C, eps,
                               static_cast<const bf16_t*>(rms_gain), xrows, xn, rstd, chunk_major_xn, s);
@@ -303,12 +300,14 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
         if (e != hipSuccess) return hip_fail(e);
     }
 
-    if (few || mid) {
+    if (plan.gate_up != FWD_CORE) {
         const bf16_t *wg = static_cast<const bf16_t*>(w_gate), *wu = static_cast<const bf16_t*>(w_up);
         const bf16_t *wd = static_cast<const bf16_t*>(w_down), *res = static_cast<const bf16_t*>(hidden);
         const int no_residual = (flags & SKIPFFN_FLAG_NO_RESIDUAL) ? 1 : 0;
+        const int splits = plan.k_down.splits;
         profile_mark_begin(KC_GEMM_GATE_UP, s);
-        e = few ? launch_few_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_xn, s)
+        e = plan.gate_up == FWD_FEW
+                ? launch_few_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_xn, s)
                 : launch_mid_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_h, s);
         profile_mark_end(KC_GEMM_GATE_UP, s);
         if (e != hipSuccess) return hip_fail(e);
@@ -317,14 +316,13 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
             e = launch_gather_transpose(H, (int)I, nullptr, (int)Rb, r_dev, nullptr, HT, (int)ld_transposed(Rb), s);
             if (e != hipSuccess) return hip_fail(e);
         }
-        int splits = choose_k_split_narrow(mid_row_tiles(Rb), (int)((C + 127) / 128), (int)((I + BK - 1) / BK), num_cus()).splits;
-        if (Rb > 256) splits = std::min(splits, kMaxSplits);            // what the workspace holds (fwd_ws)
         profile_mark_begin(KC_GEMM_DOWN, s);
-        e = few_down ? launch_few_rows_down(H, (int)Rb, r_dev, (int)C, (int)I, wd, idx, res, static_cast<bf16_t*>(out),
-                                            no_residual, chunk_major_h, s)
-                     : launch_mid_rows_down(H, (int)Rb, r_dev, (int)C, (int)I, wd, splits, partial, s);
+        e = plan.down == FWD_FEW
+                ? launch_few_rows_down(H, (int)Rb, r_dev, (int)C, (int)I, wd, idx, res, static_cast<bf16_t*>(out), no_residual,
+                                       chunk_major_h, s)
+                : launch_mid_rows_down(H, (int)Rb, r_dev, (int)C, (int)I, wd, splits, partial, s);
         profile_mark_end(KC_GEMM_DOWN, s);
-        if (e == hipSuccess && !few_down)
+        if (e == hipSuccess && plan.down == FWD_MID)
             e = launch_resid_scatter(partial, PartialLayout{splits, 0, 0}, (int)Rb, r_dev, (int)C, idx, res,
                                      static_cast<bf16_t*>(out), no_residual, s);
         return e == hipSuccess ? SKIPFFN_OK : hip_fail(e);
@@ -353,9 +351,8 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
         a.A0 = H; a.lda = (int)I; a.a_bytes = (uint32_t)(Rb * I * 2);
         a.B0 = static_cast<const bf16_t*>(w_down); a.ldb = (int)I; a.b_bytes = (uint32_t)(C * I * 2);
         a.pairs = 1;
-        const int tiles_m = (int)((Rb + BM - 1) / BM), tiles_n = (int)((C + BN - 1) / BN);
         const int ktiles = (int)((I + BK - 1) / BK);
-        const KPartition kp = choose_k_partition(tiles_m, tiles_n, ktiles, balanced, num_cus());
+        const KPartition kp = plan.k_down;
         a.splits = kp.splits;
         a.idx = idx; a.ldo = (int)C;
         a.no_residual = (flags & SKIPFFN_FLAG_NO_RESIDUAL) ? 1 : 0;

@@ -79,17 +79,18 @@ inline int mid_row_tiles(int64_t rows) { return (int)((rows + 255) / 256); }
 inline bool mid_rows(int64_t rows, int64_t I, int ncu) {
     return rows <= 256 || mid_row_tiles(rows) * ((I + 63) / 64) <= ncu;
 }
-// plain split-K: fill the CUs, keep at least 4 slabs per workgroup (see choose_k_partition)
-inline KPartition choose_k_split_narrow(int tiles_m, int tiles_n, int ktiles, int ncu) {
-    const int tiles = tiles_m * tiles_n;
-    KPartition best{1, 0};
+// plain split-K into at most max_splits slabs: fill the CUs, keep at least 4 K slabs per workgroup (see
+// choose_k_partition).  max_splits bounds the search itself: 33 K slabs cut for 9 splits and then held to 8 would
+// leave the eighth without any, where the search up to 8 takes 7 splits of 5.
+inline int choose_k_split(int tiles, int ktiles, int max_splits, int ncu) {
+    int best = 1;
     double best_cost = 1e30;
-    for (int s = 1; s <= kMaxSplitsNarrow; ++s) {
+    for (int s = 1; s <= max_splits; ++s) {
         const int per = (ktiles + s - 1) / s;
         if (s > 1 && per < 4) break;
         const int rounds = (tiles * s + ncu - 1) / ncu;
         const double cost = rounds * (per + 8.0 + (s > 1 ? 8.0 : 0.0)) + (s > 1 ? 0.02 * s * tiles : 0.0);
-        if (cost < best_cost - 1e-9) { best_cost = cost; best = KPartition{s, 0}; }
+        if (cost < best_cost - 1e-9) { best_cost = cost; best = s; }
     }
     return best;
 }
@@ -110,10 +111,28 @@ inline bool few_rows(int64_t rows, int64_t C, int64_t I, bool has_saved) {
 // sums and the residual in one launch, 24.6 us at 8 rows and C = 4096 where the tiles take 25.8 and their reduction 5.5.
 inline bool few_rows_down(int64_t rows, bool has_saved) { return rows <= 16 && !has_saved; }
 
-// The gate/up GEMM is not split along K: with 64 columns of each weight per workgroup it has enough workgroups, and
-// its epilogue needs complete sums.
-inline int gate_up_splits(int64_t, int64_t, int64_t, int) { return 0; }
-inline size_t gate_up_partial_bytes(int64_t, int64_t, int64_t, int) { return 0; }
+// Which kernels a forward call launches.
+enum FwdKernel { FWD_FEW, FWD_MID, FWD_CORE };           // fewrows.hip, midrows.hip, gemm.hpp
+struct ForwardPlan {
+    FwdKernel gate_up, down;
+    KPartition k_down;                                   // FWD_MID: plain split; FWD_CORE: as choose_k_partition; FWD_FEW: none
+};
+// most fp32 slabs the down GEMM of `rows` rows may write (fwd_ws has room for them)
+inline int max_down_splits(int64_t rows) { return rows <= 256 ? kMaxSplitsNarrow : kMaxSplits; }
+inline ForwardPlan plan_forward(int64_t rows, int64_t C, int64_t I, bool has_saved, bool balanced, int ncu) {
+    ForwardPlan p{FWD_CORE, FWD_CORE, KPartition{1, 0}};
+    if (!balanced && few_rows(rows, C, I, has_saved)) p.gate_up = p.down = FWD_FEW;
+    else if (!balanced && mid_rows(rows, I, ncu)) {
+        p.gate_up = FWD_MID;
+        p.down = few_rows_down(rows, has_saved) ? FWD_FEW : FWD_MID;
+    }
+    const int ktiles = (int)((I + BK - 1) / BK);
+    if (p.down == FWD_MID)
+        p.k_down.splits = choose_k_split(mid_row_tiles(rows) * (int)((C + 127) / 128), ktiles, max_down_splits(rows), ncu);
+    if (p.down == FWD_CORE)
+        p.k_down = choose_k_partition((int)((rows + BM - 1) / BM), (int)((C + BN - 1) / BN), ktiles, balanced, ncu);
+    return p;
+}
 
 // Leading dimension of the transposed copies ([columns][rows]): rows rounded up to 64 elements, so that every
 // row of a copy starts on a 128-byte line (with a multiple of 8 only, each 128-byte piece the GEMMs load
@@ -136,8 +155,8 @@ inline SavedLayout saved_layout(int64_t R, int64_t C, int64_t I) {
     return L;
 }
 
-struct FwdWs { size_t xn, rstd, h, partial, gu_partial, status, total; };
-inline FwdWs fwd_ws(int64_t R, int64_t C, int64_t I, bool has_saved, int ncu) {
+struct FwdWs { size_t xn, rstd, h, partial, status, total; };
+inline FwdWs fwd_ws(int64_t R, int64_t C, int64_t I, bool has_saved) {
     FwdWs w; size_t o = 0;
     w.xn = o;   if (!has_saved) o += align_up((size_t)R * C * 2);
     w.rstd = o; if (!has_saved) o += align_up((size_t)R * 4);
@@ -145,7 +164,6 @@ inline FwdWs fwd_ws(int64_t R, int64_t C, int64_t I, bool has_saved, int ncu) {
     // a buffer sized for R_max rows must do for every smaller count: up to 256 rows may use more slabs
     const size_t slab_rows = std::max<size_t>((size_t)kMaxSplits * R, (size_t)kMaxSplitsNarrow * std::min<int64_t>(R, 256));
     w.partial = o; o += align_up(slab_rows * C * 4);
-    w.gu_partial = o; o += align_up(gate_up_partial_bytes(R, C, I, ncu));
     w.status = o; o += 256;              // verdict of SKIPFFN_FLAG_VALIDATE_IDX
     w.total = o;
     return w;

@@ -1,8 +1,8 @@
 // Host check of the buffer carving and K-split planning (csrc/layout.hpp), meant to be built with
 // -fsanitize=address,undefined: every section of `saved` and of the two workspaces is 256-byte
 // aligned, the sections are disjoint, in order and large enough for what the kernels put there,
-// totals never decrease as the row bound grows, and every K partition the planner picks stays
-// within the partial-slab budget the workspaces are sized for.  A byte map of each buffer is
+// totals never decrease as the row bound grows, and every K partition the planner picks - for a forward
+// call the very plan it launches - stays within the partial-slab budget the workspaces are sized for.  A byte map of each buffer is
 // painted section by section, so an overlap or an overrun is also a sanitizer report.
 // Prints "ok <cases>" or the first violation.
 #include <cstdio>
@@ -25,6 +25,31 @@ static bool paint(std::vector<unsigned char>& map, size_t off, size_t bytes, siz
         map[i] = 1;
     }
     return true;
+}
+
+// what is wrong with the forward plan, or null
+static const char* check_plan(long R, long C, long I, bool hs, bool balanced, int ncu) {
+    const ForwardPlan p = plan_forward(R, C, I, hs, balanced, ncu);
+    const FwdWs W = fwd_ws(R, C, I, hs);
+    const size_t room = W.status - W.partial, slab = (size_t)R * C * 4;
+    const int ktiles = (int)((I + BK - 1) / BK);
+    if (balanced && (p.gate_up != FWD_CORE || p.down != FWD_CORE)) return "the balanced split is the core's";
+    if (p.down == FWD_FEW) return R <= kFewRowsMax && !(p.gate_up == FWD_CORE) ? nullptr : "too many rows for the register path";
+    if (p.down == FWD_MID) {
+        if (p.k_down.splits < 1 || p.k_down.sk_nbg != 0) return "split of the tiles of all rows";
+        if (p.k_down.splits * slab > room) return "the slabs of the tiles of all rows do not fit";
+        const int per = (ktiles + p.k_down.splits - 1) / p.k_down.splits;
+        if ((p.k_down.splits - 1) * per >= ktiles) return "an empty split";
+        return nullptr;
+    }
+    const int tiles_m = (int)((R + BM - 1) / BM), tiles_n = (int)((C + BN - 1) / BN);
+    if (p.k_down.sk_nbg > 0) {
+        const StreamKPlan sk = streamk_plan(tiles_m, ktiles, p.k_down.sk_nbg);
+        if (p.k_down.sk_nbg * tiles_n > ncu) return "balanced split larger than the chip";
+        for (int i = 0; i < tiles_m; ++i)
+            if (streamk_count(sk, i) * slab > room) return "the slabs of the balanced split do not fit";
+    } else if (p.k_down.splits > 1 && p.k_down.splits * slab > room) return "the slabs of the core do not fit";
+    return nullptr;
 }
 
 int main() {
@@ -54,13 +79,13 @@ int main() {
                     prev_sv = L.total;
                     // ---- forward workspace, with and without a saved buffer
                     for (int hs = 0; hs < 2; ++hs) {
-                        const FwdWs W = fwd_ws(R, C, I, hs != 0, ncu);
+                        const FwdWs W = fwd_ws(R, C, I, hs != 0);
                         std::vector<unsigned char> m2(W.total / unit + 2, 0);
                         const size_t slab_rows = std::max<size_t>((size_t)kMaxSplits * R, (size_t)kMaxSplitsNarrow * std::min<long>(R, 256));
-                        const size_t offs[6] = {W.xn, W.rstd, W.h, W.partial, W.gu_partial, W.status};
-                        const size_t sz[6] = {hs ? 0 : (size_t)R * C * 2, hs ? 0 : (size_t)R * 4, hs ? 0 : (size_t)R * I * 2,
-                                              slab_rows * C * 4, gate_up_partial_bytes(R, C, I, ncu), 8};
-                        for (int k = 0; k < 6; ++k) {
+                        const size_t offs[5] = {W.xn, W.rstd, W.h, W.partial, W.status};
+                        const size_t sz[5] = {hs ? 0 : (size_t)R * C * 2, hs ? 0 : (size_t)R * 4, hs ? 0 : (size_t)R * I * 2,
+                                              slab_rows * C * 4, 8};
+                        for (int k = 0; k < 5; ++k) {
                             if (offs[k] % 256) return fail("forward workspace section not aligned", R, C, I, ncu);
                             if (offs[k] + sz[k] > W.total) return fail("forward workspace section past the end", R, C, I, ncu);
                             if (!paint(m2, offs[k], sz[k], unit)) return fail("forward workspace sections overlap", R, C, I, ncu);
@@ -99,17 +124,20 @@ int main() {
                                         if (streamk_count(p, i) > kMaxSplits) return fail("more partial slabs than the workspace holds", R, C, I, ncu);
                                 }
                             }
-                        if (R <= 256) {
-                            const int tiles_m = (int)((R + BM / 2 - 1) / (BM / 2)), ktiles = (int)((I + BK - 1) / BK);
-                            const KPartition kp = choose_k_split_narrow(tiles_m, tiles_n, ktiles, ncu);
-                            if (kp.splits < 1 || kp.splits > kMaxSplitsNarrow || kp.sk_nbg != 0) return fail("narrow split out of range", R, C, I, ncu);
-                        }
-                        const int gs = gate_up_splits(R, C, I, ncu);
-                        if (gs < 0 || gs == 1 || gs > 4 || (R > BM / 2 && gs != 0)) return fail("gate/up split out of range", R, C, I, ncu);
                     }
                     ++cases;
                 }
             }
+    // the plan that a forward call launches: widths in both orders
+    const long widths[] = {8, 64, 256, 264, 512, 688, 1024, 2048, 2112, 4096, 7168, 8192, 14336, 32768};
+    for (int ncu : ncus)
+        for (long C : widths)
+            for (long I : widths)
+                for (long R = 1; R <= 16384; R += R < 300 ? 1 : R / 16)
+                    for (int variant = 0; variant < 4; ++variant) {
+                        if (const char* what = check_plan(R, C, I, variant & 1, variant & 2, ncu)) return fail(what, R, C, I, ncu);
+                        ++cases;
+                    }
     printf("ok %ld\n", cases);
     return 0;
 }
