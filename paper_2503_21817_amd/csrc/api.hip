@@ -219,7 +219,7 @@ int skipffn_saved_layout(int64_t R_max, int64_t C, int64_t I, size_t* offsets) {
 }
 size_t skipffn_forward_workspace_bytes(int64_t R_max, int64_t C, int64_t I, int has_saved) {
     if (R_max < 0 || C <= 0 || I <= 0) return 0;
-    return fwd_ws(R_max, C, I, has_saved != 0).total + 256;
+    return fwd_ws(R_max, C, I, has_saved != 0, num_cus()).total + 256;
 }
 size_t skipffn_backward_workspace_bytes(int64_t R_max, int64_t C, int64_t I) {
     if (R_max < 0 || C <= 0 || I <= 0) return 0;
@@ -246,13 +246,13 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
     if (Rb > 0) {
         if (idx == nullptr || (reinterpret_cast<uintptr_t>(idx) & 3u)) return SKIPFFN_EINVAL;
         if (bad_ptr(w_gate) || bad_ptr(w_up) || bad_ptr(w_down)) return SKIPFFN_EINVAL;
-        FwdWs W = fwd_ws(Rb, C, I, saved != nullptr);
+        FwdWs W = fwd_ws(Rb, C, I, saved != nullptr, num_cus());
         if (workspace == nullptr || !aligned16(workspace)) return SKIPFFN_EWORKSPACE;
         if (workspace_bytes < W.total) return SKIPFFN_EWORKSPACE;
     }
     if (T == 0) return SKIPFFN_OK;
     if ((flags & SKIPFFN_FLAG_VALIDATE_IDX) && Rb > 0) {
-        st = validate_idx_now(idx, Rb, r_dev, T, static_cast<char*>(workspace) + fwd_ws(Rb, C, I, saved != nullptr).status, s);
+        st = validate_idx_now(idx, Rb, r_dev, T, static_cast<char*>(workspace) + fwd_ws(Rb, C, I, saved != nullptr, num_cus()).status, s);
         if (st != SKIPFFN_OK) return st;
     }
 
@@ -264,7 +264,7 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
     if (Rb == 0) return SKIPFFN_OK;
     if ((e = ensure_gemm_init()) != hipSuccess) return hip_fail(e);
 
-    FwdWs W = fwd_ws(Rb, C, I, saved != nullptr);
+    FwdWs W = fwd_ws(Rb, C, I, saved != nullptr, num_cus());
     char* ws = static_cast<char*>(workspace);
     bf16_t *xrows = nullptr, *xn, *xnT = nullptr, *G = nullptr, *U = nullptr, *H, *HT = nullptr;
     float* rstd;
@@ -308,7 +308,8 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
         profile_mark_begin(KC_GEMM_GATE_UP, s);
         e = plan.gate_up == FWD_FEW
                 ? launch_few_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_xn, s)
-                : launch_mid_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_h, s);
+                : launch_mid_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_h,
+                                          plan.gate_up_splits, partial, s);
         profile_mark_end(KC_GEMM_GATE_UP, s);
         if (e != hipSuccess) return hip_fail(e);
         // the K-contiguous copy of H for the dW_down GEMM comes from a copy kernel

@@ -111,19 +111,42 @@ inline bool few_rows(int64_t rows, int64_t C, int64_t I, bool has_saved) {
 // sums and the residual in one launch, 24.6 us at 8 rows and C = 4096 where the tiles take 25.8 and their reduction 5.5.
 inline bool few_rows_down(int64_t rows, bool has_saved) { return rows <= 16 && !has_saved; }
 
+// The gate/up GEMM has I / 64 workgroups a row tile, each walking the whole K range: a layer of small I leaves most of
+// the chip idle for C / 64 slabs.  Where three fifths or more of it would be idle, up to 256 rows split K as well; the SwiGLU
+// then waits for a reducing kernel, which costs about 16 slabs' time and the traffic of the fp32 sums.  Layer forward, us,
+// split / whole:  C = 8192, I = 512: 16 rows 29 / 61, 128 rows 40 / 88;  C = 4096, I = 2048: 64 rows 36 / 49, 128 rows
+// 45 / 59;  C = 4096, I = 4096: 256 rows 61 / 82;  C = 16384, I = 512: 64 rows 41 / 124;  C = 8192, I = 6400: 128 rows
+// 99 / 115.  Past the line:  C = 8192, I = 8192 (half the chip idle): 128 rows 133 / 128;  C = 1024, I = 2048 (16
+// slabs): 256 rows 42 / 35.
+inline int gate_up_splits(int64_t C, int64_t I, int ncu) {
+    const int tiles = (int)((I + 63) / 64), ktiles = (int)((C + BK - 1) / BK);
+    if (tiles * 5 > 2 * ncu) return 1;
+    int best = 1;
+    double best_cost = ktiles + 8.0;
+    for (int s = 2; s <= kMaxSplitsNarrow && s * tiles <= ncu; ++s) {
+        const int per = (ktiles + s - 1) / s;
+        if (per < 4) break;
+        const double cost = per + 8.0 + 8.0 + 0.08 * s * tiles;
+        if (cost < best_cost - 1e-9) { best_cost = cost; best = s; }
+    }
+    return best;
+}
+
 // Which kernels a forward call launches.
 enum FwdKernel { FWD_FEW, FWD_MID, FWD_CORE };           // fewrows.hip, midrows.hip, gemm.hpp
 struct ForwardPlan {
     FwdKernel gate_up, down;
+    int gate_up_splits;                                  // FWD_MID
     KPartition k_down;                                   // FWD_MID: plain split; FWD_CORE: as choose_k_partition; FWD_FEW: none
 };
 // most fp32 slabs the down GEMM of `rows` rows may write (fwd_ws has room for them)
 inline int max_down_splits(int64_t rows) { return rows <= 256 ? kMaxSplitsNarrow : kMaxSplits; }
 inline ForwardPlan plan_forward(int64_t rows, int64_t C, int64_t I, bool has_saved, bool balanced, int ncu) {
-    ForwardPlan p{FWD_CORE, FWD_CORE, KPartition{1, 0}};
+    ForwardPlan p{FWD_CORE, FWD_CORE, 1, KPartition{1, 0}};
     if (!balanced && few_rows(rows, C, I, has_saved)) p.gate_up = p.down = FWD_FEW;
     else if (!balanced && mid_rows(rows, I, ncu)) {
         p.gate_up = FWD_MID;
+        if (rows <= 256) p.gate_up_splits = gate_up_splits(C, I, ncu);
         p.down = few_rows_down(rows, has_saved) ? FWD_FEW : FWD_MID;
     }
     const int ktiles = (int)((I + BK - 1) / BK);
@@ -156,14 +179,15 @@ inline SavedLayout saved_layout(int64_t R, int64_t C, int64_t I) {
 }
 
 struct FwdWs { size_t xn, rstd, h, partial, status, total; };
-inline FwdWs fwd_ws(int64_t R, int64_t C, int64_t I, bool has_saved) {
+inline FwdWs fwd_ws(int64_t R, int64_t C, int64_t I, bool has_saved, int ncu) {
     FwdWs w; size_t o = 0;
     w.xn = o;   if (!has_saved) o += align_up((size_t)R * C * 2);
     w.rstd = o; if (!has_saved) o += align_up((size_t)R * 4);
     w.h = o;    if (!has_saved) o += align_up((size_t)R * I * 2);
     // a buffer sized for R_max rows must do for every smaller count: up to 256 rows may use more slabs
     const size_t slab_rows = std::max<size_t>((size_t)kMaxSplits * R, (size_t)kMaxSplitsNarrow * std::min<int64_t>(R, 256));
-    w.partial = o; o += align_up(slab_rows * C * 4);
+    const size_t gate_up_slabs = (size_t)gate_up_splits(C, I, ncu) * std::min<int64_t>(R, 256) * 2 * I;
+    w.partial = o; o += align_up(std::max<size_t>(slab_rows * C, gate_up_slabs) * 4);       // one GEMM after the other
     w.status = o; o += 256;              // verdict of SKIPFFN_FLAG_VALIDATE_IDX
     w.total = o;
     return w;

@@ -3,7 +3,7 @@
 //
 // Bound by streaming the weights from HBM.  A tile is ALL rows (16 * MT of them) times 128 weight rows, so that every
 // weight byte goes to one CU only and the tiles are many (I / 64 for gate/up; C / 128 with K split for down, whose
-// fp32 slabs a reducing kernel adds).  What limits a CU is the bytes its address unit takes, weights and activations
+// fp32 slabs a reducing kernel adds; gate/up splits K as well where I is so small that most CUs would have no tile).  What limits a CU is the bytes its address unit takes, weights and activations
 // together: about 9 TB/s over the chip here.  Hence both operands go to LDS by direct loads of whole 128-byte lines
 // (weights straight to registers, 16 rows x 64 bytes a load: 65 instead of 57 us at 184 rows), and the rows are not
 // padded further than to 64.
@@ -27,10 +27,10 @@ struct MidRowsArgs {
     int N, K;                                 // output columns, contraction length (multiples of 8)
     const bf16_t* A; uint32_t a_bytes;        // [rows][K]
     const bf16_t* B0; const bf16_t* B1; uint32_t b_bytes;   // [N][K]; gate/up: W_gate, W_up
-    int splits;                               // gate/up: 1
+    int splits;
     // gate/up: 16-byte chunk c (8 columns) of row r of H at byte r * h_row + c * h_chunk; G, U [rows][N], optional
     bf16_t* H; uint32_t h_row, h_chunk; bf16_t* G; bf16_t* U;
-    float* partial;                           // down: [splits][rows][N]
+    float* partial;                           // down: [splits][rows][N]; gate/up with splits > 1: [splits][rows][2][N]
 };
 
 template <int MT, bool GATE_UP>
@@ -81,6 +81,12 @@ __global__ __launch_bounds__(SLAB_THREADS) void mid_rows_kernel(MidRowsArgs P) {
             const int n = n0 + wn * 16 + 4 * kq;
             if (n >= P.N) continue;
             const f32x4 g = acc[m][0], u = acc[m][1];
+            if (P.splits > 1) {               // uniform
+                float* p = P.partial + ((int64_t)z * P.rows + row) * 2 * P.N + n;
+                *reinterpret_cast<f32x4*>(p) = g;
+                *reinterpret_cast<f32x4*>(p + P.N) = u;
+                continue;
+            }
             float h[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) h[j] = g[j] * sigmoid_f(g[j]) * u[j];
@@ -98,6 +104,60 @@ __global__ __launch_bounds__(SLAB_THREADS) void mid_rows_kernel(MidRowsArgs P) {
                 if (n < P.N) *reinterpret_cast<f32x4*>(P.partial + ((int64_t)z * P.rows + row) * P.N + n) = acc[m][f];
             }
         }
+    }
+}
+
+// H = silu(sum_z gate) * sum_z up over the slabs of a split gate/up GEMM; one thread per 8 columns of a row, the
+// slabs added in order, two of them in flight.
+constexpr int SWIGLU_THREADS = 256;
+__global__ __launch_bounds__(SWIGLU_THREADS) void swiglu_reduce_kernel(MidRowsArgs P) {
+    const int R = effective_rows(P.rows, P.r_dev), chunks = P.N >> 3;
+    const int64_t gid = (int64_t)blockIdx.x * SWIGLU_THREADS + threadIdx.x;
+    const int r = (int)(gid / chunks), c = (int)(gid - (int64_t)r * chunks);
+    if (r >= R) return;
+    const float* p = P.partial + (int64_t)r * 2 * P.N + c * 8;
+    const int64_t zstride = (int64_t)P.rows * 2 * P.N;
+    float g[8], u[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) g[j] = u[j] = 0.0f;
+    auto load = [&](int z, f32x4 (&v)[4]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            v[q] = *reinterpret_cast<const f32x4*>(p + z * zstride + (q >> 1) * P.N + (q & 1) * 4);
+    };
+    auto add = [&](const f32x4 (&v)[4]) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            g[j] += v[0][j]; g[4 + j] += v[1][j];
+            u[j] += v[2][j]; u[4 + j] += v[3][j];
+        }
+    };
+    int z = 0;
+    for (; z + 2 <= P.splits; z += 2) {
+        f32x4 a[4], b[4];
+        load(z, a);
+        load(z + 1, b);
+        add(a);
+        add(b);
+    }
+    if (z < P.splits) {
+        f32x4 a[4];
+        load(z, a);
+        add(a);
+    }
+    u32x4 h, gb, ub;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const float g0 = g[2 * k], g1 = g[2 * k + 1], u0 = u[2 * k], u1 = u[2 * k + 1];
+        h[k] = pack_bf16x2(g0 * sigmoid_f(g0) * u0, g1 * sigmoid_f(g1) * u1);
+        gb[k] = pack_bf16x2(g0, g1);
+        ub[k] = pack_bf16x2(u0, u1);
+    }
+    *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(P.H) + (uint32_t)r * P.h_row + (uint32_t)c * P.h_chunk) = h;
+    if (P.G != nullptr) {
+        const int64_t o = (int64_t)r * P.N + c * 8;
+        *reinterpret_cast<u32x4*>(P.G + o) = gb;
+        *reinterpret_cast<u32x4*>(P.U + o) = ub;
     }
 }
 
@@ -138,14 +198,20 @@ hipError_t mid_rows_init() {
 }
 
 hipError_t launch_mid_rows_gate_up(const bf16_t* xn, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_gate,
-                                   const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major_h, hipStream_t s) {
+                                   const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major_h, int splits,
+                                   float* partial, hipStream_t s) {
     MidRowsArgs a{};
     a.rows = rows; a.r_dev = r_dev; a.N = I; a.K = C;
     a.A = xn; a.a_bytes = (uint32_t)((int64_t)rows * C * 2);
     a.B0 = w_gate; a.B1 = w_up; a.b_bytes = (uint32_t)((int64_t)I * C * 2);
-    a.splits = 1; a.H = H; a.G = G; a.U = U;
+    a.splits = splits; a.partial = partial; a.H = H; a.G = G; a.U = U;
     a.h_row = chunk_major_h ? 16u : (uint32_t)I * 2; a.h_chunk = chunk_major_h ? (uint32_t)rows * 16 : 16u;
-    return launch_mid_rows<true>(a, s);
+    const hipError_t e = launch_mid_rows<true>(a, s);
+    if (e != hipSuccess || splits <= 1 || rows <= 0) return e;
+    const int64_t threads = (int64_t)rows * (I >> 3);
+    hipLaunchKernelGGL(swiglu_reduce_kernel, dim3((unsigned)((threads + SWIGLU_THREADS - 1) / SWIGLU_THREADS)),
+                       dim3(SWIGLU_THREADS), 0, s, a);
+    return hipGetLastError();
 }
 
 hipError_t launch_mid_rows_down(const bf16_t* H, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_down,

@@ -30,10 +30,19 @@ static bool paint(std::vector<unsigned char>& map, size_t off, size_t bytes, siz
 // what is wrong with the forward plan, or null
 static const char* check_plan(long R, long C, long I, bool hs, bool balanced, int ncu) {
     const ForwardPlan p = plan_forward(R, C, I, hs, balanced, ncu);
-    const FwdWs W = fwd_ws(R, C, I, hs);
+    const FwdWs W = fwd_ws(R, C, I, hs, ncu);
     const size_t room = W.status - W.partial, slab = (size_t)R * C * 4;
     const int ktiles = (int)((I + BK - 1) / BK);
     if (balanced && (p.gate_up != FWD_CORE || p.down != FWD_CORE)) return "the balanced split is the core's";
+    if (p.gate_up_splits != 1) {
+        const int kt = (int)((C + BK - 1) / BK), per = (kt + p.gate_up_splits - 1) / p.gate_up_splits;
+        if (p.gate_up != FWD_MID || R > 256 || (p.gate_up_splits - 1) * per >= kt) return "split of the gate/up GEMM";
+        if ((size_t)p.gate_up_splits * R * 2 * I * 4 > room) return "the slabs of the gate/up GEMM do not fit";
+    }
+    // where two thirds of the chip are idle, no workgroup walks more than 48 K slabs
+    if (p.gate_up == FWD_MID && R <= 256 && 3 * ((I + 63) / 64) * p.gate_up_splits <= ncu &&
+        (C + BK - 1) / BK > 48 * p.gate_up_splits)
+        return "a long K range on an idle chip";
     if (p.down == FWD_FEW) return R <= kFewRowsMax && !(p.gate_up == FWD_CORE) ? nullptr : "too many rows for the register path";
     if (p.down == FWD_MID) {
         if (p.k_down.splits < 1 || p.k_down.sk_nbg != 0) return "split of the tiles of all rows";
@@ -79,7 +88,7 @@ int main() {
                     prev_sv = L.total;
                     // ---- forward workspace, with and without a saved buffer
                     for (int hs = 0; hs < 2; ++hs) {
-                        const FwdWs W = fwd_ws(R, C, I, hs != 0);
+                        const FwdWs W = fwd_ws(R, C, I, hs != 0, ncu);
                         std::vector<unsigned char> m2(W.total / unit + 2, 0);
                         const size_t slab_rows = std::max<size_t>((size_t)kMaxSplits * R, (size_t)kMaxSplitsNarrow * std::min<long>(R, 256));
                         const size_t offs[5] = {W.xn, W.rstd, W.h, W.partial, W.status};

@@ -660,3 +660,35 @@ def test_decode_of_a_wide_layer(R):
             got = bits_of(gpu_forward(p, R_host=r_host, saved=saved)[0])
             assert np.array_equal(got[sk], p.hidden[sk])
             assert max_slice_rel_l2(O.bf16_bits_to_f64(got[idx]), want, axis=1) < REL_L2_TOL
+
+
+@pytest.mark.parametrize("R,C,I", [(65, 4096, 8), (100, 4104, 72), (129, 2056, 264), (200, 4096, 520), (256, 3080, 1032),
+                                   (9, 12296, 2056)],
+                         ids=["one-column-tile", "ragged-k", "cut-off-tiles", "rotated-starts", "256-rows", "chunk-major-h"])
+@pytest.mark.parametrize("r_host", [True, False], ids=["R-host", "R-device"])
+def test_gate_up_split_along_k(R, C, I, r_host):
+    """Layers whose gate/up GEMM has few column tiles and a long K range: K is cut, the sums of gate and up meet in the
+    reducing kernel.  One tile cut off at 8 columns, a K range that ends inside a slab, workgroups that start at different
+    slabs of their range (C a multiple of 4096), H chunk-major for the register path of the down GEMM (9 rows of a
+    layer above its weight limit, without a saved buffer).  Rows are checked one by one, and columns where they have 65
+    entries or more: error and value of an entry are independent, so the largest of N relative errors of columns of n
+    entries is the whole tensor's (4e-3) times about the root of the 1 - 1/N quantile of F(n, n) - 1.6 at n = 65 and
+    N = 4104, but 4 at n = 9 and N = 12296."""
+    from helpers import max_slice_rel_l2
+    w = W.small(C=C, I=I, visual=(R + (0 if r_host is False else 23),), text=(1,), keep=(R - 1,), seed=8000 + R,
+                name=f"split-gate-up-{R}")
+    assert w.R == R
+    p = Problem(w, unit_gain=True, with_gain_tensor=False)
+    fo = O.skipffn_forward(p.hidden, p.mask, p.wg, p.wu, p.wd, None, w.eps, no_residual=True)
+    idx, sk = fo["idx"], p.mask != 0
+    want = O.bf16_bits_to_f64(fo["out_bits"][idx])
+    for saved in (False, True):
+        print(f"split gate/up R={R} T={w.T} C={C} I={I} r_host={r_host} saved={saved}", flush=True)
+        out, bufs = gpu_forward(p, R_host=r_host, saved=saved, flags=B.FLAG_NO_RESIDUAL)
+        got = bits_of(out)
+        assert np.array_equal(got[sk], p.hidden[sk])
+        for axis in (0, 1) if R >= 65 else (1,):
+            assert max_slice_rel_l2(O.bf16_bits_to_f64(got[idx]), want, axis=axis) < REL_L2_TOL
+    sv = bufs.saved_views(R)
+    for k in ("G", "U", "H"):
+        assert max_slice_rel_l2(f64_of(sv[k]), fo[k], axis=1) < REL_L2_TOL, k
