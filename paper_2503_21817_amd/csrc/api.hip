@@ -300,23 +300,37 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
         if (e != hipSuccess) return hip_fail(e);
     }
 
-    if (plan.gate_up != FWD_CORE) {
-        const bf16_t *wg = static_cast<const bf16_t*>(w_gate), *wu = static_cast<const bf16_t*>(w_up);
-        const bf16_t *wd = static_cast<const bf16_t*>(w_down), *res = static_cast<const bf16_t*>(hidden);
-        const int no_residual = (flags & SKIPFFN_FLAG_NO_RESIDUAL) ? 1 : 0;
-        const int splits = plan.k_down.splits;
-        profile_mark_begin(KC_GEMM_GATE_UP, s);
-        e = plan.gate_up == FWD_FEW
-                ? launch_few_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_xn, s)
-                : launch_mid_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_h,
-                                          plan.gate_up_splits, partial, s);
-        profile_mark_end(KC_GEMM_GATE_UP, s);
+    // (3) gate/up GEMM + SiLU*mul
+    const bf16_t *wg = static_cast<const bf16_t*>(w_gate), *wu = static_cast<const bf16_t*>(w_up);
+    profile_mark_begin(KC_GEMM_GATE_UP, s);
+    if (plan.gate_up == FWD_FEW) {
+        e = launch_few_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_xn, s);
+    } else if (plan.gate_up == FWD_MID) {
+        e = launch_mid_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_h, plan.gate_up_splits,
+                                    partial, s);
+    } else {
+        GemmArgs a{};
+        a.M = (int)Rb; a.N = (int)I; a.K = (int)C; a.m_dev = r_dev;
+        a.A0 = xn; a.lda = (int)C; a.a_bytes = (uint32_t)(Rb * C * 2);
+        a.B0 = wg; a.B1 = wu;
+        a.ldb = (int)C; a.b_bytes = (uint32_t)(I * C * 2);
+        a.pairs = 1; a.splits = 1;
+        a.out0 = H; a.out1 = G; a.out2 = U; a.ldo = (int)I;
+        a.outT0 = HT; a.ldt = (int)ld_transposed(Rb);         // written by the epilogue when training
+        e = launch_gemm(true, true, EPI_SWIGLU, a, s);
+    }
+    profile_mark_end(KC_GEMM_GATE_UP, s);
+    if (e != hipSuccess) return hip_fail(e);
+    if (HT != nullptr && plan.gate_up != FWD_CORE) {          // from a copy kernel, for the dW_down GEMM
+        e = launch_gather_transpose(H, (int)I, nullptr, (int)Rb, r_dev, nullptr, HT, (int)ld_transposed(Rb), s);
         if (e != hipSuccess) return hip_fail(e);
-        // the K-contiguous copy of H for the dW_down GEMM comes from a copy kernel
-        if (HT != nullptr) {
-            e = launch_gather_transpose(H, (int)I, nullptr, (int)Rb, r_dev, nullptr, HT, (int)ld_transposed(Rb), s);
-            if (e != hipSuccess) return hip_fail(e);
-        }
+    }
+
+    // (4) down GEMM + residual scatter-add
+    const int no_residual = (flags & SKIPFFN_FLAG_NO_RESIDUAL) ? 1 : 0;
+    if (plan.down != FWD_CORE) {
+        const bf16_t *wd = static_cast<const bf16_t*>(w_down), *res = static_cast<const bf16_t*>(hidden);
+        const int splits = plan.k_down.splits;
         profile_mark_begin(KC_GEMM_DOWN, s);
         e = plan.down == FWD_FEW
                 ? launch_few_rows_down(H, (int)Rb, r_dev, (int)C, (int)I, wd, idx, res, static_cast<bf16_t*>(out), no_residual,
@@ -326,27 +340,8 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
         if (e == hipSuccess && plan.down == FWD_MID)
             e = launch_resid_scatter(partial, PartialLayout{splits, 0, 0}, (int)Rb, r_dev, (int)C, idx, res,
                                      static_cast<bf16_t*>(out), no_residual, s);
-        return e == hipSuccess ? SKIPFFN_OK : hip_fail(e);
-    }
-
-    // (3) gate/up GEMM + SiLU*mul
-    {
-        GemmArgs a{};
-        a.M = (int)Rb; a.N = (int)I; a.K = (int)C; a.m_dev = r_dev;
-        a.A0 = xn; a.lda = (int)C; a.a_bytes = (uint32_t)(Rb * C * 2);
-        a.B0 = static_cast<const bf16_t*>(w_gate); a.B1 = static_cast<const bf16_t*>(w_up);
-        a.ldb = (int)C; a.b_bytes = (uint32_t)(I * C * 2);
-        a.pairs = 1; a.splits = 1;
-        a.out0 = H; a.out1 = G; a.out2 = U; a.ldo = (int)I;
-        a.outT0 = HT; a.ldt = (int)ld_transposed(Rb);         // written by the epilogue when training
-        profile_mark_begin(KC_GEMM_GATE_UP, s);
-        e = launch_gemm(true, true, EPI_SWIGLU, a, s);
-        profile_mark_end(KC_GEMM_GATE_UP, s);
         if (e != hipSuccess) return hip_fail(e);
-    }
-
-    // (4) down GEMM + residual scatter-add
-    {
+    } else {
         GemmArgs a{};
         a.M = (int)Rb; a.N = (int)C; a.K = (int)I; a.m_dev = r_dev;
         a.A0 = H; a.lda = (int)I; a.a_bytes = (uint32_t)(Rb * I * 2);
@@ -356,7 +351,7 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
         const KPartition kp = plan.k_down;
         a.splits = kp.splits;
         a.idx = idx; a.ldo = (int)C;
-        a.no_residual = (flags & SKIPFFN_FLAG_NO_RESIDUAL) ? 1 : 0;
+        a.no_residual = no_residual;
         profile_mark_begin(KC_GEMM_DOWN, s);
         if (kp.splits == 1 && kp.sk_nbg == 0) {
             a.out0 = out; a.e0 = static_cast<const bf16_t*>(hidden);

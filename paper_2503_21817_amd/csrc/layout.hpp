@@ -74,10 +74,19 @@ inline KPartition choose_k_partition(int tiles_m, int tiles_n, int ktiles, bool 
 // Beyond 256 rows a second row of tiles reads the weights again, from L2, and pays where it finds idle CUs: a narrow
 // layer whose gate/up tiles all fit on the chip at once (the general core gives such a layer a few dozen 256-row
 // tiles).  C = 2048: 300 rows 55 / 79, 512 rows 67 / 86;  C = 1024: 300 rows 34 / 51, 1024 rows 47 / 58;  C = 256: 1024 rows
-// 30 / 41;  C = 3072, I = 8192: 512 rows 105 / 112.  One tile more than the chip holds (1500 rows, C = 1024) is even.
+// 30 / 41;  C = 3072, I = 8192: 512 rows 105 / 112.  One tile more than the chip holds (1500 rows, C = 1024) is even, and
+// so are, at C = 8192 and I = 512, 6144 rows on 192 tiles; 7168 rows take 323 / 313 (the larger tiles read less).
 inline int mid_row_tiles(int64_t rows) { return (int)((rows + 255) / 256); }
-inline bool mid_rows(int64_t rows, int64_t I, int ncu) {
-    return rows <= 256 || mid_row_tiles(rows) * ((I + 63) / 64) <= ncu;
+inline bool mid_rows(int64_t rows, int64_t C, int64_t I, int ncu) {
+    return rows <= 256 || (mid_row_tiles(rows) * ((I + 63) / 64) <= ncu && (rows <= 6144 || C <= 4096));
+}
+// The down GEMM of such a layer follows with its own tiles.  Where I is below C these are many and their K range is short:
+// once they are more than the chip holds, writing fp32 slabs (of the one split that is left) and reading them back
+// costs more than the general core with its fused epilogue.  Layer forward, us, core / slabs:  I = 512, C = 4096: 2300
+// rows 76 / 89, 4096 rows 86 / 122;  C = 8192: 2048 rows 135 / 155;  I = 64, C = 4096: 4096 rows 74 / 91.  With tiles
+// that fit:  C = 2048, I = 512: 2048 rows 54 / 50;  C = 4096, I = 2048: 2048 rows 119 / 114.
+inline bool mid_rows_down(int64_t rows, int64_t C, int ncu) {
+    return rows <= 256 || mid_row_tiles(rows) * ((C + 127) / 128) <= ncu;
 }
 // plain split-K into at most max_splits slabs: fill the CUs, keep at least 4 K slabs per workgroup (see
 // choose_k_partition).  max_splits bounds the search itself: 33 K slabs cut for 9 splits and then held to 8 would
@@ -144,10 +153,10 @@ inline int max_down_splits(int64_t rows) { return rows <= 256 ? kMaxSplitsNarrow
 inline ForwardPlan plan_forward(int64_t rows, int64_t C, int64_t I, bool has_saved, bool balanced, int ncu) {
     ForwardPlan p{FWD_CORE, FWD_CORE, 1, KPartition{1, 0}};
     if (!balanced && few_rows(rows, C, I, has_saved)) p.gate_up = p.down = FWD_FEW;
-    else if (!balanced && mid_rows(rows, I, ncu)) {
+    else if (!balanced && mid_rows(rows, C, I, ncu)) {
         p.gate_up = FWD_MID;
         if (rows <= 256) p.gate_up_splits = gate_up_splits(C, I, ncu);
-        p.down = few_rows_down(rows, has_saved) ? FWD_FEW : FWD_MID;
+        p.down = few_rows_down(rows, has_saved) ? FWD_FEW : mid_rows_down(rows, C, ncu) ? FWD_MID : FWD_CORE;
     }
     const int ktiles = (int)((I + BK - 1) / BK);
     if (p.down == FWD_MID)

@@ -46,6 +46,7 @@ static const char* check_plan(long R, long C, long I, bool hs, bool balanced, in
     if (p.down == FWD_FEW) return R <= kFewRowsMax && !(p.gate_up == FWD_CORE) ? nullptr : "too many rows for the register path";
     if (p.down == FWD_MID) {
         if (p.k_down.splits < 1 || p.k_down.sk_nbg != 0) return "split of the tiles of all rows";
+        if (R > 256 && ((R + 255) / 256) * ((C + 127) / 128) > ncu) return "slabs of more tiles than the chip holds";
         if (p.k_down.splits * slab > room) return "the slabs of the tiles of all rows do not fit";
         const int per = (ktiles + p.k_down.splits - 1) / p.k_down.splits;
         if ((p.k_down.splits - 1) * per >= ktiles) return "an empty split";

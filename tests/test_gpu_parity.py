@@ -692,3 +692,29 @@ def test_gate_up_split_along_k(R, C, I, r_host):
     sv = bufs.saved_views(R)
     for k in ("G", "U", "H"):
         assert max_slice_rel_l2(f64_of(sv[k]), fo[k], axis=1) < REL_L2_TOL, k
+
+
+@pytest.mark.parametrize("R,C,I", [(300, 16520, 72), (700, 12296, 136), (2305, 4104, 264)],
+                         ids=["two-row-tiles", "three-row-tiles", "ten-row-tiles"])
+@pytest.mark.parametrize("r_host", [True, False], ids=["R-host", "R-device"])
+def test_narrow_intermediate_width_with_many_rows(R, C, I, r_host):
+    """More than 256 rows with I far below C: gate/up on several tiles of 256 rows, the down GEMM - more column tiles than
+    CUs, a K range of two to five slabs - on the general core with its fused epilogue.  With the count on the device
+    the last row tile of the bound is empty or cut off.  Every row is checked on its own."""
+    from helpers import max_slice_rel_l2
+    w = W.small(C=C, I=I, visual=(R + (300 if r_host is False else 23),), text=(1,), keep=(R - 1,), seed=9000 + R,
+                name=f"short-k-{R}")
+    assert w.R == R
+    p = Problem(w, unit_gain=True, with_gain_tensor=False)
+    fo = O.skipffn_forward(p.hidden, p.mask, p.wg, p.wu, p.wd, None, w.eps, no_residual=True)
+    idx, sk = fo["idx"], p.mask != 0
+    want = O.bf16_bits_to_f64(fo["out_bits"][idx])
+    for saved in (False, True):
+        print(f"narrow I R={R} T={w.T} C={C} I={I} r_host={r_host} saved={saved}", flush=True)
+        out, bufs = gpu_forward(p, R_host=r_host, saved=saved, flags=B.FLAG_NO_RESIDUAL)
+        got = bits_of(out)
+        assert np.array_equal(got[sk], p.hidden[sk])
+        assert max_slice_rel_l2(O.bf16_bits_to_f64(got[idx]), want, axis=1) < REL_L2_TOL
+    sv = bufs.saved_views(R)
+    for k in ("G", "U", "H"):
+        assert max_slice_rel_l2(f64_of(sv[k]), fo[k], axis=1) < REL_L2_TOL, k
