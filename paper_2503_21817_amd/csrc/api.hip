@@ -304,7 +304,7 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
     const bf16_t *wg = static_cast<const bf16_t*>(w_gate), *wu = static_cast<const bf16_t*>(w_up);
     profile_mark_begin(KC_GEMM_GATE_UP, s);
     if (plan.gate_up == FWD_FEW) {
-        e = launch_few_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_xn, s);
+        e = launch_few_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_xn, chunk_major_h, s);
     } else if (plan.gate_up == FWD_MID) {
         e = launch_mid_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_h, plan.gate_up_splits,
                                     partial, s);

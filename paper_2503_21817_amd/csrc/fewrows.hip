@@ -15,7 +15,8 @@
 //
 // Measured at C = 4096, I = 14336, 8 rows: down 24.6 us (4.8 TB/s of weights; the loads alone, without activations and
 // epilogue, 21), where tiles with split K take 25.8 + 5.5 for the reduction; gate/up 48.6, slower than the tiles of
-// midrows.hip (42), which read the activations once per 64 columns.  Which layers and row counts come here: layout.hpp.
+// midrows.hip (42), which read the activations once per 64 columns.  Which layers and row counts come here, each GEMM for
+// itself: layout.hpp.
 #include "kernels.hpp"
 
 namespace skipffn {
@@ -177,13 +178,14 @@ static hipError_t launch_few_rows(const FewRowsArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_few_rows_gate_up(const bf16_t* xn, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_gate,
-                                   const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major, hipStream_t s) {
+                                   const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major, bool chunk_major_h,
+                                   hipStream_t s) {
     FewRowsArgs a{};
     a.rows = rows; a.r_dev = r_dev; a.N = I; a.K = C;
     a.A = xn; a.a_bytes = (uint32_t)((int64_t)rows * C * 2);
     a.a_row = chunk_major ? 16u : (uint32_t)C * 2; a.a_chunk = chunk_major ? (uint32_t)rows * 16 : 16u;
     a.B0 = w_gate; a.B1 = w_up; a.b_bytes = (uint32_t)((int64_t)I * C * 2);
-    a.H = H; a.h_row = chunk_major ? 16u : (uint32_t)I * 2; a.h_chunk = a.a_chunk;
+    a.H = H; a.h_row = chunk_major_h ? 16u : (uint32_t)I * 2; a.h_chunk = chunk_major_h ? (uint32_t)rows * 16 : 16u;
     a.G = G; a.U = U;
     return launch_few_rows<FR_WAVES_GU, true>(a, s);
 }

@@ -124,9 +124,10 @@ hipError_t launch_mfma_probe(int blocks, int iters, int random_operands, float* 
                              hipStream_t s);
 
 // ---- the forward GEMMs of a handful of rows (rows <= 64) -----------------------------------------------
-// H = silu(xn Wg^T) * (xn Wu^T); G and U optional.  chunk_major: xn and H are [C / 8][rows][8] instead of row-major
+// H = silu(xn Wg^T) * (xn Wu^T); G and U optional.  chunk_major, chunk_major_h: xn, H are [K / 8][rows][8] instead of row-major
 hipError_t launch_few_rows_gate_up(const bf16_t* xn, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_gate,
-                                   const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major, hipStream_t s);
+                                   const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major, bool chunk_major_h,
+                                   hipStream_t s);
 // out[idx[r]] = bf16(res[idx[r]] + H[r] Wd^T)
 hipError_t launch_few_rows_down(const bf16_t* H, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_down,
                                 const int32_t* idx, const bf16_t* res, bf16_t* out, int no_residual, bool chunk_major,

@@ -104,21 +104,30 @@ inline int choose_k_split(int tiles, int ktiles, int max_splits, int ncu) {
     return best;
 }
 
-// A handful of rows of a narrow layer: the weights go straight to registers (fewrows.hip), two launches with
-// fused epilogues instead of three.  Every 16 columns read all activations again - a time that grows with
-// rows * C * I - while what is saved, a reducing launch and the ends of the split, does not.  Layer forward, us,
-// against the tiles above:  C = 4096: 1 row 75 / 74, 16 rows 83 / 74;  C = 3072: 16 rows 57 / 55;  C = 2048: 16 rows
-// 32 / 43, 32 rows 38 / 43, 48 rows 46 / 43;  C = 1024: 64 rows 21 / 27;  C = 256: 64 rows 14 / 20.  Row-major
-// activations (a saved buffer) cost more to read: C = 2048: 16 rows 38 / 43, 32 rows 49 / 43.
+// A handful of rows: the weights go straight to registers (fewrows.hip), complete sums and a fused epilogue in one launch.
+// Every 16 columns read all activations again, a time that grows with rows * C * I, and a wavefront walks its share
+// of K in a chain of loads whose length K sets, one, two or four row fragments (16, 32, 64 rows) wide; the tiles above
+// cut K instead.  Row-major activations (a saved buffer) cost more to read, the more the more rows.  Each of the two GEMMs
+// chooses for itself; measured as registers minus tiles, us of a layer forward, saved buffer in brackets:
+//   gate/up (K = C)   C = 256, I = 688: -2 at any rows;  C = 1024, I = 3584: -4 at 16 rows, -2.7 (-1.7) at 64;  C = 2048,
+//     I = 7168: -3 (-1.3) at 16, -3 (0) at 32, -1.3 (6) at 64;  C = 4096, I = 4096: -3.5 at 16, 0.5 (2.7) at 32, 5 (10) at
+//     64;  C = 8192, I = 512: 11 at 16;  C = 4096, I = 14336 (above 24 Mi weights): 5 to 49
+//   down (K = I)      C = 256, I = 688: -6.5;  C = 2048, I = 2048: -4.8 (-3.9) at 16, -3.7 (-0.8) at 64;  C = 1024, I = 3584:
+//     -2.9 (-1.9) at 16, 0.7 (6) at 64;  C = 512, I = 8192: 0.4 (4) at 16, 5 (12) at 32, 11 (27) at 64;  I = 32768: 21 to
+//     133.  With a column block for every CU (C = 4096) the tiles are slower too: I = 14336: -3.3 at 1 row, -0.2 at 16.
 constexpr int64_t kFewRowsMax = 64;
-inline bool few_rows(int64_t rows, int64_t C, int64_t I, bool has_saved) {
+inline bool few_rows_gate_up(int64_t rows, int64_t C, int64_t I, bool has_saved) {
     const int64_t weight = C * I, limit = (int64_t)40 * 2048 * 7168;
-    return rows <= kFewRowsMax && weight <= (int64_t)24 << 20 && rows * weight <= (has_saved ? limit / 2 : limit);
+    if (rows > kFewRowsMax || weight > (int64_t)24 << 20 || rows * weight > (has_saved ? limit / 2 : limit)) return false;
+    return C <= (rows <= 16 ? 4096 : rows <= 32 ? (has_saved ? 2048 : 3072) : (has_saved ? 1024 : 2048));
 }
-
-// Up to 16 rows the down GEMM takes the register path whatever the layer's width, if it may have H chunk-major: complete
-// sums and the residual in one launch, 24.6 us at 8 rows and C = 4096 where the tiles take 25.8 and their reduction 5.5.
-inline bool few_rows_down(int64_t rows, bool has_saved) { return rows <= 16 && !has_saved; }
+inline bool few_rows_down(int64_t rows, int64_t C, int64_t I, bool has_saved, int ncu) {
+    if (rows > kFewRowsMax || rows * C * I > (int64_t)1 << (has_saved ? 29 : 30)) return false;
+    // time of a step of the chain, in units of the one-fragment step: 8192 k of those take what the tiles' split costs
+    const double step = has_saved ? (rows <= 8 ? 1.0 : 0.8 + 0.05 * rows) : rows <= 16 ? 1.0 : rows <= 32 ? 1.6 : 2.0;
+    if (I * step <= 8192.0) return true;
+    return !has_saved && rows <= 16 && I * ncu <= 14336 * std::min<int64_t>((C + 15) / 16, ncu);
+}
 
 // The gate/up GEMM has I / 64 workgroups a row tile, each walking the whole K range: a layer of small I leaves most of
 // the chip idle for C / 64 slabs.  Where three fifths or more of it would be idle, up to 256 rows split K as well; the SwiGLU
@@ -152,11 +161,10 @@ struct ForwardPlan {
 inline int max_down_splits(int64_t rows) { return rows <= 256 ? kMaxSplitsNarrow : kMaxSplits; }
 inline ForwardPlan plan_forward(int64_t rows, int64_t C, int64_t I, bool has_saved, bool balanced, int ncu) {
     ForwardPlan p{FWD_CORE, FWD_CORE, 1, KPartition{1, 0}};
-    if (!balanced && few_rows(rows, C, I, has_saved)) p.gate_up = p.down = FWD_FEW;
-    else if (!balanced && mid_rows(rows, C, I, ncu)) {
-        p.gate_up = FWD_MID;
-        if (rows <= 256) p.gate_up_splits = gate_up_splits(C, I, ncu);
-        p.down = few_rows_down(rows, has_saved) ? FWD_FEW : mid_rows_down(rows, C, ncu) ? FWD_MID : FWD_CORE;
+    if (!balanced && mid_rows(rows, C, I, ncu)) {
+        p.gate_up = few_rows_gate_up(rows, C, I, has_saved) ? FWD_FEW : FWD_MID;
+        if (p.gate_up == FWD_MID && rows <= 256) p.gate_up_splits = gate_up_splits(C, I, ncu);
+        p.down = few_rows_down(rows, C, I, has_saved, ncu) ? FWD_FEW : mid_rows_down(rows, C, ncu) ? FWD_MID : FWD_CORE;
     }
     const int ktiles = (int)((I + BK - 1) / BK);
     if (p.down == FWD_MID)

@@ -43,7 +43,12 @@ static const char* check_plan(long R, long C, long I, bool hs, bool balanced, in
     if (p.gate_up == FWD_MID && R <= 256 && 3 * ((I + 63) / 64) * p.gate_up_splits <= ncu &&
         (C + BK - 1) / BK > 48 * p.gate_up_splits)
         return "a long K range on an idle chip";
-    if (p.down == FWD_FEW) return R <= kFewRowsMax && !(p.gate_up == FWD_CORE) ? nullptr : "too many rows for the register path";
+    if ((p.gate_up == FWD_FEW || p.down == FWD_FEW) && R > kFewRowsMax) return "too many rows for the register path";
+    // its workgroups walk all of K: a chain of loads, twice as long with four row fragments
+    if (p.gate_up == FWD_FEW && C > 4096) return "a long K range of the gate/up GEMM on the register path";
+    if (p.down == FWD_FEW && I * (R > 32 ? 2 : 1) > (R > 16 || hs ? 8192 : 14336))
+        return "a long K range of the down GEMM on the register path";
+    if (p.down == FWD_FEW) return nullptr;
     if (p.down == FWD_MID) {
         if (p.k_down.splits < 1 || p.k_down.sk_nbg != 0) return "split of the tiles of all rows";
         if (R > 256 && ((R + 255) / 256) * ((C + 127) / 128) > ncu) return "slabs of more tiles than the chip holds";

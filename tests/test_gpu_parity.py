@@ -644,11 +644,13 @@ def test_tiles_of_all_rows(R, C, I, r_host):
 
 
 @pytest.mark.parametrize("R", [1, 9, 16, 17])
-def test_decode_of_a_wide_layer(R):
-    """A layer too wide for the register path of the gate/up GEMM: up to 16 rows its down GEMM takes that path, on the
-    chunk-major result of the tiles; from 17 rows (and with a saved buffer) both run on tiles."""
+@pytest.mark.parametrize("C,I", [(2056, 12296), (4104, 8200)], ids=["tiles", "registers-for-down"])
+def test_decode_of_a_wide_layer(R, C, I):
+    """A layer too wide for the register path of the gate/up GEMM.  Where the down GEMM has a column block for every CU, up to
+    16 rows take that path, on the chunk-major result of the tiles; from 17 rows (and with a saved buffer) both run
+    on tiles, as both do where the down GEMM is narrow and its K range long."""
     from helpers import max_slice_rel_l2
-    w = W.small(C=2056, I=12296, visual=(R,), text=(1,), keep=(R - 1,), seed=7000 + R, name=f"wide-{R}")
+    w = W.small(C=C, I=I, visual=(R,), text=(1,), keep=(R - 1,), seed=7000 + R, name=f"wide-{R}")
     assert w.R == R
     p = Problem(w, unit_gain=True, with_gain_tensor=False)
     fo = O.skipffn_forward(p.hidden, p.mask, p.wg, p.wu, p.wd, None, w.eps)
@@ -716,5 +718,30 @@ def test_narrow_intermediate_width_with_many_rows(R, C, I, r_host):
         assert np.array_equal(got[sk], p.hidden[sk])
         assert max_slice_rel_l2(O.bf16_bits_to_f64(got[idx]), want, axis=1) < REL_L2_TOL
     sv = bufs.saved_views(R)
+    for k in ("G", "U", "H"):
+        assert max_slice_rel_l2(f64_of(sv[k]), fo[k], axis=1) < REL_L2_TOL, k
+
+
+@pytest.mark.parametrize("R,C,I", [(9, 264, 8200), (17, 264, 8200), (64, 520, 8200), (40, 2056, 1032), (64, 4104, 520)],
+                         ids=["9-long-k", "17-long-k", "64-long-k", "40-wide", "64-wide"])
+@pytest.mark.parametrize("r_host", [True, False], ids=["R-host", "R-device"])
+def test_one_gemm_on_the_register_path(R, C, I, r_host):
+    """Each GEMM of the forward pass chooses its path: gate/up on registers and, for a long K range, down on tiles (H
+    row-major, normalised rows chunk-major without a saved buffer); or gate/up on tiles and down on registers (H
+    chunk-major without a saved buffer).  Rows are checked one by one."""
+    from helpers import max_slice_rel_l2
+    w = W.small(C=C, I=I, visual=(R + (0 if r_host is False else 23),), text=(1,), keep=(R - 2 if r_host is False else R - 1,),
+                seed=9500 + R, name=f"one-side-{R}")
+    p = Problem(w, unit_gain=False, with_gain_tensor=True)
+    fo = O.skipffn_forward(p.hidden, p.mask, p.wg, p.wu, p.wd, p.gain, w.eps, no_residual=True)
+    idx, sk = fo["idx"], p.mask != 0
+    want = O.bf16_bits_to_f64(fo["out_bits"][idx])
+    for saved in (False, True):
+        print(f"one register GEMM R={w.R} T={w.T} C={C} I={I} r_host={r_host} saved={saved}", flush=True)
+        out, bufs = gpu_forward(p, R_host=r_host, saved=saved, flags=B.FLAG_NO_RESIDUAL)
+        got = bits_of(out)
+        assert np.array_equal(got[sk], p.hidden[sk])
+        assert max_slice_rel_l2(O.bf16_bits_to_f64(got[idx]), want, axis=1) < REL_L2_TOL
+    sv = bufs.saved_views(w.R)
     for k in ("G", "U", "H"):
         assert max_slice_rel_l2(f64_of(sv[k]), fo[k], axis=1) < REL_L2_TOL, k
