@@ -104,4 +104,16 @@ __device__ __forceinline__ int topk_prefix(Flag&& flag, int nv, TopkShared& sh, 
     return sh.total;
 }
 
+// For short lists (4 n <= TOPK_THREADS): how many of the n keys in LDS come before entry threadIdx.x / 4 in the order
+// (key, index); four lanes share an entry.  All lanes of a wavefront call it (entries from n on count something).
+__device__ __forceinline__ int rank_in_lds(const uint32_t* keys, int n) {
+    const int t = threadIdx.x >> 2;
+    const uint64_t mine = ((uint64_t)keys[t < n ? t : 0] << 32) | (uint32_t)t;
+    int before = 0;
+#pragma unroll 4
+    for (int u = threadIdx.x & 3; u < n; u += 4) before += (((uint64_t)keys[u] << 32) | (uint32_t)u) < mine ? 1 : 0;
+    before += __shfl_xor(before, 1);
+    return before + __shfl_xor(before, 2);
+}
+
 }  // namespace skipffn

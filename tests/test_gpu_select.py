@@ -93,30 +93,32 @@ def test_mask_scattered_to_token_positions_feeds_the_compaction():
     assert np.array_equal(sk, want)
 
 
-def test_non_finite_features_still_retain_exactly_n():
+@pytest.mark.parametrize("lens", [(120, 180), (420, 1180)], ids=["counted", "searched"])
+def test_non_finite_features_still_retain_exactly_n(lens):
     """A feature row holding Inf has a NaN similarity (Inf / Inf); a row that is NaN throughout has
     no length at all and gets similarity 0, like a zero row.  NaN loses to every number (the
     oracle's sort puts it last as well), so exactly n tokens are retained whatever the input."""
     rng = np.random.default_rng(15)
-    f = rng.standard_normal((300, 128))
+    first, n = lens[0], sum(lens)
+    f = rng.standard_normal((n, 128))
     f[7, 3] = np.inf
     f[100, :] = np.nan
-    f[299, 0] = -np.inf
+    f[n - 1, 0] = -np.inf
     feat = O.f64_to_bf16_bits(f)
     cls = O.f64_to_bf16_bits(rng.standard_normal((2, 128)))
-    off = np.array([0, 120, 300], dtype=np.int32)
-    for keep in (1, 50, 119, 120, 179, 180):
+    off = np.array([0, first, n], dtype=np.int32)
+    for keep in (1, 50, first - 1, first, lens[1] - 1, lens[1]):
         mask, sim, _ = run_gpu(feat, cls, off, keep)
-        assert np.isnan(sim[[7, 299]]).all() and sim[100] == 0.0
-        assert np.isfinite(np.delete(sim, [7, 299])).all()
+        assert np.isnan(sim[[7, n - 1]]).all() and sim[100] == 0.0
+        assert np.isfinite(np.delete(sim, [7, n - 1])).all()
         for b in range(2):
             lo, hi = off[b], off[b + 1]
             assert int((mask[lo:hi] == 0).sum()) == min(keep, hi - lo)
             assert np.array_equal(mask[lo:hi], O.select_top_n(sim[lo:hi], keep))
 
 
-@pytest.mark.parametrize("lens", [(1, 63, 64, 65), (1023, 1024, 1025), (16384,), (16385,), (3,) * 130],
-                         ids=["one-wave-edges", "one-step-edges", "last-in-registers", "first-from-memory", "many-sets"])
+@pytest.mark.parametrize("lens", [(1, 63, 64, 65), (255, 256, 257), (1023, 1024, 1025), (16384,), (16385,), (3,) * 130],
+                         ids=["one-wave-edges", "last-counted-first-searched", "one-step-edges", "last-in-registers", "first-from-memory", "many-sets"])
 @pytest.mark.parametrize("distinct", [3, 10**9], ids=["repeated-rows", "random-rows"])
 def test_cut_search_edges(lens, distinct):
     """Lengths around the steps of the cut search, with similarities that all differ and with only
