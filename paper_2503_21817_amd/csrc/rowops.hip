@@ -511,11 +511,12 @@ __global__ __launch_bounds__(ROW_THREADS) void rmsnorm_bwd_scatter_kernel(
 }
 
 // dgain[c] (+)= sum over strips of gpart[strip][c]
-__global__ __launch_bounds__(COLSUM_THREADS) void gain_grad_reduce_kernel(
+template <int LANES>
+__global__ __launch_bounds__(32 * LANES) void gain_grad_reduce_kernel(
     const float* __restrict__ gpart, int Rbound, const int32_t* __restrict__ r_dev, int C,
     float* __restrict__ dgain, int accumulate) {
     const int R = effective_rows(Rbound, r_dev);
-    column_sum(gpart, (R + GAIN_STRIP - 1) / GAIN_STRIP, C, dgain, accumulate);
+    column_sum<LANES>(gpart, (R + GAIN_STRIP - 1) / GAIN_STRIP, C, dgain, accumulate);
 }
 
 hipError_t launch_rmsnorm_bwd_scatter(const float* dxn_partial, PartialLayout pl, int R,
@@ -544,8 +545,13 @@ hipError_t launch_rmsnorm_bwd_scatter(const float* dxn_partial, PartialLayout pl
     }
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && gg) {
-        hipLaunchKernelGGL(gain_grad_reduce_kernel, dim3((C + 31) / 32), dim3(COLSUM_THREADS), 0, s, gain_partial, R,
-                           r_dev, C, dgain, accumulate);
+        const dim3 cols((C + 31) / 32);
+        if ((R + GAIN_STRIP - 1) / GAIN_STRIP <= COLSUM_FEW_ROWS)
+            hipLaunchKernelGGL(gain_grad_reduce_kernel<COLSUM_LANES_FEW>, cols, dim3(32 * COLSUM_LANES_FEW), 0, s,
+                               gain_partial, R, r_dev, C, dgain, accumulate);
+        else
+            hipLaunchKernelGGL(gain_grad_reduce_kernel<COLSUM_LANES>, cols, dim3(32 * COLSUM_LANES), 0, s, gain_partial, R,
+                               r_dev, C, dgain, accumulate);
         e = hipGetLastError();
     }
     profile_mark_end(KC_RMSNORM_BWD, s);

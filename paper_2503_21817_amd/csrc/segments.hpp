@@ -18,12 +18,25 @@ __device__ __forceinline__ void seg_bounds(const int32_t* __restrict__ seg, int 
 // chunk q -> (set s, first position t0, count nt); false past the last chunk.  Called by whole
 // wavefronts: a lane takes a set, a prefix sum over the lanes finds the chunk's set.  (A scalar walk over the
 // sets costs a load's latency per few sets before a workgroup knows its rows: the reducing kernels of the
-// summary layer 13.4 -> 11.7 and 7.3 -> 5.9 us at 32 sets.)
+// summary layer 13.4 -> 11.7 and 7.3 -> 5.9 us at 32 sets.  For one or two sets the scalar loads are the faster way:
+// forward + backward of the summary layer 26.9 / 27.5 us at one set of 16 tokens, C = 4096.)
 template <int CH>
 __device__ __forceinline__ bool locate_chunk(const int32_t* __restrict__ seg, int S, int n_tok, int q,
                                              int& s, int& t0, int& nt) {
     const int lane = threadIdx.x & 63;
     int cc = 0;
+    if (S <= 2) {                                // uniform: both sets' bounds by scalar loads
+        int b0, e0, b1, e1;
+        seg_bounds(seg, 0, n_tok, b0, e0);
+        seg_bounds(seg, S - 1, n_tok, b1, e1);
+        const int nc0 = (e0 - b0 + CH - 1) / CH, nc1 = S == 2 ? (e1 - b1 + CH - 1) / CH : 0;
+        if (q >= nc0 + nc1) return false;
+        s = q < nc0 ? 0 : 1;
+        const int e = s ? e1 : e0;
+        t0 = s ? b1 + (q - nc0) * CH : b0 + q * CH;
+        nt = e - t0 < CH ? e - t0 : CH;
+        return true;
+    }
     for (int i0 = 0; i0 < S; i0 += 64) {
         int b = 0, e = 0;
         if (i0 + lane < S) seg_bounds(seg, i0 + lane, n_tok, b, e);
@@ -49,7 +62,11 @@ __device__ __forceinline__ void chunk_range(const int32_t* __restrict__ seg, int
                                             int& q0, int& q1) {
     const int lane = threadIdx.x & 63;
     int cc = 0;
-    for (int i0 = 0; i0 < s; i0 += 64) {
+    if (s == 1) {                                // uniform
+        int b, e;
+        seg_bounds(seg, 0, n_tok, b, e);
+        cc = (e - b + CH - 1) / CH;
+    } else for (int i0 = 0; i0 < s; i0 += 64) {
         int b = 0, e = 0;
         if (i0 + lane < s) seg_bounds(seg, i0 + lane, n_tok, b, e);
         cc += __builtin_amdgcn_readlane(wave_inclusive_sum((e - b + CH - 1) / CH), 63);

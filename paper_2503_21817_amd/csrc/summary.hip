@@ -325,12 +325,13 @@ __global__ __launch_bounds__(SUM_THREADS) void summary_chunk_bwd_kernel(
 }
 
 // dw[c] (+)= sum over all chunks of part_dw[q][c]
-__global__ __launch_bounds__(COLSUM_THREADS) void summary_dw_reduce_kernel(
+template <int LANES>
+__global__ __launch_bounds__(32 * LANES) void summary_dw_reduce_kernel(
     const float* __restrict__ part_dw, const int32_t* __restrict__ seg, int S, int n_tok, int nq_max,
     int C, float* __restrict__ dw, int accumulate) {
     int q0, q1;
     chunk_range<SUM_CH>(seg, S - 1, n_tok, nq_max, q0, q1);           // q1 = total number of chunks
-    column_sum(part_dw, q1, C, dw, accumulate);
+    column_sum<LANES>(part_dw, q1, C, dw, accumulate);
 }
 
 // ---- launchers -----------------------------------------------------------------------------------
@@ -368,8 +369,13 @@ hipError_t launch_summary_backward(const bf16_t* hidden, int64_t T, int C, const
                        S, (int)n_tok, w, xs_f32, scores, lse, gout, grad_hidden, part_dw);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(summary_dw_reduce_kernel, dim3((unsigned)((C + 31) / 32)), dim3(COLSUM_THREADS), 0,
-                           s, part_dw, seg, S, (int)n_tok, (int)nq, C, dw, accumulate);
+        const dim3 cols((unsigned)((C + 31) / 32));
+        if (nq <= COLSUM_FEW_ROWS)
+            hipLaunchKernelGGL(summary_dw_reduce_kernel<COLSUM_LANES_FEW>, cols, dim3(32 * COLSUM_LANES_FEW), 0, s, part_dw,
+                               seg, S, (int)n_tok, (int)nq, C, dw, accumulate);
+        else
+            hipLaunchKernelGGL(summary_dw_reduce_kernel<COLSUM_LANES>, cols, dim3(32 * COLSUM_LANES), 0, s, part_dw, seg, S,
+                               (int)n_tok, (int)nq, C, dw, accumulate);
         e = hipGetLastError();
     }
     profile_mark_end(KC_SUMMARY_BWD, s);

@@ -387,6 +387,8 @@ GAIN_CASES = [
     W.small(C=264, I=520, visual=(700,), text=(9,), keep=(600,), seed=42, name="gain-odd-dims"),
     W.small(C=1024, I=256, visual=(64,), text=(1,), keep=(0,), seed=43, name="gain-one-row"),
     W.small(C=4104, I=128, visual=(40,), text=(3,), keep=(19,), seed=44, name="gain-wide-row"),   # C > 4096: streaming path
+    W.small(C=264, I=128, visual=(300,), text=(6,), keep=(122,), seed=46, name="gain-32-strips"),  # the last in the small column sum
+    W.small(C=264, I=128, visual=(300,), text=(7,), keep=(122,), seed=47, name="gain-33-strips"),
 ]
 
 

@@ -55,6 +55,10 @@ CASES = [
     (64, 4096, (40,)),                        # backbone width
     (500, 264, (15, 31, 250)),                # C not a multiple of the thread count
     (200, 9000 // 8 * 8, (120,)),             # wide rows
+    # one and two sets (bounds by scalar loads; an empty one first, last and alone), three (by the lanes of a wavefront)
+    (20, 256, (16,)), (20, 256, (0,)), (40, 256, (17, 16)), (40, 256, (0, 33)), (40, 256, (33, 0)), (40, 256, (0, 33, 1)),
+    # chunks + sets = 32 and 33: the two forms of the sum over chunks
+    (600, 264, (472, 8)), (600, 264, (488, 8)),
 ]
 
 
