@@ -18,25 +18,26 @@ __device__ __forceinline__ void seg_bounds(const int32_t* __restrict__ seg, int 
 // chunk q -> (set s, first position t0, count nt); false past the last chunk.  Called by whole
 // wavefronts: a lane takes a set, a prefix sum over the lanes finds the chunk's set.  (A scalar walk over the
 // sets costs a load's latency per few sets before a workgroup knows its rows: the reducing kernels of the
-// summary layer 13.4 -> 11.7 and 7.3 -> 5.9 us at 32 sets.  For one or two sets the scalar loads are the faster way:
-// forward + backward of the summary layer 26.9 / 27.5 us at one set of 16 tokens, C = 4096.)
-template <int CH>
+// summary layer 13.4 -> 11.7 and 7.3 -> 5.9 us at 32 sets.)  FEW_SETS (S <= 2): the scalar loads are the faster way:
+// forward + backward of the summary layer 26.9 / 27.5 us at one set of 16 tokens, C = 4096.
+constexpr int SEG_FEW_SETS = 2;
+template <int CH, bool FEW_SETS>
 __device__ __forceinline__ bool locate_chunk(const int32_t* __restrict__ seg, int S, int n_tok, int q,
                                              int& s, int& t0, int& nt) {
-    const int lane = threadIdx.x & 63;
-    int cc = 0;
-    if (S <= 2) {                                // uniform: both sets' bounds by scalar loads
+    if constexpr (FEW_SETS) {
         int b0, e0, b1, e1;
         seg_bounds(seg, 0, n_tok, b0, e0);
         seg_bounds(seg, S - 1, n_tok, b1, e1);
         const int nc0 = (e0 - b0 + CH - 1) / CH, nc1 = S == 2 ? (e1 - b1 + CH - 1) / CH : 0;
         if (q >= nc0 + nc1) return false;
         s = q < nc0 ? 0 : 1;
-        const int e = s ? e1 : e0;
-        t0 = s ? b1 + (q - nc0) * CH : b0 + q * CH;
+        const int e = s == 0 ? e0 : e1;
+        t0 = s == 0 ? b0 + q * CH : b1 + (q - nc0) * CH;
         nt = e - t0 < CH ? e - t0 : CH;
         return true;
     }
+    const int lane = threadIdx.x & 63;
+    int cc = 0;
     for (int i0 = 0; i0 < S; i0 += 64) {
         int b = 0, e = 0;
         if (i0 + lane < S) seg_bounds(seg, i0 + lane, n_tok, b, e);
@@ -57,19 +58,21 @@ __device__ __forceinline__ bool locate_chunk(const int32_t* __restrict__ seg, in
     return false;
 }
 // chunks [q0, q1) of set s, clamped to the nq_max chunks the launch covers (called by whole wavefronts)
-template <int CH>
+template <int CH, bool FEW_SETS>
 __device__ __forceinline__ void chunk_range(const int32_t* __restrict__ seg, int s, int n_tok, int nq_max,
                                             int& q0, int& q1) {
-    const int lane = threadIdx.x & 63;
     int cc = 0;
-    if (s == 1) {                                // uniform
+    if constexpr (FEW_SETS) {
         int b, e;
         seg_bounds(seg, 0, n_tok, b, e);
-        cc = (e - b + CH - 1) / CH;
-    } else for (int i0 = 0; i0 < s; i0 += 64) {
-        int b = 0, e = 0;
-        if (i0 + lane < s) seg_bounds(seg, i0 + lane, n_tok, b, e);
-        cc += __builtin_amdgcn_readlane(wave_inclusive_sum((e - b + CH - 1) / CH), 63);
+        cc = s == 0 ? 0 : (e - b + CH - 1) / CH;
+    } else {
+        const int lane = threadIdx.x & 63;
+        for (int i0 = 0; i0 < s; i0 += 64) {
+            int b = 0, e = 0;
+            if (i0 + lane < s) seg_bounds(seg, i0 + lane, n_tok, b, e);
+            cc += __builtin_amdgcn_readlane(wave_inclusive_sum((e - b + CH - 1) / CH), 63);
+        }
     }
     int b, e;
     seg_bounds(seg, s, n_tok, b, e);

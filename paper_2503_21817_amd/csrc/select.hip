@@ -20,7 +20,7 @@ __global__ __launch_bounds__(SEL_THREADS) void cls_sim_kernel(
     const bf16_t* __restrict__ feat, const bf16_t* __restrict__ cls, const int32_t* __restrict__ seq_off,
     int B, int n_feat, int Cv, float* __restrict__ sim) {
     int b, t0, nt;
-    if (!locate_chunk<SEL_CH>(seq_off, B, n_feat, (int)blockIdx.x, b, t0, nt)) return;
+    if (!locate_chunk<SEL_CH, false>(seq_off, B, n_feat, (int)blockIdx.x, b, t0, nt)) return;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int chunks = Cv >> 3;
     const u32x4* pc = reinterpret_cast<const u32x4*>(cls + (int64_t)b * Cv);

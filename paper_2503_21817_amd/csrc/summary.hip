@@ -70,6 +70,7 @@ __device__ __forceinline__ void wave_dot4(const bf16_t* __restrict__ hidden, int
 }
 
 // ---- forward, per chunk ---------------------------------------------------------------------
+template <bool FEW_SETS>
 __global__ __launch_bounds__(SUM_THREADS) void summary_chunk_fwd_kernel(
     const bf16_t* __restrict__ hidden, int64_t T, int C, const int32_t* __restrict__ tok,
     const int32_t* __restrict__ seg, int S, int n_tok, const bf16_t* __restrict__ w,
@@ -77,7 +78,7 @@ __global__ __launch_bounds__(SUM_THREADS) void summary_chunk_fwd_kernel(
     __shared__ float sc[SUM_CH];
     __shared__ int rowid[SUM_CH];
     int s, t0, nt;
-    if (!locate_chunk<SUM_CH>(seg, S, n_tok, (int)blockIdx.x, s, t0, nt)) return;   // uniform over the workgroup
+    if (!locate_chunk<SUM_CH, FEW_SETS>(seg, S, n_tok, (int)blockIdx.x, s, t0, nt)) return;   // uniform over the workgroup
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int chunks = C >> 3;
     // phase A: scores s_t = X_t . w, four tokens per wavefront (SUM_CH = 16 = 4 waves x 4)
@@ -153,6 +154,7 @@ __global__ __launch_bounds__(SUM_THREADS) void summary_chunk_fwd_kernel(
 // grid (S, ceil(C / 8 / 64)): 64 column chunks x 4 interleaved chunk lanes per workgroup.
 // out bf16 [S, C]; xs_f32 [S, C] and lse [S] for the backward.
 constexpr int MERGE_Q = 256;              // chunk scales staged in LDS per pass
+template <bool FEW_SETS>
 __global__ __launch_bounds__(SUM_THREADS) void summary_merge_fwd_kernel(
     int C, const int32_t* __restrict__ seg, int n_tok, int nq_max, const float* __restrict__ part_acc,
     const float* __restrict__ part_md, bf16_t* __restrict__ out, float* __restrict__ xs_f32,
@@ -163,7 +165,7 @@ __global__ __launch_bounds__(SUM_THREADS) void summary_merge_fwd_kernel(
     const int s = blockIdx.x;
     const int tid = threadIdx.x;
     int q0, q1;
-    chunk_range<SUM_CH>(seg, s, n_tok, nq_max, q0, q1);
+    chunk_range<SUM_CH, FEW_SETS>(seg, s, n_tok, nq_max, q0, q1);
     // global maximum and denominator of the set
     float M = kNoScore;
     for (int q = q0 + tid; q < q1; q += SUM_THREADS) M = fmaxf(M, part_md[2 * q]);
@@ -224,6 +226,7 @@ __global__ __launch_bounds__(SUM_THREADS) void summary_merge_fwd_kernel(
 // With p_t = exp(s_t - lse), dp_t = g . X_t and delta = g . x^s (= sum_u p_u dp_u):
 //   ds_t = p_t (dp_t - delta);  dX_t = p_t g + ds_t w  (added to grad_hidden row t);
 //   dw = sum_t ds_t X_t  (per chunk into part_dw, summed by summary_dw_reduce_kernel)
+template <bool FEW_SETS>
 __global__ __launch_bounds__(SUM_THREADS) void summary_chunk_bwd_kernel(
     const bf16_t* __restrict__ hidden, int64_t T, int C, const int32_t* __restrict__ tok,
     const int32_t* __restrict__ seg, int S, int n_tok, const bf16_t* __restrict__ w,
@@ -233,7 +236,7 @@ __global__ __launch_bounds__(SUM_THREADS) void summary_chunk_bwd_kernel(
     __shared__ int rowid[SUM_CH];
     __shared__ float red[4];
     int s, t0, nt;
-    if (!locate_chunk<SUM_CH>(seg, S, n_tok, (int)blockIdx.x, s, t0, nt)) return;
+    if (!locate_chunk<SUM_CH, FEW_SETS>(seg, S, n_tok, (int)blockIdx.x, s, t0, nt)) return;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int chunks = C >> 3;
     const bf16_t* g = gout + (int64_t)s * C;
@@ -325,36 +328,64 @@ __global__ __launch_bounds__(SUM_THREADS) void summary_chunk_bwd_kernel(
 }
 
 // dw[c] (+)= sum over all chunks of part_dw[q][c]
-template <int LANES>
+template <int LANES, bool FEW_SETS>
 __global__ __launch_bounds__(32 * LANES) void summary_dw_reduce_kernel(
     const float* __restrict__ part_dw, const int32_t* __restrict__ seg, int S, int n_tok, int nq_max,
     int C, float* __restrict__ dw, int accumulate) {
     int q0, q1;
-    chunk_range<SUM_CH>(seg, S - 1, n_tok, nq_max, q0, q1);           // q1 = total number of chunks
+    chunk_range<SUM_CH, FEW_SETS>(seg, S - 1, n_tok, nq_max, q0, q1);           // q1 = total number of chunks
     column_sum<LANES>(part_dw, q1, C, dw, accumulate);
 }
 
 // ---- launchers -----------------------------------------------------------------------------------
 int64_t summary_max_chunks(int64_t n_tok, int64_t S) { return (n_tok + SUM_CH - 1) / SUM_CH + S; }
 
+template <bool FEW_SETS>
+static hipError_t summary_forward(const bf16_t* hidden, int64_t T, int C, const int32_t* tok, const int32_t* seg, int64_t n_tok,
+                                  int S, const bf16_t* w, bf16_t* out, float* scores, float* lse, float* xs_f32,
+                                  float* part_acc, float* part_md, hipStream_t s) {
+    const unsigned nq = (unsigned)summary_max_chunks(n_tok, S);
+    hipLaunchKernelGGL(summary_chunk_fwd_kernel<FEW_SETS>, dim3(nq), dim3(SUM_THREADS), 0, s, hidden, T, C, tok, seg,
+                       S, (int)n_tok, w, scores, part_acc, part_md);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    dim3 grid((unsigned)S, (unsigned)(((C >> 3) + 63) / 64));
+    hipLaunchKernelGGL(summary_merge_fwd_kernel<FEW_SETS>, grid, dim3(SUM_THREADS), 0, s, C, seg, (int)n_tok, (int)nq,
+                       part_acc, part_md, out, xs_f32, lse);
+    return hipGetLastError();
+}
+
 hipError_t launch_summary_forward(const bf16_t* hidden, int64_t T, int C, const int32_t* tok,
                                   const int32_t* seg, int64_t n_tok, int S, const bf16_t* w,
                                   bf16_t* out, float* scores, float* lse, float* xs_f32,
                                   float* part_acc, float* part_md, hipStream_t s) {
     if (S <= 0) return hipSuccess;
-    const unsigned nq = (unsigned)summary_max_chunks(n_tok, S);
     profile_mark_begin(KC_SUMMARY_FWD, s);
-    hipLaunchKernelGGL(summary_chunk_fwd_kernel, dim3(nq), dim3(SUM_THREADS), 0, s, hidden, T, C, tok, seg,
-                       S, (int)n_tok, w, scores, part_acc, part_md);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) {
-        dim3 grid((unsigned)S, (unsigned)(((C >> 3) + 63) / 64));
-        hipLaunchKernelGGL(summary_merge_fwd_kernel, grid, dim3(SUM_THREADS), 0, s, C, seg, (int)n_tok, (int)nq,
-                           part_acc, part_md, out, xs_f32, lse);
-        e = hipGetLastError();
-    }
+    const hipError_t e = S <= SEG_FEW_SETS
+        ? summary_forward<true>(hidden, T, C, tok, seg, n_tok, S, w, out, scores, lse, xs_f32, part_acc, part_md, s)
+        : summary_forward<false>(hidden, T, C, tok, seg, n_tok, S, w, out, scores, lse, xs_f32, part_acc, part_md, s);
     profile_mark_end(KC_SUMMARY_FWD, s);
     return e;
+}
+
+template <bool FEW_SETS>
+static hipError_t summary_backward(const bf16_t* hidden, int64_t T, int C, const int32_t* tok, const int32_t* seg, int64_t n_tok,
+                                   int S, const bf16_t* w, const float* xs_f32, const float* scores, const float* lse,
+                                   const bf16_t* gout, bf16_t* grad_hidden, float* part_dw, float* dw, int accumulate,
+                                   hipStream_t s) {
+    const unsigned nq = (unsigned)summary_max_chunks(n_tok, S);
+    hipLaunchKernelGGL(summary_chunk_bwd_kernel<FEW_SETS>, dim3(nq), dim3(SUM_THREADS), 0, s, hidden, T, C, tok, seg,
+                       S, (int)n_tok, w, xs_f32, scores, lse, gout, grad_hidden, part_dw);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const dim3 cols((unsigned)((C + 31) / 32));
+    if (nq <= COLSUM_FEW_ROWS)
+        hipLaunchKernelGGL((summary_dw_reduce_kernel<COLSUM_LANES_FEW, FEW_SETS>), cols, dim3(32 * COLSUM_LANES_FEW), 0, s,
+                           part_dw, seg, S, (int)n_tok, (int)nq, C, dw, accumulate);
+    else
+        hipLaunchKernelGGL((summary_dw_reduce_kernel<COLSUM_LANES, FEW_SETS>), cols, dim3(32 * COLSUM_LANES), 0, s, part_dw,
+                           seg, S, (int)n_tok, (int)nq, C, dw, accumulate);
+    return hipGetLastError();
 }
 
 hipError_t launch_summary_backward(const bf16_t* hidden, int64_t T, int C, const int32_t* tok,
@@ -363,21 +394,10 @@ hipError_t launch_summary_backward(const bf16_t* hidden, int64_t T, int C, const
                                    const bf16_t* gout, bf16_t* grad_hidden, float* part_dw, float* dw,
                                    int accumulate, hipStream_t s) {
     if (S <= 0) return hipSuccess;
-    const unsigned nq = (unsigned)summary_max_chunks(n_tok, S);
     profile_mark_begin(KC_SUMMARY_BWD, s);
-    hipLaunchKernelGGL(summary_chunk_bwd_kernel, dim3(nq), dim3(SUM_THREADS), 0, s, hidden, T, C, tok, seg,
-                       S, (int)n_tok, w, xs_f32, scores, lse, gout, grad_hidden, part_dw);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) {
-        const dim3 cols((unsigned)((C + 31) / 32));
-        if (nq <= COLSUM_FEW_ROWS)
-            hipLaunchKernelGGL(summary_dw_reduce_kernel<COLSUM_LANES_FEW>, cols, dim3(32 * COLSUM_LANES_FEW), 0, s, part_dw,
-                               seg, S, (int)n_tok, (int)nq, C, dw, accumulate);
-        else
-            hipLaunchKernelGGL(summary_dw_reduce_kernel<COLSUM_LANES>, cols, dim3(32 * COLSUM_LANES), 0, s, part_dw, seg, S,
-                               (int)n_tok, (int)nq, C, dw, accumulate);
-        e = hipGetLastError();
-    }
+    const hipError_t e = S <= SEG_FEW_SETS
+        ? summary_backward<true>(hidden, T, C, tok, seg, n_tok, S, w, xs_f32, scores, lse, gout, grad_hidden, part_dw, dw, accumulate, s)
+        : summary_backward<false>(hidden, T, C, tok, seg, n_tok, S, w, xs_f32, scores, lse, gout, grad_hidden, part_dw, dw, accumulate, s);
     profile_mark_end(KC_SUMMARY_BWD, s);
     return e;
 }
