@@ -236,12 +236,11 @@ def test_cfg5_32_stacked_layers():
 
 
 @pytest.mark.timeout(300)
-@pytest.mark.parametrize("keep", [64, 144], ids=["104-rows-split-gate-up", "184-rows-two-128-row-tiles"])
+@pytest.mark.parametrize("keep", [64, 144], ids=["104-rows", "184-rows"])
 def test_batch1_prefill_full_width(keep):
     """One LLaVA-shaped sequence (576 visual + 40 text tokens) at the backbone's width, forward only
-    with nothing saved, as `bench.py --sweep prefill` times it: the few-row variants of both GEMMs
-    (128-row tiles; below 129 rows also the K split of gate/up with the SwiGLU in the reducing
-    kernel; 16 K splits in the down projection)."""
+    with nothing saved, as `bench.py --sweep prefill` times it: both GEMMs on tiles of all rows (128 and
+    192 high), workgroups of gate/up starting at different slabs, K splits in the down projection."""
     w = W.small(C=4096, I=14336, visual=(576,), text=(40,), keep=(keep,), seed=4100 + keep,
                 name=f"llava-b1-keep{keep}")
     print(f"prefill {w.name}: T={w.T} R={w.R}", flush=True)

@@ -275,11 +275,13 @@ def test_random_shapes_forward_backward(seed):
             assert rel_l2(f64_of(t), bo[k]) < REL_L2_TOL, (k, r_host)
 
 
-@pytest.mark.parametrize("C,I", [(264, 200), (1096, 456), (456, 1096), (2056, 136), (192, 2056)],
+@pytest.mark.parametrize("C,I", [(264, 200), (1096, 456), (456, 1096), (2056, 136), (192, 2056), (264, 8264)],
                          ids=lambda v: str(v))
-def test_k_ranges_that_end_inside_a_slab(C, I):
+@pytest.mark.parametrize("flags", [0, B.FLAG_BALANCED_SPLIT], ids=["", "core"])
+def test_k_ranges_that_end_inside_a_slab(C, I, flags):
     """256-row tiles (R > 256) with contraction lengths that are no multiple of the 64-deep K slab, from
-    3 to 33 slabs: the main loop runs its steady state (unmasked loads, offsets stepped per slab) up to
+    3 to 130 slabs.  The forward of these narrow layers runs on tiles of all rows; the balanced split (a flag) and the
+    widest I take it to the general core, where the backward always runs: its main loop runs its steady state (unmasked loads, offsets stepped per slab) up to
     the slabs at the end of the K range - and, in the dXn GEMM, of each of its two operand pairs - which
     take the guarded, masked path.  R = 300 is no multiple of 64 either (the weight-gradient GEMMs
     contract over it)."""
@@ -290,14 +292,14 @@ def test_k_ranges_that_end_inside_a_slab(C, I):
     bo = O.skipffn_backward(p.hidden, p.mask, p.wg, p.wu, p.wd, p.grad, p.gain, w.eps)
     idx, sk = fo["idx"], p.mask != 0
     for r_host in (True, False):
-        out, bufs = gpu_forward(p, R_host=r_host)
+        out, bufs = gpu_forward(p, R_host=r_host, flags=flags)
         got = bits_of(out)
         assert np.array_equal(got[sk], p.hidden[sk])
         assert rel_l2(O.bf16_bits_to_f64(got[idx]), O.bf16_bits_to_f64(fo["out_bits"][idx])) < REL_L2_TOL
         sv = bufs.saved_views(w.R)
         for k in ("G", "U", "H"):
             assert rel_l2(f64_of(sv[k]), fo[k]) < REL_L2_TOL, k
-        gh, dw = gpu_backward(p, bufs, R_host=r_host)
+        gh, dw = gpu_backward(p, bufs, R_host=r_host, flags=flags)
         gb = bits_of(gh)
         assert np.array_equal(gb[sk], p.grad[sk])
         assert rel_l2(O.bf16_bits_to_f64(gb[idx]), O.bf16_bits_to_f64(bo["dx_bits"][idx])) < REL_L2_TOL
@@ -472,13 +474,11 @@ def test_smallest_and_widest_shapes(w):
 @pytest.mark.parametrize("R", [1, 63, 64, 65, 127, 128, 129, 191, 255, 256, 257])
 @pytest.mark.parametrize("r_host", [True, False], ids=["R-host", "R-device"])
 @pytest.mark.parametrize("C,I", [(520, 1368), (1024, 1368), (2048, 2816)],
-                         ids=["fused-gate-up", "gate-up-2-splits", "gate-up-4-splits"])
-def test_row_counts_around_the_128_row_tiles(R, r_host, C, I):
-    """Up to 256 retained rows the forward GEMMs run on 128-row tiles (one or two rows of tiles,
-    split-K partial sums for the down projection); 257 is the first count on 256-row tiles.  Up
-    to 128 rows the gate/up GEMM is split along K as well when K is long enough (C = 520 is not:
-    fused epilogue; C = 1024 gives 2 splits, C = 2048 with 22 column tiles 4) and the SwiGLU runs
-    in the reducing kernel.  With the count on the device the row bound is T, which selects the
+                         ids=["C520", "C1024", "C2048"])
+def test_row_counts_around_the_tile_heights(R, r_host, C, I):
+    """Row counts around 64, 128, 192 and 256, the heights of the tiles of all rows (257 is the first count on two of
+    them), with split-K partial sums for the down projection and, from 65 to 256 rows at C = 2048, for gate/up; 1 to 64 rows
+    run on the register path.  With the count on the device the row bound is T, which selects the
     variant."""
     visual = R - 7 if R > 7 else R
     text = R - visual
@@ -486,7 +486,7 @@ def test_row_counts_around_the_128_row_tiles(R, r_host, C, I):
     w = W.small(C=C, I=I, visual=(visual + T_pad,), text=(text,), keep=(visual,), seed=300 + R,
                 name=f"rows-{R}")
     assert w.R == R
-    print(f"narrow tiles R={R} T={w.T} r_host={r_host}", flush=True)
+    print(f"tile heights R={R} T={w.T} r_host={r_host}", flush=True)
     p = Problem(w, unit_gain=False, with_gain_tensor=True)
     fo = O.skipffn_forward(p.hidden, p.mask, p.wg, p.wu, p.wd, p.gain, w.eps)
     fo_nr = O.skipffn_forward(p.hidden, p.mask, p.wg, p.wu, p.wd, p.gain, w.eps, no_residual=True)
@@ -512,8 +512,8 @@ def test_row_counts_around_the_128_row_tiles(R, r_host, C, I):
 
 @pytest.mark.parametrize("R_max", [300, 2000])
 def test_buffers_sized_for_a_larger_row_bound(R_max):
-    """Buffers sized once for R_max rows serve a call with fewer rows (here a count that takes the
-    128-row tiles and more K splits than the bound's own configuration would)."""
+    """Buffers sized once for R_max rows serve a call with fewer rows (here a count that takes one tile of all
+    rows and more K splits than the bound's own configuration would)."""
     w = W.small(C=520, I=1368, visual=(200,), text=(13,), keep=(87,), seed=55, name="bound")
     p = Problem(w)
     bufs = B.SkipFFNBuffers(w.T, R_max, w.C, w.I, training=True)
@@ -538,13 +538,15 @@ def test_buffers_sized_for_a_larger_row_bound(R_max):
 
 
 @pytest.mark.parametrize("R", [257, 300, 384, 385, 512 + 1, 512 + 128, 768 + 100])
-def test_last_tile_row_of_at_most_128_rows(R):
+@pytest.mark.parametrize("I", [1368, 8264], ids=["tiles-of-all-rows", "core"])
+def test_last_tile_row_of_at_most_128_rows(R, I):
     """A row count that leaves at most 128 rows for the last row of tiles runs that row on
-    128-row tiles in the gate/up GEMM (257, 300, 384, 513, 640, 868; 385 leaves 129 rows
-    and keeps a full-height tile).  Every row is checked on its own: the tail rows sit in
+    128-row tiles in the gate/up GEMM of the general core (257, 300, 384, 513, 640, 868; 385 leaves 129 rows
+    and keeps a full-height tile), which I = 8264 takes: more gate/up tiles than CUs.  The narrower layer runs on several
+    tiles of all rows, the last one cut off.  Every row is checked on its own: the tail rows sit in
     different tiles from the rest.  The intermediate width leaves a ragged column tile too."""
     from helpers import max_slice_rel_l2
-    w = W.small(C=520, I=1368, visual=(R + 30,), text=(9,), keep=(R - 9,), seed=900 + R, name=f"tail-{R}")
+    w = W.small(C=520, I=I, visual=(R + 30,), text=(9,), keep=(R - 9,), seed=900 + R, name=f"tail-{R}")
     assert w.R == R
     print(f"tail row R={R} T={w.T}", flush=True)
     p = Problem(w)
@@ -570,7 +572,8 @@ def test_last_tile_row_of_at_most_128_rows(R):
 def test_device_row_count_far_below_the_bound(R, T):
     """The tile map is laid over the effective rows: the bound has 10 to 18 tile rows (two or three panels),
     of which one to three are live - with a last row of at most 128 rows, a full one, or one in between.  The layer is
-    wide enough for the 256-row tiles at this bound."""
+    wide enough for the 256-row tiles of the general core at this bound.  Every row is checked on its own."""
+    from helpers import max_slice_rel_l2
     w = W.small(C=520, I=2056, visual=(T - 1,), text=(1,), keep=(R - 1,), seed=4000 + R)
     print(f"device count R={R} bound T={T}", flush=True)
     p = Problem(w, unit_gain=True, with_gain_tensor=False)
@@ -581,6 +584,11 @@ def test_device_row_count_far_below_the_bound(R, T):
     idx = fo["idx"]
     assert rel_l2(f64_of(out)[idx], O.bf16_bits_to_f64(fo["out_bits"][idx])) < REL_L2_TOL
     assert rel_l2(f64_of(gx)[idx], O.bf16_bits_to_f64(bo["dx_bits"][idx])) < REL_L2_TOL
+    assert max_slice_rel_l2(f64_of(out)[idx], O.bf16_bits_to_f64(fo["out_bits"][idx]), axis=1) < REL_L2_TOL
+    assert max_slice_rel_l2(f64_of(gx)[idx], O.bf16_bits_to_f64(bo["dx_bits"][idx]), axis=1) < REL_L2_TOL
+    sv = bufs.saved_views(R)
+    for k in ("G", "U", "H"):
+        assert max_slice_rel_l2(f64_of(sv[k]), fo[k], axis=1) < REL_L2_TOL, k
     for a, k in zip(dw, ("dw_gate", "dw_up", "dw_down")):
         assert rel_l2(f64_of(a), bo[k]) < REL_L2_TOL, k
     sk = p.mask != 0
@@ -621,11 +629,14 @@ def test_weights_streamed_to_registers(R, C, I, r_host):
 
 @pytest.mark.parametrize("R,C,I", [(41, 2056, 7176), (64, 2048, 7168), (65, 264, 328), (128, 640, 1664), (129, 640, 1664),
                                    (192, 264, 328), (193, 136, 2056), (256, 640, 1664), (257, 264, 328), (385, 640, 1664),
-                                   (640, 264, 1000)])
+                                   (640, 264, 1000),
+                                   (300, 4096, 328), (65, 136, 4096), (200, 264, 8192), (256, 136, 12288), (300, 264, 4096)])
 @pytest.mark.parametrize("r_host", [True, False], ids=["R-host", "R-device"])
 def test_tiles_of_all_rows(R, C, I, r_host):
     """Up to 256 rows in one tile of 64, 128, 192 or 256, more in several (the last one cut off): K ranges of a few slabs (fewer than the ring holds), ragged ones,
-    whole ones (workgroups start at different slabs), one split and several, column tiles that are cut off."""
+    whole ones, one split and several, column tiles that are cut off.  Where K is a multiple of 4096 workgroups start at
+    different slabs of their range and wrap around: the whole range of gate/up (C = 4096), ranges of the split down GEMM
+    shorter than the ring (I = 4096 at 65 rows), a little longer (8192, 12288) and in two row tiles."""
     from helpers import max_slice_rel_l2
     w = W.small(C=C, I=I, visual=(R + (0 if r_host is False else 23),), text=(1,), keep=(R - 1,), seed=6000 + R,
                 name=f"all-rows-{R}")
