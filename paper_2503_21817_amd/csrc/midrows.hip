@@ -3,18 +3,19 @@
 //
 // Bound by streaming the weights from HBM.  A tile is ALL rows (16 * MT of them) times 128 weight rows, so that every
 // weight byte goes to one CU only and the tiles are many (I / 64 for gate/up; C / 128 with K split for down, whose
-// fp32 slabs a reducing kernel adds; gate/up splits K as well where I is so small that most CUs would have no tile).  What limits a CU is the bytes its address unit takes, weights and activations
-// together: about 9 TB/s over the chip here.  Hence both operands go to LDS by direct loads of whole 128-byte lines
+// fp32 slabs a reducing kernel adds; gate/up splits K as well where I is so small that most CUs would have no tile).
+// What limits a CU is the bytes its address unit takes, weights and activations together: about 9 TB/s over the chip
+// here.  Hence both operands go to LDS by direct loads of whole 128-byte lines
 // (weights straight to registers, 16 rows x 64 bytes a load: 65 instead of 57 us at 184 rows), and the rows are not
 // padded further than to 64.
 //
-// Where rows are a multiple of 8 KB apart,
-// workgroups of an XCD start at different slabs and wrap around: walking K in step they would all read the same few
-// L2 and HBM channels (gate/up at 64 rows 52 -> 44 us).  At strides of 6, 4 and 28 KB it makes no difference, and K
+// Where rows are a multiple of 8 KB apart, workgroups of an XCD start at different slabs and wrap around: walking K in step they would all read the same few
+// L2 and HBM channels (gate/up at 64 rows 52 -> 43 us).  At strides of 6, 4 and 28 KB it makes no difference, and K
 // is summed in order.
 //
-// Measured at C = 4096, I = 14336 (the loads of the weights alone: 41 + 21 us): gate/up 42 / 49 / 57 / 64 us and down
-// 26 / 32 / 35 / 42 us at 64 / 128 / 184 / 256 rows; 128-row tiles with the weights shared through L2: 73 and 41 at 184.
+// Measured at C = 4096, I = 14336 in a kernel trace (the loads of the weights alone: 41 + 21 us): gate/up 43 / 50 / 58 / 65
+// us and down 26 / 32 / 37 / 43 us at 64 / 128 / 184 / 256 rows; 128-row tiles with the weights shared through L2: 73
+// and 41 at 184.  Split gate/up and its reduction, 128 rows:  C = 8192, I = 512: 13.2 + 7.1 us;  C = 4096, I = 2048: 15.5 + 4.3.
 #include "kernels.hpp"
 #include "slabloop.hpp"
 
