@@ -481,7 +481,7 @@ int skipffn_backward(int64_t T, int64_t C, int64_t I, float eps, const void* gra
         a.A0 = dGT; a.A1 = dUT; a.lda = ldT; a.a_bytes = (uint32_t)(I * (int64_t)ldT * 2);
         a.B0 = xnT; a.ldb = ldT; a.b_bytes = (uint32_t)(C * (int64_t)ldT * 2);
         a.pairs = 1; a.splits = 1; a.batch = 2;
-        a.out0 = dw_gate; a.out1 = dw_up; a.ldo = (int)C; a.out_f32 = f32; a.accumulate = accum;
+        a.out0 = dw_gate; a.out1 = dw_up; a.ldo = (int)C; a.out_f32 = f32; a.accumulate = accum; a.ncu = num_cus();
         profile_mark_begin(KC_GEMM_DW_GATE_UP, s);
         e = launch_gemm(true, true, EPI_STORE, a, s);
         profile_mark_end(KC_GEMM_DW_GATE_UP, s);

@@ -73,6 +73,7 @@ struct GemmArgs {
     int out_f32;                 // EPI_STORE: 1 = fp32 output
     int accumulate;              // EPI_STORE: 1 = +=
     int no_residual;             // EPI_RESID_SCATTER: 1 = do not add the residual
+    int ncu;                     // compute units: workgroups of a kernel that runs lists of tiles (stream.hpp)
     int tail_narrow;             // 1 = a last tile row of at most 128 rows is a row of 128-row tiles, run by
                                  // the last tiles_n live workgroups of the grid
 };

@@ -1,5 +1,6 @@
 // Instantiations and launcher of the bf16 MFMA GEMM core.
 #include "kernels.hpp"
+#include "stream.hpp"
 
 namespace skipffn {
 
@@ -11,10 +12,12 @@ static hipError_t set_lds_limit() {
 
 hipError_t gemm_init() {
     hipError_t e;
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&stream_gemm_kernel<8, true, EPI_STORE>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, kStreamLds);
+    if (e != hipSuccess) return e;
     if ((e = set_lds_limit<true, true, EPI_SWIGLU>()) != hipSuccess) return e;
     if ((e = set_lds_limit<true, true, EPI_PARTIAL>()) != hipSuccess) return e;
     if ((e = set_lds_limit<true, true, EPI_RESID_SCATTER>()) != hipSuccess) return e;
-    if ((e = set_lds_limit<true, true, EPI_STORE>()) != hipSuccess) return e;
     if ((e = set_lds_limit<true, false, EPI_PARTIAL>()) != hipSuccess) return e;
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_dual_kernel<true, false, EPI_SWIGLU_BWD, true, true, EPI_STORE>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS_BYTES);
@@ -45,6 +48,14 @@ static hipError_t launch_one(const GemmArgs& a, hipStream_t s) {
     const unsigned blocks = grid_blocks(a);
     hipLaunchKernelGGL((gemm_bf16_kernel<A_KC, B_KC, EPI>), dim3(blocks), dim3(GEMM_THREADS),
                        GEMM_LDS_BYTES, s, a);
+    return hipGetLastError();
+}
+
+// One workgroup per CU (or per tile, if these are fewer), a multiple of the 8 XCDs
+template <int MI, bool B_KC, int EPI>
+static hipError_t launch_stream(const GemmArgs& a, hipStream_t s) {
+    const unsigned cus = (unsigned)(a.ncu >= 8 ? a.ncu / 8 * 8 : 8), tiles = (grid_blocks(a) + 7) / 8 * 8;
+    hipLaunchKernelGGL((stream_gemm_kernel<MI, B_KC, EPI>), dim3(tiles < cus ? tiles : cus), dim3(GEMM_THREADS), kStreamLds, s, a);
     return hipGetLastError();
 }
 
@@ -82,7 +93,7 @@ hipError_t launch_gemm(bool a_kc, bool b_kc, int epi, GemmArgs& a, hipStream_t s
     if (a_kc && b_kc && epi == EPI_SWIGLU) return launch_one<true, true, EPI_SWIGLU>(a, s);
     if (a_kc && b_kc && epi == EPI_PARTIAL) return launch_one<true, true, EPI_PARTIAL>(a, s);
     if (a_kc && b_kc && epi == EPI_RESID_SCATTER) return launch_one<true, true, EPI_RESID_SCATTER>(a, s);
-    if (a_kc && b_kc && epi == EPI_STORE) return launch_one<true, true, EPI_STORE>(a, s);
+    if (a_kc && b_kc && epi == EPI_STORE) return launch_stream<8, true, EPI_STORE>(a, s);
     if (a_kc && !b_kc && epi == EPI_PARTIAL) return launch_one<true, false, EPI_PARTIAL>(a, s);
     return hipErrorInvalidValue;
 }

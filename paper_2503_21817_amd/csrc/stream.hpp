@@ -1,0 +1,498 @@
+// The GEMM core as a stream: a workgroup runs a list of output tiles, and the K slabs of all of them pass through one
+// pipeline.  (gemm.hpp: operand layouts, LDS swizzles, epilogue kinds, the ping-pong schedule.)
+//
+// With one tile per workgroup a tile costs 11.5 us beside its slabs (1.15 us each): the launch, the first loads, and an
+// epilogue that goes through LDS in passes with barriers between them.  Here the loads of the next tile are under way
+// before a tile's last slab is computed, and the sums leave from the registers while they fly; the stores are waited for
+// a slab later.  What is left at the end of a tile is 2-4 us: the instructions of the epilogue, of which each row group
+// hides only what fits under a compute phase of the other.
+//
+// dW_gate + dW_up (I = 14336, C = 4096, 1792 tiles, R the contraction), us, one tile per workgroup / stream:
+// R = 64 69 / 52, 256 97 / 76, 368 120 / 99, 640 157 / 137, 1472 277 / 251, 2944 499 / 471.
+#pragma once
+
+#include "gemm.hpp"
+
+namespace skipffn {
+
+constexpr int kStreamRingB = 3;               // slabs of B in LDS
+template <int MI>
+constexpr int kStreamRingA = (GEMM_LDS_BYTES - kStreamRingB * OPER_BYTES) / (MI * 4096) < 3 ? 2 : 3;
+constexpr int kStreamLds = GEMM_LDS_BYTES;
+
+// A value that is the same in all lanes, in a scalar register: descriptors that the compiler keeps in vector registers
+// turn every load into a loop over the lanes.
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(const void* base, uint32_t offset, uint32_t bytes) {
+    const uint64_t p = reinterpret_cast<uint64_t>(base) + offset;
+    return make_rsrc(reinterpret_cast<const void*>((uint64_t)uniform((uint32_t)(p >> 32)) << 32 | uniform((uint32_t)p)), uniform(bytes));
+}
+
+struct StreamTile { int tm, tn, z, kb, ke; bool second; };
+
+// n / d and n % d of tile counts by a multiplication (n * d < 2^32): the tile lists are read in the middle of the pipeline,
+// where a division by a variable costs as much as a memory phase.
+struct TileDiv {
+    uint32_t d, m;
+    __device__ __forceinline__ explicit TileDiv(int v) : d((uint32_t)v), m(0xFFFFFFFFu / (uint32_t)(v > 1 ? v : 2) + 1) {}
+    __device__ __forceinline__ int div(int n) const { return d > 1 ? (int)__umulhi((uint32_t)n, m) : n; }
+};
+
+// Tiles of a plain grid (optionally split-K, optionally two problems), dealt to `workgroups` workgroups in the XCD-aware
+// order of tile_of_block: get(i) is the i-th tile of workgroup `block`.
+struct GridWork {
+    int tiles_m, splits, ktiles, per_k;
+    int first, count, step;                   // tile i of this workgroup: number first + i * step of the order, i * step < count
+    TileDiv split_tiles, panel_tiles, last_panel;
+    __device__ __forceinline__ GridWork(int block, int workgroups, int tiles_m_, int tiles_n, int splits_, int batch, int ktiles_)
+        : tiles_m(tiles_m_), splits(splits_), ktiles(ktiles_), per_k((ktiles_ + splits_ - 1) / splits_), split_tiles(tiles_m_ * tiles_n),
+          panel_tiles(PANEL_M * tiles_n), last_panel(tiles_m_ % PANEL_M != 0 ? tiles_m_ % PANEL_M : PANEL_M) {
+        const int nb = tiles_m * tiles_n * splits * batch, xcd = block & 7, q = nb >> 3, rem = nb & 7;
+        first = xcd * q + (xcd < rem ? xcd : rem) + (block >> 3);
+        count = q + (xcd < rem ? 1 : 0) - (block >> 3);
+        step = workgroups >> 3;
+    }
+    __device__ __forceinline__ bool get(const int i, StreamTile& t) const {
+        if (i * step >= count) return false;
+        int L = first + i * step;
+        const int z = split_tiles.div(L);
+        L -= z * (int)split_tiles.d;
+        const int p = panel_tiles.div(L), in_panel = L - p * (int)panel_tiles.d;
+        if ((p + 1) * PANEL_M <= tiles_m) {
+            t.tn = in_panel / PANEL_M;
+            t.tm = p * PANEL_M + in_panel % PANEL_M;
+        } else {
+            t.tn = last_panel.div(in_panel);
+            t.tm = p * PANEL_M + (in_panel - t.tn * (int)last_panel.d);
+        }
+        t.second = z >= splits;
+        t.z = t.second ? z - splits : z;
+        t.kb = t.z * per_k;
+        t.ke = t.kb + per_k < ktiles ? t.kb + per_k : ktiles;
+        return true;
+    }
+};
+
+// ---- epilogue --------------------------------------------------------------------------------------------
+// acc[mi][ni][r] of wavefront (wm, wn) is C[m0 + wm * 16 MI + 16 mi + lane % 16][n0 + 16 ni' + 4 (lane / 16) + r].  A lane
+// holds four consecutive columns of a row; exchanging a register of fragment 2 p + 1 with the neighbouring row of 16
+// lanes (v_permlane16_swap) gives it eight: columns 8 (q / 2) .. + 7 of fragment 2 p + q % 2, q = lane / 16.  So every
+// access is 16 bytes, four lanes cover 64 contiguous bytes of a row (bf16), and no LDS round trip is needed.
+struct Cols8 { float v[8]; };
+__device__ __forceinline__ Cols8 swap_cols(const f32x4& even, const f32x4& odd) {
+    Cols8 c;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(even[r]), __float_as_uint(odd[r]), false, false);
+        c.v[r] = __uint_as_float(s[0]);
+        c.v[4 + r] = __uint_as_float(s[1]);
+    }
+    return c;
+}
+__device__ __forceinline__ u32x4 pack_cols(const Cols8& c) {
+    u32x4 v;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = pack_bf16x2(c.v[2 * k], c.v[2 * k + 1]);
+    return v;
+}
+
+constexpr uint32_t kStoreOob = 0xFFFFFF00u;   // byte offset past every descriptor of an output block, also with 16 added to it
+
+// The rows of a wavefront in an output matrix, 16 at a time.  Blocks whose rows all exist share a descriptor and step the
+// lane's offset; others have one of their own that ends at the last row (stores past it are dropped, loads read zeros).
+// Stores keep a zero scalar offset: of a store of 16 bytes a lane with its offset in a scalar register, the compiler lets
+// the next instruction overwrite the data, and single words of some lanes then went out wrong.
+struct OutRows {
+    char* base; int64_t row_bytes; int rows;  // first row and column of the wavefront's part; how many rows exist
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t block(int mi) const {
+        const int left = rows - 16 * mi;
+        return make_rsrc(base + 16 * mi * row_bytes, left <= 0 ? 0u : (left >= 16 ? kStoreOob : (uint32_t)(left * row_bytes)));
+    }
+};
+// f(descriptor, offset of the lane's 8 columns for p = 0, 1, mi) for the MI blocks of 16 rows; off: in a block, or kStoreOob
+template <int MI, class F>
+__device__ __forceinline__ void for_row_blocks(const OutRows& o, const uint32_t (&off)[2], F&& f) {
+    if (o.rows >= 16 * MI && 16 * MI * o.row_bytes < (int64_t)kOobOffset) {    // uniform
+        const __amdgpu_buffer_rsrc_t d = make_rsrc(o.base, kOobOffset);
+        const uint32_t step = (uint32_t)(16 * o.row_bytes);
+        const uint32_t lane[2] = {off[0] < kOobOffset ? off[0] : kOobOffset, off[1] < kOobOffset ? off[1] : kOobOffset};
+        static_for<MI>([&](auto mi) {
+            const uint32_t at[2] = {lane[0] + mi * step, lane[1] + mi * step};
+            f(d, at, mi);
+        });
+    } else {
+        static_for<MI>([&](auto mi) { f(o.block(mi), off, mi); });
+    }
+}
+__device__ __forceinline__ f32x4 buf_load_f32x4(__amdgpu_buffer_rsrc_t d, uint32_t off) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(d, (int)off, 0, 0));
+}
+
+template <int MI, int EPI>
+__device__ __forceinline__ void stream_epilogue(const GemmArgs& P, const StreamTile& t, const int Meff, f32x4 (&acc)[MI][4]) {
+    constexpr int WROWS = 16 * MI;
+    const int lane = threadIdx.x & 63, r16 = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row0 = t.tm * (2 * WROWS) + (wave >> 2) * WROWS;           // first row of the wavefront
+    const int lane_col = (q & 1) * 16 + (q >> 1) * 8;
+    // byte offset of the lane's 8 columns, column pair p, in a 16-row block
+    auto lane_offset = [&](int64_t row_bytes, int es, int col0, int p) {
+        const int64_t o = r16 * row_bytes + (lane_col + 32 * p) * es;
+        return col0 + lane_col + 32 * p < P.N && o < (int64_t)kStoreOob ? (uint32_t)o : kStoreOob;
+    };
+    if constexpr (EPI == EPI_STORE) {
+        const int col0 = t.tn * BN + (wave & 3) * 64;
+        const int es = P.out_f32 ? 4 : 2;
+        OutRows o;
+        o.row_bytes = (int64_t)P.ldo * es;
+        o.base = static_cast<char*>(t.second ? P.out1 : P.out0) + row0 * o.row_bytes + col0 * es;
+        o.rows = Meff - row0;
+        const uint32_t off[2] = {lane_offset(o.row_bytes, es, col0, 0), lane_offset(o.row_bytes, es, col0, 1)};
+        if (P.out_f32 && !P.accumulate) {
+            for_row_blocks<MI>(o, off, [&](__amdgpu_buffer_rsrc_t d, const uint32_t (&at)[2], auto mi) {
+                static_for<2>([&](auto p) {
+                    const Cols8 c = swap_cols(acc[mi][2 * p], acc[mi][2 * p + 1]);
+                    const f32x4 lo = {c.v[0], c.v[1], c.v[2], c.v[3]}, hi = {c.v[4], c.v[5], c.v[6], c.v[7]};
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, lo), d, (int)at[p], 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, hi), d, (int)at[p] + 16, 0, 0);
+                });
+            });
+        } else if (P.out_f32) {
+            for_row_blocks<MI>(o, off, [&](__amdgpu_buffer_rsrc_t d, const uint32_t (&at)[2], auto mi) {
+                f32x4 old[4];
+                static_for<4>([&](auto h) { old[h] = buf_load_f32x4(d, at[h >> 1] + (h & 1) * 16); });
+                static_for<2>([&](auto p) {
+                    const Cols8 c = swap_cols(acc[mi][2 * p], acc[mi][2 * p + 1]);
+                    const f32x4 lo = {c.v[0], c.v[1], c.v[2], c.v[3]}, hi = {c.v[4], c.v[5], c.v[6], c.v[7]};
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, lo + old[2 * p]), d, (int)at[p], 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, hi + old[2 * p + 1]), d, (int)at[p] + 16, 0, 0);
+                });
+            });
+        } else if (!P.accumulate) {
+            for_row_blocks<MI>(o, off, [&](__amdgpu_buffer_rsrc_t d, const uint32_t (&at)[2], auto mi) {
+                static_for<2>([&](auto p) {
+                    __builtin_amdgcn_raw_buffer_store_b128(pack_cols(swap_cols(acc[mi][2 * p], acc[mi][2 * p + 1])), d, (int)at[p], 0, 0);
+                });
+            });
+        } else {
+            for_row_blocks<MI>(o, off, [&](__amdgpu_buffer_rsrc_t d, const uint32_t (&at)[2], auto mi) {
+                u32x4 old[2];
+                static_for<2>([&](auto p) { old[p] = __builtin_amdgcn_raw_buffer_load_b128(d, (int)at[p], 0, 0); });
+                static_for<2>([&](auto p) {
+                    Cols8 c = swap_cols(acc[mi][2 * p], acc[mi][2 * p + 1]);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        c.v[2 * k] += bf16lo_to_f32(old[p][k]);
+                        c.v[2 * k + 1] += bf16hi_to_f32(old[p][k]);
+                    }
+                    __builtin_amdgcn_raw_buffer_store_b128(pack_cols(c), d, (int)at[p], 0, 0);
+                });
+            });
+        }
+    }
+}
+
+// All 512 threads of the workgroup call it with the same arguments.  K of an operand whose rows are zero from Keff to the
+// next multiple of 64 may be passed rounded up: only a slab that reaches past Keff masks its lanes.
+template <int MI, bool B_KC, int EPI, class Work>
+__device__ __forceinline__ void stream_gemm(const GemmArgs& P, const Work work, const int Meff, const int Keff) {
+    constexpr bool GU = EPI == EPI_SWIGLU;   // B tile = 128 rows of W_gate + 128 of W_up
+    constexpr int TM = 32 * MI, WROWS = 16 * MI;
+    constexpr int STAGE_A = TM * 128, NSA = kStreamRingA<MI>, A_AHEAD = NSA - 1, B_BASE = NSA * STAGE_A;
+    constexpr int AL0 = (MI + 1) / 2, AL1 = MI / 2;         // 1 KB regions of an A slab a wavefront of row group 0 / 1 loads
+    constexpr bool ODD = AL0 != AL1;
+    static_assert(B_BASE + kStreamRingB * OPER_BYTES <= GEMM_LDS_BYTES, "operand rings must fit in LDS");
+    extern __shared__ __align__(16) char smem[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 2, wn = wave & 3;
+    const uint32_t lds0 = lds_addr_of(smem);
+    typedef __attribute__((address_space(3))) void* lds_void_ptr;
+
+    StreamTile tile;
+    if (!work.get(0, tile)) return;                          // uniform over the workgroup
+
+    // ---- per-lane offsets of the loads inside a tile (constant: the tile's place is in the descriptor, which also ends
+    // at the last row, so that rows past it read zeros)
+    const int region_a = wm == 0 ? wave * AL0 : 4 * AL0 + (wave - 4) * AL1;
+    uint32_t a_goff[AL0], b_goff[4];
+    auto lane_off = [](int64_t bytes) { return bytes < (int64_t)kOobOffset ? (uint32_t)bytes : kOobOffset; };
+#pragma unroll
+    for (int l = 0; l < AL0; ++l) {
+        const int row = 8 * (region_a + l) + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
+        a_goff[l] = lane_off(((int64_t)row * P.lda + c * 8) * 2);
+    }
+#pragma unroll
+    for (int l = 0; l < 4; ++l) {
+        const int qb = wave * 4 + l;
+        if (B_KC) {
+            const int row = 8 * qb + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
+            b_goff[l] = lane_off(((int64_t)(GU ? row & 127 : row) * P.ldb + c * 8) * 2);
+        } else {
+            const int krow = 2 * qb + (lane >> 5), pslot = lane & 31;
+            b_goff[l] = lane_off(((int64_t)krow * P.ldb + (2 * ((pslot >> 1) ^ mnc_swz(krow)) + (pslot & 1)) * 8) * 2);
+        }
+    }
+
+    // ---- load cursors: the next slab of A (of B) to fetch, A_AHEAD (2) slabs ahead of the one that is read.  Operands
+    // are smaller than 2 GiB, so offsets of existing tiles fit 32 bits.  (Flags are kept as integers: as truth values
+    // they travel in lane masks.)
+    const int ktp = Keff > 0 ? (Keff + BK - 1) / BK : 1;     // slabs of an operand pair; K = 0: one slab of zeros (empty operands)
+    const bool ragged = Keff % BK != 0;                      // the last slab of a pair reaches past K
+    const uint32_t a_tile = (uint32_t)TM * (uint32_t)P.lda * 2u, a_end = Keff > 0 ? (uint32_t)Meff * (uint32_t)P.lda * 2u : 0u;
+    const uint32_t b_tile = B_KC ? (uint32_t)(GU ? BN / 2 : BN) * (uint32_t)P.ldb * 2u : BN * 2u;
+    const uint32_t b_end = Keff > 0 ? (uint32_t)(B_KC ? P.N : Keff) * (uint32_t)P.ldb * 2u : 0u;
+    const uint32_t bstep = B_KC ? BK * 2u : (uint32_t)BK * (uint32_t)P.ldb * 2u;
+    const bool pairs = P.pairs == 2;
+    // *_kt: slab within the operand pair; *_left: slabs until the pair or the tile ends (0: the list has ended), of which
+    // the last *_mask reach past K; *_more: slabs of the tile after that
+    int a_i = 0, a_kt = 0, a_left = 0, a_more = 0, a_mask = 0, b_i = 0, b_kt = 0, b_left = 0, b_more = 0, b_mask = 0;
+    uint32_t a_step = 0, b_step = 0;
+    StreamTile a_t = tile, b_t = tile;
+    __amdgpu_buffer_rsrc_t a_src, b_src;
+    auto open_a = [&](int second) {
+        const uint32_t o = (uint32_t)a_t.tm * a_tile;
+        a_src = uniform_rsrc(second ? P.A1 : P.A0, o, a_end > o ? a_end - o : 0u);
+        a_step = (uint32_t)a_kt * (BK * 2u);
+        a_mask = ragged && a_kt + a_left == ktp ? 1 : 0;
+    };
+    auto open_b = [&](int second) {
+        const uint32_t o = (uint32_t)b_t.tn * b_tile;
+        b_src = uniform_rsrc((GU ? wave >= 4 : second) ? P.B1 : P.B0, o, b_end > o ? b_end - o : 0u);   // GU: regions 16 .. = rows 128 ..
+        b_step = (uint32_t)b_kt * bstep;
+        b_mask = ragged && b_kt + b_left == ktp ? 1 : 0;
+    };
+    auto begin_a = [&]() {                                   // tile a_t
+        const int second = pairs && a_t.kb >= ktp ? 1 : 0;
+        a_kt = a_t.kb - (second ? ktp : 0);
+        a_left = a_t.ke - a_t.kb;
+        a_more = 0;
+        if (pairs && !second && a_t.ke > ktp) { a_more = a_t.ke - ktp; a_left -= a_more; }
+        open_a(second | (a_t.second ? 1 : 0));
+    };
+    auto begin_b = [&]() {
+        const int second = pairs && b_t.kb >= ktp ? 1 : 0;
+        b_kt = b_t.kb - (second ? ktp : 0);
+        b_left = b_t.ke - b_t.kb;
+        b_more = 0;
+        if (pairs && !second && b_t.ke > ktp) { b_more = b_t.ke - ktp; b_left -= b_more; }
+        open_b(second);
+    };
+    uint32_t a_ld = region_a * 1024, b_ld = B_BASE + wave * 4096;        // LDS offsets this wavefront loads to
+    const uint32_t a_ld_end = NSA * STAGE_A + region_a * 1024, b_ld_end = B_BASE + kStreamRingB * OPER_BYTES + wave * 4096;
+    // after a slab has been issued
+    auto step_a = [&]() {
+        a_ld += STAGE_A;
+        if (a_ld == a_ld_end) a_ld -= NSA * STAGE_A;
+        a_step += BK * 2u;
+        ++a_kt;
+        if (--a_left == 0) {
+            if (a_more > 0) {
+                a_left = a_more; a_more = 0; a_kt = 0;
+                open_a(1);
+            } else if (work.get(++a_i, a_t)) {
+                begin_a();
+            }
+        }
+    };
+    auto step_b = [&]() {
+        b_ld += OPER_BYTES;
+        if (b_ld == b_ld_end) b_ld -= kStreamRingB * OPER_BYTES;
+        b_step += bstep;
+        ++b_kt;
+        if (--b_left == 0) {
+            if (b_more > 0) {
+                b_left = b_more; b_more = 0; b_kt = 0;
+                open_b(1);
+            } else if (work.get(++b_i, b_t)) {
+                begin_b();
+            }
+        }
+    };
+    auto load_a1 = [&](auto l, uint32_t off) {
+        if (ODD && l == AL0 - 1 && wm != 0) return;          // uniform
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(a_src, (lds_void_ptr)(smem + a_ld + l * 1024), 16, (int)off, (int)a_step, 0, 0);
+    };
+    auto load_b1 = [&](auto l, uint32_t off) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(b_src, (lds_void_ptr)(smem + b_ld + l * 1024), 16, (int)off, (int)b_step, 0, 0);
+    };
+    // a whole share; a slab that reaches past K masks its lanes (the mask has to be in the per-lane offset)
+    auto load_a = [&]() {
+        if (a_left == 0) return;                             // uniform
+        if (a_left > a_mask) {
+            static_for<AL0>([&](auto l) { load_a1(l, a_goff[l]); });
+        } else {
+            asm volatile("; K tail" ::: "memory");
+            static_for<AL0>([&](auto l) {
+                const int row = 8 * (region_a + l) + (lane >> 3), kk = a_kt * BK + ((lane & 7) ^ ((row >> 1) & 7)) * 8;
+                load_a1(l, kk < Keff ? a_goff[l] : kOobOffset);
+            });
+            asm volatile("; K tail end" ::: "memory");
+        }
+        step_a();
+    };
+    auto load_b = [&]() {
+        if (b_left == 0) return;
+        if (b_left > b_mask) {
+            static_for<4>([&](auto l) { load_b1(l, b_goff[l]); });
+        } else {
+            asm volatile("; K tail" ::: "memory");
+            static_for<4>([&](auto l) {
+                const int qb = wave * 4 + l, row = 8 * qb + (lane >> 3);
+                const int kk = b_kt * BK + (B_KC ? ((lane & 7) ^ ((row >> 1) & 7)) * 8 : 2 * qb + (lane >> 5));
+                load_b1(l, kk < Keff ? b_goff[l] : kOobOffset);
+            });
+            asm volatile("; K tail end" ::: "memory");
+        }
+        step_b();
+    };
+
+    // ---- fragment reads: see gemm.hpp
+    uint32_t a_rd[2], b_rd[B_KC ? 2 : 4];
+    const int b_row0 = GU ? wn * 32 : wn * 64;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        a_rd[ks] = lds0 + kc_off(wm * WROWS + (lane & 15), 4 * ks + (lane >> 4));
+        if (B_KC) b_rd[ks] = lds0 + B_BASE + kc_off(b_row0 + (lane & 15), 4 * ks + (lane >> 4));
+    }
+    if (!B_KC) {
+#pragma unroll
+        for (int ni = 0; ni < 4; ++ni)
+            b_rd[ni] = lds0 + B_BASE + mnc_off(8 * (lane >> 4) + ((lane & 15) >> 2), (b_row0 >> 4) + ni, 8 * (lane & 3));
+    }
+    uint32_t rd_a = 0, rd_b = 0;                             // byte offsets of the stages that are read
+    f32x4 acc[MI][4];
+    bf16x8 af[MI], bfr[4];
+    // the reads of half slab KS; LOADS: with the loads of A (KS = 0) or B (KS = 1) spread between them
+    auto read_frags = [&](auto ks, auto loads) {
+        constexpr int KS = decltype(ks)::value;
+        constexpr int NL = !decltype(loads)::value ? 0 : (KS == 0 ? AL0 : 4), NR = MI + 4;
+        const uint32_t aa = a_rd[KS] + rd_a;
+        const uint32_t ba = B_KC ? b_rd[KS] + rd_b : rd_b;
+        static_for<NR>([&](auto r) {
+            static_for<NL>([&](auto l) {
+                if constexpr (l * NR / (NL > 0 ? NL : 1) == r) {
+                    if constexpr (KS == 0) load_a1(l, a_goff[l]); else load_b1(l, b_goff[l]);
+                }
+            });
+            if constexpr (r < MI) {
+                af[r] = ds_read_b128_imm<r * 2048>(aa);
+            } else if constexpr (B_KC) {
+                constexpr int ni = r - MI;
+                bfr[ni] = ds_read_b128_imm<GU ? (ni >> 1) * 16384 + (ni & 1) * 2048 : ni * 2048>(ba);
+            } else {
+                constexpr int ni = r - MI;
+                const uint32_t bn = b_rd[ni] + ba;
+                const u32x2 lo = ds_read_tr16_b64_imm<KS * 16384>(bn);
+                const u32x2 hi = ds_read_tr16_b64_imm<KS * 16384 + 2048>(bn);
+                const u32x4 both = {lo[0], lo[1], hi[0], hi[1]};
+                bfr[ni] = __builtin_bit_cast(bf16x8, both);
+            }
+        });
+    };
+    auto phase_barrier = [&]() {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // FIRST: the sums begin here
+    auto compute_phase = [&](auto first) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int nj = 0; nj < 4; ++nj) {
+                const int ni = (mi & 1) ? 3 - nj : nj;
+                acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[ni], af[mi], decltype(first)::value ? f32x4{0.0f, 0.0f, 0.0f, 0.0f} : acc[mi][ni], 0, 0, 0);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // slab j + 1 has landed; what slab j issued for slab j + 2 may still fly
+    auto wait_next_slab = [&](int issued) {
+        if (issued == 0) SKIPFFN_WAIT_VMCNT(0);
+        else if (A_AHEAD == 1) SKIPFFN_WAIT_VMCNT(4);
+        else if (!ODD || wm == 0) SKIPFFN_WAIT_VMCNT(4 + AL0);
+        else SKIPFFN_WAIT_VMCNT(4 + AL1);
+    };
+
+    begin_a();
+    begin_b();
+    load_a();
+    load_b();
+    {
+        const int two = b_left;
+        if (A_AHEAD == 2) load_a();
+        load_b();
+        wait_next_slab(two);
+    }
+    phase_barrier();
+    if (wm == 1) phase_barrier();                            // row group 1 runs one phase later
+    const std::integral_constant<int, 0> k0{};
+    const std::integral_constant<int, 1> k1{};
+    // M(j, 1), C(j, 1)
+    auto second_half = [&]() {
+        const int issued = b_left;
+        if (b_left > b_mask) {
+            read_frags(k1, std::true_type{});
+            step_b();
+        } else {
+            load_b();
+            read_frags(k1, std::false_type{});
+        }
+        if (wm == 1) wait_next_slab(issued);
+        SKIPFFN_WAIT_LGKMCNT0();
+        phase_barrier();
+        compute_phase(std::false_type{});
+        if (wm == 0) wait_next_slab(issued);
+        rd_a += STAGE_A; if (rd_a == NSA * STAGE_A) rd_a = 0;
+        rd_b += OPER_BYTES; if (rd_b == kStreamRingB * OPER_BYTES) rd_b = 0;
+        phase_barrier();
+    };
+    StreamTile done = tile;                                  // the tile whose sums are in acc
+    for (int i = 0;;) {
+        // M(0, 0): the tile before leaves while the loads for this one fly
+        load_a();
+        if (i > 0) {
+            __builtin_amdgcn_sched_barrier(0);
+            stream_epilogue<MI, EPI>(P, done, Meff, acc);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        read_frags(k0, std::false_type{});
+        SKIPFFN_WAIT_LGKMCNT0();
+        phase_barrier();
+        compute_phase(std::true_type{});
+        phase_barrier();
+        second_half();
+        for (int j = tile.ke - tile.kb - 1; j > 0; --j) {
+            if (a_left > a_mask) {
+                read_frags(k0, std::true_type{});
+                step_a();
+            } else {
+                load_a();
+                read_frags(k0, std::false_type{});
+            }
+            SKIPFFN_WAIT_LGKMCNT0();
+            phase_barrier();
+            compute_phase(std::false_type{});
+            phase_barrier();
+            second_half();
+        }
+        done = tile;
+        if (!work.get(++i, tile)) break;
+    }
+    if (wm == 0) phase_barrier();                            // balances group 1's extra barrier
+    stream_epilogue<MI, EPI>(P, done, Meff, acc);
+}
+
+template <int MI, bool B_KC, int EPI>
+__global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_kernel(GemmArgs P) {
+    const int Meff = effective_rows(P.M, P.m_dev);
+    int Keff = effective_rows(P.K, P.k_dev);
+    if (EPI == EPI_STORE) Keff = (Keff + BK - 1) / BK * BK;  // the transposed copies are zero up to the next multiple of 64
+    if (Meff <= 0) return;
+    const GridWork w((int)blockIdx.x, (int)gridDim.x, (Meff + 32 * MI - 1) / (32 * MI), P.tiles_n, P.splits, P.batch,
+                     (Keff > 0 ? (Keff + BK - 1) / BK : 1) * P.pairs);
+    stream_gemm<MI, B_KC, EPI>(P, w, Meff, Keff);
+}
+
+}  // namespace skipffn

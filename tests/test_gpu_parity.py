@@ -758,3 +758,42 @@ def test_one_gemm_on_the_register_path(R, C, I, r_host):
     sv = bufs.saved_views(w.R)
     for k in ("G", "U", "H"):
         assert max_slice_rel_l2(f64_of(sv[k]), fo[k], axis=1) < REL_L2_TOL, k
+
+
+@pytest.mark.parametrize("R", [0, 1, 64, 65, 130, 257])
+@pytest.mark.parametrize("flags", [0, B.FLAG_DW_FP32, B.FLAG_DW_ACCUMULATE, B.FLAG_DW_FP32 | B.FLAG_DW_ACCUMULATE],
+                         ids=["bf16", "fp32", "bf16-add", "fp32-add"])
+def test_weight_gradients_of_more_tiles_than_compute_units(R, flags):
+    """Every workgroup runs several tiles of dW as one stream of K slabs: 1 slab a tile (the loads run two tiles ahead) to 5,
+    cut-off tiles at the right and lower edge, both data types, overwritten and added to; the row count on the device, 0
+    included (zeros, or nothing added).  Bound: REL_L2_TOL for the gradient, plus one rounding of a sum of gradient and
+    old value of like size to bf16 (2^-9 of it) where it is added to."""
+    C, I = 2056, 8712                                    # 9 x 35 tiles of 256 x 256 for each matrix
+    w = W.small(C=C, I=I, visual=(300,), text=(1 if R else 0,), keep=(max(R - 1, 0),), seed=610 + R, name=f"dw-stream-{R}")
+    assert w.R == R
+    p = Problem(w)
+    fo = O.skipffn_forward(p.hidden, p.mask, p.wg, p.wu, p.wd, None, w.eps)
+    bo = O.skipffn_backward(p.hidden, p.mask, p.wg, p.wu, p.wd, p.grad, None, w.eps)
+    assert fo["R"] == R
+    _, bufs = gpu_forward(p, R_host=False)
+    dt = torch.float32 if flags & B.FLAG_DW_FP32 else torch.bfloat16
+    rng = np.random.default_rng(R)
+    add = bool(flags & B.FLAG_DW_ACCUMULATE)
+    old = {}
+    for k in ("dw_gate", "dw_up", "dw_down"):
+        scale = max(float(np.sqrt(np.mean(bo[k] ** 2))), 1e-3)
+        old[k] = torch.from_numpy((rng.standard_normal(bo[k].shape) * scale).astype(np.float32)).to(dt)
+    _, dw = gpu_backward(p, bufs, R_host=False, flags=flags, dw=[old[k].cuda() for k in ("dw_gate", "dw_up", "dw_down")])
+    for t, k in zip(dw, ("dw_gate", "dw_up", "dw_down")):
+        want = bo[k] + (old[k].to(torch.float64).numpy() if add else 0.0)
+        got = t.to(torch.float64).cpu().numpy()
+        if R == 0:
+            assert np.array_equal(got, want), k
+            continue
+        assert rel_l2(got, want) < REL_L2_TOL, k
+        # every row and column: REL_L2_TOL of its own size, plus, with one retained row, where a row of dW_gate is dG_i * xn and
+        # a dG_i that cancels to nearly nothing keeps the rounding of its terms, REL_L2_TOL of a typical row times 4 (the
+        # factors are normal, of at most 4 standard deviations over these counts).  A wrong tile edge would be off by 1
+        for axis in (0, 1):
+            err, size = np.linalg.norm(got - want, axis=axis), np.linalg.norm(want, axis=axis)
+            assert np.all(err < REL_L2_TOL * (size + 4 * np.sqrt(np.mean(size ** 2)))), (k, axis)
