@@ -317,6 +317,7 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
         a.pairs = 1; a.splits = 1;
         a.out0 = H; a.out1 = G; a.out2 = U; a.ldo = (int)I;
         a.outT0 = HT; a.ldt = (int)ld_transposed(Rb);         // written by the epilogue when training
+        a.ncu = num_cus();
         e = launch_gemm(true, true, EPI_SWIGLU, a, s);
     }
     profile_mark_end(KC_GEMM_GATE_UP, s);

@@ -10,12 +10,14 @@ static hipError_t set_lds_limit() {
                                hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS_BYTES);
 }
 
+static hipError_t set_stream_lds(void (*kernel)(GemmArgs)) {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kStreamLds);
+}
+
 hipError_t gemm_init() {
     hipError_t e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&stream_gemm_kernel<8, true, EPI_STORE>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, kStreamLds);
-    if (e != hipSuccess) return e;
-    if ((e = set_lds_limit<true, true, EPI_SWIGLU>()) != hipSuccess) return e;
+    if ((e = set_stream_lds(&stream_gemm_kernel<true, EPI_STORE>)) != hipSuccess) return e;
+    if ((e = set_stream_lds(&stream_gemm_rows_kernel<true, EPI_SWIGLU>)) != hipSuccess) return e;
     if ((e = set_lds_limit<true, true, EPI_PARTIAL>()) != hipSuccess) return e;
     if ((e = set_lds_limit<true, true, EPI_RESID_SCATTER>()) != hipSuccess) return e;
     if ((e = set_lds_limit<true, false, EPI_PARTIAL>()) != hipSuccess) return e;
@@ -51,11 +53,13 @@ static hipError_t launch_one(const GemmArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// One workgroup per CU (or per tile, if these are fewer), a multiple of the 8 XCDs
-template <int MI, bool B_KC, int EPI>
-static hipError_t launch_stream(const GemmArgs& a, hipStream_t s) {
-    const unsigned cus = (unsigned)(a.ncu >= 8 ? a.ncu / 8 * 8 : 8), tiles = (grid_blocks(a) + 7) / 8 * 8;
-    hipLaunchKernelGGL((stream_gemm_kernel<MI, B_KC, EPI>), dim3(tiles < cus ? tiles : cus), dim3(GEMM_THREADS), kStreamLds, s, a);
+// One workgroup per CU, a multiple of the 8 XCDs; fewer where the tiles, counted at their smallest height, are fewer
+template <int EPI>
+static hipError_t launch_stream(void (*kernel)(GemmArgs), const GemmArgs& a, hipStream_t s) {
+    const int height = EPI == EPI_STORE ? 256 : 128;
+    const unsigned cus = (unsigned)(a.ncu >= 8 ? a.ncu / 8 * 8 : 8);
+    const unsigned tiles = ((unsigned)((a.M + height - 1) / height * a.tiles_n * a.splits * a.batch) + 7) / 8 * 8;
+    hipLaunchKernelGGL(kernel, dim3(tiles < cus ? tiles : cus), dim3(GEMM_THREADS), kStreamLds, s, a);
     return hipGetLastError();
 }
 
@@ -90,10 +94,10 @@ hipError_t launch_gemm_streamk(bool a_kc, bool b_kc, GemmArgs& a, int nbg, hipSt
 hipError_t launch_gemm(bool a_kc, bool b_kc, int epi, GemmArgs& a, hipStream_t s) {
     finish_args(epi, a);
     if (grid_blocks(a) == 0 || a.tiles_n <= 0) return hipSuccess;
-    if (a_kc && b_kc && epi == EPI_SWIGLU) return launch_one<true, true, EPI_SWIGLU>(a, s);
+    if (a_kc && b_kc && epi == EPI_SWIGLU) return launch_stream<EPI_SWIGLU>(&stream_gemm_rows_kernel<true, EPI_SWIGLU>, a, s);
     if (a_kc && b_kc && epi == EPI_PARTIAL) return launch_one<true, true, EPI_PARTIAL>(a, s);
     if (a_kc && b_kc && epi == EPI_RESID_SCATTER) return launch_one<true, true, EPI_RESID_SCATTER>(a, s);
-    if (a_kc && b_kc && epi == EPI_STORE) return launch_stream<8, true, EPI_STORE>(a, s);
+    if (a_kc && b_kc && epi == EPI_STORE) return launch_stream<EPI_STORE>(&stream_gemm_kernel<true, EPI_STORE>, a, s);
     if (a_kc && !b_kc && epi == EPI_PARTIAL) return launch_one<true, false, EPI_PARTIAL>(a, s);
     return hipErrorInvalidValue;
 }

@@ -30,33 +30,46 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(const void* base,
 
 struct StreamTile { int tm, tn, z, kb, ke; bool second; };
 
-// n / d and n % d of tile counts by a multiplication (n * d < 2^32): the tile lists are read in the middle of the pipeline,
-// where a division by a variable costs as much as a memory phase.
+// n / d of tile counts by a multiplication: the tile lists are read in the middle of the pipeline, where a division by a
+// variable costs as much as a memory phase.  m >= 2^32 / d, so the product is at most one too large.
 struct TileDiv {
     uint32_t d, m;
     __device__ __forceinline__ explicit TileDiv(int v) : d((uint32_t)v), m(0xFFFFFFFFu / (uint32_t)(v > 1 ? v : 2) + 1) {}
-    __device__ __forceinline__ int div(int n) const { return d > 1 ? (int)__umulhi((uint32_t)n, m) : n; }
+    __device__ __forceinline__ int div(int n) const {
+        if (d == 1) return n;
+        const uint32_t q = __umulhi((uint32_t)n, m);
+        return (int)(q * d > (uint32_t)n ? q - 1 : q);
+    }
 };
 
-// Tiles of a plain grid (optionally split-K, optionally two problems), dealt to `workgroups` workgroups in the XCD-aware
-// order of tile_of_block: get(i) is the i-th tile of workgroup `block`.
+// Tiles of a plain grid, dealt to `workgroups` workgroups in the XCD-aware order of tile_of_block: get(i) is the i-th tile
+// of workgroup `block`.  SPLIT: the K range is cut into `splits`, or the grid holds two problems (batch), one after the other.
+template <bool SPLIT>
 struct GridWork {
-    int tiles_m, splits, ktiles, per_k;
+    int tiles_m, ktiles;
     int first, count, step;                   // tile i of this workgroup: number first + i * step of the order, i * step < count
-    TileDiv split_tiles, panel_tiles, last_panel;
-    __device__ __forceinline__ GridWork(int block, int workgroups, int tiles_m_, int tiles_n, int splits_, int batch, int ktiles_)
-        : tiles_m(tiles_m_), splits(splits_), ktiles(ktiles_), per_k((ktiles_ + splits_ - 1) / splits_), split_tiles(tiles_m_ * tiles_n),
-          panel_tiles(PANEL_M * tiles_n), last_panel(tiles_m_ % PANEL_M != 0 ? tiles_m_ % PANEL_M : PANEL_M) {
-        const int nb = tiles_m * tiles_n * splits * batch, xcd = block & 7, q = nb >> 3, rem = nb & 7;
-        first = xcd * q + (xcd < rem ? xcd : rem) + (block >> 3);
-        count = q + (xcd < rem ? 1 : 0) - (block >> 3);
+    TileDiv panel_tiles, last_panel, split_tiles;
+    int splits, per_k;
+    // after: tiles that these workgroups have been dealt before, in the same order
+    __device__ __forceinline__ GridWork(int block, int workgroups, int tiles_m_, int tiles_n, int splits_, int batch, int ktiles_, int after = 0)
+        : tiles_m(tiles_m_), ktiles(ktiles_), panel_tiles(PANEL_M * tiles_n),
+          last_panel(tiles_m_ % PANEL_M != 0 ? tiles_m_ % PANEL_M : PANEL_M), split_tiles(SPLIT ? tiles_m_ * tiles_n : 1),
+          splits(SPLIT ? splits_ : 1), per_k(SPLIT ? (ktiles_ + splits_ - 1) / splits_ : ktiles_) {
+        const int nb = tiles_m * tiles_n * (SPLIT ? splits * batch : 1), xcd = block & 7, q = nb >> 3, rem = nb & 7;
         step = workgroups >> 3;
+        const int before = (after >> 3) + (xcd < (after & 7) ? 1 : 0);               // of this XCD
+        int slot = (block >> 3) - before % step;
+        slot = slot < 0 ? slot + step : slot;
+        first = xcd * q + (xcd < rem ? xcd : rem) + slot;
+        count = q + (xcd < rem ? 1 : 0) - slot;
     }
     __device__ __forceinline__ bool get(const int i, StreamTile& t) const {
         if (i * step >= count) return false;
-        int L = first + i * step;
-        const int z = split_tiles.div(L);
-        L -= z * (int)split_tiles.d;
+        int L = first + i * step, z = 0;
+        if (SPLIT) {
+            z = split_tiles.div(L);
+            L -= z * (int)split_tiles.d;
+        }
         const int p = panel_tiles.div(L), in_panel = L - p * (int)panel_tiles.d;
         if ((p + 1) * PANEL_M <= tiles_m) {
             t.tn = in_panel / PANEL_M;
@@ -65,10 +78,10 @@ struct GridWork {
             t.tn = last_panel.div(in_panel);
             t.tm = p * PANEL_M + (in_panel - t.tn * (int)last_panel.d);
         }
-        t.second = z >= splits;
+        t.second = SPLIT && z >= splits;
         t.z = t.second ? z - splits : z;
         t.kb = t.z * per_k;
-        t.ke = t.kb + per_k < ktiles ? t.kb + per_k : ktiles;
+        t.ke = SPLIT && t.kb + per_k >= ktiles ? ktiles : t.kb + per_k;
         return true;
     }
 };
@@ -109,31 +122,70 @@ struct OutRows {
         return make_rsrc(base + 16 * mi * row_bytes, left <= 0 ? 0u : (left >= 16 ? kStoreOob : (uint32_t)(left * row_bytes)));
     }
 };
-// f(descriptor, offset of the lane's 8 columns for p = 0, 1, mi) for the MI blocks of 16 rows; off: in a block, or kStoreOob
+// f(desc, at, mi) for the MI blocks of 16 rows: desc(o') the descriptor of the block in a matrix of the same shape, at(off)
+// the lane's offset there; off: its offset in a block, or kStoreOob
 template <int MI, class F>
-__device__ __forceinline__ void for_row_blocks(const OutRows& o, const uint32_t (&off)[2], F&& f) {
+__device__ __forceinline__ void for_row_blocks(const OutRows& o, F&& f) {
     if (o.rows >= 16 * MI && 16 * MI * o.row_bytes < (int64_t)kOobOffset) {    // uniform
-        const __amdgpu_buffer_rsrc_t d = make_rsrc(o.base, kOobOffset);
         const uint32_t step = (uint32_t)(16 * o.row_bytes);
-        const uint32_t lane[2] = {off[0] < kOobOffset ? off[0] : kOobOffset, off[1] < kOobOffset ? off[1] : kOobOffset};
         static_for<MI>([&](auto mi) {
-            const uint32_t at[2] = {lane[0] + mi * step, lane[1] + mi * step};
-            f(d, at, mi);
+            f([](const OutRows& m) { return make_rsrc(m.base, kOobOffset); },
+              [&](uint32_t off) { return (off < kOobOffset ? off : kOobOffset) + mi * step; }, mi);
         });
     } else {
-        static_for<MI>([&](auto mi) { f(o.block(mi), off, mi); });
+        static_for<MI>([&](auto mi) {
+            f([&](const OutRows& m) { return m.block(mi); }, [](uint32_t off) { return off; }, mi);
+        });
     }
+}
+__device__ __forceinline__ void buf_store(const u32x4& v, __amdgpu_buffer_rsrc_t d, uint32_t off) {
+    __builtin_amdgcn_raw_buffer_store_b128(v, d, (int)off, 0, 0);
 }
 __device__ __forceinline__ f32x4 buf_load_f32x4(__amdgpu_buffer_rsrc_t d, uint32_t off) {
     return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(d, (int)off, 0, 0));
 }
 
+__device__ __forceinline__ void store_f32(const Cols8& c, __amdgpu_buffer_rsrc_t d, uint32_t off) {
+    const f32x4 lo = {c.v[0], c.v[1], c.v[2], c.v[3]}, hi = {c.v[4], c.v[5], c.v[6], c.v[7]};
+    buf_store(__builtin_bit_cast(u32x4, lo), d, off);
+    buf_store(__builtin_bit_cast(u32x4, hi), d, off + 16);
+}
+
+// Transposition of 32 rows x 32 columns of bf16 inside a wavefront, through 2 KB of LDS of its own: 64 bytes a row, the two
+// 32-byte halves of rows 8 - 15 and 24 - 31 exchanged (a transposing read takes 4 rows x 32 bytes per 16 lanes, two such
+// groups, 8 rows apart, at a time).  No barrier: a wavefront's LDS operations are done in order.  Inline assembly, because
+// the compiler would wait for every direct-to-LDS load in flight first.
+struct TransposedBlock {
+    uint32_t wr, rd;
+    __device__ __forceinline__ TransposedBlock(uint32_t lds, int lane) {
+        const int r16 = lane & 15, q = lane >> 4, half = (r16 >> 3) & 1;
+        wr = lds + r16 * 64 + ((((q & 1) ^ half) << 1 | (q >> 1)) << 4);
+        rd = lds + (8 * q + (r16 >> 2)) * 64 + ((q & 1) << 5) + (r16 & 3) * 8;
+    }
+    // the lane's 8 columns (chunk 2 (q % 2) + q / 2) of row 16 I + lane % 16
+    template <int I>
+    __device__ __forceinline__ void put(const u32x4& v) const {
+        asm volatile("ds_write_b128 %0, %1 offset:%2" ::"v"(wr), "v"(v), "n"(I * 1024) : "memory");
+    }
+    // rows 8 q .. 8 q + 7 of columns lane % 16 (c0) and 16 + lane % 16 (c1)
+    __device__ __forceinline__ void get(u32x4& c0, u32x4& c1) const {
+        u32x2 a, b, c, d;
+        asm volatile("ds_read_b64_tr_b16 %0, %4\n\tds_read_b64_tr_b16 %1, %4 offset:256\n\t"
+                     "ds_read_b64_tr_b16 %2, %5\n\tds_read_b64_tr_b16 %3, %5 offset:256\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d) : "v"(rd), "v"(rd ^ 32u) : "memory");
+        c0 = u32x4{a[0], a[1], b[0], b[1]};
+        c1 = u32x4{c[0], c[1], d[0], d[1]};
+    }
+};
+
+// scratch: 4 KB of LDS of the wavefront's own
 template <int MI, int EPI>
-__device__ __forceinline__ void stream_epilogue(const GemmArgs& P, const StreamTile& t, const int Meff, f32x4 (&acc)[MI][4]) {
+__device__ __forceinline__ void stream_epilogue(const GemmArgs& P, const StreamTile& t, const int Meff, const int row_base,
+                                                f32x4 (&acc)[MI][4], const uint32_t scratch) {
     constexpr int WROWS = 16 * MI;
     const int lane = threadIdx.x & 63, r16 = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int row0 = t.tm * (2 * WROWS) + (wave >> 2) * WROWS;           // first row of the wavefront
+    const int row0 = row_base + t.tm * (2 * WROWS) + (wave >> 2) * WROWS;           // first row of the wavefront
     const int lane_col = (q & 1) * 16 + (q >> 1) * 8;
     // byte offset of the lane's 8 columns, column pair p, in a 16-row block
     auto lane_offset = [&](int64_t row_bytes, int es, int col0, int p) {
@@ -149,35 +201,32 @@ __device__ __forceinline__ void stream_epilogue(const GemmArgs& P, const StreamT
         o.rows = Meff - row0;
         const uint32_t off[2] = {lane_offset(o.row_bytes, es, col0, 0), lane_offset(o.row_bytes, es, col0, 1)};
         if (P.out_f32 && !P.accumulate) {
-            for_row_blocks<MI>(o, off, [&](__amdgpu_buffer_rsrc_t d, const uint32_t (&at)[2], auto mi) {
-                static_for<2>([&](auto p) {
-                    const Cols8 c = swap_cols(acc[mi][2 * p], acc[mi][2 * p + 1]);
-                    const f32x4 lo = {c.v[0], c.v[1], c.v[2], c.v[3]}, hi = {c.v[4], c.v[5], c.v[6], c.v[7]};
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, lo), d, (int)at[p], 0, 0);
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, hi), d, (int)at[p] + 16, 0, 0);
-                });
+            for_row_blocks<MI>(o, [&](auto desc, auto at, auto mi) {
+                const __amdgpu_buffer_rsrc_t d = desc(o);
+                static_for<2>([&](auto p) { store_f32(swap_cols(acc[mi][2 * p], acc[mi][2 * p + 1]), d, at(off[p])); });
             });
         } else if (P.out_f32) {
-            for_row_blocks<MI>(o, off, [&](__amdgpu_buffer_rsrc_t d, const uint32_t (&at)[2], auto mi) {
+            for_row_blocks<MI>(o, [&](auto desc, auto at, auto mi) {
+                const __amdgpu_buffer_rsrc_t d = desc(o);
                 f32x4 old[4];
-                static_for<4>([&](auto h) { old[h] = buf_load_f32x4(d, at[h >> 1] + (h & 1) * 16); });
+                static_for<4>([&](auto h) { old[h] = buf_load_f32x4(d, at(off[h >> 1]) + (h & 1) * 16); });
                 static_for<2>([&](auto p) {
-                    const Cols8 c = swap_cols(acc[mi][2 * p], acc[mi][2 * p + 1]);
-                    const f32x4 lo = {c.v[0], c.v[1], c.v[2], c.v[3]}, hi = {c.v[4], c.v[5], c.v[6], c.v[7]};
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, lo + old[2 * p]), d, (int)at[p], 0, 0);
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, hi + old[2 * p + 1]), d, (int)at[p] + 16, 0, 0);
+                    Cols8 c = swap_cols(acc[mi][2 * p], acc[mi][2 * p + 1]);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) { c.v[k] += old[2 * p][k]; c.v[4 + k] += old[2 * p + 1][k]; }
+                    store_f32(c, d, at(off[p]));
                 });
             });
         } else if (!P.accumulate) {
-            for_row_blocks<MI>(o, off, [&](__amdgpu_buffer_rsrc_t d, const uint32_t (&at)[2], auto mi) {
-                static_for<2>([&](auto p) {
-                    __builtin_amdgcn_raw_buffer_store_b128(pack_cols(swap_cols(acc[mi][2 * p], acc[mi][2 * p + 1])), d, (int)at[p], 0, 0);
-                });
+            for_row_blocks<MI>(o, [&](auto desc, auto at, auto mi) {
+                const __amdgpu_buffer_rsrc_t d = desc(o);
+                static_for<2>([&](auto p) { buf_store(pack_cols(swap_cols(acc[mi][2 * p], acc[mi][2 * p + 1])), d, at(off[p])); });
             });
         } else {
-            for_row_blocks<MI>(o, off, [&](__amdgpu_buffer_rsrc_t d, const uint32_t (&at)[2], auto mi) {
+            for_row_blocks<MI>(o, [&](auto desc, auto at, auto mi) {
+                const __amdgpu_buffer_rsrc_t d = desc(o);
                 u32x4 old[2];
-                static_for<2>([&](auto p) { old[p] = __builtin_amdgcn_raw_buffer_load_b128(d, (int)at[p], 0, 0); });
+                static_for<2>([&](auto p) { old[p] = __builtin_amdgcn_raw_buffer_load_b128(d, (int)at(off[p]), 0, 0); });
                 static_for<2>([&](auto p) {
                     Cols8 c = swap_cols(acc[mi][2 * p], acc[mi][2 * p + 1]);
 #pragma unroll
@@ -185,17 +234,66 @@ __device__ __forceinline__ void stream_epilogue(const GemmArgs& P, const StreamT
                         c.v[2 * k] += bf16lo_to_f32(old[p][k]);
                         c.v[2 * k + 1] += bf16hi_to_f32(old[p][k]);
                     }
-                    __builtin_amdgcn_raw_buffer_store_b128(pack_cols(c), d, (int)at[p], 0, 0);
+                    buf_store(pack_cols(c), d, at(off[p]));
                 });
             });
         }
+    } else if constexpr (EPI == EPI_PARTIAL) {
+        const int col0 = t.tn * BN + (wave & 3) * 64;
+        OutRows o;
+        o.row_bytes = (int64_t)P.N * 4;
+        o.base = reinterpret_cast<char*>(P.partial) + ((int64_t)t.z * P.M + row0) * o.row_bytes + col0 * 4;
+        o.rows = Meff - row0;
+        const uint32_t off[2] = {lane_offset(o.row_bytes, 4, col0, 0), lane_offset(o.row_bytes, 4, col0, 1)};
+        for_row_blocks<MI>(o, [&](auto desc, auto at, auto mi) {
+            const __amdgpu_buffer_rsrc_t d = desc(o);
+            static_for<2>([&](auto p) { store_f32(swap_cols(acc[mi][2 * p], acc[mi][2 * p + 1]), d, at(off[p])); });
+        });
+    } else if constexpr (EPI == EPI_SWIGLU) {
+        // fragments 0, 1: 32 columns of gate, 2, 3: the same of up
+        const int col0 = t.tn * (BN / 2) + (wave & 3) * 32;
+        OutRows h;
+        h.row_bytes = (int64_t)P.ldo * 2;
+        h.base = static_cast<char*>(P.out0) + row0 * h.row_bytes + col0 * 2;
+        h.rows = Meff - row0;
+        OutRows g = h, u = h;
+        g.base = static_cast<char*>(P.out1) + row0 * h.row_bytes + col0 * 2;
+        u.base = static_cast<char*>(P.out2) + row0 * h.row_bytes + col0 * 2;
+        const uint32_t off = lane_offset(h.row_bytes, 2, col0, 0);
+        const bool saved = P.out1 != nullptr, transposed = P.outT0 != nullptr;
+        const TransposedBlock tb(scratch, lane);
+        // the lane's column and first row in the transposed copy, columns 16 further on for the second half
+        bf16_t* to = static_cast<bf16_t*>(P.outT0) + (int64_t)(col0 + r16) * P.ldt + row0 + 8 * q;
+        for_row_blocks<MI>(h, [&](auto desc, auto at, auto mi) {
+            const Cols8 gc = swap_cols(acc[mi][0], acc[mi][1]), uc = swap_cols(acc[mi][2], acc[mi][3]);
+            Cols8 hc;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) hc.v[k] = gc.v[k] * sigmoid_f(gc.v[k]) * uc.v[k];
+            const u32x4 hp = pack_cols(hc);
+            buf_store(hp, desc(h), at(off));
+            if (saved) {
+                buf_store(pack_cols(gc), desc(g), at(off));
+                buf_store(pack_cols(uc), desc(u), at(off));
+            }
+            if (transposed) {
+                tb.template put<mi & 1>(hp);
+                if constexpr ((mi & 1) == 1) {
+                    u32x4 c0, c1;
+                    tb.get(c0, c1);
+                    if (row0 + (mi - 1) * 16 + 8 * q < P.ldt) {
+                        if (col0 + r16 < P.N) *reinterpret_cast<u32x4*>(to + (mi - 1) * 16) = c0;
+                        if (col0 + 16 + r16 < P.N) *reinterpret_cast<u32x4*>(to + (int64_t)16 * P.ldt + (mi - 1) * 16) = c1;
+                    }
+                }
+            }
+        });
     }
 }
 
-// All 512 threads of the workgroup call it with the same arguments.  K of an operand whose rows are zero from Keff to the
+// All 512 threads of the workgroup call it with the same arguments; tile rows count from row_base.  K of an operand whose rows are zero from Keff to the
 // next multiple of 64 may be passed rounded up: only a slab that reaches past Keff masks its lanes.
 template <int MI, bool B_KC, int EPI, class Work>
-__device__ __forceinline__ void stream_gemm(const GemmArgs& P, const Work work, const int Meff, const int Keff) {
+__device__ __forceinline__ void stream_gemm(const GemmArgs& P, const Work work, const int Meff, const int Keff, const int row_base = 0) {
     constexpr bool GU = EPI == EPI_SWIGLU;   // B tile = 128 rows of W_gate + 128 of W_up
     constexpr int TM = 32 * MI, WROWS = 16 * MI;
     constexpr int STAGE_A = TM * 128, NSA = kStreamRingA<MI>, A_AHEAD = NSA - 1, B_BASE = NSA * STAGE_A;
@@ -239,11 +337,12 @@ __device__ __forceinline__ void stream_gemm(const GemmArgs& P, const Work work, 
     // they travel in lane masks.)
     const int ktp = Keff > 0 ? (Keff + BK - 1) / BK : 1;     // slabs of an operand pair; K = 0: one slab of zeros (empty operands)
     const bool ragged = Keff % BK != 0;                      // the last slab of a pair reaches past K
+    const uint32_t a_base = (uint32_t)row_base * (uint32_t)P.lda * 2u;
     const uint32_t a_tile = (uint32_t)TM * (uint32_t)P.lda * 2u, a_end = Keff > 0 ? (uint32_t)Meff * (uint32_t)P.lda * 2u : 0u;
     const uint32_t b_tile = B_KC ? (uint32_t)(GU ? BN / 2 : BN) * (uint32_t)P.ldb * 2u : BN * 2u;
     const uint32_t b_end = Keff > 0 ? (uint32_t)(B_KC ? P.N : Keff) * (uint32_t)P.ldb * 2u : 0u;
     const uint32_t bstep = B_KC ? BK * 2u : (uint32_t)BK * (uint32_t)P.ldb * 2u;
-    const bool pairs = P.pairs == 2;
+    constexpr bool PAIRS = !B_KC && EPI == EPI_PARTIAL;      // dXn: K runs over (A0, B0), then (A1, B1)
     // *_kt: slab within the operand pair; *_left: slabs until the pair or the tile ends (0: the list has ended), of which
     // the last *_mask reach past K; *_more: slabs of the tile after that
     int a_i = 0, a_kt = 0, a_left = 0, a_more = 0, a_mask = 0, b_i = 0, b_kt = 0, b_left = 0, b_more = 0, b_mask = 0;
@@ -251,7 +350,7 @@ __device__ __forceinline__ void stream_gemm(const GemmArgs& P, const Work work, 
     StreamTile a_t = tile, b_t = tile;
     __amdgpu_buffer_rsrc_t a_src, b_src;
     auto open_a = [&](int second) {
-        const uint32_t o = (uint32_t)a_t.tm * a_tile;
+        const uint32_t o = a_base + (uint32_t)a_t.tm * a_tile;
         a_src = uniform_rsrc(second ? P.A1 : P.A0, o, a_end > o ? a_end - o : 0u);
         a_step = (uint32_t)a_kt * (BK * 2u);
         a_mask = ragged && a_kt + a_left == ktp ? 1 : 0;
@@ -263,19 +362,19 @@ __device__ __forceinline__ void stream_gemm(const GemmArgs& P, const Work work, 
         b_mask = ragged && b_kt + b_left == ktp ? 1 : 0;
     };
     auto begin_a = [&]() {                                   // tile a_t
-        const int second = pairs && a_t.kb >= ktp ? 1 : 0;
+        const int second = PAIRS && a_t.kb >= ktp ? 1 : 0;
         a_kt = a_t.kb - (second ? ktp : 0);
         a_left = a_t.ke - a_t.kb;
         a_more = 0;
-        if (pairs && !second && a_t.ke > ktp) { a_more = a_t.ke - ktp; a_left -= a_more; }
+        if (PAIRS && !second && a_t.ke > ktp) { a_more = a_t.ke - ktp; a_left -= a_more; }
         open_a(second | (a_t.second ? 1 : 0));
     };
     auto begin_b = [&]() {
-        const int second = pairs && b_t.kb >= ktp ? 1 : 0;
+        const int second = PAIRS && b_t.kb >= ktp ? 1 : 0;
         b_kt = b_t.kb - (second ? ktp : 0);
         b_left = b_t.ke - b_t.kb;
         b_more = 0;
-        if (pairs && !second && b_t.ke > ktp) { b_more = b_t.ke - ktp; b_left -= b_more; }
+        if (PAIRS && !second && b_t.ke > ktp) { b_more = b_t.ke - ktp; b_left -= b_more; }
         open_b(second);
     };
     uint32_t a_ld = region_a * 1024, b_ld = B_BASE + wave * 4096;        // LDS offsets this wavefront loads to
@@ -287,7 +386,7 @@ __device__ __forceinline__ void stream_gemm(const GemmArgs& P, const Work work, 
         a_step += BK * 2u;
         ++a_kt;
         if (--a_left == 0) {
-            if (a_more > 0) {
+            if (PAIRS && a_more > 0) {
                 a_left = a_more; a_more = 0; a_kt = 0;
                 open_a(1);
             } else if (work.get(++a_i, a_t)) {
@@ -301,7 +400,7 @@ __device__ __forceinline__ void stream_gemm(const GemmArgs& P, const Work work, 
         b_step += bstep;
         ++b_kt;
         if (--b_left == 0) {
-            if (b_more > 0) {
+            if (PAIRS && b_more > 0) {
                 b_left = b_more; b_more = 0; b_kt = 0;
                 open_b(1);
             } else if (work.get(++b_i, b_t)) {
@@ -449,12 +548,15 @@ __device__ __forceinline__ void stream_gemm(const GemmArgs& P, const Work work, 
         phase_barrier();
     };
     StreamTile done = tile;                                  // the tile whose sums are in acc
+    // LDS for the epilogue: this wavefront's part of the stage that the tile's last slab of B was read from, which it
+    // fills again itself, after the epilogue
+    auto scratch = [&]() { return lds0 + B_BASE + wave * 4096 + (rd_b == 0 ? (kStreamRingB - 1) * OPER_BYTES : rd_b - OPER_BYTES); };
     for (int i = 0;;) {
         // M(0, 0): the tile before leaves while the loads for this one fly
         load_a();
         if (i > 0) {
             __builtin_amdgcn_sched_barrier(0);
-            stream_epilogue<MI, EPI>(P, done, Meff, acc);
+            stream_epilogue<MI, EPI>(P, done, Meff, row_base, acc, scratch());
             __builtin_amdgcn_sched_barrier(0);
         }
         read_frags(k0, std::false_type{});
@@ -481,18 +583,46 @@ __device__ __forceinline__ void stream_gemm(const GemmArgs& P, const Work work, 
         if (!work.get(++i, tile)) break;
     }
     if (wm == 0) phase_barrier();                            // balances group 1's extra barrier
-    stream_epilogue<MI, EPI>(P, done, Meff, acc);
+    stream_epilogue<MI, EPI>(P, done, Meff, row_base, acc, scratch());
 }
 
+// Tiles over the rows [row_base, rows); `after` tiles have been dealt to the workgroups already
 template <int MI, bool B_KC, int EPI>
+__device__ __forceinline__ void stream_grid(const GemmArgs& P, const int rows, const int Meff, const int Keff, const int row_base = 0,
+                                            const int after = 0) {
+    constexpr bool SPLIT = EPI == EPI_STORE || EPI == EPI_PARTIAL;
+    const GridWork<SPLIT> w((int)blockIdx.x, (int)gridDim.x, (rows - row_base + 32 * MI - 1) / (32 * MI), P.tiles_n, P.splits, P.batch,
+                            (Keff > 0 ? (Keff + BK - 1) / BK : 1) * P.pairs, after);
+    stream_gemm<MI, B_KC, EPI>(P, w, Meff, Keff, row_base);
+}
+
+// 256-row tiles
+template <bool B_KC, int EPI>
 __global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_kernel(GemmArgs P) {
     const int Meff = effective_rows(P.M, P.m_dev);
     int Keff = effective_rows(P.K, P.k_dev);
     if (EPI == EPI_STORE) Keff = (Keff + BK - 1) / BK * BK;  // the transposed copies are zero up to the next multiple of 64
+    if (Meff > 0) stream_grid<8, B_KC, EPI>(P, Meff, Meff, Keff);
+}
+
+// tiles of the heights that suit the row count
+template <bool B_KC, int EPI>
+__global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_rows_kernel(GemmArgs P) {
+    const int Meff = effective_rows(P.M, P.m_dev), Keff = effective_rows(P.K, P.k_dev);
     if (Meff <= 0) return;
-    const GridWork w((int)blockIdx.x, (int)gridDim.x, (Meff + 32 * MI - 1) / (32 * MI), P.tiles_n, P.splits, P.batch,
-                     (Keff > 0 ? (Keff + BK - 1) / BK : 1) * P.pairs);
-    stream_gemm<MI, B_KC, EPI>(P, w, Meff, Keff);
+    const StreamRows plan = stream_rows_plan(Meff, P.tiles_n, (int)gridDim.x, P.outT0 != nullptr);
+    const int base = plan.full * 256 < Meff ? plan.full * 256 : Meff, after = plan.full * P.tiles_n;
+    if (plan.full > 0) {
+        stream_grid<8, B_KC, EPI>(P, base, Meff, Keff);
+        if (plan.mi == 0) return;
+        lds_barrier();                                       // other stages, other parts of them
+    }
+    switch (plan.mi) {                                       // uniform
+        case 4: stream_grid<4, B_KC, EPI>(P, Meff, Meff, Keff, base, after); break;
+        case 5: stream_grid<5, B_KC, EPI>(P, Meff, Meff, Keff, base, after); break;
+        case 6: stream_grid<6, B_KC, EPI>(P, Meff, Meff, Keff, base, after); break;
+        default: stream_grid<7, B_KC, EPI>(P, Meff, Meff, Keff, base, after); break;
+    }
 }
 
 }  // namespace skipffn

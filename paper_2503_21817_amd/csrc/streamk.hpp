@@ -118,4 +118,41 @@ SKIPFFN_HD inline bool streamk_next(const StreamKPlan& p, StreamKIter& it, Strea
     return true;
 }
 
+// Output tiles of a GEMM with `rows` rows and `tiles_n` tile columns on `cus` workgroups: `full` rows of tiles of 256 rows,
+// then tiles of 32 * mi rows (mi = 4 .. 7) over the rest, if any.  (The kernels plan with the row count on the device.)
+//
+// A round of tiles costs 34 + 6.5 mi us (measured, gate/up at C = 4096, I = 14336: 60, 67, 74, 79, 86 a round for mi = 4 .. 8
+// on 448 to 2944 rows; a slab's phases and loads do not shrink with the rows).  So tall tiles win unless others leave fewer
+// rows empty or save a round, or a last row of lower tiles fits where tall ones end unevenly: 368 rows 93 us on 192-row
+// tiles, 102 on 256; 640 rows 139 on 160, 163; 768 rows 148 on 192, 165; 1200 rows 245 on 224, 250; 940, 1472 and 2048
+// rows best on 256.  Between the two parts the pipeline drains once (about 5 us); a sixteenth of the work in all decides
+// between equal makespans.  even: heights of 64 rows only (transposed copies are zero up to a multiple of 64 rows).
+struct StreamRows { int full, mi; };
+SKIPFFN_HD inline int stream_tile_cost(int mi) { return 68 + 13 * mi; }
+SKIPFFN_HD inline StreamRows stream_rows_plan(int rows, int tiles_n, int cus, bool even) {
+    const int tall = stream_tile_cost(8);
+    StreamRows best{(rows + 255) / 256, 0};
+    int n = best.full * tiles_n;
+    int best_cost = (n + cus - 1) / cus * tall + n / 16 * tall / cus;
+    for (int mi = 7; mi >= 4; --mi) {
+        if (even && (mi & 1)) continue;
+        n = (rows + 32 * mi - 1) / (32 * mi) * tiles_n;
+        const int cost = (n + cus - 1) / cus * stream_tile_cost(mi) + n / 16 * stream_tile_cost(mi) / cus;
+        if (cost < best_cost) { best = StreamRows{0, mi}; best_cost = cost; }
+    }
+    const int full = rows / 256, rest = rows - full * 256;
+    int mi = (rest + 31) / 32;
+    mi = mi < 4 ? 4 : (even ? (mi + 1) / 2 * 2 : mi);
+    if (full > 0 && rest > 0 && mi < 8) {
+        // the tall tiles go round the workgroups, the low ones on from there
+        const int low = stream_tile_cost(mi), q = full * tiles_n / cus, r = full * tiles_n - q * cus;
+        const int after = r + tiles_n;                       // low tiles end here, counted from the first workgroup of the last round
+        int span = q * tall + (r > 0 ? tall : 0);
+        if (after > cus || r == 0) span = q * tall + (r > 0 ? tall : 0) + (after - (r > 0 ? cus : 0) + cus - 1) / cus * low;
+        const int cost = span + 10 + (full * tiles_n / 16 * tall + tiles_n / 16 * low) / cus;
+        if (cost < best_cost) best = StreamRows{full, mi};
+    }
+    return best;
+}
+
 }  // namespace skipffn

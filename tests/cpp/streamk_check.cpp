@@ -49,6 +49,20 @@ int main() {
                 }
                 ++cases;
             }
+    // tile rows of the row plan: all rows covered, no tile row without rows, the heights that exist
+    for (int even = 0; even < 2; ++even)
+        for (int tiles_n : {1, 6, 17, 56, 65, 112, 300})
+            for (int rows = 1; rows <= 3000; rows += rows < 700 ? 1 : 13) {
+                const StreamRows p = stream_rows_plan(rows, tiles_n, 256, even != 0);
+                const int base = p.full * 256, step = 32 * p.mi;
+                const bool low = p.mi >= 4 && p.mi <= 7 && (!even || p.mi % 2 == 0);
+                if ((p.mi == 0 && (base < rows || base - rows >= 256)) || (p.mi != 0 && (!low || base >= rows)) ||
+                    (p.full > 0 && p.mi != 0 && rows - base > step)) {
+                    printf("rows=%d tiles_n=%d even=%d: full=%d mi=%d\n", rows, tiles_n, even, p.full, p.mi);
+                    return 1;
+                }
+                ++cases;
+            }
     printf("ok %ld\n", cases);
     return 0;
 }

@@ -797,3 +797,30 @@ def test_weight_gradients_of_more_tiles_than_compute_units(R, flags):
         for axis in (0, 1):
             err, size = np.linalg.norm(got - want, axis=axis), np.linalg.norm(want, axis=axis)
             assert np.all(err < REL_L2_TOL * (size + 4 * np.sqrt(np.mean(size ** 2)))), (k, axis)
+
+
+@pytest.mark.parametrize("R,I", [(257, 8264), (385, 8264), (481, 8264), (577, 8264), (673, 8264), (769, 8264), (1400, 12808)])
+@pytest.mark.parametrize("r_host", [True, False], ids=["R-host", "R-device"])
+@pytest.mark.parametrize("saved", [False, True], ids=["inference", "training"])
+def test_gate_up_tile_heights(R, I, r_host, saved):
+    """65 tile columns: without a saved buffer tiles of 128, 160, 192, 224, 256 and 128 rows, with one (heights of 64 rows
+    only) of 128, 192, 192, 256, 256 and 128; row counts one past a tile's height, where the last is nearly empty.  101
+    tile columns and 1400 rows: five rows of 256-row tiles, then one of 128.
+    Every row is checked on its own, the transposed copy bit for bit, zeros up to the next multiple of 64 rows included."""
+    from helpers import max_slice_rel_l2
+    w = W.small(C=264, I=I, visual=(R + 30,), text=(9,), keep=(R - 9,), seed=3300 + R, name=f"heights-{R}")
+    assert w.R == R
+    p = Problem(w)
+    fo = O.skipffn_forward(p.hidden, p.mask, p.wg, p.wu, p.wd, None, w.eps)
+    idx, sk = fo["idx"], p.mask != 0
+    out, bufs = gpu_forward(p, R_host=r_host, saved=saved)
+    got = bits_of(out)
+    assert np.array_equal(got[sk], p.hidden[sk])
+    assert max_slice_rel_l2(O.bf16_bits_to_f64(got[idx]), O.bf16_bits_to_f64(fo["out_bits"][idx]), axis=1) < REL_L2_TOL
+    if saved:
+        sv = bufs.saved_views(R)
+        for k in ("G", "U", "H"):
+            assert max_slice_rel_l2(f64_of(sv[k]), fo[k], axis=1) < REL_L2_TOL, k
+        h, ht = bits_of(sv["H"]), bits_of(sv["HT"])
+        assert np.array_equal(ht[:, :R], h.T)
+        assert not ht[:, R:(R + 63) // 64 * 64].any()
