@@ -351,7 +351,7 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
         const int ktiles = (int)((I + BK - 1) / BK);
         const KPartition kp = plan.k_down;
         a.splits = kp.splits;
-        a.idx = idx; a.ldo = (int)C;
+        a.idx = idx; a.ldo = (int)C; a.ncu = num_cus();
         a.no_residual = no_residual;
         profile_mark_begin(KC_GEMM_DOWN, s);
         if (kp.splits == 1 && kp.sk_nbg == 0) {
@@ -502,7 +502,7 @@ int skipffn_backward(int64_t T, int64_t C, int64_t I, float eps, const void* gra
         const int ktiles = 2 * (int)((I + BK - 1) / BK);
         const KPartition kp = choose_k_partition(tiles_m, tiles_n, ktiles, (flags & SKIPFFN_FLAG_BALANCED_SPLIT) != 0,
                                                  num_cus());
-        a.splits = kp.splits;
+        a.splits = kp.splits; a.ncu = num_cus();
         pl = PartialLayout{kp.splits, kp.sk_nbg, ktiles};
         a.partial = partial;
         profile_mark_begin(KC_GEMM_DXN, s);

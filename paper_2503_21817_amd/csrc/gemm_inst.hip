@@ -16,18 +16,16 @@ static hipError_t set_stream_lds(void (*kernel)(GemmArgs)) {
 
 hipError_t gemm_init() {
     hipError_t e;
-    if ((e = set_stream_lds(&stream_gemm_kernel<true, EPI_STORE>)) != hipSuccess) return e;
-    if ((e = set_stream_lds(&stream_gemm_rows_kernel<true, EPI_SWIGLU>)) != hipSuccess) return e;
-    if ((e = set_lds_limit<true, true, EPI_PARTIAL>()) != hipSuccess) return e;
-    if ((e = set_lds_limit<true, true, EPI_RESID_SCATTER>()) != hipSuccess) return e;
+    if ((e = set_stream_lds(&stream_gemm_kernel<EPI_STORE>)) != hipSuccess) return e;
+    if ((e = set_stream_lds(&stream_gemm_rows_kernel<EPI_SWIGLU>)) != hipSuccess) return e;
+    if ((e = set_stream_lds(&stream_gemm_kernel<EPI_PARTIAL>)) != hipSuccess) return e;
+    if ((e = set_stream_lds(&stream_gemm_kernel<EPI_RESID_SCATTER>)) != hipSuccess) return e;
+    if ((e = set_stream_lds(&stream_gemm_balanced_kernel)) != hipSuccess) return e;
     if ((e = set_lds_limit<true, false, EPI_PARTIAL>()) != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_dual_kernel<true, false, EPI_SWIGLU_BWD, true, true, EPI_STORE>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS_BYTES);
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_streamk_kernel<true, true>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS_BYTES);
-    if (e != hipSuccess) return e;
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_streamk_kernel<true, false>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS_BYTES);
+    if (e != hipSuccess) return e;
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_dual_kernel<true, false, EPI_SWIGLU_BWD, true, true, EPI_STORE>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS_BYTES);
     if (e != hipSuccess) return e;
     return hipSuccess;
@@ -56,7 +54,7 @@ static hipError_t launch_one(const GemmArgs& a, hipStream_t s) {
 // One workgroup per CU, a multiple of the 8 XCDs; fewer where the tiles, counted at their smallest height, are fewer
 template <int EPI>
 static hipError_t launch_stream(void (*kernel)(GemmArgs), const GemmArgs& a, hipStream_t s) {
-    const int height = EPI == EPI_STORE ? 256 : 128;
+    const int height = EPI == EPI_SWIGLU ? 128 : 256;
     const unsigned cus = (unsigned)(a.ncu >= 8 ? a.ncu / 8 * 8 : 8);
     const unsigned tiles = ((unsigned)((a.M + height - 1) / height * a.tiles_n * a.splits * a.batch) + 7) / 8 * 8;
     hipLaunchKernelGGL(kernel, dim3(tiles < cus ? tiles : cus), dim3(GEMM_THREADS), kStreamLds, s, a);
@@ -83,21 +81,19 @@ hipError_t launch_gemm_streamk(bool a_kc, bool b_kc, GemmArgs& a, int nbg, hipSt
     a.splits = nbg;
     const unsigned blocks = (unsigned)(a.tiles_n * nbg);
     if (b_kc)
-        hipLaunchKernelGGL((gemm_bf16_streamk_kernel<true, true>), dim3(blocks), dim3(GEMM_THREADS),
-                           GEMM_LDS_BYTES, s, a);
+        hipLaunchKernelGGL(stream_gemm_balanced_kernel, dim3(blocks), dim3(GEMM_THREADS), kStreamLds, s, a);
     else
-        hipLaunchKernelGGL((gemm_bf16_streamk_kernel<true, false>), dim3(blocks), dim3(GEMM_THREADS),
-                           GEMM_LDS_BYTES, s, a);
+        hipLaunchKernelGGL((gemm_bf16_streamk_kernel<true, false>), dim3(blocks), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_gemm(bool a_kc, bool b_kc, int epi, GemmArgs& a, hipStream_t s) {
     finish_args(epi, a);
     if (grid_blocks(a) == 0 || a.tiles_n <= 0) return hipSuccess;
-    if (a_kc && b_kc && epi == EPI_SWIGLU) return launch_stream<EPI_SWIGLU>(&stream_gemm_rows_kernel<true, EPI_SWIGLU>, a, s);
-    if (a_kc && b_kc && epi == EPI_PARTIAL) return launch_one<true, true, EPI_PARTIAL>(a, s);
-    if (a_kc && b_kc && epi == EPI_RESID_SCATTER) return launch_one<true, true, EPI_RESID_SCATTER>(a, s);
-    if (a_kc && b_kc && epi == EPI_STORE) return launch_stream<EPI_STORE>(&stream_gemm_kernel<true, EPI_STORE>, a, s);
+    if (a_kc && b_kc && epi == EPI_SWIGLU) return launch_stream<EPI_SWIGLU>(&stream_gemm_rows_kernel<EPI_SWIGLU>, a, s);
+    if (a_kc && b_kc && epi == EPI_PARTIAL) return launch_stream<EPI_PARTIAL>(&stream_gemm_kernel<EPI_PARTIAL>, a, s);
+    if (a_kc && b_kc && epi == EPI_RESID_SCATTER) return launch_stream<EPI_RESID_SCATTER>(&stream_gemm_kernel<EPI_RESID_SCATTER>, a, s);
+    if (a_kc && b_kc && epi == EPI_STORE) return launch_stream<EPI_STORE>(&stream_gemm_kernel<EPI_STORE>, a, s);
     if (a_kc && !b_kc && epi == EPI_PARTIAL) return launch_one<true, false, EPI_PARTIAL>(a, s);
     return hipErrorInvalidValue;
 }

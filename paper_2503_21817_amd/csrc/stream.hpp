@@ -1,5 +1,7 @@
 // The GEMM core as a stream: a workgroup runs a list of output tiles, and the K slabs of all of them pass through one
-// pipeline.  (gemm.hpp: operand layouts, LDS swizzles, epilogue kinds, the ping-pong schedule.)
+// pipeline; both operands K-contiguous.  (gemm.hpp: operand layouts, LDS swizzles, epilogue kinds, the ping-pong
+// schedule.)  The GEMMs with an N-contiguous operand stay there, a tile at a time: their memory phases are the longer ones,
+// and with the cursors of a stream in them dXn took 675 us instead of 640 at 4096 rows.
 //
 // With one tile per workgroup a tile costs 11.5 us beside its slabs (1.15 us each): the launch, the first loads, and an
 // epilogue that goes through LDS in passes with barriers between them.  Here the loads of the next tile are under way
@@ -20,8 +22,10 @@ template <int MI>
 constexpr int kStreamRingA = (GEMM_LDS_BYTES - kStreamRingB * OPER_BYTES) / (MI * 4096) < 3 ? 2 : 3;
 constexpr int kStreamLds = GEMM_LDS_BYTES;
 
-// A value that is the same in all lanes, in a scalar register: descriptors that the compiler keeps in vector registers
-// turn every load into a loop over the lanes.
+// A value that is the same in all lanes, in a scalar register.  Divisions and loads of the row count leave their
+// results in vector registers, and a descriptor that comes from there turns every load into a loop over the lanes (dW at
+// 1472 rows 250 -> 320 us).
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(const void* base, uint32_t offset, uint32_t bytes) {
     const uint64_t p = reinterpret_cast<uint64_t>(base) + offset;
@@ -34,7 +38,7 @@ struct StreamTile { int tm, tn, z, kb, ke; bool second; };
 // variable costs as much as a memory phase.  m >= 2^32 / d, so the product is at most one too large.
 struct TileDiv {
     uint32_t d, m;
-    __device__ __forceinline__ explicit TileDiv(int v) : d((uint32_t)v), m(0xFFFFFFFFu / (uint32_t)(v > 1 ? v : 2) + 1) {}
+    __device__ __forceinline__ explicit TileDiv(int v) : d((uint32_t)v), m(uniform(0xFFFFFFFFu / (uint32_t)(v > 1 ? v : 2) + 1)) {}
     __device__ __forceinline__ int div(int n) const {
         if (d == 1) return n;
         const uint32_t q = __umulhi((uint32_t)n, m);
@@ -56,10 +60,11 @@ struct GridWork {
           last_panel(tiles_m_ % PANEL_M != 0 ? tiles_m_ % PANEL_M : PANEL_M), split_tiles(SPLIT ? tiles_m_ * tiles_n : 1),
           splits(SPLIT ? splits_ : 1), per_k(SPLIT ? (ktiles_ + splits_ - 1) / splits_ : ktiles_) {
         const int nb = tiles_m * tiles_n * (SPLIT ? splits * batch : 1), xcd = block & 7, q = nb >> 3, rem = nb & 7;
+        per_k = uniform(per_k);
         step = workgroups >> 3;
         const int before = (after >> 3) + (xcd < (after & 7) ? 1 : 0);               // of this XCD
         int slot = (block >> 3) - before % step;
-        slot = slot < 0 ? slot + step : slot;
+        slot = uniform(slot < 0 ? slot + step : slot);
         first = xcd * q + (xcd < rem ? xcd : rem) + slot;
         count = q + (xcd < rem ? 1 : 0) - slot;
     }
@@ -82,6 +87,52 @@ struct GridWork {
         t.z = t.second ? z - splits : z;
         t.kb = t.z * per_k;
         t.ke = SPLIT && t.kb + per_k >= ktiles ? ktiles : t.kb + per_k;
+        return true;
+    }
+};
+
+// The share of a workgroup in the balanced split of streamk.hpp (the segments streamk_next yields, by index): workgroup j of
+// the group of tile column tn.
+struct BalancedWork {
+    int tn, j, nbg, full, base, kt, ke_whole;
+    int aligned, tile0, kb0, ke0, slot0;      // an aligned chunk: one segment after the whole tiles
+    int rem, u0, u_end, ir0, a, rj; TileDiv qr;           // or pieces [u0, u_end) of the remainders laid end to end
+    __device__ __forceinline__ BalancedWork(const StreamKPlan& p, int tn_, int j_)
+        : tn(tn_), j(j_), nbg(p.nbg), full(p.full), base(p.base), kt(p.kt), ke_whole(p.kt), aligned(j_ < p.a * p.gr ? 1 : 0),
+          tile0(0), kb0(0), ke0(0), slot0(0), rem(p.rem), u0(0), u_end(0), ir0(0), a(p.a), rj(j_ - p.a * p.gr), qr(p.qr) {
+        if (aligned) {
+            slot0 = j / p.gr;
+            tile0 = base + j - slot0 * p.gr;
+            kb0 = slot0 * p.q;
+            ke0 = kb0 + p.q;
+        } else if (rj < p.nr) {
+            u0 = rj * p.qr;
+            u_end = u0 + p.qr < p.gr * rem ? u0 + p.qr : p.gr * rem;
+            ir0 = u0 / rem;
+        }
+        tn = uniform(tn); j = uniform(j); full = uniform(full); base = uniform(base); aligned = uniform(aligned);
+        tile0 = uniform(tile0); kb0 = uniform(kb0); ke0 = uniform(ke0); slot0 = uniform(slot0);
+        rem = uniform(rem); u0 = uniform(u0); u_end = uniform(u_end); ir0 = uniform(ir0); a = uniform(a); rj = uniform(rj);
+        qr.d = uniform(qr.d);
+    }
+    __device__ __forceinline__ bool get(const int i, StreamTile& t) const {
+        t.tn = tn;
+        t.second = false;
+        if (i < full) {
+            t.tm = i * nbg + j; t.z = 0; t.kb = 0; t.ke = ke_whole;
+            return true;
+        }
+        const int k = i - full;
+        if (aligned) {
+            t.tm = tile0; t.z = slot0; t.kb = kb0; t.ke = ke0;
+            return k == 0;
+        }
+        const int ir = ir0 + k, first = ir * rem, u = first > u0 ? first : u0;
+        if (u >= u_end) return false;
+        t.tm = base + ir;
+        t.z = a + rj - qr.div(first);
+        t.kb = kt - rem + u - first;
+        t.ke = kt - rem + (first + rem < u_end ? rem : u_end - first);
         return true;
     }
 };
@@ -249,6 +300,38 @@ __device__ __forceinline__ void stream_epilogue(const GemmArgs& P, const StreamT
             const __amdgpu_buffer_rsrc_t d = desc(o);
             static_for<2>([&](auto p) { store_f32(swap_cols(acc[mi][2 * p], acc[mi][2 * p + 1]), d, at(off[p])); });
         });
+    } else if constexpr (EPI == EPI_RESID_SCATTER) {
+        // rows idx[row] of out and of the residual (the same tensor in place: a lane reads what it writes); below 2 GiB
+        const int col0 = t.tn * BN + (wave & 3) * 64;
+        const __amdgpu_buffer_rsrc_t res = make_rsrc(P.e0, kOobOffset), out = make_rsrc(P.out0, kOobOffset);
+        uint32_t at[MI][2];
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) {
+            const int row = row0 + mi * 16 + r16;
+            const uint32_t r = row < Meff ? (uint32_t)P.idx[row] * (uint32_t)P.ldo : 0u;
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const int col = col0 + lane_col + 32 * p;
+                at[mi][p] = row < Meff && col < P.N ? (r + (uint32_t)col) * 2u : kOobOffset;
+            }
+        }
+        static_for<MI / 2>([&](auto h) {
+            u32x4 x[2][2];
+            if (!P.no_residual)
+                static_for<4>([&](auto k) { x[k >> 1][k & 1] = buf_load16(res, at[2 * h + (k >> 1)][k & 1]); });
+            static_for<4>([&](auto k) {
+                constexpr int mi = 2 * h + (k >> 1), p = k & 1;
+                Cols8 c = swap_cols(acc[mi][2 * p], acc[mi][2 * p + 1]);
+                if (!P.no_residual) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        c.v[2 * e] += bf16lo_to_f32(x[k >> 1][p][e]);
+                        c.v[2 * e + 1] += bf16hi_to_f32(x[k >> 1][p][e]);
+                    }
+                }
+                buf_store(pack_cols(c), out, at[mi][p]);
+            });
+        });
     } else if constexpr (EPI == EPI_SWIGLU) {
         // fragments 0, 1: 32 columns of gate, 2, 3: the same of up
         const int col0 = t.tn * (BN / 2) + (wave & 3) * 32;
@@ -292,7 +375,7 @@ __device__ __forceinline__ void stream_epilogue(const GemmArgs& P, const StreamT
 
 // All 512 threads of the workgroup call it with the same arguments; tile rows count from row_base.  K of an operand whose rows are zero from Keff to the
 // next multiple of 64 may be passed rounded up: only a slab that reaches past Keff masks its lanes.
-template <int MI, bool B_KC, int EPI, class Work>
+template <int MI, int EPI, class Work>
 __device__ __forceinline__ void stream_gemm(const GemmArgs& P, const Work work, const int Meff, const int Keff, const int row_base = 0) {
     constexpr bool GU = EPI == EPI_SWIGLU;   // B tile = 128 rows of W_gate + 128 of W_up
     constexpr int TM = 32 * MI, WROWS = 16 * MI;
@@ -323,59 +406,41 @@ __device__ __forceinline__ void stream_gemm(const GemmArgs& P, const Work work, 
 #pragma unroll
     for (int l = 0; l < 4; ++l) {
         const int qb = wave * 4 + l;
-        if (B_KC) {
-            const int row = 8 * qb + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
-            b_goff[l] = lane_off(((int64_t)(GU ? row & 127 : row) * P.ldb + c * 8) * 2);
-        } else {
-            const int krow = 2 * qb + (lane >> 5), pslot = lane & 31;
-            b_goff[l] = lane_off(((int64_t)krow * P.ldb + (2 * ((pslot >> 1) ^ mnc_swz(krow)) + (pslot & 1)) * 8) * 2);
-        }
+        const int row = 8 * qb + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
+        b_goff[l] = lane_off(((int64_t)(GU ? row & 127 : row) * P.ldb + c * 8) * 2);
     }
 
     // ---- load cursors: the next slab of A (of B) to fetch, A_AHEAD (2) slabs ahead of the one that is read.  Operands
     // are smaller than 2 GiB, so offsets of existing tiles fit 32 bits.  (Flags are kept as integers: as truth values
     // they travel in lane masks.)
-    const int ktp = Keff > 0 ? (Keff + BK - 1) / BK : 1;     // slabs of an operand pair; K = 0: one slab of zeros (empty operands)
-    const bool ragged = Keff % BK != 0;                      // the last slab of a pair reaches past K
+    const int ktp = Keff > 0 ? (Keff + BK - 1) / BK : 1;     // slabs of K; K = 0: one slab of zeros (empty operands)
+    const int ragged = Keff % BK != 0 ? 1 : 0;               // the last one reaches past K
     const uint32_t a_base = (uint32_t)row_base * (uint32_t)P.lda * 2u;
     const uint32_t a_tile = (uint32_t)TM * (uint32_t)P.lda * 2u, a_end = Keff > 0 ? (uint32_t)Meff * (uint32_t)P.lda * 2u : 0u;
-    const uint32_t b_tile = B_KC ? (uint32_t)(GU ? BN / 2 : BN) * (uint32_t)P.ldb * 2u : BN * 2u;
-    const uint32_t b_end = Keff > 0 ? (uint32_t)(B_KC ? P.N : Keff) * (uint32_t)P.ldb * 2u : 0u;
-    const uint32_t bstep = B_KC ? BK * 2u : (uint32_t)BK * (uint32_t)P.ldb * 2u;
-    constexpr bool PAIRS = !B_KC && EPI == EPI_PARTIAL;      // dXn: K runs over (A0, B0), then (A1, B1)
-    // *_kt: slab within the operand pair; *_left: slabs until the pair or the tile ends (0: the list has ended), of which
-    // the last *_mask reach past K; *_more: slabs of the tile after that
-    int a_i = 0, a_kt = 0, a_left = 0, a_more = 0, a_mask = 0, b_i = 0, b_kt = 0, b_left = 0, b_more = 0, b_mask = 0;
+    const uint32_t b_tile = (uint32_t)(GU ? BN / 2 : BN) * (uint32_t)P.ldb * 2u;
+    const uint32_t b_end = Keff > 0 ? (uint32_t)P.N * (uint32_t)P.ldb * 2u : 0u;
+    // *_left: slabs until the tile ends (0: the list has ended), of which the last *_mask reach past K
+    int a_i = 0, a_kt = 0, a_left = 0, a_mask = 0, b_i = 0, b_kt = 0, b_left = 0, b_mask = 0;
     uint32_t a_step = 0, b_step = 0;
     StreamTile a_t = tile, b_t = tile;
     __amdgpu_buffer_rsrc_t a_src, b_src;
-    auto open_a = [&](int second) {
-        const uint32_t o = a_base + (uint32_t)a_t.tm * a_tile;
-        a_src = uniform_rsrc(second ? P.A1 : P.A0, o, a_end > o ? a_end - o : 0u);
-        a_step = (uint32_t)a_kt * (BK * 2u);
-        a_mask = ragged && a_kt + a_left == ktp ? 1 : 0;
-    };
-    auto open_b = [&](int second) {
-        const uint32_t o = (uint32_t)b_t.tn * b_tile;
-        b_src = uniform_rsrc((GU ? wave >= 4 : second) ? P.B1 : P.B0, o, b_end > o ? b_end - o : 0u);   // GU: regions 16 .. = rows 128 ..
-        b_step = (uint32_t)b_kt * bstep;
-        b_mask = ragged && b_kt + b_left == ktp ? 1 : 0;
-    };
     auto begin_a = [&]() {                                   // tile a_t
-        const int second = PAIRS && a_t.kb >= ktp ? 1 : 0;
-        a_kt = a_t.kb - (second ? ktp : 0);
+        a_kt = a_t.kb;
         a_left = a_t.ke - a_t.kb;
-        a_more = 0;
-        if (PAIRS && !second && a_t.ke > ktp) { a_more = a_t.ke - ktp; a_left -= a_more; }
-        open_a(second | (a_t.second ? 1 : 0));
+        a_mask = ragged - (ktp - a_t.ke);
+        a_mask = a_mask > 0 ? a_mask : 0;
+        const uint32_t o = a_base + (uint32_t)a_t.tm * a_tile;
+        a_src = uniform_rsrc(a_t.second ? P.A1 : P.A0, o, a_end > o ? a_end - o : 0u);
+        a_step = (uint32_t)a_kt * (BK * 2u);
     };
-    auto begin_b = [&]() {
-        const int second = PAIRS && b_t.kb >= ktp ? 1 : 0;
-        b_kt = b_t.kb - (second ? ktp : 0);
+    auto begin_b = [&]() {                                   // tile b_t
+        b_kt = b_t.kb;
         b_left = b_t.ke - b_t.kb;
-        b_more = 0;
-        if (PAIRS && !second && b_t.ke > ktp) { b_more = b_t.ke - ktp; b_left -= b_more; }
-        open_b(second);
+        b_mask = ragged - (ktp - b_t.ke);
+        b_mask = b_mask > 0 ? b_mask : 0;
+        const uint32_t o = (uint32_t)b_t.tn * b_tile;
+        b_src = uniform_rsrc(GU && wave >= 4 ? P.B1 : P.B0, o, b_end > o ? b_end - o : 0u);       // GU: regions 16 .. = rows 128 ..
+        b_step = (uint32_t)b_kt * (BK * 2u);
     };
     uint32_t a_ld = region_a * 1024, b_ld = B_BASE + wave * 4096;        // LDS offsets this wavefront loads to
     const uint32_t a_ld_end = NSA * STAGE_A + region_a * 1024, b_ld_end = B_BASE + kStreamRingB * OPER_BYTES + wave * 4096;
@@ -386,26 +451,16 @@ __device__ __forceinline__ void stream_gemm(const GemmArgs& P, const Work work, 
         a_step += BK * 2u;
         ++a_kt;
         if (--a_left == 0) {
-            if (PAIRS && a_more > 0) {
-                a_left = a_more; a_more = 0; a_kt = 0;
-                open_a(1);
-            } else if (work.get(++a_i, a_t)) {
-                begin_a();
-            }
+            if (work.get(++a_i, a_t)) begin_a();
         }
     };
     auto step_b = [&]() {
         b_ld += OPER_BYTES;
         if (b_ld == b_ld_end) b_ld -= kStreamRingB * OPER_BYTES;
-        b_step += bstep;
+        b_step += BK * 2u;
         ++b_kt;
         if (--b_left == 0) {
-            if (PAIRS && b_more > 0) {
-                b_left = b_more; b_more = 0; b_kt = 0;
-                open_b(1);
-            } else if (work.get(++b_i, b_t)) {
-                begin_b();
-            }
+            if (work.get(++b_i, b_t)) begin_b();
         }
     };
     auto load_a1 = [&](auto l, uint32_t off) {
@@ -438,7 +493,7 @@ __device__ __forceinline__ void stream_gemm(const GemmArgs& P, const Work work, 
             asm volatile("; K tail" ::: "memory");
             static_for<4>([&](auto l) {
                 const int qb = wave * 4 + l, row = 8 * qb + (lane >> 3);
-                const int kk = b_kt * BK + (B_KC ? ((lane & 7) ^ ((row >> 1) & 7)) * 8 : 2 * qb + (lane >> 5));
+                const int kk = b_kt * BK + ((lane & 7) ^ ((row >> 1) & 7)) * 8;
                 load_b1(l, kk < Keff ? b_goff[l] : kOobOffset);
             });
             asm volatile("; K tail end" ::: "memory");
@@ -447,17 +502,12 @@ __device__ __forceinline__ void stream_gemm(const GemmArgs& P, const Work work, 
     };
 
     // ---- fragment reads: see gemm.hpp
-    uint32_t a_rd[2], b_rd[B_KC ? 2 : 4];
+    uint32_t a_rd[2], b_rd[2];
     const int b_row0 = GU ? wn * 32 : wn * 64;
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
         a_rd[ks] = lds0 + kc_off(wm * WROWS + (lane & 15), 4 * ks + (lane >> 4));
-        if (B_KC) b_rd[ks] = lds0 + B_BASE + kc_off(b_row0 + (lane & 15), 4 * ks + (lane >> 4));
-    }
-    if (!B_KC) {
-#pragma unroll
-        for (int ni = 0; ni < 4; ++ni)
-            b_rd[ni] = lds0 + B_BASE + mnc_off(8 * (lane >> 4) + ((lane & 15) >> 2), (b_row0 >> 4) + ni, 8 * (lane & 3));
+        b_rd[ks] = lds0 + B_BASE + kc_off(b_row0 + (lane & 15), 4 * ks + (lane >> 4));
     }
     uint32_t rd_a = 0, rd_b = 0;                             // byte offsets of the stages that are read
     f32x4 acc[MI][4];
@@ -467,7 +517,7 @@ __device__ __forceinline__ void stream_gemm(const GemmArgs& P, const Work work, 
         constexpr int KS = decltype(ks)::value;
         constexpr int NL = !decltype(loads)::value ? 0 : (KS == 0 ? AL0 : 4), NR = MI + 4;
         const uint32_t aa = a_rd[KS] + rd_a;
-        const uint32_t ba = B_KC ? b_rd[KS] + rd_b : rd_b;
+        const uint32_t ba = b_rd[KS] + rd_b;
         static_for<NR>([&](auto r) {
             static_for<NL>([&](auto l) {
                 if constexpr (l * NR / (NL > 0 ? NL : 1) == r) {
@@ -476,16 +526,9 @@ __device__ __forceinline__ void stream_gemm(const GemmArgs& P, const Work work, 
             });
             if constexpr (r < MI) {
                 af[r] = ds_read_b128_imm<r * 2048>(aa);
-            } else if constexpr (B_KC) {
-                constexpr int ni = r - MI;
-                bfr[ni] = ds_read_b128_imm<GU ? (ni >> 1) * 16384 + (ni & 1) * 2048 : ni * 2048>(ba);
             } else {
                 constexpr int ni = r - MI;
-                const uint32_t bn = b_rd[ni] + ba;
-                const u32x2 lo = ds_read_tr16_b64_imm<KS * 16384>(bn);
-                const u32x2 hi = ds_read_tr16_b64_imm<KS * 16384 + 2048>(bn);
-                const u32x4 both = {lo[0], lo[1], hi[0], hi[1]};
-                bfr[ni] = __builtin_bit_cast(bf16x8, both);
+                bfr[ni] = ds_read_b128_imm<GU ? (ni >> 1) * 16384 + (ni & 1) * 2048 : ni * 2048>(ba);
             }
         });
     };
@@ -587,42 +630,71 @@ __device__ __forceinline__ void stream_gemm(const GemmArgs& P, const Work work, 
 }
 
 // Tiles over the rows [row_base, rows); `after` tiles have been dealt to the workgroups already
-template <int MI, bool B_KC, int EPI>
+template <int MI, int EPI>
 __device__ __forceinline__ void stream_grid(const GemmArgs& P, const int rows, const int Meff, const int Keff, const int row_base = 0,
                                             const int after = 0) {
     constexpr bool SPLIT = EPI == EPI_STORE || EPI == EPI_PARTIAL;
     const GridWork<SPLIT> w((int)blockIdx.x, (int)gridDim.x, (rows - row_base + 32 * MI - 1) / (32 * MI), P.tiles_n, P.splits, P.batch,
                             (Keff > 0 ? (Keff + BK - 1) / BK : 1) * P.pairs, after);
-    stream_gemm<MI, B_KC, EPI>(P, w, Meff, Keff, row_base);
+    stream_gemm<MI, EPI>(P, w, Meff, Keff, row_base);
 }
 
 // 256-row tiles
-template <bool B_KC, int EPI>
+template <int EPI>
 __global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_kernel(GemmArgs P) {
-    const int Meff = effective_rows(P.M, P.m_dev);
-    int Keff = effective_rows(P.K, P.k_dev);
+    const int Meff = uniform(effective_rows(P.M, P.m_dev));
+    int Keff = uniform(effective_rows(P.K, P.k_dev));
     if (EPI == EPI_STORE) Keff = (Keff + BK - 1) / BK * BK;  // the transposed copies are zero up to the next multiple of 64
-    if (Meff > 0) stream_grid<8, B_KC, EPI>(P, Meff, Meff, Keff);
+    if (Meff > 0) stream_grid<8, EPI>(P, Meff, Meff, Keff);
 }
 
 // tiles of the heights that suit the row count
-template <bool B_KC, int EPI>
+template <int EPI>
 __global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_rows_kernel(GemmArgs P) {
-    const int Meff = effective_rows(P.M, P.m_dev), Keff = effective_rows(P.K, P.k_dev);
+    const int Meff = uniform(effective_rows(P.M, P.m_dev)), Keff = uniform(effective_rows(P.K, P.k_dev));
     if (Meff <= 0) return;
-    const StreamRows plan = stream_rows_plan(Meff, P.tiles_n, (int)gridDim.x, P.outT0 != nullptr);
+    StreamRows plan = stream_rows_plan(Meff, P.tiles_n, (int)gridDim.x, P.outT0 != nullptr);
+    plan = StreamRows{uniform(plan.full), uniform(plan.mi)};
     const int base = plan.full * 256 < Meff ? plan.full * 256 : Meff, after = plan.full * P.tiles_n;
     if (plan.full > 0) {
-        stream_grid<8, B_KC, EPI>(P, base, Meff, Keff);
+        stream_grid<8, EPI>(P, base, Meff, Keff);
         if (plan.mi == 0) return;
         lds_barrier();                                       // other stages, other parts of them
     }
     switch (plan.mi) {                                       // uniform
-        case 4: stream_grid<4, B_KC, EPI>(P, Meff, Meff, Keff, base, after); break;
-        case 5: stream_grid<5, B_KC, EPI>(P, Meff, Meff, Keff, base, after); break;
-        case 6: stream_grid<6, B_KC, EPI>(P, Meff, Meff, Keff, base, after); break;
-        default: stream_grid<7, B_KC, EPI>(P, Meff, Meff, Keff, base, after); break;
+        case 4: stream_grid<4, EPI>(P, Meff, Meff, Keff, base, after); break;
+        case 5: stream_grid<5, EPI>(P, Meff, Meff, Keff, base, after); break;
+        case 6: stream_grid<6, EPI>(P, Meff, Meff, Keff, base, after); break;
+        default: stream_grid<7, EPI>(P, Meff, Meff, Keff, base, after); break;
     }
+}
+
+// The balanced split-K of streamk.hpp into fp32 slabs.  grid = tiles_n * nbg workgroups (P.splits carries nbg)
+__global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_balanced_kernel(GemmArgs P) {
+    const int nbg = P.splits, nb = (int)gridDim.x, tiles_n = nb / nbg;
+    int b = (int)blockIdx.x;
+    // workgroups are dealt round-robin to the 8 XCDs: give each XCD a contiguous range of the order below
+    if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);
+    const int Meff = uniform(effective_rows(P.M, P.m_dev)), Keff = uniform(effective_rows(P.K, P.k_dev));
+    const int g = (Meff + BM - 1) / BM, kt = ((Keff + BK - 1) / BK) * P.pairs;
+    if (g == 0 || kt == 0) return;
+    const StreamKPlan p = streamk_plan(g, kt, nbg);
+    // Aligned chunks first, chunk-major, then tile column, then tile row - so an XCD works on ONE K range of many tile
+    // columns (the tile rows of a column share the weight slabs, the columns share the activation slabs, and no XCD
+    // streams the whole K extent of the activations); the remainder pieces follow.
+    int tn, j;
+    const int gr = p.gr, aligned_total = p.a * gr * tiles_n;
+    if (b < aligned_total) {
+        const int c = b / (tiles_n * gr), r = b - c * (tiles_n * gr);
+        tn = r / gr;
+        j = c * gr + (r - tn * gr);
+    } else {
+        const int per = nbg - p.a * gr;           // workgroups per group left for the remainder
+        const int r = b - aligned_total;
+        tn = r / per;
+        j = p.a * gr + (r - tn * per);
+    }
+    stream_gemm<8, EPI_PARTIAL>(P, BalancedWork(p, tn, j), Meff, Keff);
 }
 
 }  // namespace skipffn
