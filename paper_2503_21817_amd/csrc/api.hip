@@ -468,7 +468,7 @@ int skipffn_backward(int64_t T, int64_t C, int64_t I, float eps, const void* gra
         b.A0 = dYT; b.lda = ldT; b.a_bytes = (uint32_t)(C * (int64_t)ldT * 2);   // K (= R) contiguous
         b.B0 = HT; b.ldb = ldT; b.b_bytes = (uint32_t)(I * (int64_t)ldT * 2);
         b.pairs = 1; b.splits = 1;
-        b.out0 = dw_down; b.ldo = (int)I; b.out_f32 = f32; b.accumulate = accum;
+        b.out0 = dw_down; b.ldo = (int)I; b.out_f32 = f32; b.accumulate = accum; b.ncu = num_cus();
         profile_mark_begin(KC_GEMM_DH_DWDOWN, s);
         e = launch_gemm_dual(DUAL_DH_DWDOWN, a, b, s);
         profile_mark_end(KC_GEMM_DH_DWDOWN, s);

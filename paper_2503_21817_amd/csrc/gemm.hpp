@@ -881,22 +881,6 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_kernel(GemmArgs P) {
     gemm_block<A_KC, B_KC, EPI>(P, (int)blockIdx.x);
 }
 
-// Two independent GEMMs in one grid: workgroups [0, nblocks0) run problem 0 (launched
-// first: give it the longer tiles), the rest problem 1, so the last round of one fills
-// with tiles of the other instead of leaving CUs idle.  nblocks0 is a multiple of 8 (the
-// host pads with workgroups that exit at once) so that both problems see the round-robin
-// XCD assignment from its start.
-template <bool A0_KC, bool B0_KC, int EPI0, bool A1_KC, bool B1_KC, int EPI1>
-__global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_dual_kernel(GemmArgs P0, GemmArgs P1,
-                                                                      int nblocks0) {
-    const int b = (int)blockIdx.x;
-    if (b < nblocks0) {
-        gemm_block<A0_KC, B0_KC, EPI0>(P0, b);      // workgroups past its tiles leave
-    } else {
-        gemm_block<A1_KC, B1_KC, EPI1>(P1, b - nblocks0);
-    }
-}
-
 // ---- balanced split-K for GEMMs that leave through fp32 partial slabs (see streamk.hpp) ------
 // grid = tiles_n * nbg workgroups (P.splits carries nbg); EPI_PARTIAL only
 template <bool A_KC, bool B_KC>

@@ -1,8 +1,23 @@
 // Instantiations and launcher of the bf16 MFMA GEMM core.
+#include <algorithm>
+
 #include "kernels.hpp"
 #include "stream.hpp"
 
 namespace skipffn {
+
+// dH with the SwiGLU backward in its epilogue and dW_down, which depend on each other in nothing, in one grid: workgroups
+// [0, n0) run a tile of dH each (the longer ones, dispatched first), the rest lists of tiles of dW_down, so the last round
+// of one fills with work of the other.  n0 is a multiple of 8 (workgroups past the tiles leave at once): both problems see the
+// round-robin XCD assignment from its start.  dW_down as a stream, sums stored from registers, us a launch before / after:
+// 368 rows 126 / 122, 640 rows 177 / 172, 2944 rows 604 / 590, 4096 rows 811 / 805.
+__global__ __launch_bounds__(GEMM_THREADS) void gemm_dh_dw_down_kernel(GemmArgs P0, GemmArgs P1, int n0) {
+    const int b = (int)blockIdx.x;
+    if (b < n0)
+        gemm_block<true, false, EPI_SWIGLU_BWD>(P0, b);
+    else
+        stream_tall<EPI_STORE>(P1, b - n0, (int)gridDim.x - n0);
+}
 
 template <bool A_KC, bool B_KC, int EPI>
 static hipError_t set_lds_limit() {
@@ -25,7 +40,7 @@ hipError_t gemm_init() {
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_streamk_kernel<true, false>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS_BYTES);
     if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_dual_kernel<true, false, EPI_SWIGLU_BWD, true, true, EPI_STORE>),
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dh_dw_down_kernel),
                             hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS_BYTES);
     if (e != hipSuccess) return e;
     return hipSuccess;
@@ -65,12 +80,13 @@ hipError_t launch_gemm_dual(int which, GemmArgs& a0, GemmArgs& a1, hipStream_t s
     if (which != DUAL_DH_DWDOWN) return hipErrorInvalidValue;
     finish_args(EPI_SWIGLU_BWD, a0);
     finish_args(EPI_STORE, a1);
-    const int real0 = (int)grid_blocks(a0);
-    const int n0 = (real0 + 7) / 8 * 8;
-    const int n1 = a1.tiles_m * a1.tiles_n * a1.splits * a1.batch;
-    if (real0 <= 0 || n1 <= 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((gemm_bf16_dual_kernel<true, false, EPI_SWIGLU_BWD, true, true, EPI_STORE>),
-                       dim3((unsigned)(n0 + n1)), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a0, a1, n0);
+    const int real0 = (int)grid_blocks(a0), n0 = (real0 + 7) / 8 * 8, tiles1 = (int)grid_blocks(a1);
+    if (real0 <= 0 || tiles1 <= 0) return hipErrorInvalidValue;
+    // lists of about 16 slabs (of short tiles several, whose ends overlap; no longer: they also even out the end of the
+    // grid), and no fewer lists than compute units
+    const int slabs = std::max((a1.K + BK - 1) / BK, 1), per = std::max(std::min(16 / slabs, tiles1 / std::max(a1.ncu, 1)), 1);
+    const int n1 = ((tiles1 + per - 1) / per + 7) / 8 * 8;
+    hipLaunchKernelGGL(gemm_dh_dw_down_kernel, dim3((unsigned)(n0 + n1)), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a0, a1, n0);
     return hipGetLastError();
 }
 

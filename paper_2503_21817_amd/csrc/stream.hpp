@@ -631,21 +631,25 @@ __device__ __forceinline__ void stream_gemm(const GemmArgs& P, const Work work, 
 
 // Tiles over the rows [row_base, rows); `after` tiles have been dealt to the workgroups already
 template <int MI, int EPI>
-__device__ __forceinline__ void stream_grid(const GemmArgs& P, const int rows, const int Meff, const int Keff, const int row_base = 0,
-                                            const int after = 0) {
+__device__ __forceinline__ void stream_grid(const GemmArgs& P, const int block, const int workgroups, const int rows, const int Meff,
+                                            const int Keff, const int row_base = 0, const int after = 0) {
     constexpr bool SPLIT = EPI == EPI_STORE || EPI == EPI_PARTIAL;
-    const GridWork<SPLIT> w((int)blockIdx.x, (int)gridDim.x, (rows - row_base + 32 * MI - 1) / (32 * MI), P.tiles_n, P.splits, P.batch,
+    const GridWork<SPLIT> w(block, workgroups, (rows - row_base + 32 * MI - 1) / (32 * MI), P.tiles_n, P.splits, P.batch,
                             (Keff > 0 ? (Keff + BK - 1) / BK : 1) * P.pairs, after);
     stream_gemm<MI, EPI>(P, w, Meff, Keff, row_base);
 }
 
-// 256-row tiles
+// 256-row tiles: workgroup `block` of `workgroups`
 template <int EPI>
-__global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_kernel(GemmArgs P) {
+__device__ __forceinline__ void stream_tall(const GemmArgs& P, const int block, const int workgroups) {
     const int Meff = uniform(effective_rows(P.M, P.m_dev));
     int Keff = uniform(effective_rows(P.K, P.k_dev));
     if (EPI == EPI_STORE) Keff = (Keff + BK - 1) / BK * BK;  // the transposed copies are zero up to the next multiple of 64
-    if (Meff > 0) stream_grid<8, EPI>(P, Meff, Meff, Keff);
+    if (Meff > 0) stream_grid<8, EPI>(P, block, workgroups, Meff, Meff, Keff);
+}
+template <int EPI>
+__global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_kernel(GemmArgs P) {
+    stream_tall<EPI>(P, (int)blockIdx.x, (int)gridDim.x);
 }
 
 // tiles of the heights that suit the row count
@@ -653,19 +657,20 @@ template <int EPI>
 __global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_rows_kernel(GemmArgs P) {
     const int Meff = uniform(effective_rows(P.M, P.m_dev)), Keff = uniform(effective_rows(P.K, P.k_dev));
     if (Meff <= 0) return;
-    StreamRows plan = stream_rows_plan(Meff, P.tiles_n, (int)gridDim.x, P.outT0 != nullptr);
+    const int b = (int)blockIdx.x, nb = (int)gridDim.x;
+    StreamRows plan = stream_rows_plan(Meff, P.tiles_n, nb, P.outT0 != nullptr);
     plan = StreamRows{uniform(plan.full), uniform(plan.mi)};
     const int base = plan.full * 256 < Meff ? plan.full * 256 : Meff, after = plan.full * P.tiles_n;
     if (plan.full > 0) {
-        stream_grid<8, EPI>(P, base, Meff, Keff);
+        stream_grid<8, EPI>(P, b, nb, base, Meff, Keff);
         if (plan.mi == 0) return;
         lds_barrier();                                       // other stages, other parts of them
     }
     switch (plan.mi) {                                       // uniform
-        case 4: stream_grid<4, EPI>(P, Meff, Meff, Keff, base, after); break;
-        case 5: stream_grid<5, EPI>(P, Meff, Meff, Keff, base, after); break;
-        case 6: stream_grid<6, EPI>(P, Meff, Meff, Keff, base, after); break;
-        default: stream_grid<7, EPI>(P, Meff, Meff, Keff, base, after); break;
+        case 4: stream_grid<4, EPI>(P, b, nb, Meff, Meff, Keff, base, after); break;
+        case 5: stream_grid<5, EPI>(P, b, nb, Meff, Meff, Keff, base, after); break;
+        case 6: stream_grid<6, EPI>(P, b, nb, Meff, Meff, Keff, base, after); break;
+        default: stream_grid<7, EPI>(P, b, nb, Meff, Meff, Keff, base, after); break;
     }
 }
 
