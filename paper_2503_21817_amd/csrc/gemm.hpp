@@ -1,4 +1,6 @@
-// bf16 MFMA GEMM core for gfx950 with the fused epilogues of the Skip-FFN block.
+// bf16 MFMA GEMM core for gfx950: the parts every GEMM of the Skip-FFN block shares, and the kernels of the two GEMMs whose
+// weight operand is N-contiguous (dH with the SwiGLU backward in its epilogue, dXn).  The GEMMs with two K-contiguous
+// operands run lists of tiles on the same schedule (stream.hpp).
 //
 // One workgroup = 512 threads = 8 wavefronts (2 per SIMD) computes a 256 x 256
 // tile of C = A * B with fp32 accumulation, stepping K in slabs of 64.  Waves
@@ -14,8 +16,9 @@
 // staging, no ds_write) and with no transposition: KC tiles are read back with
 // ds_read_b128 (8 consecutive k per lane), MNC tiles with the transposing
 // ds_read_b64_tr_b16 of gfx950, which hands each lane 4 consecutive k for its own
-// column (two of them make the 8 consecutive k of an MFMA operand register set).  XOR swizzles, applied on the global-address side of the direct loads,
-// keep both read patterns free of LDS bank conflicts.
+// column (two of them make the 8 consecutive k of an MFMA operand register set).  XOR
+// swizzles, applied on the global-address side of the direct loads, keep both read
+// patterns free of LDS bank conflicts.
 //
 // LDS (160 KB) holds a ring of 2 A slabs and 3 B slabs of 256 x 64 (32 KB each):
 // B is the operand that streams from HBM in every GEMM of the block (weights, or
@@ -60,7 +63,7 @@ struct GemmArgs {
     const int32_t* k_dev;        // optional device count replacing K
     const bf16_t* A0; const bf16_t* A1; int lda; uint32_t a_bytes;
     const bf16_t* B0; const bf16_t* B1; int ldb; uint32_t b_bytes;
-    int pairs;                   // 1, or 2: K runs over (A0,B0) then (A1,B1)
+    int pairs;                   // 1, or 2: K runs over (A0,B0) then (A1,B1).  2 with an N-contiguous B only
     int splits;                  // split-K factor
     int batch;                   // 1, or 2 independent problems: (A0 -> out0), (A1 -> out1) sharing B.  pairs == 1
     int tiles_m, tiles_n;
@@ -74,8 +77,6 @@ struct GemmArgs {
     int accumulate;              // EPI_STORE: 1 = +=
     int no_residual;             // EPI_RESID_SCATTER: 1 = do not add the residual
     int ncu;                     // compute units: workgroups of a kernel that runs lists of tiles (stream.hpp)
-    int tail_narrow;             // 1 = a last tile row of at most 128 rows is a row of 128-row tiles, run by
-                                 // the last tiles_n live workgroups of the grid
 };
 
 // Row offsets of up to SEG_TABLE_MAX token sets, passed by value in the kernel arguments
@@ -192,31 +193,16 @@ __device__ __forceinline__ void tile_of_block(int b, int nb, int tiles_m, int ti
     tm = p * PANEL_M + (in_panel - tn * pm);
 }
 
-// One output tile (tm, tn) over the K slabs [kt_begin, kt_end) of the concatenated pairs;
+// One output tile (tm, tn) over the K slabs [kt_begin, kt_end) of the concatenated pairs, A K-contiguous, B N-contiguous;
 // z selects the fp32 slab an EPI_PARTIAL result goes to.
-//
-// NARROW: the tile is 128 rows tall (a last tile row of at most 128 rows: half the MFMA work per slab).  The eight
-// waves keep their 2 x 4 arrangement, each owning 64 x 64 = 4 x 4 MFMA tiles; only the first
-// 16 KB of an A stage are used.  KC A operands only.
-template <bool A_KC, bool B_KC, int EPI, bool NARROW = false>
+template <int EPI>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const int tn, const int z,
                                           const int kt_begin, const int kt_end, const int Meff,
                                           const int Keff) {
-    static_assert(A_KC, "the A operand of every GEMM of the block is K-contiguous");
-    constexpr int TM = NARROW ? BM / 2 : BM;        // tile rows
-    constexpr int WROWS = TM / 2;                   // rows per wave row group
+    static_assert(EPI == EPI_PARTIAL || EPI == EPI_SWIGLU_BWD, "the other epilogues belong to the stream of tiles");
+    constexpr int WROWS = BM / 2;                   // rows per wave row group
     constexpr int MT = WROWS / 32;                  // epilogue passes (32 rows per row group each)
     constexpr int MI = WROWS / 16;                  // MFMA tiles per wave along M (4 along N)
-    constexpr int A_LOADS = TM / 64;                // 1 KB regions of an A slab each wave fills
-    constexpr bool GU = EPI == EPI_SWIGLU;   // B tile = 128 rows of W_gate + 128 of W_up
-    // The A ring: 2 stages of 32 KB, fetched one slab ahead - or, for the 128-row tile, 3 stages
-    // of 16 KB fetched two slabs ahead, in the same phase as B: issuing everything in the first phase of
-    // slab j lets a load stay in flight for 2 slab times instead of 1 (A) and 1.4 (B), 4-6 % faster.
-    constexpr int NSA = NARROW ? 3 : NSTAGE_A;
-    constexpr int A_STAGE = NARROW ? OPER_BYTES / 2 : OPER_BYTES;
-    constexpr int A_AHEAD = NARROW ? 2 : 1;
-    constexpr int B_BASE = NSA * A_STAGE;
-    static_assert(B_BASE + NSTAGE_B * OPER_BYTES <= GEMM_LDS_BYTES, "operand rings must fit in LDS");
     extern __shared__ __align__(16) char smem[];
     const int t = threadIdx.x;
     const int lane = t & 63;
@@ -224,8 +210,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
     const int wm = wave >> 2;      // 0..1
     const int wn = wave & 3;       // 0..3
 
-    const int m0 = tm * TM;
-    const int n0 = GU ? tn * (BN / 2) : tn * BN;
+    const int m0 = tm * BM;
+    const int n0 = tn * BN;
     const int ktiles_pair = (Keff + BK - 1) / BK;
     const int nk = kt_end > kt_begin ? kt_end - kt_begin : 0;
 
@@ -247,22 +233,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
     for (int i = 0; i < 4; ++i) {
         const int q = wave * 4 + i;
         {
-            const int qa = wave * A_LOADS + i;      // regions of A: wave w owns A_LOADS consecutive ones
-            int row = 8 * qa + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
+            int row = 8 * q + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
             int gr = m0 + row;
             a_goff[i] = gr < Meff ? (uint32_t)(((int64_t)gr * P.lda + c * 8) * 2) : kOobOffset;
         }
-        if (B_KC) {
-            int row = 8 * q + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
-            // SWIGLU: tile rows 0..127 are W_gate rows, 128..255 the same rows of W_up
-            int gr = GU ? n0 + (row & 127) : n0 + row;
-            b_goff[i] = gr < P.N ? (uint32_t)(((int64_t)gr * P.ldb + c * 8) * 2) : kOobOffset;
-        } else {
-            int krow = 2 * q + (lane >> 5), pslot = lane & 31;
-            int c16 = 2 * ((pslot >> 1) ^ mnc_swz(krow)) + (pslot & 1);
-            int gc = n0 + c16 * 8;
-            b_goff[i] = gc < P.N ? (uint32_t)(((int64_t)krow * P.ldb + gc) * 2) : kOobOffset;
-        }
+        int krow = 2 * q + (lane >> 5), pslot = lane & 31;
+        int c16 = 2 * ((pslot >> 1) ^ mnc_swz(krow)) + (pslot & 1);
+        int gc = n0 + c16 * 8;
+        b_goff[i] = gc < P.N ? (uint32_t)(((int64_t)krow * P.ldb + gc) * 2) : kOobOffset;
     }
     typedef __attribute__((address_space(3))) void* lds_void_ptr;
     // Issue this wave's share of A slab j / B slab j (0-based inside this block's K range).
@@ -277,17 +255,17 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
         const int pair = kt >= ktiles_pair ? 1 : 0;
         const int kg = (kt - pair * ktiles_pair) * BK;  // k offset inside the pair
         __amdgpu_buffer_rsrc_t src = pair ? rA1 : rA0;
-        char* dst = smem + (j % NSA) * A_STAGE + wave * (A_LOADS * 1024);
+        char* dst = smem + (j % NSTAGE_A) * OPER_BYTES + wave * 4096;
         const uint32_t step = (uint32_t)kg * 2u;
         if (kg + BK <= Keff) {
 #pragma unroll
-            for (int i = 0; i < A_LOADS; ++i)
+            for (int i = 0; i < 4; ++i)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (lds_void_ptr)(dst + i * 1024), 16, (int)a_goff[i], (int)step, 0, 0);
         } else {
             asm volatile("; K tail" ::: "memory");
 #pragma unroll
-            for (int i = 0; i < A_LOADS; ++i) {
-                const int row = 8 * (wave * A_LOADS + i) + (lane >> 3);
+            for (int i = 0; i < 4; ++i) {
+                const int row = 8 * (wave * 4 + i) + (lane >> 3);
                 const int kk = ((lane & 7) ^ ((row >> 1) & 7)) * 8;
                 const uint32_t off = (a_goff[i] != kOobOffset && kg + kk < Keff) ? a_goff[i] + step : kOobOffset;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (lds_void_ptr)(dst + i * 1024), 16, (int)off, 0, 0, 0);
@@ -300,9 +278,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
         const int pair = kt >= ktiles_pair ? 1 : 0;
         const int kg = (kt - pair * ktiles_pair) * BK;
         __amdgpu_buffer_rsrc_t src = pair ? rB1 : rB0;
-        if (GU) src = wave >= 4 ? rB1 : rB0;   // regions 16.. = rows 128..
-        char* dst = smem + B_BASE + (j % NSTAGE_B) * OPER_BYTES + wave * 4096;
-        const uint32_t step = B_KC ? (uint32_t)kg * 2u : (uint32_t)(((int64_t)kg * P.ldb) * 2);
+        char* dst = smem + LDS_B_BASE + (j % NSTAGE_B) * OPER_BYTES + wave * 4096;
+        const uint32_t step = (uint32_t)(((int64_t)kg * P.ldb) * 2);
         if (kg + BK <= Keff) {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
@@ -311,13 +288,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
             asm volatile("; K tail" ::: "memory");
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                int kk;
-                if (B_KC) {
-                    const int row = 8 * (wave * 4 + i) + (lane >> 3);
-                    kk = ((lane & 7) ^ ((row >> 1) & 7)) * 8;
-                } else {
-                    kk = 2 * (wave * 4 + i) + (lane >> 5);
-                }
+                const int kk = 2 * (wave * 4 + i) + (lane >> 5);
                 const uint32_t off = (b_goff[i] != kOobOffset && kg + kk < Keff) ? b_goff[i] + step : kOobOffset;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (lds_void_ptr)(dst + i * 1024), 16, (int)off, 0, 0, 0);
             }
@@ -334,22 +305,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
             for (int r = 0; r < 4; ++r) acc[mi][ni][r] = 0.0f;
 
     // Per-lane LDS offsets of this wave's fragments inside an operand stage (see the fragment
-    // layouts above): the A fragment of MFMA tile mi lies mi * 2048 bytes after a_rd[ks]; B tile
-    // ni of a KC stage b_tile_imm(ni) bytes after b_rd[ks], of an MNC stage at b_rd[ni] plus
+    // layouts above): the A fragment of MFMA tile mi lies mi * 2048 bytes after a_rd[ks], B tile ni at b_rd[ni] plus
     // ks * 16384 (and + 2048 for its second half).
-    uint32_t a_rd[2], b_rd[B_KC ? 2 : 4];
-    // SWIGLU: 32 gate columns (n-tiles 0, 1) and the same 32 columns of up (n-tiles 2, 3), 128 tile rows on
-    const int b_row0 = GU ? wn * 32 : wn * 64;
+    uint32_t a_rd[2], b_rd[4];
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-        a_rd[ks] = kc_off(wm * WROWS + (lane & 15), 4 * ks + (lane >> 4));
-        if (B_KC) b_rd[ks] = kc_off(b_row0 + (lane & 15), 4 * ks + (lane >> 4));
-    }
-    if (!B_KC) {
+    for (int ks = 0; ks < 2; ++ks) a_rd[ks] = kc_off(wm * WROWS + (lane & 15), 4 * ks + (lane >> 4));
 #pragma unroll
-        for (int ni = 0; ni < 4; ++ni)
-            b_rd[ni] = mnc_off(8 * (lane >> 4) + ((lane & 15) >> 2), (b_row0 >> 4) + ni, 8 * (lane & 3));
-    }
+    for (int ni = 0; ni < 4; ++ni)
+        b_rd[ni] = mnc_off(8 * (lane >> 4) + ((lane & 15) >> 2), wn * 4 + ni, 8 * (lane & 3));
 
     if (nk > 0) {
         // Ping-pong schedule.  The two waves that share a SIMD (wave w and w + 4, i.e.
@@ -374,24 +337,17 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
         bf16x8 af[MI], bfr[4];
         const uint32_t lds0 = lds_addr_of(smem);
         auto load_frags = [&](int j, auto ks) {
-            const uint32_t sa = lds0 + (uint32_t)((j % NSA) * A_STAGE);
-            const uint32_t sb = lds0 + (uint32_t)(B_BASE + (j % NSTAGE_B) * OPER_BYTES);
+            const uint32_t sa = lds0 + (uint32_t)((j % NSTAGE_A) * OPER_BYTES);
+            const uint32_t sb = lds0 + (uint32_t)(LDS_B_BASE + (j % NSTAGE_B) * OPER_BYTES);
             const uint32_t aa = a_rd[ks] + sa;
             static_for<MI>([&](auto mi) { af[mi] = ds_read_b128_imm<mi * 2048>(aa); });
-            if constexpr (B_KC) {
-                const uint32_t ba = b_rd[ks] + sb;
-                static_for<4>([&](auto ni) {
-                    bfr[ni] = ds_read_b128_imm<GU ? (ni >> 1) * 16384 + (ni & 1) * 2048 : ni * 2048>(ba);
-                });
-            } else {
-                static_for<4>([&](auto ni) {
-                    const uint32_t ba = b_rd[ni] + sb;
-                    const u32x2 lo = ds_read_tr16_b64_imm<ks * 16384>(ba);
-                    const u32x2 hi = ds_read_tr16_b64_imm<ks * 16384 + 2048>(ba);
-                    const u32x4 both = {lo[0], lo[1], hi[0], hi[1]};
-                    bfr[ni] = __builtin_bit_cast(bf16x8, both);
-                });
-            }
+            static_for<4>([&](auto ni) {
+                const uint32_t ba = b_rd[ni] + sb;
+                const u32x2 lo = ds_read_tr16_b64_imm<ks * 16384>(ba);
+                const u32x2 hi = ds_read_tr16_b64_imm<ks * 16384 + 2048>(ba);
+                const u32x4 both = {lo[0], lo[1], hi[0], hi[1]};
+                bfr[ni] = __builtin_bit_cast(bf16x8, both);
+            });
         };
         // The memory phase of the steady state: the loads of this phase (slabs that exist and lie
         // inside K: no test, no mask) spread evenly between the fragment reads.  A direct-to-LDS load
@@ -403,16 +359,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
         // stages, the scalar offsets of the loads, the operand descriptors) is kept in registers
         // and stepped once per slab instead of being derived from the slab index.
         uint32_t st_rd_a = 0, st_rd_b = 0;       // LDS address of the stages slab j is read from
-        uint32_t st_ld_a = 0, st_ld_b = 0;       // LDS offset this wave loads slab j + A_AHEAD of A / slab j + 2 of B to
+        uint32_t st_ld_a = 0, st_ld_b = 0;       // LDS offset this wave loads slab j + 1 of A / slab j + 2 of B to
         uint32_t st_step_a = 0, st_step_b = 0;   // scalar offsets of those loads
         __amdgpu_buffer_rsrc_t st_src_a = rA0, st_src_b = rB0;
         auto memory_phase_fast = [&](auto ks) {
             constexpr int KS = decltype(ks)::value;
-            constexpr int NLA = KS == 0 ? A_LOADS : 0;
-            constexpr int NLB = (NARROW ? KS == 0 : KS == 1) ? 4 : 0;
-            constexpr int NL = NLA + NLB, NR = MI + 4;
+            constexpr int NL = 4, NR = MI + 4;
             const uint32_t aa = a_rd[KS] + st_rd_a;
-            const uint32_t ba = B_KC ? b_rd[KS] + st_rd_b : st_rd_b;
+            const uint32_t ba = st_rd_b;
             const uint32_t stepa = st_step_a, stepb = st_step_b;
             const __amdgpu_buffer_rsrc_t srca = st_src_a, srcb = st_src_b;
             char* dsta = smem + st_ld_a;
@@ -420,19 +374,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
             static_for<NR>([&](auto r) {
                 static_for<NL>([&](auto l) {
                     if constexpr (l * NR / NL == r) {
-                        if constexpr (l < NLA)
+                        if constexpr (KS == 0)
                             __builtin_amdgcn_raw_ptr_buffer_load_lds(srca, (lds_void_ptr)(dsta + l * 1024), 16,
                                                                      (int)a_goff[l], (int)stepa, 0, 0);
                         else
-                            __builtin_amdgcn_raw_ptr_buffer_load_lds(srcb, (lds_void_ptr)(dstb + (l - NLA) * 1024), 16,
-                                                                     (int)b_goff[l - NLA], (int)stepb, 0, 0);
+                            __builtin_amdgcn_raw_ptr_buffer_load_lds(srcb, (lds_void_ptr)(dstb + l * 1024), 16,
+                                                                     (int)b_goff[l], (int)stepb, 0, 0);
                     }
                 });
                 if constexpr (r < MI) {
                     af[r] = ds_read_b128_imm<r * 2048>(aa);
-                } else if constexpr (B_KC) {
-                    constexpr int ni = r - MI;
-                    bfr[ni] = ds_read_b128_imm<GU ? (ni >> 1) * 16384 + (ni & 1) * 2048 : ni * 2048>(ba);
                 } else {
                     constexpr int ni = r - MI;
                     const uint32_t bn = b_rd[ni] + ba;
@@ -462,21 +413,17 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
         };
-        // slab j+1 of both operands has landed; what slab j issued for slab j+2 (B, and A when it
-        // is fetched two ahead) may still fly
-        constexpr int FLYING = 4 + (A_AHEAD == 2 ? A_LOADS : 0);
+        // slab j+1 of both operands has landed; what slab j issued of B for slab j+2 may still fly
         auto wait_next_slab = [&](int j) {
-            if (j + 2 < nk) SKIPFFN_WAIT_VMCNT(FLYING); else SKIPFFN_WAIT_VMCNT(0);
+            if (j + 2 < nk) SKIPFFN_WAIT_VMCNT(4); else SKIPFFN_WAIT_VMCNT(0);
         };
 
-        // prologue: slabs 0 and 1 issued (A(1) only when A is fetched two ahead); A(0) and B(0)
-        // landed and visible
+        // prologue: slab 0 of A, slabs 0 and 1 of B issued; A(0) and B(0) landed and visible
         gload_a(0);
         gload_b(0);
         if (nk > 1) {
-            if (A_AHEAD == 2) gload_a(1);
             gload_b(1);
-            SKIPFFN_WAIT_VMCNT(FLYING);
+            SKIPFFN_WAIT_VMCNT(4);
         } else {
             SKIPFFN_WAIT_VMCNT(0);
         }
@@ -485,23 +432,22 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
 
         // slabs [0, kfull) of a pair lie inside K
         const int kfull = Keff / BK;
-        const uint32_t dstep_b = B_KC ? (uint32_t)BK * 2u : (uint32_t)BK * (uint32_t)P.ldb * 2u;
-        const uint32_t rd_a_end = lds0 + NSA * A_STAGE, rd_b_end = lds0 + B_BASE + NSTAGE_B * OPER_BYTES;
-        const uint32_t ld_a_end = NSA * A_STAGE + wave * (A_LOADS * 1024);
-        const uint32_t ld_b_end = B_BASE + NSTAGE_B * OPER_BYTES + wave * 4096;
+        const uint32_t dstep_b = (uint32_t)BK * (uint32_t)P.ldb * 2u;
+        const uint32_t rd_a_end = lds0 + LDS_B_BASE, rd_b_end = lds0 + GEMM_LDS_BYTES;
+        const uint32_t ld_a_end = LDS_B_BASE + wave * 4096, ld_b_end = GEMM_LDS_BYTES + wave * 4096;
         int fast_end = 0;                  // iterations [j, fast_end) are steady state
         for (int j = 0; j < nk; ++j) {
             bool fast = j < fast_end;
             if (!fast) {
                 // does a steady-state run start at slab j?  For `run` iterations the slabs to load
-                // (j + A_AHEAD of A, j + 2 of B) exist, lie inside K and stay in the operand pair they
+                // (j + 1 of A, j + 2 of B) exist, lie inside K and stay in the operand pair they
                 // are in now.
                 // (the empty assembly statements pin this rarely executed arithmetic to this place and to
                 // scalar registers: derived from the loop counter, it would otherwise be hoisted to the
                 // top of every iteration)
                 int js = j;
                 asm volatile("" : "+s"(js));
-                const int kta = kt_begin + js + A_AHEAD, ktb = kt_begin + js + 2;
+                const int kta = kt_begin + js + 1, ktb = kt_begin + js + 2;
                 const int paira = kta >= ktiles_pair ? 1 : 0, pairb = ktb >= ktiles_pair ? 1 : 0;
                 const int ia = kta - paira * ktiles_pair, ib = ktb - pairb * ktiles_pair;
                 int run = nk - 2 - js;
@@ -512,14 +458,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
                 if (run > 0) {
                     fast = true;
                     fast_end = js + run;
-                    st_rd_a = lds0 + (uint32_t)((js % NSA) * A_STAGE);
-                    st_rd_b = lds0 + (uint32_t)(B_BASE + (js % NSTAGE_B) * OPER_BYTES);
-                    st_ld_a = (uint32_t)(((js + A_AHEAD) % NSA) * A_STAGE + wave * (A_LOADS * 1024));
-                    st_ld_b = (uint32_t)(B_BASE + ((js + 2) % NSTAGE_B) * OPER_BYTES + wave * 4096);
+                    st_rd_a = lds0 + (uint32_t)((js % NSTAGE_A) * OPER_BYTES);
+                    st_rd_b = lds0 + (uint32_t)(LDS_B_BASE + (js % NSTAGE_B) * OPER_BYTES);
+                    st_ld_a = (uint32_t)(((js + 1) % NSTAGE_A) * OPER_BYTES + wave * 4096);
+                    st_ld_b = (uint32_t)(LDS_B_BASE + ((js + 2) % NSTAGE_B) * OPER_BYTES + wave * 4096);
                     st_step_a = (uint32_t)(ia * BK) * 2u;
                     st_step_b = (uint32_t)ib * dstep_b;
                     st_src_a = paira ? rA1 : rA0;
-                    st_src_b = GU ? (wave >= 4 ? rB1 : rB0) : (pairb ? rB1 : rB0);
+                    st_src_b = pairb ? rB1 : rB0;
                 }
             }
             // M(j,0)
@@ -530,8 +476,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
                 int js = j;
                 asm volatile("" : "+s"(js));
                 load_frags(js, std::integral_constant<int, 0>{});
-                if (js + A_AHEAD < nk) gload_a(js + A_AHEAD);
-                if (NARROW && js + 2 < nk) gload_b(js + 2);
+                if (js + 1 < nk) gload_a(js + 1);
             }
             SKIPFFN_WAIT_LGKMCNT0();
             phase_barrier();
@@ -545,7 +490,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
                 int js = j;
                 asm volatile("" : "+s"(js));
                 load_frags(js, std::integral_constant<int, 1>{});
-                if (!NARROW && js + 2 < nk) gload_b(js + 2);
+                if (js + 2 < nk) gload_b(js + 2);
             }
             if (wm == 1) wait_next_slab(j);
             SKIPFFN_WAIT_LGKMCNT0();
@@ -555,9 +500,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
             if (wm == 0) wait_next_slab(j);
             if (fast) {
                 // next slab: rotate the ring stages, step the load offsets
-                st_rd_a += A_STAGE; if (st_rd_a == rd_a_end) st_rd_a -= NSA * A_STAGE;
+                st_rd_a += OPER_BYTES; if (st_rd_a == rd_a_end) st_rd_a -= NSTAGE_A * OPER_BYTES;
                 st_rd_b += OPER_BYTES; if (st_rd_b == rd_b_end) st_rd_b -= NSTAGE_B * OPER_BYTES;
-                st_ld_a += A_STAGE; if (st_ld_a == ld_a_end) st_ld_a -= NSA * A_STAGE;
+                st_ld_a += OPER_BYTES; if (st_ld_a == ld_a_end) st_ld_a -= NSTAGE_A * OPER_BYTES;
                 st_ld_b += OPER_BYTES; if (st_ld_b == ld_b_end) st_ld_b -= NSTAGE_B * OPER_BYTES;
                 st_step_a += (uint32_t)BK * 2u;
                 st_step_b += dstep_b;
@@ -569,40 +514,38 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
 
     // ---- epilogue --------------------------------------------------------------
     // With the B fragment as first MFMA operand, acc[mi][ni][r] is C[row][col] with
-    //   row = m0 + wm*WROWS + mi*16 + lane%16        (WROWS = 128, or 64 in the 128-row variant)
+    //   row = m0 + wm*128 + mi*16 + lane%16
     //   col = (tile column base) + ni*16 + 4*(lane/16) + r
     // i.e. the four registers of an MFMA tile are four consecutive columns of one row.
     // The tile leaves through LDS (free after the main loop): per pass mt, every
     // row group (wm) dumps its 32 x 256 fp32 slice (MFMA tile rows 2mt, 2mt+1) as 16-byte vectors, and after a
     // barrier each thread takes row-contiguous chunks of 8 columns, applies the epilogue
-    // arithmetic and moves 16 bytes per global access.  The barriers order LDS traffic only, so the stores of one pass overlap
-    // the staging of the next.
+    // arithmetic and moves 16 bytes per global access.  The barriers order LDS traffic only,
+    // so the stores of one pass overlap the staging of the next.
     //
-    // The SwiGLU epilogues also leave TRANSPOSED copies of their results (H^T; dG^T and dU^T:
+    // The SwiGLU backward also leaves TRANSPOSED copies of its results (dG^T and dU^T:
     // [columns][rows], leading dimension ldt) for the weight-gradient GEMMs, which contract
     // over the rows and read both operands with plain 16-byte LDS reads when the row index is
     // contiguous.  A thread's packed results (pairs of columns, adjacent rows) go to an LDS
     // buffer T[column pair][row] with one 8- or 16-byte write per column pair; after a second
     // barrier each thread picks up 8 consecutive rows of a column pair (two 16-byte reads),
     // separates the two columns with byte permutes and stores 16 bytes per column.
-    constexpr bool HAS_T = (EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_BWD);
-    constexpr int SLICE_COLS = (EPI == EPI_SWIGLU) ? 128 : 256;       // per staged matrix
-    constexpr int SLICE_STRIDE = SLICE_COLS * 4 + 16;                   // bytes; +16 spreads rows over banks
-    constexpr int SLICE_MATS = (EPI == EPI_SWIGLU) ? 2 : 1;             // G and U
-    constexpr int SLICE_BYTES = SLICE_MATS * EPI_ROWS * SLICE_STRIDE;   // per row group
+    constexpr bool HAS_T = EPI == EPI_SWIGLU_BWD;
+    constexpr int SLICE_STRIDE = BN * 4 + 16;                           // bytes; +16 spreads rows over banks
+    constexpr int SLICE_BYTES = EPI_ROWS * SLICE_STRIDE;                // per row group
     // Staging buffers: two per row group, alternating between passes, so that one barrier per
     // pass suffices - except for the SwiGLU backward, whose two transposition buffers leave
     // room for one per row group only (it takes a second barrier per pass anyway).
-    constexpr int NSTAGING = (EPI == EPI_SWIGLU_BWD) ? 1 : 2;
-    constexpr int T_MATS = (EPI == EPI_SWIGLU_BWD) ? 2 : 1;
-    constexpr int T_PAIRS = SLICE_COLS / 2;                             // column pairs per row group
+    constexpr int NSTAGING = HAS_T ? 1 : 2;
+    constexpr int T_MATS = 2;                                           // dG^T, dU^T
+    constexpr int T_PAIRS = BN / 2;                                     // column pairs per row group
     constexpr int T_ROWB = EPI_ROWS * 4 + 16;                           // bytes per column pair: 32 rows + pad
     constexpr int T_BYTES = T_PAIRS * T_ROWB + (T_PAIRS / 4) * 16;      // per matrix and row group (skewed, see t_off)
     constexpr int T_BASE = 2 * NSTAGING * SLICE_BYTES;
     static_assert(T_BASE + (HAS_T ? 2 * T_MATS * T_BYTES : 0) <= GEMM_LDS_BYTES, "staging must fit in LDS");
     const int cq = lane >> 4;                     // column quad of this lane inside an MFMA tile
     const int tg = t & 255;                       // thread index inside the row group
-    constexpr int CHUNKS_PER_ROW = SLICE_COLS / 8;
+    constexpr int CHUNKS_PER_ROW = BN / 8;
     constexpr int CHUNKS_PER_THREAD = EPI_ROWS * CHUNKS_PER_ROW / 256;
     // chunk i of this thread: column chunk cc, row rbase + i * RSTEP - adjacent rows where the
     // transposed copies want them (one wide LDS write per column pair), else rows spread over the slice
@@ -644,11 +587,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
 #pragma unroll
             for (int ni = 0; ni < 4; ++ni) {
                 const f32x4 v = acc[2 * mt + s2][ni];
-                int col, mat;
-                if (EPI == EPI_SWIGLU)          { mat = ni >> 1; col = wn * 32 + (ni & 1) * 16 + 4 * cq; }
-                else                            { mat = 0;  col = wn * 64 + ni * 16 + 4 * cq; }
-                *reinterpret_cast<f32x4*>(sbuf + mat * EPI_ROWS * SLICE_STRIDE +
-                                          (s2 * 16 + (lane & 15)) * SLICE_STRIDE + col * 4) = v;
+                const int col = wn * 64 + ni * 16 + 4 * cq;
+                *reinterpret_cast<f32x4*>(sbuf + (s2 * 16 + (lane & 15)) * SLICE_STRIDE + col * 4) = v;
             }
         lds_barrier();
         if (mt + 1 < MT) prefetch_gu(mt + 1);
@@ -670,7 +610,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
             if (!live) continue;
             // lanes c >= 8 (mod 16) read their second half first: conflict-free 16-byte reads
             const int swap = (c >> 3) & 1;
-            float v[8], w[8];
+            float v[8];
             {
                 const char* src = sbuf + r * SLICE_STRIDE + c * 32;
                 f32x4 a = *reinterpret_cast<const f32x4*>(src + (swap ? 16 : 0));
@@ -679,71 +619,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
 #pragma unroll
                 for (int k = 0; k < 4; ++k) { v[k] = lo[k]; v[4 + k] = hi[k]; }
             }
-            if (EPI == EPI_SWIGLU) {
-                const char* src = sbuf + EPI_ROWS * SLICE_STRIDE + r * SLICE_STRIDE + c * 32;
-                f32x4 a = *reinterpret_cast<const f32x4*>(src + (swap ? 16 : 0));
-                f32x4 b = *reinterpret_cast<const f32x4*>(src + (swap ? 0 : 16));
-                f32x4 lo = swap ? b : a, hi = swap ? a : b;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) { w[k] = lo[k]; w[4 + k] = hi[k]; }
-                const uint32_t o = (uint32_t)row * (uint32_t)P.ldo + (uint32_t)col;
-                u32x4 ph, pg, pu;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    float g0 = v[2 * k], g1 = v[2 * k + 1], u0 = w[2 * k], u1 = w[2 * k + 1];
-                    ph[k] = pack_bf16x2(g0 * sigmoid_f(g0) * u0, g1 * sigmoid_f(g1) * u1);
-                    pg[k] = pack_bf16x2(g0, g1);
-                    pu[k] = pack_bf16x2(u0, u1);
-                    if (HAS_T) tpk[0][k][i] = ph[k];
-                }
-                *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(P.out0) + o) = ph;
-                if (P.out1 != nullptr) {
-                    *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(P.out1) + o) = pg;
-                    *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(P.out2) + o) = pu;
-                }
-            } else if (EPI == EPI_STORE) {
-                const uint32_t o = (uint32_t)row * (uint32_t)P.ldo + (uint32_t)col;
-                if (P.out_f32) {
-                    f32x4* O = reinterpret_cast<f32x4*>(static_cast<float*>(P.out0) + o);
-                    f32x4 lo = {v[0], v[1], v[2], v[3]}, hi = {v[4], v[5], v[6], v[7]};
-                    if (P.accumulate) { lo += O[0]; hi += O[1]; }
-                    O[0] = lo;
-                    O[1] = hi;
-                } else {
-                    u32x4* O = reinterpret_cast<u32x4*>(static_cast<bf16_t*>(P.out0) + o);
-                    if (P.accumulate) {
-                        u32x4 old = *O;
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            v[2 * k] += bf16lo_to_f32(old[k]);
-                            v[2 * k + 1] += bf16hi_to_f32(old[k]);
-                        }
-                    }
-                    u32x4 pk;
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) pk[k] = pack_bf16x2(v[2 * k], v[2 * k + 1]);
-                    *O = pk;
-                }
-            } else if (EPI == EPI_PARTIAL) {
+            if (EPI == EPI_PARTIAL) {
                 f32x4* O = reinterpret_cast<f32x4*>(P.partial + ((int64_t)z * P.M + row) * P.N + col);
                 f32x4 lo = {v[0], v[1], v[2], v[3]}, hi = {v[4], v[5], v[6], v[7]};
                 O[0] = lo;
                 O[1] = hi;
-            } else if (EPI == EPI_RESID_SCATTER) {
-                const uint32_t o = (uint32_t)P.idx[row] * (uint32_t)P.ldo + (uint32_t)col;
-                if (!P.no_residual) {
-                    u32x4 x = *reinterpret_cast<const u32x4*>(P.e0 + o);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        v[2 * k] += bf16lo_to_f32(x[k]);
-                        v[2 * k + 1] += bf16hi_to_f32(x[k]);
-                    }
-                }
-                u32x4 pk;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) pk[k] = pack_bf16x2(v[2 * k], v[2 * k + 1]);
-                *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(P.out0) + o) = pk;
-            } else if (EPI == EPI_SWIGLU_BWD) {
+            } else {
                 const uint32_t o = (uint32_t)row * (uint32_t)P.ldo + (uint32_t)col;
                 const u32x4 gq = pre_g[mt & 1][i];
                 const u32x4 uq = pre_u[mt & 1][i];
@@ -762,7 +643,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
                     }
                     dgq[k] = pack_bf16x2(dg[0], dg[1]);
                     duq[k] = pack_bf16x2(du[0], du[1]);
-                    if (HAS_T) { tpk[0][k][i] = dgq[k]; tpk[T_MATS - 1][k][i] = duq[k]; }
+                    if (HAS_T) { tpk[0][k][i] = dgq[k]; tpk[1][k][i] = duq[k]; }
                 }
                 *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(P.out0) + o) = dgq;
                 *reinterpret_cast<u32x4*>(static_cast<bf16_t*>(P.out1) + o) = duq;
@@ -771,20 +652,15 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
         if constexpr (HAS_T) {
             if (want_t) {
                 // ---- transposed copies: T[matrix][row group][column pair][row]
-                static_assert(CHUNKS_PER_THREAD == 2 || CHUNKS_PER_THREAD == 4, "one 8- or 16-byte write per column pair");
+                static_assert(CHUNKS_PER_THREAD == 4, "one 16-byte write per column pair");
 #pragma unroll
                 for (int m = 0; m < T_MATS; ++m) {
                     char* tb = smem + T_BASE + (m * 2 + wm) * T_BYTES;
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         char* dst = tb + t_off(cc * 4 + k, rbase);
-                        if (CHUNKS_PER_THREAD == 4) {
-                            u32x4 q = {tpk[m][k][0], tpk[m][k][1], tpk[m][k][2], tpk[m][k][3]};
-                            *reinterpret_cast<u32x4*>(dst) = q;
-                        } else {
-                            u32x2 q = {tpk[m][k][0], tpk[m][k][1]};
-                            *reinterpret_cast<u32x2*>(dst) = q;
-                        }
+                        u32x4 q = {tpk[m][k][0], tpk[m][k][1], tpk[m][k][2], tpk[m][k][3]};
+                        *reinterpret_cast<u32x4*>(dst) = q;
                     }
                 }
                 lds_barrier();
@@ -820,112 +696,29 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& P, const int tm, const
     }
 }
 
-// The gate/up GEMM may end in a row of 128-row tiles: a row count just above a multiple of 256
-// then costs half a tile row instead of a whole one (R = 2944 = 11.5 tile rows: 1288 tile units
-// of work instead of 1344), and the half-height tiles, dispatched last, even out the end of the
-// grid (measured 635 -> 597 us).  The dH GEMM does not get it: its 128-row tiles are bound by the
-// memory phases of the N-contiguous weight operand and take as long as full ones, and the extra
-// code path cost the shared dH + dW_down kernel 2 % (713 -> 730 us with the path unused).
-template <bool A_KC, int EPI>
-constexpr bool kTailNarrowOk = A_KC && EPI == EPI_SWIGLU;
-
-// One workgroup's share of a plain (optionally split-K, optionally batched) GEMM: workgroup `block`
+// One workgroup's share of a plain (optionally split-K) GEMM: workgroup `block`
 // in the launch order of this problem.  The tile map is laid over the EFFECTIVE rows: with the
 // row count on the device the grid covers the host's bound, and a map over the bound would give
 // the live tile rows - the first ones of each panel - to some XCDs only (640 of 2944 rows: 5.3 of the 8
 // XCDs had work).  Workgroups past the live tiles come last in the launch order and leave at once.
-template <bool A_KC, bool B_KC, int EPI>
-__device__ __forceinline__ void gemm_block(GemmArgs P, const int block) {
+//
+// No 128-row tiles at the end of the rows: bound by the memory phases of the N-contiguous weight operand they take as long
+// as full ones, and the extra code path cost the shared dH + dW_down kernel 2 % (713 -> 730 us with the path unused).
+template <int EPI>
+__device__ __forceinline__ void gemm_block(const GemmArgs& P, const int block) {
     const int Meff = effective_rows(P.M, P.m_dev);
     const int Keff = effective_rows(P.K, P.k_dev);
-    if constexpr (kTailNarrowOk<A_KC, EPI>) {
-        // host contract: tail_narrow comes with splits == 1 and batch == 1
-        const int rem = Meff % BM;
-        if (P.tail_narrow && rem > 0 && rem <= BM / 2) {
-            const int tiles_m = Meff / BM, full = tiles_m * P.tiles_n;
-            if (block >= full + P.tiles_n) return;
-            const int ktotal = ((Keff + BK - 1) / BK) * P.pairs;
-            if (block >= full) {
-                gemm_tile<A_KC, B_KC, EPI, true>(P, 2 * tiles_m, block - full, 0, 0, ktotal, Meff, Keff);
-            } else {
-                int tm, tn, z;
-                tile_of_block(block, full, tiles_m, P.tiles_n, tm, tn, z);
-                gemm_tile<A_KC, B_KC, EPI, false>(P, tm, tn, 0, 0, ktotal, Meff, Keff);
-            }
-            return;
-        }
-    }
     const int tiles_m = (Meff + BM - 1) / BM;
-    const int nblocks = tiles_m * P.tiles_n * P.splits * P.batch;
+    const int nblocks = tiles_m * P.tiles_n * P.splits;
     if (block >= nblocks) return;                        // whole block leaves together: no barrier was reached yet
     int tm, tn, z;
     tile_of_block(block, nblocks, tiles_m, P.tiles_n, tm, tn, z);
-    // batched launch (two problems in one grid, used for dW_gate / dW_up): the upper half of
-    // the z range is problem 1
-    const bool second = P.batch == 2 && z >= P.splits;
-    if (second) {
-        z -= P.splits;
-        P.A0 = P.A1;
-        P.out0 = P.out1;
-    }
     const int ktotal = ((Keff + BK - 1) / BK) * P.pairs;
     const int per_split = (ktotal + P.splits - 1) / P.splits;
     const int kt_begin = z * per_split;
     int kt_end = kt_begin + per_split;
     if (kt_end > ktotal) kt_end = ktotal;
-    gemm_tile<A_KC, B_KC, EPI>(P, tm, tn, z, kt_begin, kt_end, Meff, Keff);
-}
-
-template <bool A_KC, bool B_KC, int EPI>
-__global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_kernel(GemmArgs P) {
-    gemm_block<A_KC, B_KC, EPI>(P, (int)blockIdx.x);
-}
-
-// ---- balanced split-K for GEMMs that leave through fp32 partial slabs (see streamk.hpp) ------
-// grid = tiles_n * nbg workgroups (P.splits carries nbg); EPI_PARTIAL only
-template <bool A_KC, bool B_KC>
-__global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_streamk_kernel(GemmArgs P) {
-    const int nbg = P.splits;
-    const int nb = (int)gridDim.x;
-    const int tiles_n = nb / nbg;
-    int b = (int)blockIdx.x;
-    // workgroups are dealt round-robin to the 8 XCDs: give each XCD a contiguous range of the
-    // logical order below
-    if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);
-    const int Meff = effective_rows(P.M, P.m_dev);
-    const int Keff = effective_rows(P.K, P.k_dev);
-    const int g = (Meff + BM - 1) / BM;
-    const int kt = ((Keff + BK - 1) / BK) * P.pairs;
-    if (g == 0 || kt == 0) return;
-    const StreamKPlan p = streamk_plan(g, kt, nbg);
-    // Logical order: aligned chunks first, chunk-major, then n-tile, then m-tile - so an XCD
-    // works on ONE K range of many n-tiles (the m-tiles of an n-tile share the weight slabs,
-    // the n-tiles share the activation slabs, and no XCD streams the whole K extent of the
-    // activations); the remainder pieces follow.  (tn, j) = n-tile and workgroup index in its group.
-    // (With more tiles than workgroups in a group every workgroup starts with whole tiles of its own,
-    // see streamk.hpp; the order below is that of the gr tiles that are split.)
-    int tn, j;
-    const int gr = p.gr;
-    const int aligned_total = p.a * gr * tiles_n;
-    if (b < aligned_total) {
-        const int c = b / (tiles_n * gr);
-        const int r = b - c * (tiles_n * gr);
-        tn = r / gr;
-        j = c * gr + (r - tn * gr);
-    } else {
-        const int per = nbg - p.a * gr;           // workgroups per group left for the remainder
-        const int r = b - aligned_total;
-        tn = r / per;
-        j = p.a * gr + (r - tn * per);
-    }
-    StreamKIter it = streamk_begin(p, j);
-    StreamKSeg sg;
-    bool first = true;
-    while (streamk_next(p, it, sg)) {      // uniform over the workgroup
-        if (!first) lds_barrier();          // the staging buffers of the previous epilogue are free again
-        first = false;
-        gemm_tile<A_KC, B_KC, EPI_PARTIAL>(P, sg.i, tn, sg.slot, sg.kb, sg.ke, Meff, Keff);
-    }
+    gemm_tile<EPI>(P, tm, tn, z, kt_begin, kt_end, Meff, Keff);
 }
 
 }  // namespace skipffn

@@ -1,10 +1,60 @@
-// Instantiations and launcher of the bf16 MFMA GEMM core.
+// Kernels and launchers of the bf16 MFMA GEMM core.
 #include <algorithm>
 
 #include "kernels.hpp"
 #include "stream.hpp"
 
 namespace skipffn {
+
+__global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_kernel(GemmArgs P) {
+    gemm_block<EPI_PARTIAL>(P, (int)blockIdx.x);
+}
+
+// ---- balanced split-K for GEMMs that leave through fp32 partial slabs (see streamk.hpp) ------
+// grid = tiles_n * nbg workgroups (P.splits carries nbg); EPI_PARTIAL only
+__global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_streamk_kernel(GemmArgs P) {
+    const int nbg = P.splits;
+    const int nb = (int)gridDim.x;
+    const int tiles_n = nb / nbg;
+    int b = (int)blockIdx.x;
+    // workgroups are dealt round-robin to the 8 XCDs: give each XCD a contiguous range of the
+    // logical order below
+    if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);
+    const int Meff = effective_rows(P.M, P.m_dev);
+    const int Keff = effective_rows(P.K, P.k_dev);
+    const int g = (Meff + BM - 1) / BM;
+    const int kt = ((Keff + BK - 1) / BK) * P.pairs;
+    if (g == 0 || kt == 0) return;
+    const StreamKPlan p = streamk_plan(g, kt, nbg);
+    // Logical order: aligned chunks first, chunk-major, then n-tile, then m-tile - so an XCD
+    // works on ONE K range of many n-tiles (the m-tiles of an n-tile share the weight slabs,
+    // the n-tiles share the activation slabs, and no XCD streams the whole K extent of the
+    // activations); the remainder pieces follow.  (tn, j) = n-tile and workgroup index in its group.
+    // (With more tiles than workgroups in a group every workgroup starts with whole tiles of its own,
+    // see streamk.hpp; the order below is that of the gr tiles that are split.)
+    int tn, j;
+    const int gr = p.gr;
+    const int aligned_total = p.a * gr * tiles_n;
+    if (b < aligned_total) {
+        const int c = b / (tiles_n * gr);
+        const int r = b - c * (tiles_n * gr);
+        tn = r / gr;
+        j = c * gr + (r - tn * gr);
+    } else {
+        const int per = nbg - p.a * gr;           // workgroups per group left for the remainder
+        const int r = b - aligned_total;
+        tn = r / per;
+        j = p.a * gr + (r - tn * per);
+    }
+    StreamKIter it = streamk_begin(p, j);
+    StreamKSeg sg;
+    bool first = true;
+    while (streamk_next(p, it, sg)) {      // uniform over the workgroup
+        if (!first) lds_barrier();          // the staging buffers of the previous epilogue are free again
+        first = false;
+        gemm_tile<EPI_PARTIAL>(P, sg.i, tn, sg.slot, sg.kb, sg.ke, Meff, Keff);
+    }
+}
 
 // dH with the SwiGLU backward in its epilogue and dW_down, which depend on each other in nothing, in one grid: workgroups
 // [0, n0) run a tile of dH each (the longer ones, dispatched first), the rest lists of tiles of dW_down, so the last round
@@ -14,36 +64,26 @@ namespace skipffn {
 __global__ __launch_bounds__(GEMM_THREADS) void gemm_dh_dw_down_kernel(GemmArgs P0, GemmArgs P1, int n0) {
     const int b = (int)blockIdx.x;
     if (b < n0)
-        gemm_block<true, false, EPI_SWIGLU_BWD>(P0, b);
+        gemm_block<EPI_SWIGLU_BWD>(P0, b);
     else
         stream_tall<EPI_STORE>(P1, b - n0, (int)gridDim.x - n0);
 }
 
-template <bool A_KC, bool B_KC, int EPI>
-static hipError_t set_lds_limit() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_kernel<A_KC, B_KC, EPI>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS_BYTES);
-}
-
-static hipError_t set_stream_lds(void (*kernel)(GemmArgs)) {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kStreamLds);
+template <class... Args>
+static hipError_t set_lds(void (*kernel)(Args...)) {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS_BYTES);
 }
 
 hipError_t gemm_init() {
     hipError_t e;
-    if ((e = set_stream_lds(&stream_gemm_kernel<EPI_STORE>)) != hipSuccess) return e;
-    if ((e = set_stream_lds(&stream_gemm_rows_kernel<EPI_SWIGLU>)) != hipSuccess) return e;
-    if ((e = set_stream_lds(&stream_gemm_kernel<EPI_PARTIAL>)) != hipSuccess) return e;
-    if ((e = set_stream_lds(&stream_gemm_kernel<EPI_RESID_SCATTER>)) != hipSuccess) return e;
-    if ((e = set_stream_lds(&stream_gemm_balanced_kernel)) != hipSuccess) return e;
-    if ((e = set_lds_limit<true, false, EPI_PARTIAL>()) != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_streamk_kernel<true, false>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS_BYTES);
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dh_dw_down_kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS_BYTES);
-    if (e != hipSuccess) return e;
-    return hipSuccess;
+    if ((e = set_lds(&stream_gemm_kernel<EPI_STORE>)) != hipSuccess) return e;
+    if ((e = set_lds(&stream_gemm_rows_kernel<EPI_SWIGLU>)) != hipSuccess) return e;
+    if ((e = set_lds(&stream_gemm_kernel<EPI_PARTIAL>)) != hipSuccess) return e;
+    if ((e = set_lds(&stream_gemm_kernel<EPI_RESID_SCATTER>)) != hipSuccess) return e;
+    if ((e = set_lds(&stream_gemm_balanced_kernel)) != hipSuccess) return e;
+    if ((e = set_lds(&gemm_bf16_kernel)) != hipSuccess) return e;
+    if ((e = set_lds(&gemm_bf16_streamk_kernel)) != hipSuccess) return e;
+    return set_lds(&gemm_dh_dw_down_kernel);
 }
 
 static void finish_args(int epi, GemmArgs& a) {
@@ -51,20 +91,9 @@ static void finish_args(int epi, GemmArgs& a) {
     a.tiles_n = epi == EPI_SWIGLU ? (a.N + BN / 2 - 1) / (BN / 2) : (a.N + BN - 1) / BN;
     if (a.splits < 1) a.splits = 1;
     if (a.batch < 1) a.batch = 1;
-    // a last tile row of at most 128 rows runs on 128-row tiles (one workgroup per tile: the gate/up GEMM);
-    // the kernel looks at the effective row count
-    a.tail_narrow = (epi == EPI_SWIGLU && a.splits == 1 && a.batch == 1) ? 1 : 0;
 }
 // workgroups of a one-tile-per-workgroup launch
 static unsigned grid_blocks(const GemmArgs& a) { return (unsigned)(a.tiles_m * a.tiles_n * a.splits * a.batch); }
-
-template <bool A_KC, bool B_KC, int EPI>
-static hipError_t launch_one(const GemmArgs& a, hipStream_t s) {
-    const unsigned blocks = grid_blocks(a);
-    hipLaunchKernelGGL((gemm_bf16_kernel<A_KC, B_KC, EPI>), dim3(blocks), dim3(GEMM_THREADS),
-                       GEMM_LDS_BYTES, s, a);
-    return hipGetLastError();
-}
 
 // One workgroup per CU, a multiple of the 8 XCDs; fewer where the tiles, counted at their smallest height, are fewer
 template <int EPI>
@@ -72,7 +101,7 @@ static hipError_t launch_stream(void (*kernel)(GemmArgs), const GemmArgs& a, hip
     const int height = EPI == EPI_SWIGLU ? 128 : 256;
     const unsigned cus = (unsigned)(a.ncu >= 8 ? a.ncu / 8 * 8 : 8);
     const unsigned tiles = ((unsigned)((a.M + height - 1) / height * a.tiles_n * a.splits * a.batch) + 7) / 8 * 8;
-    hipLaunchKernelGGL(kernel, dim3(tiles < cus ? tiles : cus), dim3(GEMM_THREADS), kStreamLds, s, a);
+    hipLaunchKernelGGL(kernel, dim3(tiles < cus ? tiles : cus), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a);
     return hipGetLastError();
 }
 
@@ -93,25 +122,27 @@ hipError_t launch_gemm_dual(int which, GemmArgs& a0, GemmArgs& a1, hipStream_t s
 hipError_t launch_gemm_streamk(bool a_kc, bool b_kc, GemmArgs& a, int nbg, hipStream_t s) {
     finish_args(EPI_PARTIAL, a);
     if (a.tiles_m <= 0 || a.tiles_n <= 0) return hipSuccess;
-    if (nbg < 1 || !a_kc || a.batch != 1) return hipErrorInvalidValue;
+    if (nbg < 1 || !a_kc || a.batch != 1 || (b_kc && a.pairs != 1)) return hipErrorInvalidValue;
     a.splits = nbg;
     const unsigned blocks = (unsigned)(a.tiles_n * nbg);
     if (b_kc)
-        hipLaunchKernelGGL(stream_gemm_balanced_kernel, dim3(blocks), dim3(GEMM_THREADS), kStreamLds, s, a);
+        hipLaunchKernelGGL(stream_gemm_balanced_kernel, dim3(blocks), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a);
     else
-        hipLaunchKernelGGL((gemm_bf16_streamk_kernel<true, false>), dim3(blocks), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a);
+        hipLaunchKernelGGL(gemm_bf16_streamk_kernel, dim3(blocks), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_gemm(bool a_kc, bool b_kc, int epi, GemmArgs& a, hipStream_t s) {
     finish_args(epi, a);
     if (grid_blocks(a) == 0 || a.tiles_n <= 0) return hipSuccess;
+    if (b_kc && a.pairs != 1) return hipErrorInvalidValue;
     if (a_kc && b_kc && epi == EPI_SWIGLU) return launch_stream<EPI_SWIGLU>(&stream_gemm_rows_kernel<EPI_SWIGLU>, a, s);
     if (a_kc && b_kc && epi == EPI_PARTIAL) return launch_stream<EPI_PARTIAL>(&stream_gemm_kernel<EPI_PARTIAL>, a, s);
     if (a_kc && b_kc && epi == EPI_RESID_SCATTER) return launch_stream<EPI_RESID_SCATTER>(&stream_gemm_kernel<EPI_RESID_SCATTER>, a, s);
     if (a_kc && b_kc && epi == EPI_STORE) return launch_stream<EPI_STORE>(&stream_gemm_kernel<EPI_STORE>, a, s);
-    if (a_kc && !b_kc && epi == EPI_PARTIAL) return launch_one<true, false, EPI_PARTIAL>(a, s);
-    return hipErrorInvalidValue;
+    if (!a_kc || b_kc || epi != EPI_PARTIAL || a.batch != 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(gemm_bf16_kernel, dim3(grid_blocks(a)), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a);
+    return hipGetLastError();
 }
 
 }  // namespace skipffn

@@ -20,7 +20,6 @@ namespace skipffn {
 constexpr int kStreamRingB = 3;               // slabs of B in LDS
 template <int MI>
 constexpr int kStreamRingA = (GEMM_LDS_BYTES - kStreamRingB * OPER_BYTES) / (MI * 4096) < 3 ? 2 : 3;
-constexpr int kStreamLds = GEMM_LDS_BYTES;
 
 // A value that is the same in all lanes, in a scalar register.  Divisions and loads of the row count leave their
 // results in vector registers, and a descriptor that comes from there turns every load into a loop over the lanes (dW at
@@ -635,7 +634,7 @@ __device__ __forceinline__ void stream_grid(const GemmArgs& P, const int block, 
                                             const int Keff, const int row_base = 0, const int after = 0) {
     constexpr bool SPLIT = EPI == EPI_STORE || EPI == EPI_PARTIAL;
     const GridWork<SPLIT> w(block, workgroups, (rows - row_base + 32 * MI - 1) / (32 * MI), P.tiles_n, P.splits, P.batch,
-                            (Keff > 0 ? (Keff + BK - 1) / BK : 1) * P.pairs, after);
+                            Keff > 0 ? (Keff + BK - 1) / BK : 1, after);
     stream_gemm<MI, EPI>(P, w, Meff, Keff, row_base);
 }
 
@@ -681,7 +680,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_balanced_kernel(Gemm
     // workgroups are dealt round-robin to the 8 XCDs: give each XCD a contiguous range of the order below
     if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);
     const int Meff = uniform(effective_rows(P.M, P.m_dev)), Keff = uniform(effective_rows(P.K, P.k_dev));
-    const int g = (Meff + BM - 1) / BM, kt = ((Keff + BK - 1) / BK) * P.pairs;
+    const int g = (Meff + BM - 1) / BM, kt = (Keff + BK - 1) / BK;
     if (g == 0 || kt == 0) return;
     const StreamKPlan p = streamk_plan(g, kt, nbg);
     // Aligned chunks first, chunk-major, then tile column, then tile row - so an XCD works on ONE K range of many tile
