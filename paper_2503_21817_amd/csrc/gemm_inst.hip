@@ -78,8 +78,8 @@ hipError_t gemm_init() {
     hipError_t e;
     if ((e = set_lds(&stream_gemm_kernel<EPI_STORE>)) != hipSuccess) return e;
     if ((e = set_lds(&stream_gemm_rows_kernel<EPI_SWIGLU>)) != hipSuccess) return e;
-    if ((e = set_lds(&stream_gemm_kernel<EPI_PARTIAL>)) != hipSuccess) return e;
-    if ((e = set_lds(&stream_gemm_kernel<EPI_RESID_SCATTER>)) != hipSuccess) return e;
+    if ((e = set_lds(&stream_gemm_rows_kernel<EPI_PARTIAL>)) != hipSuccess) return e;
+    if ((e = set_lds(&stream_gemm_rows_kernel<EPI_RESID_SCATTER>)) != hipSuccess) return e;
     if ((e = set_lds(&stream_gemm_balanced_kernel)) != hipSuccess) return e;
     if ((e = set_lds(&gemm_bf16_kernel)) != hipSuccess) return e;
     if ((e = set_lds(&gemm_bf16_streamk_kernel)) != hipSuccess) return e;
@@ -98,7 +98,7 @@ static unsigned grid_blocks(const GemmArgs& a) { return (unsigned)(a.tiles_m * a
 // One workgroup per CU, a multiple of the 8 XCDs; fewer where the tiles, counted at their smallest height, are fewer
 template <int EPI>
 static hipError_t launch_stream(void (*kernel)(GemmArgs), const GemmArgs& a, hipStream_t s) {
-    const int height = EPI == EPI_SWIGLU ? 128 : 256;
+    const int height = EPI == EPI_STORE ? 256 : 128;
     const unsigned cus = (unsigned)(a.ncu >= 8 ? a.ncu / 8 * 8 : 8);
     const unsigned tiles = ((unsigned)((a.M + height - 1) / height * a.tiles_n * a.splits * a.batch) + 7) / 8 * 8;
     hipLaunchKernelGGL(kernel, dim3(tiles < cus ? tiles : cus), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a);
@@ -137,8 +137,8 @@ hipError_t launch_gemm(bool a_kc, bool b_kc, int epi, GemmArgs& a, hipStream_t s
     if (grid_blocks(a) == 0 || a.tiles_n <= 0) return hipSuccess;
     if (b_kc && a.pairs != 1) return hipErrorInvalidValue;
     if (a_kc && b_kc && epi == EPI_SWIGLU) return launch_stream<EPI_SWIGLU>(&stream_gemm_rows_kernel<EPI_SWIGLU>, a, s);
-    if (a_kc && b_kc && epi == EPI_PARTIAL) return launch_stream<EPI_PARTIAL>(&stream_gemm_kernel<EPI_PARTIAL>, a, s);
-    if (a_kc && b_kc && epi == EPI_RESID_SCATTER) return launch_stream<EPI_RESID_SCATTER>(&stream_gemm_kernel<EPI_RESID_SCATTER>, a, s);
+    if (a_kc && b_kc && epi == EPI_PARTIAL) return launch_stream<EPI_PARTIAL>(&stream_gemm_rows_kernel<EPI_PARTIAL>, a, s);
+    if (a_kc && b_kc && epi == EPI_RESID_SCATTER) return launch_stream<EPI_RESID_SCATTER>(&stream_gemm_rows_kernel<EPI_RESID_SCATTER>, a, s);
     if (a_kc && b_kc && epi == EPI_STORE) return launch_stream<EPI_STORE>(&stream_gemm_kernel<EPI_STORE>, a, s);
     if (!a_kc || b_kc || epi != EPI_PARTIAL || a.batch != 1) return hipErrorInvalidValue;
     hipLaunchKernelGGL(gemm_bf16_kernel, dim3(grid_blocks(a)), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a);

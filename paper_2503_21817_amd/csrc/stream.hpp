@@ -314,11 +314,12 @@ __device__ __forceinline__ void stream_epilogue(const GemmArgs& P, const StreamT
                 at[mi][p] = row < Meff && col < P.N ? (r + (uint32_t)col) * 2u : kOobOffset;
             }
         }
-        static_for<MI / 2>([&](auto h) {
+        static_for<(MI + 1) / 2>([&](auto h) {
+            constexpr int n = 2 * h + 2 <= MI ? 4 : 2;       // the last row of an odd height stands alone
             u32x4 x[2][2];
             if (!P.no_residual)
-                static_for<4>([&](auto k) { x[k >> 1][k & 1] = buf_load16(res, at[2 * h + (k >> 1)][k & 1]); });
-            static_for<4>([&](auto k) {
+                static_for<n>([&](auto k) { x[k >> 1][k & 1] = buf_load16(res, at[2 * h + (k >> 1)][k & 1]); });
+            static_for<n>([&](auto k) {
                 constexpr int mi = 2 * h + (k >> 1), p = k & 1;
                 Cols8 c = swap_cols(acc[mi][2 * p], acc[mi][2 * p + 1]);
                 if (!P.no_residual) {
@@ -651,15 +652,19 @@ __global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_kernel(GemmArgs P) {
     stream_tall<EPI>(P, (int)blockIdx.x, (int)gridDim.x);
 }
 
-// tiles of the heights that suit the row count
+// Tiles of the heights that suit the row count: gate/up (streamk.hpp), and the down GEMM where its K range is cut evenly or not
+// at all.  Down, 256-row tiles / these, us: 300 rows 59 / 51, 368 58 / 52, 420 58 / 54 (C = 4096, I = 14336; 480 to 512 rows
+// even), 368 rows 173 / 154 (C = 8192, I = 28672), 1100 rows 50 / 46 (2048, 8192); with the residual in the epilogue 2300 rows
+// 25 / 21, 4200 rows 43 / 34 (4096, 512).
 template <int EPI>
 __global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_rows_kernel(GemmArgs P) {
     const int Meff = uniform(effective_rows(P.M, P.m_dev)), Keff = uniform(effective_rows(P.K, P.k_dev));
     if (Meff <= 0) return;
     const int b = (int)blockIdx.x, nb = (int)gridDim.x;
-    StreamRows plan = stream_rows_plan(Meff, P.tiles_n, nb, P.outT0 != nullptr);
+    const int columns = P.tiles_n * P.splits;                // tiles of a tile row
+    StreamRows plan = stream_rows_plan(Meff, columns, nb, P.outT0 != nullptr);
     plan = StreamRows{uniform(plan.full), uniform(plan.mi)};
-    const int base = plan.full * 256 < Meff ? plan.full * 256 : Meff, after = plan.full * P.tiles_n;
+    const int base = plan.full * 256 < Meff ? plan.full * 256 : Meff, after = plan.full * columns;
     if (plan.full > 0) {
         stream_grid<8, EPI>(P, b, nb, base, Meff, Keff);
         if (plan.mi == 0) return;

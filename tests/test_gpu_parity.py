@@ -824,3 +824,22 @@ def test_gate_up_tile_heights(R, I, r_host, saved):
         h, ht = bits_of(sv["H"]), bits_of(sv["HT"])
         assert np.array_equal(ht[:, :R], h.T)
         assert not ht[:, R:(R + 63) // 64 * 64].any()
+
+
+@pytest.mark.parametrize("R,C,I", [(257, 1032, 8264), (769, 1032, 8264), (961, 1032, 8264), (1153, 1032, 8264),
+                                   (1793, 4104, 72), (1921, 4104, 72), (2401, 4104, 72), (2881, 4104, 72)])
+@pytest.mark.parametrize("r_host", [True, False], ids=["R-host", "R-device"])
+def test_down_tile_heights(R, C, I, r_host):
+    """The down GEMM on 256 compute units: eight K ranges into fp32 slabs, then (I = 72) one with the residual in its epilogue,
+    each on tiles of 128, 160, 192 and 224 rows; row counts one past a tile's height, where the last is nearly empty.
+    Every row is checked on its own."""
+    from helpers import max_slice_rel_l2
+    w = W.small(C=C, I=I, visual=(R + 30,), text=(9,), keep=(R - 9,), seed=3400 + R, name=f"down-heights-{R}")
+    assert w.R == R
+    p = Problem(w)
+    fo = O.skipffn_forward(p.hidden, p.mask, p.wg, p.wu, p.wd, None, w.eps)
+    idx, sk = fo["idx"], p.mask != 0
+    out, _ = gpu_forward(p, R_host=r_host)
+    got = bits_of(out)
+    assert np.array_equal(got[sk], p.hidden[sk])
+    assert max_slice_rel_l2(O.bf16_bits_to_f64(got[idx]), O.bf16_bits_to_f64(fo["out_bits"][idx]), axis=1) < REL_L2_TOL
