@@ -33,7 +33,7 @@ constexpr int kMaxSplitsNarrow = 16;     // up to 256 rows: small fp32 slabs, an
 // slabs on 2 workgroups, ended its training step at 65.1 us, on 5 at 61.3).
 //   splits == 1, sk_nbg == 0 : one workgroup per tile, epilogue fused
 //   splits  > 1, sk_nbg == 0 : plain split-K into `splits` fp32 slabs
-//   sk_nbg  > 0              : balanced split (gemm_bf16_streamk_kernel), sk_nbg workgroups per
+//   sk_nbg  > 0              : balanced split (stream_gemm_balanced_kernel), sk_nbg workgroups per
 //                              n-tile group (with more m-tiles than workgroups in a group, every
 //                              workgroup first runs whole tiles of its own; the rest is split)
 struct KPartition { int splits; int sk_nbg; };
