@@ -172,19 +172,19 @@ struct OutRows {
         return make_rsrc(base + 16 * mi * row_bytes, left <= 0 ? 0u : (left >= 16 ? kStoreOob : (uint32_t)(left * row_bytes)));
     }
 };
-// f(desc, at, mi) for the MI blocks of 16 rows: desc(o') the descriptor of the block in a matrix of the same shape, at(off)
-// the lane's offset there; off: its offset in a block, or kStoreOob
+// f(desc, at, mi, whole) for the MI blocks of 16 rows: desc(o') the descriptor of the block in a matrix of the same shape,
+// at(off) the lane's offset there; off: its offset in a block, or kStoreOob; whole: true_type where every row is known to exist
 template <int MI, class F>
 __device__ __forceinline__ void for_row_blocks(const OutRows& o, F&& f) {
     if (o.rows >= 16 * MI && 16 * MI * o.row_bytes < (int64_t)kOobOffset) {    // uniform
         const uint32_t step = (uint32_t)(16 * o.row_bytes);
         static_for<MI>([&](auto mi) {
             f([](const OutRows& m) { return make_rsrc(m.base, kOobOffset); },
-              [&](uint32_t off) { return (off < kOobOffset ? off : kOobOffset) + mi * step; }, mi);
+              [&](uint32_t off) { return (off < kOobOffset ? off : kOobOffset) + mi * step; }, mi, std::true_type{});
         });
     } else {
         static_for<MI>([&](auto mi) {
-            f([&](const OutRows& m) { return m.block(mi); }, [](uint32_t off) { return off; }, mi);
+            f([&](const OutRows& m) { return m.block(mi); }, [](uint32_t off) { return off; }, mi, std::false_type{});
         });
     }
 }
@@ -251,12 +251,12 @@ __device__ __forceinline__ void stream_epilogue(const GemmArgs& P, const StreamT
         o.rows = Meff - row0;
         const uint32_t off[2] = {lane_offset(o.row_bytes, es, col0, 0), lane_offset(o.row_bytes, es, col0, 1)};
         if (P.out_f32 && !P.accumulate) {
-            for_row_blocks<MI>(o, [&](auto desc, auto at, auto mi) {
+            for_row_blocks<MI>(o, [&](auto desc, auto at, auto mi, auto) {
                 const __amdgpu_buffer_rsrc_t d = desc(o);
                 static_for<2>([&](auto p) { store_f32(swap_cols(acc[mi][2 * p], acc[mi][2 * p + 1]), d, at(off[p])); });
             });
         } else if (P.out_f32) {
-            for_row_blocks<MI>(o, [&](auto desc, auto at, auto mi) {
+            for_row_blocks<MI>(o, [&](auto desc, auto at, auto mi, auto) {
                 const __amdgpu_buffer_rsrc_t d = desc(o);
                 f32x4 old[4];
                 static_for<4>([&](auto h) { old[h] = buf_load_f32x4(d, at(off[h >> 1]) + (h & 1) * 16); });
@@ -268,12 +268,12 @@ __device__ __forceinline__ void stream_epilogue(const GemmArgs& P, const StreamT
                 });
             });
         } else if (!P.accumulate) {
-            for_row_blocks<MI>(o, [&](auto desc, auto at, auto mi) {
+            for_row_blocks<MI>(o, [&](auto desc, auto at, auto mi, auto) {
                 const __amdgpu_buffer_rsrc_t d = desc(o);
                 static_for<2>([&](auto p) { buf_store(pack_cols(swap_cols(acc[mi][2 * p], acc[mi][2 * p + 1])), d, at(off[p])); });
             });
         } else {
-            for_row_blocks<MI>(o, [&](auto desc, auto at, auto mi) {
+            for_row_blocks<MI>(o, [&](auto desc, auto at, auto mi, auto) {
                 const __amdgpu_buffer_rsrc_t d = desc(o);
                 u32x4 old[2];
                 static_for<2>([&](auto p) { old[p] = __builtin_amdgcn_raw_buffer_load_b128(d, (int)at(off[p]), 0, 0); });
@@ -295,7 +295,7 @@ __device__ __forceinline__ void stream_epilogue(const GemmArgs& P, const StreamT
         o.base = reinterpret_cast<char*>(P.partial) + ((int64_t)t.z * P.M + row0) * o.row_bytes + col0 * 4;
         o.rows = Meff - row0;
         const uint32_t off[2] = {lane_offset(o.row_bytes, 4, col0, 0), lane_offset(o.row_bytes, 4, col0, 1)};
-        for_row_blocks<MI>(o, [&](auto desc, auto at, auto mi) {
+        for_row_blocks<MI>(o, [&](auto desc, auto at, auto mi, auto) {
             const __amdgpu_buffer_rsrc_t d = desc(o);
             static_for<2>([&](auto p) { store_f32(swap_cols(acc[mi][2 * p], acc[mi][2 * p + 1]), d, at(off[p])); });
         });
@@ -347,18 +347,20 @@ __device__ __forceinline__ void stream_epilogue(const GemmArgs& P, const StreamT
         const TransposedBlock tb(scratch, lane);
         // the lane's column and first row in the transposed copy, columns 16 further on for the second half
         bf16_t* to = static_cast<bf16_t*>(P.outT0) + (int64_t)(col0 + r16) * P.ldt + row0 + 8 * q;
-        for_row_blocks<MI>(h, [&](auto desc, auto at, auto mi) {
+        for_row_blocks<MI>(h, [&](auto desc, auto at, auto mi, auto whole) {
             const Cols8 gc = swap_cols(acc[mi][0], acc[mi][1]), uc = swap_cols(acc[mi][2], acc[mi][3]);
             Cols8 hc;
 #pragma unroll
             for (int k = 0; k < 8; ++k) hc.v[k] = gc.v[k] * sigmoid_f(gc.v[k]) * uc.v[k];
-            const u32x4 hp = pack_cols(hc);
+            u32x4 hp = pack_cols(hc);
             buf_store(hp, desc(h), at(off));
             if (saved) {
                 buf_store(pack_cols(gc), desc(g), at(off));
                 buf_store(pack_cols(uc), desc(u), at(off));
             }
             if (transposed) {
+                // zeros past the last row: the sums there are 0 * W, and that is NaN where W is not finite
+                if (!whole && row0 + mi * 16 + r16 >= Meff) hp = u32x4{0u, 0u, 0u, 0u};
                 tb.template put<mi & 1>(hp);
                 if constexpr ((mi & 1) == 1) {
                     u32x4 c0, c1;

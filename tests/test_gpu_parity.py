@@ -843,3 +843,35 @@ def test_down_tile_heights(R, C, I, r_host):
     got = bits_of(out)
     assert np.array_equal(got[sk], p.hidden[sk])
     assert max_slice_rel_l2(O.bf16_bits_to_f64(got[idx]), O.bf16_bits_to_f64(fo["out_bits"][idx]), axis=1) < REL_L2_TOL
+
+
+@pytest.mark.parametrize("R", [1, 64, 65, 200, 300, 773, 1400])
+@pytest.mark.parametrize("r_host", [True, False], ids=["R-host", "R-device"])
+def test_weights_that_are_not_finite_stay_in_their_columns(R, r_host):
+    """An infinite weight makes a column of H infinite (here in every row: its gate and the weighted activation are positive),
+    a NaN makes one NaN.  Past the row count the transposed copy is zero all the same, so the gradient of an infinite column
+    is infinite where it has one sign in every row, and the other columns are as ever."""
+    C, I, c_in, i_inf, i_nan = 264, 8264, 17, 4101, 133
+    w = W.small(C=C, I=I, visual=(R + 30,), text=(1,), keep=(R - 1,), seed=3600 + R, name=f"non-finite-{R}")
+    assert w.R == R
+    p = Problem(w)
+    p.hidden[:, c_in] &= 0x7FFF                          # positive activations in column c_in, gradients in column 0
+    p.grad[:, 0] &= 0x7FFF
+    p.wg[i_inf, :] = 0
+    p.wg[i_inf, c_in] = 0x3F80                           # gate = that activation
+    fo = O.skipffn_forward(p.hidden, p.mask, p.wg, p.wu, p.wd, None, w.eps)
+    bo = O.skipffn_backward(p.hidden, p.mask, p.wg, p.wu, p.wd, p.grad, None, w.eps)
+    p.wu[i_inf, c_in] = 0x7F80                           # infinity
+    p.wg[i_nan, c_in] = 0x7FC0                           # NaN
+    p.d_hidden, p.d_grad, p.d_wg, p.d_wu = (to_dev_bf16(x) for x in (p.hidden, p.grad, p.wg, p.wu))
+    assert np.all(p.hidden[fo["idx"], c_in] != 0) and np.all(p.grad[fo["idx"], 0] != 0)
+    _, bufs = gpu_forward(p, R_host=r_host)
+    _, dw = gpu_backward(p, bufs, R_host=r_host)
+    ht = bits_of(bufs.saved_views(R)["HT"])
+    assert not ht[:, R:(R + 63) // 64 * 64].any()
+    assert np.all(ht[i_inf, :R] == 0x7F80)
+    got = f64_of(dw[2])
+    assert got[0, i_inf] == np.inf
+    assert np.isnan(got[:, i_nan]).all()
+    finite = np.delete(np.arange(I), [i_inf, i_nan])
+    assert rel_l2(got[:, finite], bo["dw_down"][:, finite]) < REL_L2_TOL
