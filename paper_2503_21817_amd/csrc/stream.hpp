@@ -664,12 +664,17 @@ __global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_rows_kernel(GemmArgs
     if (Meff <= 0) return;
     const int b = (int)blockIdx.x, nb = (int)gridDim.x;
     const int columns = P.tiles_n * P.splits;                // tiles of a tile row
-    StreamRows plan = stream_rows_plan(Meff, columns, nb, P.outT0 != nullptr);
+    const int slabs = ((Keff + BK - 1) / BK + P.splits - 1) / P.splits;
+    StreamRows plan = stream_rows_plan(Meff, columns, slabs, nb, P.outT0 != nullptr, EPI == EPI_SWIGLU);
     plan = StreamRows{uniform(plan.full), uniform(plan.mi)};
-    const int base = plan.full * 256 < Meff ? plan.full * 256 : Meff, after = plan.full * columns;
+    int base = 0, after = 0;                                 // rows and tiles of the first of two parts
     if (plan.full > 0) {
-        stream_grid<8, EPI>(P, b, nb, base, Meff, Keff);
-        if (plan.mi == 0) return;
+        if constexpr (EPI == EPI_SWIGLU) {
+            base = plan.full * 256 < Meff ? plan.full * 256 : Meff;
+            after = plan.full * columns;
+        }
+        stream_grid<8, EPI>(P, b, nb, EPI == EPI_SWIGLU ? base : Meff, Meff, Keff);
+        if (EPI != EPI_SWIGLU || plan.mi == 0) return;
         lds_barrier();                                       // other stages, other parts of them
     }
     switch (plan.mi) {                                       // uniform

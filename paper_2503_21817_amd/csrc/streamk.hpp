@@ -118,38 +118,52 @@ SKIPFFN_HD inline bool streamk_next(const StreamKPlan& p, StreamKIter& it, Strea
     return true;
 }
 
-// Output tiles of a GEMM with `rows` rows and `tiles_n` tile columns on `cus` workgroups: `full` rows of tiles of 256 rows,
-// then tiles of 32 * mi rows (mi = 4 .. 7) over the rest, if any.  (The kernels plan with the row count on the device.)
+// Output tiles of a GEMM with `rows` rows, `columns` tile columns (times the parts its K range is cut into) and `slabs` K
+// slabs a tile on `cus` workgroups: `full` rows of tiles of 256 rows, then one row of tiles of 32 * mi rows (mi = 4 .. 7)
+// over the rest, if any (two_parts); or (full = 0) tiles of 32 * mi rows throughout.  (The kernels plan with the row count on
+// the device.)
 //
-// A round of tiles costs 34 + 6.5 mi us (measured, gate/up at C = 4096, I = 14336: 60, 67, 74, 79, 86 a round for mi = 4 .. 8
-// on 448 to 2944 rows; a slab's phases and loads do not shrink with the rows).  So tall tiles win unless others leave fewer
-// rows empty or save a round, or a last row of lower tiles fits where tall ones end unevenly: 368 rows 93 us on 192-row
-// tiles, 102 on 256; 640 rows 139 on 160, 163; 768 rows 148 on 192, 165; 1200 rows 245 on 224, 250; 940, 1472 and 2048
-// rows best on 256.  Between the two parts the pipeline drains once (about 5 us); a sixteenth of the work in all decides
-// between equal makespans.  even: heights of 64 rows only (transposed copies are zero up to a multiple of 64 rows).
+// A round of tiles costs 34 + 6.5 mi us (measured, gate/up at C = 4096, I = 14336, 64 slabs: 60, 67, 74, 79, 86 a round for
+// mi = 4 .. 8 on 448 to 2944 rows; a slab's phases and loads do not shrink with the rows).  So tall tiles win unless others
+// leave fewer rows empty or save a round, or a last row of lower tiles fits where tall ones end unevenly: 368 rows 93 us on
+// 192-row tiles, 102 on 256; 640 rows 139 on 160, 163; 768 rows 148 on 192, 165; 1200 rows 245 on 224, 250; 940, 1472 and 2048
+// rows best on 256.  A sixteenth of the work in all decides between equal makespans.  even: heights of 64 rows only
+// (transposed copies are zero up to a multiple of 64 rows).
+//
+// Two parts are the gate/up GEMM's: in the down GEMM they gave nothing (0.93 to 1.05 of the best single height, 1.00 on average,
+// at 5000 to 10500 rows, C = 11520 to 15360, I = 256 to 3072).  Between the two the pipeline drains, about 5 us whatever K.  And the low tiles read the weights again, alone: rows of
+// tiles that run together share them, but a row of its own is no faster than its 32 KB a slab and tile come from memory (5 TB/s).
+// Gate/up with saved buffers, two parts / one height, us:  C = 8192, I = 28672: 420 rows 400 / 351, 580 rows 528 / 489, 700 rows
+// 562 / 519;  C = 1024, I = 32768: 640 rows 104 / 97, 1472 rows 218 / 201;  without:  C = 8192, I = 28672: 396 rows 1.18 times as
+// long.  Where the low tiles fit into a round that the tall ones leave uneven, two parts stay the better ones:  C = 8192, I = 14336:
+// 420 rows 163 / 174;  C = 4096, I = 14336, without: 5149 rows 4 % shorter.
 struct StreamRows { int full, mi; };
-SKIPFFN_HD inline int stream_tile_cost(int mi) { return 68 + 13 * mi; }
-SKIPFFN_HD inline StreamRows stream_rows_plan(int rows, int tiles_n, int cus, bool even) {
+SKIPFFN_HD inline int stream_tile_cost(int mi) { return 68 + 13 * mi; }       // 64 slabs, in units of 0.5 us
+SKIPFFN_HD inline StreamRows stream_rows_plan(int rows, int columns, int slabs, int cus, bool even, bool two_parts) {
     const int tall = stream_tile_cost(8);
     StreamRows best{(rows + 255) / 256, 0};
-    int n = best.full * tiles_n;
+    int n = best.full * columns;
     int best_cost = (n + cus - 1) / cus * tall + n / 16 * tall / cus;
     for (int mi = 7; mi >= 4; --mi) {
         if (even && (mi & 1)) continue;
-        n = (rows + 32 * mi - 1) / (32 * mi) * tiles_n;
+        n = (rows + 32 * mi - 1) / (32 * mi) * columns;
         const int cost = (n + cus - 1) / cus * stream_tile_cost(mi) + n / 16 * stream_tile_cost(mi) / cus;
         if (cost < best_cost) { best = StreamRows{0, mi}; best_cost = cost; }
     }
     const int full = rows / 256, rest = rows - full * 256;
     int mi = (rest + 31) / 32;
     mi = mi < 4 ? 4 : (even ? (mi + 1) / 2 * 2 : mi);
-    if (full > 0 && rest > 0 && mi < 8) {
+    if (two_parts && full > 0 && rest > 0 && mi < 8) {
         // the tall tiles go round the workgroups, the low ones on from there
-        const int low = stream_tile_cost(mi), q = full * tiles_n / cus, r = full * tiles_n - q * cus;
-        const int after = r + tiles_n;                       // low tiles end here, counted from the first workgroup of the last round
-        int span = q * tall + (r > 0 ? tall : 0);
-        if (after > cus || r == 0) span = q * tall + (r > 0 ? tall : 0) + (after - (r > 0 ? cus : 0) + cus - 1) / cus * low;
-        const int cost = span + 10 + (full * tiles_n / 16 * tall + tiles_n / 16 * low) / cus;
+        const int low = stream_tile_cost(mi), read = columns * 5 / 6, q = full * columns / cus, r = full * columns - q * cus;
+        const int last = r + columns;                        // low tiles end here, counted from the first workgroup of the last round
+        int head = q * tall + (r > 0 ? tall : 0), tail = 0;
+        if (r == 0 || last > cus) {
+            tail = (last - (r > 0 ? cus : 0) + cus - 1) / cus * low;
+            tail = tail > read ? tail : read;
+            if (full == 1) head = head > read ? head : read;
+        }
+        const int cost = head + tail + 640 / (slabs > 0 ? slabs : 1) + (full * columns / 16 * tall + columns / 16 * low) / cus;
         if (cost < best_cost) best = StreamRows{full, mi};
     }
     return best;

@@ -11,6 +11,18 @@ from paper_2503_21817_amd import workloads as W
 REL_L2_TOL = 1e-2   # relative L2 bound on retained outputs and gradients (bf16 in, fp32 accumulate)
 
 
+# (R, C, I, with a saved buffer) -> tiles of the gate/up GEMM on 256 compute units: rows of 256-row tiles + 32nds of
+# the rows of the tiles after them, as tests/cpp/plan_print.cpp writes them.  Two parts, every height of the second, its last row just begun.
+TWO_PART_GATE_UP = {
+    (1345, 1016, 18776, False): "5+4",
+    (897, 1016, 19672, False): "3+5",
+    (929, 2040, 19672, False): "3+6",
+    (449, 4088, 21848, False): "1+7",
+    (769, 1016, 19672, True): "3+4",
+    (385, 2040, 21848, True): "1+6",
+}
+
+
 def to_dev_bf16(bits: np.ndarray) -> torch.Tensor:
     return torch.from_numpy(np.ascontiguousarray(bits).view(np.int16)).cuda().view(torch.bfloat16)
 

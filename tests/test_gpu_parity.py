@@ -9,7 +9,7 @@ import torch
 from oracle import skipffn_oracle as O
 from paper_2503_21817_amd import binding as B
 from paper_2503_21817_amd import workloads as W
-from helpers import REL_L2_TOL, Problem, bits_of, f64_of, rel_l2, to_dev_bf16
+from helpers import REL_L2_TOL, TWO_PART_GATE_UP, Problem, bits_of, f64_of, rel_l2, to_dev_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -540,11 +540,10 @@ def test_buffers_sized_for_a_larger_row_bound(R_max):
 @pytest.mark.parametrize("R", [257, 300, 384, 385, 512 + 1, 512 + 128, 768 + 100])
 @pytest.mark.parametrize("I", [1368, 8264], ids=["tiles-of-all-rows", "core"])
 def test_last_tile_row_of_at_most_128_rows(R, I):
-    """A row count that leaves at most 128 rows for the last row of tiles runs that row on
-    128-row tiles in the gate/up GEMM of the general core (257, 300, 384, 513, 640, 868; 385 leaves 129 rows
-    and keeps a full-height tile), which I = 8264 takes: more gate/up tiles than CUs.  The narrower layer runs on several
-    tiles of all rows, the last one cut off.  Every row is checked on its own: the tail rows sit in
-    different tiles from the rest.  The intermediate width leaves a ragged column tile too."""
+    """Row counts that leave 1 to 129 rows past a multiple of 256.  The wide layer (more gate/up tiles than CUs) runs its
+    gate/up GEMM on tiles of 128 rows (257, 300, 384, 868), 192 (385, 513) or 256 (640), the last row of them cut off or
+    whole.  The narrower layer runs on several tiles of all rows, the last one cut off.  Every row is checked on its
+    own, forward and backward.  The intermediate width leaves a ragged column tile too."""
     from helpers import max_slice_rel_l2
     w = W.small(C=520, I=I, visual=(R + 30,), text=(9,), keep=(R - 9,), seed=900 + R, name=f"tail-{R}")
     assert w.R == R
@@ -805,7 +804,7 @@ def test_weight_gradients_of_more_tiles_than_compute_units(R, flags):
 def test_gate_up_tile_heights(R, I, r_host, saved):
     """65 tile columns: without a saved buffer tiles of 128, 160, 192, 224, 256 and 128 rows, with one (heights of 64 rows
     only) of 128, 192, 192, 256, 256 and 128; row counts one past a tile's height, where the last is nearly empty.  101
-    tile columns and 1400 rows: five rows of 256-row tiles, then one of 128.
+    tile columns and 1400 rows: seven rows of 224-row tiles, or six of 256.
     Every row is checked on its own, the transposed copy bit for bit, zeros up to the next multiple of 64 rows included."""
     from helpers import max_slice_rel_l2
     w = W.small(C=264, I=I, visual=(R + 30,), text=(9,), keep=(R - 9,), seed=3300 + R, name=f"heights-{R}")
@@ -824,6 +823,32 @@ def test_gate_up_tile_heights(R, I, r_host, saved):
         h, ht = bits_of(sv["H"]), bits_of(sv["HT"])
         assert np.array_equal(ht[:, :R], h.T)
         assert not ht[:, R:(R + 63) // 64 * 64].any()
+
+
+@pytest.mark.parametrize("R,C,I,saved", TWO_PART_GATE_UP, ids=lambda v: str(v))
+def test_gate_up_in_two_parts(R, C, I, saved):
+    """Rows of 256-row tiles, then one row of 128 to 224 rows in the same launch, one row past the last height, K and the last
+    tile column cut off; the row count on the host and on the device.  Every row is checked on its own, the transposed copy
+    bit for bit."""
+    from helpers import max_slice_rel_l2
+    w = W.small(C=C, I=I, visual=(R + 30,), text=(9,), keep=(R - 9,), seed=3500 + R, name=f"two-parts-{R}")
+    assert w.R == R
+    p = Problem(w)
+    fo = O.skipffn_forward(p.hidden, p.mask, p.wg, p.wu, p.wd, None, w.eps)
+    idx, sk = fo["idx"], p.mask != 0
+    for r_host in (True, False):
+        print(f"two parts R={R} C={C} I={I} saved={saved} R_host={r_host}", flush=True)
+        out, bufs = gpu_forward(p, R_host=r_host, saved=saved)
+        got = bits_of(out)
+        assert np.array_equal(got[sk], p.hidden[sk])
+        assert max_slice_rel_l2(O.bf16_bits_to_f64(got[idx]), O.bf16_bits_to_f64(fo["out_bits"][idx]), axis=1) < REL_L2_TOL
+        if saved:
+            sv = bufs.saved_views(R)
+            for k in ("G", "U", "H"):
+                assert max_slice_rel_l2(f64_of(sv[k]), fo[k], axis=1) < REL_L2_TOL, k
+            h, ht = bits_of(sv["H"]), bits_of(sv["HT"])
+            assert np.array_equal(ht[:, :R], h.T)
+            assert not ht[:, R:(R + 63) // 64 * 64].any()
 
 
 @pytest.mark.parametrize("R,C,I", [(257, 1032, 8264), (769, 1032, 8264), (961, 1032, 8264), (1153, 1032, 8264),
