@@ -23,6 +23,8 @@
 // down and dXn GEMMs at 17 and 33 tile rows.)
 #pragma once
 
+#include <stdint.h>
+
 #if defined(__HIPCC__)
 #define SKIPFFN_HD __host__ __device__
 #else
@@ -137,6 +139,11 @@ SKIPFFN_HD inline bool streamk_next(const StreamKPlan& p, StreamKIter& it, Strea
 // 562 / 519;  C = 1024, I = 32768: 640 rows 104 / 97, 1472 rows 218 / 201;  without:  C = 8192, I = 28672: 396 rows 1.18 times as
 // long.  Where the low tiles fit into a round that the tall ones leave uneven, two parts stay the better ones:  C = 8192, I = 14336:
 // 420 rows 163 / 174;  C = 4096, I = 14336, without: 5149 rows 4 % shorter.
+//
+// With saved buffers (even) a tile column stores 1 KB a row.  Where K is so short that a round takes no longer than its stores (a
+// tall tile's 256 KB about 26 us, its slabs 1.35 us each) and all stores are more than the last-level cache of 256 MB takes in,
+// low tiles only shorten the runs in which the transposed copy is written.  C = 520, I = 28672 (9 slabs), 192-row tiles / 256, us:
+// 1300 rows 162 / 147, 1700 rows 216 / 174, 2000 rows 279 / 191; below that size 300 rows 41 / 47.  16 slabs (C = 1024) are even.
 struct StreamRows { int full, mi; };
 SKIPFFN_HD inline int stream_tile_cost(int mi) { return 68 + 13 * mi; }       // 64 slabs, in units of 0.5 us
 SKIPFFN_HD inline StreamRows stream_rows_plan(int rows, int columns, int slabs, int cus, bool even, bool two_parts) {
@@ -144,6 +151,7 @@ SKIPFFN_HD inline StreamRows stream_rows_plan(int rows, int columns, int slabs, 
     StreamRows best{(rows + 255) / 256, 0};
     int n = best.full * columns;
     int best_cost = (n + cus - 1) / cus * tall + n / 16 * tall / cus;
+    if (even && slabs <= 12 && (int64_t)rows * columns > 256 * 1024) return best;
     for (int mi = 7; mi >= 4; --mi) {
         if (even && (mi & 1)) continue;
         n = (rows + 32 * mi - 1) / (32 * mi) * columns;

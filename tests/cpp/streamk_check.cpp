@@ -80,6 +80,12 @@ int main() {
         }
         ++cases;
     }
+    // a short K and more to store than the last-level cache takes in: 256-row tiles (measured, C = 520, I = 28672)
+    for (int rows : {1300, 1625, 1700, 2000, 2121}) {
+        const StreamRows p = stream_rows_plan(rows, 224, 9, 256, true, true);
+        if (p.mi != 0) { printf("rows=%d short K: full=%d mi=%d\n", rows, p.full, p.mi); return 1; }
+        ++cases;
+    }
     printf("ok %ld\n", cases);
     return 0;
 }
