@@ -38,6 +38,7 @@
 #include "common.hpp"
 #include "layout.hpp"
 #include "streamk.hpp"
+#include "tilelists.hpp"
 
 namespace skipffn {
 
@@ -47,7 +48,6 @@ constexpr int OPER_BYTES = BM * BK * 2;             // 32 KB per operand slab
 constexpr int LDS_B_BASE = NSTAGE_A * OPER_BYTES;
 constexpr int GEMM_LDS_BYTES = (NSTAGE_A + NSTAGE_B) * OPER_BYTES;  // 160 KB
 constexpr int EPI_ROWS = 32;                         // rows of C staged per epilogue pass and row group
-constexpr int PANEL_M = 8;                          // tile-order panel width (L2 locality)
 
 enum EpiKind : int {
     EPI_SWIGLU = 0,        // B = {W_gate, W_up} interleaved per tile; out0=H, out1=G, out2=U (bf16)

@@ -13,39 +13,15 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_kernel(GemmArgs P) {
 // ---- balanced split-K for GEMMs that leave through fp32 partial slabs (see streamk.hpp) ------
 // grid = tiles_n * nbg workgroups (P.splits carries nbg); EPI_PARTIAL only
 __global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_streamk_kernel(GemmArgs P) {
-    const int nbg = P.splits;
-    const int nb = (int)gridDim.x;
-    const int tiles_n = nb / nbg;
-    int b = (int)blockIdx.x;
-    // workgroups are dealt round-robin to the 8 XCDs: give each XCD a contiguous range of the
-    // logical order below
-    if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);
+    const int nbg = P.splits, tiles_n = (int)gridDim.x / nbg;
     const int Meff = effective_rows(P.M, P.m_dev);
     const int Keff = effective_rows(P.K, P.k_dev);
     const int g = (Meff + BM - 1) / BM;
     const int kt = ((Keff + BK - 1) / BK) * P.pairs;
     if (g == 0 || kt == 0) return;
     const StreamKPlan p = streamk_plan(g, kt, nbg);
-    // Logical order: aligned chunks first, chunk-major, then n-tile, then m-tile - so an XCD
-    // works on ONE K range of many n-tiles (the m-tiles of an n-tile share the weight slabs,
-    // the n-tiles share the activation slabs, and no XCD streams the whole K extent of the
-    // activations); the remainder pieces follow.  (tn, j) = n-tile and workgroup index in its group.
-    // (With more tiles than workgroups in a group every workgroup starts with whole tiles of its own,
-    // see streamk.hpp; the order below is that of the gr tiles that are split.)
     int tn, j;
-    const int gr = p.gr;
-    const int aligned_total = p.a * gr * tiles_n;
-    if (b < aligned_total) {
-        const int c = b / (tiles_n * gr);
-        const int r = b - c * (tiles_n * gr);
-        tn = r / gr;
-        j = c * gr + (r - tn * gr);
-    } else {
-        const int per = nbg - p.a * gr;           // workgroups per group left for the remainder
-        const int r = b - aligned_total;
-        tn = r / per;
-        j = p.a * gr + (r - tn * per);
-    }
+    balanced_share(p, tiles_n, (int)blockIdx.x, tn, j);
     StreamKIter it = streamk_begin(p, j);
     StreamKSeg sg;
     bool first = true;
@@ -136,6 +112,8 @@ hipError_t launch_gemm(bool a_kc, bool b_kc, int epi, GemmArgs& a, hipStream_t s
     finish_args(epi, a);
     if (grid_blocks(a) == 0 || a.tiles_n <= 0) return hipSuccess;
     if (b_kc && a.pairs != 1) return hipErrorInvalidValue;
+    const int kt = std::max((a.K + BK - 1) / BK, 1);         // a part of K without slabs would end a list of tiles
+    if (b_kc && (a.splits - 1) * ((kt + a.splits - 1) / a.splits) >= kt) return hipErrorInvalidValue;
     if (a_kc && b_kc && epi == EPI_SWIGLU) return launch_stream<EPI_SWIGLU>(&stream_gemm_rows_kernel<EPI_SWIGLU>, a, s);
     if (a_kc && b_kc && epi == EPI_PARTIAL) return launch_stream<EPI_PARTIAL>(&stream_gemm_rows_kernel<EPI_PARTIAL>, a, s);
     if (a_kc && b_kc && epi == EPI_RESID_SCATTER) return launch_stream<EPI_RESID_SCATTER>(&stream_gemm_rows_kernel<EPI_RESID_SCATTER>, a, s);

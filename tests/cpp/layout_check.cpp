@@ -63,7 +63,11 @@ static const char* check_plan(long R, long C, long I, bool hs, bool balanced, in
         if (p.k_down.sk_nbg * tiles_n > ncu) return "balanced split larger than the chip";
         for (int i = 0; i < tiles_m; ++i)
             if (streamk_count(sk, i) * slab > room) return "the slabs of the balanced split do not fit";
-    } else if (p.k_down.splits > 1 && p.k_down.splits * slab > room) return "the slabs of the core do not fit";
+    } else {
+        const int s = p.k_down.splits;
+        if (s > 1 && s * slab > room) return "the slabs of the core do not fit";
+        if ((s - 1) * ((ktiles + s - 1) / s) >= ktiles) return "a split of the core without slabs";
+    }
     return nullptr;
 }
 
@@ -132,6 +136,7 @@ int main() {
                                 const int tiles_m = (int)((R + BM - 1) / BM), ktiles = pairs * (int)((I + BK - 1) / BK);
                                 const KPartition kp = choose_k_partition(tiles_m, tiles_n, ktiles, forced != 0, ncu);
                                 if (kp.splits < 1 || kp.splits > kMaxSplits) return fail("split factor out of range", R, C, I, ncu);
+                                if ((kp.splits - 1) * ((ktiles + kp.splits - 1) / kp.splits) >= ktiles) return fail("a split without slabs", R, C, I, ncu);
                                 if (kp.sk_nbg > 0) {
                                     if (kp.sk_nbg * tiles_n > ncu) return fail("balanced split larger than the chip", R, C, I, ncu);
                                     const StreamKPlan p = streamk_plan(tiles_m, ktiles, kp.sk_nbg);

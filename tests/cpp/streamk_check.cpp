@@ -1,11 +1,42 @@
 // Brute-force check of the balanced K split (csrc/streamk.hpp): for every (g, kt, nbg) in a
 // range, every K slab of every tile is covered exactly once, slot numbers of a tile are
 // 0..count-1 without repeats, counts stay within the partial-slab budget, and no workgroup
-// gets more than q slabs beyond its whole tiles.  Prints "ok <cases>" or the first violation.
+// gets more than q slabs beyond its whole tiles.  Then the lists of tiles that the kernels run (csrc/tilelists.hpp): the
+// balanced lists are the segments of streamk_next, the lists of a plain grid cover every tile and K slab once, and the
+// launch order hands out every share once.  Prints "ok <cases>" or the first violation.
+#include <algorithm>
 #include <cstdio>
+#include <random>
 #include <vector>
-#include "../../paper_2503_21817_amd/csrc/streamk.hpp"
+#include "../../paper_2503_21817_amd/csrc/layout.hpp"
+#include "../../paper_2503_21817_amd/csrc/tilelists.hpp"
 using namespace skipffn;
+
+// the lists of all workgroups of one grid
+template <bool SPLIT>
+static const char* check_grid(int workgroups, int tiles_m, int tiles_n, int splits, int batch, int ktiles, int after) {
+    std::vector<int> cover((size_t)tiles_m * tiles_n * batch * ktiles, 0);
+    long total = 0, most = 0;
+    for (int b = 0; b < workgroups; ++b) {
+        const GridWork<SPLIT> w(b, workgroups, tiles_m, tiles_n, splits, batch, ktiles, after);
+        StreamTile t{};
+        long n = 0;
+        for (; w.get((int)n, t); ++n) {
+            if (t.tm < 0 || t.tm >= tiles_m || t.tn < 0 || t.tn >= tiles_n || t.z < 0 || t.z >= splits || (t.second && batch == 1))
+                return "tile out of range";
+            if (t.kb < 0 || t.kb >= t.ke || t.ke > ktiles) return "K range";
+            const size_t tile = ((size_t)(t.second ? 1 : 0) * tiles_m + t.tm) * tiles_n + t.tn;
+            for (int k = t.kb; k < t.ke; ++k) cover[tile * ktiles + k]++;
+        }
+        if (w.get((int)n + 1, t)) return "a list that goes on after its end";
+        total += n;
+        most = std::max(most, n);
+    }
+    for (int c : cover) if (c != 1) return "coverage";
+    if (total != (long)tiles_m * tiles_n * splits * batch) return "number of tiles";
+    if (most > (total + workgroups - 1) / workgroups + 1) return "balance";
+    return nullptr;
+}
 
 int main() {
     long cases = 0;
@@ -24,8 +55,14 @@ int main() {
                 for (int j = 0; j < nbg; ++j) {
                     StreamKIter it = streamk_begin(p, j);
                     StreamKSeg s;
-                    int work = 0;
+                    const BalancedWork list(p, 3, j);
+                    StreamTile t{};
+                    int work = 0, i = 0;
                     while (streamk_next(p, it, s)) {
+                        if (!list.get(i++, t) || t.tm != s.i || t.kb != s.kb || t.ke != s.ke || t.z != s.slot || t.tn != 3 || t.second) {
+                            printf("list g=%d kt=%d nbg=%d j=%d segment %d\n", g, kt, nbg, j, i - 1);
+                            return 1;
+                        }
                         if (s.i < 0 || s.i >= g || s.kb < 0 || s.ke > kt || s.kb >= s.ke) {
                             printf("bad segment g=%d kt=%d nbg=%d j=%d: i=%d [%d,%d)\n", g, kt, nbg, j, s.i, s.kb, s.ke);
                             return 1;
@@ -34,6 +71,7 @@ int main() {
                         slots[s.i].push_back(s.slot);
                         work += s.ke - s.kb;
                     }
+                    if (list.get(i, t)) { printf("list too long g=%d kt=%d nbg=%d j=%d\n", g, kt, nbg, j); return 1; }
                     if (work > p.full * kt + (p.gr > 0 ? p.q : 0)) { printf("overload g=%d kt=%d nbg=%d j=%d: %d > q=%d\n", g, kt, nbg, j, work, p.q); return 1; }
                 }
                 for (int x = 0; x < g * kt; ++x)
@@ -49,6 +87,45 @@ int main() {
                 }
                 ++cases;
             }
+    // every share of a balanced split is taken by one workgroup
+    for (int tiles_n : {1, 2, 3, 5, 8, 12, 16, 31})
+        for (int nbg : {1, 2, 5, 8, 16, 21, 64})
+            for (int g : {1, 3, 6, 17, 70})
+                for (int kt : {1, 9, 64, 224}) {
+                    const StreamKPlan p = streamk_plan(g, kt, nbg);
+                    std::vector<int> seen(tiles_n * nbg, 0);
+                    for (int b = 0; b < tiles_n * nbg; ++b) {
+                        int tn = -1, j = -1;
+                        balanced_share(p, tiles_n, b, tn, j);
+                        if (tn < 0 || tn >= tiles_n || j < 0 || j >= nbg || seen[tn * nbg + j]++) {
+                            printf("order g=%d kt=%d nbg=%d tiles_n=%d b=%d: tn=%d j=%d\n", g, kt, nbg, tiles_n, b, tn, j);
+                            return 1;
+                        }
+                    }
+                    ++cases;
+                }
+    // divisions of tile counts, at the multiples and one below, up to the largest count
+    for (int d = 1; d < 70000; d += d < 300 ? 1 : 997)
+        for (int64_t n = d; n <= 0x7fffffff; n = n < 50 * (int64_t)d ? n + d : n / d * 2 * d + d)
+            for (const int64_t m : {n - 1, n, std::min<int64_t>(n + d - 1, 0x7fffffff)})
+                if (TileDiv(d).div((int)m) != m / d) { printf("%ld / %d = %d\n", (long)m, d, TileDiv(d).div((int)m)); return 1; }
+    // plain grids: one or two problems, K whole or cut as the planner cuts it, fewer than 256 workgroups too, and the second
+    // part of a launch, which goes on where the first ended
+    std::mt19937 rng(1);
+    auto pick = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
+    for (int n = 0; n < 4000; ++n) {
+        const int workgroups = 8 * pick(1, 32), tiles_m = pick(1, n % 4 ? 12 : 40), tiles_n = pick(1, n % 3 ? 20 : 120), ktiles = pick(1, 70);
+        const int after = n % 2 ? pick(0, 3000) : 0;
+        const int splits = choose_k_split(tiles_m * tiles_n, ktiles, kMaxSplits, workgroups), batch = splits == 1 ? pick(1, 2) : 1;
+        const char* bad = check_grid<true>(workgroups, tiles_m, tiles_n, splits, batch, ktiles, after);
+        if (bad == nullptr) bad = check_grid<false>(workgroups, tiles_m, tiles_n, 1, 1, ktiles, after);
+        if (bad != nullptr) {
+            printf("%s: workgroups=%d tiles %d x %d splits=%d batch=%d ktiles=%d after=%d\n", bad, workgroups, tiles_m, tiles_n, splits, batch,
+                   ktiles, after);
+            return 1;
+        }
+        ++cases;
+    }
     // tile rows of the row plan: all rows covered, no tile row without rows, the heights that exist
     for (int even = 0; even < 2; ++even)
         for (int tiles_n : {1, 6, 17, 56, 65, 112, 300})
