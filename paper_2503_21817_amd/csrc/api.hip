@@ -318,7 +318,7 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
         a.out0 = H; a.out1 = G; a.out2 = U; a.ldo = (int)I;
         a.outT0 = HT; a.ldt = (int)ld_transposed(Rb);         // written by the epilogue when training
         a.ncu = num_cus();
-        e = launch_gemm(true, true, EPI_SWIGLU, a, s);
+        e = launch_gemm(true, EPI_SWIGLU, a, s);
     }
     profile_mark_end(KC_GEMM_GATE_UP, s);
     if (e != hipSuccess) return hip_fail(e);
@@ -356,13 +356,13 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
         profile_mark_begin(KC_GEMM_DOWN, s);
         if (kp.splits == 1 && kp.sk_nbg == 0) {
             a.out0 = out; a.e0 = static_cast<const bf16_t*>(hidden);
-            e = launch_gemm(true, true, EPI_RESID_SCATTER, a, s);
+            e = launch_gemm(true, EPI_RESID_SCATTER, a, s);
             profile_mark_end(KC_GEMM_DOWN, s);
             if (e != hipSuccess) return hip_fail(e);
         } else {
             a.partial = partial;
-            e = kp.sk_nbg > 0 ? launch_gemm_streamk(true, true, a, kp.sk_nbg, s)
-                              : launch_gemm(true, true, EPI_PARTIAL, a, s);
+            e = kp.sk_nbg > 0 ? launch_gemm_streamk(true, a, kp.sk_nbg, s)
+                              : launch_gemm(true, EPI_PARTIAL, a, s);
             profile_mark_end(KC_GEMM_DOWN, s);
             if (e != hipSuccess) return hip_fail(e);
             const PartialLayout pl{kp.splits, kp.sk_nbg, ktiles};
@@ -470,7 +470,7 @@ int skipffn_backward(int64_t T, int64_t C, int64_t I, float eps, const void* gra
         b.pairs = 1; b.splits = 1;
         b.out0 = dw_down; b.ldo = (int)I; b.out_f32 = f32; b.accumulate = accum; b.ncu = num_cus();
         profile_mark_begin(KC_GEMM_DH_DWDOWN, s);
-        e = launch_gemm_dual(DUAL_DH_DWDOWN, a, b, s);
+        e = launch_gemm_dh_dw_down(a, b, s);
         profile_mark_end(KC_GEMM_DH_DWDOWN, s);
         if (e != hipSuccess) return hip_fail(e);
     }
@@ -484,7 +484,7 @@ int skipffn_backward(int64_t T, int64_t C, int64_t I, float eps, const void* gra
         a.pairs = 1; a.splits = 1; a.batch = 2;
         a.out0 = dw_gate; a.out1 = dw_up; a.ldo = (int)C; a.out_f32 = f32; a.accumulate = accum; a.ncu = num_cus();
         profile_mark_begin(KC_GEMM_DW_GATE_UP, s);
-        e = launch_gemm(true, true, EPI_STORE, a, s);
+        e = launch_gemm(true, EPI_STORE, a, s);
         profile_mark_end(KC_GEMM_DW_GATE_UP, s);
         if (e != hipSuccess) return hip_fail(e);
     }
@@ -502,12 +502,12 @@ int skipffn_backward(int64_t T, int64_t C, int64_t I, float eps, const void* gra
         const int ktiles = 2 * (int)((I + BK - 1) / BK);
         const KPartition kp = choose_k_partition(tiles_m, tiles_n, ktiles, (flags & SKIPFFN_FLAG_BALANCED_SPLIT) != 0,
                                                  num_cus());
-        a.splits = kp.splits; a.ncu = num_cus();
+        a.splits = kp.splits;
         pl = PartialLayout{kp.splits, kp.sk_nbg, ktiles};
         a.partial = partial;
         profile_mark_begin(KC_GEMM_DXN, s);
-        e = kp.sk_nbg > 0 ? launch_gemm_streamk(true, false, a, kp.sk_nbg, s)
-                          : launch_gemm(true, false, EPI_PARTIAL, a, s);
+        e = kp.sk_nbg > 0 ? launch_gemm_streamk(false, a, kp.sk_nbg, s)
+                          : launch_gemm(false, EPI_PARTIAL, a, s);
         profile_mark_end(KC_GEMM_DXN, s);
         if (e != hipSuccess) return hip_fail(e);
     }

@@ -81,8 +81,7 @@ static hipError_t launch_stream(void (*kernel)(GemmArgs), const GemmArgs& a, hip
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_dual(int which, GemmArgs& a0, GemmArgs& a1, hipStream_t s) {
-    if (which != DUAL_DH_DWDOWN) return hipErrorInvalidValue;
+hipError_t launch_gemm_dh_dw_down(GemmArgs& a0, GemmArgs& a1, hipStream_t s) {
     finish_args(EPI_SWIGLU_BWD, a0);
     finish_args(EPI_STORE, a1);
     const int real0 = (int)grid_blocks(a0), n0 = (real0 + 7) / 8 * 8, tiles1 = (int)grid_blocks(a1);
@@ -95,10 +94,10 @@ hipError_t launch_gemm_dual(int which, GemmArgs& a0, GemmArgs& a1, hipStream_t s
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_streamk(bool a_kc, bool b_kc, GemmArgs& a, int nbg, hipStream_t s) {
+hipError_t launch_gemm_streamk(bool b_kc, GemmArgs& a, int nbg, hipStream_t s) {
     finish_args(EPI_PARTIAL, a);
     if (a.tiles_m <= 0 || a.tiles_n <= 0) return hipSuccess;
-    if (nbg < 1 || !a_kc || a.batch != 1 || (b_kc && a.pairs != 1)) return hipErrorInvalidValue;
+    if (nbg < 1 || a.batch != 1 || (b_kc && a.pairs != 1)) return hipErrorInvalidValue;
     a.splits = nbg;
     const unsigned blocks = (unsigned)(a.tiles_n * nbg);
     if (b_kc)
@@ -108,17 +107,17 @@ hipError_t launch_gemm_streamk(bool a_kc, bool b_kc, GemmArgs& a, int nbg, hipSt
     return hipGetLastError();
 }
 
-hipError_t launch_gemm(bool a_kc, bool b_kc, int epi, GemmArgs& a, hipStream_t s) {
+hipError_t launch_gemm(bool b_kc, int epi, GemmArgs& a, hipStream_t s) {
     finish_args(epi, a);
     if (grid_blocks(a) == 0 || a.tiles_n <= 0) return hipSuccess;
     if (b_kc && a.pairs != 1) return hipErrorInvalidValue;
     const int kt = std::max((a.K + BK - 1) / BK, 1);         // a part of K without slabs would end a list of tiles
     if (b_kc && (a.splits - 1) * ((kt + a.splits - 1) / a.splits) >= kt) return hipErrorInvalidValue;
-    if (a_kc && b_kc && epi == EPI_SWIGLU) return launch_stream<EPI_SWIGLU>(&stream_gemm_rows_kernel<EPI_SWIGLU>, a, s);
-    if (a_kc && b_kc && epi == EPI_PARTIAL) return launch_stream<EPI_PARTIAL>(&stream_gemm_rows_kernel<EPI_PARTIAL>, a, s);
-    if (a_kc && b_kc && epi == EPI_RESID_SCATTER) return launch_stream<EPI_RESID_SCATTER>(&stream_gemm_rows_kernel<EPI_RESID_SCATTER>, a, s);
-    if (a_kc && b_kc && epi == EPI_STORE) return launch_stream<EPI_STORE>(&stream_gemm_kernel<EPI_STORE>, a, s);
-    if (!a_kc || b_kc || epi != EPI_PARTIAL || a.batch != 1) return hipErrorInvalidValue;
+    if (b_kc && epi == EPI_SWIGLU) return launch_stream<EPI_SWIGLU>(&stream_gemm_rows_kernel<EPI_SWIGLU>, a, s);
+    if (b_kc && epi == EPI_PARTIAL) return launch_stream<EPI_PARTIAL>(&stream_gemm_rows_kernel<EPI_PARTIAL>, a, s);
+    if (b_kc && epi == EPI_RESID_SCATTER) return launch_stream<EPI_RESID_SCATTER>(&stream_gemm_rows_kernel<EPI_RESID_SCATTER>, a, s);
+    if (b_kc && epi == EPI_STORE) return launch_stream<EPI_STORE>(&stream_gemm_kernel<EPI_STORE>, a, s);
+    if (b_kc || epi != EPI_PARTIAL || a.batch != 1) return hipErrorInvalidValue;
     hipLaunchKernelGGL(gemm_bf16_kernel, dim3(grid_blocks(a)), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a);
     return hipGetLastError();
 }

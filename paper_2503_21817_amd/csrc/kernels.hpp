@@ -145,14 +145,11 @@ hipError_t launch_mid_rows_down(const bf16_t* H, int rows, const int32_t* r_dev,
 
 // ---- GEMMs -----------------------------------------------------------------------
 hipError_t gemm_init();   // raises the dynamic-LDS limit of every instantiation (once per process)
-// layouts: a_kc / b_kc as in gemm.hpp
-hipError_t launch_gemm(bool a_kc, bool b_kc, int epi, GemmArgs& args, hipStream_t s);
-// two independent GEMMs in one grid (problem 0 is dispatched first)
-enum DualKind : int {
-    DUAL_DH_DWDOWN = 0    // SwiGLU backward (dH -> dG, dU)  +  store (dW_down = dY^T * H)
-};
-hipError_t launch_gemm_dual(int which, GemmArgs& a0, GemmArgs& a1, hipStream_t s);
+// A is K-contiguous; b_kc: B too (stream.hpp), or N-contiguous (gemm.hpp)
+hipError_t launch_gemm(bool b_kc, int epi, GemmArgs& args, hipStream_t s);
+// two independent GEMMs in one grid, the first dispatched first: SwiGLU backward (dH -> dG, dU), and store (dW_down = dY^T * H)
+hipError_t launch_gemm_dh_dw_down(GemmArgs& dh, GemmArgs& dw, hipStream_t s);
 // balanced split-K GEMM into fp32 partial slabs (EPI_PARTIAL): nbg workgroups per n-tile group
-hipError_t launch_gemm_streamk(bool a_kc, bool b_kc, GemmArgs& args, int nbg, hipStream_t s);
+hipError_t launch_gemm_streamk(bool b_kc, GemmArgs& args, int nbg, hipStream_t s);
 
 }  // namespace skipffn

@@ -31,11 +31,12 @@ constexpr int kMaxSplitsNarrow = 16;     // up to 256 rows: small fp32 slabs, an
 // cost a write now and a read in the reducing kernel.
 // A split of fewer than 4 slabs would be all prologue (at least 8 before: the dXn GEMM of the 32-row, C = 256 layer, 22
 // slabs on 2 workgroups, ended its training step at 65.1 us, on 5 at 61.3).
-//   splits == 1, sk_nbg == 0 : one workgroup per tile, epilogue fused
+//   splits == 1, sk_nbg == 0 : K whole; the epilogue of the down GEMM adds the residual, dXn leaves as one fp32 slab
 //   splits  > 1, sk_nbg == 0 : plain split-K into `splits` fp32 slabs
-//   sk_nbg  > 0              : balanced split (stream_gemm_balanced_kernel), sk_nbg workgroups per
-//                              n-tile group (with more m-tiles than workgroups in a group, every
+//   sk_nbg  > 0              : balanced split (down: stream_gemm_balanced_kernel, dXn: gemm_bf16_streamk_kernel), sk_nbg
+//                              workgroups per n-tile group (with more m-tiles than workgroups in a group, every
 //                              workgroup first runs whole tiles of its own; the rest is split)
+// Both GEMMs are planned in 256-row tiles.  The down GEMM then lowers them where K is not balanced (stream_rows_plan).
 struct KPartition { int splits; int sk_nbg; };
 inline KPartition choose_k_partition(int tiles_m, int tiles_n, int ktiles, bool force_balanced, int ncu) {
     const int tiles = tiles_m * tiles_n;
@@ -151,7 +152,7 @@ inline int gate_up_splits(int64_t C, int64_t I, int ncu) {
 }
 
 // Which kernels a forward call launches.
-enum FwdKernel { FWD_FEW, FWD_MID, FWD_CORE };           // fewrows.hip, midrows.hip, gemm.hpp
+enum FwdKernel { FWD_FEW, FWD_MID, FWD_CORE };           // fewrows.hip, midrows.hip, stream.hpp
 struct ForwardPlan {
     FwdKernel gate_up, down;
     int gate_up_splits;                                  // FWD_MID

@@ -765,8 +765,8 @@ def test_one_gemm_on_the_register_path(R, C, I, r_host):
 def test_weight_gradients_of_more_tiles_than_compute_units(R, flags):
     """Every workgroup runs several tiles of dW as one stream of K slabs: 1 slab a tile (the loads run two tiles ahead) to 5,
     cut-off tiles at the right and lower edge, both data types, overwritten and added to; the row count on the device, 0
-    included (zeros, or nothing added).  Bound: REL_L2_TOL for the gradient, plus one rounding of a sum of gradient and
-    old value of like size to bf16 (2^-9 of it) where it is added to."""
+    included (zeros, or nothing added).  Bound: REL_L2_TOL; where a bf16 gradient is added to, the rounding of the sum with an
+    old value of like size (2^-9 of it) is far inside it."""
     C, I = 2056, 8712                                    # 9 x 35 tiles of 256 x 256 for each matrix
     w = W.small(C=C, I=I, visual=(300,), text=(1 if R else 0,), keep=(max(R - 1, 0),), seed=610 + R, name=f"dw-stream-{R}")
     assert w.R == R
