@@ -36,7 +36,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_streamk_kernel(GemmArg
 // [0, n0) run a tile of dH each (the longer ones, dispatched first), the rest lists of tiles of dW_down, so the last round
 // of one fills with work of the other.  n0 is a multiple of 8 (workgroups past the tiles leave at once): both problems see the
 // round-robin XCD assignment from its start.  dW_down as a stream, sums stored from registers, us a launch before / after:
-// 368 rows 126 / 122, 640 rows 177 / 172, 2944 rows 604 / 590, 4096 rows 811 / 805.
+// 368 rows 120 / 120, 640 rows 165 / 160, 2944 rows 609 / 598, 4096 rows 792 / 791.
 __global__ __launch_bounds__(GEMM_THREADS) void gemm_dh_dw_down_kernel(GemmArgs P0, GemmArgs P1, int n0) {
     const int b = (int)blockIdx.x;
     if (b < n0)
