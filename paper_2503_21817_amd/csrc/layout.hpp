@@ -1,6 +1,6 @@
 // Host-side planning of the Skip-FFN block: how the `saved` buffer and the workspaces are carved
 // into sections, and how the K range of a GEMM is cut over the compute units.  Plain C++ (no HIP
-// constructs), shared by the library's entry points and by a host checker that is built with the
+// constructs), shared by the library's entry points and by a host test that is built with the
 // address and undefined-behaviour sanitizers.
 #pragma once
 

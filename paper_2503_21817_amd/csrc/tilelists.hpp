@@ -1,5 +1,5 @@
 // Lists of output tiles that a workgroup of the stream of tiles (stream.hpp) runs, and the order in which the workgroups of a
-// balanced split take their shares.  Plain C++ but for the qualifiers: the kernels and a host checker walk the same code.
+// balanced split take their shares.  Plain C++ but for the qualifiers: the kernels and a host test walk the same code.
 #pragma once
 
 #include "streamk.hpp"
