@@ -288,10 +288,14 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
 
     // which GEMMs: see layout.hpp.  Without a saved buffer (whose layout is the caller's to read) a handful of rows lie
     // chunk-major, as they are loaded.
-    const ForwardPlan plan = plan_forward(Rb, C, I, saved != nullptr, (flags & SKIPFFN_FLAG_BALANCED_SPLIT) != 0, num_cus());
+    const ForwardPlan plan = plan_forward(Rb, C, I, saved != nullptr, (flags & SKIPFFN_FLAG_BALANCED_SPLIT) != 0, num_cus(),
+                                          rms_gain != nullptr);
     const bool chunk_major_xn = plan.gate_up == FWD_FEW && saved == nullptr, chunk_major_h = plan.down == FWD_FEW && saved == nullptr;
-    // (2) gather + RMSNorm
-    e = launch_gather_rmsnorm(static_cast<const bf16_t*>(hidden), idx, (int)Rb, r_dev, (int)C, eps,
+    // (2) gather + RMSNorm, or in the gate/up GEMM
+    const RowNorm rows{static_cast<const bf16_t*>(hidden), T, idx, static_cast<const bf16_t*>(rms_gain), eps};
+    const RowNorm* norm = plan.norm_in_gate_up ? &rows : nullptr;
+    if (norm == nullptr)
+        e = launch_gather_rmsnorm(static_cast<const bf16_t*>(hidden), idx, (int)Rb, r_dev, (int)C, eps,
                               static_cast<const bf16_t*>(rms_gain), xrows, xn, rstd, chunk_major_xn, s);
     if (e != hipSuccess) return hip_fail(e);
     if (xnT != nullptr) {   // K-contiguous copy of the normalised rows for the dW_gate / dW_up GEMMs
@@ -304,10 +308,10 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
     const bf16_t *wg = static_cast<const bf16_t*>(w_gate), *wu = static_cast<const bf16_t*>(w_up);
     profile_mark_begin(KC_GEMM_GATE_UP, s);
     if (plan.gate_up == FWD_FEW) {
-        e = launch_few_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_xn, chunk_major_h, s);
+        e = launch_few_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_xn, chunk_major_h, norm, s);
     } else if (plan.gate_up == FWD_MID) {
         e = launch_mid_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_h, plan.gate_up_splits,
-                                    partial, s);
+                                    partial, norm, s);
     } else {
         GemmArgs a{};
         a.M = (int)Rb; a.N = (int)I; a.K = (int)C; a.m_dev = r_dev;

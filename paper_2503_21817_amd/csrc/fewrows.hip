@@ -23,6 +23,8 @@ namespace skipffn {
 
 constexpr int FR_COLS = 16;                   // output columns per workgroup
 constexpr int FR_UNROLL = 8;                  // k-steps of 32 loaded together
+// RMSNorm of the rows beside their product: no, x * rstd, x * gain * rstd
+enum FewNorm : int { NORM_NONE = 0, NORM_PLAIN = 1, NORM_GAIN = 2 };
 constexpr int FR_WAVES_GU = 4, FR_WAVES_DOWN = 8;      // wavefronts that share K
 
 struct FewRowsArgs {
@@ -34,13 +36,15 @@ struct FewRowsArgs {
     // gate/up: H as A with strides h_row, h_chunk; G, U [rows][N], optional
     bf16_t* H; uint32_t h_row, h_chunk; bf16_t* G; bf16_t* U;
     const int32_t* idx; const bf16_t* res; bf16_t* out; int no_residual;   // down: res, out [T][N]
+    const bf16_t* gain; float eps;            // gate/up that normalises its rows itself: A = hidden [T][K], rows idx
 };
 
-template <int MT, int WAVES, bool GATE_UP>
+template <int MT, int WAVES, bool GATE_UP, int NORM>
 __global__ __launch_bounds__(WAVES * 64) void few_rows_kernel(FewRowsArgs P) {
     constexpr int NW = GATE_UP ? 2 : 1;       // weight matrices
     static_assert(MT <= WAVES, "a wavefront of the epilogue per 16 rows");
     __shared__ f32x4 red[WAVES][NW * MT][64];
+    __shared__ float red_ss[NORM != NORM_NONE ? WAVES : 1][MT][64];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int R = effective_rows(P.rows, P.r_dev);
@@ -58,8 +62,10 @@ __global__ __launch_bounds__(WAVES * 64) void few_rows_kernel(FewRowsArgs P) {
     const uint32_t b_off = n0 + r16 < P.N ? (uint32_t)(((int64_t)(n0 + r16) * P.K + kq * 8) * 2) : kOobOffset;
     uint32_t a_off[MT];
 #pragma unroll
-    for (int m = 0; m < MT; ++m)
-        a_off[m] = m * 16 + r16 < R ? (uint32_t)(m * 16 + r16) * P.a_row + (uint32_t)kq * P.a_chunk : kOobOffset;
+    for (int m = 0; m < MT; ++m) {
+        const int row = m * 16 + r16;
+        a_off[m] = row < R ? (uint32_t)(NORM != NORM_NONE ? P.idx[row] : row) * P.a_row + (uint32_t)kq * P.a_chunk : kOobOffset;
+    }
     const uint32_t a_step = 4 * P.a_chunk;
 
     f32x4 acc[NW][MT];
@@ -67,6 +73,19 @@ __global__ __launch_bounds__(WAVES * 64) void few_rows_kernel(FewRowsArgs P) {
     for (int w = 0; w < NW; ++w)
 #pragma unroll
         for (int m = 0; m < MT; ++m) acc[w][m] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    float ss[MT];                             // squares of the lane's k of its rows
+#pragma unroll
+    for (int m = 0; m < MT; ++m) ss[m] = 0.0f;
+    const __amdgpu_buffer_rsrc_t rg = make_rsrc(P.gain, NORM == NORM_GAIN ? (uint32_t)P.K * 2 : 0u);
+    auto normalise = [&](int m, u32x4& av, const u32x4& gv) {
+        bf16x8 x = __builtin_bit_cast(bf16x8, av);
+        ss[m] = add_squares(x, ss[m]);
+        if (NORM == NORM_GAIN) {
+            float g[8];
+            unpack_bf16x8(__builtin_bit_cast(bf16x8, gv), g);
+            av = __builtin_bit_cast(u32x4, scale_bf16x8(x, g));
+        }
+    };
     auto mfma = [&](int w, int m, const u32x4& bv, const u32x4& av) {
         // weights first: a lane's four results are four consecutive columns of one row
         acc[w][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bv), __builtin_bit_cast(bf16x8, av),
@@ -78,7 +97,7 @@ __global__ __launch_bounds__(WAVES * 64) void few_rows_kernel(FewRowsArgs P) {
     int s = wave * per;
     const int s_end = s + per < steps ? s + per : steps;
     const int s_full = s_end < P.K / 32 ? s_end : P.K / 32;
-    u32x4 b[NW][FR_UNROLL], a[MT][FR_UNROLL];
+    u32x4 b[NW][FR_UNROLL], a[MT][FR_UNROLL], g[NORM == NORM_GAIN ? FR_UNROLL : 1];
     auto load_batch = [&]() {
 #pragma unroll
         for (int u = 0; u < FR_UNROLL; ++u) {
@@ -87,15 +106,18 @@ __global__ __launch_bounds__(WAVES * 64) void few_rows_kernel(FewRowsArgs P) {
 #pragma unroll
             for (int m = 0; m < MT; ++m)
                 a[m][u] = __builtin_amdgcn_raw_buffer_load_b128(ra, (int)a_off[m], (int)((uint32_t)(s + u) * a_step), 0);
+            if (NORM == NORM_GAIN) g[u] = __builtin_amdgcn_raw_buffer_load_b128(rg, kq * 16, (s + u) * 64, 0);
         }
     };
     auto mfma_batch = [&]() {
 #pragma unroll
         for (int u = 0; u < FR_UNROLL; ++u)
 #pragma unroll
-            for (int m = 0; m < MT; ++m)
+            for (int m = 0; m < MT; ++m) {
+                if (NORM != NORM_NONE) normalise(m, a[m][u], g[NORM == NORM_GAIN ? u : 0]);
 #pragma unroll
                 for (int w = 0; w < NW; ++w) mfma(w, m, b[w][u], a[m][u]);
+            }
     };
     const bool any_batch = s + FR_UNROLL <= s_full;
     if (any_batch) load_batch();
@@ -121,7 +143,9 @@ __global__ __launch_bounds__(WAVES * 64) void few_rows_kernel(FewRowsArgs P) {
         if (NW == 2) bt[NW - 1] = buf_load16(rb1, bo);
 #pragma unroll
         for (int m = 0; m < MT; ++m) {
-            const u32x4 at = buf_load16(ra, in && a_off[m] != kOobOffset ? a_off[m] + (uint32_t)s * a_step : kOobOffset);
+            u32x4 at = buf_load16(ra, in && a_off[m] != kOobOffset ? a_off[m] + (uint32_t)s * a_step : kOobOffset);
+            if (NORM != NORM_NONE)
+                normalise(m, at, NORM == NORM_GAIN ? buf_load16(rg, in ? (uint32_t)(s * 64 + kq * 16) : kOobOffset) : u32x4{0u, 0u, 0u, 0u});
 #pragma unroll
             for (int w = 0; w < NW; ++w) mfma(w, m, bt[w], at);
         }
@@ -131,7 +155,18 @@ __global__ __launch_bounds__(WAVES * 64) void few_rows_kernel(FewRowsArgs P) {
     for (int w = 0; w < NW; ++w)
 #pragma unroll
         for (int m = 0; m < MT; ++m) red[wave][w * MT + m][lane] = acc[w][m];
+    if (NORM != NORM_NONE) {
+#pragma unroll
+        for (int m = 0; m < MT; ++m) red_ss[wave][m][lane] = ss[m];
+    }
     __syncthreads();
+    float rstd = 1.0f;
+    if (NORM != NORM_NONE && wave < MT) {
+        float sq = red_ss[0][wave][lane];
+#pragma unroll
+        for (int q = 1; q < WAVES; ++q) sq += red_ss[q][wave][lane];
+        rstd = rstd_of_lanes(sq, P.K, P.eps);
+    }
     if (!mine) return;
     f32x4 v[NW];
 #pragma unroll
@@ -141,7 +176,11 @@ __global__ __launch_bounds__(WAVES * 64) void few_rows_kernel(FewRowsArgs P) {
         for (int q = 1; q < WAVES; ++q) v[w] += red[q][w * MT + wave][lane];
     }
     if (GATE_UP) {
-        const f32x4 g = v[0], u = v[NW - 1];
+        f32x4 g = v[0], u = v[NW - 1];
+        if (NORM != NORM_NONE) {
+            g *= rstd;
+            u *= rstd;
+        }
         float h[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) h[j] = g[j] * sigmoid_f(g[j]) * u[j];
@@ -162,16 +201,16 @@ __global__ __launch_bounds__(WAVES * 64) void few_rows_kernel(FewRowsArgs P) {
     }
 }
 
-template <int WAVES, bool GATE_UP>
+template <int WAVES, bool GATE_UP, int NORM = NORM_NONE>
 static hipError_t launch_few_rows(const FewRowsArgs& a, hipStream_t s) {
     if (a.rows <= 0 || a.N <= 0) return hipSuccess;
     const dim3 grid((unsigned)((a.N + FR_COLS - 1) / FR_COLS)), block(WAVES * 64);
     if (a.rows <= 16)
-        hipLaunchKernelGGL((few_rows_kernel<1, WAVES, GATE_UP>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((few_rows_kernel<1, WAVES, GATE_UP, NORM>), grid, block, 0, s, a);
     else if (a.rows <= 32)
-        hipLaunchKernelGGL((few_rows_kernel<2, WAVES, GATE_UP>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((few_rows_kernel<2, WAVES, GATE_UP, NORM>), grid, block, 0, s, a);
     else if (a.rows <= kFewRowsMax)
-        hipLaunchKernelGGL((few_rows_kernel<4, WAVES, GATE_UP>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((few_rows_kernel<4, WAVES, GATE_UP, NORM>), grid, block, 0, s, a);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();
@@ -179,7 +218,7 @@ static hipError_t launch_few_rows(const FewRowsArgs& a, hipStream_t s) {
 
 hipError_t launch_few_rows_gate_up(const bf16_t* xn, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_gate,
                                    const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major, bool chunk_major_h,
-                                   hipStream_t s) {
+                                   const RowNorm* norm, hipStream_t s) {
     FewRowsArgs a{};
     a.rows = rows; a.r_dev = r_dev; a.N = I; a.K = C;
     a.A = xn; a.a_bytes = (uint32_t)((int64_t)rows * C * 2);
@@ -187,6 +226,12 @@ hipError_t launch_few_rows_gate_up(const bf16_t* xn, int rows, const int32_t* r_
     a.B0 = w_gate; a.B1 = w_up; a.b_bytes = (uint32_t)((int64_t)I * C * 2);
     a.H = H; a.h_row = chunk_major_h ? 16u : (uint32_t)I * 2; a.h_chunk = chunk_major_h ? (uint32_t)rows * 16 : 16u;
     a.G = G; a.U = U;
+    if (norm != nullptr) {
+        a.A = norm->hidden; a.a_bytes = (uint32_t)(norm->T * C * 2); a.a_row = (uint32_t)C * 2; a.a_chunk = 16u;
+        a.idx = norm->idx; a.gain = norm->gain; a.eps = norm->eps;
+        return norm->gain != nullptr ? launch_few_rows<FR_WAVES_GU, true, NORM_GAIN>(a, s)
+                                     : launch_few_rows<FR_WAVES_GU, true, NORM_PLAIN>(a, s);
+    }
     return launch_few_rows<FR_WAVES_GU, true>(a, s);
 }
 

@@ -152,6 +152,36 @@ __device__ __forceinline__ void static_for(F&& f) {
     static_for_impl(static_cast<F&&>(f), std::make_integer_sequence<int, N>{});
 }
 
+__device__ __forceinline__ void unpack_bf16x8(const bf16x8& x, float (&f)[8]) {
+    const u32x4 v = __builtin_bit_cast(u32x4, x);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        f[2 * k] = bf16lo_to_f32(v[k]);
+        f[2 * k + 1] = bf16hi_to_f32(v[k]);
+    }
+}
+// s + the squares of eight values
+__device__ __forceinline__ float add_squares(const bf16x8& x, float s) {
+    float f[8];
+    unpack_bf16x8(x, f);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) s += f[j] * f[j];
+    return s;
+}
+__device__ __forceinline__ bf16x8 scale_bf16x8(const bf16x8& x, const float (&g)[8]) {
+    float f[8];
+    unpack_bf16x8(x, f);
+    u32x4 v;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = pack_bf16x2(f[2 * k] * g[2 * k], f[2 * k + 1] * g[2 * k + 1]);
+    return __builtin_bit_cast(bf16x8, v);
+}
+// 1 / rms of a row from the sums of squares that the four lanes of a row (lane % 16) hold
+__device__ __forceinline__ float rstd_of_lanes(float ss, int K, float eps) {
+    ss += __shfl_xor(ss, 16, 64);
+    ss += __shfl_xor(ss, 32, 64);
+    return 1.0f / sqrtf(ss / (float)K + eps);
+}
 __device__ __forceinline__ float sigmoid_f(float g) {
     return __builtin_amdgcn_rcpf(1.0f + __expf(-g));
 }

@@ -123,11 +123,14 @@ hipError_t launch_merge_bwd_group(const bf16_t* dout, const SegTable& st, int n_
 hipError_t launch_mfma_probe(int blocks, int iters, int random_operands, float* out, long long* clocks,
                              hipStream_t s);
 
+// A gate/up GEMM that normalises its rows itself reads rows idx of hidden [T][C] and multiplies its sums by 1 / rms
+struct RowNorm { const bf16_t* hidden; int64_t T; const int32_t* idx; const bf16_t* gain; float eps; };
+
 // ---- the forward GEMMs of a handful of rows (rows <= 64) -----------------------------------------------
-// H = silu(xn Wg^T) * (xn Wu^T); G and U optional.  chunk_major, chunk_major_h: xn, H are [K / 8][rows][8] instead of row-major
+// H = silu(xn Wg^T) * (xn Wu^T); G and U optional.  norm != null: xn is not read (few_rows_norm).  chunk_major, chunk_major_h: xn, H are [K / 8][rows][8] instead of row-major
 hipError_t launch_few_rows_gate_up(const bf16_t* xn, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_gate,
                                    const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major, bool chunk_major_h,
-                                   hipStream_t s);
+                                   const RowNorm* norm, hipStream_t s);
 // out[idx[r]] = bf16(res[idx[r]] + H[r] Wd^T)
 hipError_t launch_few_rows_down(const bf16_t* H, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_down,
                                 const int32_t* idx, const bf16_t* res, bf16_t* out, int no_residual, bool chunk_major,
@@ -135,10 +138,10 @@ hipError_t launch_few_rows_down(const bf16_t* H, int rows, const int32_t* r_dev,
 
 // ---- the forward GEMMs of up to 256 rows ------------------------------------------------------------------
 hipError_t mid_rows_init();      // raises the dynamic-LDS limit of every instantiation (once per process)
-// chunk_major_h: H is [I / 8][rows][8] instead of row-major; splits > 1: K cut in fp32 partial[splits][rows][2][I]
+// norm != null: xn is not read (mid_rows_norm).  chunk_major_h: H is [I / 8][rows][8] instead of row-major; splits > 1: K cut in fp32 partial[splits][rows][2][I]
 hipError_t launch_mid_rows_gate_up(const bf16_t* xn, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_gate,
                                    const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major_h, int splits,
-                                   float* partial, hipStream_t s);
+                                   float* partial, const RowNorm* norm, hipStream_t s);
 // fp32 partial[splits][rows][C]
 hipError_t launch_mid_rows_down(const bf16_t* H, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_down,
                                 int splits, float* partial, hipStream_t s);

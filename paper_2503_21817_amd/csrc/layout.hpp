@@ -116,11 +116,13 @@ inline int choose_k_split(int tiles, int ktiles, int max_splits, int ncu) {
 //   down (K = I)      C = 256, I = 688: -6.5;  C = 2048, I = 2048: -4.8 (-3.9) at 16, -3.7 (-0.8) at 64;  C = 1024, I = 3584:
 //     -2.9 (-1.9) at 16, 0.7 (6) at 64;  C = 512, I = 8192: 0.4 (4) at 16, 5 (12) at 32, 11 (27) at 64;  I = 32768: 21 to
 //     133.  With a column block for every CU (C = 4096) the tiles are slower too: I = 14336: -3.3 at 1 row, -0.2 at 16.
+// (Without a saved buffer and a gain the tiles normalise their rows themselves, see norm_in_gate_up: from 33 rows on they take C = 2048, I = 7168
+// in 38.7 us at 64 rows, registers 40.9.)
 constexpr int64_t kFewRowsMax = 64;
-inline bool few_rows_gate_up(int64_t rows, int64_t C, int64_t I, bool has_saved) {
+inline bool few_rows_gate_up(int64_t rows, int64_t C, int64_t I, bool has_saved, bool has_gain) {
     const int64_t weight = C * I, limit = (int64_t)40 * 2048 * 7168;
     if (rows > kFewRowsMax || weight > (int64_t)24 << 20 || rows * weight > (has_saved ? limit / 2 : limit)) return false;
-    return C <= (rows <= 16 ? 4096 : rows <= 32 ? (has_saved ? 2048 : 3072) : (has_saved ? 1024 : 2048));
+    return C <= (rows <= 16 ? 4096 : rows <= 32 ? (has_saved ? 2048 : 3072) : (has_saved || !has_gain ? 1024 : 2048));
 }
 inline bool few_rows_down(int64_t rows, int64_t C, int64_t I, bool has_saved, int ncu) {
     if (rows > kFewRowsMax || rows * C * I > (int64_t)1 << (has_saved ? 29 : 30)) return false;
@@ -151,20 +153,36 @@ inline int gate_up_splits(int64_t C, int64_t I, int ncu) {
     return best;
 }
 
+// Without a saved buffer nothing but the gate/up GEMM reads the normalised rows, and 1 / rms can be applied to its sums: the
+// squares of a row are added beside the product, the gain is multiplied into the rows.  It saves a launch, and the rounding of
+// the normalised rows: error of a layer against 64 bits 2.3e-3 instead of 3.5e-3.  On registers (row-major rows then) it
+// pays where these are few or narrow, on tiles for 64 rows without a gain, whose product every wavefront would have to form for all
+// rows.  Layer forward, us, in the GEMM / before it:  registers  C = 256, I = 688: 11.4 / 14.3;  C = 1024, I = 3584: 8 rows 14.9 /
+// 17.7, 64 rows 24.4 / 27.2 (with a gain 26.4 / 27.3);  C = 2048, I = 7168: 8 rows 28.0 / 29.8, 16 rows 31.3 / 32.2, 32 rows 36.0
+// / 34.6;  C = 4096, I = 4096: 16 rows 26.2 / 29.7;  tiles  C = 4096, I = 14336: 8 rows 67.4 / 70.5, 64 rows 74.0 / 76.3 (with
+// a gain 92.1 / 71.2 and 98.8 / 76.7);  C = 3072, I = 10752: 8 rows 45.6 / 48.9, 64 rows 57.1 / 59.4.
+constexpr int64_t kNormInMidRows = 64;
+inline bool norm_in_gate_up(int64_t rows, int64_t C, bool has_gain, bool registers) {
+    return registers ? rows <= 16 || C <= 1024 : rows <= kNormInMidRows && !has_gain;
+}
+
 // Which kernels a forward call launches.
 enum FwdKernel { FWD_FEW, FWD_MID, FWD_CORE };           // fewrows.hip, midrows.hip, stream.hpp
 struct ForwardPlan {
     FwdKernel gate_up, down;
+    bool norm_in_gate_up;                                // the rows are normalised by the gate/up GEMM, not before it
     int gate_up_splits;                                  // FWD_MID
     KPartition k_down;                                   // FWD_MID: plain split; FWD_CORE: as choose_k_partition; FWD_FEW: none
 };
 // most fp32 slabs the down GEMM of `rows` rows may write (fwd_ws has room for them)
 inline int max_down_splits(int64_t rows) { return rows <= 256 ? kMaxSplitsNarrow : kMaxSplits; }
-inline ForwardPlan plan_forward(int64_t rows, int64_t C, int64_t I, bool has_saved, bool balanced, int ncu) {
-    ForwardPlan p{FWD_CORE, FWD_CORE, 1, KPartition{1, 0}};
+inline ForwardPlan plan_forward(int64_t rows, int64_t C, int64_t I, bool has_saved, bool balanced, int ncu,
+                                bool has_gain = false) {
+    ForwardPlan p{FWD_CORE, FWD_CORE, false, 1, KPartition{1, 0}};
     if (!balanced && mid_rows(rows, C, I, ncu)) {
-        p.gate_up = few_rows_gate_up(rows, C, I, has_saved) ? FWD_FEW : FWD_MID;
+        p.gate_up = few_rows_gate_up(rows, C, I, has_saved, has_gain) ? FWD_FEW : FWD_MID;
         if (p.gate_up == FWD_MID && rows <= 256) p.gate_up_splits = gate_up_splits(C, I, ncu);
+        p.norm_in_gate_up = !has_saved && p.gate_up_splits == 1 && norm_in_gate_up(rows, C, has_gain, p.gate_up == FWD_FEW);
         p.down = few_rows_down(rows, C, I, has_saved, ncu) ? FWD_FEW : mid_rows_down(rows, C, ncu) ? FWD_MID : FWD_CORE;
     }
     const int ktiles = (int)((I + BK - 1) / BK);

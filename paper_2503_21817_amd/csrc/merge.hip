@@ -84,7 +84,8 @@ __global__ __launch_bounds__(SLAB_THREADS) void selfsim_kernel(const bf16_t* __r
         goff[l] = gr < n ? (uint32_t)(((int64_t)gr * C + c * 8) * 2) : kOobOffset;
     }
     f32x4 acc[TILE / 32][2];
-    slab_loop<TILE, 16>(rx, rx, goff, (wave & 3) * 32, 0, (C + BK - 1) / BK, 0, C, acc);
+    float ss[TILE / 32];
+    slab_loop<TILE, 16>(rx, rx, goff, (wave & 3) * 32, 0, (C + BK - 1) / BK, 0, C, acc, ss);
     float* S = sim + set * sim_stride;
 #pragma unroll
     for (int m = 0; m < TILE / 32; ++m)

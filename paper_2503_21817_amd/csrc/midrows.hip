@@ -16,6 +16,10 @@
 // Measured at C = 4096, I = 14336 in a kernel trace (the loads of the weights alone: 41 + 21 us): gate/up 43 / 50 / 58 / 65
 // us and down 26 / 32 / 37 / 43 us at 64 / 128 / 184 / 256 rows; 128-row tiles with the weights shared through L2: 73
 // and 41 at 184.  Split gate/up and its reduction, 128 rows:  C = 8192, I = 512: 13.2 + 7.1 us;  C = 4096, I = 2048: 15.5 + 4.3.
+//
+// NORM: gate/up of up to 64 rows on the rows as they are in the hidden states, normalised beside the product (layout.hpp,
+// norm_in_gate_up).  A fragment's squares are 16 vector operations of one of the four wavefronts that read it; with all
+// four adding all fragments and a gain multiplied in, the loop becomes bound by them (C = 4096, 8 rows: 92 instead of 67 us a layer).
 #include "kernels.hpp"
 #include "slabloop.hpp"
 
@@ -32,9 +36,11 @@ struct MidRowsArgs {
     // gate/up: 16-byte chunk c (8 columns) of row r of H at byte r * h_row + c * h_chunk; G, U [rows][N], optional
     bf16_t* H; uint32_t h_row, h_chunk; bf16_t* G; bf16_t* U;
     float* partial;                           // down: [splits][rows][N]; gate/up with splits > 1: [splits][rows][2][N]
+    // gate/up that normalises its rows itself: A = hidden [T][K], of which the rows idx are taken
+    const int32_t* idx; float eps;
 };
 
-template <int MT, bool GATE_UP>
+template <int MT, bool GATE_UP, bool NORM>
 __global__ __launch_bounds__(SLAB_THREADS) void mid_rows_kernel(MidRowsArgs P) {
     constexpr int MI = MT / 2;                // row fragments of a wavefront
     constexpr int NLA = kSlabPiecesA<16 * MT>, NL = kSlabPieces<16 * MT>;
@@ -67,21 +73,38 @@ __global__ __launch_bounds__(SLAB_THREADS) void mid_rows_kernel(MidRowsArgs P) {
     for (int l = 0; l < NL; ++l) {
         const int q = l < NLA ? wave * NLA + l : wave * 2 + (l - NLA);
         const int row = 8 * q + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
-        const int gr = l < NLA ? m0 + row : n0 + (GATE_UP ? row & 63 : row);
+        int gr = l < NLA ? m0 + row : n0 + (GATE_UP ? row & 63 : row);
         const bool in = l < NLA ? gr < R : gr < P.N;
+        if (NORM && l < NLA && in) gr = P.idx[gr];
         goff[l] = in ? (uint32_t)(((int64_t)gr * P.K + c * 8) * 2) : kOobOffset;
     }
     f32x4 acc[MI][2];
-    slab_loop<16 * MT, GATE_UP ? 64 : 16>(ra, rb, goff, wn * (GATE_UP ? 16 : 32), kt0, nk, rot, P.K, acc);
+    float ss[MI];
+    slab_loop<16 * MT, GATE_UP ? 64 : 16, NORM>(ra, rb, goff, wn * (GATE_UP ? 16 : 32), kt0, nk, rot, P.K, acc, ss);
 
+    __shared__ float sq[NORM ? 8 : 1][MI][64];
+    if (NORM) {
+#pragma unroll
+        for (int m = 0; m < MI; ++m) sq[wave][m][lane] = ss[m];
+        __syncthreads();
+    }
 #pragma unroll
     for (int m = 0; m < MI; ++m) {
         const int row = m0 + (wm * MI + m) * 16 + r16;
+        float rstd = 1.0f;
+        if (NORM) {
+            const int w0 = wm * 4;
+            rstd = rstd_of_lanes((sq[w0][m][lane] + sq[w0 + 1][m][lane]) + (sq[w0 + 2][m][lane] + sq[w0 + 3][m][lane]), P.K, P.eps);
+        }
         if (row >= R) continue;
         if (GATE_UP) {
             const int n = n0 + wn * 16 + 4 * kq;
             if (n >= P.N) continue;
-            const f32x4 g = acc[m][0], u = acc[m][1];
+            f32x4 g = acc[m][0], u = acc[m][1];
+            if (NORM) {
+                g *= rstd;
+                u *= rstd;
+            }
             if (P.splits > 1) {               // uniform
                 float* p = P.partial + ((int64_t)z * P.rows + row) * 2 * P.N + n;
                 *reinterpret_cast<f32x4*>(p) = g;
@@ -162,11 +185,11 @@ __global__ __launch_bounds__(SWIGLU_THREADS) void swiglu_reduce_kernel(MidRowsAr
     }
 }
 
-template <int MT, bool GATE_UP>
+template <int MT, bool GATE_UP, bool NORM = false>
 static hipError_t launch_mid(const MidRowsArgs& a, hipStream_t s) {
     const int tiles_m = (a.rows + 16 * MT - 1) / (16 * MT), cols = GATE_UP ? SLAB_B_ROWS / 2 : SLAB_B_ROWS;
     const int tiles_n = (a.N + cols - 1) / cols;
-    hipLaunchKernelGGL((mid_rows_kernel<MT, GATE_UP>), dim3((unsigned)(tiles_m * tiles_n * a.splits)), dim3(SLAB_THREADS),
+    hipLaunchKernelGGL((mid_rows_kernel<MT, GATE_UP, NORM>), dim3((unsigned)(tiles_m * tiles_n * a.splits)), dim3(SLAB_THREADS),
                        kSlabLds<16 * MT>, s, a);
     return hipGetLastError();
 }
@@ -181,14 +204,15 @@ static hipError_t launch_mid_rows(const MidRowsArgs& a, hipStream_t s) {
     return launch_mid<16, GATE_UP>(a, s);
 }
 
-template <int MT, bool GATE_UP>
+template <int MT, bool GATE_UP, bool NORM = false>
 static hipError_t mid_lds_limit() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&mid_rows_kernel<MT, GATE_UP>),
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&mid_rows_kernel<MT, GATE_UP, NORM>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, kSlabLds<16 * MT>);
 }
 hipError_t mid_rows_init() {
     hipError_t e;
     if ((e = mid_lds_limit<4, true>()) != hipSuccess) return e;
+    if ((e = mid_lds_limit<4, true, true>()) != hipSuccess) return e;
     if ((e = mid_lds_limit<4, false>()) != hipSuccess) return e;
     if ((e = mid_lds_limit<8, true>()) != hipSuccess) return e;
     if ((e = mid_lds_limit<8, false>()) != hipSuccess) return e;
@@ -200,13 +224,19 @@ hipError_t mid_rows_init() {
 
 hipError_t launch_mid_rows_gate_up(const bf16_t* xn, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_gate,
                                    const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major_h, int splits,
-                                   float* partial, hipStream_t s) {
+                                   float* partial, const RowNorm* norm, hipStream_t s) {
     MidRowsArgs a{};
     a.rows = rows; a.r_dev = r_dev; a.N = I; a.K = C;
     a.A = xn; a.a_bytes = (uint32_t)((int64_t)rows * C * 2);
     a.B0 = w_gate; a.B1 = w_up; a.b_bytes = (uint32_t)((int64_t)I * C * 2);
     a.splits = splits; a.partial = partial; a.H = H; a.G = G; a.U = U;
     a.h_row = chunk_major_h ? 16u : (uint32_t)I * 2; a.h_chunk = chunk_major_h ? (uint32_t)rows * 16 : 16u;
+    if (norm != nullptr) {                    // one row tile; a part of K would not know a row's norm
+        if (rows > kNormInMidRows || splits > 1 || norm->gain != nullptr) return hipErrorInvalidValue;
+        a.A = norm->hidden; a.a_bytes = (uint32_t)(norm->T * C * 2);
+        a.idx = norm->idx; a.eps = norm->eps;
+        return rows <= 0 || I <= 0 ? hipSuccess : launch_mid<4, true, true>(a, s);
+    }
     const hipError_t e = launch_mid_rows<true>(a, s);
     if (e != hipSuccess || splits <= 1 || rows <= 0) return e;
     const int64_t threads = (int64_t)rows * (I >> 3);

@@ -31,10 +31,15 @@ constexpr int kSlabPieces = kSlabPiecesA<A_ROWS> + 2;                    // and 
 // otherwise every slab has to lie inside K); k past K count as zeros.
 // acc[m][f], wavefront (wm, wn): A rows wm * A_ROWS / 2 + 16 m + lane % 16, B rows b_row + f * B_STRIDE + 4 (lane / 16) + r.
 // All 512 threads call it with the same kt0, nk, rot, K.
-template <int A_ROWS, int B_STRIDE>
+//
+// NORM: the rows of A are not normalised yet; their squares are added from the MFMA operands in registers, a fragment by one
+// of the four wavefronts that hold it: ss[m] of a lane gathers k of row ... + 16 m + lane % 16, and the sum over the four lanes
+// of a row in the four wavefronts of the row group is the row's.
+template <int A_ROWS, int B_STRIDE, bool NORM = false>
 __device__ __forceinline__ void slab_loop(const __amdgpu_buffer_rsrc_t ra, const __amdgpu_buffer_rsrc_t rb,
                                           const uint32_t (&goff)[kSlabPieces<A_ROWS>], const int b_row, const int kt0,
-                                          const int nk, const int rot, const int K, f32x4 (&acc)[A_ROWS / 32][2]) {
+                                          const int nk, const int rot, const int K, f32x4 (&acc)[A_ROWS / 32][2],
+                                          float (&ss)[A_ROWS / 32]) {
     static_assert(A_ROWS % 64 == 0 && A_ROWS <= 256, "two row groups, whole pieces per wavefront");
     constexpr int NST = kSlabStages<A_ROWS>, STAGE = kSlabStage<A_ROWS>, B_BASE = A_ROWS * 128;
     constexpr int MI = A_ROWS / 32;           // row fragments of a wavefront
@@ -66,6 +71,8 @@ __device__ __forceinline__ void slab_loop(const __amdgpu_buffer_rsrc_t ra, const
     for (int m = 0; m < MI; ++m)
 #pragma unroll
         for (int f = 0; f < 2; ++f) acc[m][f] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int m = 0; m < MI; ++m) ss[m] = 0.0f;
     uint32_t a_rd[2], b_rd[2];
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
@@ -107,6 +114,13 @@ __device__ __forceinline__ void slab_loop(const __amdgpu_buffer_rsrc_t ra, const
         if (wm == 1) wait_next_slab(steady);
         SKIPFFN_WAIT_LGKMCNT0();
         phase_barrier();
+        if constexpr (NORM) {
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int m = 0; m < MI; ++m)
+                    if (((ks * MI + m) & 3) == (wave & 3)) ss[m] = add_squares(af[ks][m], ss[m]);      // uniform
+        }
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks)
 #pragma unroll

@@ -676,6 +676,30 @@ def test_decode_of_a_wide_layer(R, C, I):
             assert max_slice_rel_l2(O.bf16_bits_to_f64(got[idx]), want, axis=1) < REL_L2_TOL
 
 
+@pytest.mark.parametrize("R,C,I,gain", [(1, 136, 344, True), (16, 2056, 520, True), (17, 1024, 1032, True), (64, 520, 344, False),
+                                        (33, 2056, 7176, False), (64, 4096, 6600, False), (1, 2064, 12296, False)])
+@pytest.mark.parametrize("r_host", [True, False], ids=["R-host", "R-device"])
+def test_norm_inside_the_gate_up_gemm(R, C, I, gain, r_host):
+    """Without a saved buffer few rows are normalised by the gate/up GEMM, on registers (one, two and four row fragments, K
+    ranges that end inside a step) and on 64-row tiles (one row, all of them, ragged K, workgroups that start at different
+    slabs): rows 2^-12 to 2^12 times as large as others, one of zeros.  Rows are checked one by one: xn, H and out are
+    rounded to bf16, 2^-9 rms each."""
+    from helpers import max_slice_rel_l2
+    w = W.small(C=C, I=I, visual=(R + (0 if r_host else min(23, 64 - R)),), text=(1,), keep=(R - 1,), seed=8500 + R, name=f"norm-{R}")
+    assert w.R == R and w.T <= 66
+    p = Problem(w, unit_gain=not gain, with_gain_tensor=gain)
+    scale = 2.0 ** (torch.arange(w.T, device="cuda") * 5 % 25 - 12).float()
+    if R > 8:
+        scale[int(np.flatnonzero(p.mask == 0)[3])] = 0.0
+    p.d_hidden = (p.d_hidden.float() * scale[:, None]).bfloat16()
+    p.hidden = bits_of(p.d_hidden)
+    fo = O.skipffn_forward(p.hidden, p.mask, p.wg, p.wu, p.wd, p.gain if gain else None, w.eps, no_residual=True)
+    idx, sk = fo["idx"], p.mask != 0
+    got = bits_of(gpu_forward(p, R_host=r_host, saved=False, flags=B.FLAG_NO_RESIDUAL)[0])
+    assert np.array_equal(got[sk], p.hidden[sk])
+    assert max_slice_rel_l2(O.bf16_bits_to_f64(got[idx]), O.bf16_bits_to_f64(fo["out_bits"][idx]), axis=1) < REL_L2_TOL
+
+
 @pytest.mark.parametrize("R,C,I", [(65, 4096, 8), (100, 4104, 72), (129, 2056, 264), (200, 4096, 520), (256, 3080, 1032),
                                    (9, 12296, 2056)],
                          ids=["one-column-tile", "ragged-k", "cut-off-tiles", "rotated-starts", "256-rows", "chunk-major-h"])
