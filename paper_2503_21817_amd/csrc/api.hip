@@ -39,6 +39,7 @@ hipError_t ensure_gemm_init() {
     std::call_once(g_gemm_once, [] {
         g_gemm_init_err = gemm_init();
         if (g_gemm_init_err == hipSuccess) g_gemm_init_err = mid_rows_init();
+        if (g_gemm_init_err == hipSuccess) g_gemm_init_err = count_rows_init();
         if (g_gemm_init_err == hipSuccess) g_gemm_init_err = merge_init();
     });
     return g_gemm_init_err;
@@ -291,6 +292,7 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
     const ForwardPlan plan = plan_forward(Rb, C, I, saved != nullptr, (flags & SKIPFFN_FLAG_BALANCED_SPLIT) != 0, num_cus(),
                                           rms_gain != nullptr);
     const bool chunk_major_xn = plan.gate_up == FWD_FEW && saved == nullptr, chunk_major_h = plan.down == FWD_FEW && saved == nullptr;
+    const bool by_count = r_dev != nullptr && Rb > 256 && (flags & SKIPFFN_FLAG_BALANCED_SPLIT) == 0;     // countrows.hip
     // (2) gather + RMSNorm, or in the gate/up GEMM
     const RowNorm rows{static_cast<const bf16_t*>(hidden), T, idx, static_cast<const bf16_t*>(rms_gain), eps};
     const RowNorm* norm = plan.norm_in_gate_up ? &rows : nullptr;
@@ -322,7 +324,9 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
         a.out0 = H; a.out1 = G; a.out2 = U; a.ldo = (int)I;
         a.outT0 = HT; a.ldt = (int)ld_transposed(Rb);         // written by the epilogue when training
         a.ncu = num_cus();
-        e = launch_gemm(true, EPI_SWIGLU, a, s);
+        // (the tiles of all rows leave no transposed copy, and a split gate/up GEMM needs a second kernel)
+        e = by_count && saved == nullptr && gate_up_splits(C, I, num_cus()) == 1 ? launch_gate_up_count(a, s)
+                                                                                : launch_gemm(true, EPI_SWIGLU, a, s);
     }
     profile_mark_end(KC_GEMM_GATE_UP, s);
     if (e != hipSuccess) return hip_fail(e);
@@ -358,7 +362,16 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
         a.idx = idx; a.ldo = (int)C; a.ncu = num_cus();
         a.no_residual = no_residual;
         profile_mark_begin(KC_GEMM_DOWN, s);
-        if (kp.splits == 1 && kp.sk_nbg == 0) {
+        if (by_count) {
+            const RowPlans plans = plan_rows(Rb, C, I, num_cus());
+            a.out0 = out; a.e0 = static_cast<const bf16_t*>(hidden); a.partial = partial;
+            e = launch_down_count(a, plans, s);
+            profile_mark_end(KC_GEMM_DOWN, s);
+            if (e == hipSuccess)
+                e = launch_resid_scatter_count(partial, plans, ktiles, (int)Rb, r_dev, (int)C, idx, static_cast<const bf16_t*>(hidden),
+                                               static_cast<bf16_t*>(out), no_residual, s);
+            if (e != hipSuccess) return hip_fail(e);
+        } else if (kp.splits == 1 && kp.sk_nbg == 0) {
             a.out0 = out; a.e0 = static_cast<const bf16_t*>(hidden);
             e = launch_gemm(true, EPI_RESID_SCATTER, a, s);
             profile_mark_end(KC_GEMM_DOWN, s);

@@ -10,6 +10,11 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_kernel(GemmArgs P) {
     gemm_block<EPI_PARTIAL>(P, (int)blockIdx.x);
 }
 
+// the balanced split with two K-contiguous operands: grid = tiles_n * nbg workgroups (P.splits carries nbg)
+__global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_balanced_kernel(GemmArgs P) {
+    stream_balanced(P, (int)blockIdx.x, (int)gridDim.x / P.splits, P.splits);
+}
+
 // ---- balanced split-K for GEMMs that leave through fp32 partial slabs (see streamk.hpp) ------
 // grid = tiles_n * nbg workgroups (P.splits carries nbg); EPI_PARTIAL only
 __global__ __launch_bounds__(GEMM_THREADS) void gemm_bf16_streamk_kernel(GemmArgs P) {

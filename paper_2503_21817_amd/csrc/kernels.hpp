@@ -61,6 +61,9 @@ struct PartialLayout { int splits; int sk_nbg; int sk_kt; };
 hipError_t launch_resid_scatter(const float* partial, PartialLayout pl, int R, const int32_t* r_dev,
                                 int C, const int32_t* idx, const bf16_t* res, bf16_t* out,
                                 int no_residual, hipStream_t s);
+// the same after launch_down_count: the slabs of the plan that the count on the device has (nothing where its K was whole)
+hipError_t launch_resid_scatter_count(const float* partial, const RowPlans& plans, int ktiles, int R, const int32_t* r_dev, int C,
+                                      const int32_t* idx, const bf16_t* res, bf16_t* out, int no_residual, hipStream_t s);
 // dst[r] = src[idx[r]]  (rows of row_bytes, multiple of 16)
 hipError_t launch_gather_rows(const void* src, void* dst, int64_t row_bytes, const int32_t* idx,
                               int R, const int32_t* r_dev, hipStream_t s);
@@ -145,6 +148,13 @@ hipError_t launch_mid_rows_gate_up(const bf16_t* xn, int rows, const int32_t* r_
 // fp32 partial[splits][rows][C]
 hipError_t launch_mid_rows_down(const bf16_t* H, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_down,
                                 int splits, float* partial, hipStream_t s);
+
+// ---- the forward GEMMs with a row count on the device, below a bound of more than 256 rows (countrows.hip) -----------
+hipError_t count_rows_init();    // raises the dynamic-LDS limits (once per process)
+// up to 256 rows on tiles of all rows, so neither G and U nor the transposed copy
+hipError_t launch_gate_up_count(GemmArgs& args, hipStream_t s);
+// partial (for 16 slabs of 256 rows and 8 of the bound) or out0, e0, idx, as the plan of the count wants them
+hipError_t launch_down_count(GemmArgs& args, const RowPlans& plans, hipStream_t s);
 
 // ---- GEMMs -----------------------------------------------------------------------
 hipError_t gemm_init();   // raises the dynamic-LDS limit of every instantiation (once per process)

@@ -193,6 +193,28 @@ inline ForwardPlan plan_forward(int64_t rows, int64_t C, int64_t I, bool has_sav
     return p;
 }
 
+// A row count on the device, below a bound for which the core runs the down GEMM: the plan of every row of tiles, so that the kernels
+// take that of the rows there are.  Up to 256 rows `mid_splits` parts on tiles of all rows (zstride: 256 rows).
+constexpr int kRowPlans = 64;                            // 16384 rows; the bound's plan beyond
+constexpr uint16_t kRowPlanBalanced = 0x8000;
+struct RowPlans { int mid_splits; uint16_t beyond, down[kRowPlans]; };
+SKIPFFN_HD inline KPartition row_plan(const RowPlans& p, int tiles_m) {
+    const uint16_t v = tiles_m <= kRowPlans ? p.down[tiles_m - 1] : p.beyond;
+    return v & kRowPlanBalanced ? KPartition{1, v & ~kRowPlanBalanced} : KPartition{v, 0};
+}
+inline RowPlans plan_rows(int64_t bound, int64_t C, int64_t I, int ncu) {
+    RowPlans p{};
+    const int ktiles = (int)((I + BK - 1) / BK), tiles_m = (int)((bound + BM - 1) / BM);
+    p.mid_splits = choose_k_split((int)((C + 127) / 128), ktiles, kMaxSplitsNarrow, ncu);
+    auto code = [&](int t) {
+        const KPartition k = choose_k_partition(t, (int)((C + BN - 1) / BN), ktiles, false, ncu);
+        return (uint16_t)(k.sk_nbg > 0 ? kRowPlanBalanced | k.sk_nbg : k.splits);
+    };
+    for (int t = 1; t <= kRowPlans; ++t) p.down[t - 1] = t <= tiles_m ? code(t) : 1;
+    p.beyond = tiles_m > kRowPlans ? code(tiles_m) : 1;
+    return p;
+}
+
 // Leading dimension of the transposed copies ([columns][rows]): rows rounded up to 64 elements, so that every
 // row of a copy starts on a 128-byte line (with a multiple of 8 only, each 128-byte piece the GEMMs load
 // straddles two lines: the weight-gradient GEMMs ran 11-23 % slower at such row counts).

@@ -133,16 +133,16 @@ __device__ __forceinline__ int partial_count(const PartialLayout& pl, int R, int
     return streamk_count(p, r / BM);
 }
 
-__global__ __launch_bounds__(ROW_THREADS) void resid_scatter_kernel(
-    const float* __restrict__ partial, PartialLayout pl, int Rbound, const int32_t* __restrict__ r_dev,
-    int C, const int32_t* __restrict__ idx, const bf16_t* res, bf16_t* out, int no_residual) {
-    const int R = effective_rows(Rbound, r_dev);
+// zrows: rows of a slab
+__device__ __forceinline__ void resid_scatter_chunk(const float* __restrict__ partial, const PartialLayout& pl, const int zrows,
+                                                    const int R, const int C, const int32_t* __restrict__ idx, const bf16_t* res,
+                                                    bf16_t* out, const int no_residual) {
     const int chunks = C >> 3;
     const int64_t g = (int64_t)blockIdx.x * ROW_THREADS + threadIdx.x;
     const int r = (int)(g / chunks), c = (int)(g - (int64_t)r * chunks);
     if (r >= R) return;
     const int64_t orow = (int64_t)idx[r] * C;
-    const int64_t zstride = (int64_t)Rbound * C;
+    const int64_t zstride = (int64_t)zrows * C;
     float acc[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = 0.0f;
@@ -182,6 +182,32 @@ __global__ __launch_bounds__(ROW_THREADS) void resid_scatter_kernel(
         for (int j = 0; j < 8; ++j) acc[j] += x[j];
     }
     *reinterpret_cast<u32x4*>(out + orow + c * 8) = pack8(acc);
+}
+__global__ __launch_bounds__(ROW_THREADS) void resid_scatter_kernel(
+    const float* __restrict__ partial, PartialLayout pl, int Rbound, const int32_t* __restrict__ r_dev,
+    int C, const int32_t* __restrict__ idx, const bf16_t* res, bf16_t* out, int no_residual) {
+    resid_scatter_chunk(partial, pl, Rbound, effective_rows(Rbound, r_dev), C, idx, res, out, no_residual);
+}
+__global__ __launch_bounds__(ROW_THREADS) void resid_scatter_count_kernel(
+    const float* __restrict__ partial, RowPlans plans, int ktiles, int Rbound, const int32_t* __restrict__ r_dev,
+    int C, const int32_t* __restrict__ idx, const bf16_t* res, bf16_t* out, int no_residual) {
+    const int R = effective_rows(Rbound, r_dev);
+    if (R <= 0) return;
+    const bool all_rows = R <= 256;
+    const KPartition k = all_rows ? KPartition{plans.mid_splits, 0} : row_plan(plans, (R + BM - 1) / BM);
+    if (!all_rows && k.splits == 1 && k.sk_nbg == 0) return;            // the GEMM has written the rows itself
+    resid_scatter_chunk(partial, PartialLayout{k.splits, k.sk_nbg, ktiles}, all_rows ? 256 : Rbound, R, C, idx, res, out, no_residual);
+}
+
+hipError_t launch_resid_scatter_count(const float* partial, const RowPlans& plans, int ktiles, int R, const int32_t* r_dev, int C,
+                                      const int32_t* idx, const bf16_t* res, bf16_t* out, int no_residual, hipStream_t s) {
+    if (R <= 0) return hipSuccess;
+    const int64_t total = (int64_t)R * (C >> 3);
+    profile_mark_begin(KC_RESID_SCATTER, s);
+    hipLaunchKernelGGL(resid_scatter_count_kernel, dim3((unsigned)((total + ROW_THREADS - 1) / ROW_THREADS)), dim3(ROW_THREADS), 0, s,
+                       partial, plans, ktiles, R, r_dev, C, idx, res, out, no_residual);
+    profile_mark_end(KC_RESID_SCATTER, s);
+    return hipGetLastError();
 }
 
 hipError_t launch_resid_scatter(const float* partial, PartialLayout pl, int R, const int32_t* r_dev,

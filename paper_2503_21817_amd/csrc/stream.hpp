@@ -524,10 +524,10 @@ __device__ __forceinline__ void stream_gemm(const GemmArgs& P, const Work work, 
 
 // Tiles over the rows [row_base, rows); `after` tiles have been dealt to the workgroups already
 template <int MI, int EPI>
-__device__ __forceinline__ void stream_grid(const GemmArgs& P, const int block, const int workgroups, const int rows, const int Meff,
-                                            const int Keff, const int row_base = 0, const int after = 0) {
+__device__ __forceinline__ void stream_grid(const GemmArgs& P, const int splits, const int block, const int workgroups, const int rows,
+                                            const int Meff, const int Keff, const int row_base = 0, const int after = 0) {
     constexpr bool SPLIT = EPI == EPI_STORE || EPI == EPI_PARTIAL;
-    const GridWork<SPLIT> w(block, workgroups, (rows - row_base + 32 * MI - 1) / (32 * MI), P.tiles_n, P.splits, P.batch,
+    const GridWork<SPLIT> w(block, workgroups, (rows - row_base + 32 * MI - 1) / (32 * MI), P.tiles_n, splits, P.batch,
                             Keff > 0 ? (Keff + BK - 1) / BK : 1, after);
     stream_gemm<MI, EPI>(P, w, Meff, Keff, row_base);
 }
@@ -538,7 +538,7 @@ __device__ __forceinline__ void stream_tall(const GemmArgs& P, const int block, 
     const int Meff = uniform(effective_rows(P.M, P.m_dev));
     int Keff = uniform(effective_rows(P.K, P.k_dev));
     if (EPI == EPI_STORE) Keff = (Keff + BK - 1) / BK * BK;  // the transposed copies are zero up to the next multiple of 64
-    if (Meff > 0) stream_grid<8, EPI>(P, block, workgroups, Meff, Meff, Keff);
+    if (Meff > 0) stream_grid<8, EPI>(P, P.splits, block, workgroups, Meff, Meff, Keff);
 }
 template <int EPI>
 __global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_kernel(GemmArgs P) {
@@ -550,12 +550,11 @@ __global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_kernel(GemmArgs P) {
 // even), 368 rows 173 / 154 (C = 8192, I = 28672), 1100 rows 50 / 46 (2048, 8192); with the residual in the epilogue 2300 rows
 // 25 / 21, 4200 rows 43 / 34 (4096, 512).
 template <int EPI>
-__global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_rows_kernel(GemmArgs P) {
+__device__ __forceinline__ void stream_rows(const GemmArgs& P, const int splits, const int b, const int nb) {
     const int Meff = uniform(effective_rows(P.M, P.m_dev)), Keff = uniform(effective_rows(P.K, P.k_dev));
     if (Meff <= 0) return;
-    const int b = (int)blockIdx.x, nb = (int)gridDim.x;
-    const int columns = P.tiles_n * P.splits;                // tiles of a tile row
-    const int slabs = ((Keff + BK - 1) / BK + P.splits - 1) / P.splits;
+    const int columns = P.tiles_n * splits;                  // tiles of a tile row
+    const int slabs = ((Keff + BK - 1) / BK + splits - 1) / splits;
     StreamRows plan = stream_rows_plan(Meff, columns, slabs, nb, P.outT0 != nullptr, EPI == EPI_SWIGLU);
     plan = StreamRows{uniform(plan.full), uniform(plan.mi)};
     int base = 0, after = 0;                                 // rows and tiles of the first of two parts
@@ -564,27 +563,31 @@ __global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_rows_kernel(GemmArgs
             base = plan.full * 256 < Meff ? plan.full * 256 : Meff;
             after = plan.full * columns;
         }
-        stream_grid<8, EPI>(P, b, nb, EPI == EPI_SWIGLU ? base : Meff, Meff, Keff);
+        stream_grid<8, EPI>(P, splits, b, nb, EPI == EPI_SWIGLU ? base : Meff, Meff, Keff);
         if (EPI != EPI_SWIGLU || plan.mi == 0) return;
         lds_barrier();                                       // other stages, other parts of them
     }
     switch (plan.mi) {                                       // uniform
-        case 4: stream_grid<4, EPI>(P, b, nb, Meff, Meff, Keff, base, after); break;
-        case 5: stream_grid<5, EPI>(P, b, nb, Meff, Meff, Keff, base, after); break;
-        case 6: stream_grid<6, EPI>(P, b, nb, Meff, Meff, Keff, base, after); break;
-        default: stream_grid<7, EPI>(P, b, nb, Meff, Meff, Keff, base, after); break;
+        case 4: stream_grid<4, EPI>(P, splits, b, nb, Meff, Meff, Keff, base, after); break;
+        case 5: stream_grid<5, EPI>(P, splits, b, nb, Meff, Meff, Keff, base, after); break;
+        case 6: stream_grid<6, EPI>(P, splits, b, nb, Meff, Meff, Keff, base, after); break;
+        default: stream_grid<7, EPI>(P, splits, b, nb, Meff, Meff, Keff, base, after); break;
     }
 }
 
-// The balanced split-K of streamk.hpp into fp32 slabs.  grid = tiles_n * nbg workgroups (P.splits carries nbg)
-__global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_balanced_kernel(GemmArgs P) {
-    const int nbg = P.splits, tiles_n = (int)gridDim.x / nbg;
+template <int EPI>
+__global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_rows_kernel(GemmArgs P) {
+    stream_rows<EPI>(P, P.splits, (int)blockIdx.x, (int)gridDim.x);
+}
+
+// The balanced split-K of streamk.hpp into fp32 slabs: workgroup `block` of tiles_n * nbg
+__device__ __forceinline__ void stream_balanced(const GemmArgs& P, const int block, const int tiles_n, const int nbg) {
     const int Meff = uniform(effective_rows(P.M, P.m_dev)), Keff = uniform(effective_rows(P.K, P.k_dev));
     const int g = (Meff + BM - 1) / BM, kt = (Keff + BK - 1) / BK;
     if (g == 0 || kt == 0) return;
     const StreamKPlan p = streamk_plan(g, kt, nbg);
     int tn, j;
-    balanced_share(p, tiles_n, (int)blockIdx.x, tn, j);
+    balanced_share(p, tiles_n, block, tn, j);
     stream_gemm<8, EPI_PARTIAL>(P, BalancedWork(p, tn, j), Meff, Keff);
 }
 

@@ -594,6 +594,31 @@ def test_device_row_count_far_below_the_bound(R, T):
     assert np.array_equal(bits_of(out)[sk], p.hidden[sk])
 
 
+@pytest.mark.parametrize("R,T,C,I", [(0, 300, 520, 8200), (1, 300, 520, 8200), (64, 400, 520, 8200), (65, 700, 520, 8200),
+                                     (129, 700, 1032, 2056), (193, 3000, 1032, 2056), (256, 3000, 520, 8200), (257, 3000, 520, 8200),
+                                     (700, 3000, 1032, 2056), (5500, 6000, 520, 8200), (400, 4000, 2056, 1032),
+                                     (600, 4000, 2056, 1032), (16450, 16700, 264, 520)])
+def test_every_path_of_a_device_row_count(R, T, C, I):
+    """Inference with the count on the device and a bound for which the core runs: tiles of all rows of each height (the smallest
+    and largest count of some, no row at all), K cut evenly, balanced (5500 rows) and whole, row counts past the list of
+    plans.  Every row is checked on its own: xn, H and out are rounded to bf16, 2^-9 rms each."""
+    from helpers import max_slice_rel_l2
+    w = W.small(C=C, I=I, visual=(T - 1,), text=(1,), keep=(max(R - 1, 0),), seed=9000 + R)
+    print(f"device count R={R} bound T={T} C={C} I={I}", flush=True)
+    p = Problem(w, unit_gain=True, with_gain_tensor=False)
+    if R == 0:
+        p.mask[:] = 1
+        p.d_mask.fill_(1)
+    got = bits_of(gpu_forward(p, R_host=False, saved=False, flags=B.FLAG_NO_RESIDUAL)[0])
+    sk = p.mask != 0
+    assert np.array_equal(got[sk], p.hidden[sk])
+    if R > 0:
+        fo = O.skipffn_forward(p.hidden, p.mask, p.wg, p.wu, p.wd, None, w.eps, no_residual=True)
+        idx = fo["idx"]
+        assert len(idx) == R
+        assert max_slice_rel_l2(O.bf16_bits_to_f64(got[idx]), O.bf16_bits_to_f64(fo["out_bits"][idx]), axis=1) < REL_L2_TOL
+
+
 @pytest.mark.parametrize("R", [1, 15, 16, 17, 32, 33, 48, 49, 64])
 @pytest.mark.parametrize("C,I", [(136, 344), (512, 1368), (1032, 2056)], ids=["ragged-k", "whole-k", "batches-and-rest"])
 @pytest.mark.parametrize("r_host", [True, False], ids=["R-host", "R-device"])
