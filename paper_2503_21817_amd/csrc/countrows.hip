@@ -32,7 +32,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void gate_up_count_kernel(GemmArgs P,
     if (rows <= 256) {
         if (block < mid) mid_rows_of_count<true>(M, rows, block);
     } else if (block < lists) {
-        stream_rows<EPI_SWIGLU>(P, 1, block, lists);
+        stream_rows<EPI_SWIGLU>(P, stream_plan_of_count<EPI_SWIGLU>(P, 1, lists), 1, block, lists);
     }
 }
 __global__ __launch_bounds__(GEMM_THREADS) void down_count_kernel(GemmArgs P, MidRowsArgs M, RowPlans plans, int lists, int mid) {
@@ -46,8 +46,8 @@ __global__ __launch_bounds__(GEMM_THREADS) void down_count_kernel(GemmArgs P, Mi
     if (nbg > 0) {
         if (block < P.tiles_n * nbg) stream_balanced(P, block, P.tiles_n, nbg);
     } else if (block < lists) {
-        if (splits > 1) stream_rows<EPI_PARTIAL>(P, splits, block, lists);
-        else stream_rows<EPI_RESID_SCATTER>(P, 1, block, lists);
+        if (splits > 1) stream_rows<EPI_PARTIAL>(P, stream_plan_of_count<EPI_PARTIAL>(P, splits, lists), splits, block, lists);
+        else stream_rows<EPI_RESID_SCATTER>(P, stream_plan_of_count<EPI_RESID_SCATTER>(P, 1, lists), 1, block, lists);
     }
 }
 

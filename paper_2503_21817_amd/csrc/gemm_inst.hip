@@ -78,11 +78,25 @@ static unsigned grid_blocks(const GemmArgs& a) { return (unsigned)(a.tiles_m * a
 
 // One workgroup per CU, a multiple of the 8 XCDs; fewer where the tiles, counted at their smallest height, are fewer
 template <int EPI>
-static hipError_t launch_stream(void (*kernel)(GemmArgs), const GemmArgs& a, hipStream_t s) {
+static unsigned stream_workgroups(const GemmArgs& a) {
     const int height = EPI == EPI_STORE ? 256 : 128;
     const unsigned cus = (unsigned)(a.ncu >= 8 ? a.ncu / 8 * 8 : 8);
     const unsigned tiles = ((unsigned)((a.M + height - 1) / height * a.tiles_n * a.splits * a.batch) + 7) / 8 * 8;
-    hipLaunchKernelGGL(kernel, dim3(tiles < cus ? tiles : cus), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a);
+    return tiles < cus ? tiles : cus;
+}
+// Tiles by the row count, planned here where the host knows it: some twenty divisions, 2-3 us at the start of every workgroup.
+// Layer forward, us, planned on the device / here:  C = 1024, I = 3584: 1200 rows 53.8 / 51.1;  C = 2048, I = 7168: 640 rows 73.6 /
+// 70.7, 1472 rows 137.0 / 134.4;  C = 4096, I = 14336: 300 rows 132.8 / 129.9, 1472 rows 406.3 / 405.6.  (A kernel for each height
+// was no faster than that.)
+template <int EPI>
+static hipError_t launch_stream_rows(const GemmArgs& a, hipStream_t s) {
+    const unsigned workgroups = stream_workgroups<EPI>(a);
+    StreamRows plan{0, 0};
+    if (a.m_dev == nullptr && a.k_dev == nullptr) {
+        const int slabs = ((a.K + BK - 1) / BK + a.splits - 1) / a.splits;
+        plan = stream_rows_plan(a.M, a.tiles_n * a.splits, slabs, (int)workgroups, a.outT0 != nullptr, EPI == EPI_SWIGLU);
+    }
+    hipLaunchKernelGGL(stream_gemm_rows_kernel<EPI>, dim3(workgroups), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a, plan);
     return hipGetLastError();
 }
 
@@ -118,10 +132,13 @@ hipError_t launch_gemm(bool b_kc, int epi, GemmArgs& a, hipStream_t s) {
     if (b_kc && a.pairs != 1) return hipErrorInvalidValue;
     const int kt = std::max((a.K + BK - 1) / BK, 1);         // a part of K without slabs would end a list of tiles
     if (b_kc && (a.splits - 1) * ((kt + a.splits - 1) / a.splits) >= kt) return hipErrorInvalidValue;
-    if (b_kc && epi == EPI_SWIGLU) return launch_stream<EPI_SWIGLU>(&stream_gemm_rows_kernel<EPI_SWIGLU>, a, s);
-    if (b_kc && epi == EPI_PARTIAL) return launch_stream<EPI_PARTIAL>(&stream_gemm_rows_kernel<EPI_PARTIAL>, a, s);
-    if (b_kc && epi == EPI_RESID_SCATTER) return launch_stream<EPI_RESID_SCATTER>(&stream_gemm_rows_kernel<EPI_RESID_SCATTER>, a, s);
-    if (b_kc && epi == EPI_STORE) return launch_stream<EPI_STORE>(&stream_gemm_kernel<EPI_STORE>, a, s);
+    if (b_kc && epi == EPI_SWIGLU) return launch_stream_rows<EPI_SWIGLU>(a, s);
+    if (b_kc && epi == EPI_PARTIAL) return launch_stream_rows<EPI_PARTIAL>(a, s);
+    if (b_kc && epi == EPI_RESID_SCATTER) return launch_stream_rows<EPI_RESID_SCATTER>(a, s);
+    if (b_kc && epi == EPI_STORE) {
+        hipLaunchKernelGGL(stream_gemm_kernel<EPI_STORE>, dim3(stream_workgroups<EPI_STORE>(a)), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a);
+        return hipGetLastError();
+    }
     if (b_kc || epi != EPI_PARTIAL || a.batch != 1) return hipErrorInvalidValue;
     hipLaunchKernelGGL(gemm_bf16_kernel, dim3(grid_blocks(a)), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a);
     return hipGetLastError();

@@ -550,13 +550,10 @@ __global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_kernel(GemmArgs P) {
 // even), 368 rows 173 / 154 (C = 8192, I = 28672), 1100 rows 50 / 46 (2048, 8192); with the residual in the epilogue 2300 rows
 // 25 / 21, 4200 rows 43 / 34 (4096, 512).
 template <int EPI>
-__device__ __forceinline__ void stream_rows(const GemmArgs& P, const int splits, const int b, const int nb) {
+__device__ __forceinline__ void stream_rows(const GemmArgs& P, const StreamRows plan, const int splits, const int b, const int nb) {
     const int Meff = uniform(effective_rows(P.M, P.m_dev)), Keff = uniform(effective_rows(P.K, P.k_dev));
     if (Meff <= 0) return;
     const int columns = P.tiles_n * splits;                  // tiles of a tile row
-    const int slabs = ((Keff + BK - 1) / BK + splits - 1) / splits;
-    StreamRows plan = stream_rows_plan(Meff, columns, slabs, nb, P.outT0 != nullptr, EPI == EPI_SWIGLU);
-    plan = StreamRows{uniform(plan.full), uniform(plan.mi)};
     int base = 0, after = 0;                                 // rows and tiles of the first of two parts
     if (plan.full > 0) {
         if constexpr (EPI == EPI_SWIGLU) {
@@ -575,9 +572,19 @@ __device__ __forceinline__ void stream_rows(const GemmArgs& P, const int splits,
     }
 }
 
+// the plan of a row count on the device
 template <int EPI>
-__global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_rows_kernel(GemmArgs P) {
-    stream_rows<EPI>(P, P.splits, (int)blockIdx.x, (int)gridDim.x);
+__device__ __forceinline__ StreamRows stream_plan_of_count(const GemmArgs& P, const int splits, const int nb) {
+    const int Meff = uniform(effective_rows(P.M, P.m_dev)), Keff = uniform(effective_rows(P.K, P.k_dev));
+    const int slabs = ((Keff + BK - 1) / BK + splits - 1) / splits;
+    const StreamRows plan = stream_rows_plan(Meff, P.tiles_n * splits, slabs, nb, P.outT0 != nullptr, EPI == EPI_SWIGLU);
+    return StreamRows{uniform(plan.full), uniform(plan.mi)};
+}
+// plan: of a row count on the host; {0, 0}: the count is on the device
+template <int EPI>
+__global__ __launch_bounds__(GEMM_THREADS) void stream_gemm_rows_kernel(GemmArgs P, StreamRows plan) {
+    if (plan.full == 0 && plan.mi == 0) plan = stream_plan_of_count<EPI>(P, P.splits, (int)gridDim.x);
+    stream_rows<EPI>(P, plan, P.splits, (int)blockIdx.x, (int)gridDim.x);
 }
 
 // The balanced split-K of streamk.hpp into fp32 slabs: workgroup `block` of tiles_n * nbg
