@@ -76,9 +76,8 @@ __global__ __launch_bounds__(SEL_THREADS) void cls_sim_kernel(
 
 // ---- mask: one workgroup per sequence searches the cut (topk.hpp) ----------------------------------
 // Up to SEL_MAXV * 1024 tokens the keys stay in registers; a longer sequence reads its similarities
-// again in every step of the search (from L2).  Up to 256 tokens, four threads to each, counting the
-// tokens that beat it takes less than the search's 10-16 barriers: the whole call at 1 / 16 sequences
-// of 144 tokens 7.2 / 7.8 us (search 9.9 / 11.5), of 256 tokens 8.7 / 9.2 (10.6 / 12.7).
+// again for every cut of the search (from L2).  Up to 256 tokens, four threads to each, counting the tokens that beat it
+// takes less than the search's barriers.
 constexpr int SEL_MAXV = 16;
 constexpr int SEL_RANK_MAX = TOPK_THREADS / 4;
 

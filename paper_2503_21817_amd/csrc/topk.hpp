@@ -1,17 +1,14 @@
 // The k smallest of n keys by one workgroup, without a sort: a search for the cut.
 //
-// Keys are rank_key values (segments.hpp), the order is (key, index).  The cut is built from the
-// most significant bits down, two bits per step: the workgroup counts the keys below the three
-// candidate cuts (ballots of keys held in registers; nothing but 16 LDS adds and one barrier a
-// step) and keeps the largest candidate that has fewer than k keys below it.  A candidate with
-// exactly k keys below it ends the search: for values that differ that is after about 20 of the
-// 32 bits.  Only if entries equal to the cut have to be told apart by index (repeated values) a
-// prefix count over the workgroup follows.
+// Keys are rank_key values (segments.hpp), the order is (key, index).  The range of the keys is cut into 2048 equal parts, the
+// keys are counted per part in LDS, and a prefix sum finds the part in which the k-th lies; that part is cut again, three times at
+// most (32 bits in steps of 11), as a rule twice: a part of the second cut that ends at the k-th key ends the search.  Only if
+// entries equal to the cut have to be told apart by index (repeated values) a prefix count over the workgroup follows.
 //
-// Bound by latency: 10-16 steps of a ballot count, a barrier and an LDS read.  Measured, whole
-// kernels: 11.1 us at 4 sequences of 2880 tokens (a count of the entries that come before each
-// entry, which reads n keys per entry: 64 us); kept tokens and slots of 8 sets of 1024 7.9 us and of a
-// set of 2304 9.3 us (24 + 5 and 52 + 6 us).
+// Bound by latency: four barriers and an LDS round trip between each two for every cut.  Measured, whole
+// kernels, us: 7.0 at 4 sequences of 2880 tokens (two bits a step, counted with ballots, 10-16 steps of a barrier each: 11.6; a rank for every
+// entry by counting, 64 entries to a workgroup: 9.2); kept tokens and slots of 8 sets of 1024 5.5 (8.1) and of a set of 2304
+// 6.1 (10.2).
 #pragma once
 
 #include "common.hpp"
@@ -22,8 +19,12 @@ constexpr int TOPK_THREADS = 1024;
 constexpr int TOPK_WAVES = TOPK_THREADS / 64;
 constexpr uint32_t TOPK_NONE = 0xFFFFFFFFu;     // key of an absent entry: below no candidate
 
+constexpr int TOPK_BINS = 2048;
 struct TopkShared {
-    int below[3][4];                             // counts of three steps in rotation (one barrier a step)
+    int hist[2][TOPK_BINS];                      // of a cut, and cleared for the next one
+    uint32_t lo[TOPK_WAVES], hi[TOPK_WAVES];
+    int count[TOPK_WAVES];
+    int part, before, inside;                    // the part with the k-th key, keys before and in it
     int scan[16 * TOPK_WAVES];
     int total;
 };
@@ -34,41 +35,79 @@ struct TopkCut { uint32_t cut; int ties; };
 // loops over i are unrolled (keys in registers), MAXV == 0: any nv.  0 < k < n, uniform.
 template <int MAXV, class Key>
 __device__ __forceinline__ TopkCut topk_cut(Key&& key, int nv, int k, TopkShared& sh) {
-    const int tid = threadIdx.x, lane = tid & 63;
-    if (tid < 4) sh.below[0][tid] = 0;
-    __syncthreads();
-    uint32_t p = 0;
-    int less = 0;                                // keys below p
-    int cur = 0;
-    for (int shift = 30; shift >= 0; shift -= 2) {
-        const uint32_t c1 = p | (1u << shift), c2 = p | (2u << shift), c3 = p | (3u << shift);
-        int n1 = 0, n2 = 0, n3 = 0;
-        auto count = [&](uint32_t v) {
-            n1 += __popcll(__ballot(v < c1));
-            n2 += __popcll(__ballot(v < c2));
-            n3 += __popcll(__ballot(v < c3));
-        };
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    auto for_keys = [&](auto&& f) {
         if constexpr (MAXV > 0) {
 #pragma unroll
             for (int i = 0; i < MAXV; ++i)
-                if (i < nv) count(key(i));
+                if (i < nv) f(key(i));
         } else {
-            for (int i = 0; i < nv; ++i) count(key(i));
+            for (int i = 0; i < nv; ++i) f(key(i));
         }
-        const int nxt = cur == 2 ? 0 : cur + 1;
-        if (lane < 3) atomicAdd(&sh.below[cur][lane], lane == 0 ? n1 : (lane == 1 ? n2 : n3));
-        if (tid < 4) sh.below[nxt][tid] = 0;     // last read two steps ago
-        __syncthreads();
-        const int b1 = sh.below[cur][0], b2 = sh.below[cur][1], b3 = sh.below[cur][2];
-        cur = nxt;
-        if (b1 == k) return TopkCut{c1, 0};
-        if (b2 == k) return TopkCut{c2, 0};
-        if (b3 == k) return TopkCut{c3, 0};
-        if (b3 < k)      { p = c3; less = b3; }
-        else if (b2 < k) { p = c2; less = b2; }
-        else if (b1 < k) { p = c1; less = b1; }
+    };
+    constexpr int PER = TOPK_BINS / TOPK_THREADS;
+    static_assert(PER == 2, "two bins a thread");
+    // the range of the keys that are numbers, and how many they are
+    uint32_t lo = TOPK_NONE, hi = 0;
+    int m = 0;
+    for_keys([&](uint32_t v) {
+        if (v != TOPK_NONE) {
+            lo = v < lo ? v : lo;
+            hi = v > hi ? v : hi;
+            ++m;
+        }
+    });
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const uint32_t l = __shfl_xor(lo, off), h = __shfl_xor(hi, off);
+        lo = l < lo ? l : lo;
+        hi = h > hi ? h : hi;
+        m += __shfl_xor(m, off);
     }
-    return TopkCut{p, k - less};
+    if (lane == 0) { sh.lo[wave] = lo; sh.hi[wave] = hi; sh.count[wave] = m; }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) sh.hist[0][tid + q * TOPK_THREADS] = 0;
+    __syncthreads();
+    m = 0;
+#pragma unroll
+    for (int w = 0; w < TOPK_WAVES; ++w) {
+        lo = sh.lo[w] < lo ? sh.lo[w] : lo;
+        hi = sh.hi[w] > hi ? sh.hi[w] : hi;
+        m += sh.count[w];
+    }
+    if (m <= k) return TopkCut{TOPK_NONE, k - m};        // all numbers, and the first of the others
+    for (int cur = 0;; cur ^= 1) {
+        // lo <= hi, and the k-th key is the k-th smallest of those in [lo, hi], of which there are more than k
+        const int width = 32 - __builtin_clz((hi - lo) | 1u), shift = width > 11 ? width - 11 : 0;
+        for_keys([&](uint32_t v) {
+            if (v >= lo && v <= hi) atomicAdd(&sh.hist[cur][(v - lo) >> shift], 1);
+        });
+        __syncthreads();
+        const int h0 = sh.hist[cur][2 * tid], h1 = sh.hist[cur][2 * tid + 1];
+        const int incl = wave_inclusive_sum(h0 + h1);
+        if (lane == 63) sh.count[wave] = incl;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) sh.hist[cur ^ 1][tid + q * TOPK_THREADS] = 0;
+        __syncthreads();
+        int before = incl - h0 - h1;
+#pragma unroll
+        for (int w = 0; w < TOPK_WAVES - 1; ++w) before += w < wave ? sh.count[w] : 0;
+        if (before < k && k <= before + h0 + h1) {       // one thread
+            const bool second = k > before + h0;
+            sh.part = 2 * tid + (second ? 1 : 0);
+            sh.before = second ? before + h0 : before;
+            sh.inside = second ? h1 : h0;
+        }
+        __syncthreads();
+        const uint32_t from = lo + ((uint32_t)sh.part << shift);
+        const int b = sh.before, in = sh.inside;
+        if (k == b + in) return TopkCut{from + (1u << shift), 0};       // at most hi + 2^shift: see below
+        if (shift == 0) return TopkCut{from, k - b};
+        k -= b;
+        const uint32_t to = from + ((1u << shift) - 1);
+        lo = from;
+        hi = to < hi ? to : hi;
+    }
 }
 
 // before[i] = number of entries flagged by flag(i) that precede entry i * TOPK_THREADS + threadIdx.x;

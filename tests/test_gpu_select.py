@@ -133,3 +133,17 @@ def test_cut_search_edges(lens, distinct):
     for share in (0.0, 0.25, 0.5, 1.0):
         keep = [min(m, int(m * share) + (1 if 0 < share < 1 else 0)) for m in lens]
         check(feat, cls, off, keep)
+
+
+@pytest.mark.parametrize("n", [300, 2049, 17000], ids=["registers", "three-a-thread", "from-memory"])
+def test_cut_among_similarities_that_lie_close(n):
+    """Most similarities within a few units in the last place of each other and some far away: the part of the range that
+    holds the cut keeps nearly all of them, and has to be cut down to single values, of which several are equal."""
+    rng = np.random.default_rng(n)
+    c = np.ones((1, 16))
+    rows = np.tile(c, (n, 1)) + rng.integers(0, 2, (n, 16)) / 128.0
+    rows[5], rows[7], rows[11, :8] = -c[0], 0.0, -1.0          # -1, 0 and near 0
+    feat, cls = O.f64_to_bf16_bits(rows), O.f64_to_bf16_bits(c)
+    off = np.array([0, n], dtype=np.int32)
+    for keep in (1, n // 3, n // 2, n - 4, n - 3, n - 2, n - 1):
+        check(feat, cls, off, keep)
