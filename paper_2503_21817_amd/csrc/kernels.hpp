@@ -109,15 +109,14 @@ hipError_t launch_select_retained(const bf16_t* feat, const bf16_t* cls, const i
                                   uint8_t* skip_mask, int64_t T, hipStream_t s);
 
 // ---- token merge -----------------------------------------------------------------------------------
-constexpr int MERGE_MAX_N = 4096;   // tokens per set (the similarity matrix is n x n fp32)
-hipError_t launch_row_normalize(const bf16_t* x, int64_t rows, int C, bf16_t* xn, hipStream_t s);
-hipError_t merge_init();         // raises the dynamic-LDS limit of the similarity kernel (once per process)
-hipError_t launch_selfsim(const bf16_t* xn, int C, const SegTable& st, int n_max, float* sim, int ld,
-                          int64_t sim_stride, hipStream_t s);
-hipError_t launch_merge_group(const bf16_t* x, const SegTable& st, int n_max, int C, int k, int set_base,
-                              const float* sim, int ld, int64_t sim_stride, float* avg,
-                              int32_t* slot_of, int32_t* kept_idx, int32_t* assign, bf16_t* out,
-                              hipStream_t s);
+constexpr int MERGE_MAX_N = 4096;   // tokens per set
+constexpr int MERGE_CHUNK = 8;      // rows of a partial sum of normalised rows
+hipError_t merge_init();         // raises the dynamic-LDS limits (once per process)
+// normalised rows [n_tok][C]; partial sums [n_tok / MERGE_CHUNK + sets + 1][C] and sums [sets][C] of the sets of a group; per token
+// 8 bytes and 4 bytes
+struct MergeScratch { bf16_t* xn; float* part; float* sum; void* goal; int32_t* dropped; };
+hipError_t launch_merge_group(const bf16_t* x, const SegTable& st, int n_max, int C, int k, int set_base, const MergeScratch& ws,
+                              float* avg, int32_t* kept_idx, int32_t* assign, bf16_t* out, hipStream_t s);
 hipError_t launch_merge_bwd_group(const bf16_t* dout, const SegTable& st, int n_max, int C, int k, int set_base,
                                   const int32_t* assign, bf16_t* dx, hipStream_t s);
 

@@ -2,15 +2,19 @@
 //   1. cosine similarity between every pair of tokens of a set, averaged per token;
 //   2. the k tokens of lowest average similarity are kept;
 //   3. every other token is merged into the kept token it is most similar to (plain mean).
-// The similarity matrices are dense contractions and run on the matrix cores (normalised rows
-// times their transpose, fp32 out, all sets of a group in one grid); everything else is
-// small and memory-bound and also runs for a whole group of sets per launch (blockIdx.y = set;
-// the sets' row offsets travel in the kernel arguments, so nothing is copied to the device).
+// The averages need no pair: with s the sum of a set's normalised rows, the sum of token i's similarities to the others is
+// xn_i . (s - xn_i).  Only similarities of dropped tokens to kept ones are formed, on the matrix cores, and of those only each
+// row's largest leaves the kernel.  (All similarities of a set, averaged and searched from memory: 43 of 78 us at 8 sets of
+// 1024, k = 256.)  Every kernel runs for a whole group of sets per launch; the sets' row offsets travel in the kernel
+// arguments, so nothing is copied to the device.
 // Decisions that depend on floating point (which tokens are kept, where a token goes) are
 // taken on the float32 averages / similarities computed here, with ties to the lower index,
 // so they are unique for those values.  A token with a non-finite feature has NaN similarities:
 // its average ranks after every number, so exactly min(k, n) tokens are kept whatever the input;
 // a token whose similarities are all NaN goes to no slot (assign = -1) and gets a zero gradient.
+#include <algorithm>
+
+#include "colsum.hpp"
 #include "kernels.hpp"
 #include "segments.hpp"
 #include "slabloop.hpp"
@@ -20,136 +24,158 @@ namespace skipffn {
 
 constexpr int MG_THREADS = 256;
 
-// ---- Xn = X / |X| (a zero row stays zero), one workgroup per row ------------------------------
-__global__ __launch_bounds__(MG_THREADS) void row_normalize_kernel(const bf16_t* __restrict__ x, int C,
-                                                                   bf16_t* __restrict__ xn) {
-    __shared__ float red[4];
-    const int64_t r = blockIdx.x;
-    const int tid = threadIdx.x, chunks = C >> 3;
-    const u32x4* src = reinterpret_cast<const u32x4*>(x + r * C);
-    u32x4* dst = reinterpret_cast<u32x4*>(xn + r * C);
-    float ss = 0.0f;
-    for (int c = tid; c < chunks; c += MG_THREADS) {
-        float f[8];
-        unpack8s(src[c], f);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) ss += f[j] * f[j];
-    }
-    ss = block_sum256(ss, red);
-    const float inv = ss > 0.0f ? 1.0f / sqrtf(ss) : 0.0f;
-    for (int c = tid; c < chunks; c += MG_THREADS) {
-        float f[8];
-        unpack8s(src[c], f);
-        u32x4 pk;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) pk[j] = pack_bf16x2(f[2 * j] * inv, f[2 * j + 1] * inv);
-        dst[c] = pk;
-    }
+// In the kernels below: set = blockIdx.y, rows [lo, lo + n) of the token list.
+
+// ---- Xn = X / |X| (a zero row stays zero), and the sum of the MERGE_CHUNK rows of a workgroup of Xn ----
+// Bound by latency and HBM: a wavefront holds its two rows in registers, V chunks of each a lane, all loads in flight at once; its
+// sum of them meets those of the other three in LDS.  V = 0: rows of more than 4096 columns, read again for the second step.
+// 9.3 us at 8192 rows of 1024 columns, 11.5 at 2304 of 4096 (16 rows a workgroup, read twice: 14.2 and 20.4).
+__device__ __forceinline__ int64_t merge_part_row(const SegTable& st, int set, int chunk) {
+    return (st.off[set] - st.off[0]) / MERGE_CHUNK + set + chunk;           // the sets' rows of `part` do not overlap
 }
-
-// In the kernels below: set = blockIdx.y, rows [lo, lo + n) of the token list; S_set is its
-// similarity matrix [n][ld] inside the group's buffer (stride sim_stride floats per set).
-
-// ---- S_set = Xn Xn^T, fp32 ----------------------------------------------------------------------
-// S is symmetric: only the 128 x 128 tiles on and above the diagonal are computed, the others are their mirror
-// images (products commute and K is summed in one order, so the values are those of the full product).  Bound by
-// the loop's phases and, for one set, by how many CUs have a tile: 36 tiles per set of 1024, 171 of 2304.  On 256 x 256
-// tiles of the whole square (16 and 81): 82 us at one set of 2304 x 4096, here 37; 8 sets of 1024 x 1024 33 and
-// 27 us.
-__global__ __launch_bounds__(SLAB_THREADS) void selfsim_kernel(const bf16_t* __restrict__ xn, SegTable st, int pairs, int C,
-                                                               int ld, int64_t sim_stride, float* __restrict__ sim) {
-    constexpr int TILE = 128, NL = kSlabPieces<TILE>;
-    static_assert(TILE == SLAB_B_ROWS && kSlabPiecesA<TILE> == 2, "square tiles");
-    // workgroups are dealt round-robin to the 8 XCDs: each gets a contiguous range of the tiles, so that few sets (or
-    // few rows of a set) share its L2
-    const int nb = (int)gridDim.x, xcd = (int)blockIdx.x & 7, q8 = nb >> 3, rem8 = nb & 7;
-    const int b = xcd * q8 + (xcd < rem8 ? xcd : rem8) + ((int)blockIdx.x >> 3);
-    const int set = b / pairs;
-    const int lo = st.off[set], n = st.off[set + 1] - lo;
-    // pair p = tn (tn + 1) / 2 + tm, tm <= tn
-    const int p = b - set * pairs;
-    int tn = (int)((sqrtf(8.0f * (float)p + 1.0f) - 1.0f) * 0.5f);
-    while (tn * (tn + 1) / 2 > p) --tn;
-    while ((tn + 1) * (tn + 2) / 2 <= p) ++tn;
-    const int tm = p - tn * (tn + 1) / 2;
-    if (tn * TILE >= n) return;                          // whole workgroup leaves together
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const __amdgpu_buffer_rsrc_t rx = make_rsrc(xn + (int64_t)lo * C, (uint32_t)((int64_t)n * C * 2));
-    uint32_t goff[NL];
+static_assert(MERGE_CHUNK == MG_THREADS / 64 * 2, "two rows a wavefront");
+template <int V>
+__global__ __launch_bounds__(MG_THREADS) void merge_normalize_kernel(const bf16_t* __restrict__ x, SegTable st, int C,
+                                                                     bf16_t* __restrict__ xn, float* __restrict__ part) {
+    extern __shared__ __align__(16) float sums[];        // [4][C]
+    const int set = blockIdx.y, n = st.off[set + 1] - st.off[set];
+    if ((int)blockIdx.x * MERGE_CHUNK >= n) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, chunks = C >> 3;
+    const int r = (int)blockIdx.x * MERGE_CHUNK + wave * 2;
+    const bool has[2] = {r < n, r + 1 < n};              // uniform over a wavefront
+    const int64_t row0 = st.off[set] + (has[0] ? r : 0), row1 = has[1] ? row0 + 1 : row0;
+    const u32x4* src[2] = {reinterpret_cast<const u32x4*>(x + row0 * C), reinterpret_cast<const u32x4*>(x + row1 * C)};
+    u32x4* dst[2] = {reinterpret_cast<u32x4*>(xn + row0 * C), reinterpret_cast<u32x4*>(xn + row1 * C)};
+    constexpr int HELD = V > 0 ? V : 1;
+    u32x4 held[2][HELD];
+    float ss[2] = {0.0f, 0.0f};
+    auto add = [](const u32x4& raw, float& s) {
+        float f[8];
+        unpack8s(raw, f);
 #pragma unroll
-    for (int l = 0; l < NL; ++l) {
-        const int row = 8 * (wave * 2 + (l & 1)) + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
-        const int gr = (l < 2 ? tm : tn) * TILE + row;
-        goff[l] = gr < n ? (uint32_t)(((int64_t)gr * C + c * 8) * 2) : kOobOffset;
-    }
-    f32x4 acc[TILE / 32][2];
-    float ss[TILE / 32];
-    slab_loop<TILE, 16>(rx, rx, goff, (wave & 3) * 32, 0, (C + BK - 1) / BK, 0, C, acc, ss);
-    float* S = sim + set * sim_stride;
+        for (int j = 0; j < 8; ++j) s += f[j] * f[j];
+    };
+    if constexpr (V > 0) {
 #pragma unroll
-    for (int m = 0; m < TILE / 32; ++m)
-#pragma unroll
-        for (int f = 0; f < 2; ++f) {
-            const int i = tm * TILE + (wave >> 2) * 64 + m * 16 + (lane & 15);
-            const int j = tn * TILE + (wave & 3) * 32 + f * 16 + 4 * (lane >> 4);
-            if (i >= n || j >= n) continue;
-            // ld is a multiple of 8 >= n: a quad that begins inside the row ends inside it
-            *reinterpret_cast<f32x4*>(S + (int64_t)i * ld + j) = acc[m][f];
-            if (tm != tn) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (j + r < n) S[(int64_t)(j + r) * ld + i] = acc[m][f][r];
-            }
+        for (int v = 0; v < V; ++v) {
+            const int c = lane + 64 * v < chunks ? lane + 64 * v : 0;
+            held[0][v] = src[0][c];
+            held[1][v] = src[1][c];
         }
-}
-
-hipError_t merge_init() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&selfsim_kernel),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, kSlabLds<128>);
-}
-
-hipError_t launch_selfsim(const bf16_t* xn, int C, const SegTable& st, int n_max, float* sim, int ld,
-                          int64_t sim_stride, hipStream_t s) {
-    if (st.count <= 0 || n_max <= 0) return hipSuccess;
-    const int t = (n_max + 127) / 128, pairs = t * (t + 1) / 2;
-    hipLaunchKernelGGL(selfsim_kernel, dim3((unsigned)(pairs * st.count)), dim3(SLAB_THREADS), kSlabLds<128>, s,
-                       xn, st, pairs, C, ld, sim_stride, sim);
-    return hipGetLastError();
-}
-
-// ---- avg_i = (sum_j S_ij - S_ii) / (n - 1), one wavefront per row ------------------------------
-// Bound by reading S (from L2 and the memory-side cache); 16 bytes per lane and load.  Rows of S start on 32 bytes.
-__global__ __launch_bounds__(MG_THREADS) void sim_rowmean_kernel(const float* __restrict__ sim, SegTable st,
-                                                                 int ld, int64_t sim_stride,
-                                                                 float* __restrict__ avg) {
-    const int set = blockIdx.y;
-    const int lo = st.off[set], n = st.off[set + 1] - lo;
-    const int lane = threadIdx.x & 63;
-    const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (i >= n) return;
-    const float* row = sim + set * sim_stride + (int64_t)i * ld;
-    float acc = 0.0f;
-    int j = lane * 4;
-    for (; j + 3 < n; j += 256) {
-        const f32x4 v = *reinterpret_cast<const f32x4*>(row + j);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc += j + e == i ? 0.0f : v[e];
+        for (int v = 0; v < V; ++v)
+            if (lane + 64 * v < chunks) {
+                add(held[0][v], ss[0]);
+                add(held[1][v], ss[1]);
+            }
+    } else {
+        for (int c = lane; c < chunks; c += 64) {
+            add(src[0][c], ss[0]);
+            add(src[1][c], ss[1]);
+        }
     }
-    for (int e = j; e < n && e < j + 4; ++e) acc += e == i ? 0.0f : row[e];      // the lane of a ragged end
-    acc = wave_sum(acc);
-    if (lane == 0) avg[lo + i] = n > 1 ? acc / (float)(n - 1) : 0.0f;
+    float inv[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const float v = wave_sum(ss[q]);
+        inv[q] = v > 0.0f ? 1.0f / sqrtf(v) : 0.0f;
+    }
+    auto emit = [&](int c, const u32x4& a, const u32x4& b) {
+        float sum[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sum[j] = 0.0f;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            if (!has[q]) continue;                       // uniform
+            float f[8];
+            unpack8s(q == 0 ? a : b, f);
+            u32x4 pk;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) pk[j] = pack_bf16x2(f[2 * j] * inv[q], f[2 * j + 1] * inv[q]);
+            dst[q][c] = pk;
+            unpack8s(pk, f);                             // the sum of what the similarities are formed of
+#pragma unroll
+            for (int j = 0; j < 8; ++j) sum[j] += f[j];
+        }
+        f32x4* to = reinterpret_cast<f32x4*>(sums + (int64_t)wave * C + c * 8);
+        to[0] = f32x4{sum[0], sum[1], sum[2], sum[3]};
+        to[1] = f32x4{sum[4], sum[5], sum[6], sum[7]};
+    };
+    if constexpr (V > 0) {
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+            if (lane + 64 * v < chunks) emit(lane + 64 * v, held[0][v], held[1][v]);
+    } else {
+        for (int c = lane; c < chunks; c += 64) emit(c, src[0][c], src[1][c]);
+    }
+    __syncthreads();
+    f32x4* out = reinterpret_cast<f32x4*>(part + merge_part_row(st, set, (int)blockIdx.x) * C);
+    const f32x4* in = reinterpret_cast<const f32x4*>(sums);
+    const int quads = C >> 2;
+    for (int c = tid; c < quads; c += MG_THREADS) out[c] = (in[c] + in[c + quads]) + (in[c + 2 * quads] + in[c + 3 * quads]);
+}
+
+// ---- s_set = the sum of the set's partial rows ------------------------------------------------------
+template <int LANES>
+__global__ __launch_bounds__(32 * LANES) void merge_sum_kernel(const float* __restrict__ part, SegTable st, int C, float* __restrict__ s) {
+    const int set = blockIdx.y, n = st.off[set + 1] - st.off[set];
+    if (n <= 0) return;
+    column_sum<LANES>(part + merge_part_row(st, set, 0) * C, (n + MERGE_CHUNK - 1) / MERGE_CHUNK, C, s + (int64_t)set * C, 0);
+}
+
+// ---- avg_i = xn_i . (s - xn_i) / (n - 1), two rows per wavefront ------------------------------------
+__global__ __launch_bounds__(MG_THREADS) void merge_average_kernel(const bf16_t* __restrict__ xn, SegTable st, int C,
+                                                                   const float* __restrict__ s, float* __restrict__ avg) {
+    const int set = blockIdx.y, lo = st.off[set], n = st.off[set + 1] - lo;
+    const int lane = threadIdx.x & 63, i = (int)blockIdx.x * 8 + (threadIdx.x >> 6) * 2;
+    if (i >= n) return;
+    const int chunks = C >> 3;
+    const u32x4* p0 = reinterpret_cast<const u32x4*>(xn + (int64_t)(lo + i) * C);
+    const u32x4* p1 = i + 1 < n ? p0 + chunks : p0;
+    const f32x4* ps = reinterpret_cast<const f32x4*>(s + (int64_t)set * C);
+    float d0 = 0.0f, d1 = 0.0f;
+    auto add = [&](const u32x4& a, const u32x4& b, const f32x4& lo4, const f32x4& hi4) {
+        float x0[8], x1[8];
+        unpack8s(a, x0);
+        unpack8s(b, x1);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const float t = j < 4 ? lo4[j & 3] : hi4[j & 3];
+            d0 += x0[j] * (t - x0[j]);
+            d1 += x1[j] * (t - x1[j]);
+        }
+    };
+    int c = lane;
+    for (; c + 64 < chunks; c += 128) {
+        const u32x4 a0 = p0[c], a1 = p0[c + 64], b0 = p1[c], b1 = p1[c + 64];
+        const f32x4 l0 = ps[2 * c], h0 = ps[2 * c + 1], l1 = ps[2 * c + 128], h1 = ps[2 * c + 129];
+        add(a0, b0, l0, h0);
+        add(a1, b1, l1, h1);
+    }
+    if (c < chunks) add(p0[c], p1[c], ps[2 * c], ps[2 * c + 1]);
+    d0 = wave_sum(d0);
+    d1 = wave_sum(d1);
+    if (lane == 0) {
+        avg[lo + i] = n > 1 ? d0 / (float)(n - 1) : 0.0f;
+        if (i + 1 < n) avg[lo + i + 1] = d1 / (float)(n - 1);
+    }
 }
 
 // ---- which tokens are kept, and their slots ------------------------------------------------------
 // One workgroup per set: the k tokens of lowest average (topk.hpp), then the position of every kept
-// token among the kept ones, in index order.  slot_of[t] = slot or -1; kept_idx[set][slot] = lo + t, -1
-// padding.
+// token among the kept ones, in index order, and of every other among the others.  kept_idx[set][slot] = lo + t, -1
+// padding; dropped[lo + position] = t.  goal[lo + t] = where token t goes: a key that grows with the similarity and, for equal
+// ones, falls with the slot; a kept token's own slot, before every similarity, 0 for the others (no slot yet).
+typedef unsigned long long goal_t;
+__device__ __forceinline__ goal_t merge_goal(uint32_t key, int slot) { return (goal_t)key << 32 | (uint32_t)~slot; }
+__device__ __forceinline__ int slot_of_goal(uint32_t lower) { return (int)~lower; }      // of goal 0: -1
+constexpr uint32_t GOAL_KEPT = 0xFFFFFFFFu;   // rank_key of no number
+
 constexpr int MG_MAXV = MERGE_MAX_N / TOPK_THREADS;
 __global__ __launch_bounds__(TOPK_THREADS) void merge_select_kernel(const float* __restrict__ avg, SegTable st,
-                                                                    int k, int set_base,
-                                                                    int32_t* __restrict__ slot_of,
-                                                                    int32_t* __restrict__ kept_idx) {
+                                                                    int k, int set_base, goal_t* __restrict__ goal,
+                                                                    int32_t* __restrict__ dropped, int32_t* __restrict__ kept_idx,
+                                                                    int32_t* __restrict__ assign) {
     __shared__ TopkShared sh;
     const int set = blockIdx.x, tid = threadIdx.x;
     const int lo = st.off[set], n = st.off[set + 1] - lo;
@@ -181,138 +207,187 @@ __global__ __launch_bounds__(TOPK_THREADS) void merge_select_kernel(const float*
         const int t = i * TOPK_THREADS + tid;
         if (t >= n) continue;
         // exactly min(k, n) tokens are in, so a slot is below k
-        slot_of[lo + t] = in[i] ? before[i] : -1;
+        goal[lo + t] = in[i] ? merge_goal(GOAL_KEPT, before[i]) : 0;
         if (in[i]) kout[before[i]] = lo + t;
+        else dropped[lo + t - before[i]] = t;
+        if (k <= 0) assign[lo + t] = -1;         // no slot to go to
     }
 }
 
-// ---- destination of every token: own slot if kept, else the most similar kept token ----------
-__global__ __launch_bounds__(MG_THREADS) void merge_assign_kernel(const float* __restrict__ sim, SegTable st,
-                                                                  int ld, int64_t sim_stride,
-                                                                  const int32_t* __restrict__ slot_of,
-                                                                  int32_t* __restrict__ assign) {
-    const int set = blockIdx.y;
-    const int lo = st.off[set], n = st.off[set + 1] - lo;
+// ---- the kept token that every dropped one is most similar to -------------------------------------
+// Xn Xn^T of dropped rows and kept rows, gathered by their lists as they are loaded; a tile keeps the largest entry of each of its
+// rows (ties: the lower slot) and adds it to the token's goal by an atomic maximum, whose order does not matter.  Bound by
+// the loop's phases and by how many CUs have a tile; the launcher picks the tile.  8 sets of 1024 x 1024, k = 256: 12.0 us, a
+// set of 2304 x 4096, k = 576: 22.2, 6 of 2880 x 1024, k = 1200: 49.7; all similarities on and above the diagonal, 128 x 128, and the search for the
+// largest one in memory: 25.1 + 11.1, 34.5 + 10.1, 95 + 44.
+template <int A_ROWS, int B_ROWS>
+__global__ __launch_bounds__(SLAB_THREADS) void merge_target_kernel(const bf16_t* __restrict__ xn, SegTable st, int C, int k, int set_base,
+                                                                    int tiles_m, int tiles_n, const int32_t* __restrict__ dropped,
+                                                                    const int32_t* __restrict__ kept_idx, goal_t* __restrict__ goal) {
+    constexpr int MI = A_ROWS / 32, NF = B_ROWS / 64;
+    constexpr int NLA = kSlabPiecesA<A_ROWS>, NL = kSlabPieces<A_ROWS, B_ROWS>;
+    // workgroups are dealt round-robin to the 8 XCDs: each gets a contiguous range of the tiles, so that few sets (or
+    // few rows of a set) share its L2
+    const int nb = (int)gridDim.x, xcd = (int)blockIdx.x & 7, q8 = nb >> 3, rem8 = nb & 7;
+    const int b = xcd * q8 + (xcd < rem8 ? xcd : rem8) + ((int)blockIdx.x >> 3);
+    const int set = b / (tiles_m * tiles_n), t = b - set * tiles_m * tiles_n, tm = t / tiles_n, tn = t - tm * tiles_n;
+    const int lo = st.off[set], n = st.off[set + 1] - lo, kk = k < n ? k : n, nd = n - kk;
+    if (tm * A_ROWS >= nd || tn * B_ROWS >= kk) return;  // whole workgroup leaves together
+    const int32_t* rows_a = dropped + lo;                // relative to the set
+    const int32_t* rows_b = kept_idx + (int64_t)(set_base + set) * k;        // absolute
     const int lane = threadIdx.x & 63;
-    const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (i >= n) return;
-    const int own = slot_of[lo + i];
-    if (own >= 0) {
-        if (lane == 0) assign[lo + i] = own;
-        return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const __amdgpu_buffer_rsrc_t rx = make_rsrc(xn + (int64_t)lo * C, (uint32_t)((int64_t)n * C * 2));
+    uint32_t goff[NL];
+#pragma unroll
+    for (int l = 0; l < NL; ++l) {
+        const int row = 8 * (l < NLA ? wave * NLA + l : wave * NF + (l - NLA)) + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
+        const int i = (l < NLA ? tm * A_ROWS : tn * B_ROWS) + row;
+        const bool in = i < (l < NLA ? nd : kk);
+        const int gr = !in ? 0 : l < NLA ? rows_a[i] : rows_b[i] - lo;
+        goff[l] = in ? (uint32_t)(((int64_t)gr * C + c * 8) * 2) : kOobOffset;
     }
-    const float* row = sim + set * sim_stride + (int64_t)i * ld;
-    float best = -3.0e38f;
-    int bj = 0x7fffffff;
-    // four entries of S and four slots per lane and step, two steps' loads in flight; j ascending per lane, so a tie
-    // keeps the lower index
-    for (int j0 = lane * 4; j0 < n; j0 += 512) {
-        float v[2][4];
-        int sl[2][4];
+    extern __shared__ __align__(16) char smem[];
+    goal_t (*best)[A_ROWS] = reinterpret_cast<goal_t (*)[A_ROWS]>(smem);     // [4][A_ROWS], once the slabs have been read
+    const int wm = wave >> 2, wn = wave & 3;
+    f32x4 acc[MI][NF];
+    float ss[MI];
+    slab_loop<A_ROWS, 16, false, B_ROWS>(rx, rx, goff, wn * 16 * NF, 0, (C + BK - 1) / BK, 0, C, acc, ss);
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int j = j0 + h * 256;
-            if (j + 3 < n) {
-                const f32x4 q = *reinterpret_cast<const f32x4*>(row + j);
+    for (int m = 0; m < MI; ++m) {
+        goal_t g = 0;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[h][e] = q[e];
+        for (int f = 0; f < NF; ++f)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int j = tn * B_ROWS + wn * 16 * NF + f * 16 + 4 * (lane >> 4) + r;
+                const float v = acc[m][f][r];
+                if (j < kk && v == v) {
+                    const goal_t o = merge_goal(rank_key<false>(v), j);
+                    g = o > g ? o : g;
+                }
             }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                sl[h][e] = j + e < n ? slot_of[lo + j + e] : -1;
-                if (j + 3 >= n) v[h][e] = j + e < n ? row[j + e] : 0.0f;
-            }
+        for (int off = 16; off < 64; off <<= 1) {
+            const goal_t o = __shfl_xor(g, off, 64);
+            g = o > g ? o : g;
         }
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (sl[h][e] >= 0 && v[h][e] > best) { best = v[h][e]; bj = j0 + h * 256 + e; }
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const float ov = __shfl_xor(best, off, 64);
-        const int oj = __shfl_xor(bj, off, 64);
-        if (ov > best || (ov == best && oj < bj)) { best = ov; bj = oj; }
-    }
-    if (lane == 0) assign[lo + i] = bj != 0x7fffffff ? slot_of[lo + bj] : -1;
-}
-
-// ---- out[set][slot] = mean of the rows assigned to the slot, added in index order --------------
-__global__ __launch_bounds__(MG_THREADS) void merge_mean_kernel(const bf16_t* __restrict__ x, SegTable st, int C,
-                                                                int k, int set_base,
-                                                                const int32_t* __restrict__ assign,
-                                                                bf16_t* __restrict__ out) {
-    constexpr int WAVES = MG_THREADS / 64, SHARE = MERGE_MAX_N / WAVES;
-    __shared__ int members[WAVES][SHARE];
-    __shared__ int nmem[WAVES];
-    const int set = blockIdx.y, slot = blockIdx.x;
-    const int lo = st.off[set], n = st.off[set + 1] - lo;
-    const int kk = k < n ? k : n;
-    const int tid = threadIdx.x, chunks = C >> 3;
-    u32x4* dst = reinterpret_cast<u32x4*>(out + ((int64_t)(set_base + set) * k + slot) * C);
-    // a workgroup takes MG_THREADS chunks of the row: the largest slot of a set ends the kernel, and its row is split
-    const int c = (int)blockIdx.z * MG_THREADS + tid;
-    if (slot >= kk) {                       // fewer tokens than slots: zero rows
-        if (c < chunks) dst[c] = u32x4{0u, 0u, 0u, 0u};
-        return;
-    }
-    // the slot's members, in index order: every wavefront compacts a quarter of the set with ballots, eight loads in
-    // flight (one wavefront over the whole set, a load at a time: 13 of this kernel's 33 us at 2304 tokens)
-    {
-        const int lane = tid & 63, wave = tid >> 6;
-        const int share = ((n + WAVES - 1) / WAVES + 63) / 64 * 64;          // <= SHARE
-        const int i1 = (wave + 1) * share < n ? (wave + 1) * share : n;
-        int count = 0;
-        for (int base = wave * share; base < i1; base += 512) {
-            int a[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int i = base + q * 64 + lane;
-                a[q] = i < i1 ? assign[lo + i] : -1;
-            }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const uint64_t m = __ballot(a[q] == slot);
-                if (a[q] == slot) members[wave][count + lanes_below(m)] = base + q * 64 + lane;
-                count += __popcll(m);
-            }
-        }
-        if (lane == 0) nmem[wave] = count;
+        if (lane < 16) best[wn][wm * (A_ROWS / 2) + m * 16 + lane] = g;
     }
     __syncthreads();
-    int m = 0;
+    const int i = tm * A_ROWS + (int)threadIdx.x;
+    if ((int)threadIdx.x < A_ROWS && i < nd) {
+        goal_t g = best[0][threadIdx.x];
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) m += nmem[w];
-    const float inv = 1.0f / (float)(m > 0 ? m : 1);
-    if (c < chunks) {
-        float acc[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] = 0.0f;
-        auto add = [&](const u32x4& raw) {
-            float f[8];
-            unpack8s(raw, f);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) acc[j] += f[j];
-        };
-        for (int w = 0; w < WAVES; ++w) {
-            const int cnt = nmem[w];
-            auto row = [&](int q) { return *reinterpret_cast<const u32x4*>(x + (int64_t)(lo + members[w][q]) * C + c * 8); };
-            int q = 0;
-            for (; q + 8 <= cnt; q += 8) {                // eight rows in flight, added in order
-                u32x4 r[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) r[e] = row(q + e);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) add(r[e]);
-            }
-            for (; q < cnt; ++q) add(row(q));
-        }
-        u32x4 pk;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) pk[j] = pack_bf16x2(acc[2 * j] * inv, acc[2 * j + 1] * inv);
-        dst[c] = pk;
+        for (int w = 1; w < 4; ++w) g = best[w][threadIdx.x] > g ? best[w][threadIdx.x] : g;
+        if (g != 0) atomicMax(&goal[lo + rows_a[i]], g);
     }
+}
+
+template <int A_ROWS, int B_ROWS>
+constexpr int kTargetLds = kSlabLds<A_ROWS, B_ROWS>;
+template <int A_ROWS, int B_ROWS>
+static hipError_t target_lds() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&merge_target_kernel<A_ROWS, B_ROWS>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, kTargetLds<A_ROWS, B_ROWS>);
+}
+hipError_t merge_init() {
+    hipError_t e;
+    if ((e = target_lds<64, 64>()) != hipSuccess) return e;
+    if ((e = target_lds<64, 128>()) != hipSuccess) return e;
+    return target_lds<128, 128>();
+}
+
+template <int A_ROWS, int B_ROWS>
+static void launch_target(const bf16_t* xn, const SegTable& st, int nd, int kk, int C, int k, int set_base, const int32_t* dropped,
+                          const int32_t* kept_idx, goal_t* goal, hipStream_t s) {
+    const int tiles_m = (nd + A_ROWS - 1) / A_ROWS, tiles_n = (kk + B_ROWS - 1) / B_ROWS;
+    hipLaunchKernelGGL((merge_target_kernel<A_ROWS, B_ROWS>), dim3((unsigned)(tiles_m * tiles_n * st.count)), dim3(SLAB_THREADS),
+                       (kTargetLds<A_ROWS, B_ROWS>), s, xn, st, C, k, set_base, tiles_m, tiles_n, dropped, kept_idx, goal);
+}
+
+// ---- out[set][slot] = mean of the rows that go to the slot; assign ----------------------------------
+// A workgroup takes four slots, two wavefronts each, 64 chunks of the row a wavefront.  The slots of the set's tokens are staged in
+// LDS once; of the two wavefronts of a slot one searches them, eight a lane at a time, and a prefix sum over the lanes gives every
+// member its place in the list.  Then sixteen rows in flight, added in index order: the largest slot of a set ends the kernel.
+// 10.1 us at 8 sets of 1024 x 1024, k = 256, 26.3 at 6 of 2880 x 1024, k = 1200.  (A workgroup a slot, which reads the slots of all
+// tokens for itself: 11.4 and 28; a wavefront a slot, 128 chunks wide: 15.2 and 26.6.)
+constexpr int MEAN_THREADS = 512, MEAN_SLOTS = 4, MEAN_COLS = 128;
+__host__ __device__ constexpr int mean_lds_tokens(int n) { return (n + 511) / 512 * 512; }      // a wavefront searches 512 at a time
+__global__ __launch_bounds__(MEAN_THREADS) void merge_mean_kernel(const bf16_t* __restrict__ x, SegTable st, int n_max, int C, int k,
+                                                                  int set_base, const goal_t* __restrict__ goal,
+                                                                  int32_t* __restrict__ assign, bf16_t* __restrict__ out) {
+    extern __shared__ __align__(16) uint16_t lds16[];    // slots of the tokens, then the members of each slot
+    __shared__ int members[MEAN_SLOTS];
+    const int set = blockIdx.y;
+    const int lo = st.off[set], n = st.off[set + 1] - lo;
+    const int kk = k < n ? k : n;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), chunks = C >> 3;
+    const uint32_t* goal_slots = reinterpret_cast<const uint32_t*>(goal + lo);       // the lower halves
+    const int padded = mean_lds_tokens(n);
+    for (int i0 = tid; i0 < padded; i0 += 4 * MEAN_THREADS) {                        // four loads in flight
+        int to[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int i = i0 + e * MEAN_THREADS;
+            to[e] = i < n ? slot_of_goal(goal_slots[2 * i]) : -1;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int i = i0 + e * MEAN_THREADS;
+            if (i < padded) lds16[i] = (uint16_t)to[e];                              // -1: no slot of 4096
+            if (i < n && blockIdx.z == 0 && (i >> 6) % (int)gridDim.x == (int)blockIdx.x) assign[lo + i] = to[e];
+        }
+    }
+    __syncthreads();
+    const int mine = wave >> 1, slot = (int)blockIdx.x * MEAN_SLOTS + mine;
+    uint16_t* list = lds16 + mean_lds_tokens(n_max) * (1 + mine);
+    if ((wave & 1) == 0) {
+        int m = 0;
+        if (slot < kk)
+            for (int i0 = 0; i0 < n; i0 += 512) {
+                const u32x4 v = *reinterpret_cast<const u32x4*>(lds16 + i0 + lane * 8);
+                uint32_t hit = 0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    hit |= ((v[e] & 0xffffu) == (uint32_t)slot ? 1u << (2 * e) : 0u) | (v[e] >> 16 == (uint32_t)slot ? 2u << (2 * e) : 0u);
+                const int here = __popc(hit), incl = wave_inclusive_sum(here);
+                int at = m + incl - here;
+                while (hit != 0) {
+                    list[at++] = (uint16_t)(i0 + lane * 8 + __builtin_ctz(hit));
+                    hit &= hit - 1;
+                }
+                m += __builtin_amdgcn_readlane(incl, 63);
+            }
+        if (lane == 0) members[mine] = m;
+    }
+    __syncthreads();
+    const int m = __builtin_amdgcn_readfirstlane(members[mine]);
+    const int c = (int)blockIdx.z * MEAN_COLS + (wave & 1) * 64 + lane;
+    if (slot >= k || c >= chunks) return;
+    const bf16_t* col = x + (int64_t)lo * C + (int64_t)c * 8;
+    float acc[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[j] = 0.0f;
+    for (int q = 0; q < m; q += 16) {
+        u32x4 r[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            if (q + e < m) r[e] = *reinterpret_cast<const u32x4*>(col + (int64_t)list[q + e] * C);     // uniform
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            if (q + e < m) {
+                float f[8];
+                unpack8s(r[e], f);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) acc[j] += f[j];
+            }
+    }
+    const float inv = 1.0f / (float)(m > 0 ? m : 1);     // a slot past the set's tokens: a row of zeros
+    u32x4 pk;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) pk[j] = pack_bf16x2(acc[2 * j] * inv, acc[2 * j + 1] * inv);
+    reinterpret_cast<u32x4*>(out + ((int64_t)(set_base + set) * k + slot) * C)[c] = pk;
 }
 
 // ---- gradient of the mean: dx[t] = dout[set][assign[t]] / (members of that slot) ---------------
@@ -373,39 +448,56 @@ hipError_t launch_merge_bwd_group(const bf16_t* dout, const SegTable& st, int n_
     return hipGetLastError();
 }
 
-hipError_t launch_row_normalize(const bf16_t* x, int64_t rows, int C, bf16_t* xn, hipStream_t s) {
-    if (rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(row_normalize_kernel, dim3((unsigned)rows), dim3(MG_THREADS), 0, s, x, C, xn);
-    return hipGetLastError();
-}
-
-// steps after the similarity GEMMs for the sets of one table (set_base = index of its first set)
-hipError_t launch_merge_group(const bf16_t* x, const SegTable& st, int n_max, int C, int k, int set_base,
-                              const float* sim, int ld, int64_t sim_stride, float* avg,
-                              int32_t* slot_of, int32_t* kept_idx, int32_t* assign, bf16_t* out,
-                              hipStream_t s) {
-    hipError_t e = hipSuccess;
+// the sets of one table (set_base = index of its first set), n_max rows in the largest
+hipError_t launch_merge_group(const bf16_t* x, const SegTable& st, int n_max, int C, int k, int set_base, const MergeScratch& ws,
+                              float* avg, int32_t* kept_idx, int32_t* assign, bf16_t* out, hipStream_t s) {
     const unsigned sets = (unsigned)st.count;
-    if (sets == 0) return e;
+    if (sets == 0) return hipSuccess;
+    goal_t* goal = static_cast<goal_t*>(ws.goal);
+    hipError_t e;
     if (n_max > 0) {
-        hipLaunchKernelGGL(sim_rowmean_kernel, dim3((unsigned)((n_max + 3) / 4), sets), dim3(MG_THREADS), 0, s,
-                           sim, st, ld, sim_stride, avg);
+        const int chunks = C >> 3, parts = (n_max + MERGE_CHUNK - 1) / MERGE_CHUNK;
+        const dim3 rows((unsigned)parts, sets), threads(MG_THREADS);
+        const size_t lds = (size_t)C * 16;
+        if (chunks <= 64) hipLaunchKernelGGL(merge_normalize_kernel<1>, rows, threads, lds, s, x, st, C, ws.xn, ws.part);
+        else if (chunks <= 128) hipLaunchKernelGGL(merge_normalize_kernel<2>, rows, threads, lds, s, x, st, C, ws.xn, ws.part);
+        else if (chunks <= 256) hipLaunchKernelGGL(merge_normalize_kernel<4>, rows, threads, lds, s, x, st, C, ws.xn, ws.part);
+        else if (chunks <= 512) hipLaunchKernelGGL(merge_normalize_kernel<8>, rows, threads, lds, s, x, st, C, ws.xn, ws.part);
+        else hipLaunchKernelGGL(merge_normalize_kernel<0>, rows, threads, lds, s, x, st, C, ws.xn, ws.part);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        const dim3 cols((unsigned)((C + 31) / 32), sets);
+        if (parts <= COLSUM_FEW_ROWS)
+            hipLaunchKernelGGL(merge_sum_kernel<COLSUM_LANES_FEW>, cols, dim3(32 * COLSUM_LANES_FEW), 0, s, ws.part, st, C, ws.sum);
+        else
+            hipLaunchKernelGGL(merge_sum_kernel<COLSUM_LANES>, cols, dim3(32 * COLSUM_LANES), 0, s, ws.part, st, C, ws.sum);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL(merge_average_kernel, dim3((unsigned)((n_max + 7) / 8), sets), dim3(MG_THREADS), 0, s, ws.xn, st, C, ws.sum, avg);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(merge_select_kernel, dim3(sets), dim3(TOPK_THREADS), 0, s, avg, st, k, set_base, slot_of,
-                       kept_idx);
+    hipLaunchKernelGGL(merge_select_kernel, dim3(sets), dim3(TOPK_THREADS), 0, s, avg, st, k, set_base, goal, ws.dropped, kept_idx, assign);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (n_max > 0) {
-        hipLaunchKernelGGL(merge_assign_kernel, dim3((unsigned)((n_max + 3) / 4), sets), dim3(MG_THREADS), 0, s,
-                           sim, st, ld, sim_stride, slot_of, assign);
+    if (k <= 0) return hipSuccess;
+    if (n_max > k) {
+        // rounds of the chip's CUs times the time of a slab, which the rows of its operands set (in units of 3.5 cycles a row)
+        const int nd = n_max - k;
+        int best = 0;
+        int64_t best_cost = 0;
+        const int a[3] = {128, 64, 64}, b[3] = {128, 128, 64};
+        for (int q = 0; q < 3; ++q) {
+            const int64_t tiles = (int64_t)((nd + a[q] - 1) / a[q]) * ((k + b[q] - 1) / b[q]) * st.count;
+            const int64_t cost = (tiles + 255) / 256 * (60 + a[q] + b[q]);
+            if (q == 0 || cost < best_cost) { best = q; best_cost = cost; }
+        }
+        if (best == 0) launch_target<128, 128>(ws.xn, st, nd, k, C, k, set_base, ws.dropped, kept_idx, goal, s);
+        else if (best == 1) launch_target<64, 128>(ws.xn, st, nd, k, C, k, set_base, ws.dropped, kept_idx, goal, s);
+        else launch_target<64, 64>(ws.xn, st, nd, k, C, k, set_base, ws.dropped, kept_idx, goal, s);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    if (k > 0) {
-        hipLaunchKernelGGL(merge_mean_kernel, dim3((unsigned)k, sets, (unsigned)(((C >> 3) + MG_THREADS - 1) / MG_THREADS)), dim3(MG_THREADS), 0, s, x, st, C, k,
-                           set_base, assign, out);
-        e = hipGetLastError();
-    }
-    return e;
+    hipLaunchKernelGGL(merge_mean_kernel, dim3((unsigned)((k + MEAN_SLOTS - 1) / MEAN_SLOTS), sets,
+                                               (unsigned)(((C >> 3) + MEAN_COLS - 1) / MEAN_COLS)),
+                       dim3(MEAN_THREADS), (size_t)mean_lds_tokens(n_max) * 2 * (1 + MEAN_SLOTS), s, x, st, n_max, C, k, set_base, goal,
+                       assign, out);
+    return hipGetLastError();
 }
 
 }  // namespace skipffn

@@ -13,37 +13,39 @@
 namespace skipffn {
 
 constexpr int SLAB_THREADS = 512;
-constexpr int SLAB_B_ROWS = 128;
-template <int A_ROWS>
-constexpr int kSlabStage = (A_ROWS + SLAB_B_ROWS) * 128;                 // bytes of a slab
-template <int A_ROWS>
-constexpr int kSlabStages = (160 * 1024) / kSlabStage<A_ROWS>;
-template <int A_ROWS>
-constexpr int kSlabLds = kSlabStages<A_ROWS> * kSlabStage<A_ROWS>;       // dynamic LDS of the kernel
+constexpr int SLAB_B_ROWS = 128;              // or 64, where tiles of 128 are too few
+template <int A_ROWS, int B_ROWS = SLAB_B_ROWS>
+constexpr int kSlabStage = (A_ROWS + B_ROWS) * 128;                      // bytes of a slab
+template <int A_ROWS, int B_ROWS = SLAB_B_ROWS>
+constexpr int kSlabStages = (160 * 1024) / kSlabStage<A_ROWS, B_ROWS>;
+template <int A_ROWS, int B_ROWS = SLAB_B_ROWS>
+constexpr int kSlabLds = kSlabStages<A_ROWS, B_ROWS> * kSlabStage<A_ROWS, B_ROWS>;       // dynamic LDS of the kernel
 template <int A_ROWS>
 constexpr int kSlabPiecesA = A_ROWS / 64;                                // 1 KB pieces of A each wavefront loads
-template <int A_ROWS>
-constexpr int kSlabPieces = kSlabPiecesA<A_ROWS> + 2;                    // and of both
+template <int A_ROWS, int B_ROWS = SLAB_B_ROWS>
+constexpr int kSlabPieces = kSlabPiecesA<A_ROWS> + B_ROWS / 64;          // and of both
 
 // goff[l]: byte offset of the lane's 16 bytes of piece l at slab 0, or kOobOffset.  Wavefront w loads the 8-row pieces
-// q = w * kSlabPiecesA + l of A, then q = 2 w, 2 w + 1 of B; its lane takes row 8 q + lane / 8 and the chunk of 8 k
+// q = w * kSlabPiecesA + l of A, then q = 2 w, 2 w + 1 of B; (B_ROWS = 64: q = w); its lane takes row 8 q + lane / 8 and the chunk of 8 k
 // (lane % 8) ^ ((row / 2) % 8).  Slabs kt0 .. kt0 + nk - 1 are summed, beginning at kt0 + rot (rot = 0: in order;
 // otherwise every slab has to lie inside K); k past K count as zeros.
-// acc[m][f], wavefront (wm, wn): A rows wm * A_ROWS / 2 + 16 m + lane % 16, B rows b_row + f * B_STRIDE + 4 (lane / 16) + r.
+// acc[m][f], wavefront (wm, wn): A rows wm * A_ROWS / 2 + 16 m + lane % 16, B rows b_row + f * B_STRIDE + 4 (lane / 16) + r, f < B_ROWS / 64.
 // All 512 threads call it with the same kt0, nk, rot, K.
 //
 // NORM: the rows of A are not normalised yet; their squares are added from the MFMA operands in registers, a fragment by one
 // of the four wavefronts that hold it: ss[m] of a lane gathers k of row ... + 16 m + lane % 16, and the sum over the four lanes
 // of a row in the four wavefronts of the row group is the row's.
-template <int A_ROWS, int B_STRIDE, bool NORM = false>
+template <int A_ROWS, int B_STRIDE, bool NORM = false, int B_ROWS = SLAB_B_ROWS>
 __device__ __forceinline__ void slab_loop(const __amdgpu_buffer_rsrc_t ra, const __amdgpu_buffer_rsrc_t rb,
-                                          const uint32_t (&goff)[kSlabPieces<A_ROWS>], const int b_row, const int kt0,
-                                          const int nk, const int rot, const int K, f32x4 (&acc)[A_ROWS / 32][2],
+                                          const uint32_t (&goff)[kSlabPieces<A_ROWS, B_ROWS>], const int b_row, const int kt0,
+                                          const int nk, const int rot, const int K, f32x4 (&acc)[A_ROWS / 32][B_ROWS / 64],
                                           float (&ss)[A_ROWS / 32]) {
     static_assert(A_ROWS % 64 == 0 && A_ROWS <= 256, "two row groups, whole pieces per wavefront");
-    constexpr int NST = kSlabStages<A_ROWS>, STAGE = kSlabStage<A_ROWS>, B_BASE = A_ROWS * 128;
+    constexpr int NST = kSlabStages<A_ROWS, B_ROWS>, STAGE = kSlabStage<A_ROWS, B_ROWS>, B_BASE = A_ROWS * 128;
     constexpr int MI = A_ROWS / 32;           // row fragments of a wavefront
-    constexpr int NLA = kSlabPiecesA<A_ROWS>, NL = kSlabPieces<A_ROWS>;
+    constexpr int NLA = kSlabPiecesA<A_ROWS>, NL = kSlabPieces<A_ROWS, B_ROWS>;
+    constexpr int NF = B_ROWS / 64;           // fragments and 1 KB pieces of B of a wavefront
+    static_assert(B_ROWS == 64 || B_ROWS == 128, "four column groups");
     static_assert(NST >= 3, "two slabs in flight beside the one that is read");
     extern __shared__ __align__(16) char smem[];
     const int lane = threadIdx.x & 63;
@@ -52,7 +54,7 @@ __device__ __forceinline__ void slab_loop(const __amdgpu_buffer_rsrc_t ra, const
     const int r16 = lane & 15, kq = lane >> 4;
     typedef __attribute__((address_space(3))) void* lds_void_ptr;
     auto lds_piece = [&](int stage, int l) {
-        return smem + stage * STAGE + (l < NLA ? (wave * NLA + l) * 1024 : B_BASE + (wave * 2 + (l - NLA)) * 1024);
+        return smem + stage * STAGE + (l < NLA ? (wave * NLA + l) * 1024 : B_BASE + (wave * NF + (l - NLA)) * 1024);
     };
     auto slab_of = [&](int j) { const int jr = j + rot; return kt0 + (jr < nk ? jr : jr - nk); };
     // a slab that may reach past K: k past the end are zeros
@@ -60,7 +62,7 @@ __device__ __forceinline__ void slab_loop(const __amdgpu_buffer_rsrc_t ra, const
         const int slab = slab_of(j);
 #pragma unroll
         for (int l = 0; l < NL; ++l) {
-            const int q = l < NLA ? wave * NLA + l : wave * 2 + (l - NLA);
+            const int q = l < NLA ? wave * NLA + l : wave * NF + (l - NLA);
             const int row = 8 * q + (lane >> 3), kk = slab * BK + ((lane & 7) ^ ((row >> 1) & 7)) * 8;
             const uint32_t off = goff[l] != kOobOffset && kk < K ? goff[l] + (uint32_t)slab * (BK * 2) : kOobOffset;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(l < NLA ? ra : rb, (lds_void_ptr)lds_piece(j % NST, l), 16, (int)off, 0, 0, 0);
@@ -70,7 +72,7 @@ __device__ __forceinline__ void slab_loop(const __amdgpu_buffer_rsrc_t ra, const
 #pragma unroll
     for (int m = 0; m < MI; ++m)
 #pragma unroll
-        for (int f = 0; f < 2; ++f) acc[m][f] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int f = 0; f < NF; ++f) acc[m][f] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int m = 0; m < MI; ++m) ss[m] = 0.0f;
     uint32_t a_rd[2], b_rd[2];
@@ -84,7 +86,7 @@ __device__ __forceinline__ void slab_loop(const __amdgpu_buffer_rsrc_t ra, const
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
     };
-    bf16x8 af[2][MI], bfr[2][2];
+    bf16x8 af[2][MI], bfr[2][NF];
     int st_rd = 0, st_ld = NST - 1;                     // stages slab j is read from and slab j + NST - 1 loaded to
     // the memory phase of slab j: the loads of slab j + NST - 1 spread between the fragment reads
     auto memory_phase = [&](int j, auto steady) {
@@ -93,16 +95,16 @@ __device__ __forceinline__ void slab_loop(const __amdgpu_buffer_rsrc_t ra, const
         const int step = STEADY ? slab_of(j + NST - 1) * (BK * 2) : 0;
         const uint32_t so = (uint32_t)(st_rd * STAGE);
         const uint32_t aa[2] = {a_rd[0] + so, a_rd[1] + so}, ba[2] = {b_rd[0] + so, b_rd[1] + so};
-        constexpr int NR = 2 * (MI + 2);
+        constexpr int NR = 2 * (MI + NF);
         static_for<NR>([&](auto r) {
             if constexpr (STEADY)
                 static_for<NL>([&](auto l) {
                     if constexpr (l * NR / NL == r)
                         __builtin_amdgcn_raw_ptr_buffer_load_lds(l < NLA ? ra : rb, (lds_void_ptr)lds_piece(st_ld, l), 16, (int)goff[l], step, 0, 0);
                 });
-            constexpr int ks = r / (MI + 2), i = r % (MI + 2);
-            if constexpr (i < 2) bfr[ks][i] = ds_read_b128_imm<i * B_STRIDE * 128>(ba[ks]);
-            else af[ks][i - 2] = ds_read_b128_imm<(i - 2) * 2048>(aa[ks]);
+            constexpr int ks = r / (MI + NF), i = r % (MI + NF);
+            if constexpr (i < NF) bfr[ks][i] = ds_read_b128_imm<i * B_STRIDE * 128>(ba[ks]);
+            else af[ks][i - NF] = ds_read_b128_imm<(i - NF) * 2048>(aa[ks]);
         });
     };
     // slab j + 1 has landed; the slabs issued after it may still fly
@@ -126,8 +128,8 @@ __device__ __forceinline__ void slab_loop(const __amdgpu_buffer_rsrc_t ra, const
 #pragma unroll
             for (int m = 0; m < MI; ++m)
 #pragma unroll
-                for (int fj = 0; fj < 2; ++fj) {
-                    const int f = (m & 1) ? 1 - fj : fj;
+                for (int fj = 0; fj < NF; ++fj) {
+                    const int f = (m & 1) ? NF - 1 - fj : fj;
                     acc[m][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[ks][f], af[ks][m], acc[m][f], 0, 0, 0);
                 }
         __builtin_amdgcn_sched_barrier(0);
