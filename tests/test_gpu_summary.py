@@ -169,3 +169,10 @@ def test_no_sets_is_a_no_op_and_zeroes_dw():
     B.skipffn_summary_backward(d_h, tok, seg, w, sv, out, d_h.clone(), dw, workspace=ws)
     torch.cuda.synchronize()
     assert torch.count_nonzero(dw).item() == 0
+
+
+@pytest.mark.parametrize("C", [8, 1024, 1032, 2048, 2056, 4088, 4104])
+def test_rows_held_in_registers(C):
+    """Widths at the ends of the forms that hold the rows of a chunk in registers, and past the last; a chunk of one token, a full
+    one, and sets of several."""
+    test_summary_forward_backward_against_oracle(300, C, (1, 16, 17, 130))
