@@ -258,11 +258,11 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
     }
 
     hipError_t e;
-    if (out != hidden && R != T) {       // R == T: every row is retained
-        e = launch_passthrough(hidden, out, T, C * 2, idx, (int)Rb, r_dev, s);
-        if (e != hipSuccess) return hip_fail(e);
+    const SkippedRows skipped{hidden, out != hidden && R != T ? out : nullptr, T, C / 8, idx};    // R == T: every row is retained
+    if (Rb == 0) {
+        e = launch_passthrough(skipped, 0, r_dev, s);
+        return e == hipSuccess ? SKIPFFN_OK : hip_fail(e);
     }
-    if (Rb == 0) return SKIPFFN_OK;
     if ((e = ensure_gemm_init()) != hipSuccess) return hip_fail(e);
 
     FwdWs W = fwd_ws(Rb, C, I, saved != nullptr, num_cus());
@@ -296,13 +296,16 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
     // (2) gather + RMSNorm, or in the gate/up GEMM
     const RowNorm rows{static_cast<const bf16_t*>(hidden), T, idx, static_cast<const bf16_t*>(rms_gain), eps};
     const RowNorm* norm = plan.norm_in_gate_up ? &rows : nullptr;
-    if (norm == nullptr)
-        e = launch_gather_rmsnorm(static_cast<const bf16_t*>(hidden), idx, (int)Rb, r_dev, (int)C, eps,
-                              static_cast<const bf16_t*>(rms_gain), xrows, xn, rstd, chunk_major_xn, s);
+    e = norm != nullptr ? launch_passthrough(skipped, (int)Rb, r_dev, s)
+                        : launch_gather_rmsnorm(static_cast<const bf16_t*>(hidden), idx, (int)Rb, r_dev, (int)C, eps,
+                                                static_cast<const bf16_t*>(rms_gain), xrows, xn, rstd, chunk_major_xn, skipped, s);
     if (e != hipSuccess) return hip_fail(e);
-    if (xnT != nullptr) {   // K-contiguous copy of the normalised rows for the dW_gate / dW_up GEMMs
-        e = launch_gather_transpose(xn, (int)C, nullptr, (int)Rb, r_dev, nullptr, xnT,
-                                    (int)ld_transposed(Rb), s);
+    // K-contiguous copies for the dW GEMMs: of the normalised rows, and of silu(gate) * up unless the core's epilogue writes it; both
+    // at once where the second has to wait for the gate/up GEMM
+    const TransposeJob transposes[2] = {{xn, (int)C, nullptr, nullptr, xnT}, {H, (int)I, nullptr, nullptr, HT}};
+    const bool transpose_h = HT != nullptr && plan.gate_up != FWD_CORE;
+    if (xnT != nullptr && !transpose_h) {
+        e = launch_gather_transpose(transposes, 1, (int)Rb, r_dev, (int)ld_transposed(Rb), SkippedRows{}, s);
         if (e != hipSuccess) return hip_fail(e);
     }
 
@@ -330,8 +333,8 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
     }
     profile_mark_end(KC_GEMM_GATE_UP, s);
     if (e != hipSuccess) return hip_fail(e);
-    if (HT != nullptr && plan.gate_up != FWD_CORE) {          // from a copy kernel, for the dW_down GEMM
-        e = launch_gather_transpose(H, (int)I, nullptr, (int)Rb, r_dev, nullptr, HT, (int)ld_transposed(Rb), s);
+    if (transpose_h) {
+        e = launch_gather_transpose(transposes, 2, (int)Rb, r_dev, (int)ld_transposed(Rb), SkippedRows{}, s);
         if (e != hipSuccess) return hip_fail(e);
     }
 
@@ -426,11 +429,9 @@ int skipffn_backward(int64_t T, int64_t C, int64_t I, float eps, const void* gra
         if (st != SKIPFFN_OK) return st;
     }
     hipError_t e;
-    if (T > 0 && grad_hidden != grad_out && R != T) {
-        e = launch_passthrough(grad_out, grad_hidden, T, C * 2, idx, (int)Rb, r_dev, s);
-        if (e != hipSuccess) return hip_fail(e);
-    }
+    const SkippedRows skipped{grad_out, grad_hidden != grad_out && R != T ? grad_hidden : nullptr, T, C / 8, idx};
     if (Rb == 0) {
+        if ((e = launch_passthrough(skipped, 0, r_dev, s)) != hipSuccess) return hip_fail(e);
         if (!accum) {
             size_t wbytes = (size_t)I * C * (f32 ? 4 : 2);
             if ((e = launch_fill_zero(dw_gate, wbytes, s)) != hipSuccess) return hip_fail(e);
@@ -463,8 +464,8 @@ int skipffn_backward(int64_t T, int64_t C, int64_t I, float eps, const void* gra
     // dY = dOut[idx], and its transposed copy dY^T [C][ldT] for the dW_down GEMM
     bf16_t* dYT = reinterpret_cast<bf16_t*>(ws + W.dyT);
     const int ldT = (int)ld_transposed(Rb);
-    e = launch_gather_transpose(static_cast<const bf16_t*>(grad_out), (int)C, idx, (int)Rb, r_dev, dY,
-                                dYT, ldT, s);
+    const TransposeJob dy_job{static_cast<const bf16_t*>(grad_out), (int)C, idx, dY, dYT};
+    e = launch_gather_transpose(&dy_job, 1, (int)Rb, r_dev, ldT, skipped, s);
     if (e != hipSuccess) return hip_fail(e);
 
     // dH = dY * W_down fused with the SiLU*mul backward (-> dG, dU and their transposed copies),

@@ -49,10 +49,13 @@ hipError_t launch_validate_idx(const int32_t* idx, int R, const int32_t* r_dev, 
                                hipStream_t s);
 
 // ---- row kernels ---------------------------------------------------------------
+// Rows 0 .. T - 1 of row_chunks 16-byte pieces each; those NOT listed in idx are copied from src to dst (null: none).  A
+// job of its own (launch_passthrough), or beside another kernel that reads the same rows.
+struct SkippedRows { const void* src; void* dst; int64_t T, row_chunks; const int32_t* idx; };
 // x rows (optional copy), normalised rows and 1/rms for rows idx[0..R); chunk_major: xn is [C / 8][R][8]
 hipError_t launch_gather_rmsnorm(const bf16_t* hidden, const int32_t* idx, int R,
                                  const int32_t* r_dev, int C, float eps, const bf16_t* gain,
-                                 bf16_t* xrows, bf16_t* xn, float* rstd, bool chunk_major, hipStream_t s);
+                                 bf16_t* xrows, bf16_t* xn, float* rstd, bool chunk_major, const SkippedRows& sk, hipStream_t s);
 // How many fp32 partial slabs a reducing kernel adds per output element: `splits` for a plain
 // split-K GEMM (sk_nbg == 0), else the per-tile count of the balanced split (streamk_count)
 // with sk_nbg workgroups per n-tile group and sk_kt K slabs per tile.
@@ -72,13 +75,11 @@ hipError_t launch_kv_compact(const void* src, void* dst, int64_t n_slabs, int64_
                              int64_t src_slab_bytes, int64_t dst_slab_bytes, const int32_t* idx,
                              int R, const int32_t* r_dev, hipStream_t s);
 // dst[r] = src[idx ? idx[r] : r] (dst optional) and the transposed copy dstT[c][r], leading
-// dimension ldT (multiple of 8, >= R bound), columns r >= R zero
-hipError_t launch_gather_transpose(const bf16_t* src, int C, const int32_t* idx, int R,
-                                   const int32_t* r_dev, bf16_t* dst, bf16_t* dstT, int ldT,
+// dimension ldT (multiple of 8, >= R bound), columns r >= R zero; one or two copies of the same R rows
+struct TransposeJob { const bf16_t* src; int C; const int32_t* idx; bf16_t* dst; bf16_t* dstT; };
+hipError_t launch_gather_transpose(const TransposeJob* jobs, int count, int R, const int32_t* r_dev, int ldT, const SkippedRows& sk,
                                    hipStream_t s);
-// copy every row t of src to dst that is NOT listed in idx (skipped tokens)
-hipError_t launch_passthrough(const void* src, void* dst, int64_t T, int64_t row_bytes,
-                              const int32_t* idx, int R, const int32_t* r_dev, hipStream_t s);
+hipError_t launch_passthrough(const SkippedRows& sk, int R, const int32_t* r_dev, hipStream_t s);
 // dX[idx[r]] = bf16(dY[r] + rmsnorm_bwd(sum_z dxn_partial[z][r], x[r], rstd[r], gain)); with dgain != null
 // also dgain[c] (+)= sum_r dxn[r][c] * x[r][c] * rstd[r] (fp32, through gain_partial)
 hipError_t launch_rmsnorm_bwd_scatter(const float* dxn_partial, PartialLayout pl, int R,

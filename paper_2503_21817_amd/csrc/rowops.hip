@@ -33,6 +33,45 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
     return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
+// ---- bit copy of skipped rows (out-of-place calls) ---------------------------------------
+// A wavefront takes a row t and copies it unless t is in the ascending list idx.  The search probes 64 positions at a
+// time: two dependent loads up to 4096 entries, where halving takes 12 before the copy can begin; the row is then
+// copied with eight loads in flight per lane (a row of 4096 at once).  616 rows 7.8 -> 5.2 us, 1232 rows 9.8 ->
+// 6.1, 4928 rows 16.4 -> 14.0.  It depends on nothing but the hidden states (the gradient), so it shares a launch with the first
+// kernel of the call that reads them too.
+constexpr int ROWS_PER_BLOCK = ROW_THREADS / 64;   // copy kernels: one wavefront per row
+static unsigned skipped_blocks(const SkippedRows& sk) {
+    return sk.dst == nullptr ? 0u : (unsigned)((sk.T + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK);
+}
+__device__ __forceinline__ void copy_skipped_rows(const SkippedRows& sk, const int block, const int R) {
+    const int lane = threadIdx.x & 63;
+    const int64_t t = (int64_t)block * ROWS_PER_BLOCK + (threadIdx.x >> 6);
+    const int32_t* idx = sk.idx;
+    if (t >= sk.T) return;
+    int lo = 0, hi = R;              // the first position with idx[pos] >= t lies in [lo, hi]
+    while (hi - lo > 63) {
+        const int step = (hi - lo + 63) >> 6;
+        const int p = lo + lane * step;
+        const int below = __popcll(__ballot(p < hi && idx[p < hi ? p : lo] < t));    // ascending: a prefix of the lanes
+        const int end = lo + below * step;
+        if (below == 0) hi = lo;
+        else { lo = end - step + 1; hi = end < hi ? end : hi; }
+    }
+    const int p = lo + lane;
+    if (__ballot(p <= hi && p < R && idx[p < R ? p : 0] == t) != 0) return;   // retained: written by the scatter epilogue
+    const u32x4* s = static_cast<const u32x4*>(sk.src) + t * sk.row_chunks;
+    u32x4* d = static_cast<u32x4*>(sk.dst) + t * sk.row_chunks;
+    int64_t c = lane;
+    for (; c + 7 * 64 < sk.row_chunks; c += 8 * 64) {
+        u32x4 v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = s[c + k * 64];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) d[c + k * 64] = v[k];
+    }
+    for (; c < sk.row_chunks; c += 64) d[c] = s[c];
+}
+
 // ---- gather + RMSNorm -------------------------------------------------------------
 // n(x) = x * rsqrt(mean(x^2) + eps) * gain for the rows idx[r]; x is read once
 // (held in registers), the un-normalised row is optionally copied for backward.
@@ -40,11 +79,12 @@ template <bool IN_REGS>
 __global__ __launch_bounds__(ROW_THREADS) void gather_rmsnorm_kernel(
     const bf16_t* __restrict__ hidden, const int32_t* __restrict__ idx, int Rbound,
     const int32_t* __restrict__ r_dev, int C, float eps, const bf16_t* __restrict__ gain,
-    bf16_t* __restrict__ xrows, bf16_t* __restrict__ xn, int64_t xn_row, int xn_chunk, float* __restrict__ rstd_out) {
+    bf16_t* __restrict__ xrows, bf16_t* __restrict__ xn, int64_t xn_row, int xn_chunk, float* __restrict__ rstd_out, SkippedRows sk) {
     __shared__ float red[4];
     const int R = effective_rows(Rbound, r_dev);
     const int tid = threadIdx.x;
     const int r = blockIdx.x;
+    if (r >= Rbound) return copy_skipped_rows(sk, r - Rbound, R);
     if (r >= R) return;                       // the whole workgroup leaves together
     const int chunks = C >> 3;
     const u32x4* src = reinterpret_cast<const u32x4*>(hidden + (int64_t)idx[r] * C);
@@ -106,18 +146,18 @@ __global__ __launch_bounds__(ROW_THREADS) void gather_rmsnorm_kernel(
 
 hipError_t launch_gather_rmsnorm(const bf16_t* hidden, const int32_t* idx, int R,
                                  const int32_t* r_dev, int C, float eps, const bf16_t* gain,
-                                 bf16_t* xrows, bf16_t* xn, float* rstd, bool chunk_major, hipStream_t s) {
+                                 bf16_t* xrows, bf16_t* xn, float* rstd, bool chunk_major, const SkippedRows& sk, hipStream_t s) {
     if (R <= 0) return hipSuccess;
     const int64_t xn_row = chunk_major ? 1 : C >> 3;
     const int xn_chunk = chunk_major ? R : 1;
-    dim3 grid(R), block(ROW_THREADS);
+    dim3 grid((unsigned)R + skipped_blocks(sk)), block(ROW_THREADS);
     profile_mark_begin(KC_GATHER_RMSNORM, s);
     if (C <= ROW_THREADS * 8 * RMS_MAXV)
         hipLaunchKernelGGL(gather_rmsnorm_kernel<true>, grid, block, 0, s, hidden, idx, R, r_dev, C,
-                           eps, gain, xrows, xn, xn_row, xn_chunk, rstd);
+                           eps, gain, xrows, xn, xn_row, xn_chunk, rstd, sk);
     else
         hipLaunchKernelGGL(gather_rmsnorm_kernel<false>, grid, block, 0, s, hidden, idx, R, r_dev, C,
-                           eps, gain, xrows, xn, xn_row, xn_chunk, rstd);
+                           eps, gain, xrows, xn, xn_row, xn_chunk, rstd, sk);
     profile_mark_end(KC_GATHER_RMSNORM, s);
     return hipGetLastError();
 }
@@ -224,7 +264,6 @@ hipError_t launch_resid_scatter(const float* partial, PartialLayout pl, int R, c
 }
 
 // ---- row gather (upstream gradient rows; skip KV-cache of Section 4.3) -----------------
-constexpr int ROWS_PER_BLOCK = ROW_THREADS / 64;   // copy kernels: one wavefront per row
 __global__ __launch_bounds__(ROW_THREADS) void gather_rows_kernel(
     const u32x4* __restrict__ src, u32x4* __restrict__ dst, int64_t row_chunks,
     const int32_t* __restrict__ idx, int Rbound, const int32_t* __restrict__ r_dev) {
@@ -290,13 +329,27 @@ hipError_t launch_kv_compact(const void* src, void* dst, int64_t n_slabs, int64_
 // bound); columns r >= R of dstT are written as zeros so that K-slabs reading past R see
 // zeros.  The weight-gradient GEMMs contract over R: a copy with R contiguous lets them read
 // this operand with plain 16-byte LDS reads instead of transposing ones.
+// A launch takes up to two such copies of the same rows, and the skipped rows: each is a few us of latency at small sizes.
 constexpr int TR_TILE = 64;
-__global__ __launch_bounds__(256) void gather_transpose_kernel(
-    const bf16_t* __restrict__ src, int C, const int32_t* __restrict__ idx, int Rbound,
-    const int32_t* __restrict__ r_dev, bf16_t* __restrict__ dst, bf16_t* __restrict__ dstT, int ldT) {
+struct TransposeArgs {
+    TransposeJob job[2];
+    int blocks[2], tiles_r;                              // workgroups of a job, tiles of TR_TILE rows
+    int Rbound; const int32_t* r_dev; int ldT;
+    SkippedRows sk;
+};
+__global__ __launch_bounds__(256) void gather_transpose_kernel(TransposeArgs P) {
     __shared__ bf16_t tile[TR_TILE][TR_TILE + 2];
-    const int R = effective_rows(Rbound, r_dev);
-    const int r0 = blockIdx.x * TR_TILE, c0 = blockIdx.y * TR_TILE;
+    const int R = effective_rows(P.Rbound, P.r_dev);
+    int b = (int)blockIdx.x;
+    if (b >= P.blocks[0] + P.blocks[1]) return copy_skipped_rows(P.sk, b - P.blocks[0] - P.blocks[1], R);
+    const bool second = b >= P.blocks[0];                // uniform
+    if (second) b -= P.blocks[0];
+    const bf16_t* src = second ? P.job[1].src : P.job[0].src;
+    const int32_t* idx = second ? P.job[1].idx : P.job[0].idx;
+    bf16_t* dst = second ? P.job[1].dst : P.job[0].dst;
+    bf16_t* dstT = second ? P.job[1].dstT : P.job[0].dstT;
+    const int C = second ? P.job[1].C : P.job[0].C, ldT = P.ldT;
+    const int r0 = b % P.tiles_r * TR_TILE, c0 = b / P.tiles_r * TR_TILE;
     const int t = threadIdx.x;
     // phase 1: 64 rows x 64 columns, 16 bytes per access
 #pragma unroll
@@ -333,60 +386,31 @@ __global__ __launch_bounds__(256) void gather_transpose_kernel(
     }
 }
 
-hipError_t launch_gather_transpose(const bf16_t* src, int C, const int32_t* idx, int R,
-                                   const int32_t* r_dev, bf16_t* dst, bf16_t* dstT, int ldT,
+hipError_t launch_gather_transpose(const TransposeJob* jobs, int count, int R, const int32_t* r_dev, int ldT, const SkippedRows& sk,
                                    hipStream_t s) {
-    if (R <= 0 || C <= 0) return hipSuccess;
-    dim3 grid((ldT + TR_TILE - 1) / TR_TILE, (C + TR_TILE - 1) / TR_TILE), block(256);
+    if (R <= 0 || count <= 0) return hipSuccess;
+    if (count > 2) return hipErrorInvalidValue;
+    TransposeArgs a{};
+    a.tiles_r = (ldT + TR_TILE - 1) / TR_TILE;
+    for (int j = 0; j < count; ++j) {
+        a.job[j] = jobs[j];
+        a.blocks[j] = a.tiles_r * ((jobs[j].C + TR_TILE - 1) / TR_TILE);
+    }
+    a.Rbound = R; a.r_dev = r_dev; a.ldT = ldT; a.sk = sk;
     profile_mark_begin(KC_GATHER_ROWS, s);
-    hipLaunchKernelGGL(gather_transpose_kernel, grid, block, 0, s, src, C, idx, R, r_dev, dst, dstT, ldT);
+    hipLaunchKernelGGL(gather_transpose_kernel, dim3((unsigned)(a.blocks[0] + a.blocks[1]) + skipped_blocks(sk)), dim3(256), 0, s, a);
     profile_mark_end(KC_GATHER_ROWS, s);
     return hipGetLastError();
 }
 
-// ---- bit copy of skipped rows (out-of-place calls) ---------------------------------------
-// A wavefront takes a row t and copies it unless t is in the ascending list idx.  The search probes 64 positions at a
-// time: two dependent loads up to 4096 entries, where halving takes 12 before the copy can begin; the row is then
-// copied with eight loads in flight per lane (a row of 4096 at once).  616 rows 7.8 -> 5.2 us, 1232 rows 9.8 ->
-// 6.1, 4928 rows 16.4 -> 14.0.
-__global__ __launch_bounds__(ROW_THREADS) void passthrough_kernel(
-    const u32x4* __restrict__ src, u32x4* __restrict__ dst, int64_t T, int64_t row_chunks,
-    const int32_t* __restrict__ idx, int Rbound, const int32_t* __restrict__ r_dev) {
-    const int R = effective_rows(Rbound, r_dev);
-    const int lane = threadIdx.x & 63;
-    const int64_t t = (int64_t)blockIdx.x * ROWS_PER_BLOCK + (threadIdx.x >> 6);
-    if (t >= T) return;
-    int lo = 0, hi = R;              // the first position with idx[pos] >= t lies in [lo, hi]
-    while (hi - lo > 63) {
-        const int step = (hi - lo + 63) >> 6;
-        const int p = lo + lane * step;
-        const int below = __popcll(__ballot(p < hi && idx[p < hi ? p : lo] < t));    // ascending: a prefix of the lanes
-        const int end = lo + below * step;
-        if (below == 0) hi = lo;
-        else { lo = end - step + 1; hi = end < hi ? end : hi; }
-    }
-    const int p = lo + lane;
-    if (__ballot(p <= hi && p < R && idx[p < R ? p : 0] == t) != 0) return;   // retained: written by the scatter epilogue
-    const u32x4* s = src + t * row_chunks;
-    u32x4* d = dst + t * row_chunks;
-    int64_t c = lane;
-    for (; c + 7 * 64 < row_chunks; c += 8 * 64) {
-        u32x4 v[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = s[c + k * 64];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) d[c + k * 64] = v[k];
-    }
-    for (; c < row_chunks; c += 64) d[c] = s[c];
+__global__ __launch_bounds__(ROW_THREADS) void passthrough_kernel(SkippedRows sk, int Rbound, const int32_t* __restrict__ r_dev) {
+    copy_skipped_rows(sk, (int)blockIdx.x, effective_rows(Rbound, r_dev));
 }
 
-hipError_t launch_passthrough(const void* src, void* dst, int64_t T, int64_t row_bytes,
-                              const int32_t* idx, int R, const int32_t* r_dev, hipStream_t s) {
-    if (T <= 0 || row_bytes <= 0) return hipSuccess;
-    dim3 grid((unsigned)((T + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK)), block(ROW_THREADS);
+hipError_t launch_passthrough(const SkippedRows& sk, int R, const int32_t* r_dev, hipStream_t s) {
+    if (sk.dst == nullptr || sk.T <= 0 || sk.row_chunks <= 0) return hipSuccess;
     profile_mark_begin(KC_PASSTHROUGH, s);
-    hipLaunchKernelGGL(passthrough_kernel, grid, block, 0, s, static_cast<const u32x4*>(src),
-                       static_cast<u32x4*>(dst), T, row_bytes / 16, idx, R < 0 ? 0 : R, r_dev);
+    hipLaunchKernelGGL(passthrough_kernel, dim3(skipped_blocks(sk)), dim3(ROW_THREADS), 0, s, sk, R < 0 ? 0 : R, r_dev);
     profile_mark_end(KC_PASSTHROUGH, s);
     return hipGetLastError();
 }
