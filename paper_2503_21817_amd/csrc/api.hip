@@ -316,7 +316,7 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
         e = launch_few_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_xn, chunk_major_h, norm, s);
     } else if (plan.gate_up == FWD_MID) {
         e = launch_mid_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_h, plan.gate_up_splits,
-                                    partial, norm, s);
+                                    plan.gate_up_cols, partial, norm, s);
     } else {
         GemmArgs a{};
         a.M = (int)Rb; a.N = (int)I; a.K = (int)C; a.m_dev = r_dev;

@@ -70,8 +70,8 @@ hipError_t launch_gate_up_count(GemmArgs& a, hipStream_t s) {
     a.tiles_n = (a.N + BN / 2 - 1) / (BN / 2);
     a.splits = a.batch = 1;
     const MidRowsArgs m = mid_rows_gate_up_args(a.A0, a.M, a.m_dev, a.K, a.N, a.B0, a.B1, static_cast<bf16_t*>(a.out0), nullptr,
-                                                nullptr, false);
-    const int lists = list_workgroups(a), mid = (a.N + SLAB_B_ROWS / 2 - 1) / (SLAB_B_ROWS / 2);
+                                                nullptr, false, gate_up_cols(256, a.N, a.ncu));
+    const int lists = list_workgroups(a), mid = (a.N + m.cols - 1) / m.cols;
     hipLaunchKernelGGL(gate_up_count_kernel, dim3((unsigned)std::max(lists, mid)), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a, m,
                        lists, mid);
     return hipGetLastError();

@@ -141,10 +141,10 @@ hipError_t launch_few_rows_down(const bf16_t* H, int rows, const int32_t* r_dev,
 
 // ---- the forward GEMMs of up to 256 rows ------------------------------------------------------------------
 hipError_t mid_rows_init();      // raises the dynamic-LDS limit of every instantiation (once per process)
-// norm != null: xn is not read (mid_rows_norm).  chunk_major_h: H is [I / 8][rows][8] instead of row-major; splits > 1: K cut in fp32 partial[splits][rows][2][I]
+// norm != null: xn is not read, up to kNormInMidRows rows.  cols: gate_up_cols.  chunk_major_h: H is [I / 8][rows][8] instead of row-major; splits > 1: K cut in fp32 partial[splits][rows][2][I]
 hipError_t launch_mid_rows_gate_up(const bf16_t* xn, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_gate,
                                    const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major_h, int splits,
-                                   float* partial, const RowNorm* norm, hipStream_t s);
+                                   int cols, float* partial, const RowNorm* norm, hipStream_t s);
 // fp32 partial[splits][rows][C]
 hipError_t launch_mid_rows_down(const bf16_t* H, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_down,
                                 int splits, float* partial, hipStream_t s);

@@ -116,13 +116,15 @@ inline int choose_k_split(int tiles, int ktiles, int max_splits, int ncu) {
 //   down (K = I)      C = 256, I = 688: -6.5;  C = 2048, I = 2048: -4.8 (-3.9) at 16, -3.7 (-0.8) at 64;  C = 1024, I = 3584:
 //     -2.9 (-1.9) at 16, 0.7 (6) at 64;  C = 512, I = 8192: 0.4 (4) at 16, 5 (12) at 32, 11 (27) at 64;  I = 32768: 21 to
 //     133.  With a column block for every CU (C = 4096) the tiles are slower too: I = 14336: -3.3 at 1 row, -0.2 at 16.
-// (Without a saved buffer and a gain the tiles normalise their rows themselves, see norm_in_gate_up: from 33 rows on they take C = 2048, I = 7168
-// in 38.7 us at 64 rows, registers 40.9.)
+// Without a saved buffer and a gain the tiles normalise their rows themselves (norm_in_gate_up), and they are no wider than
+// the chip needs (gate_up_cols):  C = 2048, I = 7168, registers / tiles: 17 rows 34.6 / 33.9, 32 rows 35.9 / 34.5, with a
+// gain 36.2 / 36.6, 33 rows with a gain 40.1 / 37.1;  C = 3072, I = 7168: 17 rows 45.4 / 42.1, with a gain 46.2 / 43.0;
+// C = 1024, I = 3584: 32 rows 15.2 / 19.3, 64 rows 20.4 / 22.6.
 constexpr int64_t kFewRowsMax = 64;
 inline bool few_rows_gate_up(int64_t rows, int64_t C, int64_t I, bool has_saved, bool has_gain) {
     const int64_t weight = C * I, limit = (int64_t)40 * 2048 * 7168;
     if (rows > kFewRowsMax || weight > (int64_t)24 << 20 || rows * weight > (has_saved ? limit / 2 : limit)) return false;
-    return C <= (rows <= 16 ? 4096 : rows <= 32 ? (has_saved ? 2048 : 3072) : (has_saved || !has_gain ? 1024 : 2048));
+    return C <= (rows <= 16 ? 4096 : rows <= 32 && (has_saved || has_gain) ? 2048 : 1536);
 }
 inline bool few_rows_down(int64_t rows, int64_t C, int64_t I, bool has_saved, int ncu) {
     if (rows > kFewRowsMax || rows * C * I > (int64_t)1 << (has_saved ? 29 : 30)) return false;
@@ -153,6 +155,19 @@ inline int gate_up_splits(int64_t C, int64_t I, int ncu) {
     return best;
 }
 
+// The columns of gate (and of up) that a tile takes where K is whole: 64, or fewer where these need no more rounds of the chip.
+// A slab of such a tile is fewer bytes of weights, and CUs that would be idle take part; 64 columns of I = 14336 are 224 tiles, 56
+// are 256.  Layer forward, us, 64 columns / these:  C = 4096, I = 14336 (56): 8 rows 68.2 / 66.9, 184 rows 106.5 / 105.6;
+// C = 3072, I = 10752 (48): 64 rows 57.0 / 53.6, 184 rows 81.8 / 79.8;  C = 2048, I = 7168 (32): 64 rows 39.7 / 36.2, 184
+// rows 56.1 / 54.2;  C = 1024, I = 3584 (16): 250 rows 38.0 / 36.7.  One more round than needed: 184 rows, C = 4096, 48
+// columns 141.5.
+inline int gate_up_cols(int64_t rows, int64_t I, int ncu) {
+    const int64_t tiles_m = std::max(mid_row_tiles(rows), 1), room = (tiles_m * ((I + 63) / 64) + ncu - 1) / ncu * ncu;
+    int cols = 16;
+    while (cols < 64 && tiles_m * ((I + cols - 1) / cols) > room) cols += 8;
+    return cols;
+}
+
 // Without a saved buffer nothing but the gate/up GEMM reads the normalised rows, and 1 / rms can be applied to its sums: the
 // squares of a row are added beside the product, the gain is multiplied into the rows.  It saves a launch, and the rounding of
 // the normalised rows: error of a layer against 64 bits 2.3e-3 instead of 3.5e-3.  On registers (row-major rows then) it
@@ -171,17 +186,18 @@ enum FwdKernel { FWD_FEW, FWD_MID, FWD_CORE };           // fewrows.hip, midrows
 struct ForwardPlan {
     FwdKernel gate_up, down;
     bool norm_in_gate_up;                                // the rows are normalised by the gate/up GEMM, not before it
-    int gate_up_splits;                                  // FWD_MID
+    int gate_up_splits, gate_up_cols;                    // FWD_MID
     KPartition k_down;                                   // FWD_MID: plain split; FWD_CORE: as choose_k_partition; FWD_FEW: none
 };
 // most fp32 slabs the down GEMM of `rows` rows may write (fwd_ws has room for them)
 inline int max_down_splits(int64_t rows) { return rows <= 256 ? kMaxSplitsNarrow : kMaxSplits; }
 inline ForwardPlan plan_forward(int64_t rows, int64_t C, int64_t I, bool has_saved, bool balanced, int ncu,
                                 bool has_gain = false) {
-    ForwardPlan p{FWD_CORE, FWD_CORE, false, 1, KPartition{1, 0}};
+    ForwardPlan p{FWD_CORE, FWD_CORE, false, 1, 64, KPartition{1, 0}};
     if (!balanced && mid_rows(rows, C, I, ncu)) {
         p.gate_up = few_rows_gate_up(rows, C, I, has_saved, has_gain) ? FWD_FEW : FWD_MID;
         if (p.gate_up == FWD_MID && rows <= 256) p.gate_up_splits = gate_up_splits(C, I, ncu);
+        if (p.gate_up_splits == 1) p.gate_up_cols = gate_up_cols(rows, I, ncu);
         p.norm_in_gate_up = !has_saved && p.gate_up_splits == 1 && norm_in_gate_up(rows, C, has_gain, p.gate_up == FWD_FEW);
         p.down = few_rows_down(rows, C, I, has_saved, ncu) ? FWD_FEW : mid_rows_down(rows, C, ncu) ? FWD_MID : FWD_CORE;
     }

@@ -64,7 +64,7 @@ __global__ __launch_bounds__(SWIGLU_THREADS) void swiglu_reduce_kernel(MidRowsAr
 
 template <int MT, bool GATE_UP, bool NORM = false>
 static hipError_t launch_mid(const MidRowsArgs& a, hipStream_t s) {
-    const int tiles_m = (a.rows + 16 * MT - 1) / (16 * MT), cols = GATE_UP ? SLAB_B_ROWS / 2 : SLAB_B_ROWS;
+    const int tiles_m = (a.rows + 16 * MT - 1) / (16 * MT), cols = GATE_UP ? a.cols : SLAB_B_ROWS;
     const int tiles_n = (a.N + cols - 1) / cols;
     hipLaunchKernelGGL((mid_rows_kernel<MT, GATE_UP, NORM>), dim3((unsigned)(tiles_m * tiles_n * a.splits)), dim3(SLAB_THREADS),
                        kSlabLds<16 * MT>, s, a);
@@ -100,12 +100,12 @@ hipError_t mid_rows_init() {
 }
 
 MidRowsArgs mid_rows_gate_up_args(const bf16_t* xn, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_gate,
-                                  const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major_h) {
+                                  const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major_h, int cols) {
     MidRowsArgs a{};
     a.rows = rows; a.r_dev = r_dev; a.N = I; a.K = C;
     a.A = xn; a.a_bytes = (uint32_t)((int64_t)rows * C * 2);
     a.B0 = w_gate; a.B1 = w_up; a.b_bytes = (uint32_t)((int64_t)I * C * 2);
-    a.splits = 1; a.H = H; a.G = G; a.U = U;
+    a.splits = 1; a.cols = cols; a.H = H; a.G = G; a.U = U;
     a.h_row = chunk_major_h ? 16u : (uint32_t)I * 2; a.h_chunk = chunk_major_h ? (uint32_t)rows * 16 : 16u;
     return a;
 }
@@ -121,8 +121,8 @@ MidRowsArgs mid_rows_down_args(const bf16_t* H, int rows, const int32_t* r_dev, 
 
 hipError_t launch_mid_rows_gate_up(const bf16_t* xn, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_gate,
                                    const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major_h, int splits,
-                                   float* partial, const RowNorm* norm, hipStream_t s) {
-    MidRowsArgs a = mid_rows_gate_up_args(xn, rows, r_dev, C, I, w_gate, w_up, H, G, U, chunk_major_h);
+                                   int cols, float* partial, const RowNorm* norm, hipStream_t s) {
+    MidRowsArgs a = mid_rows_gate_up_args(xn, rows, r_dev, C, I, w_gate, w_up, H, G, U, chunk_major_h, cols);
     a.splits = splits; a.partial = partial;
     if (norm != nullptr) {                    // one row tile; a part of K would not know a row's norm
         if (rows > kNormInMidRows || splits > 1 || norm->gain != nullptr) return hipErrorInvalidValue;

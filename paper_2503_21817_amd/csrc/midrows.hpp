@@ -1,8 +1,8 @@
 // The two forward GEMMs for up to 256 retained rows (decode batches, prefill of an image, small training batches), and
 // for more rows of a narrow layer, in several row tiles.
 //
-// Bound by streaming the weights from HBM.  A tile is ALL rows (16 * MT of them) times 128 weight rows, so that every
-// weight byte goes to one CU only and the tiles are many (I / 64 for gate/up; C / 128 with K split for down, whose
+// Bound by streaming the weights from HBM.  A tile is ALL rows (16 * MT of them) times up to 128 weight rows, so that every
+// weight byte goes to one CU only and the tiles are many (I / 64 or more for gate/up, see gate_up_cols; C / 128 with K split for down, whose
 // fp32 slabs a reducing kernel adds; gate/up splits K as well where I is so small that most CUs would have no tile).
 // What limits a CU is the bytes its address unit takes, weights and activations together: about 9 TB/s over the chip
 // here.  Hence both operands go to LDS by direct loads of whole 128-byte lines
@@ -19,7 +19,8 @@
 //
 // NORM: gate/up of up to 64 rows on the rows as they are in the hidden states, normalised beside the product (layout.hpp,
 // norm_in_gate_up).  A fragment's squares are 16 vector operations of one of the four wavefronts that read it; with all
-// four adding all fragments and a gain multiplied in, the loop becomes bound by them (C = 4096, 8 rows: 92 instead of 67 us a layer).
+// four adding all fragments and a gain multiplied in, the loop becomes bound by them (C = 4096, 8 rows: 92 instead of 67 us a layer),
+// and so it does on more rows (184: 122 instead of 106).
 #pragma once
 
 #include "kernels.hpp"
@@ -35,6 +36,7 @@ struct MidRowsArgs {
     const bf16_t* A; uint32_t a_bytes;        // [rows][K]
     const bf16_t* B0; const bf16_t* B1; uint32_t b_bytes;   // [N][K]; gate/up: W_gate, W_up
     int splits;
+    int cols;                                 // gate/up: columns of a tile (gate_up_cols)
     // gate/up: 16-byte chunk c (8 columns) of row r of H at byte r * h_row + c * h_chunk; G, U [rows][N], optional
     bf16_t* H; uint32_t h_row, h_chunk; bf16_t* G; bf16_t* U;
     float* partial;                           // down: [splits][rows][N]; gate/up with splits > 1: [splits][rows][2][N]
@@ -42,9 +44,9 @@ struct MidRowsArgs {
     const int32_t* idx; float eps;
 };
 
-// chunk_major_h: H is [N / 8][rows][8]; splits 1, whole rows
+// chunk_major_h: H is [N / 8][rows][8], splits 1, whole rows
 MidRowsArgs mid_rows_gate_up_args(const bf16_t* xn, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_gate,
-                                  const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major_h);
+                                  const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major_h, int cols);
 MidRowsArgs mid_rows_down_args(const bf16_t* H, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_down, int splits,
                                float* partial);
 
@@ -59,11 +61,11 @@ __device__ __forceinline__ void mid_rows_tile(const MidRowsArgs& P, const int bl
     const int R = effective_rows(P.rows, P.r_dev);
     if (R <= 0) return;                       // uniform
     // row tile by row tile, in each the column tiles, in each the K splits
-    constexpr int COLS = GATE_UP ? SLAB_B_ROWS / 2 : SLAB_B_ROWS;
-    const int per_m = (P.N + COLS - 1) / COLS * P.splits;
+    const int cols = GATE_UP ? P.cols : SLAB_B_ROWS;
+    const int per_m = (P.N + cols - 1) / cols * P.splits;
     const int tm = block / per_m, b = block - tm * per_m;
     const int z = b % P.splits;
-    const int m0 = tm * 16 * MT, n0 = b / P.splits * COLS;
+    const int m0 = tm * 16 * MT, n0 = b / P.splits * cols;
     if (m0 >= R) return;                      // uniform: the bound of a device count
     const int r16 = lane & 15, kq = lane >> 4;
 
@@ -83,7 +85,7 @@ __device__ __forceinline__ void mid_rows_tile(const MidRowsArgs& P, const int bl
         const int q = l < NLA ? wave * NLA + l : wave * 2 + (l - NLA);
         const int row = 8 * q + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
         int gr = l < NLA ? m0 + row : n0 + (GATE_UP ? row & 63 : row);
-        const bool in = l < NLA ? gr < R : gr < P.N;
+        const bool in = l < NLA ? gr < R : gr < P.N && (!GATE_UP || (row & 63) < cols);
         if (NORM && l < NLA && in) gr = P.idx[gr];
         goff[l] = in ? (uint32_t)(((int64_t)gr * P.K + c * 8) * 2) : kOobOffset;
     }
@@ -108,7 +110,7 @@ __device__ __forceinline__ void mid_rows_tile(const MidRowsArgs& P, const int bl
         if (row >= R) continue;
         if (GATE_UP) {
             const int n = n0 + wn * 16 + 4 * kq;
-            if (n >= P.N) continue;
+            if (n >= P.N || n >= n0 + cols) continue;
             f32x4 g = acc[m][0], u = acc[m][1];
             if (NORM) {
                 g *= rstd;

@@ -680,6 +680,27 @@ def test_tiles_of_all_rows(R, C, I, r_host):
         assert max_slice_rel_l2(f64_of(sv[k]), fo[k], axis=1) < REL_L2_TOL, k
 
 
+@pytest.mark.parametrize("R,C,I", [(70, 136, 24), (66, 264, 3592), (130, 264, 5000), (200, 264, 9000), (256, 136, 14000), (48, 4104, 14344),
+                                   (65, 136, 16392), (65, 136, 28680), (300, 136, 3592), (520, 136, 2184)])
+@pytest.mark.parametrize("saved", [False, True], ids=["inference", "training"])
+def test_gate_up_tile_columns(R, C, I, saved):
+    """On 256 compute units: tiles of 16, 24, 40, 56 and 64 columns that one round of them holds, of 40 and 56 in two, of
+    32 and 32 in two and three row tiles; the last tile of every row is cut off.  Every column of H is checked on its own."""
+    from helpers import max_slice_rel_l2
+    w = W.small(C=C, I=I, visual=(R + 23,), text=(1,), keep=(R - 1,), seed=6400 + R, name=f"columns-{I}")
+    p = Problem(w, unit_gain=True, with_gain_tensor=False)
+    fo = O.skipffn_forward(p.hidden, p.mask, p.wg, p.wu, p.wd, None, w.eps, no_residual=True)
+    idx, sk = fo["idx"], p.mask != 0
+    out, bufs = gpu_forward(p, saved=saved, flags=B.FLAG_NO_RESIDUAL)
+    got = bits_of(out)
+    assert np.array_equal(got[sk], p.hidden[sk])
+    assert max_slice_rel_l2(O.bf16_bits_to_f64(got[idx]), O.bf16_bits_to_f64(fo["out_bits"][idx]), axis=1) < REL_L2_TOL
+    if saved:
+        sv = bufs.saved_views(R)
+        for k in ("G", "U", "H"):
+            assert max_slice_rel_l2(f64_of(sv[k]), fo[k], axis=0) < REL_L2_TOL, k
+
+
 @pytest.mark.parametrize("R", [1, 9, 16, 17])
 @pytest.mark.parametrize("C,I", [(2056, 12296), (4104, 8200)], ids=["tiles", "registers-for-down"])
 def test_decode_of_a_wide_layer(R, C, I):
