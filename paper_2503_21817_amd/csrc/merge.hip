@@ -28,16 +28,18 @@ constexpr int MG_THREADS = 256;
 
 // ---- Xn = X / |X| (a zero row stays zero), and the sum of the MERGE_CHUNK rows of a workgroup of Xn ----
 // Bound by latency and HBM: a wavefront holds its two rows in registers, V chunks of each a lane, all loads in flight at once; its
-// sum of them meets those of the other three in LDS.  V = 0: rows of more than 4096 columns, read again for the second step.
+// sum of them meets those of the other three in LDS.  V = 0: rows of more than 4096 columns, read again for the second step, 4096
+// columns at a time: 64 KB of LDS whatever the width.
 // 9.3 us at 8192 rows of 1024 columns, 11.5 at 2304 of 4096 (16 rows a workgroup, read twice: 14.2 and 20.4).
 __device__ __forceinline__ int64_t merge_part_row(const SegTable& st, int set, int chunk) {
     return (st.off[set] - st.off[0]) / MERGE_CHUNK + set + chunk;           // the sets' rows of `part` do not overlap
 }
 static_assert(MERGE_CHUNK == MG_THREADS / 64 * 2, "two rows a wavefront");
+constexpr int MG_WIDE = 4096;
 template <int V>
 __global__ __launch_bounds__(MG_THREADS) void merge_normalize_kernel(const bf16_t* __restrict__ x, SegTable st, int C,
                                                                      bf16_t* __restrict__ xn, float* __restrict__ part) {
-    extern __shared__ __align__(16) float sums[];        // [4][C]
+    extern __shared__ __align__(16) float sums[];        // [4][C], at most MG_WIDE columns
     const int set = blockIdx.y, n = st.off[set + 1] - st.off[set];
     if ((int)blockIdx.x * MERGE_CHUNK >= n) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, chunks = C >> 3;
@@ -80,7 +82,8 @@ __global__ __launch_bounds__(MG_THREADS) void merge_normalize_kernel(const bf16_
         const float v = wave_sum(ss[q]);
         inv[q] = v > 0.0f ? 1.0f / sqrtf(v) : 0.0f;
     }
-    auto emit = [&](int c, const u32x4& a, const u32x4& b) {
+    const int width = V > 0 || C < MG_WIDE ? C : MG_WIDE;
+    auto emit = [&](int c, int c0, const u32x4& a, const u32x4& b) {
         float sum[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) sum[j] = 0.0f;
@@ -97,22 +100,32 @@ __global__ __launch_bounds__(MG_THREADS) void merge_normalize_kernel(const bf16_
 #pragma unroll
             for (int j = 0; j < 8; ++j) sum[j] += f[j];
         }
-        f32x4* to = reinterpret_cast<f32x4*>(sums + (int64_t)wave * C + c * 8);
+        f32x4* to = reinterpret_cast<f32x4*>(sums + wave * width + (c - c0) * 8);
         to[0] = f32x4{sum[0], sum[1], sum[2], sum[3]};
         to[1] = f32x4{sum[4], sum[5], sum[6], sum[7]};
+    };
+    f32x4* out = reinterpret_cast<f32x4*>(part + merge_part_row(st, set, (int)blockIdx.x) * C);
+    const f32x4* in = reinterpret_cast<const f32x4*>(sums);
+    const int quads = width >> 2;
+    auto write_sum = [&](int first, int count) {         // quads of columns
+        for (int c = tid; c < count; c += MG_THREADS)
+            out[first + c] = (in[c] + in[c + quads]) + (in[c + 2 * quads] + in[c + 3 * quads]);
     };
     if constexpr (V > 0) {
 #pragma unroll
         for (int v = 0; v < V; ++v)
-            if (lane + 64 * v < chunks) emit(lane + 64 * v, held[0][v], held[1][v]);
+            if (lane + 64 * v < chunks) emit(lane + 64 * v, 0, held[0][v], held[1][v]);
+        __syncthreads();
+        write_sum(0, quads);
     } else {
-        for (int c = lane; c < chunks; c += 64) emit(c, src[0][c], src[1][c]);
+        for (int c0 = 0; c0 < chunks; c0 += MG_WIDE / 8) {
+            const int c1 = c0 + MG_WIDE / 8 < chunks ? c0 + MG_WIDE / 8 : chunks;
+            if (c0 > 0) __syncthreads();                 // the piece before has been added
+            for (int c = c0 + lane; c < c1; c += 64) emit(c, c0, src[0][c], src[1][c]);
+            __syncthreads();
+            write_sum(c0 * 2, (c1 - c0) * 2);
+        }
     }
-    __syncthreads();
-    f32x4* out = reinterpret_cast<f32x4*>(part + merge_part_row(st, set, (int)blockIdx.x) * C);
-    const f32x4* in = reinterpret_cast<const f32x4*>(sums);
-    const int quads = C >> 2;
-    for (int c = tid; c < quads; c += MG_THREADS) out[c] = (in[c] + in[c + quads]) + (in[c + 2 * quads] + in[c + 3 * quads]);
 }
 
 // ---- s_set = the sum of the set's partial rows ------------------------------------------------------
@@ -458,7 +471,7 @@ hipError_t launch_merge_group(const bf16_t* x, const SegTable& st, int n_max, in
     if (n_max > 0) {
         const int chunks = C >> 3, parts = (n_max + MERGE_CHUNK - 1) / MERGE_CHUNK;
         const dim3 rows((unsigned)parts, sets), threads(MG_THREADS);
-        const size_t lds = (size_t)C * 16;
+        const size_t lds = (size_t)std::min(C, MG_WIDE) * 16;
         if (chunks <= 64) hipLaunchKernelGGL(merge_normalize_kernel<1>, rows, threads, lds, s, x, st, C, ws.xn, ws.part);
         else if (chunks <= 128) hipLaunchKernelGGL(merge_normalize_kernel<2>, rows, threads, lds, s, x, st, C, ws.xn, ws.part);
         else if (chunks <= 256) hipLaunchKernelGGL(merge_normalize_kernel<4>, rows, threads, lds, s, x, st, C, ws.xn, ws.part);

@@ -100,11 +100,11 @@ def test_similarity_tiles_and_their_mirror_images(lens, C, k):
 
 
 @pytest.mark.parametrize("lens,C,k", [((129,) * 70, 64, 64), ((128, 193), 72, 127), ((700,), 4104, 129), ((1024,) * 8, 40, 256),
-                                      ((1500,) * 6, 264, 700), ((513, 1, 9), 1544, 8)],
-                         ids=["more-sets-than-a-launch", "one-dropped", "wide-rows", "64x128", "128x128", "ragged-last-launch"])
+                                      ((1500,) * 6, 264, 700), ((513, 1, 9), 1544, 8), ((70, 9), 12296, 20)],
+                         ids=["more-sets-than-a-launch", "one-dropped", "wide-rows", "64x128", "128x128", "ragged-last-launch", "rows-past-lds"])
 def test_tiles_of_dropped_and_kept_rows(lens, C, k):
     """Every tile of the target kernel, dropped and kept rows that end just inside and just past one, rows too wide for the
-    registers of the normalising kernel, sets of several launches; averages against pairs formed in 64 bits."""
+    registers of the normalising kernel, and too wide for LDS, sets of several launches; averages against pairs formed in 64 bits."""
     rng = np.random.default_rng(sum(lens) + C + 2)
     xb = O.f64_to_bf16_bits(rng.standard_normal((sum(lens), C)) + 0.5 * rng.standard_normal((1, C)))
     check(xb, [0] + np.cumsum(lens).tolist(), k)
