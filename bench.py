@@ -123,6 +123,7 @@ def kernel_work(name, R, T, C, I, dw_bytes):
         "gemm_dh_swiglu_bwd+dw_down": ("mfma", 4 * R * C * I),    # two GEMMs in one grid
         "gemm_dw_gate_up": ("mfma", 4 * R * C * I),               # dW_gate and dW_up in one grid
         "gemm_dxn": ("mfma", 4 * R * C * I),
+        "gemm_dxn+dw_gate_up": ("mfma", 8 * R * C * I),           # few rows: these three in one grid
         "compact": ("hbm", T + 4 * R),
         "gather_rmsnorm": ("hbm", 2 * rc * 2 + 4 * R),
         "resid_scatter": ("hbm", 2 * rc * 2),

@@ -102,7 +102,8 @@ const char* kernel_class_name(int kc) {
     static const char* names[KC_COUNT] = {
         "compact", "gather_rmsnorm", "gemm_gate_up_swiglu", "gemm_down", "resid_scatter",
         "passthrough_copy", "gather_rows", "gemm_dh_swiglu_bwd+dw_down", "gemm_dw_gate_up",
-        "gemm_dxn", "rmsnorm_bwd_scatter", "fill_zero", "kv_compact", "summary_fwd", "summary_bwd", "select_retained", "token_merge"};
+        "gemm_dxn", "rmsnorm_bwd_scatter", "fill_zero", "kv_compact", "summary_fwd", "summary_bwd", "select_retained", "token_merge",
+        "gemm_dxn+dw_gate_up"};
     return (kc >= 0 && kc < KC_COUNT) ? names[kc] : "?";
 }
 
@@ -494,41 +495,39 @@ int skipffn_backward(int64_t T, int64_t C, int64_t I, float eps, const void* gra
     }
     // dW_gate [I, C] = dG^T * xn ; dW_up [I, C] = dU^T * xn : one launch, two problems sharing
     // the B operand, every operand in its K-contiguous (R-contiguous) copy
-    {
-        GemmArgs a{};
-        a.M = (int)I; a.N = (int)C; a.K = (int)Rb; a.k_dev = r_dev;
-        a.A0 = dGT; a.A1 = dUT; a.lda = ldT; a.a_bytes = (uint32_t)(I * (int64_t)ldT * 2);
-        a.B0 = xnT; a.ldb = ldT; a.b_bytes = (uint32_t)(C * (int64_t)ldT * 2);
-        a.pairs = 1; a.splits = 1; a.batch = 2;
-        a.out0 = dw_gate; a.out1 = dw_up; a.ldo = (int)C; a.out_f32 = f32; a.accumulate = accum; a.ncu = num_cus();
+    GemmArgs w{};
+    w.M = (int)I; w.N = (int)C; w.K = (int)Rb; w.k_dev = r_dev;
+    w.A0 = dGT; w.A1 = dUT; w.lda = ldT; w.a_bytes = (uint32_t)(I * (int64_t)ldT * 2);
+    w.B0 = xnT; w.ldb = ldT; w.b_bytes = (uint32_t)(C * (int64_t)ldT * 2);
+    w.pairs = 1; w.splits = 1; w.batch = 2;
+    w.out0 = dw_gate; w.out1 = dw_up; w.ldo = (int)C; w.out_f32 = f32; w.accumulate = accum; w.ncu = num_cus();
+    // dxn = dG * W_gate + dU * W_up  (K runs over both pairs), fp32 split-K slabs
+    GemmArgs x{};
+    x.M = (int)Rb; x.N = (int)C; x.K = (int)I; x.m_dev = r_dev;
+    x.A0 = dG; x.A1 = dU; x.lda = (int)I; x.a_bytes = (uint32_t)(Rb * I * 2);
+    x.B0 = static_cast<const bf16_t*>(w_gate); x.B1 = static_cast<const bf16_t*>(w_up);
+    x.ldb = (int)C; x.b_bytes = (uint32_t)(I * C * 2);
+    x.pairs = 2;
+    x.partial = partial;
+    const DxnPlan plan = plan_dxn(Rb, C, I, (f32 ? 4 : 2) * (accum ? 2 : 1), (flags & SKIPFFN_FLAG_BALANCED_SPLIT) != 0, r_dev != nullptr,
+                                  num_cus());
+    x.splits = plan.k.splits;
+    const PartialLayout pl{plan.k.splits, plan.k.sk_nbg, 2 * (int)((I + BK - 1) / BK)};
+    if (plan.dw_workgroups > 0) {
+        profile_mark_begin(KC_GEMM_DXN_DW, s);
+        e = launch_gemm_dxn_dw(x, w, plan.n0, plan.dw_workgroups, s);
+        profile_mark_end(KC_GEMM_DXN_DW, s);
+    } else {
         profile_mark_begin(KC_GEMM_DW_GATE_UP, s);
-        e = launch_gemm(true, EPI_STORE, a, s);
+        e = launch_gemm(true, EPI_STORE, w, s);
         profile_mark_end(KC_GEMM_DW_GATE_UP, s);
         if (e != hipSuccess) return hip_fail(e);
-    }
-    // dxn = dG * W_gate + dU * W_up  (K runs over both pairs), fp32 split-K slabs.  (Sharing a
-    // grid with the dW GEMMs above was measured slower: both are already well balanced.)
-    PartialLayout pl{1, 0, 0};
-    {
-        GemmArgs a{};
-        a.M = (int)Rb; a.N = (int)C; a.K = (int)I; a.m_dev = r_dev;
-        a.A0 = dG; a.A1 = dU; a.lda = (int)I; a.a_bytes = (uint32_t)(Rb * I * 2);
-        a.B0 = static_cast<const bf16_t*>(w_gate); a.B1 = static_cast<const bf16_t*>(w_up);
-        a.ldb = (int)C; a.b_bytes = (uint32_t)(I * C * 2);
-        a.pairs = 2;
-        const int tiles_m = (int)((Rb + BM - 1) / BM), tiles_n = (int)((C + BN - 1) / BN);
-        const int ktiles = 2 * (int)((I + BK - 1) / BK);
-        const KPartition kp = choose_k_partition(tiles_m, tiles_n, ktiles, (flags & SKIPFFN_FLAG_BALANCED_SPLIT) != 0,
-                                                 num_cus());
-        a.splits = kp.splits;
-        pl = PartialLayout{kp.splits, kp.sk_nbg, ktiles};
-        a.partial = partial;
         profile_mark_begin(KC_GEMM_DXN, s);
-        e = kp.sk_nbg > 0 ? launch_gemm_streamk(false, a, kp.sk_nbg, s)
-                          : launch_gemm(false, EPI_PARTIAL, a, s);
+        e = plan.k.sk_nbg > 0 ? launch_gemm_streamk(false, x, plan.k.sk_nbg, s)
+                              : launch_gemm(false, EPI_PARTIAL, x, s);
         profile_mark_end(KC_GEMM_DXN, s);
-        if (e != hipSuccess) return hip_fail(e);
     }
+    if (e != hipSuccess) return hip_fail(e);
     // RMSNorm backward + residual gradient, scattered to the retained rows
     e = launch_rmsnorm_bwd_scatter(partial, pl, (int)Rb, r_dev, (int)C, xrows, rstd,
                                    static_cast<const bf16_t*>(rms_gain), dY, idx,

@@ -29,6 +29,7 @@ enum KernelClass : int {
     KC_SUMMARY_BWD,
     KC_SELECT,
     KC_MERGE,
+    KC_GEMM_DXN_DW,
     KC_COUNT
 };
 const char* kernel_class_name(int kc);
@@ -162,6 +163,8 @@ hipError_t gemm_init();   // raises the dynamic-LDS limit of every instantiation
 hipError_t launch_gemm(bool b_kc, int epi, GemmArgs& args, hipStream_t s);
 // two independent GEMMs in one grid, the first dispatched first: SwiGLU backward (dH -> dG, dU), and store (dW_down = dY^T * H)
 hipError_t launch_gemm_dh_dw_down(GemmArgs& dh, GemmArgs& dw, hipStream_t s);
+// dXn (fp32 slabs, K cut evenly) and dW_gate, dW_up in one grid, see plan_dxn
+hipError_t launch_gemm_dxn_dw(GemmArgs& dxn, GemmArgs& dw, int n0, int dw_workgroups, hipStream_t s);
 // balanced split-K GEMM into fp32 partial slabs (EPI_PARTIAL): nbg workgroups per n-tile group
 hipError_t launch_gemm_streamk(bool b_kc, GemmArgs& args, int nbg, hipStream_t s);
 

@@ -38,7 +38,7 @@ constexpr int kMaxSplitsNarrow = 16;     // up to 256 rows: small fp32 slabs, an
 //                              workgroup first runs whole tiles of its own; the rest is split)
 // Both GEMMs are planned in 256-row tiles.  The down GEMM then lowers them where K is not balanced (stream_rows_plan).
 struct KPartition { int splits; int sk_nbg; };
-inline KPartition choose_k_partition(int tiles_m, int tiles_n, int ktiles, bool force_balanced, int ncu) {
+inline KPartition choose_k_partition(int tiles_m, int tiles_n, int ktiles, bool force_balanced, int ncu, double* cost_of = nullptr) {
     const int tiles = tiles_m * tiles_n;
     KPartition best{1, 0};
     double best_cost = 1e30;
@@ -65,7 +65,44 @@ inline KPartition choose_k_partition(int tiles_m, int tiles_n, int ktiles, bool 
             if (cost < best_cost - 1e-9) { best_cost = cost; best = KPartition{1, nbg}; }
         }
     }
+    if (cost_of != nullptr) *cost_of = best_cost;
     return best;
+}
+
+// dXn and dW_gate, dW_up both wait for dG and dU only.  Up to some hundred rows they share a launch: dXn, cut into fewer and
+// longer parts, on the first n0 workgroups (a multiple of 8), lists of dW's tiles on dw_workgroups others, all on the chip at
+// once.  The ends of dXn's parts and the stores of dW then fall into each other's K slabs, and dXn leaves fewer fp32 slabs.
+// dw_workgroups = 0: two launches, each with the chip to itself, which many rows of a wide layer fill as well.  Costs in slabs of
+// dXn; a slab of dW, alone or not, takes 1.15 of one, the end of a tile what its stores (and loads, where dW is added to) take:
+// dw_bytes an element.  Backward of a layer, us, two launches / one (parts of dXn), bf16 dW:  C = 4096, I = 14336: 32 rows 226 / 197
+// (8), 184 rows 277 / 248 (7), 256 rows 304 / 274 (6), 368 rows 326 / 314 (4), 600 rows 443 / 451 (3);  C = 3072, I = 10752:
+// 184 rows 210 / 184 (8), 368 rows 225 / 210 (5), 640 rows 272 / 278 (4);  C = 2048, I = 7168: 184 rows 123 / 102 (8), 640 rows
+// 167 / 150 (6), 1024 rows 209 / 196 (4), 1472 rows 295 / 277 (3);  C = 1024, I = 3584: 64 rows 69 / 59 (8), 368 rows 90 / 75
+// (8), 2944 rows 198 / 165 (3);  fp32 dW: C = 4096, I = 9952: 763 rows 456 / 478 (2).  With less than 8 % to gain by these costs
+// it measured from 6 % faster to 5 % slower, and is left.
+struct DxnPlan { KPartition k; int n0, dw_workgroups; };
+inline DxnPlan plan_dxn(int64_t rows, int64_t C, int64_t I, int dw_bytes, bool balanced, bool count_on_device, int ncu) {
+    const int tiles_m = (int)((rows + BM - 1) / BM), tiles_n = (int)((C + BN - 1) / BN);
+    const int tiles = tiles_m * tiles_n, ktiles = 2 * (int)((I + BK - 1) / BK);
+    double cost = 0.0;
+    DxnPlan p{choose_k_partition(tiles_m, tiles_n, ktiles, balanced, ncu, &cost), 0, 0};
+    if (balanced || tiles <= 0) return p;
+    const int dw_tiles = (int)((I + BM - 1) / BM) * tiles_n * 2, dw_slabs = (int)((rows + BK - 1) / BK);
+    const int whole = (dw_tiles + 7) / 8 * 8;                // a workgroup for every tile
+    auto dw_cost = [&](int workgroups) {
+        return 1.15 * ((dw_tiles + workgroups - 1) / workgroups * (dw_slabs + 1.0 + 0.75 * dw_bytes) + 8.0);
+    };
+    double best = 0.92 * (cost + dw_cost(std::min(whole, ncu)));
+    for (int s = 1; s <= kMaxSplits; ++s) {
+        const int per = (ktiles + s - 1) / s, n0 = (tiles * s + 7) / 8 * 8;
+        if ((s > 1 && per < 4) || n0 > ncu - 8) break;
+        if ((s - 1) * per >= ktiles) continue;
+        const int n1 = std::min((ncu - n0) / 8 * 8, whole);
+        if (count_on_device && n1 < whole) continue;         // the rows there are may leave dXn's workgroups without work
+        const double c = std::max(per + (s > 1 ? 16.0 : 8.0) + 0.04 * s * tiles, dw_cost(n1));
+        if (c < best - 1e-9) { best = c; p = DxnPlan{KPartition{s, 0}, n0, n1}; }
+    }
+    return p;
 }
 
 // Up to 256 rows the forward GEMMs are bound by streaming the 6 * C * I bytes of weights.  They run on tiles of ALL

@@ -163,6 +163,27 @@ int main() {
                         if (const char* what = check_plan(R, C, I, variant & 1, variant & 2, ncu)) return fail(what, R, C, I, ncu);
                         ++cases;
                     }
+    // dXn beside dW_gate and dW_up: all workgroups on the chip at once, every part of K with slabs, no more of them than the
+    // workspace holds
+    for (int ncu : ncus)
+        for (long C : widths)
+            for (long I : widths)
+                for (long R = 1; R <= 16384; R += R < 300 ? 1 : R / 16)
+                    for (int variant = 0; variant < 16; ++variant) {
+                        const int dw_bytes = 2 << (variant & 1) << (variant >> 1 & 1);
+                        const bool forced = variant & 4, on_device = variant & 8;
+                        const DxnPlan p = plan_dxn(R, C, I, dw_bytes, forced, on_device, ncu);
+                        const long tiles = (R + BM - 1) / BM * ((C + BN - 1) / BN), dw = (I + BM - 1) / BM * ((C + BN - 1) / BN) * 2;
+                        const int ktiles = 2 * (int)((I + BK - 1) / BK), s = p.k.splits;
+                        if (s < 1 || s > kMaxSplits || (s - 1) * ((ktiles + s - 1) / s) >= ktiles) return fail("split of dXn", R, C, I, ncu);
+                        if (p.dw_workgroups > 0) {
+                            if (forced || p.k.sk_nbg != 0) return fail("the balanced split shares no launch", R, C, I, ncu);
+                            if (p.n0 % 8 || p.n0 < tiles * s || p.dw_workgroups % 8 || p.n0 + p.dw_workgroups > ncu)
+                                return fail("workgroups of dXn and dW", R, C, I, ncu);
+                            if (on_device && p.dw_workgroups < dw) return fail("lists of dW by the bound of the rows", R, C, I, ncu);
+                        }
+                        ++cases;
+                    }
     printf("ok %ld\n", cases);
     return 0;
 }

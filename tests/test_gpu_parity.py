@@ -868,6 +868,36 @@ def test_weight_gradients_of_more_tiles_than_compute_units(R, flags):
             assert np.all(err < REL_L2_TOL * (size + 4 * np.sqrt(np.mean(size ** 2)))), (k, axis)
 
 
+@pytest.mark.parametrize("R,C,I", [(1, 136, 24), (33, 264, 688), (65, 1032, 3592), (300, 1032, 2056), (200, 2056, 5128), (600, 2056, 3080)],
+                         ids=["one-tile", "parts-of-a-few-slabs", "8-parts", "two-tile-rows", "two-tiles-of-dw-each", "three-tile-rows"])
+@pytest.mark.parametrize("flags", [0, B.FLAG_DW_FP32 | B.FLAG_DW_ACCUMULATE], ids=["bf16", "fp32-add"])
+@pytest.mark.parametrize("r_host", [True, False], ids=["R-host", "R-device"])
+def test_input_gradient_beside_the_weight_gradients(R, C, I, flags, r_host):
+    """dXn and dW_gate, dW_up in one launch: a workgroup for each tile of dW, lists of several (R on the host), K of dXn whole and in
+    up to 8 parts, cut-off tiles at every edge, with rows that are skipped.  Against the oracle, and against the
+    launches of their own that the balanced split takes: dW bit for bit."""
+    print(f"dxn beside dw R={R} C={C} I={I} flags={flags} r_host={r_host}", flush=True)
+    w = W.small(C=C, I=I, visual=(R + 23,), text=(1,), keep=(R - 1,), seed=7700 + R, name=f"dxn-dw-{R}")
+    assert w.R == R
+    p = Problem(w)
+    bo = O.skipffn_backward(p.hidden, p.mask, p.wg, p.wu, p.wd, p.grad, None, w.eps)
+    _, bufs = gpu_forward(p, R_host=r_host)
+    dt = torch.float32 if flags & B.FLAG_DW_FP32 else torch.bfloat16
+    old = [torch.full(s, 0.5 if flags else float("nan"), dtype=dt, device="cuda") for s in ((I, C), (I, C), (C, I))]
+    gh, dw = gpu_backward(p, bufs, R_host=r_host, flags=flags, dw=[t.clone() for t in old])
+    gh2, dw2 = gpu_backward(p, bufs, R_host=r_host, flags=flags | B.FLAG_BALANCED_SPLIT, dw=[t.clone() for t in old])
+    for a, b in zip(dw, dw2):
+        assert torch.equal(a, b)
+    idx, sk = bo["idx"], p.mask != 0
+    for g in (gh, gh2):
+        got = bits_of(g)
+        assert np.array_equal(got[sk], p.grad[sk])
+        assert rel_l2(O.bf16_bits_to_f64(got[idx]), O.bf16_bits_to_f64(bo["dx_bits"][idx])) < REL_L2_TOL
+    for t, k in zip(dw, ("dw_gate", "dw_up", "dw_down")):
+        # what was added to, 0.5, leaves a gradient's own digits: fp32 keeps them to 2^-24
+        assert rel_l2(f64_of(t) - (0.5 if flags else 0.0), bo[k]) < REL_L2_TOL, k
+
+
 @pytest.mark.parametrize("R,I", [(257, 8264), (385, 8264), (481, 8264), (577, 8264), (673, 8264), (769, 8264), (1400, 12808)])
 @pytest.mark.parametrize("r_host", [True, False], ids=["R-host", "R-device"])
 @pytest.mark.parametrize("saved", [False, True], ids=["inference", "training"])
