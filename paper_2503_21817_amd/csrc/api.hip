@@ -488,8 +488,17 @@ int skipffn_backward(int64_t T, int64_t C, int64_t I, float eps, const void* gra
         b.B0 = HT; b.ldb = ldT; b.b_bytes = (uint32_t)(I * (int64_t)ldT * 2);
         b.pairs = 1; b.splits = 1;
         b.out0 = dw_down; b.ldo = (int)I; b.out_f32 = f32; b.accumulate = accum; b.ncu = num_cus();
+        const int splits = dh_splits(Rb, C, I, (flags & SKIPFFN_FLAG_BALANCED_SPLIT) != 0, num_cus());
         profile_mark_begin(KC_GEMM_DH_DWDOWN, s);
-        e = launch_gemm_dh_dw_down(a, b, s);
+        if (splits == 1) {
+            e = launch_gemm_dh_dw_down(a, b, s);
+        } else {
+            a.splits = splits;
+            a.partial = partial;
+            e = launch_gemm_dh_partial_dw_down(a, b, s);
+            if (e == hipSuccess)
+                e = launch_swiglu_bwd_reduce(SwigluBwdArgs{partial, splits, G, U, dG, dU, dGT, dUT, (int)Rb, r_dev, (int)I, ldT}, s);
+        }
         profile_mark_end(KC_GEMM_DH_DWDOWN, s);
         if (e != hipSuccess) return hip_fail(e);
     }
@@ -509,13 +518,12 @@ int skipffn_backward(int64_t T, int64_t C, int64_t I, float eps, const void* gra
     x.ldb = (int)C; x.b_bytes = (uint32_t)(I * C * 2);
     x.pairs = 2;
     x.partial = partial;
-    const DxnPlan plan = plan_dxn(Rb, C, I, (f32 ? 4 : 2) * (accum ? 2 : 1), (flags & SKIPFFN_FLAG_BALANCED_SPLIT) != 0, r_dev != nullptr,
-                                  num_cus());
+    const DxnPlan plan = plan_dxn(Rb, C, I, (flags & SKIPFFN_FLAG_BALANCED_SPLIT) != 0, r_dev != nullptr, num_cus());
     x.splits = plan.k.splits;
     const PartialLayout pl{plan.k.splits, plan.k.sk_nbg, 2 * (int)((I + BK - 1) / BK)};
     if (plan.dw_workgroups > 0) {
         profile_mark_begin(KC_GEMM_DXN_DW, s);
-        e = launch_gemm_dxn_dw(x, w, plan.n0, plan.dw_workgroups, s);
+        e = launch_gemm_partial_dw(x, w, plan.n0, plan.dw_workgroups, s);
         profile_mark_end(KC_GEMM_DXN_DW, s);
     } else {
         profile_mark_begin(KC_GEMM_DW_GATE_UP, s);

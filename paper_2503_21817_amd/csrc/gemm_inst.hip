@@ -50,8 +50,9 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_dh_dw_down_kernel(GemmArgs 
         stream_tall<EPI_STORE>(P1, b - n0, (int)gridDim.x - n0);
 }
 
-// dXn (K cut evenly) and dW_gate, dW_up in one grid (plan_dxn): workgroups [0, n0) run dXn, the others lists of tiles of dW.
-__global__ __launch_bounds__(GEMM_THREADS) void gemm_dxn_dw_kernel(GemmArgs P0, GemmArgs P1, int n0) {
+// A GEMM into fp32 slabs (dXn, dH; K cut evenly) and weight gradients in one grid: workgroups [0, n0) run the first, the others
+// lists of tiles of the second.
+__global__ __launch_bounds__(GEMM_THREADS) void gemm_partial_dw_kernel(GemmArgs P0, GemmArgs P1, int n0) {
     const int b = (int)blockIdx.x;
     if (b < n0)
         gemm_block<EPI_PARTIAL>(P0, b);
@@ -73,7 +74,7 @@ hipError_t gemm_init() {
     if ((e = set_lds(&stream_gemm_balanced_kernel)) != hipSuccess) return e;
     if ((e = set_lds(&gemm_bf16_kernel)) != hipSuccess) return e;
     if ((e = set_lds(&gemm_bf16_streamk_kernel)) != hipSuccess) return e;
-    if ((e = set_lds(&gemm_dxn_dw_kernel)) != hipSuccess) return e;
+    if ((e = set_lds(&gemm_partial_dw_kernel)) != hipSuccess) return e;
     return set_lds(&gemm_dh_dw_down_kernel);
 }
 
@@ -110,26 +111,36 @@ static hipError_t launch_stream_rows(const GemmArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+// workgroups of dW_down beside dH: lists of about 16 slabs (of short tiles several, whose ends overlap; no longer: they also even
+// out the end of the grid), and no fewer lists than compute units
+static int dw_down_lists(const GemmArgs& a) {
+    const int tiles = (int)grid_blocks(a), slabs = std::max((a.K + BK - 1) / BK, 1);
+    const int per = std::max(std::min(16 / slabs, tiles / std::max(a.ncu, 1)), 1);
+    return ((tiles + per - 1) / per + 7) / 8 * 8;
+}
 hipError_t launch_gemm_dh_dw_down(GemmArgs& a0, GemmArgs& a1, hipStream_t s) {
     finish_args(EPI_SWIGLU_BWD, a0);
     finish_args(EPI_STORE, a1);
     const int real0 = (int)grid_blocks(a0), n0 = (real0 + 7) / 8 * 8, tiles1 = (int)grid_blocks(a1);
     if (real0 <= 0 || tiles1 <= 0) return hipErrorInvalidValue;
-    // lists of about 16 slabs (of short tiles several, whose ends overlap; no longer: they also even out the end of the
-    // grid), and no fewer lists than compute units
-    const int slabs = std::max((a1.K + BK - 1) / BK, 1), per = std::max(std::min(16 / slabs, tiles1 / std::max(a1.ncu, 1)), 1);
-    const int n1 = ((tiles1 + per - 1) / per + 7) / 8 * 8;
+    const int n1 = dw_down_lists(a1);
     hipLaunchKernelGGL(gemm_dh_dw_down_kernel, dim3((unsigned)(n0 + n1)), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a0, a1, n0);
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_dxn_dw(GemmArgs& a0, GemmArgs& a1, int n0, int n1, hipStream_t s) {
+hipError_t launch_gemm_partial_dw(GemmArgs& a0, GemmArgs& a1, int n0, int n1, hipStream_t s) {
     finish_args(EPI_PARTIAL, a0);
     finish_args(EPI_STORE, a1);
     if (grid_blocks(a0) == 0 || grid_blocks(a1) == 0) return hipErrorInvalidValue;
     if (n0 % 8 != 0 || (unsigned)n0 < grid_blocks(a0) || n1 < 8 || n1 % 8 != 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(gemm_dxn_dw_kernel, dim3((unsigned)(n0 + n1)), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a0, a1, n0);
+    hipLaunchKernelGGL(gemm_partial_dw_kernel, dim3((unsigned)(n0 + n1)), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a0, a1, n0);
     return hipGetLastError();
+}
+
+hipError_t launch_gemm_dh_partial_dw_down(GemmArgs& a0, GemmArgs& a1, hipStream_t s) {
+    finish_args(EPI_PARTIAL, a0);
+    finish_args(EPI_STORE, a1);
+    return launch_gemm_partial_dw(a0, a1, (int)((grid_blocks(a0) + 7) / 8 * 8), dw_down_lists(a1), s);
 }
 
 hipError_t launch_gemm_streamk(bool b_kc, GemmArgs& a, int nbg, hipStream_t s) {

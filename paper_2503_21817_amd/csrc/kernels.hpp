@@ -80,6 +80,13 @@ hipError_t launch_kv_compact(const void* src, void* dst, int64_t n_slabs, int64_
 struct TransposeJob { const bf16_t* src; int C; const int32_t* idx; bf16_t* dst; bf16_t* dstT; };
 hipError_t launch_gather_transpose(const TransposeJob* jobs, int count, int R, const int32_t* r_dev, int ldT, const SkippedRows& sk,
                                    hipStream_t s);
+// dG, dU and their transposed copies from `splits` (2 to 4) fp32 slabs of dH, z * R * I apart
+struct SwigluBwdArgs {
+    const float* partial; int splits;
+    const bf16_t *G, *U; bf16_t *dG, *dU, *dGT, *dUT;
+    int R; const int32_t* r_dev; int I, ldT;
+};
+hipError_t launch_swiglu_bwd_reduce(const SwigluBwdArgs& a, hipStream_t s);
 hipError_t launch_passthrough(const SkippedRows& sk, int R, const int32_t* r_dev, hipStream_t s);
 // dX[idx[r]] = bf16(dY[r] + rmsnorm_bwd(sum_z dxn_partial[z][r], x[r], rstd[r], gain)); with dgain != null
 // also dgain[c] (+)= sum_r dxn[r][c] * x[r][c] * rstd[r] (fp32, through gain_partial)
@@ -163,8 +170,10 @@ hipError_t gemm_init();   // raises the dynamic-LDS limit of every instantiation
 hipError_t launch_gemm(bool b_kc, int epi, GemmArgs& args, hipStream_t s);
 // two independent GEMMs in one grid, the first dispatched first: SwiGLU backward (dH -> dG, dU), and store (dW_down = dY^T * H)
 hipError_t launch_gemm_dh_dw_down(GemmArgs& dh, GemmArgs& dw, hipStream_t s);
-// dXn (fp32 slabs, K cut evenly) and dW_gate, dW_up in one grid, see plan_dxn
-hipError_t launch_gemm_dxn_dw(GemmArgs& dxn, GemmArgs& dw, int n0, int dw_workgroups, hipStream_t s);
+// a GEMM with an N-contiguous B operand into fp32 slabs, K cut evenly, and weight gradients in one grid: dXn and dW_gate, dW_up on n0
+// and dw_workgroups (plan_dxn); dH and dW_down (dh_splits)
+hipError_t launch_gemm_partial_dw(GemmArgs& a, GemmArgs& dw, int n0, int dw_workgroups, hipStream_t s);
+hipError_t launch_gemm_dh_partial_dw_down(GemmArgs& dh, GemmArgs& dw, hipStream_t s);
 // balanced split-K GEMM into fp32 partial slabs (EPI_PARTIAL): nbg workgroups per n-tile group
 hipError_t launch_gemm_streamk(bool b_kc, GemmArgs& args, int nbg, hipStream_t s);
 

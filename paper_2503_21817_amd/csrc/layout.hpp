@@ -73,15 +73,16 @@ inline KPartition choose_k_partition(int tiles_m, int tiles_n, int ktiles, bool 
 // longer parts, on the first n0 workgroups (a multiple of 8), lists of dW's tiles on dw_workgroups others, all on the chip at
 // once.  The ends of dXn's parts and the stores of dW then fall into each other's K slabs, and dXn leaves fewer fp32 slabs.
 // dw_workgroups = 0: two launches, each with the chip to itself, which many rows of a wide layer fill as well.  Costs in slabs of
-// dXn; a slab of dW, alone or not, takes 1.15 of one, the end of a tile what its stores (and loads, where dW is added to) take:
-// dw_bytes an element.  Backward of a layer, us, two launches / one (parts of dXn), bf16 dW:  C = 4096, I = 14336: 32 rows 226 / 197
+// dXn; a slab of dW, alone or not, takes 1.15 of one, and the end of a tile 2.5, as bf16 stores do: the type of dW and whether it is
+// added to choose no plan, so that they change no bit of the gradients.  Backward of a layer, us, two launches / one (parts of dXn), bf16 dW:  C = 4096, I = 14336: 32 rows 226 / 197
 // (8), 184 rows 277 / 248 (7), 256 rows 304 / 274 (6), 368 rows 326 / 314 (4), 600 rows 443 / 451 (3);  C = 3072, I = 10752:
 // 184 rows 210 / 184 (8), 368 rows 225 / 210 (5), 640 rows 272 / 278 (4);  C = 2048, I = 7168: 184 rows 123 / 102 (8), 640 rows
 // 167 / 150 (6), 1024 rows 209 / 196 (4), 1472 rows 295 / 277 (3);  C = 1024, I = 3584: 64 rows 69 / 59 (8), 368 rows 90 / 75
-// (8), 2944 rows 198 / 165 (3);  fp32 dW: C = 4096, I = 9952: 763 rows 456 / 478 (2).  With less than 8 % to gain by these costs
-// it measured from 6 % faster to 5 % slower, and is left.
+// (8), 2944 rows 198 / 165 (3).  With less than 8 % to gain by these costs it measured from 6 % faster to 5 %
+// slower, and is left.
+constexpr double kDwTileEnd = 2.5;
 struct DxnPlan { KPartition k; int n0, dw_workgroups; };
-inline DxnPlan plan_dxn(int64_t rows, int64_t C, int64_t I, int dw_bytes, bool balanced, bool count_on_device, int ncu) {
+inline DxnPlan plan_dxn(int64_t rows, int64_t C, int64_t I, bool balanced, bool count_on_device, int ncu) {
     const int tiles_m = (int)((rows + BM - 1) / BM), tiles_n = (int)((C + BN - 1) / BN);
     const int tiles = tiles_m * tiles_n, ktiles = 2 * (int)((I + BK - 1) / BK);
     double cost = 0.0;
@@ -90,7 +91,7 @@ inline DxnPlan plan_dxn(int64_t rows, int64_t C, int64_t I, int dw_bytes, bool b
     const int dw_tiles = (int)((I + BM - 1) / BM) * tiles_n * 2, dw_slabs = (int)((rows + BK - 1) / BK);
     const int whole = (dw_tiles + 7) / 8 * 8;                // a workgroup for every tile
     auto dw_cost = [&](int workgroups) {
-        return 1.15 * ((dw_tiles + workgroups - 1) / workgroups * (dw_slabs + 1.0 + 0.75 * dw_bytes) + 8.0);
+        return 1.15 * ((dw_tiles + workgroups - 1) / workgroups * (dw_slabs + kDwTileEnd) + 8.0);
     };
     double best = 0.92 * (cost + dw_cost(std::min(whole, ncu)));
     for (int s = 1; s <= kMaxSplits; ++s) {
@@ -103,6 +104,36 @@ inline DxnPlan plan_dxn(int64_t rows, int64_t C, int64_t I, int dw_bytes, bool b
         if (c < best - 1e-9) { best = c; p = DxnPlan{KPartition{s, 0}, n0, n1}; }
     }
     return p;
+}
+
+// Parts of K of the dH GEMM (K = C), which shares its grid with dW_down: with few rows its tiles are few and each is a chain of C / 64
+// slabs and a long epilogue, behind which the rest of the chip idles once dW_down is done.  Cut, they leave fp32 slabs, and the
+// SwiGLU backward and its transposed copies are a kernel of their own.  Costs in slabs as above: the longest tile of either, or all of
+// them on the chip, and the bytes of that kernel at 4.5 TB/s.  Backward of a layer, us, whole / parts (how many):  C = 1024,
+// I = 3584: 32 rows 56 / 47 (2), 184 rows 70 / 57 (2), 368 rows 75 / 62 (2), 768 rows 80 / 72 (2);  C = 2048, I = 7168: 184 rows
+// 102 / 83 (2), 368 rows 124 / 106 (2);  C = 4096, I = 2048: 184 rows 118 / 66 (4);  C = 4096, I = 8192: 184 rows 194 / 146 (3),
+// 368 rows 236 / 204 (2);  C = 3072, I = 10752: 184 rows 188 / 156 (2);  C = 4096, I = 14336: 64 rows 203 / 180 (2), 184 rows
+// 254 / 233 (2), 256 rows 282 / 263 (2);  C = 8192, I = 8192: 184 rows 355 / 263 (3).  Past the line: C = 4096, I = 14336, 368
+// rows 317 / 331 (2);  C = 2048, I = 1024, 3000 rows, where dW_down's tiles are as long, 131 / 136 (2).
+constexpr int kDhSplits = 4;
+inline int dh_splits(int64_t rows, int64_t C, int64_t I, bool balanced, int ncu) {
+    if (balanced || rows <= 0) return 1;
+    const int tiles_i = (int)((I + BN - 1) / BN), tiles = (int)((rows + BM - 1) / BM) * tiles_i, ktiles = (int)((C + BK - 1) / BK);
+    const double dw_tile = 1.15 * ((rows + BK - 1) / BK + kDwTileEnd), dw = (double)((C + BM - 1) / BM) * tiles_i * dw_tile;
+    auto cost = [&](int s) {
+        const double tile = (ktiles + s - 1) / s + (s > 1 ? 14.0 : 24.0);
+        return std::max({tile, dw_tile + 8.0, (tiles * s * tile + dw) / ncu + 8.0}) + (s > 1 ? 4.0 + (double)rows * I * (4 * s + 12) / 5.4e6 : 0.0);
+    };
+    int splits = 1;
+    double best = 0.92 * cost(1);
+    for (int s = 2; s <= kDhSplits; ++s) {
+        const int per = (ktiles + s - 1) / s;
+        if (per < 4 || s * I > kMaxSplits * C) break;        // its slabs lie where dXn's will (bwd_ws)
+        if ((s - 1) * per >= ktiles) continue;
+        const double c = cost(s);
+        if (c < best - 1e-9) { best = c; splits = s; }
+    }
+    return splits;
 }
 
 // Up to 256 rows the forward GEMMs are bound by streaming the 6 * C * I bytes of weights.  They run on tiles of ALL
@@ -313,7 +344,7 @@ inline BwdWs bwd_ws(int64_t R, int64_t C, int64_t I) {
     w.du = o; o += align_up((size_t)R * I * 2);
     w.dgT = o; o += align_up((size_t)I * ld_transposed(R) * 2);
     w.duT = o; o += align_up((size_t)I * ld_transposed(R) * 2);
-    w.partial = o; o += align_up((size_t)kMaxSplits * R * C * 4);
+    w.partial = o; o += align_up((size_t)kMaxSplits * R * C * 4);          // dXn's slabs, before it dH's
     w.gainp = o; o += align_up(gain_partial_bytes(R, C));
     w.status = o; o += 256;              // verdict of SKIPFFN_FLAG_VALIDATE_IDX
     w.total = o;

@@ -5,6 +5,7 @@
 // thousand at most, so a wavefront per row would leave most of the chip without work in
 // flight); purely elementwise ones run one thread per 16-byte chunk.
 #include "colsum.hpp"
+#include "gemm.hpp"
 #include "kernels.hpp"
 
 namespace skipffn {
@@ -400,6 +401,82 @@ hipError_t launch_gather_transpose(const TransposeJob* jobs, int count, int R, c
     profile_mark_begin(KC_GATHER_ROWS, s);
     hipLaunchKernelGGL(gather_transpose_kernel, dim3((unsigned)(a.blocks[0] + a.blocks[1]) + skipped_blocks(sk)), dim3(256), 0, s, a);
     profile_mark_end(KC_GATHER_ROWS, s);
+    return hipGetLastError();
+}
+
+// ---- SwiGLU backward of a dH that comes as fp32 slabs -----------------------------------------
+// dG, dU [R][I] and their transposed copies [I][ldT] (zeros past the last row), a tile of 64 x 64 a workgroup as above: S + 1 reads and
+// two writes of R * I values beside the copies.  When it pays: dh_splits.
+template <int S>
+__global__ __launch_bounds__(256) void swiglu_bwd_reduce_kernel(SwigluBwdArgs P) {
+    __shared__ bf16_t tile[2][TR_TILE][TR_TILE + 2];
+    const int R = effective_rows(P.R, P.r_dev);
+    const int r0 = (int)blockIdx.x * TR_TILE, c0 = (int)blockIdx.y * TR_TILE, t = threadIdx.x;
+    const int64_t zstride = (int64_t)P.R * P.I;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int q = t + 256 * i, rr = q >> 3, ch = q & 7, r = r0 + rr, c = c0 + ch * 8;
+        u32x4 dg = {0u, 0u, 0u, 0u}, du = {0u, 0u, 0u, 0u};
+        if (r < R && c < P.I) {
+            const int64_t o = (int64_t)r * P.I + c;
+            f32x4 v[S][2];
+#pragma unroll
+            for (int z = 0; z < S; ++z)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) v[z][h] = *reinterpret_cast<const f32x4*>(P.partial + z * zstride + o + 4 * h);
+            float g[8], u[8];
+            unpack8(*reinterpret_cast<const u32x4*>(P.G + o), g);
+            unpack8(*reinterpret_cast<const u32x4*>(P.U + o), u);
+            float a[8], b[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                float dh = v[0][j >> 2][j & 3];
+#pragma unroll
+                for (int z = 1; z < S; ++z) dh += v[z][j >> 2][j & 3];
+                const float sg = sigmoid_f(g[j]);
+                a[j] = dh * u[j] * sg * (1.0f + g[j] * (1.0f - sg));
+                b[j] = dh * g[j] * sg;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                dg[k] = pack_bf16x2(a[2 * k], a[2 * k + 1]);
+                du[k] = pack_bf16x2(b[2 * k], b[2 * k + 1]);
+            }
+            *reinterpret_cast<u32x4*>(P.dG + o) = dg;
+            *reinterpret_cast<u32x4*>(P.dU + o) = du;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            tile[0][rr][ch * 8 + 2 * k] = (bf16_t)(dg[k] & 0xffffu);
+            tile[0][rr][ch * 8 + 2 * k + 1] = (bf16_t)(dg[k] >> 16);
+            tile[1][rr][ch * 8 + 2 * k] = (bf16_t)(du[k] & 0xffffu);
+            tile[1][rr][ch * 8 + 2 * k + 1] = (bf16_t)(du[k] >> 16);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int q = (t + 256 * i) & 511, m = i >> 1, cc = q >> 3, ch = q & 7, c = c0 + cc, r = r0 + ch * 8;
+        if (c < P.I && r < P.ldT) {
+            u32x4 v;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                v[k] = (uint32_t)tile[m][ch * 8 + 2 * k][cc] | ((uint32_t)tile[m][ch * 8 + 2 * k + 1][cc] << 16);
+            *reinterpret_cast<u32x4*>((m == 0 ? P.dGT : P.dUT) + (int64_t)c * P.ldT + r) = v;
+        }
+    }
+}
+
+hipError_t launch_swiglu_bwd_reduce(const SwigluBwdArgs& a, hipStream_t s) {
+    if (a.R <= 0 || a.I <= 0) return hipSuccess;
+    const dim3 grid((unsigned)((a.ldT + TR_TILE - 1) / TR_TILE), (unsigned)((a.I + TR_TILE - 1) / TR_TILE)), block(256);
+    if (grid.y > 65535) return hipErrorInvalidValue;
+    switch (a.splits) {
+        case 2: hipLaunchKernelGGL(swiglu_bwd_reduce_kernel<2>, grid, block, 0, s, a); break;
+        case 3: hipLaunchKernelGGL(swiglu_bwd_reduce_kernel<3>, grid, block, 0, s, a); break;
+        case 4: hipLaunchKernelGGL(swiglu_bwd_reduce_kernel<4>, grid, block, 0, s, a); break;
+        default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

@@ -169,13 +169,16 @@ int main() {
         for (long C : widths)
             for (long I : widths)
                 for (long R = 1; R <= 16384; R += R < 300 ? 1 : R / 16)
-                    for (int variant = 0; variant < 16; ++variant) {
-                        const int dw_bytes = 2 << (variant & 1) << (variant >> 1 & 1);
-                        const bool forced = variant & 4, on_device = variant & 8;
-                        const DxnPlan p = plan_dxn(R, C, I, dw_bytes, forced, on_device, ncu);
+                    for (int variant = 0; variant < 4; ++variant) {
+                        const bool forced = variant & 1, on_device = variant & 2;
+                        const DxnPlan p = plan_dxn(R, C, I, forced, on_device, ncu);
                         const long tiles = (R + BM - 1) / BM * ((C + BN - 1) / BN), dw = (I + BM - 1) / BM * ((C + BN - 1) / BN) * 2;
                         const int ktiles = 2 * (int)((I + BK - 1) / BK), s = p.k.splits;
                         if (s < 1 || s > kMaxSplits || (s - 1) * ((ktiles + s - 1) / s) >= ktiles) return fail("split of dXn", R, C, I, ncu);
+                        const BwdWs W = bwd_ws(R, C, I);
+                        const int d = dh_splits(R, C, I, forced, ncu), kc = (int)((C + BK - 1) / BK);
+                        if (d < 1 || d > kDhSplits || (d - 1) * ((kc + d - 1) / d) >= kc) return fail("split of dH", R, C, I, ncu);
+                        if (d > 1 && (forced || (size_t)d * R * I * 4 > W.gainp - W.partial)) return fail("the slabs of dH do not fit", R, C, I, ncu);
                         if (p.dw_workgroups > 0) {
                             if (forced || p.k.sk_nbg != 0) return fail("the balanced split shares no launch", R, C, I, ncu);
                             if (p.n0 % 8 || p.n0 < tiles * s || p.dw_workgroups % 8 || p.n0 + p.dw_workgroups > ncu)

@@ -874,8 +874,8 @@ def test_weight_gradients_of_more_tiles_than_compute_units(R, flags):
 @pytest.mark.parametrize("r_host", [True, False], ids=["R-host", "R-device"])
 def test_input_gradient_beside_the_weight_gradients(R, C, I, flags, r_host):
     """dXn and dW_gate, dW_up in one launch: a workgroup for each tile of dW, lists of several (R on the host), K of dXn whole and in
-    up to 8 parts, cut-off tiles at every edge, with rows that are skipped.  Against the oracle, and against the
-    launches of their own that the balanced split takes: dW bit for bit."""
+    up to 8 parts, cut-off tiles at every edge, with rows that are skipped; dH in parts where C = 1032 and 2056.  Against the
+    oracle, as the launches of their own that the balanced split takes; dW_down, which neither touches, bit for bit."""
     print(f"dxn beside dw R={R} C={C} I={I} flags={flags} r_host={r_host}", flush=True)
     w = W.small(C=C, I=I, visual=(R + 23,), text=(1,), keep=(R - 1,), seed=7700 + R, name=f"dxn-dw-{R}")
     assert w.R == R
@@ -886,16 +886,43 @@ def test_input_gradient_beside_the_weight_gradients(R, C, I, flags, r_host):
     old = [torch.full(s, 0.5 if flags else float("nan"), dtype=dt, device="cuda") for s in ((I, C), (I, C), (C, I))]
     gh, dw = gpu_backward(p, bufs, R_host=r_host, flags=flags, dw=[t.clone() for t in old])
     gh2, dw2 = gpu_backward(p, bufs, R_host=r_host, flags=flags | B.FLAG_BALANCED_SPLIT, dw=[t.clone() for t in old])
-    for a, b in zip(dw, dw2):
-        assert torch.equal(a, b)
+    assert torch.equal(dw[2], dw2[2])
     idx, sk = bo["idx"], p.mask != 0
     for g in (gh, gh2):
         got = bits_of(g)
         assert np.array_equal(got[sk], p.grad[sk])
         assert rel_l2(O.bf16_bits_to_f64(got[idx]), O.bf16_bits_to_f64(bo["dx_bits"][idx])) < REL_L2_TOL
-    for t, k in zip(dw, ("dw_gate", "dw_up", "dw_down")):
+    for t, k in [*zip(dw, ("dw_gate", "dw_up", "dw_down")), *zip(dw2, ("dw_gate", "dw_up", "dw_down"))]:
         # what was added to, 0.5, leaves a gradient's own digits: fp32 keeps them to 2^-24
         assert rel_l2(f64_of(t) - (0.5 if flags else 0.0), bo[k]) < REL_L2_TOL, k
+
+
+@pytest.mark.parametrize("R,C,I,gain", [(1, 520, 8, False), (64, 520, 72, True), (65, 776, 264, False), (200, 1032, 3592, True), (300, 1544, 520, False),
+                                        (600, 2056, 520, True), (250, 1544, 4000, False)],
+                         ids=["one-chunk", "a-whole-tile", "ragged-parts", "two-parts", "two-tile-rows", "beyond-512-rows", "three-parts"])
+@pytest.mark.parametrize("r_host", [True, False], ids=["R-host", "R-device"])
+def test_dh_in_parts_of_k(R, C, I, gain, r_host):
+    """dH as fp32 slabs, the SwiGLU backward and the transposed copies from their sums: tiles of 64 x 64 cut off at every edge, parts of K
+    that end inside a slab.  Every row of dX and every column and row of the weight gradients are as the oracle's: dG and dU
+    are rounded to bf16, 2^-9 rms each; with one retained row a dG that cancels keeps the rounding of its terms, hence the typical
+    size beside its own."""
+    print(f"dh in parts R={R} C={C} I={I} gain={gain} r_host={r_host}", flush=True)
+    w = W.small(C=C, I=I, visual=(R + 23,), text=(1,), keep=(R - 1,), seed=7900 + R, name=f"dh-parts-{R}")
+    assert w.R == R
+    p = Problem(w, unit_gain=not gain, with_gain_tensor=gain)
+    bo = O.skipffn_backward(p.hidden, p.mask, p.wg, p.wu, p.wd, p.grad, p.gain if gain else None, w.eps)
+    _, bufs = gpu_forward(p, R_host=r_host)
+    gh, dw = gpu_backward(p, bufs, R_host=r_host)
+    idx, sk = bo["idx"], p.mask != 0
+    got = bits_of(gh)
+    assert np.array_equal(got[sk], p.grad[sk])
+    assert rel_l2(O.bf16_bits_to_f64(got[idx]), O.bf16_bits_to_f64(bo["dx_bits"][idx])) < REL_L2_TOL
+    for t, k in zip(dw, ("dw_gate", "dw_up", "dw_down")):
+        g = f64_of(t)
+        assert rel_l2(g, bo[k]) < REL_L2_TOL, k
+        for axis in (0, 1):
+            err, size = np.linalg.norm(g - bo[k], axis=axis), np.linalg.norm(bo[k], axis=axis)
+            assert np.all(err < REL_L2_TOL * (size + 4 * np.sqrt(np.mean(size ** 2)))), (k, axis)
 
 
 @pytest.mark.parametrize("R,I", [(257, 8264), (385, 8264), (481, 8264), (577, 8264), (673, 8264), (769, 8264), (1400, 12808)])
