@@ -120,16 +120,18 @@ __global__ __launch_bounds__(SUM_THREADS) void summary_chunk_fwd_kernel(
         d += e[i];
     }
     // phase B: every thread owns 16-byte column chunks: sum_t e_t X_t.  The sixteen row loads of
-    // a chunk are unconditional (an absent token reads row 0 with weight 0) and issued together.
-    const bf16_t* rp[SUM_CH];
+    // a chunk are unconditional and issued together; an absent token reads zeros, no row: its weight 0 times
+    // an infinity or a NaN would not be 0.
+    const __amdgpu_buffer_rsrc_t rx = make_rsrc(hidden, (uint32_t)(T * C * 2));
+    uint32_t ro[SUM_CH];
 #pragma unroll
     for (int i = 0; i < SUM_CH; ++i)
-        rp[i] = hidden + (int64_t)((i < nt && rowid[i] >= 0) ? rowid[i] : 0) * C;
+        ro[i] = i < nt && rowid[i] >= 0 ? (uint32_t)rowid[i] * (uint32_t)C * 2u : kOobOffset;
     float* pa = part_acc + (int64_t)blockIdx.x * C;
     for (int c = tid; c < chunks; c += SUM_THREADS) {
         u32x4 xr[SUM_CH];
 #pragma unroll
-        for (int i = 0; i < SUM_CH; ++i) xr[i] = *reinterpret_cast<const u32x4*>(rp[i] + c * 8);
+        for (int i = 0; i < SUM_CH; ++i) xr[i] = buf_load16(rx, ro[i] + (uint32_t)c * 16u);
         float acc[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc[j] = 0.0f;
@@ -170,7 +172,7 @@ __global__ __launch_bounds__(WAVES * 64, 3) void summary_held_fwd_kernel(
     uint32_t col[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) col[v] = tid + v * THREADS < chunks ? (uint32_t)(tid + v * THREADS) * 16u : kOobOffset;
-    int row[SUM_CH];                                     // -1: absent
+    int row[SUM_CH];                                     // -1: absent, reads row 0
 #pragma unroll
     for (int i = 0; i < SUM_CH; ++i) {
         const int r = i < nt ? tok[t0 + i] : -1;
@@ -251,6 +253,7 @@ __global__ __launch_bounds__(WAVES * 64, 3) void summary_held_fwd_kernel(
         for (int j = 0; j < 8; ++j) acc[j] = 0.0f;
 #pragma unroll
         for (int i = 0; i < SUM_CH; ++i) {
+            if (row[i] < 0) continue;                    // uniform; weight 0 times an infinity or a NaN of row 0 is not 0
             float f[8];
             unpack8s(x[i][v], f);
 #pragma unroll

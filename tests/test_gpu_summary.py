@@ -176,3 +176,21 @@ def test_rows_held_in_registers(C):
     """Widths at the ends of the forms that hold the rows of a chunk in registers, and past the last; a chunk of one token, a full
     one, and sets of several."""
     test_summary_forward_backward_against_oracle(300, C, (1, 16, 17, 130))
+
+
+@pytest.mark.parametrize("lens", [(1, 17, 130), (19,)], ids=str)      # sets found by the lanes of a wavefront; by scalar loads
+@pytest.mark.parametrize("C", [1024, 2048, 4096, 4104])
+def test_a_non_finite_row_outside_the_sets_changes_no_bit(C, lens):
+    """Row 0 is in no set: sets that do not fill their last chunk, and a token index out of range, must not read its values in."""
+    hid, tok, seg, wb, gout, gh0 = random_case(300, C, lens, seed=41 + C)
+    tok = np.where(tok == 0, 299 if 299 not in tok else -1, tok).astype(np.int32)
+    tok[-1] = 300
+    clean = run_gpu(hid, tok, seg, wb, gout, gh0)
+    for bits in (0x7F80, 0xFF80, 0x7FC0):                              # inf, -inf, NaN
+        dirty = hid.copy()
+        dirty[0] = bits
+        r = run_gpu(dirty, tok, seg, wb, gout, gh0)
+        for key in ("out", "gh"):
+            assert np.array_equal(bits_of(r[key]), bits_of(clean[key])), key
+        assert torch.equal(r["dw"], clean["dw"])
+        assert np.all(np.isfinite(f64_of(r["out"])))
