@@ -229,10 +229,15 @@ inline int gate_up_splits(int64_t C, int64_t I, int ncu) {
 // C = 3072, I = 10752 (48): 64 rows 57.0 / 53.6, 184 rows 81.8 / 79.8;  C = 2048, I = 7168 (32): 64 rows 39.7 / 36.2, 184
 // rows 56.1 / 54.2;  C = 1024, I = 3584 (16): 250 rows 38.0 / 36.7.  One more round than needed: 184 rows, C = 4096, 48
 // columns 141.5.
+// Only where the tiles are of all rows: in several row tiles every column tile loads its 256 rows again, and those bytes, not the
+// weights, bound it.  Gate/up kernel, us, 64 columns / as few as fit the chip:  C = 4096: I = 512, 1500 rows 42 / 48, 4200 rows 48 /
+// 54, I = 2048, 400 rows 43 / 49;  C = 8192: I = 1024, 2944 rows 92 / 107, I = 4096, 400 rows 83 / 93;  C = 2048, I = 2048, 512 rows
+// 25.0 / 27.5;  no shape was faster with fewer.
 inline int gate_up_cols(int64_t rows, int64_t I, int ncu) {
-    const int64_t tiles_m = std::max(mid_row_tiles(rows), 1), room = (tiles_m * ((I + 63) / 64) + ncu - 1) / ncu * ncu;
+    if (rows > 256) return 64;
+    const int64_t room = ((I + 63) / 64 + ncu - 1) / ncu * ncu;
     int cols = 16;
-    while (cols < 64 && tiles_m * ((I + cols - 1) / cols) > room) cols += 8;
+    while (cols < 64 && (I + cols - 1) / cols > room) cols += 8;
     return cols;
 }
 

@@ -42,6 +42,7 @@ static const char* check_plan(long R, long C, long I, bool hs, bool balanced, in
     // whole 16-byte chunks of H, and no more rounds of the chip than tiles of 64 columns take
     const long row_tiles = (R + 255) / 256, cols = p.gate_up_cols;
     if (cols % 8 || cols < 16 || cols > 64) return "columns of a gate/up tile";
+    if (R > 256 && cols != 64) return "narrow gate/up tiles load the rows of several row tiles again";
     if (p.gate_up == FWD_MID && (row_tiles * ((I + cols - 1) / cols) + ncu - 1) / ncu > (row_tiles * ((I + 63) / 64) + ncu - 1) / ncu)
         return "narrow gate/up tiles take another round";
     // where two thirds of the chip are idle, no workgroup walks more than 48 K slabs
