@@ -187,12 +187,21 @@ inline int choose_k_split(int tiles, int ktiles, int max_splits, int ncu) {
 // Without a saved buffer and a gain the tiles normalise their rows themselves (norm_in_gate_up), and they are no wider than
 // the chip needs (gate_up_cols):  C = 2048, I = 7168, registers / tiles: 17 rows 34.6 / 33.9, 32 rows 35.9 / 34.5, with a
 // gain 36.2 / 36.6, 33 rows with a gain 40.1 / 37.1;  C = 3072, I = 7168: 17 rows 45.4 / 42.1, with a gain 46.2 / 43.0;
-// C = 1024, I = 3584: 32 rows 15.2 / 19.3, 64 rows 20.4 / 22.6.
+// C = 1024, I = 3584: 32 rows 15.2 / 19.3, 64 rows 20.4 / 22.6.  Below 12 Mi weights the tiles of C = 2048 have nothing to gain (a split K
+// range, which needs a launch that adds its parts, or 16 columns).  Kernels of a layer, weights from memory, us:  I = 4096: 20 rows
+// 25.5 / 28.1, 32 rows 26.7 / 29.5;  I = 3072: 32 rows 25.4 / 30.2, 64 rows 32.5 / 33.1;  I = 2048: 32 rows 22.6 / 25.6, 64 rows
+// 28.1 / 29.4;  I = 6144: 32 rows 34.0 / 33.6;  I = 1024: 40 rows 25.6 / 25.1;  I = 512: 40 rows 24.6 / 20.9;  C = 3072,
+// I = 3072: 20 rows 29.2 / 30.7;  I = 4608: 20 rows 38.2 / 34.0.
 constexpr int64_t kFewRowsMax = 64;
 inline bool few_rows_gate_up(int64_t rows, int64_t C, int64_t I, bool has_saved, bool has_gain) {
     const int64_t weight = C * I, limit = (int64_t)40 * 2048 * 7168;
     if (rows > kFewRowsMax || weight > (int64_t)24 << 20 || rows * weight > (has_saved ? limit / 2 : limit)) return false;
-    return C <= (rows <= 16 ? 4096 : rows <= 32 && (has_saved || has_gain) ? 2048 : 1536);
+    if (rows <= 16) return C <= 4096;
+    if (weight <= (int64_t)12 << 20) {
+        if (C <= 2048 && (rows <= 32 || (!has_saved && I >= 2048))) return true;
+        if (C <= 3072 && I >= C && rows <= 32 && !has_saved) return true;
+    }
+    return C <= (rows <= 32 && (has_saved || has_gain) ? 2048 : 1536);
 }
 inline bool few_rows_down(int64_t rows, int64_t C, int64_t I, bool has_saved, int ncu) {
     if (rows > kFewRowsMax || rows * C * I > (int64_t)1 << (has_saved ? 29 : 30)) return false;

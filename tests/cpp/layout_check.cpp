@@ -50,6 +50,9 @@ static const char* check_plan(long R, long C, long I, bool hs, bool balanced, in
         (C + BK - 1) / BK > 48 * p.gate_up_splits)
         return "a long K range on an idle chip";
     if ((p.gate_up == FWD_FEW || p.down == FWD_FEW) && R > kFewRowsMax) return "too many rows for the register path";
+    // a layer of the widths that the register path takes, too small for tiles of their own: no split K range instead
+    if (!hs && !balanced && ncu == 256 && R > 16 && C == 2048 && I >= 2048 && I <= 6144 && R <= kFewRowsMax && p.gate_up != FWD_FEW)
+        return "tiles for a small layer";
     // its workgroups walk all of K: a chain of loads, twice as long with four row fragments
     if (p.gate_up == FWD_FEW && C > 4096) return "a long K range of the gate/up GEMM on the register path";
     if (p.down == FWD_FEW && I * (R > 32 ? 2 : 1) > (R > 16 || hs ? 8192 : 14336))
