@@ -258,9 +258,12 @@ inline int gate_up_cols(int64_t rows, int64_t I, int ncu) {
 // 17.7, 64 rows 24.4 / 27.2 (with a gain 26.4 / 27.3);  C = 2048, I = 7168: 8 rows 28.0 / 29.8, 16 rows 31.3 / 32.2, 32 rows 36.0
 // / 34.6;  C = 4096, I = 4096: 16 rows 26.2 / 29.7;  tiles  C = 4096, I = 14336: 8 rows 67.4 / 70.5, 64 rows 74.0 / 76.3 (with
 // a gain 92.1 / 71.2 and 98.8 / 76.7);  C = 3072, I = 10752: 8 rows 45.6 / 48.9, 64 rows 57.1 / 59.4.
+// From 33 rows only while all workgroups of 16 columns run at once, each of which forms the squares and the gain's products of all
+// rows:  C = 1024, I = 7168, before it / in the GEMM: 64 rows 30.3 / 31.2, with a gain 30.5 / 36.1, 40 rows with a gain 30.3 / 33.7.
 constexpr int64_t kNormInMidRows = 64;
-inline bool norm_in_gate_up(int64_t rows, int64_t C, bool has_gain, bool registers) {
-    return registers ? rows <= 16 || C <= 1024 : rows <= kNormInMidRows && !has_gain;
+inline bool norm_in_gate_up(int64_t rows, int64_t C, int64_t I, bool has_gain, bool registers, int ncu) {
+    if (!registers) return rows <= kNormInMidRows && !has_gain;
+    return rows <= 16 || (C <= 1024 && (rows <= 32 || (I + 15) / 16 <= ncu));
 }
 
 // Which kernels a forward call launches.
@@ -280,7 +283,7 @@ inline ForwardPlan plan_forward(int64_t rows, int64_t C, int64_t I, bool has_sav
         p.gate_up = few_rows_gate_up(rows, C, I, has_saved, has_gain) ? FWD_FEW : FWD_MID;
         if (p.gate_up == FWD_MID && rows <= 256) p.gate_up_splits = gate_up_splits(C, I, ncu);
         if (p.gate_up_splits == 1) p.gate_up_cols = gate_up_cols(rows, I, ncu);
-        p.norm_in_gate_up = !has_saved && p.gate_up_splits == 1 && norm_in_gate_up(rows, C, has_gain, p.gate_up == FWD_FEW);
+        p.norm_in_gate_up = !has_saved && p.gate_up_splits == 1 && norm_in_gate_up(rows, C, I, has_gain, p.gate_up == FWD_FEW, ncu);
         p.down = few_rows_down(rows, C, I, has_saved, ncu) ? FWD_FEW : mid_rows_down(rows, C, ncu) ? FWD_MID : FWD_CORE;
     }
     const int ktiles = (int)((I + BK - 1) / BK);
