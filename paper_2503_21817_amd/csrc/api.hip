@@ -774,7 +774,7 @@ int skipffn_token_merge(const void* x, const int32_t* seg_host, int64_t S, int64
         for (int i = st.count + 1; i <= SEG_TABLE_MAX; ++i) st.off[i] = st.off[st.count];
         for (int i = 0; i < st.count; ++i) gmax = std::max(gmax, st.off[i + 1] - st.off[i]);
         e = launch_merge_group(static_cast<const bf16_t*>(x), st, gmax, (int)C, (int)k, (int)g0, scratch, avg_sim, kept_idx, assign,
-                               static_cast<bf16_t*>(out), s);
+                               static_cast<bf16_t*>(out), num_cus(), s);
     }
     profile_mark_end(KC_MERGE, s);
     return e == hipSuccess ? SKIPFFN_OK : hip_fail(e);

@@ -125,7 +125,7 @@ hipError_t merge_init();         // raises the dynamic-LDS limits (once per proc
 // 8 bytes and 4 bytes
 struct MergeScratch { bf16_t* xn; float* part; float* sum; void* goal; int32_t* dropped; };
 hipError_t launch_merge_group(const bf16_t* x, const SegTable& st, int n_max, int C, int k, int set_base, const MergeScratch& ws,
-                              float* avg, int32_t* kept_idx, int32_t* assign, bf16_t* out, hipStream_t s);
+                              float* avg, int32_t* kept_idx, int32_t* assign, bf16_t* out, int ncu, hipStream_t s);
 hipError_t launch_merge_bwd_group(const bf16_t* dout, const SegTable& st, int n_max, int C, int k, int set_base,
                                   const int32_t* assign, bf16_t* dx, hipStream_t s);
 

@@ -13,6 +13,7 @@
 // its average ranks after every number, so exactly min(k, n) tokens are kept whatever the input;
 // a token whose similarities are all NaN goes to no slot (assign = -1) and gets a zero gradient.
 #include <algorithm>
+#include <type_traits>
 
 #include "colsum.hpp"
 #include "kernels.hpp"
@@ -320,18 +321,23 @@ static void launch_target(const bf16_t* xn, const SegTable& st, int nd, int kk, 
 }
 
 // ---- out[set][slot] = mean of the rows that go to the slot; assign ----------------------------------
-// A workgroup takes four slots, two wavefronts each, 64 chunks of the row a wavefront.  The slots of the set's tokens are staged in
-// LDS once; of the two wavefronts of a slot one searches them, eight a lane at a time, and a prefix sum over the lanes gives every
-// member its place in the list.  Then sixteen rows in flight, added in index order: the largest slot of a set ends the kernel.
-// 10.1 us at 8 sets of 1024 x 1024, k = 256, 26.3 at 6 of 2880 x 1024, k = 1200.  (A workgroup a slot, which reads the slots of all
-// tokens for itself: 11.4 and 28; a wavefront a slot, 128 chunks wide: 15.2 and 26.6.)
+// A workgroup takes four slots, two wavefronts each, COLS pieces of 64 chunks of the row a wavefront at a time.  The slots of the
+// set's tokens are staged in LDS once; of the two wavefronts of a slot one searches them, eight a lane at a time, and a prefix sum over
+// the lanes gives every member its place in the list.  Then the members are added in index order, sixteen loads in flight: sixteen
+// rows, or fewer rows of more pieces.  The staging and the search are most of the time of a short list, so a workgroup walks along
+// the row where the groups of slots fill the chip by themselves (four of them a CU) and takes a part of it where they do not.
+// us, a part of the row a workgroup whatever their number and the places read one by one / this:  64 sets of 576 x 4096, k = 518 207 /
+// 107;  8 of 576 x 8192, k = 518 42 / 26;  64 of 64 x 4104, k = 57 23.4 / 15.2;  one slot of 144 rows of 256 16.8 / 10.1;
+// 8 of 1024 x 1024, k = 256 6.4 / 6.6.  (A workgroup a slot, which reads the slots of all tokens for itself: 117, 23.8, 15.7, 10.4, 7.5.)
 constexpr int MEAN_THREADS = 512, MEAN_SLOTS = 4, MEAN_COLS = 128;
 __host__ __device__ constexpr int mean_lds_tokens(int n) { return (n + 511) / 512 * 512; }      // a wavefront searches 512 at a time
+template <int COLS>
 __global__ __launch_bounds__(MEAN_THREADS) void merge_mean_kernel(const bf16_t* __restrict__ x, SegTable st, int n_max, int C, int k,
                                                                   int set_base, const goal_t* __restrict__ goal,
                                                                   int32_t* __restrict__ assign, bf16_t* __restrict__ out) {
     extern __shared__ __align__(16) uint16_t lds16[];    // slots of the tokens, then the members of each slot
     __shared__ int members[MEAN_SLOTS];
+    constexpr int ROWS = 16 / COLS;                      // in flight
     const int set = blockIdx.y;
     const int lo = st.off[set], n = st.off[set + 1] - lo;
     const int kk = k < n ? k : n;
@@ -376,31 +382,63 @@ __global__ __launch_bounds__(MEAN_THREADS) void merge_mean_kernel(const bf16_t* 
     }
     __syncthreads();
     const int m = __builtin_amdgcn_readfirstlane(members[mine]);
-    const int c = (int)blockIdx.z * MEAN_COLS + (wave & 1) * 64 + lane;
-    if (slot >= k || c >= chunks) return;
-    const bf16_t* col = x + (int64_t)lo * C + (int64_t)c * 8;
-    float acc[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] = 0.0f;
-    for (int q = 0; q < m; q += 16) {
-        u32x4 r[16];
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-            if (q + e < m) r[e] = *reinterpret_cast<const u32x4*>(col + (int64_t)list[q + e] * C);     // uniform
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-            if (q + e < m) {
-                float f[8];
-                unpack8s(r[e], f);
-#pragma unroll
-                for (int j = 0; j < 8; ++j) acc[j] += f[j];
-            }
-    }
+    if (slot >= k) return;
+    const bf16_t* rows = x + (int64_t)lo * C;
     const float inv = 1.0f / (float)(m > 0 ? m : 1);     // a slot past the set's tokens: a row of zeros
-    u32x4 pk;
+    u32x4* dst = reinterpret_cast<u32x4*>(out + ((int64_t)(set_base + set) * k + slot) * C);
+    for (int c0 = (int)blockIdx.z * MEAN_COLS * COLS + (wave & 1) * 64 + lane; c0 < chunks; c0 += (int)gridDim.z * MEAN_COLS * COLS) {
+        int col[COLS];                                   // past the row: its last chunk in reach again, not stored
 #pragma unroll
-    for (int j = 0; j < 4; ++j) pk[j] = pack_bf16x2(acc[2 * j] * inv, acc[2 * j + 1] * inv);
-    reinterpret_cast<u32x4*>(out + ((int64_t)(set_base + set) * k + slot) * C)[c] = pk;
+        for (int v = 0; v < COLS; ++v) col[v] = c0 + v * MEAN_COLS < chunks ? c0 + v * MEAN_COLS : c0;
+        float acc[COLS][8];
+#pragma unroll
+        for (int v = 0; v < COLS; ++v)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[v][j] = 0.0f;
+        // N rows of the list from q on, the first `count` of them added in order; their places are read together (a read of LDS
+        // before each row's load was most of the kernel), the rows past the count are the first one again, as zeros
+        auto add_rows = [&](auto batch, const int q, const int count) {
+            constexpr int N = decltype(batch)::value;
+            u32x4 r[N][COLS];
+            uint32_t place[(N + 1) / 2];
+#pragma unroll
+            for (int h = 0; h < (N + 1) / 2; ++h)
+                place[h] = (uint32_t)__builtin_amdgcn_readfirstlane((int)reinterpret_cast<const uint32_t*>(list + q)[h]);
+#pragma unroll
+            for (int e = 0; e < N; ++e) {
+                const uint32_t row = e < count ? (e & 1 ? place[e >> 1] >> 16 : place[e >> 1] & 0xffffu) : place[0] & 0xffffu;
+                const u32x4* p = reinterpret_cast<const u32x4*>(rows + (int64_t)row * C);
+#pragma unroll
+                for (int v = 0; v < COLS; ++v) r[e][v] = p[col[v]];
+            }
+#pragma unroll
+            for (int e = 0; e < N; ++e) {
+                const uint32_t keep = e < count ? 0xffffffffu : 0u;
+#pragma unroll
+                for (int v = 0; v < COLS; ++v) {
+                    float f[8];
+                    unpack8s(r[e][v] & u32x4{keep, keep, keep, keep}, f);
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) acc[v][j] += f[j];
+                }
+            }
+        };
+        int q = 0;
+        for (; q + ROWS <= m; q += ROWS) add_rows(std::integral_constant<int, ROWS>{}, q, ROWS);
+        const int rest = m - q;                          // uniform, below ROWS
+        if (ROWS > 8 && rest > 8) add_rows(std::integral_constant<int, 16>{}, q, rest);
+        else if (ROWS > 4 && rest > 4) add_rows(std::integral_constant<int, 8>{}, q, rest);
+        else if (rest > 2) add_rows(std::integral_constant<int, 4>{}, q, rest);
+        else if (rest == 2) add_rows(std::integral_constant<int, 2>{}, q, 2);
+        else if (rest == 1) add_rows(std::integral_constant<int, 1>{}, q, 1);
+#pragma unroll
+        for (int v = 0; v < COLS; ++v) {
+            u32x4 pk;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) pk[j] = pack_bf16x2(acc[v][2 * j] * inv, acc[v][2 * j + 1] * inv);
+            if (c0 + v * MEAN_COLS < chunks) dst[c0 + v * MEAN_COLS] = pk;
+        }
+    }
 }
 
 // ---- gradient of the mean: dx[t] = dout[set][assign[t]] / (members of that slot) ---------------
@@ -463,7 +501,7 @@ hipError_t launch_merge_bwd_group(const bf16_t* dout, const SegTable& st, int n_
 
 // the sets of one table (set_base = index of its first set), n_max rows in the largest
 hipError_t launch_merge_group(const bf16_t* x, const SegTable& st, int n_max, int C, int k, int set_base, const MergeScratch& ws,
-                              float* avg, int32_t* kept_idx, int32_t* assign, bf16_t* out, hipStream_t s) {
+                              float* avg, int32_t* kept_idx, int32_t* assign, bf16_t* out, int ncu, hipStream_t s) {
     const unsigned sets = (unsigned)st.count;
     if (sets == 0) return hipSuccess;
     goal_t* goal = static_cast<goal_t*>(ws.goal);
@@ -506,10 +544,15 @@ hipError_t launch_merge_group(const bf16_t* x, const SegTable& st, int n_max, in
         else launch_target<64, 64>(ws.xn, st, nd, k, C, k, set_base, ws.dropped, kept_idx, goal, s);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(merge_mean_kernel, dim3((unsigned)((k + MEAN_SLOTS - 1) / MEAN_SLOTS), sets,
-                                               (unsigned)(((C >> 3) + MEAN_COLS - 1) / MEAN_COLS)),
-                       dim3(MEAN_THREADS), (size_t)mean_lds_tokens(n_max) * 2 * (1 + MEAN_SLOTS), s, x, st, n_max, C, k, set_base, goal,
-                       assign, out);
+    const int groups = (k + MEAN_SLOTS - 1) / MEAN_SLOTS, pieces = ((C >> 3) + MEAN_COLS - 1) / MEAN_COLS;
+    const int64_t slot_groups = (int64_t)groups * st.count, room = (4 * (int64_t)ncu + slot_groups - 1) / slot_groups;
+    const int cols = pieces >= 4 * room ? 4 : pieces >= 2 * room ? 2 : 1, row_parts = (pieces + cols - 1) / cols;
+    const dim3 mean_grid((unsigned)groups, sets, (unsigned)std::min<int64_t>(row_parts, room));
+    const size_t mean_lds = (size_t)mean_lds_tokens(n_max) * 2 * (1 + MEAN_SLOTS);
+    auto mean = [&](auto kernel) { hipLaunchKernelGGL(kernel, mean_grid, dim3(MEAN_THREADS), mean_lds, s, x, st, n_max, C, k, set_base, goal, assign, out); };
+    if (cols == 4) mean(merge_mean_kernel<4>);
+    else if (cols == 2) mean(merge_mean_kernel<2>);
+    else mean(merge_mean_kernel<1>);
     return hipGetLastError();
 }
 

@@ -110,6 +110,16 @@ def test_tiles_of_dropped_and_kept_rows(lens, C, k):
     check(xb, [0] + np.cumsum(lens).tolist(), k)
 
 
+@pytest.mark.parametrize("lens,C,k", [((20,) * 69 + (300,), 3080, 130), ((20,) * 40 + (130,), 2056, 100), ((144,), 256, 1), ((40,), 8, 2),
+                                      ((35, 60), 4104, 3)],
+                         ids=["row-in-fours", "row-in-twos", "one-long-list", "one-chunk", "parts-of-the-row"])
+def test_slots_along_the_row(lens, C, k):
+    """A workgroup of the mean takes a part of the row, or walks along it two or four pieces at a time, the last of them one
+    chunk: lists of one member to many, with every remainder of the rows it holds at once."""
+    xb = clustered(sum(lens), C, centers=30, noise=0.3, seed=sum(lens) + C + 4)
+    check(xb, [0] + np.cumsum(lens).tolist(), k)
+
+
 def test_merge_clustered_tokens_small_margins_inside_clusters():
     xb = clustered(500, 512, centers=40, noise=0.05, seed=3)
     check(xb, [0, 200, 500], 60)
