@@ -29,14 +29,15 @@ constexpr int MG_THREADS = 256;
 
 // ---- Xn = X / |X| (a zero row stays zero), and the sum of the MERGE_CHUNK rows of a workgroup of Xn ----
 // Bound by latency and HBM: a wavefront holds its two rows in registers, V chunks of each a lane, all loads in flight at once; its
-// sum of them meets those of the other three in LDS.  V = 0: rows of more than 4096 columns, read again for the second step, 4096
-// columns at a time: 64 KB of LDS whatever the width.
-// 9.3 us at 8192 rows of 1024 columns, 11.5 at 2304 of 4096 (16 rows a workgroup, read twice: 14.2 and 20.4).
+// sum of them meets those of the other three in LDS, past 4096 columns 2048 of them at a time.  V = 0: rows of more than 8192
+// columns, read again for the second step, 4096 columns at a time: 64 KB of LDS whatever the width.
+// 9.3 us at 8192 rows of 1024 columns, 11.5 at 2304 of 4096 (16 rows a workgroup, read twice: 14.2 and 20.4).  4608 rows of
+// 8192 columns: 30.5 us, of 4104 in 64 sets: 14.7 (read again, two loads in flight: 48 and 19; eight: 40 and 18.4).
 __device__ __forceinline__ int64_t merge_part_row(const SegTable& st, int set, int chunk) {
     return (st.off[set] - st.off[0]) / MERGE_CHUNK + set + chunk;           // the sets' rows of `part` do not overlap
 }
 static_assert(MERGE_CHUNK == MG_THREADS / 64 * 2, "two rows a wavefront");
-constexpr int MG_WIDE = 4096;
+constexpr int MG_WIDE = 4096, MG_PIECE = 2048;
 template <int V>
 __global__ __launch_bounds__(MG_THREADS) void merge_normalize_kernel(const bf16_t* __restrict__ x, SegTable st, int C,
                                                                      bf16_t* __restrict__ xn, float* __restrict__ part) {
@@ -58,6 +59,20 @@ __global__ __launch_bounds__(MG_THREADS) void merge_normalize_kernel(const bf16_
 #pragma unroll
         for (int j = 0; j < 8; ++j) s += f[j] * f[j];
     };
+    // f(c, chunk c of the two rows) for c = first, first + 64, ...: eight loads in flight
+    auto in_fours = [&](int c, const int end, auto&& f) {
+        for (; c + 192 < end; c += 256) {
+            u32x4 a[4], b[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                a[u] = src[0][c + 64 * u];
+                b[u] = src[1][c + 64 * u];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) f(c + 64 * u, a[u], b[u]);
+        }
+        for (; c < end; c += 64) f(c, src[0][c], src[1][c]);
+    };
     if constexpr (V > 0) {
 #pragma unroll
         for (int v = 0; v < V; ++v) {
@@ -72,10 +87,10 @@ __global__ __launch_bounds__(MG_THREADS) void merge_normalize_kernel(const bf16_
                 add(held[1][v], ss[1]);
             }
     } else {
-        for (int c = lane; c < chunks; c += 64) {
-            add(src[0][c], ss[0]);
-            add(src[1][c], ss[1]);
-        }
+        in_fours(lane, chunks, [&](int, const u32x4& a, const u32x4& b) {
+            add(a, ss[0]);
+            add(b, ss[1]);
+        });
     }
     float inv[2];
 #pragma unroll
@@ -83,7 +98,7 @@ __global__ __launch_bounds__(MG_THREADS) void merge_normalize_kernel(const bf16_
         const float v = wave_sum(ss[q]);
         inv[q] = v > 0.0f ? 1.0f / sqrtf(v) : 0.0f;
     }
-    const int width = V > 0 || C < MG_WIDE ? C : MG_WIDE;
+    const int width = V > 0 && V <= 8 ? C : V > 8 ? MG_PIECE : C < MG_WIDE ? C : MG_WIDE;
     auto emit = [&](int c, int c0, const u32x4& a, const u32x4& b) {
         float sum[8];
 #pragma unroll
@@ -112,7 +127,20 @@ __global__ __launch_bounds__(MG_THREADS) void merge_normalize_kernel(const bf16_
         for (int c = tid; c < count; c += MG_THREADS)
             out[first + c] = (in[c] + in[c + quads]) + (in[c + 2 * quads] + in[c + 3 * quads]);
     };
-    if constexpr (V > 0) {
+    if constexpr (V > 8) {
+        constexpr int PIECE = MG_PIECE / 8;              // chunks
+#pragma unroll
+        for (int p = 0; p < V * 64 / PIECE; ++p) {
+            const int c0 = p * PIECE;
+            if (c0 >= chunks) break;                     // uniform
+            if (p > 0) __syncthreads();                  // the piece before has been added
+#pragma unroll
+            for (int v = c0 / 64; v < (c0 + PIECE) / 64; ++v)
+                if (lane + 64 * v < chunks) emit(lane + 64 * v, c0, held[0][v], held[1][v]);
+            __syncthreads();
+            write_sum(c0 * 2, (c0 + PIECE < chunks ? PIECE : chunks - c0) * 2);
+        }
+    } else if constexpr (V > 0) {
 #pragma unroll
         for (int v = 0; v < V; ++v)
             if (lane + 64 * v < chunks) emit(lane + 64 * v, 0, held[0][v], held[1][v]);
@@ -122,7 +150,7 @@ __global__ __launch_bounds__(MG_THREADS) void merge_normalize_kernel(const bf16_
         for (int c0 = 0; c0 < chunks; c0 += MG_WIDE / 8) {
             const int c1 = c0 + MG_WIDE / 8 < chunks ? c0 + MG_WIDE / 8 : chunks;
             if (c0 > 0) __syncthreads();                 // the piece before has been added
-            for (int c = c0 + lane; c < c1; c += 64) emit(c, c0, src[0][c], src[1][c]);
+            in_fours(c0 + lane, c1, [&](int c, const u32x4& a, const u32x4& b) { emit(c, c0, a, b); });
             __syncthreads();
             write_sum(c0 * 2, (c1 - c0) * 2);
         }
@@ -514,6 +542,7 @@ hipError_t launch_merge_group(const bf16_t* x, const SegTable& st, int n_max, in
         else if (chunks <= 128) hipLaunchKernelGGL(merge_normalize_kernel<2>, rows, threads, lds, s, x, st, C, ws.xn, ws.part);
         else if (chunks <= 256) hipLaunchKernelGGL(merge_normalize_kernel<4>, rows, threads, lds, s, x, st, C, ws.xn, ws.part);
         else if (chunks <= 512) hipLaunchKernelGGL(merge_normalize_kernel<8>, rows, threads, lds, s, x, st, C, ws.xn, ws.part);
+        else if (chunks <= 1024) hipLaunchKernelGGL(merge_normalize_kernel<16>, rows, threads, MG_PIECE * 16, s, x, st, C, ws.xn, ws.part);
         else hipLaunchKernelGGL(merge_normalize_kernel<0>, rows, threads, lds, s, x, st, C, ws.xn, ws.part);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         const dim3 cols((unsigned)((C + 31) / 32), sets);

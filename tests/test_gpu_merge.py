@@ -100,8 +100,8 @@ def test_similarity_tiles_and_their_mirror_images(lens, C, k):
 
 
 @pytest.mark.parametrize("lens,C,k", [((129,) * 70, 64, 64), ((128, 193), 72, 127), ((700,), 4104, 129), ((1024,) * 8, 40, 256),
-                                      ((1500,) * 6, 264, 700), ((513, 1, 9), 1544, 8), ((70, 9), 12296, 20)],
-                         ids=["more-sets-than-a-launch", "one-dropped", "wide-rows", "64x128", "128x128", "ragged-last-launch", "rows-past-lds"])
+                                      ((1500,) * 6, 264, 700), ((513, 1, 9), 1544, 8), ((70, 9), 12296, 20), ((9, 50), 8192, 20), ((41,), 6152, 7)],
+                         ids=["more-sets-than-a-launch", "one-dropped", "wide-rows", "64x128", "128x128", "ragged-last-launch", "rows-past-lds", "rows-end-of-registers", "rows-of-four-pieces"])
 def test_tiles_of_dropped_and_kept_rows(lens, C, k):
     """Every tile of the target kernel, dropped and kept rows that end just inside and just past one, rows too wide for the
     registers of the normalising kernel, and too wide for LDS, sets of several launches; averages against pairs formed in 64 bits."""
