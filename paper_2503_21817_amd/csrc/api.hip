@@ -766,9 +766,11 @@ int skipffn_token_merge(const void* x, const int32_t* seg_host, int64_t S, int64
     const MergeScratch scratch{reinterpret_cast<bf16_t*>(ws + W.xn), reinterpret_cast<float*>(ws + W.part),
                                reinterpret_cast<float*>(ws + W.sum), ws + W.goal, reinterpret_cast<int32_t*>(ws + W.dropped)};
     profile_mark_begin(KC_MERGE, s);
-    for (int64_t g0 = 0; g0 < S && e == hipSuccess; g0 += SEG_TABLE_MAX) {
+    // launches of even size: the last 6 sets of 70 alone would not fill the chip (576 x 4096 each, k = 518: 483 / 423 us)
+    const int64_t launches = (S + SEG_TABLE_MAX - 1) / SEG_TABLE_MAX, group = launches > 0 ? (S + launches - 1) / launches : 1;
+    for (int64_t g0 = 0; g0 < S && e == hipSuccess; g0 += group) {
         SegTable st;
-        st.count = (int)std::min<int64_t>(SEG_TABLE_MAX, S - g0);
+        st.count = (int)std::min<int64_t>(group, S - g0);
         int gmax = 0;
         for (int i = 0; i <= st.count; ++i) st.off[i] = seg_host[g0 + i];
         for (int i = st.count + 1; i <= SEG_TABLE_MAX; ++i) st.off[i] = st.off[st.count];

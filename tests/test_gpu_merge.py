@@ -120,6 +120,15 @@ def test_slots_along_the_row(lens, C, k):
     check(xb, [0] + np.cumsum(lens).tolist(), k)
 
 
+@pytest.mark.parametrize("lens,C,k", [((32, 25, 1, 0, 8, 9), 4104, 5), ((24, 2, 16) * 45, 72, 2), ((33, 32), 264, 10)],
+                         ids=["four-parts", "three-launches", "five-parts"])
+def test_averages_of_few_tokens(lens, C, k):
+    """Up to 32 tokens a set the averages add the partial sums themselves; launches of even size."""
+    rng = np.random.default_rng(sum(lens) + C + 5)
+    xb = O.f64_to_bf16_bits(rng.standard_normal((sum(lens), C)) + 0.5 * rng.standard_normal((1, C)))
+    check(xb, [0] + np.cumsum(lens).tolist(), k)
+
+
 def test_merge_clustered_tokens_small_margins_inside_clusters():
     xb = clustered(500, 512, centers=40, noise=0.05, seed=3)
     check(xb, [0, 200, 500], 60)
