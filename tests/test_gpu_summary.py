@@ -194,3 +194,10 @@ def test_a_non_finite_row_outside_the_sets_changes_no_bit(C, lens):
             assert np.array_equal(bits_of(r[key]), bits_of(clean[key])), key
         assert torch.equal(r["dw"], clean["dw"])
         assert np.all(np.isfinite(f64_of(r["out"])))
+
+
+@pytest.mark.parametrize("lens", [(208, 240, 257), (4200, 3)], ids=str)
+def test_many_chunks_a_set(lens):
+    """13, 15 and 17 chunks (a batch of chunks that the merge of a set holds at once, less, more), and more than the 256 whose scales it
+    stages at a time."""
+    test_summary_forward_backward_against_oracle(sum(lens) + 10, 520, lens)
