@@ -367,12 +367,13 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
         a.no_residual = no_residual;
         profile_mark_begin(KC_GEMM_DOWN, s);
         if (by_count) {
-            const RowPlans plans = plan_rows(Rb, C, I, num_cus());
+            int64_t sum_rows = 0;
+            const RowPlans plans = plan_rows(Rb, C, I, num_cus(), &sum_rows);
             a.out0 = out; a.e0 = static_cast<const bf16_t*>(hidden); a.partial = partial;
             e = launch_down_count(a, plans, s);
             profile_mark_end(KC_GEMM_DOWN, s);
             if (e == hipSuccess)
-                e = launch_resid_scatter_count(partial, plans, ktiles, (int)Rb, r_dev, (int)C, idx, static_cast<const bf16_t*>(hidden),
+                e = launch_resid_scatter_count(partial, plans, ktiles, (int)Rb, (int)sum_rows, r_dev, (int)C, idx, static_cast<const bf16_t*>(hidden),
                                                static_cast<bf16_t*>(out), no_residual, s);
             if (e != hipSuccess) return hip_fail(e);
         } else if (kp.splits == 1 && kp.sk_nbg == 0) {

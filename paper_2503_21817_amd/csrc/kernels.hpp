@@ -66,7 +66,7 @@ hipError_t launch_resid_scatter(const float* partial, PartialLayout pl, int R, c
                                 int C, const int32_t* idx, const bf16_t* res, bf16_t* out,
                                 int no_residual, hipStream_t s);
 // the same after launch_down_count: the slabs of the plan that the count on the device has (nothing where its K was whole)
-hipError_t launch_resid_scatter_count(const float* partial, const RowPlans& plans, int ktiles, int R, const int32_t* r_dev, int C,
+hipError_t launch_resid_scatter_count(const float* partial, const RowPlans& plans, int ktiles, int R, int sum_rows, const int32_t* r_dev, int C,
                                       const int32_t* idx, const bf16_t* res, bf16_t* out, int no_residual, hipStream_t s);
 // dst[r] = src[idx[r]]  (rows of row_bytes, multiple of 16)
 hipError_t launch_gather_rows(const void* src, void* dst, int64_t row_bytes, const int32_t* idx,

@@ -38,32 +38,39 @@ constexpr int kMaxSplitsNarrow = 16;     // up to 256 rows: small fp32 slabs, an
 //                              workgroup first runs whole tiles of its own; the rest is split)
 // Both GEMMs are planned in 256-row tiles.  The down GEMM then lowers them where K is not balanced (stream_rows_plan).
 struct KPartition { int splits; int sk_nbg; };
+// `slab`: the cost of writing a tile's slab and reading it back
+inline double k_partition_cost(KPartition k, int tiles_m, int tiles_n, int ktiles, int ncu, double slab = 0.04) {
+    const int tiles = tiles_m * tiles_n, s = k.splits;
+    if (k.sk_nbg == 0) {
+        const int per = (ktiles + s - 1) / s, rounds = (tiles * s + ncu - 1) / ncu;
+        return rounds * (per + 8.0 + (s > 1 ? 8.0 : 0.0)) + (s > 1 ? slab * s * tiles : 0.0);
+    }
+    const StreamKPlan p = streamk_plan(tiles_m, ktiles, k.sk_nbg);
+    double slabs = 0.0;
+    for (int i = 0; i < tiles_m; ++i) slabs += streamk_count(p, i);
+    // an aligned chunk is one segment; a remainder piece runs one segment (with its own
+    // prologue and epilogue: about 5 slabs' worth, measured) per tile it touches; with more
+    // tiles than workgroups in a group, whole tiles come first
+    const double aligned = p.a > 0 ? p.q + 16.0 : 0.0;
+    const double pieces = p.nr > 0 ? p.qr + 16.0 + 5.0 * (p.qr / p.rem) : 0.0;
+    return p.full * (ktiles + 16.0) + std::max(aligned, pieces) + slab * slabs * tiles_n;
+}
 inline KPartition choose_k_partition(int tiles_m, int tiles_n, int ktiles, bool force_balanced, int ncu, double* cost_of = nullptr) {
-    const int tiles = tiles_m * tiles_n;
     KPartition best{1, 0};
     double best_cost = 1e30;
+    auto consider = [&](KPartition k) {
+        const double cost = k_partition_cost(k, tiles_m, tiles_n, ktiles, ncu);
+        if (cost < best_cost - 1e-9) { best_cost = cost; best = k; }
+    };
     for (int s = 1; s <= kMaxSplits; ++s) {
-        int per = (ktiles + s - 1) / s;
-        if (s > 1 && per < 4) break;
-        int rounds = (tiles * s + ncu - 1) / ncu;
-        double cost = rounds * (per + 8.0 + (s > 1 ? 8.0 : 0.0)) + (s > 1 ? 0.04 * s * tiles : 0.0);
-        if (cost < best_cost - 1e-9) { best_cost = cost; best = KPartition{s, 0}; }
+        if (s > 1 && (ktiles + s - 1) / s < 4) break;
+        consider(KPartition{s, 0});
     }
     const int nbg = tiles_n > 0 ? ncu / tiles_n : 0;
-    if (nbg >= 1 && tiles > 0) {
-        const StreamKPlan p = streamk_plan(tiles_m, ktiles, nbg);
+    if (nbg >= 1 && tiles_m * tiles_n > 0) {
         if (force_balanced) return KPartition{1, nbg};
-        if (p.gr > 0 && p.q >= 8) {
-            double slabs = 0.0;
-            for (int i = 0; i < tiles_m; ++i) slabs += streamk_count(p, i);
-            // an aligned chunk is one segment; a remainder piece runs one segment (with its own
-            // prologue and epilogue: about 5 slabs' worth, measured) per tile it touches; with more
-            // tiles than workgroups in a group, whole tiles come first
-            const double aligned = p.a > 0 ? p.q + 16.0 : 0.0;
-            const double pieces = p.nr > 0 ? p.qr + 16.0 + 5.0 * (p.qr / p.rem) : 0.0;
-            double cost = p.full * (ktiles + 16.0) + std::max(aligned, pieces) + 0.04 * slabs * tiles_n;
-            if (cost < best_cost - 1e-9) { best_cost = cost; best = KPartition{1, nbg}; }
-        }
+        const StreamKPlan p = streamk_plan(tiles_m, ktiles, nbg);
+        if (p.gr > 0 && p.q >= 8) consider(KPartition{1, nbg});
     }
     if (cost_of != nullptr) *cost_of = best_cost;
     return best;
@@ -296,6 +303,13 @@ inline ForwardPlan plan_forward(int64_t rows, int64_t C, int64_t I, bool has_sav
 
 // A row count on the device, below a bound for which the core runs the down GEMM: the plan of every row of tiles, so that the kernels
 // take that of the rows there are.  Up to 256 rows `mid_splits` parts on tiles of all rows (zstride: 256 rows).
+// A count takes its own plan only where that is cheaper than the bound's with slabs at 0.12 for the rows that its tiles have at least:
+// the 0.04 that choose_k_partition prices them at is what they cost with the chip's cache to themselves, and a count's plan of many parts
+// lost to the bound's of few.  Layer forward, us, plan of the bound / of the count at 0.04 / of the two:  C = 1024, I = 3584: bound
+// 4200, 2100 rows 73.6 / 79.7 / 73;  bound 4928, 2464 rows 85 / 91 / 84;  C = 512, I = 2048: bound 4928, 2464 rows 45.3 / 49.5 / 45;
+// C = 4096, I = 4096: bound 9856, 4928 rows, with a saved buffer 473 / 490 / 472;  C = 4096, I = 14336: bound 2944, 736 rows 260 / 240 / 240.
+// sum_rows: the most rows whose plan leaves slabs, 256 at least (their tiles always do).  A reducing launch for the bound cost
+// up to 9 us of workgroups without work:  C = 8192, I = 1024: bound 9856, 4928 rows, with a saved buffer 360 / 370 / 358.
 constexpr int kRowPlans = 64;                            // 16384 rows; the bound's plan beyond
 constexpr uint16_t kRowPlanBalanced = 0x8000;
 struct RowPlans { int mid_splits; uint16_t beyond, down[kRowPlans]; };
@@ -303,16 +317,24 @@ SKIPFFN_HD inline KPartition row_plan(const RowPlans& p, int tiles_m) {
     const uint16_t v = tiles_m <= kRowPlans ? p.down[tiles_m - 1] : p.beyond;
     return v & kRowPlanBalanced ? KPartition{1, v & ~kRowPlanBalanced} : KPartition{v, 0};
 }
-inline RowPlans plan_rows(int64_t bound, int64_t C, int64_t I, int ncu) {
+inline RowPlans plan_rows(int64_t bound, int64_t C, int64_t I, int ncu, int64_t* sum_rows = nullptr) {
     RowPlans p{};
-    const int ktiles = (int)((I + BK - 1) / BK), tiles_m = (int)((bound + BM - 1) / BM);
+    const int ktiles = (int)((I + BK - 1) / BK), tiles_m = (int)((bound + BM - 1) / BM), tiles_n = (int)((C + BN - 1) / BN);
     p.mid_splits = choose_k_split((int)((C + 127) / 128), ktiles, kMaxSplitsNarrow, ncu);
+    const KPartition of_bound = choose_k_partition(tiles_m, tiles_n, ktiles, false, ncu);
+    int last = 1;                                        // row of tiles with slabs
     auto code = [&](int t) {
-        const KPartition k = choose_k_partition(t, (int)((C + BN - 1) / BN), ktiles, false, ncu);
+        KPartition k = choose_k_partition(t, tiles_n, ktiles, false, ncu);
+        const double slab = 0.12 * (t - 1) / t;
+        const bool same = k.splits == of_bound.splits && k.sk_nbg == of_bound.sk_nbg;
+        if (!same && k_partition_cost(of_bound, t, tiles_n, ktiles, ncu, slab) <= k_partition_cost(k, t, tiles_n, ktiles, ncu, slab)) k = of_bound;
+        if (k.sk_nbg > 0 || k.splits > 1) last = t;
         return (uint16_t)(k.sk_nbg > 0 ? kRowPlanBalanced | k.sk_nbg : k.splits);
     };
-    for (int t = 1; t <= kRowPlans; ++t) p.down[t - 1] = t <= tiles_m ? code(t) : 1;
+    p.down[0] = 1;                                       // up to 256 rows: tiles of all rows
+    for (int t = 2; t <= kRowPlans; ++t) p.down[t - 1] = t <= tiles_m ? code(t) : 1;
     p.beyond = tiles_m > kRowPlans ? code(tiles_m) : 1;
+    if (sum_rows != nullptr) *sum_rows = std::min<int64_t>(bound, (int64_t)last * BM);
     return p;
 }
 

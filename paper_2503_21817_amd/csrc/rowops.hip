@@ -240,10 +240,10 @@ __global__ __launch_bounds__(ROW_THREADS) void resid_scatter_count_kernel(
     resid_scatter_chunk(partial, PartialLayout{k.splits, k.sk_nbg, ktiles}, all_rows ? 256 : Rbound, R, C, idx, res, out, no_residual);
 }
 
-hipError_t launch_resid_scatter_count(const float* partial, const RowPlans& plans, int ktiles, int R, const int32_t* r_dev, int C,
+hipError_t launch_resid_scatter_count(const float* partial, const RowPlans& plans, int ktiles, int R, int sum_rows, const int32_t* r_dev, int C,
                                       const int32_t* idx, const bf16_t* res, bf16_t* out, int no_residual, hipStream_t s) {
     if (R <= 0) return hipSuccess;
-    const int64_t total = (int64_t)R * (C >> 3);
+    const int64_t total = (int64_t)sum_rows * (C >> 3);
     profile_mark_begin(KC_RESID_SCATTER, s);
     hipLaunchKernelGGL(resid_scatter_count_kernel, dim3((unsigned)((total + ROW_THREADS - 1) / ROW_THREADS)), dim3(ROW_THREADS), 0, s,
                        partial, plans, ktiles, R, r_dev, C, idx, res, out, no_residual);

@@ -27,6 +27,40 @@ static bool paint(std::vector<unsigned char>& map, size_t off, size_t bytes, siz
     return true;
 }
 
+// what is wrong with the down GEMM's plans of all counts below a bound of more than 256 rows, or null
+static const char* check_row_plans(long bound, long C, long I, int ncu) {
+    int64_t sum_rows = 0;
+    const RowPlans p = plan_rows(bound, C, I, ncu, &sum_rows);
+    const int ktiles = (int)((I + BK - 1) / BK), tiles_m = (int)((bound + BM - 1) / BM), tiles_n = (int)((C + BN - 1) / BN);
+    for (int hs = 0; hs < 2; ++hs) {
+        const FwdWs W = fwd_ws(bound, C, I, hs != 0, ncu);
+        const size_t room = W.status - W.partial, slab = (size_t)bound * C * 4;
+        if (p.mid_splits < 1 || (size_t)p.mid_splits * 256 * C * 4 > room) return "the slabs of up to 256 rows do not fit";
+        if ((size_t)kMaxSplits * slab > room) return "the slabs of a count do not fit";
+    }
+    if ((p.mid_splits - 1) * ((ktiles + p.mid_splits - 1) / p.mid_splits) >= ktiles) return "an empty part of up to 256 rows";
+    if (sum_rows < 256 || sum_rows > bound) return "rows of the reducing launch";
+    for (int t = 2; t <= tiles_m; ++t) {
+        const KPartition k = row_plan(p, t);
+        if (k.sk_nbg > 0 || k.splits > 1)
+            if (sum_rows < std::min<long>(bound, (long)t * BM)) return "slabs past the rows of the reducing launch";
+        if (t > kRowPlans && t < tiles_m) {
+            const KPartition b = row_plan(p, tiles_m);
+            if (k.splits != b.splits || k.sk_nbg != b.sk_nbg) return "a count past the table has the bound's plan";
+        }
+        if (k.sk_nbg > 0) {
+            if (k.splits != 1 || k.sk_nbg * tiles_n > ncu) return "balanced split of a count larger than the chip";
+            const StreamKPlan sk = streamk_plan(t, ktiles, k.sk_nbg);
+            for (int i = 0; i < t; ++i)
+                if (streamk_count(sk, i) > kMaxSplits) return "slabs of a balanced split of a count";
+        } else if (k.splits < 1 || k.splits > kMaxSplits || (k.splits - 1) * ((ktiles + k.splits - 1) / k.splits) >= ktiles) {
+            return "split of a count";
+        }
+    }
+    const KPartition own = choose_k_partition(tiles_m, tiles_n, ktiles, false, ncu), b = row_plan(p, tiles_m);
+    return b.splits != own.splits || b.sk_nbg != own.sk_nbg ? "the bound's own plan" : nullptr;
+}
+
 // what is wrong with the forward plan, or null
 static const char* check_plan(long R, long C, long I, bool hs, bool balanced, int ncu) {
     const ForwardPlan p = plan_forward(R, C, I, hs, balanced, ncu);
@@ -168,6 +202,14 @@ int main() {
                         if (const char* what = check_plan(R, C, I, variant & 1, variant & 2, ncu)) return fail(what, R, C, I, ncu);
                         ++cases;
                     }
+    // the plans of a count on the device
+    for (int ncu : ncus)
+        for (long C : widths)
+            for (long I : widths)
+                for (long bound : {257L, 300L, 512L, 616L, 1232L, 2944L, 4928L, 9856L, 16384L, 16385L, 20000L}) {
+                    if (const char* what = check_row_plans(bound, C, I, ncu)) return fail(what, bound, C, I, ncu);
+                    ++cases;
+                }
     // dXn beside dW_gate and dW_up: all workgroups on the chip at once, every part of K with slabs, no more of them than the
     // workspace holds
     for (int ncu : ncus)
