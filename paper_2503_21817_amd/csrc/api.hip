@@ -291,7 +291,7 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
     // which GEMMs: see layout.hpp.  Without a saved buffer (whose layout is the caller's to read) a handful of rows lie
     // chunk-major, as they are loaded.
     const ForwardPlan plan = plan_forward(Rb, C, I, saved != nullptr, (flags & SKIPFFN_FLAG_BALANCED_SPLIT) != 0, num_cus(),
-                                          rms_gain != nullptr);
+                                          rms_gain != nullptr, skipped.dst != nullptr);
     const bool chunk_major_xn = plan.gate_up == FWD_FEW && saved == nullptr, chunk_major_h = plan.down == FWD_FEW && saved == nullptr;
     const bool by_count = r_dev != nullptr && Rb > 256 && (flags & SKIPFFN_FLAG_BALANCED_SPLIT) == 0;     // countrows.hip
     // (2) gather + RMSNorm, or in the gate/up GEMM

@@ -267,9 +267,13 @@ inline int gate_up_cols(int64_t rows, int64_t I, int ncu) {
 // a gain 92.1 / 71.2 and 98.8 / 76.7);  C = 3072, I = 10752: 8 rows 45.6 / 48.9, 64 rows 57.1 / 59.4.
 // From 33 rows only while all workgroups of 16 columns run at once, each of which forms the squares and the gain's products of all
 // rows:  C = 1024, I = 7168, before it / in the GEMM: 64 rows 30.3 / 31.2, with a gain 30.5 / 36.1, 40 rows with a gain 30.3 / 33.7.
+// Where skipped rows are copied, the kernel before the GEMM is launched for them anyway and normalises beside it; the tiles then gain nothing
+// by doing it themselves, and lose where they are narrow.  8 of 64 rows, before it / in the GEMM:  C = 4096: I = 14336 68.6 / 68.8, I = 8192
+// 44.0 / 47.3;  C = 5120, I = 8192 60.9 / 64.0;  C = 8192: I = 14336 134.5 / 135.5, I = 8192 81.0 / 86.7 (a launch of its own for the norm: 83);
+// 64 of 616: C = 4096, I = 14336 77.6 / 76.2.
 constexpr int64_t kNormInMidRows = 64;
-inline bool norm_in_gate_up(int64_t rows, int64_t C, int64_t I, bool has_gain, bool registers, int ncu) {
-    if (!registers) return rows <= kNormInMidRows && !has_gain;
+inline bool norm_in_gate_up(int64_t rows, int64_t C, int64_t I, bool has_gain, bool copies_skipped, bool registers, int ncu) {
+    if (!registers) return rows <= kNormInMidRows && !has_gain && !copies_skipped;
     return rows <= 16 || (C <= 1024 && (rows <= 32 || (I + 15) / 16 <= ncu));
 }
 
@@ -284,13 +288,13 @@ struct ForwardPlan {
 // most fp32 slabs the down GEMM of `rows` rows may write (fwd_ws has room for them)
 inline int max_down_splits(int64_t rows) { return rows <= 256 ? kMaxSplitsNarrow : kMaxSplits; }
 inline ForwardPlan plan_forward(int64_t rows, int64_t C, int64_t I, bool has_saved, bool balanced, int ncu,
-                                bool has_gain = false) {
+                                bool has_gain = false, bool copies_skipped = false) {
     ForwardPlan p{FWD_CORE, FWD_CORE, false, 1, 64, KPartition{1, 0}};
     if (!balanced && mid_rows(rows, C, I, ncu)) {
         p.gate_up = few_rows_gate_up(rows, C, I, has_saved, has_gain) ? FWD_FEW : FWD_MID;
         if (p.gate_up == FWD_MID && rows <= 256) p.gate_up_splits = gate_up_splits(C, I, ncu);
         if (p.gate_up_splits == 1) p.gate_up_cols = gate_up_cols(rows, I, ncu);
-        p.norm_in_gate_up = !has_saved && p.gate_up_splits == 1 && norm_in_gate_up(rows, C, I, has_gain, p.gate_up == FWD_FEW, ncu);
+        p.norm_in_gate_up = !has_saved && p.gate_up_splits == 1 && norm_in_gate_up(rows, C, I, has_gain, copies_skipped, p.gate_up == FWD_FEW, ncu);
         p.down = few_rows_down(rows, C, I, has_saved, ncu) ? FWD_FEW : mid_rows_down(rows, C, ncu) ? FWD_MID : FWD_CORE;
     }
     const int ktiles = (int)((I + BK - 1) / BK);

@@ -84,6 +84,8 @@ static const char* check_plan(long R, long C, long I, bool hs, bool balanced, in
         (C + BK - 1) / BK > 48 * p.gate_up_splits)
         return "a long K range on an idle chip";
     if ((p.gate_up == FWD_FEW || p.down == FWD_FEW) && R > kFewRowsMax) return "too many rows for the register path";
+    if (p.gate_up == FWD_MID && plan_forward(R, C, I, hs, balanced, ncu, false, true).norm_in_gate_up)
+        return "tiles form the norms beside a launch that could";
     if (p.gate_up == FWD_FEW && p.norm_in_gate_up && R > 32 && (I + 15) / 16 > ncu) return "more workgroups form the norms than run at once";
     // a layer of the widths that the register path takes, too small for tiles of their own: no split K range instead
     if (!hs && !balanced && ncu == 256 && R > 16 && C == 2048 && I >= 2048 && I <= 6144 && R <= kFewRowsMax && p.gate_up != FWD_FEW)
