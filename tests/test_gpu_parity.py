@@ -725,7 +725,7 @@ def test_decode_of_a_wide_layer(R, C, I):
 @pytest.mark.parametrize("R,C,I,gain", [(1, 136, 344, True), (16, 2056, 520, True), (17, 1024, 1032, True), (64, 520, 344, False),
                                         (33, 2056, 7176, False), (64, 4096, 6600, False), (1, 2064, 12296, False)])
 @pytest.mark.parametrize("r_host", [True, False], ids=["R-host", "R-device"])
-def test_norm_inside_the_gate_up_gemm(R, C, I, gain, r_host):
+def test_norm_inside_the_gate_up_gemm(R, C, I, gain, r_host, inplace=False):
     """Without a saved buffer few rows are normalised by the gate/up GEMM, on registers (one, two and four row fragments, K
     ranges that end inside a step) and on 64-row tiles (one row, all of them, ragged K, workgroups that start at different
     slabs): rows 2^-12 to 2^12 times as large as others, one of zeros.  Rows are checked one by one: xn, H and out are
@@ -741,9 +741,16 @@ def test_norm_inside_the_gate_up_gemm(R, C, I, gain, r_host):
     p.hidden = bits_of(p.d_hidden)
     fo = O.skipffn_forward(p.hidden, p.mask, p.wg, p.wu, p.wd, p.gain if gain else None, w.eps, no_residual=True)
     idx, sk = fo["idx"], p.mask != 0
-    got = bits_of(gpu_forward(p, R_host=r_host, saved=False, flags=B.FLAG_NO_RESIDUAL)[0])
+    got = bits_of(gpu_forward(p, R_host=r_host, saved=False, inplace=inplace, flags=B.FLAG_NO_RESIDUAL)[0])
     assert np.array_equal(got[sk], p.hidden[sk])
     assert max_slice_rel_l2(O.bf16_bits_to_f64(got[idx]), O.bf16_bits_to_f64(fo["out_bits"][idx]), axis=1) < REL_L2_TOL
+
+
+@pytest.mark.parametrize("R,C,I", [(33, 2056, 7176), (64, 4096, 6600), (1, 2064, 12296)])
+@pytest.mark.parametrize("r_host", [True, False], ids=["R-host", "R-device"])
+def test_norm_inside_the_gate_up_gemm_in_place(R, C, I, r_host):
+    """The tiles do it where no skipped rows are copied; out of place (above) these sizes are normalised beside the copies."""
+    test_norm_inside_the_gate_up_gemm(R, C, I, False, r_host, inplace=True)
 
 
 @pytest.mark.parametrize("R,C,I", [(65, 4096, 8), (100, 4104, 72), (129, 2056, 264), (200, 4096, 520), (256, 3080, 1032),
