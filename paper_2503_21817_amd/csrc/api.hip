@@ -519,7 +519,7 @@ int skipffn_backward(int64_t T, int64_t C, int64_t I, float eps, const void* gra
     x.ldb = (int)C; x.b_bytes = (uint32_t)(I * C * 2);
     x.pairs = 2;
     x.partial = partial;
-    const DxnPlan plan = plan_dxn(Rb, C, I, (flags & SKIPFFN_FLAG_BALANCED_SPLIT) != 0, r_dev != nullptr, num_cus());
+    const DxnPlan plan = plan_dxn(Rb, C, I, (flags & SKIPFFN_FLAG_BALANCED_SPLIT) != 0, r_dev != nullptr, accum, num_cus());
     x.splits = plan.k.splits;
     const PartialLayout pl{plan.k.splits, plan.k.sk_nbg, 2 * (int)((I + BK - 1) / BK)};
     if (plan.dw_workgroups > 0) {

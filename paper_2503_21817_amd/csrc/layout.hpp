@@ -78,7 +78,7 @@ inline KPartition choose_k_partition(int tiles_m, int tiles_n, int ktiles, bool 
 
 // dXn and dW_gate, dW_up both wait for dG and dU only.  Up to some hundred rows they share a launch: dXn, cut into fewer and
 // longer parts, on the first n0 workgroups (a multiple of 8), lists of dW's tiles on dw_workgroups others, all on the chip at
-// once.  The ends of dXn's parts and the stores of dW then fall into each other's K slabs, and dXn leaves fewer fp32 slabs.
+// once (added gradients apart, see below).  The ends of dXn's parts and the stores of dW then fall into each other's K slabs, and dXn leaves fewer fp32 slabs.
 // dw_workgroups = 0: two launches, each with the chip to itself, which many rows of a wide layer fill as well.  Costs in slabs of
 // dXn; a slab of dW, alone or not, takes 1.15 of one, and the end of a tile 2.5, as bf16 stores do: the type of dW and whether it is
 // added to choose no plan, so that they change no bit of the gradients.  Backward of a layer, us, two launches / one (parts of dXn), bf16 dW:  C = 4096, I = 14336: 32 rows 226 / 197
@@ -87,9 +87,15 @@ inline KPartition choose_k_partition(int tiles_m, int tiles_n, int ktiles, bool 
 // 167 / 150 (6), 1024 rows 209 / 196 (4), 1472 rows 295 / 277 (3);  C = 1024, I = 3584: 64 rows 69 / 59 (8), 368 rows 90 / 75
 // (8), 2944 rows 198 / 165 (3).  With less than 8 % to gain by these costs it measured from 6 % faster to 5 %
 // slower, and is left.
+// Gradients that are added to are read at the end of a tile before they are written, and dXn's workgroups are through long before
+// lists on the rest of the chip.  There every tile of dW is a workgroup, so that the CUs of dXn take their part (the same sums).  Two launches /
+// lists / a workgroup a tile, added to fp32 gradients:  C = 5120, I = 17920, 1 row 762 / 931 / 725;  C = 4096, I = 14336: 100 rows
+// 496 / 551 / 477, 256 rows 552 / 548 / 511;  C = 8192, I = 8192, 184 rows 613 / 618 / 615;  C = 2048, I = 7168, 600 rows 232 / 234 /
+// 210, to bf16 ones 191 / 179 / 172.  Overwritten gradients are faster in lists, whose stores overlap:  C = 4096, I = 14336, 184 rows,
+// bf16 272 / 235 / 254, fp32 350 / 315 / 328.
 constexpr double kDwTileEnd = 2.5;
 struct DxnPlan { KPartition k; int n0, dw_workgroups; };
-inline DxnPlan plan_dxn(int64_t rows, int64_t C, int64_t I, bool balanced, bool count_on_device, int ncu) {
+inline DxnPlan plan_dxn(int64_t rows, int64_t C, int64_t I, bool balanced, bool count_on_device, bool accumulate, int ncu) {
     const int tiles_m = (int)((rows + BM - 1) / BM), tiles_n = (int)((C + BN - 1) / BN);
     const int tiles = tiles_m * tiles_n, ktiles = 2 * (int)((I + BK - 1) / BK);
     double cost = 0.0;
@@ -108,7 +114,7 @@ inline DxnPlan plan_dxn(int64_t rows, int64_t C, int64_t I, bool balanced, bool 
         const int n1 = std::min((ncu - n0) / 8 * 8, whole);
         if (count_on_device && n1 < whole) continue;         // the rows there are may leave dXn's workgroups without work
         const double c = std::max(per + (s > 1 ? 16.0 : 8.0) + 0.04 * s * tiles, dw_cost(n1));
-        if (c < best - 1e-9) { best = c; p = DxnPlan{KPartition{s, 0}, n0, n1}; }
+        if (c < best - 1e-9) { best = c; p = DxnPlan{KPartition{s, 0}, n0, accumulate ? whole : n1}; }
     }
     return p;
 }

@@ -212,15 +212,15 @@ int main() {
                     if (const char* what = check_row_plans(bound, C, I, ncu)) return fail(what, bound, C, I, ncu);
                     ++cases;
                 }
-    // dXn beside dW_gate and dW_up: all workgroups on the chip at once, every part of K with slabs, no more of them than the
-    // workspace holds
+    // dXn beside dW_gate and dW_up: all workgroups on the chip at once (a workgroup a tile where gradients are added to), every part of K with
+    // slabs, no more of them than the workspace holds
     for (int ncu : ncus)
         for (long C : widths)
             for (long I : widths)
                 for (long R = 1; R <= 16384; R += R < 300 ? 1 : R / 16)
-                    for (int variant = 0; variant < 4; ++variant) {
-                        const bool forced = variant & 1, on_device = variant & 2;
-                        const DxnPlan p = plan_dxn(R, C, I, forced, on_device, ncu);
+                    for (int variant = 0; variant < 8; ++variant) {
+                        const bool forced = variant & 1, on_device = variant & 2, added = variant & 4;
+                        const DxnPlan p = plan_dxn(R, C, I, forced, on_device, added, ncu);
                         const long tiles = (R + BM - 1) / BM * ((C + BN - 1) / BN), dw = (I + BM - 1) / BM * ((C + BN - 1) / BN) * 2;
                         const int ktiles = 2 * (int)((I + BK - 1) / BK), s = p.k.splits;
                         if (s < 1 || s > kMaxSplits || (s - 1) * ((ktiles + s - 1) / s) >= ktiles) return fail("split of dXn", R, C, I, ncu);
@@ -230,8 +230,11 @@ int main() {
                         if (d > 1 && (forced || (size_t)d * R * I * 4 > W.gainp - W.partial)) return fail("the slabs of dH do not fit", R, C, I, ncu);
                         if (p.dw_workgroups > 0) {
                             if (forced || p.k.sk_nbg != 0) return fail("the balanced split shares no launch", R, C, I, ncu);
-                            if (p.n0 % 8 || p.n0 < tiles * s || p.dw_workgroups % 8 || p.n0 + p.dw_workgroups > ncu)
+                            if (p.n0 % 8 || p.n0 < tiles * s || p.dw_workgroups % 8 || (!added && p.n0 + p.dw_workgroups > ncu))
                                 return fail("workgroups of dXn and dW", R, C, I, ncu);
+                            if (added && p.dw_workgroups < dw) return fail("lists of gradients that are added to", R, C, I, ncu);
+                            const DxnPlan q = plan_dxn(R, C, I, forced, on_device, false, ncu);
+                            if (q.k.splits != p.k.splits || q.n0 != p.n0) return fail("the sums of dXn by the type of dW", R, C, I, ncu);
                             if (on_device && p.dw_workgroups < dw) return fail("lists of dW by the bound of the rows", R, C, I, ncu);
                         }
                         ++cases;
