@@ -93,6 +93,10 @@ inline KPartition choose_k_partition(int tiles_m, int tiles_n, int ktiles, bool 
 // 496 / 551 / 477, 256 rows 552 / 548 / 511;  C = 8192, I = 8192, 184 rows 613 / 618 / 615;  C = 2048, I = 7168, 600 rows 232 / 234 /
 // 210, to bf16 ones 191 / 179 / 172.  Overwritten gradients are faster in lists, whose stores overlap:  C = 4096, I = 14336, 184 rows,
 // bf16 272 / 235 / 254, fp32 350 / 315 / 328.
+// A count on the device, far below its bound as a rule, leaves most of dXn's workgroups without work and the others a chain as long as
+// the bound's plan made it; so one launch has to gain at every row of tiles below the bound.  Two launches / one by the bound alone / now:
+// C = 1024: I = 1024, bound 2112, 264 rows 84 / 90 / 76, I = 3584, bound 7248, 906 rows 152 / 180 / two launches again;  C = 512,
+// I = 1024, bound 4160, 520 rows 80 / 83 / 68;  C = 256, I = 896, bound 2720, 340 rows 62 / 71 / 57.
 constexpr double kDwTileEnd = 2.5;
 struct DxnPlan { KPartition k; int n0, dw_workgroups; };
 inline DxnPlan plan_dxn(int64_t rows, int64_t C, int64_t I, bool balanced, bool count_on_device, bool accumulate, int ncu) {
@@ -103,17 +107,28 @@ inline DxnPlan plan_dxn(int64_t rows, int64_t C, int64_t I, bool balanced, bool 
     if (balanced || tiles <= 0) return p;
     const int dw_tiles = (int)((I + BM - 1) / BM) * tiles_n * 2, dw_slabs = (int)((rows + BK - 1) / BK);
     const int whole = (dw_tiles + 7) / 8 * 8;                // a workgroup for every tile
-    auto dw_cost = [&](int workgroups) {
-        return 1.15 * ((dw_tiles + workgroups - 1) / workgroups * (dw_slabs + kDwTileEnd) + 8.0);
+    auto dw_cost = [&](int workgroups, int slabs) {
+        return 1.15 * ((dw_tiles + workgroups - 1) / workgroups * (slabs + kDwTileEnd) + 8.0);
     };
-    double best = 0.92 * (cost + dw_cost(std::min(whole, ncu)));
+    // whether any count below the bound, by these costs, gains less than that over two launches
+    const KPartition two = p.k;
+    auto longer_below = [&](int s, int n1) {
+        for (int t = 1; t < tiles_m; ++t) {
+            const int slabs = t * (BM / BK);
+            const double one = std::max((ktiles + s - 1) / s + (s > 1 ? 16.0 : 8.0) + 0.04 * s * t * tiles_n, dw_cost(n1, slabs));
+            if (one > 0.92 * (k_partition_cost(two, t, tiles_n, ktiles, ncu) + dw_cost(std::min(whole, ncu), slabs))) return true;
+        }
+        return false;
+    };
+    double best = 0.92 * (cost + dw_cost(std::min(whole, ncu), dw_slabs));
     for (int s = 1; s <= kMaxSplits; ++s) {
         const int per = (ktiles + s - 1) / s, n0 = (tiles * s + 7) / 8 * 8;
         if ((s > 1 && per < 4) || n0 > ncu - 8) break;
         if ((s - 1) * per >= ktiles) continue;
         const int n1 = std::min((ncu - n0) / 8 * 8, whole);
         if (count_on_device && n1 < whole) continue;         // the rows there are may leave dXn's workgroups without work
-        const double c = std::max(per + (s > 1 ? 16.0 : 8.0) + 0.04 * s * tiles, dw_cost(n1));
+        const double c = std::max(per + (s > 1 ? 16.0 : 8.0) + 0.04 * s * tiles, dw_cost(n1, dw_slabs));
+        if (count_on_device && longer_below(s, n1)) continue;
         if (c < best - 1e-9) { best = c; p = DxnPlan{KPartition{s, 0}, n0, accumulate ? whole : n1}; }
     }
     return p;

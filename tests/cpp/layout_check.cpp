@@ -5,6 +5,7 @@
 // call the very plan it launches - stays within the partial-slab budget the workspaces are sized for.  A byte map of each buffer is
 // painted section by section, so an overlap or an overrun is also a sanitizer report.
 // Prints "ok <cases>" or the first violation.
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -235,6 +236,10 @@ int main() {
                             if (added && p.dw_workgroups < dw) return fail("lists of gradients that are added to", R, C, I, ncu);
                             const DxnPlan q = plan_dxn(R, C, I, forced, on_device, false, ncu);
                             if (q.k.splits != p.k.splits || q.n0 != p.n0) return fail("the sums of dXn by the type of dW", R, C, I, ncu);
+                            const int slabs = std::min<int>(BM, R) / BK + 3, n = (int)((C + BN - 1) / BN);
+                            const KPartition two = choose_k_partition((int)((R + BM - 1) / BM), n, ktiles, false, ncu);
+                            if (on_device && (ktiles + s - 1) / s > k_partition_cost(two, 1, n, ktiles, ncu) + 1.15 * ((dw + ncu - 1) / ncu * slabs + 8))
+                                return fail("a chain of dXn as the bound's rows have it, for few rows", R, C, I, ncu);
                             if (on_device && p.dw_workgroups < dw) return fail("lists of dW by the bound of the rows", R, C, I, ncu);
                         }
                         ++cases;
