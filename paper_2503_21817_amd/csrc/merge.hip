@@ -165,52 +165,103 @@ __global__ __launch_bounds__(32 * LANES) void merge_sum_kernel(const float* __re
     column_sum<LANES>(part + merge_part_row(st, set, 0) * C, (n + MERGE_CHUNK - 1) / MERGE_CHUNK, C, s + (int64_t)set * C, 0);
 }
 
+// The same sums (lane by lane, added in the same order) where there are sets and columns enough for a workgroup of a quarter of the
+// threads and four times the columns, up to 4 * LANES partial rows: all of them in flight at once.  36 sets of 377 x 4096: 14.1 -> 6.6 us,
+// 29 of 310 x 2048 9 -> 4.0.
+template <int LANES>
+__global__ __launch_bounds__(256) void merge_sum_wide_kernel(const float* __restrict__ part, SegTable st, int C, float* __restrict__ s) {
+    const int set = blockIdx.y, n = st.off[set + 1] - st.off[set];
+    if (n <= 0) return;
+    constexpr int V = LANES / 8;
+    __shared__ f32x4 lanes[LANES][32];
+    const int rows = (n + MERGE_CHUNK - 1) / MERGE_CHUNK, cx = threadIdx.x & 31, sy = threadIdx.x >> 5;
+    const int q = (int)blockIdx.x * 32 + cx;             // columns 4 q .. 4 q + 3
+    const f32x4* p = reinterpret_cast<const f32x4*>(part + merge_part_row(st, set, 0) * C) + q;
+    const f32x4 zero{0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4 x[V][4];
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int row = sy + 8 * v + k * LANES;
+            x[v][k] = q < C >> 2 && row < rows ? p[(int64_t)row * (C >> 2)] : zero;
+        }
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+        lanes[sy + 8 * v][cx] = sy + 8 * v + 3 * LANES < rows ? (x[v][0] + x[v][1]) + (x[v][2] + x[v][3]) : (x[v][0] + x[v][1]) + x[v][2];
+    __syncthreads();
+    if (sy == 0 && q < C >> 2) {
+        f32x4 v = zero;
+#pragma unroll
+        for (int k = 0; k < LANES; ++k) v += lanes[k][cx];
+        reinterpret_cast<f32x4*>(s + (int64_t)set * C)[q] = v;
+    }
+}
+
 // ---- avg_i = xn_i . (s - xn_i) / (n - 1), two rows per wavefront ------------------------------------
 // SMALL: s is added here, from the partial rows (`s` points at them), at most MG_FEW_PARTS: sets of few tokens are bound by their
-// launches.  200 sets of 16 tokens of 256 columns, four groups of launches: 94 -> 84 us a call, of 8192 columns 302 -> 278.
+// launches.  200 sets of 16 tokens of 256 columns, four groups of launches: 94 -> 84 us a call, of 8192 columns 302 -> 278.  The partial
+// rows are loaded together: 17 sets of 31 x 5912 17.4 -> 11.4 us.
 constexpr int MG_FEW_PARTS = 4;
 template <bool SMALL>
 __global__ __launch_bounds__(MG_THREADS) void merge_average_kernel(const bf16_t* __restrict__ xn, SegTable st, int C,
                                                                    const float* __restrict__ s, float* __restrict__ avg) {
+    constexpr int ROWS = 2;
     const int set = blockIdx.y, lo = st.off[set], n = st.off[set + 1] - lo;
-    const int lane = threadIdx.x & 63, i = (int)blockIdx.x * 8 + (threadIdx.x >> 6) * 2;
+    const int lane = threadIdx.x & 63, i = ((int)blockIdx.x * 4 + (threadIdx.x >> 6)) * ROWS;
     if (i >= n) return;
     const int chunks = C >> 3;
-    const u32x4* p0 = reinterpret_cast<const u32x4*>(xn + (int64_t)(lo + i) * C);
-    const u32x4* p1 = i + 1 < n ? p0 + chunks : p0;
+    const u32x4* row[ROWS];
+    float d[ROWS];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        row[r] = reinterpret_cast<const u32x4*>(xn + (int64_t)(lo + i + (i + r < n ? r : 0)) * C);
+        d[r] = 0.0f;
+    }
     const f32x4* ps = reinterpret_cast<const f32x4*>(s + (SMALL ? merge_part_row(st, set, 0) : (int64_t)set) * C);
     const int parts = SMALL ? (n + MERGE_CHUNK - 1) / MERGE_CHUNK : 1;
     auto sum_at = [&](int q) {                           // columns 4 q .. 4 q + 3
         f32x4 v = ps[q];
-        if (SMALL)
-            for (int p = 1; p < parts; ++p) v += ps[(int64_t)p * (C >> 2) + q];
+        if (SMALL) {
+            f32x4 more[MG_FEW_PARTS];                    // in flight together; past the parts the first one again, not added
+#pragma unroll
+            for (int p = 1; p < MG_FEW_PARTS; ++p) more[p] = ps[(int64_t)(p < parts ? p : 0) * (C >> 2) + q];
+#pragma unroll
+            for (int p = 1; p < MG_FEW_PARTS; ++p)
+                if (p < parts) v += more[p];
+        }
         return v;
     };
-    float d0 = 0.0f, d1 = 0.0f;
-    auto add = [&](const u32x4& a, const u32x4& b, const f32x4& lo4, const f32x4& hi4) {
-        float x0[8], x1[8];
-        unpack8s(a, x0);
-        unpack8s(b, x1);
+    auto add = [&](float& dr, const u32x4& raw, const f32x4& lo4, const f32x4& hi4) {
+        float x[8];
+        unpack8s(raw, x);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const float t = j < 4 ? lo4[j & 3] : hi4[j & 3];
-            d0 += x0[j] * (t - x0[j]);
-            d1 += x1[j] * (t - x1[j]);
-        }
+        for (int j = 0; j < 8; ++j) dr += x[j] * ((j < 4 ? lo4[j & 3] : hi4[j & 3]) - x[j]);
     };
     int c = lane;
     for (; c + 64 < chunks; c += 128) {
-        const u32x4 a0 = p0[c], a1 = p0[c + 64], b0 = p1[c], b1 = p1[c + 64];
+        u32x4 a[2][ROWS];
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            a[0][r] = row[r][c];
+            a[1][r] = row[r][c + 64];
+        }
         const f32x4 l0 = sum_at(2 * c), h0 = sum_at(2 * c + 1), l1 = sum_at(2 * c + 128), h1 = sum_at(2 * c + 129);
-        add(a0, b0, l0, h0);
-        add(a1, b1, l1, h1);
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            add(d[r], a[0][r], l0, h0);
+            add(d[r], a[1][r], l1, h1);
+        }
     }
-    if (c < chunks) add(p0[c], p1[c], sum_at(2 * c), sum_at(2 * c + 1));
-    d0 = wave_sum(d0);
-    d1 = wave_sum(d1);
-    if (lane == 0) {
-        avg[lo + i] = n > 1 ? d0 / (float)(n - 1) : 0.0f;
-        if (i + 1 < n) avg[lo + i + 1] = d1 / (float)(n - 1);
+    if (c < chunks) {
+        const f32x4 l0 = sum_at(2 * c), h0 = sum_at(2 * c + 1);
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) add(d[r], row[r][c], l0, h0);
+    }
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        const float v = wave_sum(d[r]);
+        if (lane == 0 && i + r < n) avg[lo + i + r] = n > 1 ? v / (float)(n - 1) : 0.0f;
     }
 }
 
@@ -556,17 +607,21 @@ hipError_t launch_merge_group(const bf16_t* x, const SegTable& st, int n_max, in
         else if (chunks <= 1024) hipLaunchKernelGGL(merge_normalize_kernel<16>, rows, threads, MG_PIECE * 16, s, x, st, C, ws.xn, ws.part);
         else hipLaunchKernelGGL(merge_normalize_kernel<0>, rows, threads, lds, s, x, st, C, ws.xn, ws.part);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        const dim3 pairs((unsigned)((n_max + 7) / 8), sets);
         if (parts <= MG_FEW_PARTS) {
-            hipLaunchKernelGGL(merge_average_kernel<true>, pairs, threads, 0, s, ws.xn, st, C, ws.part, avg);
+            hipLaunchKernelGGL(merge_average_kernel<true>, rows, threads, 0, s, ws.xn, st, C, ws.part, avg);
         } else {
-            const dim3 cols((unsigned)((C + 31) / 32), sets);
-            if (parts <= COLSUM_FEW_ROWS)
+            const dim3 cols((unsigned)((C + 31) / 32), sets), wide((unsigned)((C + 127) / 128), sets);
+            const bool few = parts <= COLSUM_FEW_ROWS;
+            if (parts <= 4 * COLSUM_LANES && (int64_t)wide.x * sets >= ncu) {
+                if (few) hipLaunchKernelGGL(merge_sum_wide_kernel<COLSUM_LANES_FEW>, wide, threads, 0, s, ws.part, st, C, ws.sum);
+                else hipLaunchKernelGGL(merge_sum_wide_kernel<COLSUM_LANES>, wide, threads, 0, s, ws.part, st, C, ws.sum);
+            } else if (few) {
                 hipLaunchKernelGGL(merge_sum_kernel<COLSUM_LANES_FEW>, cols, dim3(32 * COLSUM_LANES_FEW), 0, s, ws.part, st, C, ws.sum);
-            else
+            } else {
                 hipLaunchKernelGGL(merge_sum_kernel<COLSUM_LANES>, cols, dim3(32 * COLSUM_LANES), 0, s, ws.part, st, C, ws.sum);
+            }
             if ((e = hipGetLastError()) != hipSuccess) return e;
-            hipLaunchKernelGGL(merge_average_kernel<false>, pairs, threads, 0, s, ws.xn, st, C, ws.sum, avg);
+            hipLaunchKernelGGL(merge_average_kernel<false>, rows, threads, 0, s, ws.xn, st, C, ws.sum, avg);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }

@@ -129,6 +129,15 @@ def test_averages_of_few_tokens(lens, C, k):
     check(xb, [0] + np.cumsum(lens).tolist(), k)
 
 
+@pytest.mark.parametrize("lens,C,k", [((1024, 800, 769, 8), 8200, 20), ((256, 200, 193, 40), 8200, 20), ((300, 257, 0, 33) * 16, 520, 30)],
+                         ids=["past-96-rows", "past-24-rows", "many-sets"])
+def test_wide_sums(lens, C, k):
+    """Sums of partial rows with all rows of a lane in flight: three and four of them, fewer, and none; a last column group cut off."""
+    rng = np.random.default_rng(sum(lens) + C + 6)
+    xb = O.f64_to_bf16_bits(rng.standard_normal((sum(lens), C)) + 0.5 * rng.standard_normal((1, C)))
+    check(xb, [0] + np.cumsum(lens).tolist(), k)
+
+
 def test_merge_clustered_tokens_small_margins_inside_clusters():
     xb = clustered(500, 512, centers=40, noise=0.05, seed=3)
     check(xb, [0, 200, 500], 60)
