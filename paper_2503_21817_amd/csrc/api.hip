@@ -365,10 +365,10 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
         a.splits = kp.splits;
         a.idx = idx; a.ldo = (int)C; a.ncu = num_cus();
         a.no_residual = no_residual;
+        int64_t sum_rows = 0;
+        const RowPlans plans = by_count ? plan_rows(Rb, C, I, num_cus(), &sum_rows) : RowPlans{};
         profile_mark_begin(KC_GEMM_DOWN, s);
-        if (by_count) {
-            int64_t sum_rows = 0;
-            const RowPlans plans = plan_rows(Rb, C, I, num_cus(), &sum_rows);
+        if (sum_rows > 0) {
             a.out0 = out; a.e0 = static_cast<const bf16_t*>(hidden); a.partial = partial;
             e = launch_down_count(a, plans, s);
             profile_mark_end(KC_GEMM_DOWN, s);

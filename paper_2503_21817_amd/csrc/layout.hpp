@@ -334,7 +334,11 @@ inline ForwardPlan plan_forward(int64_t rows, int64_t C, int64_t I, bool has_sav
 // 4200, 2100 rows 73.6 / 79.7 / 73;  bound 4928, 2464 rows 85 / 91 / 84;  C = 512, I = 2048: bound 4928, 2464 rows 45.3 / 49.5 / 45;
 // C = 4096, I = 4096: bound 9856, 4928 rows, with a saved buffer 473 / 490 / 472;  C = 4096, I = 14336: bound 2944, 736 rows 260 / 240 / 240.
 // sum_rows: the most rows whose plan leaves slabs, 256 at least (their tiles always do).  A reducing launch for the bound cost
-// up to 9 us of workgroups without work:  C = 8192, I = 1024: bound 9856, 4928 rows, with a saved buffer 360 / 370 / 358.
+// up to 9 us of workgroups without work:  C = 8192, I = 1024: bound 9856, 4928 rows, with a saved buffer 360 / 370 / 358.  0 where no
+// plan of more than 256 rows leaves slabs: the core adds to the rows itself and nothing follows it, as without these plans.  A reducing
+// launch that has nothing to do took 4.6 us, more than the tiles of all rows save up to 256:  C = 4096, I = 512, bound 4200, of the
+// count with it / without any: 1000 rows 68.5 / 63.4, 3800 rows 91.6 / 84.6, 200 rows 62.7 / 59.6, 60 rows 57.0 / 56.0;  C = 512,
+// I = 512, bound 12000, 2442 rows 40.1 / 35.7, 200 rows 30.3 / 30.5.
 constexpr int kRowPlans = 64;                            // 16384 rows; the bound's plan beyond
 constexpr uint16_t kRowPlanBalanced = 0x8000;
 struct RowPlans { int mid_splits; uint16_t beyond, down[kRowPlans]; };
@@ -359,7 +363,7 @@ inline RowPlans plan_rows(int64_t bound, int64_t C, int64_t I, int ncu, int64_t*
     p.down[0] = 1;                                       // up to 256 rows: tiles of all rows
     for (int t = 2; t <= kRowPlans; ++t) p.down[t - 1] = t <= tiles_m ? code(t) : 1;
     p.beyond = tiles_m > kRowPlans ? code(tiles_m) : 1;
-    if (sum_rows != nullptr) *sum_rows = std::min<int64_t>(bound, (int64_t)last * BM);
+    if (sum_rows != nullptr) *sum_rows = last > 1 ? std::min<int64_t>(bound, (int64_t)last * BM) : 0;
     return p;
 }
 

@@ -40,9 +40,11 @@ static const char* check_row_plans(long bound, long C, long I, int ncu) {
         if ((size_t)kMaxSplits * slab > room) return "the slabs of a count do not fit";
     }
     if ((p.mid_splits - 1) * ((ktiles + p.mid_splits - 1) / p.mid_splits) >= ktiles) return "an empty part of up to 256 rows";
-    if (sum_rows < 256 || sum_rows > bound) return "rows of the reducing launch";
+    if (sum_rows != 0 && (sum_rows < 256 || sum_rows > bound)) return "rows of the reducing launch";
+    bool slabs = false;
     for (int t = 2; t <= tiles_m; ++t) {
         const KPartition k = row_plan(p, t);
+        slabs = slabs || k.sk_nbg > 0 || k.splits > 1;
         if (k.sk_nbg > 0 || k.splits > 1)
             if (sum_rows < std::min<long>(bound, (long)t * BM)) return "slabs past the rows of the reducing launch";
         if (t > kRowPlans && t < tiles_m) {
@@ -58,6 +60,7 @@ static const char* check_row_plans(long bound, long C, long I, int ncu) {
             return "split of a count";
         }
     }
+    if (slabs != (sum_rows > 0)) return "a reducing launch without slabs, or slabs without one";
     const KPartition own = choose_k_partition(tiles_m, tiles_n, ktiles, false, ncu), b = row_plan(p, tiles_m);
     return b.splits != own.splits || b.sk_nbg != own.sk_nbg ? "the bound's own plan" : nullptr;
 }
