@@ -1,7 +1,13 @@
 // The forward GEMMs of a layer whose row count is on the device, far below its bound as a rule (the bound is the number of
 // tokens, the count that of the retained ones).  The host can plan for the bound only: these kernels hold the paths of all counts
-// and take the one that a call with the count on the host would launch.  Everything about a path stands where it is
+// and take the one that the count wants: tiles of all rows up to 256 (also of a handful, which a call with the count on the host
+// would run on registers), lists of tiles or the balanced split beyond.  Everything about a path stands where it is
 // (midrows.hpp, stream.hpp); the reducing kernel reads the same plans (rowops.hip).
+//
+// Gate/up of more than 16384 columns or so is more tiles of all rows than the chip holds at once, and from 129 rows their second round costs more
+// than tiles of 128 rows that read the weights twice.  Layer forward, us, tiles of all rows / lists:  C = 5120, I = 20480: 154 rows 200 / 183,
+// 250 rows 247 / 220;  C = 4096, I = 17408: 154 rows 137 / 130, 250 rows 169 / 152;  C = 1024, I = 24576, 200 rows 77 / 71;
+// up to 128 rows (100, C = 5120, I = 20480) the tiles of all rows take 165, the bound's plan 179.
 //
 // One kernel for all paths, although the longer ones set its registers (the arguments of all paths are loaded at the start and
 // some spill, outside the loops): a kernel for each, of which all but one leave at once, cost 4.5 us an idle launch.  The
@@ -26,10 +32,10 @@ __device__ __forceinline__ void mid_rows_of_count(const MidRowsArgs& M, const in
     else mid_rows_tile<16, GATE_UP>(M, block);
 }
 
-// lists: workgroups that run lists of tiles; mid: workgroups of the tiles of all rows
-__global__ __launch_bounds__(GEMM_THREADS) void gate_up_count_kernel(GemmArgs P, MidRowsArgs M, int lists, int mid) {
+// lists: workgroups that run lists of tiles; mid: workgroups of the tiles of all rows, which take up to mid_max rows
+__global__ __launch_bounds__(GEMM_THREADS) void gate_up_count_kernel(GemmArgs P, MidRowsArgs M, int lists, int mid, int mid_max) {
     const int rows = uniform(effective_rows(P.M, P.m_dev)), block = (int)blockIdx.x;
-    if (rows <= 256) {
+    if (rows <= mid_max) {
         if (block < mid) mid_rows_of_count<true>(M, rows, block);
     } else if (block < lists) {
         stream_rows<EPI_SWIGLU>(P, stream_plan_of_count<EPI_SWIGLU>(P, 1, lists), 1, block, lists);
@@ -72,8 +78,9 @@ hipError_t launch_gate_up_count(GemmArgs& a, hipStream_t s) {
     const MidRowsArgs m = mid_rows_gate_up_args(a.A0, a.M, a.m_dev, a.K, a.N, a.B0, a.B1, static_cast<bf16_t*>(a.out0), nullptr,
                                                 nullptr, false, gate_up_cols(256, a.N, a.ncu));
     const int lists = list_workgroups(a), mid = (a.N + m.cols - 1) / m.cols;
+    const int mid_max = mid <= a.ncu ? 256 : 128;
     hipLaunchKernelGGL(gate_up_count_kernel, dim3((unsigned)std::max(lists, mid)), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a, m,
-                       lists, mid);
+                       lists, mid, mid_max);
     return hipGetLastError();
 }
 

@@ -597,7 +597,8 @@ def test_device_row_count_far_below_the_bound(R, T):
 @pytest.mark.parametrize("R,T,C,I", [(0, 300, 520, 8200), (1, 300, 520, 8200), (64, 400, 520, 8200), (65, 700, 520, 8200),
                                      (129, 700, 1032, 2056), (193, 3000, 1032, 2056), (256, 3000, 520, 8200), (257, 3000, 520, 8200),
                                      (700, 3000, 1032, 2056), (5500, 6000, 520, 8200), (400, 4000, 2056, 1032),
-                                     (600, 4000, 2056, 1032), (16450, 16700, 264, 520)])
+                                     (600, 4000, 2056, 1032), (16450, 16700, 264, 520),
+                                     (128, 500, 264, 16520), (129, 500, 264, 16520), (256, 500, 264, 16520)])
 def test_every_path_of_a_device_row_count(R, T, C, I):
     """Inference with the count on the device and a bound for which the core runs: tiles of all rows of each height (the smallest
     and largest count of some, no row at all), K cut evenly, balanced (5500 rows) and whole, row counts past the list of
