@@ -333,6 +333,10 @@ inline ForwardPlan plan_forward(int64_t rows, int64_t C, int64_t I, bool has_sav
 // lost to the bound's of few.  Layer forward, us, plan of the bound / of the count at 0.04 / of the two:  C = 1024, I = 3584: bound
 // 4200, 2100 rows 73.6 / 79.7 / 73;  bound 4928, 2464 rows 85 / 91 / 84;  C = 512, I = 2048: bound 4928, 2464 rows 45.3 / 49.5 / 45;
 // C = 4096, I = 4096: bound 9856, 4928 rows, with a saved buffer 473 / 490 / 472;  C = 4096, I = 14336: bound 2944, 736 rows 260 / 240 / 240.
+// Where the tiles fill half the chip, plans that do not balance K are priced with their lowered tiles, 3 % of doubt apart (fewer tiles
+// do not shorten a call by being lower: counted there too, a bound's whole K lost up to 25 %).  Layer forward, us, plan of the bound / of the count
+// without / with it:  C = 3072: I = 12288, bound 4239, 3261 rows 554 / 587 / 560, I = 10752, bound 4048, 3114 rows 496 / 524 / 497;  C = 8192,
+// I = 4096, bound 2963, 898 rows now 201, without 209.
 // sum_rows: the most rows whose plan leaves slabs, 256 at least (their tiles always do).  A reducing launch for the bound cost
 // up to 9 us of workgroups without work:  C = 8192, I = 1024: bound 9856, 4928 rows, with a saved buffer 360 / 370 / 358.  0 where no
 // plan of more than 256 rows leaves slabs: the core adds to the rows itself and nothing follows it, as without these plans.  A reducing
@@ -352,11 +356,19 @@ inline RowPlans plan_rows(int64_t bound, int64_t C, int64_t I, int ncu, int64_t*
     p.mid_splits = choose_k_split((int)((C + 127) / 128), ktiles, kMaxSplitsNarrow, ncu);
     const KPartition of_bound = choose_k_partition(tiles_m, tiles_n, ktiles, false, ncu);
     int last = 1;                                        // row of tiles with slabs
+    auto half_full = [&](int t) { return 2 * t * tiles_n >= ncu; };
+    auto cost_at = [&](KPartition k, int t) {
+        const double c = k_partition_cost(k, t, tiles_n, ktiles, ncu, 0.12 * (t - 1) / t);
+        const int n = t * tiles_n * k.splits, tall = (n + ncu - 1) / ncu * stream_tile_cost(8) + n / 16 * stream_tile_cost(8) / ncu;
+        int low = tall;
+        if (k.sk_nbg == 0 && half_full(t))
+            stream_rows_plan(t * BM - BM / 2, tiles_n * k.splits, (ktiles + k.splits - 1) / k.splits, ncu, false, false, &low);
+        return c * low / tall;
+    };
     auto code = [&](int t) {
         KPartition k = choose_k_partition(t, tiles_n, ktiles, false, ncu);
-        const double slab = 0.12 * (t - 1) / t;
         const bool same = k.splits == of_bound.splits && k.sk_nbg == of_bound.sk_nbg;
-        if (!same && k_partition_cost(of_bound, t, tiles_n, ktiles, ncu, slab) <= k_partition_cost(k, t, tiles_n, ktiles, ncu, slab)) k = of_bound;
+        if (!same && cost_at(of_bound, t) <= (half_full(t) ? 0.97 : 1.0) * cost_at(k, t)) k = of_bound;
         if (k.sk_nbg > 0 || k.splits > 1) last = t;
         return (uint16_t)(k.sk_nbg > 0 ? kRowPlanBalanced | k.sk_nbg : k.splits);
     };

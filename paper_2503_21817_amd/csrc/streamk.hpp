@@ -144,13 +144,15 @@ SKIPFFN_HD inline bool streamk_next(const StreamKPlan& p, StreamKIter& it, Strea
 // tall tile's 256 KB about 26 us, its slabs 1.35 us each) and all stores are more than the last-level cache of 256 MB takes in,
 // low tiles only shorten the runs in which the transposed copy is written.  C = 520, I = 28672 (9 slabs), 192-row tiles / 256, us:
 // 1300 rows 162 / 147, 1700 rows 216 / 174, 2000 rows 279 / 191; below that size 300 rows 41 / 47.  16 slabs (C = 1024) are even.
+// cost_of: what all rounds of the best one cost, in units of 0.5 us a tile of 64 slabs.
 struct StreamRows { int full, mi; };
 SKIPFFN_HD inline int stream_tile_cost(int mi) { return 68 + 13 * mi; }       // 64 slabs, in units of 0.5 us
-SKIPFFN_HD inline StreamRows stream_rows_plan(int rows, int columns, int slabs, int cus, bool even, bool two_parts) {
+SKIPFFN_HD inline StreamRows stream_rows_plan(int rows, int columns, int slabs, int cus, bool even, bool two_parts, int* cost_of = nullptr) {
     const int tall = stream_tile_cost(8);
     StreamRows best{(rows + 255) / 256, 0};
     int n = best.full * columns;
     int best_cost = (n + cus - 1) / cus * tall + n / 16 * tall / cus;
+    if (cost_of != nullptr) *cost_of = best_cost;
     if (even && slabs <= 12 && (int64_t)rows * columns > 256 * 1024) return best;
     for (int mi = 7; mi >= 4; --mi) {
         if (even && (mi & 1)) continue;
@@ -172,8 +174,9 @@ SKIPFFN_HD inline StreamRows stream_rows_plan(int rows, int columns, int slabs, 
             if (full == 1) head = head > read ? head : read;
         }
         const int cost = head + tail + 640 / (slabs > 0 ? slabs : 1) + (full * columns / 16 * tall + columns / 16 * low) / cus;
-        if (cost < best_cost) best = StreamRows{full, mi};
+        if (cost < best_cost) { best = StreamRows{full, mi}; best_cost = cost; }
     }
+    if (cost_of != nullptr) *cost_of = best_cost;
     return best;
 }
 
