@@ -629,16 +629,7 @@ hipError_t launch_merge_group(const bf16_t* x, const SegTable& st, int n_max, in
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (k <= 0) return hipSuccess;
     if (n_max > k) {
-        // rounds of the chip's CUs times the time of a slab, which the rows of its operands set (in units of 3.5 cycles a row)
-        const int nd = n_max - k;
-        int best = 0;
-        int64_t best_cost = 0;
-        const int a[3] = {128, 64, 64}, b[3] = {128, 128, 64};
-        for (int q = 0; q < 3; ++q) {
-            const int64_t tiles = (int64_t)((nd + a[q] - 1) / a[q]) * ((k + b[q] - 1) / b[q]) * st.count;
-            const int64_t cost = (tiles + 255) / 256 * (60 + a[q] + b[q]);
-            if (q == 0 || cost < best_cost) { best = q; best_cost = cost; }
-        }
+        const int nd = n_max - k, best = merge_target_tile(nd, k, st.count, ncu);
         if (best == 0) launch_target<128, 128>(ws.xn, st, nd, k, C, k, set_base, ws.dropped, kept_idx, goal, s);
         else if (best == 1) launch_target<64, 128>(ws.xn, st, nd, k, C, k, set_base, ws.dropped, kept_idx, goal, s);
         else launch_target<64, 64>(ws.xn, st, nd, k, C, k, set_base, ws.dropped, kept_idx, goal, s);

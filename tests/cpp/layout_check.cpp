@@ -216,6 +216,21 @@ int main() {
                     if (const char* what = check_row_plans(bound, C, I, ncu)) return fail(what, bound, C, I, ncu);
                     ++cases;
                 }
+    // tiles of the token merge: no other one is as few rounds of the chip with fewer rows
+    for (int ncu : ncus)
+        for (long dropped : {1L, 64L, 65L, 128L, 129L, 800L, 1728L, 4095L})
+            for (long kept : {1L, 64L, 65L, 129L, 256L, 1000L, 4095L})
+                for (long sets : {1L, 3L, 8L, 64L}) {
+                    auto rounds = [&](int q) {
+                        const long a = kMergeTiles[q][0], b = kMergeTiles[q][1];
+                        return ((dropped + a - 1) / a * ((kept + b - 1) / b) * sets + ncu - 1) / ncu;
+                    };
+                    const int best = merge_target_tile(dropped, kept, sets, ncu);
+                    if (best < 0 || best > 2) return fail("tile of the merge", dropped, kept, sets, ncu);
+                    for (int q = best + 1; q < 3; ++q)
+                        if (rounds(q) <= rounds(best)) return fail("a taller tile of the merge in as many rounds", dropped, kept, sets, ncu);
+                    ++cases;
+                }
     // dXn beside dW_gate and dW_up: all workgroups on the chip at once (a workgroup a tile where gradients are added to), every part of K with
     // slabs, no more of them than the workspace holds
     for (int ncu : ncus)
