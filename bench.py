@@ -103,8 +103,8 @@ def parse():
                     help="configuration 3 only: retain the leading 576 visual tokens of every sequence (the "
                          "global view of a high-resolution image) instead of seeded-random positions")
     ap.add_argument("--out-of-place", action="store_true",
-                    help="write to separate output / gradient tensors: skipped rows are then byte-copied "
-                         "by the passthrough kernel (in place they cost nothing)")
+                    help="write to separate output / gradient tensors: skipped rows are then byte-copied, beside the "
+                         "retained rows by gather_rmsnorm and gather_rows (in place they cost nothing)")
     ap.add_argument("--graph", action="store_true",
                     help="capture one step in a HIP graph and time replays (the per-kernel events "
                          "still come from eager launches)")
@@ -113,10 +113,15 @@ def parse():
     return ap.parse_args()
 
 
-def kernel_work(name, R, T, C, I, dw_bytes):
+def kernel_work(name, R, T, C, I, dw_bytes, out_of_place=False):
     """(kind, algorithmic amount per launch): flops for the MFMA kernels, bytes for
     the HBM-bound ones."""
     rc, ri = R * C, R * I
+    copied = 2 * (T - R) * C * 2 if out_of_place else 0
+    # few rows, or a narrow layer: the gate/up tiles are of all rows and leave no transposed copy of silu(gate) * up, which
+    # shares the launch of the normalised rows' copy then
+    tiles = -(-R // 256) * -(-I // 64)
+    h_copy = 2 * ri * 2 if R <= 256 or (tiles <= 256 and (R <= 6144 or C <= 4096)) else 0
     table = {
         "gemm_gate_up_swiglu": ("mfma", 4 * R * C * I),
         "gemm_down": ("mfma", 2 * R * C * I),
@@ -125,9 +130,10 @@ def kernel_work(name, R, T, C, I, dw_bytes):
         "gemm_dxn": ("mfma", 4 * R * C * I),
         "gemm_dxn+dw_gate_up": ("mfma", 8 * R * C * I),           # few rows: these three in one grid
         "compact": ("hbm", T + 4 * R),
-        "gather_rmsnorm": ("hbm", 2 * rc * 2 + 4 * R),
+        "gather_rmsnorm": ("hbm", 2 * rc * 2 + 4 * R + copied),
         "resid_scatter": ("hbm", 2 * rc * 2),
-        "gather_rows": ("hbm", 2.5 * rc * 2),                     # row gather + transposed copy
+        # the mean of the forward's transposed copies and the backward's row gather + transposed copy (+ skipped rows)
+        "gather_rows": ("hbm", 2.5 * rc * 2 + (h_copy + copied) / 2),
         "rmsnorm_bwd_scatter": ("hbm", rc * (2 + 2 + 4 + 2)),
         "passthrough_copy": ("hbm", 2 * (T - R) * C * 2),
     }
@@ -734,7 +740,7 @@ def main():
 
     kernels = {}
     for name, (ms, n) in prof.items():
-        kind, amount = kernel_work(name, R, T, C, I, 2)
+        kind, amount = kernel_work(name, R, T, C, I, 2, oop)
         avg = ms / n
         e = {"avg_ms": round(avg, 5), "launches_per_step": n / args.steps}
         if amount and avg > 0:
@@ -747,7 +753,7 @@ def main():
         e["ms_per_step"] = round(ms / args.steps, 5)
         kernels[name] = e
     dom = max(kernels, key=lambda k: kernels[k]["ms_per_step"])
-    kind, amount = kernel_work(dom, R, T, C, I, 2)
+    kind, amount = kernel_work(dom, R, T, C, I, 2, oop)
     dom_avg_s = kernels[dom]["avg_ms"] * 1e-3
     if kind == "mfma":
         achieved, peak, unit = amount / dom_avg_s / 1e12, PEAK_BF16_TFLOPS, "TFLOP/s"

@@ -258,8 +258,8 @@ int skipffn_select_retained(const void* features, const void* cls, const int32_t
  *   assign    i32 [n_tok] OUT     slot (0 .. k-1 within its set) each token ends up in
  *   avg_sim   f32 [n_tok] OUT     the average similarities
  *   workspace: at least skipffn_token_merge_workspace_bytes(n_tok, n_max, C), n_max = rows of
- *              the largest set
- * Sets are processed in groups of up to 64 per launch, in order on the stream. */
+ *              the largest set (it does not change the size)
+ * Sets are processed in groups of even size, up to 64 per launch, in order on the stream. */
 size_t skipffn_token_merge_workspace_bytes(int64_t n_tok, int64_t n_max, int64_t C);
 int skipffn_token_merge(const void* x, const int32_t* seg_host, int64_t S, int64_t C, int64_t k,
                         void* out, int32_t* kept_idx, int32_t* assign, float* avg_sim,

@@ -14,7 +14,7 @@
 // arguments are read only: a field assigned here moves the whole structure to vector registers (640 rows 20 % slower).
 //
 // C = 4096, I = 14336, us a layer's gate/up, down and reduction, plan of the bound / of the count:  bound 2944 rows, 640
-// retained 133 + 83 + 13 / 129 + 68 + 12;  bound 616, 184 retained 67 + 50 + 5 / 57 + 38 + 7;  bound 3080, 1600 retained 289
+// retained 133 + 83 + 13 / 133 + 70 + 12;  bound 616, 184 retained 67 + 50 + 5 / 57 + 38 + 7;  bound 3080, 1600 retained 289
 // + 207 / 291 + 152 + 16.
 #include <algorithm>
 

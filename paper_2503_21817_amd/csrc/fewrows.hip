@@ -4,8 +4,9 @@
 // One workgroup owns 16 output columns (16 rows of W_gate and the same 16 of W_up, or 16 rows of W_down)
 // and ALL of K, cut over its wavefronts; the wavefronts' sums meet in LDS, so the epilogue sees complete sums and
 // nothing goes through fp32 slabs in memory.  Weights go from HBM straight to the MFMA operand registers (a
-// K-contiguous fragment is 16 bytes per lane): no LDS stage and no barrier in the loop, only loads, a batch of
-// FR_UNROLL k-steps per wavefront in flight while others of the CU compute.
+// K-contiguous fragment is 16 bytes per lane): no LDS stage and no barrier in the loop, only loads.  The source asks for FR_UNROLL
+// k-steps in flight per wavefront; with the norm inside, the compiler keeps them (98 to 212 registers), without it gate/up's
+// loads sink to their uses (34 to 48 registers), so what the two forms differ by is in part this.
 //
 // The activations are the same for every workgroup and come from L2, which is what grows with the rows: they
 // lie chunk-major ([K / 8][rows][8]) where no caller reads them, so that a load is one contiguous piece (row-major,

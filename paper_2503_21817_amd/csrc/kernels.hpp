@@ -138,7 +138,8 @@ hipError_t launch_mfma_probe(int blocks, int iters, int random_operands, float* 
 struct RowNorm { const bf16_t* hidden; int64_t T; const int32_t* idx; const bf16_t* gain; float eps; };
 
 // ---- the forward GEMMs of a handful of rows (rows <= 64) -----------------------------------------------
-// H = silu(xn Wg^T) * (xn Wu^T); G and U optional.  norm != null: xn is not read (few_rows_norm).  chunk_major, chunk_major_h: xn, H are [K / 8][rows][8] instead of row-major
+// H = silu(xn Wg^T) * (xn Wu^T); G and U optional.  norm != null: xn is not read (norm_in_gate_up).
+// chunk_major, chunk_major_h: xn, H are [K / 8][rows][8] instead of row-major
 hipError_t launch_few_rows_gate_up(const bf16_t* xn, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_gate,
                                    const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major, bool chunk_major_h,
                                    const RowNorm* norm, hipStream_t s);

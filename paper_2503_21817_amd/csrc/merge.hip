@@ -9,9 +9,10 @@
 // arguments, so nothing is copied to the device.
 // Decisions that depend on floating point (which tokens are kept, where a token goes) are
 // taken on the float32 averages / similarities computed here, with ties to the lower index,
-// so they are unique for those values.  A token with a non-finite feature has NaN similarities:
-// its average ranks after every number, so exactly min(k, n) tokens are kept whatever the input;
-// a token whose similarities are all NaN goes to no slot (assign = -1) and gets a zero gradient.
+// so they are unique for those values.  A token with a non-finite feature has NaN similarities, to
+// every other, so all averages of its set are NaN (a set of one apart).  NaN ranks after every number and ties go to the lower index: the
+// set's first min(k, n) tokens are kept.  A token whose similarities are all NaN goes to no slot (assign = -1)
+// and gets a zero gradient.
 #include <algorithm>
 #include <type_traits>
 

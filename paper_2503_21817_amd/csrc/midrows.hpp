@@ -4,8 +4,9 @@
 // Bound by streaming the weights from HBM.  A tile is ALL rows (16 * MT of them) times up to 128 weight rows, so that every
 // weight byte goes to one CU only and the tiles are many (I / 64 or more for gate/up, see gate_up_cols; C / 128 with K split for down, whose
 // fp32 slabs a reducing kernel adds; gate/up splits K as well where I is so small that most CUs would have no tile).
-// What limits a CU is the bytes its address unit takes, weights and activations together: about 9 TB/s over the chip
-// here.  Hence both operands go to LDS by direct loads of whole 128-byte lines
+// What limits a CU is the bytes it loads, weights and activations together, and the ends of its K range: 56-column gate/up tiles take 620 MB
+// of both at 184 rows in 57 us (11 TB/s over the chip), down's parts of 28 slabs 294 MB in 37 (8 TB/s).  Hence both operands go to LDS by direct
+// loads of whole 128-byte lines
 // (weights straight to registers, 16 rows x 64 bytes a load: 65 instead of 57 us at 184 rows), and the rows are not
 // padded further than to 64.
 //

@@ -155,6 +155,7 @@ __global__ __launch_bounds__(SUM_THREADS) void summary_chunk_fwd_kernel(
 // The same with the rows of the chunk in registers, V <= 2 pieces of 8 columns a thread (C <= 4096): they are read once, all at the
 // same time, and up to 768 chunks run at once.  Sixteen products are summed over the lanes together, half of them given away at
 // every step.  C = 4096, held / read again from L2, us: 9216 tokens 18.0 / 26.5, 33600 tokens 66.8 / 96.0, 576 tokens 7.3 / 8.7.
+// Three workgroups a CU leave a wavefront 168 registers; past 2048 columns four more are spilled (20 bytes a lane of scratch).
 template <bool FEW_SETS, int V, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, 3) void summary_held_fwd_kernel(
     const bf16_t* __restrict__ hidden, int64_t T, int C, const int32_t* __restrict__ tok,

@@ -101,7 +101,7 @@ __device__ __forceinline__ TopkCut topk_cut(Key&& key, int nv, int k, TopkShared
         __syncthreads();
         const uint32_t from = lo + ((uint32_t)sh.part << shift);
         const int b = sh.before, in = sh.inside;
-        if (k == b + in) return TopkCut{from + (1u << shift), 0};       // at most hi + 2^shift: see below
+        if (k == b + in) return TopkCut{from + (1u << shift), 0};       // more keys follow up to hi: no wrap
         if (shift == 0) return TopkCut{from, k - b};
         k -= b;
         const uint32_t to = from + ((1u << shift) - 1);

@@ -90,10 +90,9 @@ def test_merge_random_tokens(lens, C, k):
 
 
 @pytest.mark.parametrize("lens,C,k", [((127, 128, 129, 1, 0, 255, 257), 136, 20), ((130,), 8, 129), ((385, 66), 1032, 40)],
-                         ids=["around-128", "one-slab", "mirrored-tiles-and-ragged-k"])
-def test_similarity_tiles_and_their_mirror_images(lens, C, k):
-    """Only the 128 x 128 tiles on and above the diagonal are computed: every token's average and target takes entries
-    of computed tiles and of mirrored ones, at set sizes around a tile's edge and K of one ragged slab or many."""
+                         ids=["around-128", "one-slab", "ragged-k"])
+def test_sets_around_a_tile_edge(lens, C, k):
+    """Averages and targets at set sizes around a tile's edge, sets of one token and of none, K of one ragged slab or many."""
     rng = np.random.default_rng(sum(lens) + C + 1)
     xb = O.f64_to_bf16_bits(rng.standard_normal((sum(lens), C)) + 0.5 * rng.standard_normal((1, C)))
     check(xb, [0] + np.cumsum(lens).tolist(), k)
