@@ -345,9 +345,11 @@ inline ForwardPlan plan_forward(int64_t rows, int64_t C, int64_t I, bool has_sav
 // I = 512, bound 12000, 2442 rows 40.1 / 35.7, 200 rows 30.3 / 30.5.
 constexpr int kRowPlans = 64;                            // 16384 rows; the bound's plan beyond
 constexpr uint16_t kRowPlanBalanced = 0x8000;
-struct RowPlans { int mid_splits; uint16_t beyond, down[kRowPlans]; };
+// Two plans a word, which the kernels read by a scalar load; half a word would be a vector load, and a wait for all loads before it.
+struct RowPlans { int mid_splits; uint32_t beyond, down[kRowPlans / 2]; };
 SKIPFFN_HD inline KPartition row_plan(const RowPlans& p, int tiles_m) {
-    const uint16_t v = tiles_m <= kRowPlans ? p.down[tiles_m - 1] : p.beyond;
+    const uint32_t word = tiles_m <= kRowPlans ? p.down[(tiles_m - 1) >> 1] >> ((tiles_m - 1) & 1) * 16 : p.beyond;
+    const int v = (int)(word & 0xffffu);
     return v & kRowPlanBalanced ? KPartition{1, v & ~kRowPlanBalanced} : KPartition{v, 0};
 }
 inline RowPlans plan_rows(int64_t bound, int64_t C, int64_t I, int ncu, int64_t* sum_rows = nullptr) {
@@ -372,8 +374,8 @@ inline RowPlans plan_rows(int64_t bound, int64_t C, int64_t I, int ncu, int64_t*
         if (k.sk_nbg > 0 || k.splits > 1) last = t;
         return (uint16_t)(k.sk_nbg > 0 ? kRowPlanBalanced | k.sk_nbg : k.splits);
     };
-    p.down[0] = 1;                                       // up to 256 rows: tiles of all rows
-    for (int t = 2; t <= kRowPlans; ++t) p.down[t - 1] = t <= tiles_m ? code(t) : 1;
+    for (int t = 1; t <= kRowPlans; ++t)                 // (t = 1: tiles of all rows)
+        p.down[(t - 1) >> 1] |= (uint32_t)(t > 1 && t <= tiles_m ? code(t) : 1) << ((t - 1) & 1) * 16;
     p.beyond = tiles_m > kRowPlans ? code(tiles_m) : 1;
     if (sum_rows != nullptr) *sum_rows = last > 1 ? std::min<int64_t>(bound, (int64_t)last * BM) : 0;
     return p;
