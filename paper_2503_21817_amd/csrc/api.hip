@@ -299,7 +299,8 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
     const RowNorm* norm = plan.norm_in_gate_up ? &rows : nullptr;
     e = norm != nullptr ? launch_passthrough(skipped, (int)Rb, r_dev, s)
                         : launch_gather_rmsnorm(static_cast<const bf16_t*>(hidden), idx, (int)Rb, r_dev, (int)C, eps,
-                                                static_cast<const bf16_t*>(rms_gain), xrows, xn, rstd, chunk_major_xn, skipped, s);
+                                                static_cast<const bf16_t*>(rms_gain), xrows, xn, rstd, chunk_major_xn, !plan.scale_in_gate_up, skipped, s);
+    const float* scale = plan.scale_in_gate_up ? rstd : nullptr;
     if (e != hipSuccess) return hip_fail(e);
     // K-contiguous copies for the dW GEMMs: of the normalised rows, and of silu(gate) * up unless the core's epilogue writes it; both
     // at once where the second has to wait for the gate/up GEMM
@@ -314,10 +315,10 @@ int skipffn_forward(int64_t T, int64_t C, int64_t I, float eps, const void* hidd
     const bf16_t *wg = static_cast<const bf16_t*>(w_gate), *wu = static_cast<const bf16_t*>(w_up);
     profile_mark_begin(KC_GEMM_GATE_UP, s);
     if (plan.gate_up == FWD_FEW) {
-        e = launch_few_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_xn, chunk_major_h, norm, s);
+        e = launch_few_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_xn, chunk_major_h, norm, scale, s);
     } else if (plan.gate_up == FWD_MID) {
         e = launch_mid_rows_gate_up(xn, (int)Rb, r_dev, (int)C, (int)I, wg, wu, H, G, U, chunk_major_h, plan.gate_up_splits,
-                                    plan.gate_up_cols, partial, norm, s);
+                                    plan.gate_up_cols, partial, norm, scale, s);
     } else {
         GemmArgs a{};
         a.M = (int)Rb; a.N = (int)I; a.K = (int)C; a.m_dev = r_dev;

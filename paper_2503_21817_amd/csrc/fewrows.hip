@@ -38,6 +38,7 @@ struct FewRowsArgs {
     bf16_t* H; uint32_t h_row, h_chunk; bf16_t* G; bf16_t* U;
     const int32_t* idx; const bf16_t* res; bf16_t* out; int no_residual;   // down: res, out [T][N]
     const bf16_t* gain; float eps;            // gate/up that normalises its rows itself: A = hidden [T][K], rows idx
+    const float* rstd;                        // gate/up, optional: A holds rows that are yet to be multiplied by this, 1 / rms of each
 };
 
 template <int MT, int WAVES, bool GATE_UP, int NORM>
@@ -57,6 +58,8 @@ __global__ __launch_bounds__(WAVES * 64) void few_rows_kernel(FewRowsArgs P) {
     const int em = wave * 16 + r16, en = n0 + 4 * kq;
     const bool mine = wave < MT && em < R && en < P.N;
     const int irow = !GATE_UP && mine ? P.idx[em] : 0;
+    float rstd = 1.0f;
+    if (GATE_UP && NORM == NORM_NONE && P.rstd != nullptr && mine) rstd = P.rstd[em];
 
     const __amdgpu_buffer_rsrc_t ra = make_rsrc(P.A, P.a_bytes), rb0 = make_rsrc(P.B0, P.b_bytes),
                                  rb1 = make_rsrc(GATE_UP ? P.B1 : P.B0, P.b_bytes);
@@ -161,7 +164,6 @@ __global__ __launch_bounds__(WAVES * 64) void few_rows_kernel(FewRowsArgs P) {
         for (int m = 0; m < MT; ++m) red_ss[wave][m][lane] = ss[m];
     }
     __syncthreads();
-    float rstd = 1.0f;
     if (NORM != NORM_NONE && wave < MT) {
         float sq = red_ss[0][wave][lane];
 #pragma unroll
@@ -178,10 +180,8 @@ __global__ __launch_bounds__(WAVES * 64) void few_rows_kernel(FewRowsArgs P) {
     }
     if (GATE_UP) {
         f32x4 g = v[0], u = v[NW - 1];
-        if (NORM != NORM_NONE) {
-            g *= rstd;
-            u *= rstd;
-        }
+        g *= rstd;
+        u *= rstd;
         float h[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) h[j] = g[j] * sigmoid_f(g[j]) * u[j];
@@ -219,8 +219,9 @@ static hipError_t launch_few_rows(const FewRowsArgs& a, hipStream_t s) {
 
 hipError_t launch_few_rows_gate_up(const bf16_t* xn, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_gate,
                                    const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major, bool chunk_major_h,
-                                   const RowNorm* norm, hipStream_t s) {
+                                   const RowNorm* norm, const float* rstd, hipStream_t s) {
     FewRowsArgs a{};
+    a.rstd = rstd;
     a.rows = rows; a.r_dev = r_dev; a.N = I; a.K = C;
     a.A = xn; a.a_bytes = (uint32_t)((int64_t)rows * C * 2);
     a.a_row = chunk_major ? 16u : (uint32_t)C * 2; a.a_chunk = chunk_major ? (uint32_t)rows * 16 : 16u;

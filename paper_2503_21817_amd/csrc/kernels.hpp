@@ -53,10 +53,10 @@ hipError_t launch_validate_idx(const int32_t* idx, int R, const int32_t* r_dev, 
 // Rows 0 .. T - 1 of row_chunks 16-byte pieces each; those NOT listed in idx are copied from src to dst (null: none).  A
 // job of its own (launch_passthrough), or beside another kernel that reads the same rows.
 struct SkippedRows { const void* src; void* dst; int64_t T, row_chunks; const int32_t* idx; };
-// x rows (optional copy), normalised rows and 1/rms for rows idx[0..R); chunk_major: xn is [C / 8][R][8]
+// x rows (optional copy), normalised rows (scaled = false: as they are, not multiplied) and 1/rms for rows idx[0..R); chunk_major: xn is [C / 8][R][8]
 hipError_t launch_gather_rmsnorm(const bf16_t* hidden, const int32_t* idx, int R,
                                  const int32_t* r_dev, int C, float eps, const bf16_t* gain,
-                                 bf16_t* xrows, bf16_t* xn, float* rstd, bool chunk_major, const SkippedRows& sk, hipStream_t s);
+                                 bf16_t* xrows, bf16_t* xn, float* rstd, bool chunk_major, bool scaled, const SkippedRows& sk, hipStream_t s);
 // How many fp32 partial slabs a reducing kernel adds per output element: `splits` for a plain
 // split-K GEMM (sk_nbg == 0), else the per-tile count of the balanced split (streamk_count)
 // with sk_nbg workgroups per n-tile group and sk_kt K slabs per tile.
@@ -139,10 +139,10 @@ struct RowNorm { const bf16_t* hidden; int64_t T; const int32_t* idx; const bf16
 
 // ---- the forward GEMMs of a handful of rows (rows <= 64) -----------------------------------------------
 // H = silu(xn Wg^T) * (xn Wu^T); G and U optional.  norm != null: xn is not read (norm_in_gate_up).
-// chunk_major, chunk_major_h: xn, H are [K / 8][rows][8] instead of row-major
+// rstd != null: xn holds rows whose products are multiplied by it (scale_in_gate_up).  chunk_major, chunk_major_h: xn, H are [K / 8][rows][8] instead of row-major
 hipError_t launch_few_rows_gate_up(const bf16_t* xn, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_gate,
                                    const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major, bool chunk_major_h,
-                                   const RowNorm* norm, hipStream_t s);
+                                   const RowNorm* norm, const float* rstd, hipStream_t s);
 // out[idx[r]] = bf16(res[idx[r]] + H[r] Wd^T)
 hipError_t launch_few_rows_down(const bf16_t* H, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_down,
                                 const int32_t* idx, const bf16_t* res, bf16_t* out, int no_residual, bool chunk_major,
@@ -150,10 +150,10 @@ hipError_t launch_few_rows_down(const bf16_t* H, int rows, const int32_t* r_dev,
 
 // ---- the forward GEMMs of up to 256 rows ------------------------------------------------------------------
 hipError_t mid_rows_init();      // raises the dynamic-LDS limit of every instantiation (once per process)
-// norm != null: xn is not read, up to kNormInMidRows rows.  cols: gate_up_cols.  chunk_major_h: H is [I / 8][rows][8] instead of row-major; splits > 1: K cut in fp32 partial[splits][rows][2][I]
+// norm != null: xn is not read, up to kNormInMidRows rows; rstd != null: as above, up to as many rows and splits 1.  cols: gate_up_cols.  chunk_major_h: H is [I / 8][rows][8] instead of row-major; splits > 1: K cut in fp32 partial[splits][rows][2][I]
 hipError_t launch_mid_rows_gate_up(const bf16_t* xn, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_gate,
                                    const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major_h, int splits,
-                                   int cols, float* partial, const RowNorm* norm, hipStream_t s);
+                                   int cols, float* partial, const RowNorm* norm, const float* rstd, hipStream_t s);
 // fp32 partial[splits][rows][C]
 hipError_t launch_mid_rows_down(const bf16_t* H, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_down,
                                 int splits, float* partial, hipStream_t s);

@@ -292,6 +292,9 @@ inline int gate_up_cols(int64_t rows, int64_t I, int ncu) {
 // by doing it themselves, and lose where they are narrow.  8 of 64 rows, before it / in the GEMM:  C = 4096: I = 14336 68.6 / 68.8, I = 8192
 // 44.0 / 47.3;  C = 5120, I = 8192 60.9 / 64.0;  C = 8192: I = 14336 134.5 / 135.5, I = 8192 81.0 / 86.7 (a launch of its own for the norm: 83);
 // 64 of 616: C = 4096, I = 14336 77.6 / 76.2.
+// Where the launch before the GEMM forms the norms of so few rows and there is no gain, it leaves the rows as they are, beside 1 / rms
+// (scale_in_gate_up): the sums are multiplied by it, so the rounding of the normalised rows is saved there too.  Error against 64 bits, rounded
+// rows / this:  C = 2048, I = 4096, 20 rows 3.5e-3 / 2.3e-3;  C = 8192, I = 8192, 8 of 64 rows 3.4e-3 / 2.4e-3;  time up to 0.3 us more.
 constexpr int64_t kNormInMidRows = 64;
 inline bool norm_in_gate_up(int64_t rows, int64_t C, int64_t I, bool has_gain, bool copies_skipped, bool registers, int ncu) {
     if (!registers) return rows <= kNormInMidRows && !has_gain && !copies_skipped;
@@ -303,6 +306,7 @@ enum FwdKernel { FWD_FEW, FWD_MID, FWD_CORE };           // fewrows.hip, midrows
 struct ForwardPlan {
     FwdKernel gate_up, down;
     bool norm_in_gate_up;                                // the rows are normalised by the gate/up GEMM, not before it
+    bool scale_in_gate_up;                               // their 1 / rms is formed before it and applied to its sums
     int gate_up_splits, gate_up_cols;                    // FWD_MID
     KPartition k_down;                                   // FWD_MID: plain split; FWD_CORE: as choose_k_partition; FWD_FEW: none
 };
@@ -310,12 +314,13 @@ struct ForwardPlan {
 inline int max_down_splits(int64_t rows) { return rows <= 256 ? kMaxSplitsNarrow : kMaxSplits; }
 inline ForwardPlan plan_forward(int64_t rows, int64_t C, int64_t I, bool has_saved, bool balanced, int ncu,
                                 bool has_gain = false, bool copies_skipped = false) {
-    ForwardPlan p{FWD_CORE, FWD_CORE, false, 1, 64, KPartition{1, 0}};
+    ForwardPlan p{FWD_CORE, FWD_CORE, false, false, 1, 64, KPartition{1, 0}};
     if (!balanced && mid_rows(rows, C, I, ncu)) {
         p.gate_up = few_rows_gate_up(rows, C, I, has_saved, has_gain) ? FWD_FEW : FWD_MID;
         if (p.gate_up == FWD_MID && rows <= 256) p.gate_up_splits = gate_up_splits(C, I, ncu);
         if (p.gate_up_splits == 1) p.gate_up_cols = gate_up_cols(rows, I, ncu);
         p.norm_in_gate_up = !has_saved && p.gate_up_splits == 1 && norm_in_gate_up(rows, C, I, has_gain, copies_skipped, p.gate_up == FWD_FEW, ncu);
+        p.scale_in_gate_up = !has_saved && !has_gain && rows <= kNormInMidRows && p.gate_up_splits == 1 && !p.norm_in_gate_up;
         p.down = few_rows_down(rows, C, I, has_saved, ncu) ? FWD_FEW : mid_rows_down(rows, C, ncu) ? FWD_MID : FWD_CORE;
     }
     const int ktiles = (int)((I + BK - 1) / BK);

@@ -121,9 +121,10 @@ MidRowsArgs mid_rows_down_args(const bf16_t* H, int rows, const int32_t* r_dev, 
 
 hipError_t launch_mid_rows_gate_up(const bf16_t* xn, int rows, const int32_t* r_dev, int C, int I, const bf16_t* w_gate,
                                    const bf16_t* w_up, bf16_t* H, bf16_t* G, bf16_t* U, bool chunk_major_h, int splits,
-                                   int cols, float* partial, const RowNorm* norm, hipStream_t s) {
+                                   int cols, float* partial, const RowNorm* norm, const float* rstd, hipStream_t s) {
     MidRowsArgs a = mid_rows_gate_up_args(xn, rows, r_dev, C, I, w_gate, w_up, H, G, U, chunk_major_h, cols);
-    a.splits = splits; a.partial = partial;
+    a.splits = splits; a.partial = partial; a.rstd = rstd;
+    if (rstd != nullptr && (rows > kNormInMidRows || splits > 1)) return hipErrorInvalidValue;
     if (norm != nullptr) {                    // one row tile; a part of K would not know a row's norm
         if (rows > kNormInMidRows || splits > 1 || norm->gain != nullptr) return hipErrorInvalidValue;
         a.A = norm->hidden; a.a_bytes = (uint32_t)(norm->T * C * 2);

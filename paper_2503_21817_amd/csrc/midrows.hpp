@@ -43,6 +43,7 @@ struct MidRowsArgs {
     float* partial;                           // down: [splits][rows][N]; gate/up with splits > 1: [splits][rows][2][N]
     // gate/up that normalises its rows itself: A = hidden [T][K], of which the rows idx are taken
     const int32_t* idx; float eps;
+    const float* rstd;                        // gate/up of up to 64 rows, optional: A holds rows yet to be multiplied by this
 };
 
 // chunk_major_h: H is [N / 8][rows][8], splits 1, whole rows
@@ -113,7 +114,8 @@ __device__ __forceinline__ void mid_rows_tile(const MidRowsArgs& P, const int bl
             const int n = n0 + wn * 16 + 4 * kq;
             if (n >= P.N || n >= n0 + cols) continue;
             f32x4 g = acc[m][0], u = acc[m][1];
-            if (NORM) {
+            if (MT == 4 && !NORM && P.rstd != nullptr) rstd = P.rstd[row];
+            if (MT == 4) {
                 g *= rstd;
                 u *= rstd;
             }

@@ -82,7 +82,8 @@ template <bool IN_REGS>
 __global__ __launch_bounds__(ROW_THREADS) void gather_rmsnorm_kernel(
     const bf16_t* __restrict__ hidden, const int32_t* __restrict__ idx, int Rbound,
     const int32_t* __restrict__ r_dev, int C, float eps, const bf16_t* __restrict__ gain,
-    bf16_t* __restrict__ xrows, bf16_t* __restrict__ xn, int64_t xn_row, int xn_chunk, float* __restrict__ rstd_out, SkippedRows sk) {
+    bf16_t* __restrict__ xrows, bf16_t* __restrict__ xn, int64_t xn_row, int xn_chunk, int scaled, float* __restrict__ rstd_out,
+    SkippedRows sk) {
     __shared__ float red[4];
     const int R = effective_rows(Rbound, r_dev);
     const int tid = threadIdx.x;
@@ -133,7 +134,7 @@ __global__ __launch_bounds__(ROW_THREADS) void gather_rmsnorm_kernel(
 #pragma unroll
             for (int j = 0; j < 8; ++j) f[j] = f[j] * rstd;
         }
-        dxn[(int64_t)c * xn_chunk] = pack8(f);
+        dxn[(int64_t)c * xn_chunk] = scaled ? pack8(f) : raw;
         if (dxr) dxr[c] = raw;
     };
     if (IN_REGS) {
@@ -149,7 +150,8 @@ __global__ __launch_bounds__(ROW_THREADS) void gather_rmsnorm_kernel(
 
 hipError_t launch_gather_rmsnorm(const bf16_t* hidden, const int32_t* idx, int R,
                                  const int32_t* r_dev, int C, float eps, const bf16_t* gain,
-                                 bf16_t* xrows, bf16_t* xn, float* rstd, bool chunk_major, const SkippedRows& sk, hipStream_t s) {
+                                 bf16_t* xrows, bf16_t* xn, float* rstd, bool chunk_major, bool scaled, const SkippedRows& sk,
+                                 hipStream_t s) {
     if (R <= 0) return hipSuccess;
     const int64_t xn_row = chunk_major ? 1 : C >> 3;
     const int xn_chunk = chunk_major ? R : 1;
@@ -157,10 +159,10 @@ hipError_t launch_gather_rmsnorm(const bf16_t* hidden, const int32_t* idx, int R
     profile_mark_begin(KC_GATHER_RMSNORM, s);
     if (C <= ROW_THREADS * 8 * RMS_MAXV)
         hipLaunchKernelGGL(gather_rmsnorm_kernel<true>, grid, block, 0, s, hidden, idx, R, r_dev, C,
-                           eps, gain, xrows, xn, xn_row, xn_chunk, rstd, sk);
+                           eps, gain, xrows, xn, xn_row, xn_chunk, scaled ? 1 : 0, rstd, sk);
     else
         hipLaunchKernelGGL(gather_rmsnorm_kernel<false>, grid, block, 0, s, hidden, idx, R, r_dev, C,
-                           eps, gain, xrows, xn, xn_row, xn_chunk, rstd, sk);
+                           eps, gain, xrows, xn, xn_row, xn_chunk, scaled ? 1 : 0, rstd, sk);
     profile_mark_end(KC_GATHER_RMSNORM, s);
     return hipGetLastError();
 }

@@ -754,6 +754,19 @@ def test_norm_inside_the_gate_up_gemm_in_place(R, C, I, r_host):
     test_norm_inside_the_gate_up_gemm(R, C, I, False, r_host, inplace=True)
 
 
+@pytest.mark.parametrize("R,C,I", [(1, 2064, 12296), (64, 4096, 6600), (33, 2056, 7176), (20, 3072, 3072), (48, 1032, 7176), (64, 2048, 2056)])
+def test_few_rows_are_not_rounded_after_their_norm(R, C, I):
+    """1 / rms is applied to the sums of gate/up, whichever launch forms it: of what is rounded to bf16, up to 1.65e-3 rms of
+    its size each (2^-8 / 2 over sqrt(3), by where in a binade it lies up to 1.46 times), H and the output remain: 2.3e-3.  Rounded rows
+    add themselves twice, to gate and to up: 3.3e-3 and more."""
+    w = W.small(C=C, I=I, visual=(R + 5,), text=(1,), keep=(R - 1,), seed=9200 + R + C, name=f"unrounded-{R}-{C}")
+    assert w.R == R
+    p = Problem(w)
+    fo = O.skipffn_forward(p.hidden, p.mask, p.wg, p.wu, p.wd, None, w.eps, no_residual=True)
+    got = bits_of(gpu_forward(p, saved=False, flags=B.FLAG_NO_RESIDUAL)[0])
+    assert rel_l2(O.bf16_bits_to_f64(got[fo["idx"]]), O.bf16_bits_to_f64(fo["out_bits"][fo["idx"]])) < 2.8e-3
+
+
 @pytest.mark.parametrize("R,C,I", [(65, 4096, 8), (100, 4104, 72), (129, 2056, 264), (200, 4096, 520), (256, 3080, 1032),
                                    (9, 12296, 2056)],
                          ids=["one-column-tile", "ragged-k", "cut-off-tiles", "rotated-starts", "256-rows", "chunk-major-h"])
