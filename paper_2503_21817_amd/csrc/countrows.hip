@@ -32,10 +32,12 @@ __device__ __forceinline__ void mid_rows_of_count(const MidRowsArgs& M, const in
     else mid_rows_tile<16, GATE_UP>(M, block);
 }
 
-// lists: workgroups that run lists of tiles; mid: workgroups of the tiles of all rows, which take up to mid_max rows
-__global__ __launch_bounds__(GEMM_THREADS) void gate_up_count_kernel(GemmArgs P, MidRowsArgs M, int lists, int mid, int mid_max) {
+// lists: workgroups that run lists of tiles; mid: workgroups of the tiles of all rows, which take up to MID_MAX rows (a constant: as an
+// argument, or by a comparison of these two, 1 to 2 % on every count, in scalar registers that spill)
+template <int MID_MAX>
+__global__ __launch_bounds__(GEMM_THREADS) void gate_up_count_kernel(GemmArgs P, MidRowsArgs M, int lists, int mid) {
     const int rows = uniform(effective_rows(P.M, P.m_dev)), block = (int)blockIdx.x;
-    if (rows <= mid_max) {
+    if (rows <= MID_MAX) {
         if (block < mid) mid_rows_of_count<true>(M, rows, block);
     } else if (block < lists) {
         stream_rows<EPI_SWIGLU>(P, stream_plan_of_count<EPI_SWIGLU>(P, 1, lists), 1, block, lists);
@@ -58,11 +60,13 @@ __global__ __launch_bounds__(GEMM_THREADS) void down_count_kernel(GemmArgs P, Mi
 }
 
 hipError_t count_rows_init() {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gate_up_count_kernel),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS_BYTES);
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&down_count_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               GEMM_LDS_BYTES);
+    const void* kernels[] = {reinterpret_cast<const void*>(&gate_up_count_kernel<256>), reinterpret_cast<const void*>(&gate_up_count_kernel<128>),
+                             reinterpret_cast<const void*>(&down_count_kernel)};
+    for (const void* k : kernels) {
+        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, GEMM_LDS_BYTES);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 static_assert(kSlabLds<64> <= GEMM_LDS_BYTES && kSlabLds<128> <= GEMM_LDS_BYTES && kSlabLds<192> <= GEMM_LDS_BYTES &&
               kSlabLds<256> <= GEMM_LDS_BYTES, "the rings of all paths fit");
@@ -78,9 +82,8 @@ hipError_t launch_gate_up_count(GemmArgs& a, hipStream_t s) {
     const MidRowsArgs m = mid_rows_gate_up_args(a.A0, a.M, a.m_dev, a.K, a.N, a.B0, a.B1, static_cast<bf16_t*>(a.out0), nullptr,
                                                 nullptr, false, gate_up_cols(256, a.N, a.ncu));
     const int lists = list_workgroups(a), mid = (a.N + m.cols - 1) / m.cols;
-    const int mid_max = mid <= a.ncu ? 256 : 128;
-    hipLaunchKernelGGL(gate_up_count_kernel, dim3((unsigned)std::max(lists, mid)), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a, m,
-                       lists, mid, mid_max);
+    const auto kernel = mid <= a.ncu ? &gate_up_count_kernel<256> : &gate_up_count_kernel<128>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)std::max(lists, mid)), dim3(GEMM_THREADS), GEMM_LDS_BYTES, s, a, m, lists, mid);
     return hipGetLastError();
 }
 

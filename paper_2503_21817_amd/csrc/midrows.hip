@@ -5,7 +5,7 @@ namespace skipffn {
 
 template <int MT, bool GATE_UP, bool NORM>
 __global__ __launch_bounds__(SLAB_THREADS) void mid_rows_kernel(MidRowsArgs P) {
-    mid_rows_tile<MT, GATE_UP, NORM>(P, (int)blockIdx.x);
+    mid_rows_tile<MT, GATE_UP, NORM, GATE_UP && !NORM && MT == 4>(P, (int)blockIdx.x);
 }
 
 // H = silu(sum_z gate) * sum_z up over the slabs of a split gate/up GEMM; one thread per 8 columns of a row, the

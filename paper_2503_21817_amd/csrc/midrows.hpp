@@ -53,7 +53,8 @@ MidRowsArgs mid_rows_down_args(const bf16_t* H, int rows, const int32_t* r_dev, 
                                float* partial);
 
 // workgroup `block` of the tiles' (MT fragments of 16 rows high), all 512 threads
-template <int MT, bool GATE_UP, bool NORM = false>
+// (SCALE: P.rstd may be given)
+template <int MT, bool GATE_UP, bool NORM = false, bool SCALE = false>
 __device__ __forceinline__ void mid_rows_tile(const MidRowsArgs& P, const int block) {
     constexpr int MI = MT / 2;                // row fragments of a wavefront
     constexpr int NLA = kSlabPiecesA<16 * MT>, NL = kSlabPieces<16 * MT>;
@@ -114,8 +115,8 @@ __device__ __forceinline__ void mid_rows_tile(const MidRowsArgs& P, const int bl
             const int n = n0 + wn * 16 + 4 * kq;
             if (n >= P.N || n >= n0 + cols) continue;
             f32x4 g = acc[m][0], u = acc[m][1];
-            if (MT == 4 && !NORM && P.rstd != nullptr) rstd = P.rstd[row];
-            if (MT == 4) {
+            if (SCALE && P.rstd != nullptr) rstd = P.rstd[row];
+            if (NORM || SCALE) {
                 g *= rstd;
                 u *= rstd;
             }
